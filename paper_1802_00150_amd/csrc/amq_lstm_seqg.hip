@@ -122,7 +122,7 @@ template <int KA, bool SHARED>
 __device__ __forceinline__ bool quantize_wg(const void* src_v, unsigned tag, unsigned* sync, unsigned limit, int n,
                                             int T, uint32_t* planes, float* coef, double (*sh)[16 * kMaxRed],
                                             int& phase) {
-  const int lane = lane_id(), wv = wave_id();
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
   const int wpr = 4 * ((n + 127) >> 7);
   const int nslots = wpr >> 1;
   const int nj = (nslots + kGWaves - 1) / kGWaves;
@@ -171,10 +171,7 @@ __device__ __forceinline__ bool quantize_wg(const void* src_v, unsigned tag, uns
   }
   float alpha[KA];
   unsigned long long mym[KA];
-  double q[KA];
-#pragma unroll
-  for (int i = 0; i < KA; ++i) { alpha[i] = 0.0f; mym[i] = 0ull; q[i] = 0.0; }
-  quantize_core<KA, kGNJ, kGWaves>(w, n, base, nj, true, T, true, true, alpha, mym, q, sh, phase);
+  quantize_core<KA, kGNJ, kGWaves>(w, n, base, nj, T, alpha, mym, sh, phase);
 #pragma unroll
   for (int i = 0; i < KA; ++i) {
     if (lane < nj && base + lane < nslots) reinterpret_cast<unsigned long long*>(planes + i * wpr)[base + lane] = mym[i];

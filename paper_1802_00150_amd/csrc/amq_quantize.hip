@@ -1,16 +1,6 @@
-// Alternating multi-bit quantization (Alg. 2) on gfx950: one wavefront (throughput regime,
-// many vectors) or one workgroup of NW = 4 wavefronts (latency regime, few vectors) per
-// vector, the vector held in registers, every stage of the algorithm in this one kernel.
-//
-// Element layout in a wave: "slot" j of a lane holds entry (slot_base + j) * 64 + lane, so a
-// wave-wide comparison yields, through the 64-bit ballot, exactly two packed code words of
-// the exchange format.  Lane j keeps the ballot of slot j; the Gram matrix of Eq. 5 is then a
-// per-lane popcount of xor-ed masks plus one integer reduction, and the final store of a plane
-// is one coalesced 8-byte-per-lane write.
-//
-// Precision: stored quantities are binary32; the reductions (sum |r|, B^T w) are accumulated
-// in binary64 and the k x k system is solved in binary64 with exact integer cofactors, then
-// rounded once.  The comparison "w >= midpoint" that decides a code is binary32.
+// Alternating multi-bit quantization (Alg. 2) on gfx950: one workgroup of NW wavefronts per vector, the vector
+// held in registers, every stage of the algorithm in this one kernel (amq_quantize_core.h), and the two staged
+// hooks (Eq. 5 alone, Alg. 1 alone).
 #include "amq_launch.h"
 #include "amq_quantize_body.h"
 
@@ -18,18 +8,105 @@ namespace amq {
 
 namespace {
 
-// Register budget: the 2-bit kernel of the throughput regime (16 slots per lane) needs 95 registers, one
-// bucket above what six waves per SIMD allow; asked for six, the compiler spills four registers and the
-// kernel gains 2-3 % (measured on 16384 x 4096: 145 against 148-150 us; eight waves: 176 us).
 template <int K, int NJ, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu((K == 2 && NJ == 16) ? 6 : 1)))
+__global__ __launch_bounds__(64 * NW)
 void quantize_kernel(QuantArgs a) {
   __shared__ double sh[2][16 * kMaxRed];
   asm volatile("" ::AMQ_ARG(a.seg[0].X), AMQ_ARG(a.seg[0].ld), AMQ_ARG(a.seg[0].n), AMQ_ARG(a.seg[0].count),
                AMQ_ARG(a.seg[0].planes), AMQ_ARG(a.seg[0].coef), AMQ_ARG(a.seg[1].X), AMQ_ARG(a.seg[1].ld),
                AMQ_ARG(a.seg[1].n), AMQ_ARG(a.seg[1].count), AMQ_ARG(a.seg[1].planes), AMQ_ARG(a.seg[1].coef),
-               AMQ_ARG(a.T), AMQ_ARG(a.mode), AMQ_ARG(a.gather.count));
+               AMQ_ARG(a.T), AMQ_ARG(a.gather.count));
   quantize_block<K, NJ, NW>(a, blockIdx.x, sh);
+}
+
+// Staged hooks on one vector per workgroup: Eq. 5 with the codes given (a.mode == kQuantLsOnly), or Alg. 1 with
+// the coefficients given.
+template <int K, int NJ, int NW>
+__global__ __launch_bounds__(64 * NW) void quantize_stage_kernel(QuantArgs a) {
+  __shared__ double sh[2][16 * kMaxRed];
+  int phase = 0;
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
+  const long long vec = blockIdx.x;
+  const int n = a.seg[0].n, count = a.seg[0].count;
+  const int wpr = 4 * ((n + 127) >> 7);
+  const int nslots = wpr >> 1;
+  const int nj = (nslots + NW - 1) / NW;
+  const int base = wv * nj;
+  float* coef = a.seg[0].coef + vec * K;
+  const bool holds = lane < nj && base + lane < nslots;
+  float w[NJ];
+  load_slots<NJ>(a.seg[0].X + vec * a.seg[0].ld, n, base, nj, w);
+  auto masks_of = [&](int i) {
+    return reinterpret_cast<unsigned long long*>(a.seg[0].planes + ((long long)i * count + vec) * wpr) + base + lane;
+  };
+  float alpha[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) alpha[i] = coef[i];
+  unsigned long long mym[K];
+  if (a.mode == kQuantLsOnly) {
+    constexpr int NP = K * (K - 1) / 2;
+    double red[K + NP];
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      mym[i] = holds ? *masks_of(i) : 0ull;
+      const int lo = (int)(mym[i] & 0xffffffffull), hi = (int)(mym[i] >> 32);
+      double q = 0.0;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if (j < nj) {
+          const unsigned long long mk = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane(hi, j) << 32) |
+                                        (unsigned)__builtin_amdgcn_readlane(lo, j);
+          q += ((mk >> lane) & 1ull) ? (double)w[j] : -(double)w[j];
+        }
+      }
+      red[i] = q;
+    }
+    int t = K;
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+      for (int j = i + 1; j < K; ++j) red[t++] = (double)__popcll(mym[i] ^ mym[j]);
+    block_totals<NW, K + NP>(red, sh, phase);
+    double qq[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) qq[i] = red[i];
+    ls_solve_f64<K>(n, red + K, qq, alpha);
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) coef[i] = alpha[i];
+    }
+  } else {
+    constexpr int H = 1 << (K - 1);
+#pragma unroll
+    for (int i = 0; i < K; ++i) mym[i] = 0ull;
+    CodeTable<K> ct;
+    if constexpr (K > 1) {
+      code_table_any_order<K>(alpha, ct);
+    } else {
+      // the upper code is +alpha or, for a negative coefficient, -alpha
+      ct.bm[0] = __ballot(alpha[0] < 0.0f) != 0ull ? 0u : 1u;
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      if (j < nj) {
+        const float xc = w[j] + 0.0f;
+        const unsigned b = __float_as_uint(xc);
+        const int u = (int)min(b, b + 0x7fffffffu);
+        int m = 0;
+        if constexpr (K > 1) {
+#pragma unroll
+          for (int t = 0; t < H - 1; ++t) m += (u >= ct.thr[t]) ? 1 : 0;
+        }
+        const unsigned long long in = lanes_inside(n, base + j);
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+          keep_in_lane(mym[i], __ballot((((ct.bm[i] >> m) & 1u) != 0u) != (xc < 0.0f)) & in, j);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+      if (holds) *masks_of(i) = mym[i];
+  }
 }
 
 template <int K, int NJ, int NW>
@@ -38,36 +115,52 @@ void launch_one(QuantArgs a, int total, hipStream_t s) {
   hipLaunchKernelGGL((quantize_kernel<K, NJ, NW>), dim3(total), dim3(64 * NW), 0, s, a);
 }
 
-// Waves per vector: one when there are enough vectors to fill the chip (throughput regime),
-// four when there are few (latency regime: a quarter of the per-entry work per wave, one wave
-// per SIMD so that the wave-uniform parts of the algorithm are not replicated on a SIMD); then
-// the smallest register bucket that holds the vector's share.  Vectors above 4096 entries
-// always take four waves.
+template <int K>
+hipError_t launch_stage(const QuantArgs& a, int nslots, hipStream_t s) {
+  const dim3 grid((unsigned)a.seg[0].count);
+  if (nslots <= 16) hipLaunchKernelGGL((quantize_stage_kernel<K, 4, 4>), grid, dim3(256), 0, s, a);
+  else if (nslots <= 64) hipLaunchKernelGGL((quantize_stage_kernel<K, 16, 4>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((quantize_stage_kernel<K, 16, 16>), grid, dim3(1024), 0, s, a);
+  return hipGetLastError();
+}
+
+// Waves per vector.  Many vectors (throughput): as few waves as hold the vector with at most 16 slots per lane --
+// what a wave does once per vector (reductions, solves, code tables) is then paid by few waves, and 16 slots keep
+// the registers at about 90.  Few vectors (the on-line case, latency): at most 4 slots per lane.  Then the
+// smallest register form that holds the share.
 template <int K>
 hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
   const int nvec = a.seg[0].count + a.seg[1].count;
   const int total = nvec + a.gather.count;  // one workgroup per vector, one per gathered row
   if (total == 0) return hipSuccess;
   const int nslots = nvec ? 2 * ((max_n + 127) / 128) : 1;
-  int nw = nvec >= 1024 ? 1 : 4;
-  // long rows in the throughput regime: four waves of 16 entries per lane keep about 100 registers
-  // and four to five waves per SIMD, against more than 250 registers for one wave of 64 entries per
-  // lane (measured on 16384 x 4096: 760 -> 513 us at k = 4; two waves of 32 entries per lane:
-  // 206 against 175 us at k = 2, 334 against 297 us at k = 3)
-  if (nvec >= 1024 && nslots >= 32) nw = 4;
-  if (nw > nslots) nw = 1;
-  if (nw == 1 && nslots > 64) nw = 4;
   if (nslots > 256) return hipErrorInvalidValue;
+  if (a.mode != kQuantFull) return launch_stage<K>(a, nslots, s);
+  const int most = nvec >= 1024 ? 16 : 4;
+  int nw = 1;
+  while (nw < 16 && (nslots + nw - 1) / nw > most) nw *= 2;
+  if (nvec < 1024 && nw < 4 && nslots >= 4) nw = 4;
   const int nj = (nslots + nw - 1) / nw;
   if (nw == 1) {
-    if (nj <= 4) launch_one<K, 4, 1>(a, total, s);
-    else if (nj <= 16) launch_one<K, 16, 1>(a, total, s);
-    else launch_one<K, 64, 1>(a, total, s);
-  } else {
-    if (nj <= 1) launch_one<K, 1, 4>(a, total, s);
+    if (nj <= 2) launch_one<K, 2, 1>(a, total, s);
+    else if (nj <= 4) launch_one<K, 4, 1>(a, total, s);
+    else if (nj <= 8) launch_one<K, 8, 1>(a, total, s);
+    else if (nj <= 12) launch_one<K, 12, 1>(a, total, s);
+    else launch_one<K, 16, 1>(a, total, s);
+  } else if (nw == 2) {
+    if (nj <= 12) launch_one<K, 12, 2>(a, total, s);
+    else launch_one<K, 16, 2>(a, total, s);
+  } else if (nw == 4) {
+    if (nj <= 2) launch_one<K, 2, 4>(a, total, s);
     else if (nj <= 4) launch_one<K, 4, 4>(a, total, s);
-    else if (nj <= 16) launch_one<K, 16, 4>(a, total, s);
-    else launch_one<K, 64, 4>(a, total, s);
+    else if (nj <= 12) launch_one<K, 12, 4>(a, total, s);
+    else launch_one<K, 16, 4>(a, total, s);
+  } else if (nw == 8) {
+    if (nj <= 4) launch_one<K, 4, 8>(a, total, s);
+    else launch_one<K, 16, 8>(a, total, s);
+  } else {
+    if (nj <= 4) launch_one<K, 4, 16>(a, total, s);
+    else launch_one<K, 16, 16>(a, total, s);
   }
   return hipGetLastError();
 }

@@ -24,12 +24,31 @@ __device__ __forceinline__ void gather_row(const GatherSeg& t, int g, int nthrea
   if (threadIdx.x < K) t.coef[(long long)g * K + threadIdx.x] = ok ? t.table_coef[row * K + threadIdx.x] : 0.0f;
 }
 
+// Entries (base + j) * 64 + lane of a vector of n entries, 0.0 beyond its end or beyond slot nj.  Straight-line
+// loads (the index is clamped), so that they all go out before the first is waited for.
+template <int NJ>
+__device__ __forceinline__ void load_slots(const float* x, int n, int base, int nj, float (&w)[NJ]) {
+  const int lane = lane_id();
+  if (nj == NJ && (base + NJ) * 64 <= n) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) w[j] = x[(base + j) * 64 + lane];
+  } else {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int e = (base + j) * 64 + lane;
+      w[j] = x[e < n ? e : n - 1];
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) w[j] = (j < nj && (base + j) * 64 + lane < n) ? w[j] : 0.0f;
+  }
+}
+
 // vec: index of this workgroup's vector over both segments (then over the gathered rows).  sh: two
 // buffers of 16 * kMaxRed doubles of LDS.  Every wave of the workgroup (NW of them) must call this.
 template <int K, int NJ, int NW>
 __device__ __forceinline__ void quantize_block(const QuantArgs& a, int vec, double (*sh)[16 * kMaxRed]) {
   int phase = 0;
-  const int lane = lane_id(), wv = wave_id();
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
   AMQ_PHASE(AMQ_PHASE_OF(a), 0);
   if (vec >= a.seg[0].count + a.seg[1].count) {
     // workgroups past the vectors to quantize copy table rows by index
@@ -52,58 +71,18 @@ __device__ __forceinline__ void quantize_block(const QuantArgs& a, int vec, doub
   const float* x = X + (long long)vec * ld;
 
   float w[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int e = (base + j) * 64 + lane;
-    w[j] = (j < nj && e < n) ? x[e] : 0.0f;
-  }
+  load_slots<NJ>(x, n, base, nj, w);
 
   float alpha[K];
   unsigned long long mym[K];
-  double q[K];
-#pragma unroll
-  for (int i = 0; i < K; ++i) { alpha[i] = 0.0f; mym[i] = 0ull; q[i] = 0.0; }
-
-  if (a.mode == kQuantLsOnly) {
-    // codes given: read the masks, rebuild B^T w from them
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      if (lane < nj && base + lane < nslots)
-        mym[i] = reinterpret_cast<const unsigned long long*>(planes + ((long long)i * count + vec) * wpr)[base + lane];
-      alpha[i] = coef[(long long)vec * K + i];
-    }
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      double qi = 0.0;
-      const int lo = (int)(mym[i] & 0xffffffffull), hi = (int)(mym[i] >> 32);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        if (j < nj) {
-          const unsigned long long mk = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane(hi, j) << 32) |
-                                        (unsigned)__builtin_amdgcn_readlane(lo, j);
-          const bool bit = (mk >> lane) & 1ull;
-          qi += bit ? (double)w[j] : -(double)w[j];
-        }
-      }
-      q[i] = qi;
-    }
-  } else if (a.mode == kQuantBstOnly) {
-#pragma unroll
-    for (int i = 0; i < K; ++i) alpha[i] = coef[(long long)vec * K + i];
-  }
-
   AMQ_PHASE(AMQ_PHASE_OF(a), 1);
-  quantize_core<K, NJ, NW>(w, n, base, nj, a.mode == kQuantFull, a.mode == kQuantFull ? a.T : 1,
-                           a.mode != kQuantBstOnly, a.mode != kQuantLsOnly, alpha, mym, q, sh, phase,
-                           AMQ_PHASE_OF(a));
+  quantize_core<K, NJ, NW>(w, n, base, nj, a.T, alpha, mym, sh, phase, AMQ_PHASE_OF(a));
 
-  if (a.mode != kQuantLsOnly) {
 #pragma unroll
-    for (int i = 0; i < K; ++i)
-      if (lane < nj && base + lane < nslots)
-        reinterpret_cast<unsigned long long*>(planes + ((long long)i * count + vec) * wpr)[base + lane] = mym[i];
-  }
-  if (a.mode != kQuantBstOnly && threadIdx.x == 0) {
+  for (int i = 0; i < K; ++i)
+    if (lane < nj && base + lane < nslots)
+      reinterpret_cast<unsigned long long*>(planes + ((long long)i * count + vec) * wpr)[base + lane] = mym[i];
+  if (threadIdx.x == 0) {
 #pragma unroll
     for (int i = 0; i < K; ++i) coef[(long long)vec * K + i] = alpha[i];
   }

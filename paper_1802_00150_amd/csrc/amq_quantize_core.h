@@ -1,15 +1,13 @@
-// Device-side core of the alternating multi-bit quantizer (Alg. 2), shared by the stand-alone
-// quantizer kernels and the persistent recurrent kernel.  gfx950, 64-wide wavefronts.
+// Device-side core of the alternating multi-bit quantizer (Alg. 2), shared by the stand-alone quantizer
+// kernels, the front kernel of the split recurrent step and the persistent recurrent kernel.  gfx950,
+// 64-wide wavefronts.
 //
-// Element layout in a wave: "slot" j of a lane holds entry (slot_base + j) * 64 + lane, so a
-// wave-wide comparison yields, through the 64-bit ballot, exactly two packed code words of
-// the exchange format.  Lane j keeps the ballot of slot j; the Gram matrix of Eq. 5 is then a
-// per-lane popcount of xor-ed masks plus one reduction, and the final store of a plane is one
-// coalesced 8-byte-per-lane write.
+// Element layout in a wave: "slot" j of a lane holds entry (slot_base + j) * 64 + lane, so a wave-wide
+// comparison is, as a 64-bit mask, exactly two packed code words of the exchange format.
 //
-// Precision: stored quantities are binary32; the reductions (sum |r|, B^T w) are accumulated
-// in binary64 and the k x k system is solved in binary64 with exact integer cofactors, then
-// rounded once.  The comparison "w >= midpoint" that decides a code is binary32.
+// Precision: stored quantities are binary32; the reductions (sum |r|, B^T w) are accumulated in binary64
+// and the k x k system is solved in binary64 with exact integer cofactors, then rounded once.  The
+// comparison that decides a code is binary32.
 #pragma once
 #include <type_traits>
 
@@ -107,13 +105,13 @@ __device__ __forceinline__ double recip_f64(double d) {
   return r;
 }
 
-// Eq. 5 on the vector unit in binary64 for K <= 3, from the disagreement counts d[t] of the plane
-// pairs (order (0,1), (0,2), (1,2)): G_ij = n - 2 d_ij, cofactors and determinant are integers below
-// 2^45 for n <= 16384 and therefore exact in binary64 (same values as the integer cofactors of
-// ls_solve); alpha_i = (sum_j cof_ji q_j) / det.  A singular G leaves alpha unchanged.
+// Eq. 5 on the vector unit in binary64, from the disagreement counts d[t] of the plane pairs (order (0,1),
+// (0,2), .., (1,2), ..): G_ij = n - 2 d_ij, alpha_i = (sum_j cof_ji q_j) / det with exact cofactors and an
+// exact determinant for n <= 16384: the cofactors are integers of at most 45 bits, and at K = 4, where the
+// determinant may have 56, it is formed from terms n * cof that are multiples of 16 (every 3 x 3 minor of a
+// +-1 matrix is a multiple of 4), hence exact too.  A singular G leaves alpha unchanged.
 template <int K>
 __device__ __forceinline__ void ls_solve_f64(int n, const double* d, const double (&q)[K], float (&alpha)[K]) {
-  static_assert(K >= 1 && K <= 3, "binary64 cofactors are exact up to K = 3");
   const double dn = (double)n;
   if constexpr (K == 1) {
     alpha[0] = (float)(q[0] / dn);
@@ -124,7 +122,7 @@ __device__ __forceinline__ void ls_solve_f64(int n, const double* d, const doubl
     const double inv = recip_f64(det);
     alpha[0] = (float)((dn * q[0] + (-a) * q[1]) * inv);
     alpha[1] = (float)(((-a) * q[0] + dn * q[1]) * inv);
-  } else {
+  } else if constexpr (K == 3) {
     const double a = dn - 2.0 * d[0], b = dn - 2.0 * d[1], c = dn - 2.0 * d[2];
     const double nn = dn * dn;
     const double c00 = nn - c * c, c01 = c * b - a * dn, c02 = a * c - dn * b;
@@ -135,6 +133,27 @@ __device__ __forceinline__ void ls_solve_f64(int n, const double* d, const doubl
     alpha[0] = (float)((c00 * q[0] + c01 * q[1] + c02 * q[2]) * inv);
     alpha[1] = (float)((c01 * q[0] + c11 * q[1] + c12 * q[2]) * inv);
     alpha[2] = (float)((c02 * q[0] + c12 * q[1] + c22 * q[2]) * inv);
+  } else {
+    static_assert(K == 4, "at most 4 planes");
+    const double a = dn - 2.0 * d[0], b = dn - 2.0 * d[1], c = dn - 2.0 * d[2];   // G01 G02 G03
+    const double e = dn - 2.0 * d[3], f = dn - 2.0 * d[4], g = dn - 2.0 * d[5];   // G12 G13 G23
+    // 2 x 2 minors of rows 0, 1 (s) and of rows 2, 3 (t), columns (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
+    const double s0 = dn * dn - a * a, s1 = dn * e - b * a, s2 = dn * f - c * a;
+    const double s3 = a * e - b * dn, s4 = a * f - c * dn, s5 = b * f - c * e;
+    const double t1 = b * g - dn * c, t2 = b * dn - g * c, t3 = e * g - dn * f;
+    const double t4 = e * dn - g * f, t5 = dn * dn - g * g;
+    const double c00 = dn * t5 - e * t4 + f * t3, c01 = b * t4 - a * t5 - c * t3;
+    const double c02 = f * s5 - g * s4 + dn * s3, c03 = dn * s4 - e * s5 - g * s3;
+    const double c11 = dn * t5 - b * t2 + c * t1, c12 = g * s2 - c * s5 - dn * s1;
+    const double c13 = b * s5 - dn * s2 + g * s1, c22 = c * s4 - f * s2 + dn * s0;
+    const double c23 = e * s2 - b * s4 - g * s0, c33 = b * s3 - e * s1 + dn * s0;
+    const double det = (dn * c00 + a * c01) + (b * c02 + c * c03);
+    if (det == 0.0) return;
+    const double inv = recip_f64(det);
+    alpha[0] = (float)((c00 * q[0] + c01 * q[1] + c02 * q[2] + c03 * q[3]) * inv);
+    alpha[1] = (float)((c01 * q[0] + c11 * q[1] + c12 * q[2] + c13 * q[3]) * inv);
+    alpha[2] = (float)((c02 * q[0] + c12 * q[1] + c22 * q[2] + c23 * q[3]) * inv);
+    alpha[3] = (float)((c03 * q[0] + c13 * q[1] + c23 * q[2] + c33 * q[3]) * inv);
   }
 }
 
@@ -146,11 +165,6 @@ extern "C" __device__ int amq_writelane_i32(int value, int lane, int old) __asm(
 // selects on it; no vector instruction).
 extern "C" __device__ bool amq_inverse_ballot_i64(unsigned long long mask) __asm("llvm.amdgcn.inverse.ballot.i64");
 __device__ __forceinline__ bool lane_bit(unsigned long long mask) { return amq_inverse_ballot_i64(mask); }
-
-// Up to this many planes the code assignment of the throughput path works on comparison masks (scalar
-// unit); beyond, the 2^K - 1 masks and the logic on them cost more than counting the comparisons per lane
-// (measured at K = 3 on 16384 x 4096: 320 us with mask logic, 264 us with counted comparisons).
-constexpr int kMaskLogicMaxK = 2;
 
 // Lane j keeps the wave-uniform 64-bit value `mk` (the ballot of slot j): one lane write per half, which
 // takes the value straight from the scalar registers the comparison wrote.
@@ -165,36 +179,36 @@ __device__ __forceinline__ float readlane_f(float v, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
-template <int CTRL, int ROW_MASK>
+template <int CTRL>
 __device__ __forceinline__ double dpp_d(double v) {
-  int lo = __double2loint(v), hi = __double2hiint(v);
-  if constexpr (ROW_MASK == 0xf) {
-    // every lane is written from a valid lane: no previous value to keep, no register to clear
-    lo = __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xf, 0xf, true);
-    hi = __builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, true);
-  } else {
-    lo = __builtin_amdgcn_update_dpp(0, lo, CTRL, ROW_MASK, 0xf, false);
-    hi = __builtin_amdgcn_update_dpp(0, hi, CTRL, ROW_MASK, 0xf, false);
-  }
+  // (lanes without a source read 0: no previous value to keep, no register to clear)
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
   return __hiloint2double(hi, lo);
 }
 
-// Totals of NV doubles over the 64 lanes through DPP (no LDS traffic); the results are
-// wave-uniform (read from lane 63).  The NV chains are independent and interleave.
+// Sums of NV doubles over the 64 lanes through DPP (no LDS traffic), valid in lane 63.  The NV chains are
+// independent and interleave.
+template <int NV>
+__device__ __forceinline__ void wave_sums_lane63(double (&v)[NV]) {
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] += dpp_d<0xB1>(v[i]);   // quad_perm [1,0,3,2]
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] += dpp_d<0x4E>(v[i]);   // quad_perm [2,3,0,1]
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] += dpp_d<0x141>(v[i]);  // row_half_mirror
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] += dpp_d<0x140>(v[i]);  // row_mirror: every lane holds its row's sum
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] += dpp_d<0x142>(v[i]);  // row_bcast15: rows 1 and 3 now hold two rows (0 and 2 are not used again)
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] += dpp_d<0x143>(v[i]);  // row_bcast31: row 3 holds all four
+}
+
+// The same, wave-uniform (read from lane 63).
 template <int NV>
 __device__ __forceinline__ void wave_totals(double (&v)[NV]) {
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] += dpp_d<0xB1, 0xf>(v[i]);   // quad_perm [1,0,3,2]
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] += dpp_d<0x4E, 0xf>(v[i]);   // quad_perm [2,3,0,1]
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] += dpp_d<0x141, 0xf>(v[i]);  // row_half_mirror
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] += dpp_d<0x140, 0xf>(v[i]);  // row_mirror: every lane holds its row's sum
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] += dpp_d<0x142, 0xa>(v[i]);  // row_bcast15 into rows 1 and 3
-#pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] += dpp_d<0x143, 0xc>(v[i]);  // row_bcast31 into rows 2 and 3
+  wave_sums_lane63<NV>(v);
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
     const int lo = __builtin_amdgcn_readlane(__double2loint(v[i]), 63);
@@ -227,473 +241,488 @@ __device__ __forceinline__ void block_totals(double (&v)[NV], double (*sh)[16 * 
   }
 }
 
-// Totals over the workgroup of NQ per-lane doubles q and of NC values c that are already totals of
-// their wave (wave-uniform); results in q and c.  One LDS barrier.
-template <int NW, int NQ, int NC>
-__device__ __forceinline__ void block_totals_mixed(double (&q)[NQ], double (&c)[NC > 0 ? NC : 1],
-                                                   double (*sh)[16 * kMaxRed], int& phase) {
-  wave_totals<NQ>(q);
-  if constexpr (NW > 1) {
-    const int wv = wave_id();
-    if (lane_id() == 0) {
+
+// ---------------------------------------------------------------------------------------------------------
+// Alg. 2 on magnitudes.
+//
+// The code table is symmetric (negating every plane negates the value, exactly, in binary32), so the whole
+// algorithm runs on |w|: with s the sign of an entry and H = 2^(K-1), the upper half of the sorted table holds
+// H values with H - 1 positive midpoints t_1 <= .. <= t_{H-1}, and plane i of an entry's code is
+//     plane_i = f_i(m) ^ s,     m = number of midpoints that |w| reaches,
+// f_i(m) being plane i of the code at position H + m (the middle midpoint is exactly 0).  The comparison
+// "w >= midpoint" sends ties up, which on magnitudes is >= for w >= 0 and > for w < 0; both are one integer
+// comparison u >= bits(t) with u = bits(|w|) for w >= 0 and bits(|w|) - 1 for w < 0 (-0.0 counts as +0.0).
+//   - The 2^K - 1 comparisons of a pass become 2^(K-1) - 1: one at 2 bits, three at 3.
+//   - Everything Eq. 5 needs from a pass are, per midpoint, C_t = sum of |w| over u >= t_t and N_t = the number
+//     of such entries: B_i^T w = +-sum |w| +- 2 C_t .. with signs that depend only on where f_i changes, and the
+//     disagreement counts of the plane pairs likewise.  No code is formed before the last pass.
+//   - C_t is accumulated by ONE binary64 addition under the comparison's own mask as the lane mask (a masked
+//     addition costs 5.3 cycles of a SIMD, measured; selecting +-w first costs 13).
+//   - alpha_K of the greedy start is needed only where the first Gram matrix is singular, so its sum travels with
+//     the first Eq.-5 reduction instead of having a reduction of its own.
+// Bound: vector-instruction issue at k >= 3 and HBM at k <= 2 for many vectors, the chain of reductions for a few.
+// Measured (us) against the form that compared w with all midpoints and selected +-w per plane, k = 2 / 3 / 4:
+// 16384 x 4096 135 / 239 / 443 -> 76 / 125 / 285, 4096 x 2048 33 / 54 / 100 -> 10.5 / 19 / 39, 128 vectors of 1024
+// (launches back to back) 4.4 / 5.9 / 10.1 -> 3.4 / 4.4 / 6.7.
+
+// A value the compiler must take as new: keeps it from holding the comparison masks of one pass in scalar registers
+// for a later pass (16 slots of them spill), where forming them again is one comparison.
+__device__ __forceinline__ int opaque_s(int v) { asm volatile("" : "+s"(v)); return v; }
+__device__ __forceinline__ float opaque_v(float v) { asm volatile("" : "+v"(v)); return v; }
+
+// count += number of mask bits, slot by slot: left to itself the compiler sums the counts of all slots at the end of
+// a pass and holds (spills) their masks until then.
+template <int NJ>
+__device__ __forceinline__ void add_count(int& count, unsigned long long m) {
+  count += __popcll(m);
+  if constexpr (NJ > 4) count = opaque_s(count);
+}
+
+// The mask bits of the lanes of slot (base + j) that lie inside a vector of n entries.
+__device__ __forceinline__ unsigned long long lanes_inside(int n, int slot) {
+  const int left = n - slot * 64;
+  return left >= 64 ? ~0ull : left <= 0 ? 0ull : (1ull << left) - 1ull;
+}
+
+// c[t] += |x| in the lanes of mask m[t].  The lane mask is set from the mask for the addition and restored to all
+// lanes (every wave runs whole and undiverged here).
+template <int NT>
+__device__ __forceinline__ void masked_add(double (&c)[NT], double x, const unsigned long long (&m)[NT]) {
+  static_assert(NT == 1 || NT == 3 || NT == 7, "midpoints of the upper half of the code table");
+  if constexpr (NT == 1) {
+    asm volatile("s_mov_b64 exec, %[m0]\n\tv_add_f64 %[c0], %[c0], |%[x]|\n\ts_mov_b64 exec, -1"
+                 : [c0] "+v"(c[0]) : [x] "v"(x), [m0] "s"(m[0]));
+  } else if constexpr (NT == 3) {
+    asm volatile("s_mov_b64 exec, %[m0]\n\tv_add_f64 %[c0], %[c0], |%[x]|\n\t"
+                 "s_mov_b64 exec, %[m1]\n\tv_add_f64 %[c1], %[c1], |%[x]|\n\t"
+                 "s_mov_b64 exec, %[m2]\n\tv_add_f64 %[c2], %[c2], |%[x]|\n\ts_mov_b64 exec, -1"
+                 : [c0] "+v"(c[0]), [c1] "+v"(c[1]), [c2] "+v"(c[2])
+                 : [x] "v"(x), [m0] "s"(m[0]), [m1] "s"(m[1]), [m2] "s"(m[2]));
+  } else {
+    asm volatile("s_mov_b64 exec, %[m0]\n\tv_add_f64 %[c0], %[c0], |%[x]|\n\t"
+                 "s_mov_b64 exec, %[m1]\n\tv_add_f64 %[c1], %[c1], |%[x]|\n\t"
+                 "s_mov_b64 exec, %[m2]\n\tv_add_f64 %[c2], %[c2], |%[x]|\n\t"
+                 "s_mov_b64 exec, %[m3]\n\tv_add_f64 %[c3], %[c3], |%[x]|\n\t"
+                 "s_mov_b64 exec, %[m4]\n\tv_add_f64 %[c4], %[c4], |%[x]|\n\t"
+                 "s_mov_b64 exec, %[m5]\n\tv_add_f64 %[c5], %[c5], |%[x]|\n\t"
+                 "s_mov_b64 exec, %[m6]\n\tv_add_f64 %[c6], %[c6], |%[x]|\n\ts_mov_b64 exec, -1"
+                 : [c0] "+v"(c[0]), [c1] "+v"(c[1]), [c2] "+v"(c[2]), [c3] "+v"(c[3]), [c4] "+v"(c[4]), [c5] "+v"(c[5]),
+                   [c6] "+v"(c[6])
+                 : [x] "v"(x), [m0] "s"(m[0]), [m1] "s"(m[1]), [m2] "s"(m[2]), [m3] "s"(m[3]), [m4] "s"(m[4]),
+                   [m5] "s"(m[5]), [m6] "s"(m[6]));
+  }
+}
+
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(v & 0xffffffffull), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, 0xf, 0xf, true);
+  return ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
+}
+// Sum over aligned groups of N = 8 or 16 lanes, in every lane.
+template <int N>
+__device__ __forceinline__ double lane_group_sum(double v) {
+  v += dpp_d<0xB1>(v);
+  v += dpp_d<0x4E>(v);
+  v += dpp_d<0x141>(v);
+  if constexpr (N == 16) v += dpp_d<0x140>(v);
+  return v;
+}
+template <int N>
+__device__ __forceinline__ unsigned long long lane_group_sum(unsigned long long v) {
+  v += dpp_u64<0xB1>(v);
+  v += dpp_u64<0x4E>(v);
+  v += dpp_u64<0x141>(v);
+  if constexpr (N == 16) v += dpp_u64<0x140>(v);
+  return v;
+}
+
+// Totals over a workgroup of NW waves of NV per-lane doubles v and of NC wave-uniform counts c (each at most
+// 16384 in total); the totals come back in every lane.  One LDS barrier; two buffers used alternately.  The
+// counts travel four to a 64-bit word.
+template <int NW, int NV, int NC>
+__device__ __forceinline__ void exchange_totals(double (&v)[NV], int (&c)[NC > 0 ? NC : 1], double (*sh)[16 * kMaxRed],
+                                                int& phase) {
+  if constexpr (NW == 1) {
+    wave_totals<NV>(v);
+  } else {
+    constexpr int NCW = (NC + 3) / 4;
+    constexpr int NE = NV + NCW;
+    static_assert(NE <= kMaxRed, "LDS buffer");
+    wave_sums_lane63<NV>(v);
+    unsigned long long pk[NCW > 0 ? NCW : 1];
 #pragma unroll
-      for (int i = 0; i < NQ; ++i) sh[phase][wv * (NQ + NC) + i] = q[i];
+    for (int i = 0; i < NCW; ++i) {
+      pk[i] = 0ull;
 #pragma unroll
-      for (int i = 0; i < NC; ++i) sh[phase][wv * (NQ + NC) + NQ + i] = c[i];
+      for (int k = 0; k < 4; ++k)
+        if (4 * i + k < NC) pk[i] |= (unsigned long long)(unsigned)c[4 * i + k] << (16 * k);
+    }
+    double* buf = sh[phase];
+    if (lane_id() == 63) {
+      const int wv = wave_id();
+#pragma unroll
+      for (int i = 0; i < NV; ++i) buf[wv * NE + i] = v[i];
+#pragma unroll
+      for (int i = 0; i < NCW; ++i) buf[wv * NE + NV + i] = __longlong_as_double((long long)pk[i]);
     }
     lds_barrier();
+    if constexpr (NW <= 4) {
 #pragma unroll
-    for (int i = 0; i < NQ + NC; ++i) {
-      double t = sh[phase][i];
+      for (int i = 0; i < NV; ++i) {
+        double t = buf[i];
 #pragma unroll
-      for (int w = 1; w < NW; ++w) t += sh[phase][w * (NQ + NC) + i];
-      if (i < NQ) q[i] = t; else c[i - NQ] = t;
+        for (int w = 1; w < NW; ++w) t += buf[w * NE + i];
+        v[i] = t;
+      }
+#pragma unroll
+      for (int i = 0; i < NCW; ++i) {
+        pk[i] = (unsigned long long)__double_as_longlong(buf[NV + i]);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) pk[i] += (unsigned long long)__double_as_longlong(buf[w * NE + NV + i]);
+      }
+    } else {
+      // many waves: a lane takes one wave's entry and the lanes are summed (the entries repeat every NW lanes)
+      static_assert(NW == 8 || NW == 16, "groups of lanes a DPP butterfly covers");
+      const double* mine = buf + (lane_id() & (NW - 1)) * NE;
+#pragma unroll
+      for (int i = 0; i < NV; ++i) v[i] = mine[i];
+#pragma unroll
+      for (int i = 0; i < NCW; ++i) pk[i] = (unsigned long long)__double_as_longlong(mine[NV + i]);
+#pragma unroll
+      for (int i = 0; i < NV; ++i) v[i] = lane_group_sum<NW>(v[i]);
+#pragma unroll
+      for (int i = 0; i < NCW; ++i) pk[i] = lane_group_sum<NW>(pk[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < NCW; ++i) {
+      const unsigned long long t = pk[i];
+      const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(t & 0xffffffffull));
+      const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(t >> 32));
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (4 * i + k < NC) c[4 * i + k] = (int)(((k < 2 ? lo : hi) >> (16 * (k & 1))) & 0xffffu);
     }
     phase ^= 1;
   }
 }
 
-// Alg. 2 for one vector of at most 4 slots per lane, tuned for the latency of a single vector (the
-// on-line case): the codes of a slot are kept as wave-uniform 64-bit ballots (scalar registers), so
-// the disagreement counts of Eq. 5 are scalar popcounts with no cross-lane reduction, only B^T w
-// travels through the binary64 lane reduction, and the K x K system is solved in binary64 on the
-// vector unit (K <= 3).  Same interface and results as quantize_core below.
-template <int K, int NJ, int NW>
-__device__ __forceinline__ void quantize_core_uniform(const float (&w)[NJ], int n, int base, int nj, bool do_greedy,
-                                                      int iters, bool do_ls, bool do_bst, float (&alpha)[K],
-                                                      unsigned long long (&mym)[K], double (&q)[K],
-                                                      double (*sh)[16 * kMaxRed], int& phase,
-                                                      unsigned long long* marks) {
-  (void)marks;
-  static_assert(NJ <= 4, "ballots of every slot and plane live in scalar registers");
-  constexpr int M = 1 << K;
-  constexpr int NP = K * (K - 1) / 2;
+// The upper half of the sorted code table: thr[t-1] = bits of the midpoint between positions t-1 and t (wave-
+// uniform), and per plane the H-bit mask of f_i over the positions.  Values are the binary32 left-to-right sums
+// of Alg. 2; equal values keep the order of their patterns.
+template <int K>
+struct CodeTable {
+  static constexpr int H = 1 << (K - 1);
+  int thr[H > 1 ? H - 1 : 1];
+  unsigned bm[K];
+};
+
+__device__ __forceinline__ int uniform_bits(float v) { return __builtin_amdgcn_readfirstlane(__float_as_int(v)); }
+
+template <int K>
+__device__ __forceinline__ void code_table_any_order(const float (&alpha)[K], CodeTable<K>& ct) {
+  // lane p < H owns the pair of patterns p | H and its complement, represented by the one whose value is not
+  // negative; it ranks its (value, pattern) among the H pairs and pushes it to the lane of its rank
+  constexpr int H = CodeTable<K>::H;
   const int lane = lane_id();
-  const double dn = (double)n;
-  const bool n_pow2 = (n & (n - 1)) == 0;
-  const double inv_n = 1.0 / dn;  // exact for a power of two, where s / n == s * inv_n bit for bit
-  unsigned long long mk[K][NJ];   // mk[i][j]: plane i of slot j, bit = lane
-#pragma unroll
-  for (int i = 0; i < K; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) mk[i][j] = 0ull;
-  // Which lanes of a slot lie inside the vector, as wave-uniform masks.  A comparison is written so that its
-  // ballot is the comparison's own scalar result, and "inside the vector" is an AND on the scalar unit;
-  // where a lane needs a mask as a condition it takes its bit straight from the mask (lane_bit).  A wave
-  // whose slots all lie inside (the usual case: 1024 entries on four waves) runs a form without the masks.
-  unsigned long long inside[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) inside[j] = (j < nj) ? __ballot((base + j) * 64 + lane < n) : 0ull;
-  const bool all_inside = nj == NJ && (base + NJ) * 64 <= n;
-  double wd[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) wd[j] = (double)w[j];
-
-  auto greedy = [&](auto full_c) {
-    constexpr bool FULL = decltype(full_c)::value;
-    // ---- greedy initialisation, Eq. 4 (one pass per stage, as in quantize_core)
-    float r[NJ];
-    double s[1];
-    double lane_l1;  // this lane's share of sum |w|, which is also its share of b_1^T w (same terms, same order)
-    {
-      double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        r[j] = w[j];
-        if (j & 1) s1 += (double)fabsf(w[j]); else s0 += (double)fabsf(w[j]);
-      }
-      lane_l1 = s0 + s1;
-      s[0] = lane_l1;
-    }
-    block_totals<NW, 1>(s, sh, phase);
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      const float al = n_pow2 ? (float)(s[0] * inv_n) : (float)(s[0] / dn);
-      alpha[i] = al;
-      // (sums of +-w start from their first term: 0.0 + x is an instruction the compiler may not drop,
-      // x being -0.0 for all it knows)
-      double q0 = 0.0, q1 = 0.0, s0 = 0.0, s1 = 0.0;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const unsigned long long ge = __ballot(r[j] >= 0.0f);
-        const unsigned long long m = FULL ? ge : (ge & inside[j]);
-        mk[i][j] = m;
-        const bool bit = lane_bit(m);
-        if constexpr (K > 1) {
-          float rn = r[j] - (bit ? al : -al);
-          if constexpr (!FULL) rn = lane_bit(inside[j]) ? rn : 0.0f;
-          r[j] = rn;
-          if (i > 0) {
-            const double sw = bit ? wd[j] : -wd[j];
-            if (j & 1) q1 = (j == 1) ? sw : q1 + sw; else q0 = (j == 0) ? sw : q0 + sw;
-          }
-          if (i + 1 < K) {
-            if (j & 1) s1 += (double)fabsf(rn); else s0 += (double)fabsf(rn);
-          }
-        }
-      }
-      q[i] = (i == 0) ? lane_l1 : (NJ > 1 ? q0 + q1 : q0);
-      if (i + 1 < K) {
-        s[0] = s0 + s1;
-        block_totals<NW, 1>(s, sh, phase);
-      }
-    }
-  };
-  if (do_greedy) {
-    if (all_inside) greedy(std::true_type{}); else greedy(std::false_type{});
-  } else if (do_ls) {
-    // codes given by the caller as per-lane masks (lane j holds slot j)
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      const int lo = (int)(mym[i] & 0xffffffffull), hi = (int)(mym[i] >> 32);
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        mk[i][j] = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane(hi, j) << 32) |
-                   (unsigned)__builtin_amdgcn_readlane(lo, j);
-    }
-  }
-  AMQ_PHASE(marks, 2);
-  for (int it = 0; it < iters; ++it) {
-    if (do_ls) {
-      // ---- Eq. 5: B^T w through the lane reduction, the disagreement counts of the plane pairs
-      // from the ballots on the scalar unit
-      double cnt[NP > 0 ? NP : 1];
-      {
-        int t = 0;
-#pragma unroll
-        for (int a = 0; a < K; ++a)
-#pragma unroll
-          for (int b = a + 1; b < K; ++b) {
-            int c = 0;
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) c += __popcll(mk[a][j] ^ mk[b][j]);
-            cnt[t++] = (double)c;
-          }
-      }
-      block_totals_mixed<NW, K, NP>(q, cnt, sh, phase);
-      AMQ_PHASE(marks, 4 + 4 * it);
-      if constexpr (K <= 3) {
-        ls_solve_f64<K>(n, cnt, q, alpha);
-      } else {
-        int G[K][K];
-        int t = 0;
-#pragma unroll
-        for (int a = 0; a < K; ++a) {
-          G[a][a] = n;
-#pragma unroll
-          for (int b = a + 1; b < K; ++b) {
-            const int d = __builtin_amdgcn_readfirstlane((int)cnt[t++]);
-            G[a][b] = n - 2 * d;
-            G[b][a] = G[a][b];
-          }
-        }
-        ls_solve<K>(G, q, alpha);
-      }
-      AMQ_PHASE(marks, 5 + 4 * it);
-      if (!do_bst) break;
-    }
-
-    // ---- code table in ascending order (Alg. 2), across lanes as in quantize_core
-    const int p = lane & (M - 1);
-    float v = 0.0f;
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      const float term = ((p >> (K - 1 - i)) & 1) ? alpha[i] : -alpha[i];
-      v = (i == 0) ? term : v + term;
-    }
-    int rank = 0;
-#pragma unroll
-    for (int o = 0; o < M; ++o) {
-      const float vo = readlane_f(v, o);
-      rank += (vo < v || (vo == v && o < p)) ? 1 : 0;
-    }
-    if (lane >= M) rank = lane;
-    const float sv = __int_as_float(__builtin_amdgcn_ds_permute(rank << 2, __float_as_int(v)));
-    const int sp = __builtin_amdgcn_ds_permute(rank << 2, p);
-    // midpoint of a code and its upper neighbour: every lane forms its own (the neighbour's value comes
-    // through a row shift), the first M - 1 are then read out as wave-uniform values
-    const float up = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(sv), 0x101 /* row_shl:1 */, 0xf, 0xf, true));
-    const float mid = 0.5f * (sv + up);
-    float thr[M - 1];
-#pragma unroll
-    for (int j = 0; j < M - 1; ++j) thr[j] = readlane_f(mid, j);
-    unsigned bm[K];  // bit `pos` of bm[i]: plane i is +1 for the code at sorted position pos
-#pragma unroll
-    for (int i = 0; i < K; ++i) bm[i] = (unsigned)__ballot((sp & (1 << (K - 1 - i))) != 0) & (unsigned)((1ull << M) - 1ull);
-    AMQ_PHASE(marks, 6 + 4 * it);
-
-    // ---- codes with the coefficients fixed (Alg. 1)
-    const bool more = do_ls && (it + 1 < iters);
-    auto assign = [&](auto full_c, auto more_c) {
-      constexpr bool FULL = decltype(full_c)::value;
-      constexpr bool MORE = decltype(more_c)::value;  // B^T w is needed by another cycle
-      double qa[K], qb[K];
-#pragma unroll
-      for (int i = 0; i < K; ++i) { qa[i] = 0.0; qb[i] = 0.0; }
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        int pos = 0;  // position in the sorted table = number of midpoints <= w
-#pragma unroll
-        for (int t = 0; t < M - 1; ++t) pos += (w[j] >= thr[t]) ? 1 : 0;
-        const unsigned sel = 1u << pos;
-#pragma unroll
-        for (int i = 0; i < K; ++i) {
-          const unsigned long long hit = __ballot((sel & bm[i]) != 0u);
-          const unsigned long long m = FULL ? hit : (hit & inside[j]);
-          mk[i][j] = m;
-          if constexpr (MORE) {
-            const double sw = lane_bit(m) ? wd[j] : -wd[j];
-            if (j & 1) qb[i] = (j == 1) ? sw : qb[i] + sw; else qa[i] = (j == 0) ? sw : qa[i] + sw;
-          }
-        }
-      }
-      if constexpr (MORE) {
-#pragma unroll
-        for (int i = 0; i < K; ++i) q[i] = NJ > 1 ? qa[i] + qb[i] : qa[i];
-      }
-    };
-    if (all_inside) {
-      if (more) assign(std::true_type{}, std::true_type{}); else assign(std::true_type{}, std::false_type{});
-    } else {
-      if (more) assign(std::false_type{}, std::true_type{}); else assign(std::false_type{}, std::false_type{});
-    }
-    AMQ_PHASE(marks, 7 + 4 * it);
-  }
-  // lane j takes the ballots of slot j (the layout the callers store)
+  const int p = (lane & (H - 1)) | H;
+  float v = 0.0f;
 #pragma unroll
   for (int i = 0; i < K; ++i) {
-    unsigned long long mine = 0ull;
+    const float term = ((p >> (K - 1 - i)) & 1) ? alpha[i] : -alpha[i];
+    v = (i == 0) ? term : v + term;
+  }
+  const int pat = (v < 0.0f) ? (2 * H - 1) ^ p : p;
+  const int vb = __float_as_int(fabsf(v));
+  int rank = 0;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) keep_in_lane(mine, mk[i][j], j);
-    mym[i] = mine;
+  for (int o = 0; o < H; ++o) {
+    const int vo = __builtin_amdgcn_readlane(vb, o), po = __builtin_amdgcn_readlane(pat, o);
+    rank += (vo < vb || (vo == vb && po < pat)) ? 1 : 0;
+  }
+  if (lane >= H) rank = lane;
+  const float sv = __int_as_float(__builtin_amdgcn_ds_permute(rank << 2, vb));
+  const int sp = __builtin_amdgcn_ds_permute(rank << 2, pat);
+  const float up = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(sv), 0x101 /* row_shl:1 */, 0xf, 0xf, true));
+  const int mid = __float_as_int(0.5f * (sv + up));
+#pragma unroll
+  for (int t = 0; t < H - 1; ++t) ct.thr[t] = __builtin_amdgcn_readlane(mid, t);
+#pragma unroll
+  for (int i = 0; i < K; ++i) ct.bm[i] = (unsigned)__ballot((sp & (1 << (K - 1 - i))) != 0) & ((1u << H) - 1u);
+}
+
+template <int K>
+__device__ __forceinline__ void code_table(const float (&alpha)[K], CodeTable<K>& ct) {
+  static_assert(K >= 2, "one plane has no midpoint but 0");
+  if constexpr (K == 2) {
+    // alpha_1 >= alpha_2 >= 0, the order after any ordinary least-squares step
+    const float v2 = alpha[0] - alpha[1], v3 = alpha[0] + alpha[1];
+    if (__ballot(v2 >= 0.0f && alpha[1] >= 0.0f) != 0ull) {
+      ct.thr[0] = uniform_bits(0.5f * (v2 + v3));
+      ct.bm[0] = 3u;
+      ct.bm[1] = 2u;
+      return;
+    }
+  } else if constexpr (K == 3) {
+    // patterns 100 (or its complement 011), 101, 110, 111 in this order: the two cases that occur in practice
+    const float d = alpha[0] - alpha[1], s = alpha[0] + alpha[1];
+    const float v4 = d - alpha[2], v5 = d + alpha[2], v6 = s - alpha[2], v7 = s + alpha[2];
+    const float lo = fabsf(v4);
+    if (__ballot(lo <= v5 && v5 <= v6 && v6 <= v7) != 0ull) {
+      ct.thr[0] = uniform_bits(0.5f * (lo + v5));
+      ct.thr[1] = uniform_bits(0.5f * (v5 + v6));
+      ct.thr[2] = uniform_bits(0.5f * (v6 + v7));
+      const bool swap = __ballot(v4 < 0.0f) != 0ull;
+      ct.bm[0] = swap ? 0xeu : 0xfu;
+      ct.bm[1] = swap ? 0xdu : 0xcu;
+      ct.bm[2] = swap ? 0xbu : 0xau;
+      return;
+    }
+  }
+  code_table_any_order<K>(alpha, ct);
+}
+
+// Step of f at position t: f(t) - f(t - 1), from the mask of a plane (or of the difference of two planes).
+__device__ __forceinline__ int step_at(unsigned bm, int t) { return (int)((bm >> t) & 1u) - (int)((bm >> (t - 1)) & 1u); }
+
+// B_i^T w = sum |w| (2 f_i - 1) = q0 + sum_t 2 (step of f_i at t) C_t with q0 = +-sum |w| by f_i(0); the factors
+// are exact powers of two.
+template <int NT>
+__device__ __forceinline__ double plane_dot(unsigned bm, double q0, const double (&c)[NT]) {
+  double q = q0;
+#pragma unroll
+  for (int t = 1; t <= NT; ++t) q = __builtin_fma(__hiloint2double(step_at(bm, t) << 30, 0), c[t - 1], q);
+  return q;
+}
+
+// Up to this many slots per lane the sign masks of the slots stay in scalar registers; beyond, a sign is taken from
+// the stored value where it is needed (16 slots would fill a third of the scalar registers and spill).
+constexpr int kSignMaskSlots = 4;
+
+// Alg. 2 for one vector: x[j] of lane L is entry (base + j) * 64 + L (0 beyond n), NW waves cooperate with nj
+// slots each.  On return alpha holds the coefficients and lane j of each wave, in mym[i], the 64 packed codes of
+// its slot j of plane i.  FULL: every slot of this wave is there and lies inside the vector.
+template <int K, int NJ, int NW, bool FULL>
+__device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n, int base, int nj, int T,
+                                                    float (&alpha)[K], unsigned long long (&mym)[K],
+                                                    double (*sh)[16 * kMaxRed], int& phase, unsigned long long* marks) {
+  (void)marks;  // phase timers of the profiling build: 2 = greedy done, 4 + 4 * cycle + {0: reduction, 1: solve, 2: table, 3: assignment}
+  constexpr int H = 1 << (K - 1);
+  constexpr int NT = H > 1 ? H - 1 : 1;
+  constexpr int NP = K * (K - 1) / 2;
+  const double dn = (double)n;
+  const double inv_n = recip_f64(dn);  // (exact for a power of two; the last binary64 digit is rounded away)
+  auto mean = [&](double s) { return (float)(s * inv_n); };
+  auto there = [&](int j) { return FULL || j < nj; };
+  auto inside = [&](int j) { return FULL ? ~0ull : lanes_inside(NJ > 4 ? opaque_s(n) : n, base + j); };
+  const unsigned long long lane_inside = FULL ? ~0ull : lanes_inside(n, base + lane_id());
+
+  int u[NJ];                     // order-preserving integer of |w| with the tie rule folded in
+  double wd[NJ];                 // w
+  float r[NJ];                   // greedy residual
+  unsigned long long neg[NJ <= kSignMaskSlots ? NJ : 1];  // w < 0
+  unsigned long long lane_neg = 0ull;                     // the same, slot j in lane j
+  double sum[1] = {0.0};
+  int no_counts[1] = {0};
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    if (there(j)) {
+      const float xc = x[j] + 0.0f;  // -0.0 -> +0.0
+      const unsigned b = __float_as_uint(xc);
+      // b, or bits(|w|) - 1 = b + 0x7fffffff (mod 2^32) for a set sign bit: the smaller of the two in both cases
+      u[j] = (int)min(b, b + 0x7fffffffu);
+      wd[j] = (double)xc;
+      const unsigned long long ng = __ballot(xc < 0.0f);
+      if constexpr (NJ <= kSignMaskSlots) neg[j] = ng;
+      keep_in_lane(lane_neg, ng, j);
+      r[j] = xc;
+      sum[0] = (j == 0) ? fabs(wd[j]) : sum[0] + fabs(wd[j]);
+    } else {
+      u[j] = 0;
+      wd[j] = 0.0;
+      if constexpr (NJ <= kSignMaskSlots) neg[j] = 0ull;
+      r[j] = 0.0f;
+    }
+    if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+  exchange_totals<NW, 1, 0>(sum, no_counts, sh, phase);
+  const double l1 = sum[0];
+  alpha[0] = mean(l1);
+  if constexpr (K == 1) {
+    // the sign codes are final: Eq. 5 returns mean |w| again and the only midpoint is 0
+    mym[0] = ~lane_neg & lane_inside;
+    return;
+  } else {
+    // ---- greedy stages 2 .. K (Eq. 4): the residual loses the previous plane, its sign is the next plane.
+    // s[i] = sum of |w| where plane i agrees with the sign of w, cnt = disagreement counts of the plane pairs.
+    double s[K];     // s[1 .. K-1]; s[0] carries sum |r| of the last stage into the first Eq.-5 reduction
+    int cnt[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) cnt[i] = 0;
+#pragma unroll
+    for (int i = 1; i < K; ++i) {
+      const float a = alpha[i - 1];
+      const int abits = uniform_bits(a);
+      const int a0bits = opaque_s(uniform_bits(alpha[0]));
+      double sr[1] = {0.0}, si[1] = {0.0};
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if (there(j)) {
+          const unsigned long long in = inside(j);
+          unsigned long long before = 0ull;  // previous plane against the sign of w
+          if (NJ > 4 && i > 2) r[j] = opaque_v(r[j]);
+          if (i > 1) before = __ballot(r[j] < 0.0f);
+          float rn = r[j] - copysignf(a, r[j]);  // (a difference is never -0.0)
+          if (!FULL) rn = lane_bit(in) ? rn : 0.0f;
+          r[j] = rn;
+          unsigned long long f[1];
+          if (i == 1) {
+            f[0] = __ballot(u[j] >= abits);
+          } else {
+            const unsigned long long ng = __ballot(rn < 0.0f);
+            if constexpr (NJ <= kSignMaskSlots) f[0] = ~(ng ^ neg[j]);
+            else f[0] = __ballot((__float_as_int(rn) ^ __double2hiint(wd[j])) >= 0);
+            // pairs (i - 1, i) of planes beyond the first: both signs are at hand
+            add_count<NJ>(cnt[K == 3 ? 2 : (i == 2 ? 3 : 5)], (before ^ ng) & in);
+            if (K == 4 && i == 3) add_count<NJ>(cnt[4], (__ballot(u[j] >= a0bits) ^ f[0]) & in);
+          }
+          f[0] &= in;
+          add_count<NJ>(cnt[i - 1], f[0]);
+          masked_add<1>(si, wd[j], f);
+          const double ra = (double)fabsf(rn);
+          sr[0] = (j == 0) ? ra : sr[0] + ra;
+        }
+        if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+      s[i] = si[0];
+      if (i + 1 < K) {
+        exchange_totals<NW, 1, 0>(sr, no_counts, sh, phase);
+        alpha[i] = mean(sr[0]);
+      } else {
+        s[0] = sr[0];
+      }
+    }
+    AMQ_PHASE(marks, 2);
+    exchange_totals<NW, K, NP>(s, cnt, sh, phase);
+    alpha[K - 1] = mean(s[0]);
+    if (T == 0) {
+      // the greedy result itself: its planes are formed again from the coefficients
+#pragma unroll
+      for (int i = 0; i < K; ++i) mym[i] = 0ull;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        double w0 = wd[j];
+        asm volatile("" : "+v"(w0));  // (otherwise the binary32 value is kept in registers from the start for this)
+        float rj = (float)w0;
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+          keep_in_lane(mym[i], __ballot(rj >= 0.0f), j);
+          rj = rj - copysignf(alpha[i], rj);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < K; ++i) mym[i] &= lane_inside;
+      return;
+    }
+    double q[K], d[NP];
+    q[0] = l1;
+#pragma unroll
+    for (int i = 1; i < K; ++i) {
+      q[i] = 2.0 * s[i] - l1;
+      d[i - 1] = (double)(n - cnt[i - 1]);
+    }
+#pragma unroll
+    for (int i = K - 1; i < NP; ++i) d[i] = (double)cnt[i];
+
+    CodeTable<K> ct;
+    for (int it = 0;; ++it) {
+      AMQ_PHASE(marks, 4 + 4 * it);
+      ls_solve_f64<K>(n, d, q, alpha);
+      AMQ_PHASE(marks, 5 + 4 * it);
+      code_table<K>(alpha, ct);
+      AMQ_PHASE(marks, 6 + 4 * it);
+      if (it + 1 == T) break;
+      // ---- a pass that another cycle follows: only C_t and N_t
+      double c[NT];
+      int cn[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) { c[t] = 0.0; cn[t] = 0; }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if (there(j)) {
+          const unsigned long long in = inside(j);
+          unsigned long long ge[NT];
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            ge[t] = __ballot(u[j] >= ct.thr[t]) & in;
+            add_count<NJ>(cn[t], ge[t]);
+          }
+          masked_add<NT>(c, wd[j], ge);
+        }
+        if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+      AMQ_PHASE(marks, 7 + 4 * it);
+      if constexpr (K == 4) {
+        // four plane sums instead of seven C_t through the reduction (this lane's shares, without sum |w|)
+        double sp[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) sp[i] = plane_dot<NT>(ct.bm[i], 0.0, c);
+        exchange_totals<NW, K, NT>(sp, cn, sh, phase);
+#pragma unroll
+        for (int i = 0; i < K; ++i) q[i] = ((ct.bm[i] & 1u) ? l1 : -l1) + sp[i];
+      } else {
+        exchange_totals<NW, NT, NT>(c, cn, sh, phase);
+#pragma unroll
+        for (int i = 0; i < K; ++i) q[i] = plane_dot<NT>(ct.bm[i], (ct.bm[i] & 1u) ? l1 : -l1, c);
+      }
+      int t0 = 0;
+#pragma unroll
+      for (int a = 0; a < K; ++a)
+#pragma unroll
+        for (int b = a + 1; b < K; ++b) {
+          const unsigned xo = ct.bm[a] ^ ct.bm[b];
+          int dd = (xo & 1u) ? n : 0;
+#pragma unroll
+          for (int t = 1; t <= NT; ++t) dd += step_at(xo, t) * cn[t - 1];
+          d[t0++] = (double)dd;
+        }
+    }
+
+    // ---- the last pass: the comparison masks, slot j in lane j, then the planes in the lanes
+    unsigned long long ge[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) ge[t] = 0ull;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      if (there(j)) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) keep_in_lane(ge[t], __ballot(u[j] >= ct.thr[t]), j);
+      }
+      if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      unsigned long long p = lane_neg ^ (0ull - (unsigned long long)(ct.bm[i] & 1u));
+#pragma unroll
+      for (int t = 1; t <= NT; ++t)
+        p ^= ge[t - 1] & (0ull - (unsigned long long)(((ct.bm[i] >> t) ^ (ct.bm[i] >> (t - 1))) & 1u));
+      mym[i] = p & lane_inside;
+    }
+    AMQ_PHASE(marks, 11);
   }
 }
 
-// The arithmetic of Alg. 2 for one vector held in registers: `w[j]` of lane L is entry
-// (base + j) * 64 + L (0 beyond n); NW waves cooperate (nj slots each).  On return alpha holds the
-// coefficients and lane j of each wave holds in mym[i] the 64 packed codes of its slot j of
-// plane i.  Stages are selected by the caller: greedy initialisation, then `iters` cycles of
-// { Eq. 5 if do_ls; code table + Alg. 1 if do_bst }.  With do_greedy false the caller
-// provides alpha, and (if do_ls) mym and the per-lane partial sums q of B^T w.
+// The same for a wave that may or may not have all its slots inside the vector (a wave-uniform choice; the
+// waves of a workgroup meet at the same barriers either way).
 template <int K, int NJ, int NW>
-__device__ __forceinline__ void quantize_core(const float (&w)[NJ], int n, int base, int nj, bool do_greedy,
-                                              int iters, bool do_ls, bool do_bst, float (&alpha)[K],
-                                              unsigned long long (&mym)[K], double (&q)[K],
-                                              double (*sh)[16 * kMaxRed], int& phase,
+__device__ __forceinline__ void quantize_core(const float (&x)[NJ], int n, int base, int nj, int T, float (&alpha)[K],
+                                              unsigned long long (&mym)[K], double (*sh)[16 * kMaxRed], int& phase,
                                               unsigned long long* marks = nullptr) {
-  (void)marks;  // phase timers of the profiling build: 2 = greedy done, 4 + 4 * cycle + {0: reduction, 1: solve, 2: table, 3: assignment}
-  if constexpr (NJ <= 4 && K <= 3) {  // (K = 4 would need more scalar registers than a wave has)
-    quantize_core_uniform<K, NJ, NW>(w, n, base, nj, do_greedy, iters, do_ls, do_bst, alpha, mym, q, sh, phase, marks);
-    return;
-  }
-  constexpr int M = 1 << K;
-  constexpr int NP = K * (K - 1) / 2;
-  const int lane = lane_id();
-  const double dn = (double)n;
-  const bool n_pow2 = (n & (n - 1)) == 0;
-  const double inv_n = 1.0 / dn;  // exact for a power of two, where s / n == s * inv_n bit for bit
-  // Every slot of this wave inside the vector (the common case of the throughput regime: rows whose
-  // length is a multiple of 64 * NJ * NW) takes a second instantiation of the per-entry loops without
-  // the range checks.
-  const bool full = nj == NJ && (base + NJ) * 64 <= n;
-  // One cycle has no effect at K = 1 (Eq. 5 returns sum |w| / n again -- the same terms in the same
-  // order -- and the only midpoint of the code table {-alpha, +alpha} is 0), so the greedy codes and
-  // coefficient are final there.
-  if (K == 1 && do_greedy) iters = 0;
-
-  auto greedy = [&](auto full_c) {
-    constexpr bool FULL = decltype(full_c)::value;
-    // ---- greedy initialisation, Eq. 4.  One pass per stage: it assigns the signs, updates the
-    // residual and accumulates the l1 norm of the new residual for the next stage.
-    float r[NJ];
-    double s[1];
-    double lane_l1;  // this lane's share of sum |w|, which is also its share of b_1^T w
-    {
-      double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        r[j] = w[j];
-        if (j & 1) s1 += (double)fabsf(w[j]); else s0 += (double)fabsf(w[j]);
-      }
-      lane_l1 = s0 + s1;
-      s[0] = lane_l1;
-    }
-    block_totals<NW, 1>(s, sh, phase);
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      const float al = n_pow2 ? (float)(s[0] * inv_n) : (float)(s[0] / dn);
-      alpha[i] = al;
-      unsigned long long mine = 0ull;
-      double q0 = 0.0, q1 = 0.0, s0 = 0.0, s1 = 0.0;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        if (FULL || j < nj) {
-          const bool valid = FULL || (base + j) * 64 + lane < n;
-          const bool bit = valid && (r[j] >= 0.0f);
-          keep_in_lane(mine, __ballot(bit), j);
-          if constexpr (K > 1) {
-            const float rn = valid ? r[j] - (bit ? al : -al) : 0.0f;
-            r[j] = rn;
-            if (i > 0) {  // (stage 0: b_1^T w is sum |w|, term by term)
-              const double sw = bit ? (double)w[j] : -(double)w[j];
-              if (j & 1) q1 += sw; else q0 += sw;
-            }
-            if (i + 1 < K) {
-              if (j & 1) s1 += (double)fabsf(rn); else s0 += (double)fabsf(rn);
-            }
-          }
-        }
-        // (keeps the slots apart: left alone, the scheduler forms all ballots first and spills them)
-        if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-      }
-      mym[i] = mine;
-      q[i] = (i == 0) ? lane_l1 : q0 + q1;
-      if (i + 1 < K) {
-        s[0] = s0 + s1;
-        block_totals<NW, 1>(s, sh, phase);
-      }
-    }
-  };
-  if (do_greedy) {
-    if (full) greedy(std::true_type{}); else greedy(std::false_type{});
-  }
-  AMQ_PHASE(marks, 2);
-  for (int it = 0; it < iters; ++it) {
-    if (do_ls) {
-      // ---- coefficients with the codes fixed, Eq. 5: B^T w and the disagreement counts of
-      // every plane pair go through one workgroup reduction (counts are exact in binary64)
-      double red[K + NP];
-#pragma unroll
-      for (int i = 0; i < K; ++i) red[i] = q[i];
-      {
-        int t = K;
-#pragma unroll
-        for (int i = 0; i < K; ++i)
-#pragma unroll
-          for (int j = i + 1; j < K; ++j) red[t++] = (double)__popcll(mym[i] ^ mym[j]);
-      }
-      block_totals<NW, K + NP>(red, sh, phase);
-      AMQ_PHASE(marks, 4 + 4 * it);
-      if constexpr (K <= 3) {
-        double qq[K];
-#pragma unroll
-        for (int i = 0; i < K; ++i) qq[i] = red[i];
-        ls_solve_f64<K>(n, red + K, qq, alpha);
-      } else {
-        int G[K][K];
-        double qq[K];
-        int t = K;
-#pragma unroll
-        for (int i = 0; i < K; ++i) {
-          qq[i] = red[i];
-          G[i][i] = n;
-#pragma unroll
-          for (int j = i + 1; j < K; ++j) {
-            const int d = __builtin_amdgcn_readfirstlane((int)red[t++]);  // wave-uniform: integer math on the scalar unit
-            G[i][j] = n - 2 * d;
-            G[j][i] = G[i][j];
-          }
-        }
-        ls_solve<K>(G, qq, alpha);
-      }
-      AMQ_PHASE(marks, 5 + 4 * it);
-      if (!do_bst) break;
-    }
-
-    // ---- code table in ascending order (Alg. 2) built across lanes: lane p < 2^K owns the
-    // pattern p (coefficient i positive iff bit K-1-i of p), ranks itself among all values
-    // (ties by pattern), and pushes (value, pattern) to the lane of its rank.
-    const int p = lane & (M - 1);
-    float v = 0.0f;
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      const float term = ((p >> (K - 1 - i)) & 1) ? alpha[i] : -alpha[i];
-      v = (i == 0) ? term : v + term;
-    }
-    int rank = 0;
-#pragma unroll
-    for (int o = 0; o < M; ++o) {
-      const float vo = readlane_f(v, o);
-      rank += (vo < v || (vo == v && o < p)) ? 1 : 0;
-    }
-    if (lane >= M) rank = lane;
-    const float sv = __int_as_float(__builtin_amdgcn_ds_permute(rank << 2, __float_as_int(v)));
-    const int sp = __builtin_amdgcn_ds_permute(rank << 2, p);
-    float thr[M - 1];  // midpoints of adjacent codes, wave-uniform
-#pragma unroll
-    for (int j = 0; j < M - 1; ++j) thr[j] = 0.5f * (readlane_f(sv, j) + readlane_f(sv, j + 1));
-    unsigned bm[K];  // bit `pos` of bm[i]: plane i is +1 for the code at sorted position pos
-#pragma unroll
-    for (int i = 0; i < K; ++i) bm[i] = (unsigned)__ballot(lane < M && ((sp >> (K - 1 - i)) & 1));
-    AMQ_PHASE(marks, 6 + 4 * it);
-
-    // ---- codes with the coefficients fixed (Alg. 1); the position in the sorted table is the
-    // number of midpoints <= w, which is where the k-comparison tree walk ends.
-    const bool more = do_ls && (it + 1 < iters);  // B^T w is needed by another cycle
-    // wave-uniform masks (all ones or zero): the table's bit at position 0; whether it changes after position t
-    unsigned long long first[K], flips[K][M - 1];
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      first[i] = 0ull - (unsigned long long)(bm[i] & 1u);
-#pragma unroll
-      for (int t = 0; t < M - 1; ++t) flips[i][t] = 0ull - (unsigned long long)(((bm[i] >> t) ^ (bm[i] >> (t + 1))) & 1u);
-    }
-    auto assign = [&](auto full_c, auto more_c) {
-      constexpr bool FULL = decltype(full_c)::value;
-      constexpr bool MORE = decltype(more_c)::value;
-      unsigned long long mine[K];
-      double qa[K], qb[K];
-#pragma unroll
-      for (int i = 0; i < K; ++i) { mine[i] = 0ull; qa[i] = 0.0; qb[i] = 0.0; }
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        if (FULL || j < nj) {
-          const bool valid = FULL || (base + j) * 64 + lane < n;
-          const double wd = (double)w[j];
-          unsigned long long plane[K];  // wave-uniform: plane i of the 64 codes of this slot
-          if constexpr (K <= kMaskLogicMaxK) {
-            // The comparisons with the ascending midpoints form a thermometer code, so plane i of an
-            // entry's code is the table's bit at position 0, flipped once for every midpoint <= w at which
-            // the table's bit changes: logic on whole comparison masks, on the scalar unit.
-            unsigned long long ge[M - 1];
-#pragma unroll
-            for (int t = 0; t < M - 1; ++t) ge[t] = __ballot(w[j] >= thr[t]);
-            const unsigned long long in_range = FULL ? ~0ull : __ballot(valid);
-#pragma unroll
-            for (int i = 0; i < K; ++i) {
-              unsigned long long b = first[i];
-#pragma unroll
-              for (int t = 0; t < M - 1; ++t) b ^= ge[t] & flips[i][t];
-              plane[i] = FULL ? b : (b & in_range);
-            }
-          } else {
-            int pos = 0;
-#pragma unroll
-            for (int t = 0; t < M - 1; ++t) pos += (w[j] >= thr[t]) ? 1 : 0;
-#pragma unroll
-            for (int i = 0; i < K; ++i) plane[i] = __ballot(valid && ((bm[i] >> pos) & 1u));
-          }
-#pragma unroll
-          for (int i = 0; i < K; ++i) {
-            keep_in_lane(mine[i], plane[i], j);
-            if constexpr (MORE) {
-              const bool bit = lane_bit(plane[i]);
-              if (j & 1) qb[i] += bit ? wd : -wd; else qa[i] += bit ? wd : -wd;
-            }
-          }
-        }
-        if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int i = 0; i < K; ++i) { mym[i] = mine[i]; q[i] = qa[i] + qb[i]; }
-    };
-    if (full) {
-      if (more) assign(std::true_type{}, std::true_type{}); else assign(std::true_type{}, std::false_type{});
-    } else {
-      if (more) assign(std::false_type{}, std::true_type{}); else assign(std::false_type{}, std::false_type{});
-    }
-    AMQ_PHASE(marks, 7 + 4 * it);
-  }
+  base = __builtin_amdgcn_readfirstlane(base);
+  if (nj == NJ && (base + NJ) * 64 <= n)
+    quantize_magnitudes<K, NJ, NW, true>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+  else
+    quantize_magnitudes<K, NJ, NW, false>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
 }
 
 }  // namespace amq

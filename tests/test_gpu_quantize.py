@@ -168,3 +168,30 @@ def test_weight_quantizer_heavy_tailed_full_size(amq, k):
     for t, r in enumerate(sel):
         c0, a0 = oracle.greedy(W[r], k)
         assert err[t] <= oracle.error(W[r], c0, a0) * (1 + 1e-6)
+
+
+# One row count per regime (few vectors: at most 4 slots of 64 entries per lane; 1024 and more: up to 16) and
+# lengths around the edges of the register forms: slots per wave, waves per vector, a partly filled last slot.
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+@pytest.mark.parametrize("rows,lengths", [(7, (1, 64, 129, 255, 257, 513, 1025, 2047, 4095, 4097, 9000)),
+                                          (1031, (3, 128, 200, 500, 513, 650, 769, 1024, 1025, 1500, 2048, 2500, 3001, 4096, 4100))])
+def test_register_forms_and_special_rows(amq, k, rows, lengths):
+    for n in lengths:
+        say("forms k=%d rows=%d n=%d" % (k, rows, n))
+        g = np.random.default_rng(31 * n + k)
+        base = g.standard_normal((7, n)).astype(np.float32)
+        base[1] = -0.25                                          # constant: every further residual is exactly zero
+        base[2] = np.where(np.arange(n) % 3 == 0, -0.0, 0.0)     # zeros of both signs
+        base[3] = g.integers(-3, 4, n)                           # values that can meet a midpoint exactly
+        base[4, 0] = 1e4                                         # one entry dominates: unusual order of the code table
+        base[5] = np.abs(base[5])                                # one-sided
+        base[6] = base[6] ** 3                                   # heavy tails
+        X = np.ascontiguousarray(np.tile(base, ((rows + 6) // 7, 1))[:rows])
+        for T in (0, 1, 2, 3):
+            pr, ar = oracle.quantize_rows(base, k, T)
+            pg, ag = amq.quantize_weights(to_dev(X), k, T)
+            pg, ag = planes_host(pg), host(ag)
+            for r in range(7):                                   # equal rows give equal results
+                assert (pg[:, r::7] == pg[:, r:r + 1]).all() and (ag[r::7] == ag[r]).all()
+            assert_coef_close(ag[:7], ar)
+            compare_codes(base, pg[:, :7], pr, ar)
