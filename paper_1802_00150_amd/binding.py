@@ -4,6 +4,9 @@ Argument marshalling only: every function takes torch tensors that already live 
 passes their device pointers and the current HIP stream to the entry point of the same name,
 and raises on a non-zero status.  There is no CPU fallback: without the built library, or on
 tensors that are not on a GPU, every call fails loudly.
+
+The calls that serving, scoring and training loops make are marshalled by the native module
+_amq_torch (csrc/amq_torch.cpp), the others through ctypes.
 """
 import ctypes as C
 import os
@@ -118,6 +121,23 @@ def lib():
     return _lib
 
 
+_native_module = None
+
+
+def _load_native():
+    """The native half of this binding, bound to the same library file as lib()."""
+    global _native_module
+    lib()
+    try:
+        from . import _amq_torch
+    except ImportError as e:
+        raise AmqError("_amq_torch.so is not built: run `python -m paper_1802_00150_amd.build` "
+                       "(or __graft_entry__.build()) first") from e
+    _amq_torch.load(LIB_PATH, AmqError)
+    _native_module = _amq_torch
+    return _amq_torch
+
+
 def _check(status):
     if status != 0:
         L = lib()
@@ -161,28 +181,12 @@ QUANT_FINAL_LS = 1
 def quantize_weights(W, k, T, final_ls=False):
     """W [rows, cols] float32 (rows may be strided) -> planes [k, rows, wpr] int32, alpha [rows, k].
     final_ls: one more coefficient update (Eq. 5) after the last code assignment."""
-    if W.dim() != 2 or W.stride(1) != 1 or W.dtype != torch.float32 or not W.is_cuda:
-        raise AmqError("expected a 2-D float32 GPU tensor with unit column stride")
-    rows, cols = W.shape
-    planes = _empty((k, rows, wpr(cols)), torch.int32, W)
-    alpha = _empty((rows, k), torch.float32, W)
-    if final_ls:
-        _check(lib().amq_quantize_weights_ex(W.data_ptr(), rows, cols, W.stride(0), k, T, QUANT_FINAL_LS,
-                                             planes.data_ptr(), alpha.data_ptr(), _stream()))
-    else:
-        _check(lib().amq_quantize_weights(W.data_ptr(), rows, cols, W.stride(0), k, T, planes.data_ptr(),
-                                          alpha.data_ptr(), _stream()))
-    return planes, alpha
+    return (_native_module or _load_native()).quantize_weights(W, k, T, QUANT_FINAL_LS if final_ls else 0)
 
 
 def quantize_activations(X, k, T):
     """X [batch, n] float32 -> planes [k, batch, wpr] int32, beta [batch, k]."""
-    batch, n = X.shape
-    planes = _empty((k, batch, wpr(n)), torch.int32, X)
-    beta = _empty((batch, k), torch.float32, X)
-    _check(lib().amq_quantize_activations(_dev(X, torch.float32), batch, n, k, T, planes.data_ptr(),
-                                          beta.data_ptr(), _stream()))
-    return planes, beta
+    return (_native_module or _load_native()).quantize_activations(X, k, T)
 
 
 def ls_update(X, planes, coef):
@@ -216,27 +220,11 @@ def binary_dots(Wp, n, Xp):
 
 def binary_gemm(Wp, alpha, n, Xp, beta, bias=None, Y=None):
     """Y [batch, m]; if Y is given the product is accumulated into it (in place)."""
-    k_w, m, _ = Wp.shape
-    k_a, batch, _ = Xp.shape
-    acc = Y is not None
-    if not acc:
-        Y = _empty((batch, m), torch.float32, Wp)
-    _check(lib().amq_binary_gemm(_dev(Wp, torch.int32), _dev(alpha, torch.float32), m, n, k_w,
-                                 _dev(Xp, torch.int32), _dev(beta, torch.float32), batch, k_a, _opt(bias),
-                                 1 if acc else 0, _dev(Y, torch.float32), _stream()))
-    return Y
+    return (_native_module or _load_native()).binary_gemm(Wp, alpha, n, Xp, beta, bias, Y)
 
 
 def binary_gemv(Wp, alpha, n, Xp, beta, bias=None, Y=None):
-    k_w, m, _ = Wp.shape
-    k_a = Xp.shape[0]
-    acc = Y is not None
-    if not acc:
-        Y = _empty((1, m), torch.float32, Wp)
-    _check(lib().amq_binary_gemv(_dev(Wp, torch.int32), _dev(alpha, torch.float32), m, n, k_w,
-                                 _dev(Xp, torch.int32), _dev(beta, torch.float32), k_a, _opt(bias),
-                                 1 if acc else 0, _dev(Y, torch.float32), _stream()))
-    return Y
+    return (_native_module or _load_native()).binary_gemv(Wp, alpha, n, Xp, beta, bias, Y)
 
 
 def binary_gemv_grouped(Wp, alpha, n, Xp, beta, bias=None, Y=None):
@@ -269,20 +257,8 @@ def gru_workspace(I, H, B, k_a, device):
 
 def lstm_step(Wxp, alpha_x, Whp, alpha_h, I, H, bias, x, h_prev, c_prev, k_a, T, ws=None, h_out=None,
               c_out=None):
-    k_w = Wxp.shape[0]
-    B = x.shape[0]
-    if ws is None:
-        ws = lstm_workspace(I, H, B, k_a, x.device)
-    if h_out is None:
-        h_out = torch.empty_like(h_prev)
-    if c_out is None:
-        c_out = torch.empty_like(c_prev)
-    _check(lib().amq_lstm_step(_dev(Wxp, torch.int32), _dev(alpha_x, torch.float32), _dev(Whp, torch.int32),
-                               _dev(alpha_h, torch.float32), I, H, k_w, _opt(bias), _dev(x, torch.float32),
-                               _dev(h_prev, torch.float32), _dev(c_prev, torch.float32), B, k_a, T,
-                               _dev(h_out, torch.float32), _dev(c_out, torch.float32), ws.data_ptr(),
-                               ws.numel(), _stream()))
-    return h_out, c_out
+    return (_native_module or _load_native()).lstm_step(Wxp, alpha_x, Whp, alpha_h, I, H, bias, x, h_prev, c_prev, k_a, T,
+                                                          ws, h_out, c_out)
 
 
 STATIC_SCRATCH_BYTES = 4 << 20
@@ -291,30 +267,15 @@ STATIC_SCRATCH_BYTES = 4 << 20
 def lstm_step_static(Wxp, alpha_x, Whp, alpha_h, I, H, bias, x, h_prev, c_prev, k_a, T, h_out, c_out):
     """lstm_step on the library's static scratch: the call allocates nothing, so the outputs are
     arguments too."""
-    _check(lib().amq_lstm_step_static(_dev(Wxp, torch.int32), _dev(alpha_x, torch.float32),
-                                      _dev(Whp, torch.int32), _dev(alpha_h, torch.float32), I, H, Wxp.shape[0],
-                                      _opt(bias), _dev(x, torch.float32), _dev(h_prev, torch.float32),
-                                      _dev(c_prev, torch.float32), x.shape[0], k_a, T,
-                                      _dev(h_out, torch.float32), _dev(c_out, torch.float32), _stream()))
-    return h_out, c_out
+    return (_native_module or _load_native()).lstm_step_static(Wxp, alpha_x, Whp, alpha_h, I, H, bias, x, h_prev, c_prev,
+                                                                 k_a, T, h_out, c_out)
 
 
 def lstm_step_packed(Wxp, alpha_x, Whp, alpha_h, I, H, bias, Xp, beta_x, Hp, beta_h, c_prev, h_out=None,
                      c_out=None):
     """LSTM step on operands that are already quantized (Xp [k_a, B, wpr(I)], Hp [k_a, B, wpr(H)])."""
-    k_w = Wxp.shape[0]
-    k_a, B, _ = Xp.shape
-    if h_out is None:
-        h_out = torch.empty_like(c_prev)
-    if c_out is None:
-        c_out = torch.empty_like(c_prev)
-    _check(lib().amq_lstm_step_packed(_dev(Wxp, torch.int32), _dev(alpha_x, torch.float32),
-                                      _dev(Whp, torch.int32), _dev(alpha_h, torch.float32), I, H, k_w,
-                                      _opt(bias), _dev(Xp, torch.int32), _dev(beta_x, torch.float32),
-                                      _dev(Hp, torch.int32), _dev(beta_h, torch.float32),
-                                      _dev(c_prev, torch.float32), B, k_a, _dev(h_out, torch.float32),
-                                      _dev(c_out, torch.float32), _stream()))
-    return h_out, c_out
+    return (_native_module or _load_native()).lstm_step_packed(Wxp, alpha_x, Whp, alpha_h, I, H, bias, Xp, beta_x, Hp, beta_h,
+                                                                 c_prev, h_out, c_out)
 
 
 def lstm_step_packed_grouped(Wxp, alpha_x, Whp, alpha_h, I, H, bias, Xp, beta_x, Hp, beta_h, c_prev, h_out=None,
@@ -351,17 +312,7 @@ def stream_read_probe(buf, sink=None):
 
 def lstm_sequence(Wxp, alpha_x, Whp, alpha_h, I, H, bias, xs, h, c, k_a, T, ws=None, hs=None):
     """xs [steps, B, I]; h, c [B, H] are updated in place; hs [steps, B, H] optional."""
-    k_w = Wxp.shape[0]
-    steps, B, _ = xs.shape
-    if ws is None:
-        ws = lstm_sequence_workspace(I, H, B, k_a, xs.device)
-    _check(lib().amq_lstm_sequence(_dev(Wxp, torch.int32), _dev(alpha_x, torch.float32),
-                                   _dev(Whp, torch.int32), _dev(alpha_h, torch.float32), I, H, k_w,
-                                   _opt(bias), _dev(xs, torch.float32), steps, _dev(h, torch.float32),
-                                   _dev(c, torch.float32), B, k_a, T,
-                                   None if hs is None else _dev(hs, torch.float32), ws.data_ptr(),
-                                   ws.numel(), _stream()))
-    return h, c
+    return (_native_module or _load_native()).lstm_sequence(Wxp, alpha_x, Whp, alpha_h, I, H, bias, xs, h, c, k_a, T, ws, hs)
 
 
 def gru_step_reset_before(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, x, h_prev, k_a, T, ws=None, h_out=None,
@@ -397,17 +348,8 @@ def lstm_sequence_abandoned(ws, I, H, B, k_a):
 
 
 def gru_step(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, x, h_prev, k_a, T, ws=None, h_out=None):
-    k_w = Wxp.shape[0]
-    B = x.shape[0]
-    if ws is None:
-        ws = gru_workspace(I, H, B, k_a, x.device)
-    if h_out is None:
-        h_out = torch.empty_like(h_prev)
-    _check(lib().amq_gru_step(_dev(Wxp, torch.int32), _dev(alpha_x, torch.float32), _dev(Whp, torch.int32),
-                              _dev(alpha_h, torch.float32), I, H, k_w, _opt(bias_x), _opt(bias_h),
-                              _dev(x, torch.float32), _dev(h_prev, torch.float32), B, k_a, T,
-                              _dev(h_out, torch.float32), ws.data_ptr(), ws.numel(), _stream()))
-    return h_out
+    return (_native_module or _load_native()).gru_step(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, x, h_prev, k_a, T, ws,
+                                                         h_out)
 
 
 def gru_sequence_workspace(I, H, B, k_a, device):
@@ -418,37 +360,19 @@ def gru_sequence_workspace(I, H, B, k_a, device):
 
 def gru_sequence(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, xs, h, k_a, T, ws=None, hs=None):
     """xs [steps, B, I]; h [B, H] is updated in place; hs [steps, B, H] optional."""
-    k_w = Wxp.shape[0]
-    steps, B, _ = xs.shape
-    if ws is None:
-        ws = gru_sequence_workspace(I, H, B, k_a, xs.device)
-    _check(lib().amq_gru_sequence(_dev(Wxp, torch.int32), _dev(alpha_x, torch.float32), _dev(Whp, torch.int32),
-                                  _dev(alpha_h, torch.float32), I, H, k_w, _opt(bias_x), _opt(bias_h),
-                                  _dev(xs, torch.float32), steps, _dev(h, torch.float32), B, k_a, T,
-                                  None if hs is None else _dev(hs, torch.float32), ws.data_ptr(), ws.numel(),
-                                  _stream()))
-    return h
+    return (_native_module or _load_native()).gru_sequence(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, xs, h, k_a, T, ws,
+                                                             hs)
 
 
 def embedding_lookup(Ep, alpha_e, n, ids):
     """Rows ids [B] (int64) of a quantized table Ep [k, vocab, wpr(n)], alpha_e [vocab, k] ->
     Xp [k, B, wpr(n)], beta [B, k]."""
-    k, vocab, w = Ep.shape
-    B = ids.shape[0]
-    Xp = _empty((k, B, w), torch.int32, Ep)
-    beta = _empty((B, k), torch.float32, Ep)
-    _check(lib().amq_embedding_lookup(_dev(Ep, torch.int32), _dev(alpha_e, torch.float32), vocab, n, k,
-                                      _dev(ids, torch.int64), B, Xp.data_ptr(), beta.data_ptr(), _stream()))
-    return Xp, beta
+    return (_native_module or _load_native()).embedding_lookup(Ep, alpha_e, n, ids)
 
 
 def log_softmax(Y, out=None):
     """Row-wise log-softmax of Y [B, V]; out may be Y itself."""
-    B, V = Y.shape
-    if out is None:
-        out = torch.empty_like(Y)
-    _check(lib().amq_log_softmax(_dev(Y, torch.float32), B, V, _dev(out, torch.float32), _stream()))
-    return out
+    return (_native_module or _load_native()).log_softmax(Y, out)
 
 
 def softmax_layer_workspace(V, H, B, k_a, device):
@@ -458,16 +382,7 @@ def softmax_layer_workspace(V, H, B, k_a, device):
 
 def softmax_layer(Wsp, alpha_s, H, bias, h, k_a, T, ws=None, logprob=None):
     """log softmax(W_s h + b_s) with W_s quantized (Wsp [k_w, V, wpr(H)]) and h [B, H] quantized on line."""
-    k_w, V, _ = Wsp.shape
-    B = h.shape[0]
-    if ws is None:
-        ws = softmax_layer_workspace(V, H, B, k_a, h.device)
-    if logprob is None:
-        logprob = _empty((B, V), torch.float32, h)
-    _check(lib().amq_softmax_layer(_dev(Wsp, torch.int32), _dev(alpha_s, torch.float32), V, H, k_w, _opt(bias),
-                                   _dev(h, torch.float32), B, k_a, T, _dev(logprob, torch.float32),
-                                   ws.data_ptr(), ws.numel(), _stream()))
-    return logprob
+    return (_native_module or _load_native()).softmax_layer(Wsp, alpha_s, H, bias, h, k_a, T, ws, logprob)
 
 
 def lm_workspace(E, H, V, B, k_a, k_as, device):
@@ -479,66 +394,23 @@ def lm_step(Ep, alpha_e, E, Wxp, alpha_x, Whp, alpha_h, H, bias, Wsp, alpha_s, b
             ws=None, logprob=None):
     """One language-model step: ids [B] -> embedding rows -> LSTM (h, c updated in place) -> log-probabilities
     [B, V]."""
-    vocab = Ep.shape[1]
-    k_w = Wxp.shape[0]
-    k_ws, V, _ = Wsp.shape
-    B = ids.shape[0]
-    if ws is None:
-        ws = lm_workspace(E, H, V, B, k_a, k_as, h.device)
-    if logprob is None:
-        logprob = _empty((B, V), torch.float32, h)
-    _check(lib().amq_lm_step(_dev(Ep, torch.int32), _dev(alpha_e, torch.float32), vocab, E,
-                             _dev(Wxp, torch.int32), _dev(alpha_x, torch.float32), _dev(Whp, torch.int32),
-                             _dev(alpha_h, torch.float32), H, k_w, _opt(bias), _dev(Wsp, torch.int32),
-                             _dev(alpha_s, torch.float32), V, k_ws, _opt(bias_s), _dev(ids, torch.int64),
-                             _dev(h, torch.float32), _dev(c, torch.float32), B, k_a, k_as, T,
-                             _dev(logprob, torch.float32), ws.data_ptr(), ws.numel(), _stream()))
-    return logprob
+    return (_native_module or _load_native()).lm_step(Ep, alpha_e, E, Wxp, alpha_x, Whp, alpha_h, H, bias, Wsp, alpha_s, bias_s,
+                                                        ids, h, c, k_a, k_as, T, ws, logprob)
 
 
 def lm_sequence(Ep, alpha_e, E, Wxp, alpha_x, Whp, alpha_h, H, bias, Wsp, alpha_s, bias_s, ids, h, c, k_a, k_as, T,
                 ws=None, logprob=None):
     """ids [steps, B] -> logprob [steps, B, V]; h, c [B, H] updated in place."""
-    vocab = Ep.shape[1]
-    k_w = Wxp.shape[0]
-    k_ws, V, _ = Wsp.shape
-    steps, B = ids.shape
-    if ws is None:
-        ws = torch.empty(int(lib().amq_lm_sequence_workspace_bytes(E, H, V, B, k_a, k_as)), dtype=torch.uint8,
-                         device=h.device)
-    if logprob is None:
-        logprob = _empty((steps, B, V), torch.float32, h)
-    _check(lib().amq_lm_sequence(_dev(Ep, torch.int32), _dev(alpha_e, torch.float32), vocab, E,
-                                 _dev(Wxp, torch.int32), _dev(alpha_x, torch.float32), _dev(Whp, torch.int32),
-                                 _dev(alpha_h, torch.float32), H, k_w, _opt(bias), _dev(Wsp, torch.int32),
-                                 _dev(alpha_s, torch.float32), V, k_ws, _opt(bias_s), _dev(ids, torch.int64), steps,
-                                 _dev(h, torch.float32), _dev(c, torch.float32), B, k_a, k_as, T,
-                                 _dev(logprob, torch.float32), ws.data_ptr(), ws.numel(), _stream()))
-    return logprob
+    return (_native_module or _load_native()).lm_sequence(Ep, alpha_e, E, Wxp, alpha_x, Whp, alpha_h, H, bias, Wsp, alpha_s,
+                                                            bias_s, ids, h, c, k_a, k_as, T, ws, logprob)
 
 
 def lm_sequence_score(Ep, alpha_e, E, Wxp, alpha_x, Whp, alpha_h, H, bias, Wsp, alpha_s, bias_s, ids, targets, h, c,
                       k_a, k_as, T, ws=None, out=None):
     """ids, targets [steps, B] -> log-probability of targets[t, b] at step t, [steps, B]; h, c updated in place."""
-    vocab = Ep.shape[1]
-    k_w = Wxp.shape[0]
-    k_ws, V, _ = Wsp.shape
-    steps, B = ids.shape
-    if tuple(targets.shape) != (steps, B):
-        raise AmqError("targets must have the shape of ids")
-    if ws is None:
-        ws = torch.empty(int(lib().amq_lm_sequence_score_workspace_bytes(E, H, V, B, k_a, k_as)), dtype=torch.uint8,
-                         device=h.device)
-    if out is None:
-        out = _empty((steps, B), torch.float32, h)
-    _check(lib().amq_lm_sequence_score(_dev(Ep, torch.int32), _dev(alpha_e, torch.float32), vocab, E,
-                                       _dev(Wxp, torch.int32), _dev(alpha_x, torch.float32), _dev(Whp, torch.int32),
-                                       _dev(alpha_h, torch.float32), H, k_w, _opt(bias), _dev(Wsp, torch.int32),
-                                       _dev(alpha_s, torch.float32), V, k_ws, _opt(bias_s), _dev(ids, torch.int64),
-                                       _dev(targets, torch.int64), steps, _dev(h, torch.float32),
-                                       _dev(c, torch.float32), B, k_a, k_as, T, _dev(out, torch.float32),
-                                       ws.data_ptr(), ws.numel(), _stream()))
-    return out
+    return (_native_module or _load_native()).lm_sequence_score(Ep, alpha_e, E, Wxp, alpha_x, Whp, alpha_h, H, bias, Wsp,
+                                                                  alpha_s, bias_s, ids, h, c, k_a, k_as, T, ws, out,
+                                                                  targets)
 
 
 def quantize_refined_greedy(W, k):
@@ -583,14 +455,7 @@ def relative_mse(W, planes, alpha):
 
 def dequantize(planes, alpha, cols, out=None):
     """Reconstruction [rows, cols] float32 of a row-wise quantization (planes [k, rows, wpr], alpha [rows, k])."""
-    k, rows, _ = planes.shape
-    if out is None:
-        out = _empty((rows, cols), torch.float32, planes)
-    if out.dim() != 2 or out.stride(1) != 1 or out.dtype != torch.float32 or not out.is_cuda:
-        raise AmqError("expected a 2-D float32 GPU tensor with unit column stride")
-    _check(lib().amq_dequantize(_dev(planes, torch.int32), _dev(alpha, torch.float32), rows, cols, k, out.data_ptr(),
-                                out.stride(0), _stream()))
-    return out
+    return (_native_module or _load_native()).dequantize(planes, alpha, cols, out)
 
 
 def clip_(w, lo=-1.0, hi=1.0):
@@ -599,20 +464,7 @@ def clip_(w, lo=-1.0, hi=1.0):
     return w
 
 
-class _FakeQuantize(torch.autograd.Function):
-    """w -> w_hat = sum_i alpha_i b_i (row-wise alternating quantization) with the straight-through
-    gradient of Sec. 4: d f / d w = d f / d w_hat.  Both directions are argument marshalling: the
-    forward pass is two library calls, the backward pass returns its argument."""
-
-    @staticmethod
-    def forward(ctx, W, k, T):
-        planes, alpha = quantize_weights(W.detach().contiguous(), k, T)
-        return dequantize(planes, alpha, W.shape[1])
-
-    @staticmethod
-    def backward(ctx, grad):
-        return grad, None, None
-
-
 def fake_quantize(W, k, T=2):
-    return _FakeQuantize.apply(W, k, T)
+    """w -> w_hat = sum_i alpha_i b_i (row-wise alternating quantization), differentiable with the straight-through
+    gradient of Sec. 4: d f / d w = d f / d w_hat."""
+    return (_native_module or _load_native()).fake_quantize(W, k, T)
