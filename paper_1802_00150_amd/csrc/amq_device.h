@@ -67,7 +67,7 @@ __device__ __forceinline__ float group_sum(float v, int lg) {
   return v;
 }
 
-// ---- operands of the fp4 matrix-core kernels (v_mfma_scale_f32_16x16x128_f8f6f4, E2M1 codes) ----
+// ---- operands of the fp4 matrix-core kernels (v_mfma_f32_16x16x128_f8f6f4, E2M1 codes) ----
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 
@@ -82,7 +82,6 @@ constexpr int kTileB = 16;                         // batch entries per tile
 constexpr int kSteps = 8;                          // 1024 entries / 128 per matrix instruction
 constexpr int kPlaneBytes = kSteps * kTileB * 64;  // one plane of one tile in LDS: [step][batch entry][k-block][16 B]
 constexpr unsigned kNib = 0x22222222u;
-constexpr int kScaleOne = 0x7f7f7f7f;              // E8M0 exponent 127 = 2^0 in every byte
 
 // {0, 1} codes: bit p of a packed word -> nibble 0b0010 (1.0 in E2M1) or 0; nibble q of dword s is
 // bit 4q + s (a fixed permutation of the 32 entries, the same for both operands of a product).
@@ -109,6 +108,13 @@ __device__ __forceinline__ uint4 expand4_signed_valid(uint32_t w, uint32_t valid
 __device__ __forceinline__ v8i as_operand(uint4 e) {
   const v4i lo = {(int)e.x, (int)e.y, (int)e.z, (int)e.w};
   return __builtin_shufflevector(lo, lo, 0, 1, 2, 3, -1, -1, -1, -1);
+}
+// The matrix instruction on fp4 operands, without block scales: the builtin with scale operands 0 selects the unscaled
+// form.  (Measured with one and more waves per SIMD: it occupies the issue port for 8 cycles and the matrix cores for
+// 16, so two vector instructions hide behind each; the scaled form with all scales 1 takes 12 cycles of issue and
+// hides one.)
+__device__ __forceinline__ v4f mfma_fp4(uint4 a, uint4 b, v4f c) {
+  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(as_operand(a), as_operand(b), c, 4, 4, 0, 0, 0, 0);
 }
 __device__ __forceinline__ uint32_t word_of(const uint4 (&q)[2], int t) {
   const uint4 v = q[t >> 2];

@@ -3,7 +3,7 @@
 //
 // Why fp4: the contraction only ever multiplies codes, and with both operands written as
 // {0, 1} every product and every partial sum (< 2^24) is exact in the E2M1 x E2M1 -> fp32
-// MFMA.  v_mfma_scale_f32_16x16x128_f8f6f4 in fp4 mode takes 128 entries of K per instruction
+// MFMA.  v_mfma_f32_16x16x128_f8f6f4 in fp4 mode takes 128 entries of K per instruction
 // from 16-byte operands and issues every ~19 cycles on this chip, against ~32 cycles for the
 // int8 instruction with 64 entries of K (both measured), i.e. 3.3x the rate per entry.  The
 // +-1 inner product is recovered from popcounts:
@@ -267,8 +267,7 @@ __global__ __launch_bounds__(64 * NWV) void mfma4_kernel(BmvArgs a, int rb_per_w
       for (int i = 0; i < KW; ++i)
 #pragma unroll
         for (int j = 0; j < KA; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(as_operand(aop[i]), as_operand(bop[j]), acc[i][j],
-                                                                       4, 4, 0, kScaleOne, 0, kScaleOne);
+          acc[i][j] = mfma_fp4(aop[i], bop[j], acc[i][j]);
       // issue order inside a step: the LDS reads of the next step first, then every MFMA
       // followed by up to three of the VALU instructions that expand the next step's weights
       __builtin_amdgcn_sched_group_barrier(0x100, KA, 0);

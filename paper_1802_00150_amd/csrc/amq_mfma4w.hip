@@ -3,7 +3,7 @@
 // and the recurrent steps for batches of 128 and more (mfma4wc_kernel, further down).
 //
 // Same matrix instruction as the kernel in amq_mfma4.hip (codes as E2M1 nibbles,
-// v_mfma_scale_f32_16x16x128_f8f6f4), different work split.  There a wave owns one 16 x 16 output tile
+// v_mfma_f32_16x16x128_f8f6f4), different work split.  There a wave owns one 16 x 16 output tile
 // per pass, and per pass it spends about 350 vector instructions (1400 cycles) on addressing, expanding
 // the weight words, popcounts and the coefficient epilogue against k_w k_a 8 matrix instructions (900
 // cycles at W2/A3): the vector unit, not the matrix core, bounds it.  Here a wave owns 16 rows x NBT batch
@@ -64,8 +64,7 @@ __device__ __forceinline__ void contract_tiles(const uint4 (&araw)[KW][2], const
     for (int i = 0; i < KW; ++i)
 #pragma unroll
       for (int j = 0; j < KA; ++j)
-        acc[bt][i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(as_operand(aop[i]), as_operand(bop[j]),
-                                                                         acc[bt][i][j], 4, 4, 0, kScaleOne, 0, kScaleOne);
+        acc[bt][i][j] = mfma_fp4(aop[i], bop[j], acc[bt][i][j]);
     __builtin_amdgcn_sched_group_barrier(0x100, KA, 0);
 #pragma unroll
     for (int g = 0; g < KW * KA; ++g) {

@@ -268,8 +268,7 @@ __device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int b
       for (int i = 0; i < KW; ++i)
 #pragma unroll
         for (int j = 0; j < KA; ++j)
-          acc[bt][i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(as_operand(aop[i]), as_operand(bop[bt][j]),
-                                                                           acc[bt][i][j], 4, 4, 0, kScaleOne, 0, kScaleOne);
+          acc[bt][i][j] = mfma_fp4(aop[i], bop[bt][j], acc[bt][i][j]);
     __builtin_amdgcn_sched_barrier(0);
     if (t == 0) {
       // under the contraction: here they return before the epilogue and delay no operand request
