@@ -190,10 +190,6 @@ hipError_t launch_matrix_core(const amq::BmvArgs& b, int k_w, int k_a, int epi, 
     if (lse_slots) *lse_slots = 0;
     return amq::launch_mfma4w_cell(b, k_w, k_a, epi, s);
   }
-  if (epi != amq::kEpiStore && amq::mfma4_pair_supported(b, k_w, k_a, epi)) {
-    if (lse_slots) *lse_slots = 0;
-    return amq::launch_mfma4_pair(b, k_w, k_a, epi, s);
-  }
   if (amq::mfma4_supported(b, k_w, epi)) return amq::launch_mfma4(b, k_w, k_a, epi, s, lse_slots);
   if (lse_slots) *lse_slots = 0;
   return amq::launch_mfma(b, k_w, k_a, epi, s);
@@ -377,6 +373,8 @@ static int lstm_fused_launch(const uint32_t* Wxp, const float* alpha_x, const ui
                              float* hs_out, hipStream_t s) {
   const amq::BmvArgs b = lstm_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias, Xp, beta_x, Hp, beta_h, c_prev, B, h_out,
                                    c_out, hs_out);
+  if (amq::mfma4_pair_supported(b, k_w, k_a, amq::kEpiLstm))
+    return hip_status(amq::launch_mfma4_pair(b, k_w, k_a, amq::kEpiLstm, s));
   if (amq::bmv_supported((int)I, (int)H, k_a, B, amq::kEpiLstm))
     return hip_status(amq::launch_bmv(b, k_w, k_a, amq::kEpiLstm, s));
   if (amq::mfma_supported(B))
@@ -641,6 +639,8 @@ static int gru_step_launch(const uint32_t* Wxp, const float* alpha_x, const uint
   if (st != AMQ_OK) return st;
   const amq::BmvArgs b = gru_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, w.xp, w.beta_x, w.hp, w.beta_h,
                                   h_prev, B, h_out);
+  if (amq::mfma4_pair_supported(b, k_w, k_a, amq::kEpiGru))
+    return hip_status(amq::launch_mfma4_pair(b, k_w, k_a, amq::kEpiGru, s));
   if (amq::bmv_supported((int)I, (int)H, k_a, B, amq::kEpiGru))
     return hip_status(amq::launch_bmv(b, k_w, k_a, amq::kEpiGru, s));
   if (amq::mfma_supported(B)) return hip_status(launch_matrix_core(b, k_w, k_a, amq::kEpiGru, s));

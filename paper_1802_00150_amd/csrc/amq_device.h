@@ -116,6 +116,16 @@ __device__ __forceinline__ v8i as_operand(uint4 e) {
 __device__ __forceinline__ v4f mfma_fp4(uint4 a, uint4 b, v4f c) {
   return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(as_operand(a), as_operand(b), c, 4, 4, 0, 0, 0, 0);
 }
+// After the last matrix instruction of a contraction and before its accumulators are named in an asm statement: the
+// compiler counts the wait states between a matrix instruction and the first vector instruction that reads its result
+// (11 for a 16 x 16 form, 19 for the 32 x 32 form), but not through the asm statement, so they are spent here.
+template <int TILE>
+__device__ __forceinline__ void settle_accumulators() {
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (TILE == 16) asm volatile("s_nop 11");
+  else asm volatile("s_nop 15\n\ts_nop 3");
+  __builtin_amdgcn_sched_barrier(0);
+}
 __device__ __forceinline__ uint32_t word_of(const uint4 (&q)[2], int t) {
   const uint4 v = q[t >> 2];
   return (t & 3) == 0 ? v.x : (t & 3) == 1 ? v.y : (t & 3) == 2 ? v.z : v.w;

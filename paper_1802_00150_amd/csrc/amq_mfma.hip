@@ -220,6 +220,7 @@ __global__ __launch_bounds__(256) void mfma_kernel(BmvArgs a) {
 
     // MFMAs read all 64 lanes; keep them (and the code feeding them) out of the divergent
     // branches of the epilogue by pinning the accumulators in uniform control flow.
+    settle_accumulators<16>();
 #pragma unroll
     for (int i = 0; i < KW; ++i)
 #pragma unroll

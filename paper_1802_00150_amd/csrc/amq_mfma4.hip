@@ -286,6 +286,7 @@ __global__ __launch_bounds__(64 * NWV) void mfma4_kernel(BmvArgs a, int rb_per_w
     // and would sink it (and the VALU code producing its operands) into the divergent branch
     // that guards the final stores, where lanes of padded batch columns -- which still supply
     // weight rows -- are masked off.  Pin the accumulators here, in uniform control flow.
+    settle_accumulators<16>();
 #pragma unroll
     for (int i = 0; i < KW; ++i)
 #pragma unroll

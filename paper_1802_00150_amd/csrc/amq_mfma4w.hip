@@ -83,6 +83,7 @@ __device__ __forceinline__ void contract_tiles(const uint4 (&araw)[KW][2], const
   // would sink it into the divergent branches that guard the stores of the epilogues, where lanes
   // of padded batch columns -- which still supply weight rows -- are masked off.  Pin the
   // accumulators here, in uniform control flow.
+  settle_accumulators<16>();
 #pragma unroll
   for (int bt = 0; bt < NBT; ++bt)
 #pragma unroll
@@ -525,7 +526,7 @@ __global__ __launch_bounds__(64 * NWV) void mfma4wc_kernel(BmvArgs a, int rb_per
 
 // The recurrent steps when there are too few row-block x batch-tile tasks to give every SIMD more than
 // one wave: one workgroup of pair_body per (row-block group, batch group).
-template <int KW, int KA, int NBT, int EPI, int NWV>
+template <int KW, int KA, int NBT, int EPI, int NWV, int NC>
 __global__ __launch_bounds__(64 * NWV) void mfma4p_kernel(BmvArgs a, int rowblocks) {
   __shared__ float4 xch[(NWV / 2) * NBT * 64];  // [pair][tile][lane]: the h-side sums on their way to the x wave
   extern __shared__ __attribute__((aligned(16))) uint4 turn[];
@@ -534,7 +535,7 @@ __global__ __launch_bounds__(64 * NWV) void mfma4p_kernel(BmvArgs a, int rowbloc
                AMQ_ARG(a.blk[1].beta), AMQ_ARG(a.blk[1].n), AMQ_ARG(a.m), AMQ_ARG(a.H), AMQ_ARG(a.batch), AMQ_ARG(a.bias0),
                AMQ_ARG(a.bias1), AMQ_ARG(a.c_prev), AMQ_ARG(a.h_prev), AMQ_ARG(a.h_out), AMQ_ARG(a.c_out),
                AMQ_ARG(a.hs_out), AMQ_ARG(rowblocks));
-  pair_body<KW, KA, NBT, EPI, NWV>(a, rowblocks, blockIdx.x, blockIdx.y, turn, xch);
+  pair_body<KW, KA, NBT, EPI, NWV, kPairBoth, NC>(a, rowblocks, blockIdx.x, blockIdx.y, turn, xch);
 }
 
 // Tiles per wave: as many as keep the accumulators within about 100 registers.
@@ -687,7 +688,7 @@ hipError_t launch_cell_kw(const BmvArgs& a, int k_w, int k_a, int nbt, hipStream
 // workgroups of 8 waves 12.4 us; two tiles per wave in workgroups of 4 (one wave per SIMD, weights
 // fetched half as often, activation operands shared by two row blocks instead of four) 13.0 us; two
 // tiles, 8 waves (half the compute units) 14.3 us.
-template <int KW, int KA, int EPI>
+template <int KW, int KA, int EPI, int NC>
 hipError_t launch_pair_one(const BmvArgs& a, hipStream_t s) {
   if constexpr (KW > 3 || KW * KA > 9) {
     return hipErrorInvalidValue;
@@ -698,25 +699,30 @@ hipError_t launch_pair_one(const BmvArgs& a, hipStream_t s) {
     dim3 grid((unsigned)((rowblocks + NWV / 2 - 1) / (NWV / 2)), (unsigned)groups);
     BmvArgs b = a;
     AMQ_PHASE_ATTACH(b);
-    constexpr size_t lds = pair_body_lds<KW, KA, NBT, NWV>();
+    constexpr size_t lds = pair_body_lds<KW, KA, NBT, NWV, kPairBoth, NC>();
     static std::atomic<unsigned long long> configured{0};
     {
-      hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&mfma4p_kernel<KW, KA, NBT, EPI, NWV>), (int)lds,
+      hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&mfma4p_kernel<KW, KA, NBT, EPI, NWV, NC>), (int)lds,
                                         configured);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((mfma4p_kernel<KW, KA, NBT, EPI, NWV>), grid, dim3(64 * NWV), lds, s, b, rowblocks);
+    hipLaunchKernelGGL((mfma4p_kernel<KW, KA, NBT, EPI, NWV, NC>), grid, dim3(64 * NWV), lds, s, b, rowblocks);
     return hipGetLastError();
   }
+}
+
+template <int KW, int KA, int EPI>
+hipError_t launch_pair_nc(const BmvArgs& a, hipStream_t s) {
+  return a.blk[0].n > 1024 || a.blk[1].n > 1024 ? launch_pair_one<KW, KA, EPI, 2>(a, s) : launch_pair_one<KW, KA, EPI, 1>(a, s);
 }
 
 template <int KW, int EPI>
 hipError_t launch_pair_ka(const BmvArgs& a, int k_a, hipStream_t s) {
   switch (k_a) {
-    case 1: return launch_pair_one<KW, 1, EPI>(a, s);
-    case 2: return launch_pair_one<KW, 2, EPI>(a, s);
-    case 3: return launch_pair_one<KW, 3, EPI>(a, s);
-    case 4: return launch_pair_one<KW, 4, EPI>(a, s);
+    case 1: return launch_pair_nc<KW, 1, EPI>(a, s);
+    case 2: return launch_pair_nc<KW, 2, EPI>(a, s);
+    case 3: return launch_pair_nc<KW, 3, EPI>(a, s);
+    case 4: return launch_pair_nc<KW, 4, EPI>(a, s);
   }
   return hipErrorInvalidValue;
 }
@@ -733,18 +739,21 @@ hipError_t launch_pair_kw(const BmvArgs& a, int k_w, int k_a, hipStream_t s) {
 
 }  // namespace
 
-// Recurrent steps with vectors of at most 1024 entries, two or more batch tiles, and at most two
-// row-block x tile tasks per SIMD of the chip (beyond that the several-tiles cell kernel takes over;
-// a single tile stays with the paired form of the one-tile kernel).
+// Recurrent steps at batch 2 and more with vectors of at most 2048 entries.  Where the several-tiles cell kernel
+// applies (at most 1024 entries), up to two row-block x tile tasks per SIMD of the chip.
 bool mfma4_pair_supported(const BmvArgs& a, int k_w, int k_a, int epi) {
   if (epi != kEpiLstm && epi != kEpiGru) return false;
-  if (a.blk[0].n > 1024 || a.blk[1].n > 1024) return false;
+  const long long nmax = a.blk[0].n > a.blk[1].n ? a.blk[0].n : a.blk[1].n;
+  if (nmax > 2048) return false;
   if (k_w > 3 || k_w * k_a > 9) return false;
   const long long tiles = (a.batch + kTileB - 1) / kTileB;
   const long long rowblocks = (a.H + 3) / 4;
-  if (tiles < 2 || rowblocks * tiles > 2048) return false;
-  if (a.m * 8 * k_w >= (1LL << 31)) return false;  // weight offsets in 16-byte units
-  if ((long long)a.batch * a.H >= (1LL << 31)) return false;
+  if (a.batch < 2 || tiles > 65535) return false;
+  if (nmax <= 1024 && rowblocks * tiles > 2048) return false;
+  const long long pieces = (nmax + 127) / 128;
+  if (a.m * pieces * k_w >= (1LL << 28)) return false;  // byte offsets within a plane in 32 bits
+  if (a.batch * pieces >= (1LL << 28)) return false;
+  if ((long long)a.batch * a.H >= (1LL << 29)) return false;
   return true;
 }
 

@@ -45,9 +45,9 @@ enum { kPairBoth = 0, kPairXOnly = 1, kPairHOnly = 2 };
 
 // Dynamic LDS of the body: activation operand images [block][tile][plane][k-step][64 lanes] x 16 B, then
 // one padded 16-row tile per wave.
-template <int KW, int KA, int NBT, int NWV, int MODE = kPairBoth>
+template <int KW, int KA, int NBT, int NWV, int MODE = kPairBoth, int NC = 1>
 constexpr size_t pair_body_lds() {
-  return sizeof(uint4) * ((MODE == kPairBoth ? 2 : 1) * NBT * KA * kSteps * 64 + NWV * kTileB * kTurnStride);
+  return sizeof(uint4) * ((MODE == kPairBoth ? 2 : 1) * NBT * KA * NC * kSteps * 64 + NWV * kTileB * kTurnStride);
 }
 // Row blocks (of 4 hidden units) per workgroup.
 template <int NWV, int MODE>
@@ -55,9 +55,12 @@ constexpr int pair_body_rowblocks() {
   return MODE == kPairBoth ? NWV / 2 : NWV;
 }
 
+// NC: stretches of 1024 entries that the longer operand block takes (1 or 2); a stretch is two halves of 512 entries
+// (4 k-steps each), and a wave skips the halves that lie past the end of its own block.
+//
 // bx, by: row-block group and batch group of this workgroup.  turn: pair_body_lds() bytes of LDS, 16-byte
 // aligned.  xch (kPairBoth only): (NWV / 2) * NBT * 64 float4 of LDS.
-template <int KW, int KA, int NBT, int EPI, int NWV, int MODE = kPairBoth>
+template <int KW, int KA, int NBT, int EPI, int NWV, int MODE = kPairBoth, int NC = 1>
 __device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int bx, int by, uint4* turn, float4* xch) {
   static_assert(EPI == kEpiLstm || EPI == kEpiGru, "cell modes only");
   constexpr int NG = (EPI == kEpiGru) ? 3 : 4;
@@ -92,10 +95,10 @@ __device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int b
   // pieces past the end of a short row are fetched from piece 0 and masked to zero bits.
   //
   // Activation words, shared by the workgroup: both operand blocks' tiles are kShareReq requests of 1 KiB
-  // (block, tile, plane, half: batch columns 8v .. 8v + 7 of the tile, lane -> column lane / 8, piece
-  // lane % 8); wave w issues requests w, w + NWV, ...  A wave whose share is one request short repeats
+  // (block, tile, plane, stretch, half: batch columns 8v .. 8v + 7 of the tile, lane -> column lane / 8, piece
+  // lane % 8 of the stretch); wave w issues requests w, w + NWV, ...  A wave whose share is one request short repeats
   // the last one: same bytes to the same place.
-  constexpr int kShareReq = NBLK * NBT * KA * 2;
+  constexpr int kShareReq = NBLK * NBT * KA * NC * 2;
   constexpr int kSharePer = (kShareReq + NWV - 1) / NWV;
   uint4 bshare[kSharePer];
   uint32_t bshare_keep[kSharePer];  // all ones, or zero for a lane past the end of a short row
@@ -104,23 +107,23 @@ __device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int b
     for (int q = 0; q < kSharePer; ++q) {
       int idx = wv + q * NWV;  // (uniform)
       idx = idx < kShareReq ? idx : kShareReq - 1;
-      const int v = idx & 1, j = (idx >> 1) % KA, bt = (idx >> 1) / KA % NBT;
-      const int k2 = MODE == kPairBoth ? idx / (2 * KA * NBT) : kb;
+      const int v = idx & 1, ch = (idx >> 1) % NC, j = (idx >> 1) / NC % KA, bt = (idx >> 1) / (NC * KA) % NBT;
+      const int k2 = MODE == kPairBoth ? idx / (2 * NC * KA * NBT) : kb;
       const int n2 = k2 ? a.blk[1].n : a.blk[0].n;
       const int wq2 = (n2 + 127) >> 7;
       const char* Xb = reinterpret_cast<const char*>(k2 ? a.blk[1].Xp : a.blk[0].Xp);
       int col = bg0 + bt * kTileB + 8 * v + (lane >> 3);
       col = col < batch ? col : batch - 1;
-      bshare_keep[q] = ld_piece < wq2 ? 0xffffffffu : 0u;
-      const unsigned off = (unsigned)(col * wq2 + (ld_piece < wq2 ? ld_piece : 0)) * 16u;
+      const int piece = 8 * ch + ld_piece;
+      bshare_keep[q] = piece < wq2 ? 0xffffffffu : 0u;
+      const unsigned off = (unsigned)(col * wq2 + (piece < wq2 ? piece : 0)) * 16u;
       bshare[q] = *reinterpret_cast<const uint4*>(Xb + (size_t)j * batch * wq2 * 16 + off);
     }
   };
   // Weight words, private to the wave: request v of plane i covers gates 2v and 2v + 1 of the row
   // block's 4 units, 512 contiguous bytes each (lane -> gate 2v + lane / 32, unit (lane / 8) % 4, piece
   // lane % 8).
-  uint4 araw[KW][2];
-  const uint32_t a_keep = ld_piece < wq ? 0xffffffffu : 0u;
+  uint4 araw[NC][KW][2];
   auto request_weights = [&]() {
     int unit = rb * 4 + ((lane >> 3) & 3);
     unit = unit < H ? unit : H - 1;
@@ -130,9 +133,13 @@ __device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int b
     for (int v = 0; v < 2; ++v) {
       int gate_row = 2 * v + (lane >> 5);
       gate_row = gate_row < NG ? gate_row : NG - 1;
-      const unsigned aoff = (unsigned)((gate_row * H + unit) * wq + (ld_piece < wq ? ld_piece : 0)) * 16u;
 #pragma unroll
-      for (int i = 0; i < KW; ++i) araw[i][v] = *reinterpret_cast<const uint4*>(Wb + i * wplane + aoff);
+      for (int ch = 0; ch < NC; ++ch) {
+        const int piece = 8 * ch + ld_piece;
+        const unsigned aoff = (unsigned)((gate_row * H + unit) * wq + (piece < wq ? piece : 0)) * 16u;
+#pragma unroll
+        for (int i = 0; i < KW; ++i) araw[ch][i][v] = *reinterpret_cast<const uint4*>(Wb + i * wplane + aoff);
+      }
     }
   };
   // The small operands of the epilogue: scattered 4-byte loads, each of which holds up the memory pipe
@@ -182,25 +189,30 @@ __device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int b
     }
   };
 
-  uint4* const image = turn;  // [block][tile][plane][k-step][64]
+  uint4* const image = turn;  // [block][tile][plane][stretch][k-step][64]
   uint4* const mine = turn + kShareReq / 2 * kSteps * 64 + wv * (kTileB * kTurnStride);
   // Weights: rows -> operand layout through this wave's private piece of LDS, plane after plane; tile row
   // l16 = 4 * unit + gate, lane (l16, l4) takes pieces l4 and l4 + 4.
   auto turn_weights = [&]() {
     const int row = 4 * ((lane >> 3) & 3) + (lane >> 5);
 #pragma unroll
-    for (int i = 0; i < KW; ++i) {
+    for (int ch = 0; ch < NC; ++ch) {
+      const uint32_t keep = 8 * ch + ld_piece < wq ? 0xffffffffu : 0u;
 #pragma unroll
-      for (int v = 0; v < 2; ++v)
-        mine[(row + 2 * v) * kTurnStride + ld_piece] =
-            make_uint4(araw[i][v].x & a_keep, araw[i][v].y & a_keep, araw[i][v].z & a_keep, araw[i][v].w & a_keep);
+      for (int i = 0; i < KW; ++i) {
+        uint4(&w)[2] = araw[ch][i];
 #pragma unroll
-      for (int v = 0; v < 2; ++v) araw[i][v] = mine[l16 * kTurnStride + l4 + 4 * v];
+        for (int v = 0; v < 2; ++v)
+          mine[(row + 2 * v) * kTurnStride + ld_piece] =
+              make_uint4(w[v].x & keep, w[v].y & keep, w[v].z & keep, w[v].w & keep);
+#pragma unroll
+        for (int v = 0; v < 2; ++v) w[v] = mine[l16 * kTurnStride + l4 + 4 * v];
+      }
     }
   };
   // Activations: the lane that fetched piece p of batch column c expands its four words to {-1, +1}
-  // codes and puts each where the matrix instruction wants it: the image of (block, tile, plane, k-step
-  // t) is 64 lanes x 16 bytes, and lane (column c, k-block b) of step t uses word t % 4 of piece b +
+  // codes and puts each where the matrix instruction wants it: the image of (block, tile, plane, stretch,
+  // k-step t) is 64 lanes x 16 bytes, and lane (column c, k-block b) of step t uses word t % 4 of piece b +
   // 4 * (t / 4).  The column index is xor-ed with a value that depends on (b, t / 4), which makes both
   // these writes and the reads of the contraction conflict-free.
   auto expand_activations = [&]() {
@@ -229,9 +241,10 @@ __device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int b
   turn_weights();
   AMQ_PHASE_WHEN(bx == 0 && by == 0, AMQ_PHASE_OF(a), 8, 4);
   // this lane's operand of (tile, plane, k-step)
-  const uint4* const myimage = image + (MODE == kPairBoth ? kb : 0) * (NBT * KA * kSteps * 64) + 16 * l4;
+  constexpr int kAllSteps = NC * kSteps;
+  const uint4* const myimage = image + (MODE == kPairBoth ? kb : 0) * (NBT * KA * kAllSteps * 64) + 16 * l4;
   auto b_operand = [&](int bt, int j, int t) {
-    return myimage[((bt * KA + j) * kSteps + t) * 64 + (l16 ^ ((l4 << 1) | ((t >> 2) << 3)))];
+    return myimage[((bt * KA + j) * kAllSteps + t) * 64 + (l16 ^ ((l4 << 1) | (((t >> 2) & 1) << 3)))];
   };
 
   // ---- contraction: k-step t multiplies the t-th words of this lane's k-block; the operands of step
@@ -249,44 +262,50 @@ __device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int b
 #pragma unroll
     for (int j = 0; j < KA; ++j) bop[bt][j] = b_operand(bt, j, 0);
 #pragma unroll
-  for (int i = 0; i < KW; ++i) aop[i] = expand4_signed(word_of(araw[i], 0));
+  for (int i = 0; i < KW; ++i) aop[i] = expand4_signed(word_of(araw[0][i], 0));
   AMQ_PHASE_WHEN(bx == 0 && by == 0, AMQ_PHASE_OF(a), 8, 10);
   __builtin_amdgcn_sched_barrier(0);
+  const int halves = (wq + 3) >> 2;  // stretches of 512 entries (4 k-steps) of this wave's block
 #pragma unroll
-  for (int t = 0; t < kSteps; ++t) {
-    if (t + 1 < kSteps) {
+  for (int half = 0; half < 2 * NC; ++half) {
+    if (half > 0 && half >= halves) break;  // (uniform)
+#pragma unroll
+    for (int t = 4 * half; t < 4 * half + 4; ++t) {
+      if (t + 1 < kAllSteps) {
+#pragma unroll
+        for (int bt = 0; bt < NBT; ++bt)
+#pragma unroll
+          for (int j = 0; j < KA; ++j) bnx[bt][j] = b_operand(bt, j, t + 1);
+#pragma unroll
+        for (int i = 0; i < KW; ++i) anx[i] = expand4_signed(word_of(araw[(t + 1) / kSteps][i], (t + 1) % kSteps));
+      }
 #pragma unroll
       for (int bt = 0; bt < NBT; ++bt)
 #pragma unroll
-        for (int j = 0; j < KA; ++j) bnx[bt][j] = b_operand(bt, j, t + 1);
+        for (int i = 0; i < KW; ++i)
 #pragma unroll
-      for (int i = 0; i < KW; ++i) anx[i] = expand4_signed(word_of(araw[i], t + 1));
-    }
-#pragma unroll
-    for (int bt = 0; bt < NBT; ++bt)
-#pragma unroll
-      for (int i = 0; i < KW; ++i)
-#pragma unroll
-        for (int j = 0; j < KA; ++j)
-          acc[bt][i][j] = mfma_fp4(aop[i], bop[bt][j], acc[bt][i][j]);
-    __builtin_amdgcn_sched_barrier(0);
-    if (t == 0) {
-      // under the contraction: here they return before the epilogue and delay no operand request
-      request_column_coefficients();
-      request_row_operands();
+          for (int j = 0; j < KA; ++j)
+            acc[bt][i][j] = mfma_fp4(aop[i], bop[bt][j], acc[bt][i][j]);
       __builtin_amdgcn_sched_barrier(0);
+      if (t == 0) {
+        // under the contraction: here they return before the epilogue and delay no operand request
+        request_column_coefficients();
+        request_row_operands();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int i = 0; i < KW; ++i) aop[i] = anx[i];
+#pragma unroll
+      for (int bt = 0; bt < NBT; ++bt)
+#pragma unroll
+        for (int j = 0; j < KA; ++j) bop[bt][j] = bnx[bt][j];
     }
-#pragma unroll
-    for (int i = 0; i < KW; ++i) aop[i] = anx[i];
-#pragma unroll
-    for (int bt = 0; bt < NBT; ++bt)
-#pragma unroll
-      for (int j = 0; j < KA; ++j) bop[bt][j] = bnx[bt][j];
   }
   // An MFMA reads its operands from all 64 lanes, but the compiler treats it as lane-local and
   // would sink it into the divergent branches that guard the stores of the epilogue, where lanes of
   // padded batch columns -- which still supply weight rows -- are masked off.  Pin the accumulators
   // here, in uniform control flow.
+  settle_accumulators<16>();
 #pragma unroll
   for (int bt = 0; bt < NBT; ++bt)
 #pragma unroll
@@ -295,7 +314,7 @@ __device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int b
       for (int j = 0; j < KA; ++j) asm volatile("" : "+v"(acc[bt][i][j]));
   AMQ_PHASE_WHEN(bx == 0 && by == 0, AMQ_PHASE_OF(a), 8, 5);
 
-  // ---- epilogue: d_ij = acc_ij - (1024 - n) are the dot products of the codes (integers, exact in
+  // ---- epilogue: d_ij = acc_ij - (contracted positions - n) are the dot products of the codes (integers, exact in
   // binary32); y = sum_i alpha_i sum_j beta_j d_ij
   float btv[NBT][KA];
 #pragma unroll
@@ -307,7 +326,7 @@ __device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int b
   for (int r = 0; r < 4; ++r)
 #pragma unroll
     for (int i = 0; i < KW; ++i) alr[r][i] = __shfl(alpha_req, 16 * l4 + r * KW + i, kWave);
-  const float pad = (float)(kSteps * 128 - nlen);
+  const float pad = (float)(halves * 512 - nlen);
   float ysum[NBT][4];
 #pragma unroll
   for (int bt = 0; bt < NBT; ++bt)

@@ -626,3 +626,39 @@ def test_config4_gru_batch256_with_projection(amq):
     if first_free_mismatch is not None:   # a trajectory may only part from the oracle's through moved codes
         assert first_free_mismatch[1] > 0
     assert flips_total <= 4
+
+
+@pytest.mark.parametrize("I,H,B,k_w,k_a,steps", [(1030, 520, 2, 2, 2, 3), (300, 1500, 20, 2, 3, 3), (2048, 2048, 3, 3, 3, 2),
+                                                 (1537, 130, 33, 3, 2, 3), (650, 650, 13, 2, 2, 4), (40, 1025, 16, 2, 2, 2)])
+def test_sequences_of_long_vectors_and_single_tiles(amq, I, H, B, k_w, k_a, steps):
+    # operand blocks of one to four stretches of 512 entries on paired waves, unequal blocks, a single batch tile: LSTM
+    # and GRU sequences against the oracle, and against the per-step calls exactly
+    import torch
+    g = np.random.default_rng(I + 3 * H + B)
+    for gates in (4, 3):
+        say("long vectors I=%d H=%d B=%d W%d/A%d gates=%d" % (I, H, B, k_w, k_a, gates))
+        Wx = (g.standard_normal((gates * H, I)) * 0.05).astype(np.float32)
+        Wh = (g.standard_normal((gates * H, H)) * 0.05).astype(np.float32)
+        xs = g.standard_normal((steps, B, I)).astype(np.float32)
+        h0 = np.tanh(g.standard_normal((B, H))).astype(np.float32)
+        c0 = g.standard_normal((B, H)).astype(np.float32)
+        Wxp, ax = quantized(Wx, k_w)
+        Whp, ah = quantized(Wh, k_w)
+        d = [to_dev(t) for t in (Wxp, ax, Whp, ah)]
+        dx, dh, dc = to_dev(xs), to_dev(h0), to_dev(c0)
+        hs = torch.empty((steps, B, H), device=dh.device)
+        ph, pc = dh.clone(), dc.clone()
+        if gates == 4:
+            amq.lstm_sequence(*d, I, H, None, dx, dh, dc, k_a, 2, hs=hs)
+            h1, _ = oracle.lstm_step(Wxp, ax, Whp, ah, I, H, None, xs[0], h0, c0, k_a, 2)
+        else:
+            amq.gru_sequence(*d, I, H, None, None, dx, dh, k_a, 2, hs=hs)
+            h1 = oracle.gru_step(Wxp, ax, Whp, ah, I, H, None, None, xs[0], h0, k_a, 2)
+        assert_vec_close(host(hs)[0], h1, "h_1")
+        for t in range(steps):
+            if gates == 4:
+                ph, pc = amq.lstm_step(*d, I, H, None, dx[t], ph, pc, k_a, 2)
+            else:
+                ph = amq.gru_step(*d, I, H, None, None, dx[t], ph, k_a, 2)
+            assert torch.equal(ph, hs[t])
+        assert torch.equal(dh, hs[-1])
