@@ -184,6 +184,8 @@ amq::GemmArgs gemm_args(const uint32_t* Wp, const float* alpha, int64_t m, int64
 // form for large plain products), int8 kernel otherwise.
 hipError_t launch_matrix_core(const amq::BmvArgs& b, int k_w, int k_a, int epi, hipStream_t s,
                               int* lse_slots = nullptr) {
+  if (epi == amq::kEpiStore && amq::mfma32_supported(b, k_w, k_a))
+    return amq::launch_mfma32(b, k_w, k_a, s, lse_slots);
   if (epi == amq::kEpiStore && amq::mfma4w_supported(b, k_w, k_a))
     return amq::launch_mfma4w(b, k_w, k_a, s, lse_slots);
   if (epi != amq::kEpiStore && amq::mfma4w_cell_supported(b, k_w, k_a, epi)) {
@@ -219,6 +221,8 @@ amq::BmvArgs store_args(const amq::GemmArgs& g) {
 // in g.lse_part, or 0 if the kernel that ran does not produce them.
 int run_product(const amq::GemmArgs& g, hipStream_t s, int* lse_slots = nullptr) {
   if (lse_slots) *lse_slots = 0;
+  if (!g.D && g.op.n > 1024 && amq::mfma32_supported(store_args(g), g.k_w, g.k_a))
+    return hip_status(amq::launch_mfma32(store_args(g), g.k_w, g.k_a, s, lse_slots));
   if (!g.D && amq::bmv_supported(g.op.n, 0, g.k_a, g.batch, amq::kEpiStore))
     return hip_status(amq::launch_bmv(store_args(g), g.k_w, g.k_a, amq::kEpiStore, s, lse_slots));
   if (g.groups == 1 && amq::mfma_supported(g.batch))
@@ -1086,7 +1090,8 @@ static int score_layer_launch(const uint32_t* Wsp, const float* alpha_s, int64_t
   b.tgt = tg;
   b.tgt_out = o.tlogit;
   b.groups = 1;
-  if (!amq::bmv_supported((int)H, 0, k_as, rows, amq::kEpiStore) && amq::mfma4w_supported(b, k_ws, k_as)) {
+  const bool wide = amq::mfma32_supported(b, k_ws, k_as);
+  if (wide || (!amq::bmv_supported((int)H, 0, k_as, rows, amq::kEpiStore) && amq::mfma4w_supported(b, k_ws, k_as))) {
     amq::QuantArgs q{};
     q.seg[0] = amq::QuantSeg{hs, H, (int)H, (int)rows, sw.hp, sw.beta};
     q.T = T;
@@ -1094,7 +1099,7 @@ static int score_layer_launch(const uint32_t* Wsp, const float* alpha_s, int64_t
     int st = hip_status(amq::launch_quantize(q, k_as, s));
     if (st != AMQ_OK) return st;
     int slots = 0;
-    st = hip_status(amq::launch_mfma4w(b, k_ws, k_as, s, &slots));
+    st = hip_status(wide ? amq::launch_mfma32(b, k_ws, k_as, s, &slots) : amq::launch_mfma4w(b, k_ws, k_as, s, &slots));
     if (st != AMQ_OK) return st;
     if (slots > 0)
       return hip_status(amq::launch_score_finish(o.tlogit, tg, rows, V, sw.lse_part, slots, out, s));

@@ -195,6 +195,9 @@ hipError_t launch_mfma4(BmvArgs a, int k_w, int k_a, int epi, hipStream_t s, int
 // at least 32 columns (store mode only)
 bool mfma4w_supported(const BmvArgs& a, int k_w, int k_a);
 hipError_t launch_mfma4w(const BmvArgs& a, int k_w, int k_a, hipStream_t s, int* lse_slots = nullptr);
+// large plain products on the 32 x 32 form of the instruction, any vector length whose staged planes fit LDS
+bool mfma32_supported(const BmvArgs& a, int k_w, int k_a);
+hipError_t launch_mfma32(const BmvArgs& a, int k_w, int k_a, hipStream_t s, int* lse_slots = nullptr);
 // the recurrent steps with both operands loaded straight into registers in sign form and the x / h
 // blocks on paired waves (batches of 17 and more while the row-block x tile tasks are few)
 bool mfma4_pair_supported(const BmvArgs& a, int k_w, int k_a, int epi);

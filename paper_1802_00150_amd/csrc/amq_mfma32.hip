@@ -1,0 +1,35 @@
+// Large plain products on the 32 x 32 form of the fp4 matrix instruction (amq_mfma32_body.h): the rule of when they
+// apply, and the 2-bit-weight instantiations (those with 3-bit weights are in amq_mfma32_w3.hip).
+#include "amq_mfma32_body.h"
+
+namespace amq {
+
+hipError_t launch_mfma32_w3(const BmvArgs& a, int k_a, hipStream_t s, int* lse_slots);
+
+// Plain products (no integer hook) of 2- and 3-bit codes and vectors whose staged planes fit LDS; sizes whose element
+// offsets fit 32 bits.  The lines, all measured:
+//   - vectors above 1024 entries: from batch 17 on the alternative is the int8 kernel, which takes 1.3 to 2.7 times as
+//     long; at 9 .. 16 it is the small-batch kernel, whose time grows with the batch (equal at 10000 x 1500 and batch 8);
+//   - of 769 .. 1024 entries (8 pieces per row): the kernel with 16 x 16 tiles wastes nothing either and cuts the work
+//     finer, so it stays ahead until every SIMD has eight 32 x 32 tasks, and beyond where two-bit operands write outputs;
+//   - shorter ones: the 16 x 16 kernel always contracts 1024 positions; from one task per SIMD.
+bool mfma32_supported(const BmvArgs& a, int k_w, int k_a) {
+  using namespace mfma32;
+  if (a.D || a.groups > 1 || k_w < 2 || k_w > 3 || k_a < 2 || k_a > 3) return false;
+  if (!a.Y && !(a.tgt && a.tgt_out && a.lse_part && a.lse_cap >= 256)) return false;
+  if (a.batch <= 8 || lds_bytes(k_w, k_a, 1, a.blk[0].n) > kMaxLds) return false;
+  if (a.m * ((a.blk[0].n + 127) / 128) * k_w >= (1LL << 31)) return false;  // weight offsets in 16-byte units
+  if ((long long)a.batch * a.m >= (1LL << 31)) return false;
+  if (a.blk[0].n > 1024) return a.batch > kBmvMaxBatch || (a.m >= 8192 && a.blk[0].n <= 2048);
+  const long long tasks = (a.m + kTileN - 1) / kTileN * ((a.batch + kTileN - 1) / kTileN);
+  if (half_pieces(a.blk[0].n) == kStaticPieces) return tasks >= 8192 && (k_w * k_a > 4 || !a.Y);
+  return a.batch > 16 && tasks >= 1024;
+}
+
+hipError_t launch_mfma32(const BmvArgs& a, int k_w, int k_a, hipStream_t s, int* lse_slots) {
+  if (lse_slots) *lse_slots = 0;
+  if (k_w == 3) return launch_mfma32_w3(a, k_a, s, lse_slots);
+  return k_a == 2 ? mfma32::launch_tiles<2, 2>(a, s, lse_slots) : mfma32::launch_tiles<2, 3>(a, s, lse_slots);
+}
+
+}  // namespace amq

@@ -154,3 +154,26 @@ def test_grouped_gemv(amq):
     for gi in range(G):
         ref = oracle.binary_gemm(Wp[gi], alpha[gi], n, Xp[gi][:, None, :], beta[gi][None, :], bias=bias)
         assert_vec_close(Y[gi][None, :], ref)
+
+
+# Large plain products (32 x 32 tiles): every number of pieces per k-block, rows and columns that fill no tile, long
+# vectors with few and many columns, bias and accumulation.  Reference: the dense product of the reconstructed operands.
+@pytest.mark.parametrize("m,n,B,k_w,k_a", [(33001, 64, 33, 2, 2), (16001, 300, 70, 2, 3), (8000, 513, 129, 3, 2),
+                                           (10003, 650, 129, 3, 3), (32771, 1000, 258, 2, 3), (16390, 1024, 530, 3, 3),
+                                           (50, 1025, 5, 2, 2), (1000, 1500, 17, 2, 3), (4099, 2048, 40, 3, 3),
+                                           (700, 2100, 65, 2, 2), (300, 3300, 33, 3, 3), (65, 4096, 300, 3, 2)])
+def test_large_products(amq, m, n, B, k_w, k_a):
+    import torch
+    say("large product %d x %d batch %d W%d/A%d" % (m, n, B, k_w, k_a))
+    g = torch.Generator(device="cuda").manual_seed(m + n + B)
+    W = torch.randn((m, n), generator=g, device="cuda") * 0.05
+    x = torch.randn((B, n), generator=g, device="cuda")
+    bias = torch.randn((m,), generator=g, device="cuda")
+    Wp, al = amq.quantize_weights(W, k_w, 2)
+    Xp, be = amq.quantize_activations(x, k_a, 2)
+    ref = (amq.dequantize(Xp, be, n).double() @ amq.dequantize(Wp, al, n).double().t().contiguous())
+    tol = 1e-4 * ref.abs() + 1e-4 * ref.pow(2).mean(1, keepdim=True).sqrt()
+    Y = amq.binary_gemm(Wp, al, n, Xp, be)
+    assert bool(((Y.double() - ref).abs() <= tol).all())
+    Y2 = amq.binary_gemm(Wp, al, n, Xp, be, bias=bias, Y=Y.clone())
+    assert bool(((Y2.double() - (2 * ref + bias.double())).abs() <= 2 * tol + 1e-4).all())
