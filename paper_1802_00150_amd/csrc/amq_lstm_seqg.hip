@@ -26,7 +26,7 @@
 #include <atomic>
 
 #include "amq_launch.h"
-#include "amq_quantize_core.h"
+#include "amq_quantize_body.h"
 
 namespace amq {
 
@@ -120,7 +120,7 @@ __device__ __forceinline__ bool grid_barrier(unsigned* sync, unsigned epoch, uns
 // round trip between "everything is there" and "read it".  Returns false if the wait was given up.
 template <int KA, bool SHARED>
 __device__ __forceinline__ bool quantize_wg(const void* src_v, unsigned tag, unsigned* sync, unsigned limit, int n,
-                                            int T, uint32_t* planes, float* coef, double (*sh)[16 * kMaxRed],
+                                            int T, uint32_t* planes, float* coef, double* sh,
                                             int& phase) {
   const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
   const int wpr = 4 * ((n + 127) >> 7);
@@ -171,7 +171,12 @@ __device__ __forceinline__ bool quantize_wg(const void* src_v, unsigned tag, uns
   }
   float alpha[KA];
   unsigned long long mym[KA];
-  quantize_core<KA, kGNJ, kGWaves>(w, n, base, nj, T, alpha, mym, sh, phase);
+  with_slots<kGNJ, true>(nj, [&](auto slots) {
+    float v[slots()];
+#pragma unroll
+    for (int j = 0; j < slots(); ++j) v[j] = w[j];
+    quantize_core<KA, slots(), kGWaves, true>(v, n, base, nj, T, alpha, mym, sh, phase);
+  });
 #pragma unroll
   for (int i = 0; i < KA; ++i) {
     if (lane < nj && base + lane < nslots) reinterpret_cast<unsigned long long*>(planes + i * wpr)[base + lane] = mym[i];
@@ -197,8 +202,8 @@ __global__ void seqg_poison_kernel(const unsigned* sync, float* out, long long c
 }
 
 template <int KW, int KA>
-__global__ __launch_bounds__(64 * kGWaves) void lstm_seqg_kernel(SeqGArgs a) {
-  __shared__ double sh[2][16 * kMaxRed];
+__global__ __launch_bounds__(64 * kGWaves, 2) void lstm_seqg_kernel(SeqGArgs a) {
+  __shared__ double sh[2 * kExchange<kGWaves>];
   __shared__ __attribute__((aligned(16))) uint32_t xq[KA * 32];  // codes of x_t, [KA][wpr(I)]
   __shared__ __attribute__((aligned(16))) uint32_t hq[KA * 32];  // codes of h_{t-1}
   __shared__ float bx[4], bh[4];
@@ -365,6 +370,7 @@ bool lstm_seqg_supported(long long I, long long H, long long B, int k_w, int k_a
   return (H + units_per_wg - 1) / units_per_wg <= kSeqGMaxGrid;
 }
 
+unsigned sequence_spin_limit() { return g_spin_limit.load(); }
 void set_seqg_spin_limit(unsigned polls) { g_spin_limit.store(polls ? polls : kSpinLimit); }
 
 hipError_t launch_seqg_poison(const unsigned* sync, float* out, long long count, hipStream_t s) {

@@ -8,15 +8,16 @@ namespace amq {
 
 namespace {
 
-template <int K, int NJ, int NW>
-__global__ __launch_bounds__(64 * NW)
+// (The second launch bound keeps the results of the matrix instructions in ordinary registers.)
+template <int K, int NJ, int NW, bool ONLINE>
+__global__ __launch_bounds__(64 * NW, NW < 16 ? 2 : 4)
 void quantize_kernel(QuantArgs a) {
-  __shared__ double sh[2][16 * kMaxRed];
+  __shared__ double sh[2 * kExchange<NW>];
   asm volatile("" ::AMQ_ARG(a.seg[0].X), AMQ_ARG(a.seg[0].ld), AMQ_ARG(a.seg[0].n), AMQ_ARG(a.seg[0].count),
                AMQ_ARG(a.seg[0].planes), AMQ_ARG(a.seg[0].coef), AMQ_ARG(a.seg[1].X), AMQ_ARG(a.seg[1].ld),
                AMQ_ARG(a.seg[1].n), AMQ_ARG(a.seg[1].count), AMQ_ARG(a.seg[1].planes), AMQ_ARG(a.seg[1].coef),
                AMQ_ARG(a.T), AMQ_ARG(a.gather.count));
-  quantize_block<K, NJ, NW>(a, blockIdx.x, sh);
+  quantize_block<K, NJ, NW, ONLINE>(a, blockIdx.x, sh);
 }
 
 // Staged hooks on one vector per workgroup: Eq. 5 with the codes given (a.mode == kQuantLsOnly), or Alg. 1 with
@@ -109,10 +110,10 @@ __global__ __launch_bounds__(64 * NW) void quantize_stage_kernel(QuantArgs a) {
   }
 }
 
-template <int K, int NJ, int NW>
+template <int K, int NJ, int NW, bool ONLINE = false>
 void launch_one(QuantArgs a, int total, hipStream_t s) {
   AMQ_PHASE_ATTACH(a);
-  hipLaunchKernelGGL((quantize_kernel<K, NJ, NW>), dim3(total), dim3(64 * NW), 0, s, a);
+  hipLaunchKernelGGL((quantize_kernel<K, NJ, NW, ONLINE>), dim3(total), dim3(64 * NW), 0, s, a);
 }
 
 template <int K>
@@ -126,8 +127,8 @@ hipError_t launch_stage(const QuantArgs& a, int nslots, hipStream_t s) {
 
 // Waves per vector.  Many vectors (throughput): as few waves as hold the vector with at most 16 slots per lane --
 // what a wave does once per vector (reductions, solves, code tables) is then paid by few waves, and 16 slots keep
-// the registers at about 90.  Few vectors (the on-line case, latency): at most 4 slots per lane.  Then the
-// smallest register form that holds the share.
+// the registers at about 100; then the smallest register form that holds the share.  Few vectors (the on-line case,
+// latency): at most 4 slots per lane over at least 4 waves, and the form of the algorithm made for that.
 template <int K>
 hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
   const int nvec = a.seg[0].count + a.seg[1].count;
@@ -136,10 +137,15 @@ hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
   const int nslots = nvec ? 2 * ((max_n + 127) / 128) : 1;
   if (nslots > 256) return hipErrorInvalidValue;
   if (a.mode != kQuantFull) return launch_stage<K>(a, nslots, s);
-  const int most = nvec >= 1024 ? 16 : 4;
+  if (nvec < 1024 && nslots <= 64) {
+    if (nslots <= 2) launch_one<K, 2, 1, true>(a, total, s);
+    else if (nslots <= 16) launch_one<K, 4, 4, true>(a, total, s);
+    else if (nslots <= 32) launch_one<K, 4, 8, true>(a, total, s);
+    else launch_one<K, 4, 16, true>(a, total, s);
+    return hipGetLastError();
+  }
   int nw = 1;
-  while (nw < 16 && (nslots + nw - 1) / nw > most) nw *= 2;
-  if (nvec < 1024 && nw < 4 && nslots >= 4) nw = 4;
+  while (nw < 16 && (nslots + nw - 1) / nw > 16) nw *= 2;
   const int nj = (nslots + nw - 1) / nw;
   if (nw == 1) {
     if (nj <= 2) launch_one<K, 2, 1>(a, total, s);
@@ -151,16 +157,12 @@ hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
     if (nj <= 12) launch_one<K, 12, 2>(a, total, s);
     else launch_one<K, 16, 2>(a, total, s);
   } else if (nw == 4) {
-    if (nj <= 2) launch_one<K, 2, 4>(a, total, s);
-    else if (nj <= 4) launch_one<K, 4, 4>(a, total, s);
-    else if (nj <= 12) launch_one<K, 12, 4>(a, total, s);
+    if (nj <= 12) launch_one<K, 12, 4>(a, total, s);
     else launch_one<K, 16, 4>(a, total, s);
   } else if (nw == 8) {
-    if (nj <= 4) launch_one<K, 4, 8>(a, total, s);
-    else launch_one<K, 16, 8>(a, total, s);
+    launch_one<K, 16, 8>(a, total, s);
   } else {
-    if (nj <= 4) launch_one<K, 4, 16>(a, total, s);
-    else launch_one<K, 16, 16>(a, total, s);
+    launch_one<K, 16, 16>(a, total, s);
   }
   return hipGetLastError();
 }

@@ -43,10 +43,28 @@ __device__ __forceinline__ void load_slots(const float* x, int n, int base, int 
   }
 }
 
-// vec: index of this workgroup's vector over both segments (then over the gathered rows).  sh: two
-// buffers of 16 * kMaxRed doubles of LDS.  Every wave of the workgroup (NW of them) must call this.
-template <int K, int NJ, int NW>
-__device__ __forceinline__ void quantize_block(const QuantArgs& a, int vec, double (*sh)[16 * kMaxRed]) {
+// f(number of slots to hold in registers, a constant).  The latency-bound form computes every slot it holds, so there the
+// number follows the share of the wave closely: 2, 3, 4, 6 or 8, as far as NJ goes.
+template <int NJ, bool ONLINE, typename F>
+__device__ __forceinline__ void with_slots(int nj, F f) {
+  auto call = [&](auto slots) { f(slots); };
+  if constexpr (ONLINE && NJ == 4) {
+    if (nj <= 2) call(std::integral_constant<int, 2>{});
+    else if (nj == 3) call(std::integral_constant<int, 3>{});
+    else call(std::integral_constant<int, 4>{});
+  } else if constexpr (ONLINE && NJ == 8) {
+    if (nj <= 4) call(std::integral_constant<int, 4>{});
+    else if (nj <= 6) call(std::integral_constant<int, 6>{});
+    else call(std::integral_constant<int, 8>{});
+  } else {
+    call(std::integral_constant<int, NJ>{});
+  }
+}
+
+// vec: index of this workgroup's vector over both segments (then over the gathered rows).  sh:
+// 2 * kExchange<NW> doubles of LDS.  Every wave of the workgroup (NW of them) must call this.
+template <int K, int NJ, int NW, bool ONLINE>
+__device__ __forceinline__ void quantize_block(const QuantArgs& a, int vec, double* sh) {
   int phase = 0;
   const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
   AMQ_PHASE(AMQ_PHASE_OF(a), 0);
@@ -70,13 +88,14 @@ __device__ __forceinline__ void quantize_block(const QuantArgs& a, int vec, doub
   const int base = wv * nj;
   const float* x = X + (long long)vec * ld;
 
-  float w[NJ];
-  load_slots<NJ>(x, n, base, nj, w);
-
   float alpha[K];
   unsigned long long mym[K];
   AMQ_PHASE(AMQ_PHASE_OF(a), 1);
-  quantize_core<K, NJ, NW>(w, n, base, nj, a.T, alpha, mym, sh, phase, AMQ_PHASE_OF(a));
+  with_slots<NJ, ONLINE>(nj, [&](auto slots) {
+    float w[slots()];
+    load_slots<slots()>(x, n, base, nj, w);
+    quantize_core<K, slots(), NW, ONLINE>(w, n, base, nj, a.T, alpha, mym, sh, phase, AMQ_PHASE_OF(a));
+  });
 
 #pragma unroll
   for (int i = 0; i < K; ++i)

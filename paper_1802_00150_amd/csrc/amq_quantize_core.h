@@ -313,97 +313,107 @@ __device__ __forceinline__ void masked_add(double (&c)[NT], double x, const unsi
   }
 }
 
-template <int CTRL>
-__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(v & 0xffffffffull), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), CTRL, 0xf, 0xf, true);
-  return ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
-}
-// Sum over aligned groups of N = 8 or 16 lanes, in every lane.
-template <int N>
-__device__ __forceinline__ double lane_group_sum(double v) {
-  v += dpp_d<0xB1>(v);
-  v += dpp_d<0x4E>(v);
-  v += dpp_d<0x141>(v);
-  if constexpr (N == 16) v += dpp_d<0x140>(v);
-  return v;
-}
-template <int N>
-__device__ __forceinline__ unsigned long long lane_group_sum(unsigned long long v) {
-  v += dpp_u64<0xB1>(v);
-  v += dpp_u64<0x4E>(v);
-  v += dpp_u64<0x141>(v);
-  if constexpr (N == 16) v += dpp_u64<0x140>(v);
-  return v;
+// Sums over the 64 lanes of up to four doubles on the matrix cores, which add f64 values exactly as the vector unit does
+// (v_mfma_f64_4x4x4_4b: four blocks of 4 x 4 x 4; lane i + 4 b + 16 k holds A_b[i][k] and B_b[k][i], and lane
+// j + 4 b + 16 i receives D_b[i][j]).  Value j of the lanes times column selector j, accumulated over the values, leaves
+// in column j the sums over k; ones times that, the sums over i as well: lane l then holds the sum of value l % 4 over the
+// 16 lanes of block (l / 4) % 4.
+template <int NV>
+__device__ __forceinline__ double matrix_sums(const double* v) {
+  static_assert(NV >= 1 && NV <= 4, "columns");
+  int j = lane_id() & 3;
+  asm volatile("" : "+v"(j));  // (the selectors are formed here, not kept in registers from one exchange to the next)
+  double acc = 0.0;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) acc = __builtin_amdgcn_mfma_f64_4x4x4f64(v[i], j == i ? 1.0 : 0.0, acc, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, acc, 0.0, 0, 0, 0);
 }
 
-// Totals over a workgroup of NW waves of NV per-lane doubles v and of NC wave-uniform counts c (each at most
-// 16384 in total); the totals come back in every lane.  One LDS barrier; two buffers used alternately.  The
-// counts travel four to a 64-bit word.
-template <int NW, int NV, int NC>
-__device__ __forceinline__ void exchange_totals(double (&v)[NV], int (&c)[NC > 0 ? NC : 1], double (*sh)[16 * kMaxRed],
-                                                int& phase) {
-  if constexpr (NW == 1) {
-    wave_totals<NV>(v);
-  } else {
-    constexpr int NCW = (NC + 3) / 4;
-    constexpr int NE = NV + NCW;
-    static_assert(NE <= kMaxRed, "LDS buffer");
-    wave_sums_lane63<NV>(v);
-    unsigned long long pk[NCW > 0 ? NCW : 1];
+// Doubles of LDS for one of the two buffers of the exchanges of a workgroup of NW waves.
+template <int NW>
+constexpr int kExchange = NW == 1 ? 1 : 2 * 16 * NW;
+
+// Totals over a workgroup of NW waves of the NE per-lane doubles e, left in e[0] and e[4]: value i is in e[i & ~3] of the
+// lane total_lane<NW>(i).  Latency is what counts here (the reductions are the serial part of the algorithm): per wave the
+// sums of all values take one matrix instruction each and one more, 16 partial sums (value, block) go to LDS in one
+// write, and after the one barrier every lane reads one (value, block, wave) entry of each four waves, and two matrix
+// instructions sum over waves and blocks.  Measured over four waves: 356 cycles for one value, 530 for four.
+// sh: 2 * kExchange<NW> doubles, the two buffers used alternately.
+template <int NW>
+__device__ __forceinline__ constexpr int total_lane(int i) { return (i & 3) * (NW == 1 ? 1 : 4); }
+
+template <int NW, int NE>
+__device__ __forceinline__ void exchange_raw(double (&e)[4 * ((NE + 3) / 4)], double* sh, int& phase) {
+  constexpr int NG = (NE + 3) / 4, last = NE - 4 * (NG - 1);
+  static_assert(NG <= 2, "LDS buffer");
 #pragma unroll
-    for (int i = 0; i < NCW; ++i) {
-      pk[i] = 0ull;
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (4 * i + k < NC) pk[i] |= (unsigned long long)(unsigned)c[4 * i + k] << (16 * k);
-    }
-    double* buf = sh[phase];
-    if (lane_id() == 63) {
-      const int wv = wave_id();
-#pragma unroll
-      for (int i = 0; i < NV; ++i) buf[wv * NE + i] = v[i];
-#pragma unroll
-      for (int i = 0; i < NCW; ++i) buf[wv * NE + NV + i] = __longlong_as_double((long long)pk[i]);
-    }
-    lds_barrier();
-    if constexpr (NW <= 4) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        double t = buf[i];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) t += buf[w * NE + i];
-        v[i] = t;
-      }
-#pragma unroll
-      for (int i = 0; i < NCW; ++i) {
-        pk[i] = (unsigned long long)__double_as_longlong(buf[NV + i]);
-#pragma unroll
-        for (int w = 1; w < NW; ++w) pk[i] += (unsigned long long)__double_as_longlong(buf[w * NE + NV + i]);
-      }
+  for (int g = 0; g < NG; ++g) {
+    double t = g + 1 < NG ? matrix_sums<4>(e + 4 * g) : matrix_sums<last>(e + 4 * g);
+    if constexpr (NW == 1) {
+      t += dpp_d<0x124>(t);  // row_ror:4
+      t += dpp_d<0x128>(t);  // row_ror:8: over the blocks
+      e[4 * g] = t;
     } else {
-      // many waves: a lane takes one wave's entry and the lanes are summed (the entries repeat every NW lanes)
-      static_assert(NW == 8 || NW == 16, "groups of lanes a DPP butterfly covers");
-      const double* mine = buf + (lane_id() & (NW - 1)) * NE;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) v[i] = mine[i];
-#pragma unroll
-      for (int i = 0; i < NCW; ++i) pk[i] = (unsigned long long)__double_as_longlong(mine[NV + i]);
-#pragma unroll
-      for (int i = 0; i < NV; ++i) v[i] = lane_group_sum<NW>(v[i]);
-#pragma unroll
-      for (int i = 0; i < NCW; ++i) pk[i] = lane_group_sum<NW>(pk[i]);
+      const int lane = lane_id();
+      if (lane < 16) sh[phase * kExchange<NW> + (g * NW + wave_id()) * 16 + lane] = t;
     }
+  }
+  if constexpr (NW > 1) {
+    lds_barrier();
+    const int lane = lane_id();
+    const double* mine = sh + phase * kExchange<NW> + ((lane >> 2) & 3) + 4 * (lane & 3);  // value (lane / 4) % 4, block lane % 4
 #pragma unroll
-    for (int i = 0; i < NCW; ++i) {
-      const unsigned long long t = pk[i];
-      const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(t & 0xffffffffull));
-      const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(t >> 32));
+    for (int g = 0; g < NG; ++g) {
+      double t;
+      if constexpr (NW == 2) {
+        t = 0.5 * mine[(g * NW + ((lane >> 4) & 1)) * 16];  // (both waves twice)
+      } else {
+        t = mine[(g * NW + (lane >> 4)) * 16];
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (4 * i + k < NC) c[4 * i + k] = (int)(((k < 2 ? lo : hi) >> (16 * (k & 1))) & 0xffffu);
+        for (int w = 4; w < NW; w += 4) t += mine[(g * NW + w + (lane >> 4)) * 16];
+      }
+      t = __builtin_amdgcn_mfma_f64_4x4x4f64(t, 1.0, 0.0, 0, 0, 0);
+      e[4 * g] = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, t, 0.0, 0, 0, 0);  // lane l: total of value (l / 4) % 4
     }
     phase ^= 1;
+  }
+}
+
+__device__ __forceinline__ double readlane_d(double x, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+
+// Up to three counts of at most 16384 (15 bits each) in the last places of 2^52 + packed.
+__device__ __forceinline__ int count_of(unsigned long long p, int k) { return (int)((p >> (15 * k)) & 0x7fffu); }
+
+// Totals of NV per-lane doubles v and of NC wave-uniform counts c, the same in every lane.  The counts travel three to a
+// double (the sums are exact).
+template <int NW, int NV, int NC>
+__device__ __forceinline__ void exchange_totals(double (&v)[NV], int (&c)[NC > 0 ? NC : 1], double* sh, int& phase) {
+  constexpr int NCW = NW == 1 ? 0 : (NC + 2) / 3;
+  constexpr int NE = NV + NCW;
+  double e[4 * ((NE + 3) / 4)];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) e[i] = v[i];
+#pragma unroll
+  for (int i = 0; i < NCW; ++i) {
+    unsigned long long p = 0x42d0000000000000ull;  // 2^46, in whose last place a count stands for itself / 64
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (3 * i + k < NC) p |= (unsigned long long)(unsigned)c[3 * i + k] << (15 * k);
+    e[NV + i] = __longlong_as_double((long long)p) - 0x1p46;  // a 64th of the wave's counts in every lane
+  }
+  exchange_raw<NW, NE>(e, sh, phase);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) v[i] = readlane_d(e[i & ~3], total_lane<NW>(i));
+#pragma unroll
+  for (int i = 0; i < NCW; ++i) {
+    const int at = NV + i;
+    const unsigned long long p =
+        (unsigned long long)__double_as_longlong(readlane_d(e[at & ~3] + 0x1p52, total_lane<NW>(at)));
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (3 * i + k < NC) c[3 * i + k] = count_of(p, k);
   }
 }
 
@@ -505,7 +515,7 @@ constexpr int kSignMaskSlots = 4;
 template <int K, int NJ, int NW, bool FULL>
 __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n, int base, int nj, int T,
                                                     float (&alpha)[K], unsigned long long (&mym)[K],
-                                                    double (*sh)[16 * kMaxRed], int& phase, unsigned long long* marks) {
+                                                    double* sh, int& phase, unsigned long long* marks) {
   (void)marks;  // phase timers of the profiling build: 2 = greedy done, 4 + 4 * cycle + {0: reduction, 1: solve, 2: table, 3: assignment}
   constexpr int H = 1 << (K - 1);
   constexpr int NT = H > 1 ? H - 1 : 1;
@@ -545,7 +555,9 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
     }
     if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
   }
+  AMQ_PHASE(marks, 12);
   exchange_totals<NW, 1, 0>(sum, no_counts, sh, phase);
+  AMQ_PHASE(marks, 13);
   const double l1 = sum[0];
   alpha[0] = mean(l1);
   if constexpr (K == 1) {
@@ -596,7 +608,9 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
       }
       s[i] = si[0];
       if (i + 1 < K) {
+        AMQ_PHASE(marks, 14);
         exchange_totals<NW, 1, 0>(sr, no_counts, sh, phase);
+        AMQ_PHASE(marks, 15);
         alpha[i] = mean(sr[0]);
       } else {
         s[0] = sr[0];
@@ -712,14 +726,389 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
   }
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// The same algorithm where one vector at a time is waited for (on-line quantization: one wave per SIMD, nothing to
+// hide behind).  There a wave is bound by the latency of its own instructions, and what is cheap to issue is not what
+// is quick: setting the lane mask around an addition takes 38 cycles with the comparison, a selected factor of 0 or 1
+// and a fused multiply-add 15; a scalar population count of a comparison waits for the comparison, a second fused
+// multiply-add does not.  So
+//   - sums under a comparison are c += |w| * m with m = 0 or 1 by one select;
+//   - the counts are sums of m * 2^(15 t), three to a double, and go through the same reductions;
+//   - thresholds and coefficients stay in vector registers; slots are straight-line code: an entry past the end of the
+//     vector is 0 and its u is -1, below every threshold.
+//   - coefficients, table and sums of the usual code orders are straight-line code without branches on the data, the
+//     rest is out of the way.
+// Same arithmetic otherwise.  Measured for a vector of 1024 entries on four waves of one compute unit, k = 2 / 3:
+// 2960 / 5730 -> 2650 / 4060 cycles (of which the reductions take about 1100 / 1760).
+
+// 1.0 where `yes`, else 0.0.
+__device__ __forceinline__ double one_if(bool yes) { return __hiloint2double(yes ? 0x3ff00000 : 0, 0); }
+
+// Eq. 5 from the inner products g of the planes (integers; pairs in the order of ls_solve_f64), which are exact, as are
+// all intermediate values that are in ls_solve_f64.
+template <int K>
+__device__ __forceinline__ void ls_solve_gram(int n, double dn, const double* g, const double (&q)[K], float (&alpha)[K]) {
+  if constexpr (K == 2) {
+    const double a = g[0];
+    const double det = __builtin_fma(-a, a, dn * dn);
+    const double inv = recip_f64(det);
+    const float a0 = (float)(__builtin_fma(-a, q[1], dn * q[0]) * inv);
+    const float a1 = (float)(__builtin_fma(-a, q[0], dn * q[1]) * inv);
+    alpha[0] = det != 0.0 ? a0 : alpha[0];  // (a select, so that the neighbouring steps stay one block of code)
+    alpha[1] = det != 0.0 ? a1 : alpha[1];
+  } else if constexpr (K == 3) {
+    const double a = g[0], b = g[1], c = g[2];
+    const double nn = dn * dn;
+    const double c00 = __builtin_fma(-c, c, nn), c11 = __builtin_fma(-b, b, nn), c22 = __builtin_fma(-a, a, nn);
+    const double c01 = __builtin_fma(c, b, -(a * dn)), c02 = __builtin_fma(a, c, -(dn * b)), c12 = __builtin_fma(a, b, -(dn * c));
+    const double det = __builtin_fma(b, c02, __builtin_fma(a, c01, dn * c00));
+    const double inv = recip_f64(det);
+    const float a0 = (float)(__builtin_fma(c02, q[2], __builtin_fma(c01, q[1], c00 * q[0])) * inv);
+    const float a1 = (float)(__builtin_fma(c12, q[2], __builtin_fma(c11, q[1], c01 * q[0])) * inv);
+    const float a2 = (float)(__builtin_fma(c22, q[2], __builtin_fma(c12, q[1], c02 * q[0])) * inv);
+    alpha[0] = det != 0.0 ? a0 : alpha[0];
+    alpha[1] = det != 0.0 ? a1 : alpha[1];
+    alpha[2] = det != 0.0 ? a2 : alpha[2];
+  } else {
+    double d[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) d[i] = 0.5 * (dn - g[i]);
+    ls_solve_f64<K>(n, d, q, alpha);
+  }
+}
+
+// The code table in vector registers, and which of the usual orders it is in: 0: by pattern (K = 2, 3), 1: by pattern
+// with 011 in the place of 100 (K = 3), 2: any other, given by ct.bm.
+template <int K>
+__device__ __forceinline__ int code_table_kind(const float (&alpha)[K], CodeTable<K>& ct) {
+  if constexpr (K == 2) {
+    const float v2 = alpha[0] - alpha[1], v3 = alpha[0] + alpha[1];
+    if (__builtin_expect(__ballot(v2 >= 0.0f && alpha[1] >= 0.0f) != 0ull, 1)) {
+      ct.thr[0] = __float_as_int(0.5f * (v2 + v3));
+      return 0;
+    }
+  } else if constexpr (K == 3) {
+    const float d = alpha[0] - alpha[1], s = alpha[0] + alpha[1];
+    const float v4 = d - alpha[2], v5 = d + alpha[2], v6 = s - alpha[2], v7 = s + alpha[2];
+    const float lo = fabsf(v4);
+    if (__builtin_expect(__ballot(lo <= v5 && v5 <= v6 && v6 <= v7) != 0ull, 1)) {
+      ct.thr[0] = __float_as_int(0.5f * (lo + v5));
+      ct.thr[1] = __float_as_int(0.5f * (v5 + v6));
+      ct.thr[2] = __float_as_int(0.5f * (v6 + v7));
+      if (__builtin_expect(__ballot(v4 < 0.0f) == 0ull, 1)) return 0;
+      ct.bm[0] = 0xeu;
+      ct.bm[1] = 0xdu;
+      ct.bm[2] = 0xbu;
+      return 1;
+    }
+  }
+  code_table_any_order<K>(alpha, ct);
+  return 2;
+}
+
+template <int K, int NJ, int NW, bool FULL>
+__device__ __forceinline__ void quantize_online(const float (&x)[NJ], int n, int base, int nj, int T, float (&alpha)[K],
+                                                unsigned long long (&mym)[K], double* sh, int& phase,
+                                                unsigned long long* marks) {
+  (void)marks;
+  constexpr int H = 1 << (K - 1);
+  constexpr int NT = H > 1 ? H - 1 : 1;
+  constexpr int NP = K * (K - 1) / 2;
+  constexpr int NPW = (NP + 2) / 3, NTW = (NT + 2) / 3;  // doubles that carry the counts of the pairs, of the midpoints
+  const double dn = (double)n;
+  const double inv_n = recip_f64(dn);
+  auto mean = [&](double s) { return (float)(s * inv_n); };
+  auto inside = [&](int j) { return FULL ? ~0ull : (j < nj ? lanes_inside(n, base + j) : 0ull); };
+  const unsigned long long lane_inside = FULL ? ~0ull : lanes_inside(n, base + lane_id());
+  const int outside = NW * NJ * 64 - n;  // entries past the end that the workgroup's slots hold
+  const double field[3] = {1.0, 0x1p15, 0x1p30};
+  int no_counts[1] = {0};
+
+  int u[NJ];
+  float xc[NJ];
+  double wd[NJ];
+  float r[NJ];
+  double sum[1] = {0.0};
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    xc[j] = x[j] + 0.0f;
+    const unsigned b = __float_as_uint(xc[j]);
+    u[j] = (int)min(b, b + 0x7fffffffu);
+    if (!FULL) u[j] = lane_bit(inside(j)) ? u[j] : -1;
+    wd[j] = fabs((double)xc[j]);
+    r[j] = xc[j];
+    sum[0] = (j == 0) ? wd[j] : sum[0] + wd[j];
+  }
+  AMQ_PHASE(marks, 12);
+  exchange_totals<NW, 1, 0>(sum, no_counts, sh, phase);
+  AMQ_PHASE(marks, 13);
+  const double l1 = sum[0];
+  alpha[0] = mean(l1);
+  auto signs_in_lanes = [&]() {
+    unsigned long long m = 0ull;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) keep_in_lane(m, __ballot(__float_as_int(xc[j]) < 0), j);
+    return m;
+  };
+  if constexpr (K == 1) {
+    mym[0] = ~signs_in_lanes() & lane_inside;
+    return;
+  } else {
+    // ---- greedy stages; red: the sum of |r| of the last stage, s[1 .. K-1], then the packed counts
+    double red[4 * ((K + NPW + 3) / 4)];
+    auto tally = [&](int pair, double m) {
+      double& acc = red[K + pair / 3];
+      acc = __builtin_fma(m, field[pair % 3], acc);
+    };
+#pragma unroll
+    for (int i = 0; i < NPW; ++i) red[K + i] = 0.0;
+#pragma unroll
+    for (int i = 1; i < K; ++i) {
+      const float a = alpha[i - 1];
+      double sr = 0.0, si = 0.0;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const float before = r[j];
+        float rn = before - copysignf(a, before);
+        if (!FULL) rn = lane_bit(inside(j)) ? rn : 0.0f;
+        r[j] = rn;
+        double m;  // plane i agrees with the sign of w
+        if (i == 1) {
+          m = one_if(u[j] >= __float_as_int(a));
+        } else {
+          m = one_if((__float_as_int(rn) ^ __float_as_int(xc[j])) >= 0);
+          tally(K == 3 ? 2 : (i == 2 ? 3 : 5), one_if((__float_as_int(before) ^ __float_as_int(rn)) < 0));
+          if (K == 4 && i == 3)
+            tally(4, one_if((u[j] >= __float_as_int(alpha[0])) != ((__float_as_int(rn) ^ __float_as_int(xc[j])) >= 0)));
+        }
+        si = __builtin_fma(wd[j], m, si);
+        tally(i - 1, m);
+        sr += fabs((double)rn);
+      }
+      red[i] = si;
+      if (i + 1 < K) {
+        double one[1] = {sr};
+        AMQ_PHASE(marks, 14);
+        exchange_totals<NW, 1, 0>(one, no_counts, sh, phase);
+        AMQ_PHASE(marks, 15);
+        alpha[i] = mean(one[0]);
+      } else {
+        red[0] = sr;
+      }
+    }
+    AMQ_PHASE(marks, 2);
+    exchange_raw<NW, K + NPW>(red, sh, phase);
+    auto total_of = [&](const double* e, int i) { return readlane_d(e[i & ~3], total_lane<NW>(i)); };
+    auto counts_of = [&](const double* e, int i) {
+      return (unsigned long long)__double_as_longlong(readlane_d(e[i & ~3] + 0x1p52, total_lane<NW>(i)));
+    };
+    alpha[K - 1] = mean(total_of(red, 0));
+    if (T == 0) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) mym[i] = 0ull;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        float rj = xc[j];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+          keep_in_lane(mym[i], __ballot(rj >= 0.0f), j);
+          rj = rj - copysignf(alpha[i], rj);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < K; ++i) mym[i] &= lane_inside;
+      return;
+    }
+    double q[K], g[NP];
+    {
+      unsigned long long p[NPW];
+#pragma unroll
+      for (int i = 0; i < NPW; ++i) p[i] = counts_of(red, K + i);
+      q[0] = l1;
+#pragma unroll
+      for (int i = 1; i < K; ++i) {
+        q[i] = __builtin_fma(2.0, total_of(red, i), -l1);
+        // plane 0 against plane i; entries past the end agree from the second stage on
+        g[i - 1] = (double)(2 * (count_of(p[(i - 1) / 3], (i - 1) % 3) - (i > 1 ? outside : 0)) - n);
+      }
+      // (planes 1 and 3: past the end plane 1 disagrees with the sign, u being -1, and plane 3 agrees)
+#pragma unroll
+      for (int i = K - 1; i < NP; ++i) g[i] = (double)(n - 2 * (count_of(p[i / 3], i % 3) - (K == 4 && i == 4 ? outside : 0)));
+    }
+
+    CodeTable<K> ct;
+    int kind;
+    for (int it = 0;; ++it) {
+      AMQ_PHASE(marks, 4 + 4 * it);
+      ls_solve_gram<K>(n, dn, g, q, alpha);
+      AMQ_PHASE(marks, 5 + 4 * it);
+      kind = code_table_kind<K>(alpha, ct);
+      AMQ_PHASE(marks, 6 + 4 * it);
+      if (it + 1 == T) break;
+      double c[4 * ((NT + NTW + 3) / 4)];
+#pragma unroll
+      for (int t = 0; t < NT + NTW; ++t) c[t] = 0.0;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const double m = one_if(u[j] >= ct.thr[t]);
+          c[t] = __builtin_fma(wd[j], m, c[t]);
+          c[NT + t / 3] = __builtin_fma(m, field[t % 3], c[NT + t / 3]);
+        }
+      AMQ_PHASE(marks, 7 + 4 * it);
+      if constexpr (K == 4) {
+        // four plane sums instead of seven C_t through the reduction (this lane's shares, without sum |w|)
+        double sp[8];
+        double ct7[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) ct7[t] = c[t];
+#pragma unroll
+        for (int i = 0; i < K; ++i) sp[i] = plane_dot<NT>(ct.bm[i], 0.0, ct7);
+#pragma unroll
+        for (int i = 0; i < NTW; ++i) sp[K + i] = c[NT + i];
+        exchange_raw<NW, K + NTW>(sp, sh, phase);
+        int cn[3 * NTW];
+#pragma unroll
+        for (int i = 0; i < NTW; ++i) {
+          const unsigned long long p = counts_of(sp, K + i);
+#pragma unroll
+          for (int k = 0; k < 3; ++k) cn[3 * i + k] = count_of(p, k);
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i) q[i] = ((ct.bm[i] & 1u) ? l1 : -l1) + total_of(sp, i);
+        int t0 = 0;
+#pragma unroll
+        for (int a = 0; a < K; ++a)
+#pragma unroll
+          for (int b = a + 1; b < K; ++b) {
+            const unsigned xo = ct.bm[a] ^ ct.bm[b];
+            int dd = (xo & 1u) ? n : 0;
+#pragma unroll
+            for (int t = 1; t <= NT; ++t) dd += step_at(xo, t) * cn[t - 1];
+            g[t0++] = (double)(n - 2 * dd);
+          }
+      } else {
+        exchange_raw<NW, NT + NTW>(c, sh, phase);
+        const unsigned long long p = counts_of(c, NT);
+        double cs[NT];
+        int cn[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          cs[t] = total_of(c, t);
+          cn[t] = count_of(p, t);
+        }
+        if (__builtin_expect(kind < 2, 1)) {
+          // (what the general form below gives for these two orders)
+          if constexpr (K == 2) {
+            q[1] = __builtin_fma(2.0, cs[0], -l1);
+            g[0] = (double)(2 * cn[0] - n);
+          } else {
+            g[0] = (double)(2 * cn[1] - n);
+            g[1] = (double)(2 * (cn[0] - cn[1] + cn[2]) - n);
+            g[2] = (double)(n - 2 * (cn[0] - cn[2]));
+            if (__builtin_expect(kind == 0, 1)) {
+              q[0] = l1;
+              q[1] = __builtin_fma(2.0, cs[1], -l1);
+              q[2] = __builtin_fma(2.0, (cs[0] - cs[1]) + cs[2], -l1);
+            } else {
+              q[0] = __builtin_fma(2.0, cs[0], -l1);
+              q[1] = __builtin_fma(2.0, cs[1] - cs[0], l1);
+              q[2] = __builtin_fma(2.0, cs[2] - cs[1], l1);
+            }
+          }
+          if constexpr (K == 2) q[0] = l1;
+        } else {
+#pragma unroll
+          for (int i = 0; i < K; ++i) q[i] = plane_dot<NT>(ct.bm[i], (ct.bm[i] & 1u) ? l1 : -l1, cs);
+          int t0 = 0;
+#pragma unroll
+          for (int a = 0; a < K; ++a)
+#pragma unroll
+            for (int b = a + 1; b < K; ++b) {
+              const unsigned xo = ct.bm[a] ^ ct.bm[b];
+              int dd = (xo & 1u) ? n : 0;
+#pragma unroll
+              for (int t = 1; t <= NT; ++t) dd += step_at(xo, t) * cn[t - 1];
+              g[t0++] = (double)(n - 2 * dd);
+            }
+        }
+      }
+    }
+
+    // ---- the last pass in one of the usual orders: the planes of a slot from the signs of u - threshold and of w,
+    // straight into the slot's lane
+    auto put_plane = [&](int i, int j, int sign) { keep_in_lane(mym[i], __ballot(sign < 0), j); };
+    if constexpr (K == 2) {
+      if (__builtin_expect(kind == 0, 1)) {
+        mym[0] = mym[1] = 0ull;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int w = __float_as_int(xc[j]);
+          put_plane(0, j, ~w);
+          put_plane(1, j, ~(w ^ (u[j] - ct.thr[0])));
+        }
+        mym[0] &= lane_inside;
+        mym[1] &= lane_inside;
+        return;
+      }
+    }
+    if constexpr (K == 3) {
+      if (__builtin_expect(kind == 0, 1)) {
+        mym[0] = mym[1] = mym[2] = 0ull;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int w = __float_as_int(xc[j]), u1 = u[j] - ct.thr[0], u2 = u[j] - ct.thr[1], u3 = u[j] - ct.thr[2];
+          put_plane(0, j, ~w);
+          put_plane(1, j, ~(w ^ u2));
+          put_plane(2, j, ~(w ^ u1 ^ u2 ^ u3));
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i) mym[i] &= lane_inside;
+        return;
+      }
+    }
+
+    // ---- the last pass: the comparison masks, slot j in lane j, then the planes in the lanes
+    unsigned long long ge[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) ge[t] = 0ull;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) keep_in_lane(ge[t], __ballot(u[j] >= ct.thr[t]), j);
+    const unsigned long long lane_neg = signs_in_lanes();
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+      unsigned long long p = lane_neg ^ (0ull - (unsigned long long)(ct.bm[i] & 1u));
+#pragma unroll
+      for (int t = 1; t <= NT; ++t)
+        p ^= ge[t - 1] & (0ull - (unsigned long long)(((ct.bm[i] >> t) ^ (ct.bm[i] >> (t - 1))) & 1u));
+      mym[i] = p & lane_inside;
+    }
+    AMQ_PHASE(marks, 11);
+  }
+}
+
+// Workgroup barriers that quantize_core passes (for waves of the workgroup that take no part in it).
+template <int K>
+__device__ __forceinline__ int quantize_exchanges(int T) {
+  return K == 1 ? 1 : K + (T > 1 ? T - 1 : 0);
+}
+
 // The same for a wave that may or may not have all its slots inside the vector (a wave-uniform choice; the
 // waves of a workgroup meet at the same barriers either way).
-template <int K, int NJ, int NW>
+// ONLINE: the latency-bound form.
+template <int K, int NJ, int NW, bool ONLINE>
 __device__ __forceinline__ void quantize_core(const float (&x)[NJ], int n, int base, int nj, int T, float (&alpha)[K],
-                                              unsigned long long (&mym)[K], double (*sh)[16 * kMaxRed], int& phase,
+                                              unsigned long long (&mym)[K], double* sh, int& phase,
                                               unsigned long long* marks = nullptr) {
   base = __builtin_amdgcn_readfirstlane(base);
-  if (nj == NJ && (base + NJ) * 64 <= n)
+  const bool full = nj == NJ && (base + NJ) * 64 <= n;
+  if constexpr (ONLINE) {
+    if (full) quantize_online<K, NJ, NW, true>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+    else quantize_online<K, NJ, NW, false>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+  } else if (full)
     quantize_magnitudes<K, NJ, NW, true>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
   else
     quantize_magnitudes<K, NJ, NW, false>(x, n, base, nj, T, alpha, mym, sh, phase, marks);

@@ -42,7 +42,7 @@ struct FrontArgs {
 // by one.)
 template <int KW, int KA, int EPI, int NC>
 __global__ __launch_bounds__(64 * kSplitWaves, 2) void step_front_kernel(FrontArgs f) {
-  __shared__ double sh[2][16 * kMaxRed];
+  __shared__ double sh[2 * kExchange<kSplitWaves>];
   extern __shared__ __attribute__((aligned(16))) uint4 turn[];
   asm volatile("" ::AMQ_ARG(f.q.seg[0].X), AMQ_ARG(f.q.seg[0].ld), AMQ_ARG(f.q.seg[0].n), AMQ_ARG(f.q.seg[0].count),
                AMQ_ARG(f.q.seg[0].planes), AMQ_ARG(f.q.seg[0].coef), AMQ_ARG(f.q.seg[1].X), AMQ_ARG(f.q.seg[1].ld),
@@ -51,11 +51,11 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void step_front_kernel(FrontAr
                AMQ_ARG(f.rowblocks));
   const int wg = blockIdx.x;
   if (wg < f.nq) {
-    quantize_block<KA, kSplitNJ * NC, kSplitWaves>(f.q, wg, sh);
+    quantize_block<KA, kSplitNJ * NC, kSplitWaves, true>(f.q, wg, sh);
     return;
   }
   if (wg < f.nq + f.nq2) {
-    quantize_block<KA, kSplitNJ * NC, kSplitWaves>(f.q2, wg - f.nq, sh);
+    quantize_block<KA, kSplitNJ * NC, kSplitWaves, true>(f.q2, wg - f.nq, sh);
     return;
   }
   const int p = wg - f.nq - f.nq2;

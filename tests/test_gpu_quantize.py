@@ -174,6 +174,7 @@ def test_weight_quantizer_heavy_tailed_full_size(amq, k):
 # lengths around the edges of the register forms: slots per wave, waves per vector, a partly filled last slot.
 @pytest.mark.parametrize("k", [1, 2, 3, 4])
 @pytest.mark.parametrize("rows,lengths", [(7, (1, 64, 129, 255, 257, 513, 1025, 2047, 4095, 4097, 9000)),
+                                          (9, (127, 128, 512, 768, 900, 1024, 1500, 2048, 4096)),
                                           (1031, (3, 128, 200, 500, 513, 650, 769, 1024, 1025, 1500, 2048, 2500, 3001, 4096, 4100))])
 def test_register_forms_and_special_rows(amq, k, rows, lengths):
     for n in lengths:
