@@ -8,9 +8,12 @@ namespace amq {
 
 namespace {
 
-// (The second launch bound keeps the results of the matrix instructions in ordinary registers.)
+// The second launch bound is the waves per SIMD that the registers shall allow.
+template <int K>
+constexpr int kQuantWaves = K == 4 ? 3 : 4;
+
 template <int K, int NJ, int NW, bool ONLINE>
-__global__ __launch_bounds__(64 * NW, NW < 16 ? 2 : 4)
+__global__ __launch_bounds__(64 * NW, NW < 16 ? kQuantWaves<K> : 4)
 void quantize_kernel(QuantArgs a) {
   __shared__ double sh[2 * kExchange<NW>];
   asm volatile("" ::AMQ_ARG(a.seg[0].X), AMQ_ARG(a.seg[0].ld), AMQ_ARG(a.seg[0].n), AMQ_ARG(a.seg[0].count),
@@ -147,22 +150,26 @@ hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
   int nw = 1;
   while (nw < 16 && (nslots + nw - 1) / nw > 16) nw *= 2;
   const int nj = (nslots + nw - 1) / nw;
-  if (nw == 1) {
-    if (nj <= 2) launch_one<K, 2, 1>(a, total, s);
-    else if (nj <= 4) launch_one<K, 4, 1>(a, total, s);
-    else if (nj <= 8) launch_one<K, 8, 1>(a, total, s);
-    else if (nj <= 12) launch_one<K, 12, 1>(a, total, s);
-    else launch_one<K, 16, 1>(a, total, s);
-  } else if (nw == 2) {
-    if (nj <= 12) launch_one<K, 12, 2>(a, total, s);
-    else launch_one<K, 16, 2>(a, total, s);
-  } else if (nw == 4) {
-    if (nj <= 12) launch_one<K, 12, 4>(a, total, s);
-    else launch_one<K, 16, 4>(a, total, s);
-  } else if (nw == 8) {
-    launch_one<K, 16, 8>(a, total, s);
-  } else {
-    launch_one<K, 16, 16>(a, total, s);
+  switch (nw * 32 + (nj + 1) / 2 * 2) {
+    case 32 + 2: launch_one<K, 2, 1>(a, total, s); break;
+    case 32 + 4: launch_one<K, 4, 1>(a, total, s); break;
+    case 32 + 6: launch_one<K, 6, 1>(a, total, s); break;
+    case 32 + 8: launch_one<K, 8, 1>(a, total, s); break;
+    case 32 + 10: launch_one<K, 10, 1>(a, total, s); break;
+    case 32 + 12: launch_one<K, 12, 1>(a, total, s); break;
+    case 32 + 14: launch_one<K, 14, 1>(a, total, s); break;
+    case 32 + 16: launch_one<K, 16, 1>(a, total, s); break;
+    case 64 + 10: launch_one<K, 10, 2>(a, total, s); break;
+    case 64 + 12: launch_one<K, 12, 2>(a, total, s); break;
+    case 64 + 14: launch_one<K, 14, 2>(a, total, s); break;
+    case 64 + 16: launch_one<K, 16, 2>(a, total, s); break;
+    case 128 + 10: launch_one<K, 10, 4>(a, total, s); break;
+    case 128 + 12: launch_one<K, 12, 4>(a, total, s); break;
+    case 128 + 14: launch_one<K, 14, 4>(a, total, s); break;
+    case 128 + 16: launch_one<K, 16, 4>(a, total, s); break;
+    default:
+      if (nw == 8) launch_one<K, 16, 8>(a, total, s);
+      else launch_one<K, 16, 16>(a, total, s);
   }
   return hipGetLastError();
 }

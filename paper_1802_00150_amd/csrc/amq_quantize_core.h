@@ -511,8 +511,9 @@ constexpr int kSignMaskSlots = 4;
 
 // Alg. 2 for one vector: x[j] of lane L is entry (base + j) * 64 + L (0 beyond n), NW waves cooperate with nj
 // slots each.  On return alpha holds the coefficients and lane j of each wave, in mym[i], the 64 packed codes of
-// its slot j of plane i.  FULL: every slot of this wave is there and lies inside the vector.
-template <int K, int NJ, int NW, bool FULL>
+// its slot j of plane i.  Slots below MASKED lie inside the vector; an entry of the others that does not is 0 and its u
+// is -1, below every midpoint (branches around absent slots cost a vector of 650 entries twice the time of 640).
+template <int K, int NJ, int NW, int MASKED>
 __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n, int base, int nj, int T,
                                                     float (&alpha)[K], unsigned long long (&mym)[K],
                                                     double* sh, int& phase, unsigned long long* marks) {
@@ -523,9 +524,8 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
   const double dn = (double)n;
   const double inv_n = recip_f64(dn);  // (exact for a power of two; the last binary64 digit is rounded away)
   auto mean = [&](double s) { return (float)(s * inv_n); };
-  auto there = [&](int j) { return FULL || j < nj; };
-  auto inside = [&](int j) { return FULL ? ~0ull : lanes_inside(NJ > 4 ? opaque_s(n) : n, base + j); };
-  const unsigned long long lane_inside = FULL ? ~0ull : lanes_inside(n, base + lane_id());
+  const int within = min(n - base * 64, nj * 64) - lane_id();  // this lane has an entry in slot j if j * 64 < within
+  const unsigned long long lane_inside = MASKED == NJ ? ~0ull : lanes_inside(n, base + lane_id());
 
   int u[NJ];                     // order-preserving integer of |w| with the tie rule folded in
   double wd[NJ];                 // w
@@ -536,23 +536,17 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
   int no_counts[1] = {0};
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
-    if (there(j)) {
-      const float xc = x[j] + 0.0f;  // -0.0 -> +0.0
-      const unsigned b = __float_as_uint(xc);
-      // b, or bits(|w|) - 1 = b + 0x7fffffff (mod 2^32) for a set sign bit: the smaller of the two in both cases
-      u[j] = (int)min(b, b + 0x7fffffffu);
-      wd[j] = (double)xc;
-      const unsigned long long ng = __ballot(xc < 0.0f);
-      if constexpr (NJ <= kSignMaskSlots) neg[j] = ng;
-      keep_in_lane(lane_neg, ng, j);
-      r[j] = xc;
-      sum[0] = (j == 0) ? fabs(wd[j]) : sum[0] + fabs(wd[j]);
-    } else {
-      u[j] = 0;
-      wd[j] = 0.0;
-      if constexpr (NJ <= kSignMaskSlots) neg[j] = 0ull;
-      r[j] = 0.0f;
-    }
+    const float xc = x[j] + 0.0f;  // -0.0 -> +0.0
+    const unsigned b = __float_as_uint(xc);
+    // b, or bits(|w|) - 1 = b + 0x7fffffff (mod 2^32) for a set sign bit: the smaller of the two in both cases
+    u[j] = (int)min(b, b + 0x7fffffffu);
+    if (j >= MASKED) u[j] = j * 64 < within ? u[j] : -1;
+    wd[j] = (double)xc;
+    const unsigned long long ng = __ballot(xc < 0.0f);
+    if constexpr (NJ <= kSignMaskSlots) neg[j] = ng;
+    keep_in_lane(lane_neg, ng, j);
+    r[j] = xc;
+    sum[0] = (j == 0) ? fabs(wd[j]) : sum[0] + fabs(wd[j]);
     if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
   }
   AMQ_PHASE(marks, 12);
@@ -579,31 +573,29 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
       double sr[1] = {0.0}, si[1] = {0.0};
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        if (there(j)) {
-          const unsigned long long in = inside(j);
-          unsigned long long before = 0ull;  // previous plane against the sign of w
-          if (NJ > 4 && i > 2) r[j] = opaque_v(r[j]);
-          if (i > 1) before = __ballot(r[j] < 0.0f);
-          float rn = r[j] - copysignf(a, r[j]);  // (a difference is never -0.0)
-          if (!FULL) rn = lane_bit(in) ? rn : 0.0f;
-          r[j] = rn;
-          unsigned long long f[1];
-          if (i == 1) {
-            f[0] = __ballot(u[j] >= abits);
-          } else {
-            const unsigned long long ng = __ballot(rn < 0.0f);
-            if constexpr (NJ <= kSignMaskSlots) f[0] = ~(ng ^ neg[j]);
-            else f[0] = __ballot((__float_as_int(rn) ^ __double2hiint(wd[j])) >= 0);
-            // pairs (i - 1, i) of planes beyond the first: both signs are at hand
-            add_count<NJ>(cnt[K == 3 ? 2 : (i == 2 ? 3 : 5)], (before ^ ng) & in);
-            if (K == 4 && i == 3) add_count<NJ>(cnt[4], (__ballot(u[j] >= a0bits) ^ f[0]) & in);
-          }
-          f[0] &= in;
-          add_count<NJ>(cnt[i - 1], f[0]);
-          masked_add<1>(si, wd[j], f);
-          const double ra = (double)fabsf(rn);
-          sr[0] = (j == 0) ? ra : sr[0] + ra;
+        const unsigned long long in = j < MASKED ? ~0ull : __ballot(u[j] >= 0);
+        unsigned long long before = 0ull;  // previous plane against the sign of w
+        if (NJ > 4 && i > 2) r[j] = opaque_v(r[j]);
+        if (i > 1) before = __ballot(r[j] < 0.0f);
+        float rn = r[j] - copysignf(a, r[j]);  // (a difference is never -0.0)
+        if (j >= MASKED) rn = lane_bit(in) ? rn : 0.0f;
+        r[j] = rn;
+        unsigned long long f[1];
+        if (i == 1) {
+          f[0] = __ballot(u[j] >= abits);
+        } else {
+          const unsigned long long ng = __ballot(rn < 0.0f);
+          if constexpr (NJ <= kSignMaskSlots) f[0] = ~(ng ^ neg[j]);
+          else f[0] = __ballot((__float_as_int(rn) ^ __double2hiint(wd[j])) >= 0);
+          // pairs (i - 1, i) of planes beyond the first: both signs are at hand
+          add_count<NJ>(cnt[K == 3 ? 2 : (i == 2 ? 3 : 5)], (before ^ ng) & in);
+          if (K == 4 && i == 3) add_count<NJ>(cnt[4], (__ballot(u[j] >= a0bits) ^ f[0]) & in);
         }
+        if (i > 1) f[0] &= in;
+        add_count<NJ>(cnt[i - 1], f[0]);
+        masked_add<1>(si, wd[j], f);
+        const double ra = (double)fabsf(rn);
+        sr[0] = (j == 0) ? ra : sr[0] + ra;
         if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
       }
       s[i] = si[0];
@@ -663,16 +655,13 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
       for (int t = 0; t < NT; ++t) { c[t] = 0.0; cn[t] = 0; }
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        if (there(j)) {
-          const unsigned long long in = inside(j);
-          unsigned long long ge[NT];
+        unsigned long long ge[NT];
 #pragma unroll
-          for (int t = 0; t < NT; ++t) {
-            ge[t] = __ballot(u[j] >= ct.thr[t]) & in;
-            add_count<NJ>(cn[t], ge[t]);
-          }
-          masked_add<NT>(c, wd[j], ge);
+        for (int t = 0; t < NT; ++t) {
+          ge[t] = __ballot(u[j] >= ct.thr[t]);
+          add_count<NJ>(cn[t], ge[t]);
         }
+        masked_add<NT>(c, wd[j], ge);
         if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
       }
       AMQ_PHASE(marks, 7 + 4 * it);
@@ -708,10 +697,8 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
     for (int t = 0; t < NT; ++t) ge[t] = 0ull;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      if (there(j)) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) keep_in_lane(ge[t], __ballot(u[j] >= ct.thr[t]), j);
-      }
+      for (int t = 0; t < NT; ++t) keep_in_lane(ge[t], __ballot(u[j] >= ct.thr[t]), j);
       if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
@@ -1108,10 +1095,15 @@ __device__ __forceinline__ void quantize_core(const float (&x)[NJ], int n, int b
   if constexpr (ONLINE) {
     if (full) quantize_online<K, NJ, NW, true>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
     else quantize_online<K, NJ, NW, false>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
-  } else if (full)
-    quantize_magnitudes<K, NJ, NW, true>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
-  else
-    quantize_magnitudes<K, NJ, NW, false>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+  } else if (full) {
+    quantize_magnitudes<K, NJ, NW, NJ>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+  } else {
+    // a single wave usually takes the form of its own number of slots, an even one: only the last two can be short
+    if (NW == 1 && (NJ - 2) * 64 < n)
+      quantize_magnitudes<K, NJ, NW, NW == 1 ? NJ - 2 : 0>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+    else
+      quantize_magnitudes<K, NJ, NW, 0>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+  }
 }
 
 }  // namespace amq
