@@ -211,11 +211,13 @@ int amq_stream_read_probe(const void* buf, size_t bytes, void* sink, void* strea
  */
 size_t amq_lstm_sequence_flag_offset(int64_t I, int64_t H, int64_t B, int k_a);
 /*
- * Workspace with which amq_lstm_sequence takes W_x x_t off the recurrent chain for B > 1 (Eq. 6: the
- * inputs do not depend on the recurrence): amq_lstm_workspace_bytes plus room for the codes of two
- * consecutive inputs and the x-side sums of one step.  With a smaller workspace (at least
- * amq_lstm_workspace_bytes) the call runs the steps one after the other; the results are the same bit
- * for bit.
+ * Workspace of the faster forms of amq_lstm_sequence for B > 1.  Where the grid fits the chip (vectors of at most
+ * 2048 entries, 1- to 3-bit codes, about 4096 hidden units times batch tiles of 16), pieces of about 4096 / B steps
+ * run in one launch whose workgroups stay resident and exchange h_t and its codes through the workspace; such
+ * launches take turns on a device, and if the workgroups cannot all become resident a launch that follows computes
+ * the piece on its own, so the result does not depend on what else runs.  Otherwise (and on a stream that is being
+ * captured) W_x x_t is taken off the recurrent chain with two launches per step.  With a smaller workspace (at least
+ * amq_lstm_workspace_bytes) the call runs the steps one after the other.  The arithmetic is the same in all forms.
  */
 size_t amq_lstm_sequence_workspace_bytes(int64_t I, int64_t H, int64_t B, int k_a);
 int amq_lstm_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp,

@@ -103,6 +103,35 @@ StepWs carve(void* ws, int64_t I, int64_t H, int64_t B, int k_a, int gates, int 
   return w;
 }
 
+// Steps of a batched sequence that go through one launch (and, in a language model, through the output layer)
+// together: as many as give about 4096 rows.
+int64_t piece_steps(int64_t B) { return B >= 4096 ? 1 : 4096 / B; }
+
+// What the resident sequence kernel needs for a piece: the codes of all its inputs and the kernel's own scratch.
+// Absent (no bytes) for the shapes it never takes.
+struct ResidentWs {
+  uint32_t* xq;    // [k_a][rows][wpr(I)]
+  float* xbeta;    // [rows][k_a]
+  char* scratch;
+  size_t total;
+};
+
+ResidentWs carve_resident(void* ws, int64_t I, int64_t H, int64_t B, int k_a) {
+  ResidentWs w{};
+  if (B < 2 || B > 4096 || I > 2048 || H > 2048 || k_a > 3) return w;
+  char* base = static_cast<char*>(ws);
+  auto take = [&](size_t bytes) {
+    char* p = base ? base + w.total : nullptr;
+    w.total += up256(bytes);
+    return p;
+  };
+  const size_t rows = (size_t)(piece_steps(B) * B);
+  w.xq = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * k_a * rows * amq_wpr(I)));
+  w.xbeta = reinterpret_cast<float*>(take(sizeof(float) * rows * k_a));
+  w.scratch = take(amq::seqw_scratch(nullptr, H, B, k_a).bytes);
+  return w;
+}
+
 // Workspace of a batched sequence with given inputs: the step's regions, then what the split step keeps
 // between launches -- codes and coefficients of two consecutive inputs, the x-side sums of one step.
 struct SeqWs {
@@ -110,6 +139,7 @@ struct SeqWs {
   uint32_t* xq[2];
   float* xbeta[2];
   float* xsum;
+  ResidentWs resident;
   size_t total;
 };
 
@@ -128,7 +158,8 @@ SeqWs carve_seq(void* ws, int64_t I, int64_t H, int64_t B, int k_a, int gates = 
     w.xbeta[i] = reinterpret_cast<float*>(take(sizeof(float) * (size_t)B * k_a));
   }
   w.xsum = reinterpret_cast<float*>(take(sizeof(float) * (size_t)B * H * 4));
-  w.total = off;
+  w.resident = carve_resident(base ? base + off : nullptr, I, H, B, k_a);
+  w.total = off + w.resident.total;
   return w;
 }
 
@@ -370,6 +401,54 @@ static amq::BmvArgs lstm_args(const uint32_t* Wxp, const float* alpha_x, const u
   return b;
 }
 
+// Whether a sequence takes the resident kernel: a shape it has room for, and a stream that is not being captured (it
+// orders itself after the launches of the kind on other streams, which a graph cannot).
+static bool resident_sequence(const ResidentWs& w, int64_t I, int64_t H, int64_t B, int k_w, int k_a, int epi,
+                              hipStream_t s) {
+  if (!w.total || !amq::seqw_supported(I, H, B, k_w, k_a, epi)) return false;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+}
+
+// One piece of `n` steps on it, given the codes of the piece's inputs (in w) and, in b, everything else.
+static int resident_piece(const ResidentWs& w, const amq::BmvArgs& b, int64_t n, int k_w, int k_a, int epi, int T, float* h,
+                          float* c, float* hs, hipStream_t s) {
+  amq::SeqWArgs q{};
+  q.x = b.blk[0];
+  q.x.Xp = w.xq;
+  q.x.beta = w.xbeta;
+  q.h = b.blk[1];
+  q.rows = n * b.batch;
+  q.H = (int)b.H;
+  q.batch = b.batch;
+  q.steps = (int)n;
+  q.bias0 = b.bias0;
+  q.bias1 = b.bias1;
+  q.h0 = h;
+  q.c0 = c;
+  q.hs = hs;
+  q.T = T;
+  return hip_status(amq::launch_seqw(q, amq::seqw_scratch(w.scratch, b.H, b.batch, k_a), k_w, k_a, epi, s));
+}
+
+// A whole sequence of given inputs xs [steps][B][I].
+static int resident_run(const ResidentWs& w, const amq::BmvArgs& b, const float* xs, int64_t steps, int k_w, int k_a, int epi,
+                        int T, float* h, float* c, float* hs, hipStream_t s) {
+  const int64_t B = b.batch, I = b.blk[0].n, piece = piece_steps(B);
+  for (int64_t t0 = 0; t0 < steps; t0 += piece) {
+    const int64_t n = steps - t0 < piece ? steps - t0 : piece;
+    amq::QuantArgs q{};
+    q.seg[0] = amq::QuantSeg{xs + t0 * B * I, I, (int)I, (int)(n * B), w.xq, w.xbeta};
+    q.T = T;
+    q.mode = amq::kQuantFull;
+    int st = hip_status(amq::launch_quantize(q, k_a, s));
+    if (st != AMQ_OK) return st;
+    st = resident_piece(w, b, n, k_w, k_a, epi, T, h, c, hs ? hs + t0 * B * b.H : nullptr, s);
+    if (st != AMQ_OK) return st;
+  }
+  return AMQ_OK;
+}
+
 static int lstm_fused_launch(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp,
                              const float* alpha_h, int64_t I, int64_t H, int k_w, const float* bias,
                              const uint32_t* Xp, const float* beta_x, const uint32_t* Hp, const float* beta_h,
@@ -545,6 +624,8 @@ int amq_lstm_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t*
     const SeqWs sw = carve_seq(workspace, I, H, B, k_a);
     const amq::BmvArgs probe = lstm_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias, sw.xq[0], sw.xbeta[0], w.hp, w.beta_h,
                                          c, B, h, c, nullptr);
+    if (workspace_bytes >= sw.total && resident_sequence(sw.resident, I, H, B, k_w, k_a, amq::kEpiLstm, s))
+      return resident_run(sw.resident, probe, xs, steps, k_w, k_a, amq::kEpiLstm, T, h, c, hs, s);
     if (workspace_bytes >= sw.total && amq::step_split_supported(probe, k_w, k_a, amq::kEpiLstm)) {
       auto step_args = [&](int64_t t) {
         amq::BmvArgs b = probe;
@@ -689,6 +770,8 @@ int amq_gru_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t* 
   const SeqWs sw = carve_seq(workspace, I, H, B, k_a, 3, 2);
   const amq::BmvArgs probe = gru_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, sw.xq[0], sw.xbeta[0], w.hp,
                                       w.beta_h, h, B, h);
+  if (workspace_bytes >= sw.total && resident_sequence(sw.resident, I, H, B, k_w, k_a, amq::kEpiGru, s))
+    return resident_run(sw.resident, probe, xs, steps, k_w, k_a, amq::kEpiGru, T, h, nullptr, hs, s);
   if (workspace_bytes >= sw.total && amq::step_split_supported(probe, k_w, k_a, amq::kEpiGru)) {
     // As in amq_lstm_sequence: the inputs are given, so W_x x_t leaves the recurrent chain.  Front launch of
     // step t: quantize h_{t-1}, quantize x_{t+1}, x-side sums of step t; back launch: h-side sums + the
@@ -1013,8 +1096,7 @@ int amq_lm_step(const uint32_t* Ep, const float* alpha_e, int64_t vocab, int64_t
 // Steps of a sequence whose hidden states go through the output layer together: as many as the
 // batch-1 sequence kernel takes per launch, otherwise as many as give about 4096 rows.
 static int64_t lm_piece_steps(int64_t B) {
-  if (B == 1) return amq::kSeqGMaxSteps;
-  return B >= 4096 ? 1 : 4096 / B;
+  return B == 1 ? amq::kSeqGMaxSteps : piece_steps(B);
 }
 
 // Workspace of amq_lm_sequence: that of a step, then every h_t of a piece of the sequence and the
@@ -1028,6 +1110,7 @@ struct LmSeqWs {
   uint32_t* xq[2];
   float* xbeta[2];
   float* xsum;
+  ResidentWs resident;
   size_t total;
 };
 static LmSeqWs carve_lm_seq(void* ws, int64_t E, int64_t H, int64_t V, int64_t B, int k_a, int k_as) {
@@ -1050,7 +1133,8 @@ static LmSeqWs carve_lm_seq(void* ws, int64_t E, int64_t H, int64_t V, int64_t B
     w.xbeta[i] = reinterpret_cast<float*>(take(sizeof(float) * (size_t)B * k_a));
   }
   w.xsum = reinterpret_cast<float*>(take(sizeof(float) * (size_t)B * H * 4));
-  w.total = off;
+  w.resident = carve_resident(base ? base + off : nullptr, E, H, B, k_a);
+  w.total = off + w.resident.total;
   return w;
 }
 
@@ -1229,9 +1313,20 @@ static int lm_sequence_impl(const uint32_t* Ep, const float* alpha_e, int64_t vo
     return hip_status(amq::launch_step_back(b, k_w, k_a, amq::kEpiLstm, s));
   };
   const int64_t piece = lm_piece_steps(B);
+  const bool resident = resident_sequence(lw.resident, E, H, B, k_w, k_a, amq::kEpiLstm, s);
   for (int64_t t0 = 0; t0 < steps; t0 += piece) {
     const int64_t n = steps - t0 < piece ? steps - t0 : piece;
-    for (int64_t t = 0; t < n; ++t) {
+    if (resident) {
+      amq::QuantArgs q{};
+      q.mode = amq::kQuantFull;
+      q.gather = amq::GatherSeg{Ep, alpha_e, vocab, reinterpret_cast<const long long*>(ids + t0 * B), (int)E, (int)(n * B),
+                                lw.resident.xq, lw.resident.xbeta};
+      st = hip_status(amq::launch_quantize(q, k_a, s));
+      if (st != AMQ_OK) return st;
+      st = resident_piece(lw.resident, probe, n, k_w, k_a, amq::kEpiLstm, T, h, c, lw.hs, s);
+      if (st != AMQ_OK) return st;
+    }
+    for (int64_t t = 0; t < n && !resident; ++t) {
       st = split ? split_step(t0 + t, lw.hs + t * B * H)
                  : lm_recurrent_launch(Ep, alpha_e, vocab, E, Wxp, alpha_x, Whp, alpha_h, H, k_w, bias,
                                        ids + (t0 + t) * B, h, c, B, k_a, T, lw.hs + t * B * H, w, s);

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <mutex>
 
 namespace amq {
 
@@ -245,6 +246,7 @@ struct SeqGArgs {
   float* xbeta;         // [steps][k_a]: their coefficients
   int first_piece;      // non-zero: also clear the give-up flag (once per API call; a later piece of the
                         // same call must see a flag an earlier piece raised)
+  unsigned* lock;       // filled by launch_lstm_seqg
   unsigned spin_limit;  // filled by launch_lstm_seqg: polls of a wait before it gives up
 };
 bool lstm_seqg_supported(long long I, long long H, long long B, int k_w, int k_a);
@@ -255,6 +257,60 @@ void set_seqg_spin_limit(unsigned polls);
 // After a launch of the sequence kernel and whatever consumed its hs: if the give-up flag is set,
 // overwrite out[0 .. count) with NaN (results computed from an incomplete recurrence must not look valid).
 hipError_t launch_seqg_poison(const unsigned* sync, float* out, long long count, hipStream_t s);
+
+// Polls a wait of the resident sequence kernels may take (see set_seqg_spin_limit).
+unsigned sequence_spin_limit();
+
+// Launches whose workgroups wait for each other need all of them resident, so one at a time runs per device: a small
+// kernel before each takes a lock in device memory (null: not available), the last kernel of the group returns it.  The
+// launches of a group are queued together, under resident_launches().
+unsigned* resident_lock();
+std::mutex& resident_launches();
+constexpr unsigned long long kLockTicks = 20000000ull;  // 0.2 s of the 100 MHz clock
+__device__ __forceinline__ bool take_resident_lock(unsigned* lock) {
+  if (!lock) return true;
+  const unsigned long long start = wall_clock64();
+  for (;;) {
+    unsigned free = 0u;
+    if (__hip_atomic_compare_exchange_strong(lock, &free, 1u, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      return true;
+    if (wall_clock64() - start > kLockTicks) return false;
+    __builtin_amdgcn_s_sleep(32);
+  }
+}
+__device__ __forceinline__ void give_resident_lock(unsigned* lock) {
+  if (lock) __hip_atomic_store(lock, 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// ---- whole sequences of a batch in one launch spread over the chip (amq_seqw.hip) ---------------
+struct SeqWArgs {
+  BmvBlock x, h;        // weights; x: codes and coefficients of all inputs, [k_a][rows][wpr(I)] and [rows][k_a], row
+                        // step * batch + entry; h: Wp, alpha and n only
+  long long rows;
+  int H, batch, steps;
+  const float* bias0;   // LSTM: [4H]; GRU: bias_x [3H] (nullable)
+  const float* bias1;   // GRU: bias_h [3H] (nullable)
+  float* h0;            // [batch][H] in: initial state, out: final state
+  float* c0;            // LSTM: the same
+  float* hs;            // [steps][batch][H] or null
+  int T;
+  // filled by launch_seqw
+  unsigned* flag;
+  unsigned long long* hbuf;  // [2][batch][H] {value, tag}: h_t as published
+  unsigned long long* cbuf;  // [2][tile][16][..] {word, tag}: codes of h_{t-1} and their coefficients, [k_a][wpr(H)] + [k_a]
+  float* save_h;
+  float* save_c;
+  unsigned limit;
+};
+struct SeqWScratch {
+  unsigned* flag;
+  unsigned long long *hbuf, *cbuf;
+  float *save_h, *save_c;
+  size_t pair_bytes, bytes;  // bytes: size of the whole region (256-byte aligned base)
+};
+SeqWScratch seqw_scratch(void* base, long long H, long long B, int k_a);
+bool seqw_supported(long long I, long long H, long long B, int k_w, int k_a, int epi);
+hipError_t launch_seqw(SeqWArgs a, const SeqWScratch& w, int k_w, int k_a, int epi, hipStream_t s);
 
 // ---- the recurrent step of a sequence with given inputs, cut along the operand blocks ----------
 // Front launch: quantizes the vectors of q (seg[0] = h_{t-1}, seg[1] = a later x, count 0 for none) and of

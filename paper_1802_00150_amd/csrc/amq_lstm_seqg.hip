@@ -187,11 +187,25 @@ __device__ __forceinline__ bool quantize_wg(const void* src_v, unsigned tag, uns
 
 // Before a launch: clears the arrival bytes and the tags of the published state; the give-up flag only
 // for the first launch of an API call.
-__global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, int H, int clear_flag) {
+// Takes the lock of the resident launches (see take_resident_lock; without it the launch goes ahead all the same, as
+// its waits are bounded).
+constexpr int kLeft = 1 + kSeqGMaxGrid / 4;  // words of sync after the arrival bytes: workgroups that have left,
+constexpr int kLocked = kLeft + 1;           // and whether the lock is held for this launch
+__global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, int H, int clear_flag, unsigned* lock) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
-  if (t == 0 && clear_flag) sync[0] = 0u;
+  if (t == 0) {
+    if (clear_flag) sync[0] = 0u;
+    sync[kLeft] = 0u;
+    sync[kLocked] = (lock && take_resident_lock(lock)) ? 1u : 0u;
+  }
   for (int i = 1 + t; i < 1 + kSeqGMaxGrid / 4; i += nt) sync[i] = 0u;
   for (int i = t; i < 2 * H; i += nt) hbuf[i] = 0ull;
+}
+
+// One thread of a workgroup that is about to leave: the last one returns the lock.
+__device__ __forceinline__ void leave(unsigned* sync, unsigned* lock) {
+  if (sync[kLocked] == 0u) return;
+  if (__hip_atomic_fetch_add(sync + kLeft, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) give_resident_lock(lock);
 }
 
 __global__ void seqg_poison_kernel(const unsigned* sync, float* out, long long count) {
@@ -230,7 +244,10 @@ __global__ __launch_bounds__(64 * kGWaves, 2) void lstm_seqg_kernel(SeqGArgs a) 
   __shared__ unsigned gave_up;
   if (threadIdx.x == 0) gave_up = get_u(a.sync);
   __syncthreads();
-  if (gave_up != 0u) return;
+  if (gave_up != 0u) {
+    if (threadIdx.x == 0) leave(a.sync, a.lock);
+    return;
+  }
   const unsigned limit = a.spin_limit;
 
   // ---- once: this lane's plane chunks and coefficients, the cell lane's bias and state
@@ -340,11 +357,13 @@ __global__ __launch_bounds__(64 * kGWaves, 2) void lstm_seqg_kernel(SeqGArgs a) 
     a.h[unit] = hlast;
     a.c[unit] = cst;
   }
+  if (tid == 0) leave(a.sync, a.lock);
 }
 
 template <int KW, int KA>
 hipError_t launch_kk(const SeqGArgs& a, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(seqg_reset_kernel, dim3(8), dim3(256), 0, s, a.sync, a.hbuf, a.H, a.first_piece);
+  std::lock_guard<std::mutex> together(resident_launches());
+  hipLaunchKernelGGL(seqg_reset_kernel, dim3(8), dim3(256), 0, s, a.sync, a.hbuf, a.H, a.first_piece, a.lock);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((lstm_seqg_kernel<KW, KA>), dim3(grid), dim3(64 * kGWaves), 0, s, a);
@@ -384,6 +403,7 @@ hipError_t launch_seqg_poison(const unsigned* sync, float* out, long long count,
 hipError_t launch_lstm_seqg(SeqGArgs a, int k_w, int k_a, hipStream_t s) {
   a.lg = seqg_lg(a.I, a.H);
   a.spin_limit = g_spin_limit.load();
+  a.lock = resident_lock();
   const int units_per_wg = kGWaves * (8 >> a.lg);
   const int grid = (a.H + units_per_wg - 1) / units_per_wg;
   if (grid > kSeqGMaxGrid || a.steps > kSeqGMaxSteps) return hipErrorInvalidValue;

@@ -1,0 +1,725 @@
+// Whole recurrent sequences of a batch in one launch, spread over the chip (Eq. 6 over a sequence, Sec. 4).
+//
+// With two launches per step (amq_step.hip) a step of a 1024-unit LSTM at batch 64 costs 9.4 us, of which the matrix
+// work is half a microsecond: the rest is launch gaps, the cold misses every new kernel starts with, weights fetched
+// and turned into operand layout again at every step, and state that goes through memory.  Here the grid stays
+// resident for the whole sequence:
+//   - a workgroup of 4 waves owns one batch tile (16 entries) and 4 row blocks (16 hidden units, all gates), one row
+//     block per wave; the packed weights of both operand blocks, their coefficients, the biases and the cell state
+//     stay in registers, the weights already in operand layout;
+//   - the inputs do not depend on the recurrence: their codes are all formed (or looked up) before this launch, and the
+//     x-side sums of step t are formed while the codes of h_{t-1} are under way;
+//   - per step two exchanges: every workgroup publishes its h_t; the workgroup in charge of a batch entry (one of
+//     those of its tile) gathers the entry's whole h_t, quantizes it (the shared quantizer core on 4 waves) and
+//     publishes its codes, which all workgroups of the tile gather as matrix operands.
+// What is exchanged are 8-byte {value, step tag} pairs, each written with one device-scope store; the readers poll
+// the pairs they need until all carry the tag of the step (one way across the chip: about 0.55 us measured), so the
+// data is its own arrival signal: no barrier, no ordering between locations.  Two buffers in turn suffice: whoever
+// writes the pairs of step t + 2 has seen data of step t + 1 that depend on every reader of step t.
+//
+// The arithmetic and its order are those of the per-step kernels: the results are the same bit for bit.
+//
+// All workgroups must be resident at once: the host launches this only where the grid fits the chip, and a lock on the
+// device lets one such launch run at a time (the reset kernel takes it, the recovery kernel returns it).  Should the
+// chip be shared in a way this cannot see, the waits are bounded: a workgroup that gives up raises a flag, everyone
+// leaves, and the launch that always follows (seqw_recover_kernel) computes the piece again from the saved initial
+// state, one workgroup per batch entry, with no exchange between workgroups -- slow, but it depends on nobody; without
+// the flag it returns at once.
+#include <atomic>
+#include <mutex>
+
+#include "amq_launch.h"
+#include "amq_quantize_body.h"
+
+namespace amq {
+
+namespace {
+
+constexpr int kWBlocks = 4;             // row blocks per workgroup
+constexpr int kWWaves = 2 * kWBlocks;   // waves per workgroup: one per row block and operand block
+constexpr int kBlocksPad = kWBlocks + 1;
+constexpr int kWTurn = 9;       // 16-byte units per row in the LDS piece that turns rows into operands (128 B + 16 B pad)
+
+// Pairs that the codes and coefficients of one batch entry take in the exchange buffer: whole cache lines of 16.
+__host__ __device__ constexpr int seqw_entry_pairs(int k_a, int wpr) { return (k_a * (wpr + 1) + 15) & ~15; }
+
+__device__ __forceinline__ void put_pair(unsigned long long* p, unsigned value, unsigned tag) {
+  __hip_atomic_store(p, ((unsigned long long)tag << 32) | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long get_pair(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One failed poll: counts it, and decides whether to give up (too many, or somebody else has).
+__device__ __forceinline__ bool poll_again(unsigned& spins, unsigned limit, unsigned* flag) {
+  ++spins;
+  if (spins > limit) {
+    __hip_atomic_store(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return false;
+  }
+  return (spins & 63u) != 0 || __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+}
+
+// Products of one wave's row block (16 rows) with one batch tile: packed weights in operand layout, activations as the
+// expanded image in LDS (see amq_pair_body.h for both layouts).  The accumulators start at minus the contribution of
+// the positions past the end of the vectors, so they end as the dot products of the codes.
+template <int KW, int KA, int NC>
+__device__ __forceinline__ void contract(const uint4 (&araw)[NC][KW][2], const uint4* image, int l16, int l4, int n,
+                                         v4f (&acc)[KW][KA]) {
+  constexpr int kAllSteps = NC * kSteps;
+  const int halves = (n + 511) >> 9;
+  const float start = (float)(n - halves * 512);
+#pragma unroll
+  for (int i = 0; i < KW; ++i)
+#pragma unroll
+    for (int j = 0; j < KA; ++j) acc[i][j] = v4f{start, start, start, start};
+  const uint4* const my = image + 16 * l4;
+  auto b_operand = [&](int j, int t) { return my[(j * kAllSteps + t) * 64 + (l16 ^ ((l4 << 1) | (((t >> 2) & 1) << 3)))]; };
+  uint4 aop[KW], anx[KW], bop[KA], bnx[KA];
+#pragma unroll
+  for (int j = 0; j < KA; ++j) bop[j] = b_operand(j, 0);
+#pragma unroll
+  for (int i = 0; i < KW; ++i) aop[i] = expand4_signed(word_of(araw[0][i], 0));
+#pragma unroll
+  for (int half = 0; half < 2 * NC; ++half) {
+    if (half > 0 && half >= halves) break;  // (uniform)
+#pragma unroll
+    for (int t = 4 * half; t < 4 * half + 4; ++t) {
+      if (t + 1 < kAllSteps) {
+#pragma unroll
+        for (int j = 0; j < KA; ++j) bnx[j] = b_operand(j, t + 1);
+#pragma unroll
+        for (int i = 0; i < KW; ++i) anx[i] = expand4_signed(word_of(araw[(t + 1) / kSteps][i], (t + 1) % kSteps));
+      }
+#pragma unroll
+      for (int i = 0; i < KW; ++i)
+#pragma unroll
+        for (int j = 0; j < KA; ++j) acc[i][j] = mfma_fp4(aop[i], bop[j], acc[i][j]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < KW; ++i) aop[i] = anx[i];
+#pragma unroll
+      for (int j = 0; j < KA; ++j) bop[j] = bnx[j];
+    }
+  }
+  settle_accumulators<16>();
+#pragma unroll
+  for (int i = 0; i < KW; ++i)
+#pragma unroll
+    for (int j = 0; j < KA; ++j) asm volatile("" : "+v"(acc[i][j]));
+}
+
+// Keeps the compiler from expanding these words once, ahead of the loop over the steps, and holding the result.
+template <int NC, int KW>
+__device__ __forceinline__ void keep_packed(uint4 (&w)[NC][KW][2]) {
+#pragma unroll
+  for (int ch = 0; ch < NC; ++ch)
+#pragma unroll
+    for (int i = 0; i < KW; ++i)
+#pragma unroll
+      for (int v = 0; v < 2; ++v) asm volatile("" : "+v"(w[ch][i][v].x), "+v"(w[ch][i][v].y), "+v"(w[ch][i][v].z), "+v"(w[ch][i][v].w));
+}
+
+// y_r = sum_i alpha_ri sum_j beta_j d_ij of this lane's four rows (the gates of its hidden unit) and batch entry.
+template <int KW, int KA>
+__device__ __forceinline__ void weigh(const v4f (&acc)[KW][KA], const float (&al)[4][KW], const float (&bt)[KA],
+                                      float (&y)[4]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < KW; ++i) {
+      float inner = 0.0f;
+#pragma unroll
+      for (int j = 0; j < KA; ++j) inner = fmaf(bt[j], acc[i][j][r], inner);
+      s = fmaf(al[r][i], inner, s);
+    }
+    y[r] = s;
+  }
+}
+
+// Eq. 6 on one unit's sums; bias0 / bias1 as the per-step kernels take them.  h: h_{t-1} in, h_t out.
+template <int EPI>
+__device__ __forceinline__ void cell(const float (&yx)[4], const float (&yh)[4], const float (&b0)[4], const float (&b1)[4],
+                                     float& h, float& c) {
+  if constexpr (EPI == kEpiLstm) {
+    const float gi = sigmoidf_dev(yx[0] + yh[0] + b0[0]);
+    const float gf = sigmoidf_dev(yx[1] + yh[1] + b0[1]);
+    const float go = sigmoidf_dev(yx[2] + yh[2] + b0[2]);
+    const float gg = tanhf_dev(yx[3] + yh[3] + b0[3]);
+    c = fmaf(gf, c, gi * gg);
+    h = go * tanhf_dev(c);
+  } else {
+    const float rg = sigmoidf_dev(yx[0] + yh[0] + b0[0] + b1[0]);
+    const float z = sigmoidf_dev(yx[1] + yh[1] + b0[1] + b1[1]);
+    const float nn = tanhf_dev(fmaf(rg, yh[2] + b1[2], yx[2] + b0[2]));
+    h = fmaf(z, h - nn, nn);
+  }
+}
+
+// Whether the weights stay in registers as matrix operands (32 registers per plane and stretch) or packed: as far as the
+// registers go.
+template <int KW, int KA, int NC>
+constexpr bool kExpandedOnce = NC == 1 && KW * KA < 9;
+
+template <int KW, int KA, int NC>
+constexpr size_t seqw_lds() {
+  return sizeof(uint4) * (2 * KA * NC * kSteps * 64);
+}
+
+// NC: stretches of 1024 entries of the longer operand block (1 or 2).  Waves 0 .. 3 take the h side, the cell and the
+// quantizer, waves 4 .. 7 the x side of the next step.
+template <int KW, int KA, int EPI, int NC>
+__global__ __launch_bounds__(64 * kWWaves, 2) void seqw_kernel(SeqWArgs a) {
+  constexpr int NG = (EPI == kEpiGru) ? 3 : 4;
+  constexpr int kImage = KA * NC * kSteps * 64;
+  constexpr int NJ = 4 * NC;  // slots per lane of the quantizer
+  __shared__ double sh[2 * kExchange<kWBlocks>];
+  __shared__ int dead;
+  __shared__ uint32_t codes[KA * 32 * NC + KA];            // codes of one entry, then its coefficients
+  __shared__ float hout[kTileB][4 * kBlocksPad];           // h_t of the workgroup's units
+  __shared__ float4 xsum[2][kWBlocks][64];  // x-side sums of two consecutive steps
+  extern __shared__ __attribute__((aligned(16))) uint4 lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool xwave = wv >= kWBlocks;
+  const int blk = wv & (kWBlocks - 1);            // row block of the workgroup
+  uint4* const image = lds + (xwave ? kImage : 0);  // activations of this wave's side
+  static_assert(kWBlocks * kTileB * kWTurn <= 2 * kImage, "the pieces that turn the weights borrow the images");
+  const int l16 = lane & 15, l4 = lane >> 4;
+  const int H = a.H, batch = a.batch, G = gridDim.x, bx = blockIdx.x, tile = blockIdx.y;
+  const int b0 = tile * kTileB;
+  const int ncols = batch - b0 < kTileB ? batch - b0 : kTileB;
+  const int rb = bx * kWBlocks + blk;
+  const int unit = rb * 4 + l4;
+  const bool uok = unit < H, bok = l16 < ncols;
+  const int col = bok ? l16 : ncols - 1;         // this lane's batch entry (clamped)
+  const int uc = uok ? unit : 0;
+  const bool own = uok && bok && !xwave;
+  unsigned* const flag = a.flag;
+  const int n = xwave ? a.x.n : H;               // vector length of this wave's side
+  const int wq = (n + 127) >> 7;                 // 16-byte pieces per row
+  const int piece0 = lane & 7;
+
+  // ---- once: this wave's weights in operand layout (rows through a padded piece of LDS, amq_pair_body.h; four waves
+  // at a time), coefficients, state
+  uint4 w[NC][KW][2];
+  {
+    int u = rb * 4 + ((lane >> 3) & 3);
+    u = u < H ? u : H - 1;
+    const char* Wb = reinterpret_cast<const char*>(xwave ? a.x.Wp : a.h.Wp);
+    const size_t plane = (size_t)NG * H * wq * 16;
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      int g = 2 * v + (lane >> 5);
+      g = g < NG ? g : NG - 1;
+#pragma unroll
+      for (int ch = 0; ch < NC; ++ch) {
+        const int p = 8 * ch + piece0;
+        const unsigned off = (unsigned)((g * H + u) * wq + (p < wq ? p : 0)) * 16u;
+#pragma unroll
+        for (int i = 0; i < KW; ++i) w[ch][i][v] = *reinterpret_cast<const uint4*>(Wb + i * plane + off);
+      }
+    }
+  }
+  if (tid == 0) dead = 0;
+  float al[4][KW], bs0[4], bs1[4];
+  {
+    const float* alpha = xwave ? a.x.alpha : a.h.alpha;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = (r < NG ? r : NG - 1) * H + uc;
+#pragma unroll
+      for (int i = 0; i < KW; ++i) al[r][i] = alpha[row * KW + i];
+      bs0[r] = a.bias0 ? a.bias0[row] : 0.0f;
+      bs1[r] = (EPI == kEpiGru && a.bias1) ? a.bias1[row] : 0.0f;
+    }
+  }
+  const size_t state = (size_t)(b0 + col) * H + uc;
+  float h = a.h0[state], c = EPI == kEpiLstm ? a.c0[state] : 0.0f;
+  if (own) {
+    a.save_h[state] = h;
+    if (EPI == kEpiLstm) a.save_c[state] = c;
+  }
+#pragma unroll
+  for (int side = 0; side < 2; ++side) {
+    if (xwave == (side == 1)) {
+      uint4* const mine = lds + blk * (kTileB * kWTurn);
+      const int row = 4 * ((lane >> 3) & 3) + (lane >> 5);
+#pragma unroll
+      for (int ch = 0; ch < NC; ++ch) {
+        const uint32_t keep = 8 * ch + piece0 < wq ? 0xffffffffu : 0u;
+#pragma unroll
+        for (int i = 0; i < KW; ++i) {
+#pragma unroll
+          for (int v = 0; v < 2; ++v) {
+            const uint4 t = w[ch][i][v];
+            mine[(row + 2 * v) * kWTurn + piece0] = make_uint4(t.x & keep, t.y & keep, t.z & keep, t.w & keep);
+          }
+#pragma unroll
+          for (int v = 0; v < 2; ++v) w[ch][i][v] = mine[l16 * kWTurn + l4 + 4 * v];
+        }
+      }
+    }
+    lds_barrier();
+  }
+
+  if (*flag != 0u) return;  // (the lock could not be had)
+
+  // ---- codes of the inputs (x waves), [plane][step * batch + entry][piece]: the tile is KA * NC * 2 requests of 1 KiB
+  // (plane, stretch, half of the tile; lane -> entry, 16-byte piece), dealt to the four x waves in turn
+  constexpr int kReq = KA * NC * 2;
+  constexpr int kPer = (kReq + kWBlocks - 1) / kWBlocks;
+  uint4 xw[kPer];
+  float beta_next = 0.0f;
+  auto request_inputs = [&](int t) {
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      int idx = blk + q * kWBlocks;
+      idx = idx < kReq ? idx : kReq - 1;
+      const int v = idx & 1, ch = (idx >> 1) % NC, j = (idx >> 1) / NC;
+      int cc = 8 * v + (lane >> 3);
+      cc = cc < ncols ? cc : ncols - 1;
+      const int p = 8 * ch + piece0;
+      const char* src = reinterpret_cast<const char*>(a.x.Xp) + ((size_t)j * a.rows + (size_t)t * batch + b0) * wq * 16;
+      xw[q] = *reinterpret_cast<const uint4*>(src + (unsigned)(cc * wq + (p < wq ? p : 0)) * 16u);
+    }
+    beta_next = a.x.beta[((size_t)t * batch + b0 + col) * KA + (l4 < KA ? l4 : KA - 1)];
+  };
+  auto expand_inputs = [&]() {
+    const int pb = piece0 & 3, th = piece0 >> 2;
+    const int swz = (pb << 1) | (th << 3);
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      int idx = blk + q * kWBlocks;
+      idx = idx < kReq ? idx : kReq - 1;
+      const int ch = (idx >> 1) % NC;
+      const uint32_t keep = 8 * ch + piece0 < wq ? 0xffffffffu : 0u;
+      uint4* dst = image + ((idx >> 1) * kSteps + 4 * th) * 64 + 16 * pb + ((8 * (idx & 1) + (lane >> 3)) ^ swz);
+      dst[0 * 64] = expand4_signed(xw[q].x & keep);
+      dst[1 * 64] = expand4_signed(xw[q].y & keep);
+      dst[2 * 64] = expand4_signed(xw[q].z & keep);
+      dst[3 * 64] = expand4_signed(xw[q].w & keep);
+    }
+  };
+  // this wave's sums of its row block and tile from its image
+  auto sums = [&](float beta, float (&y)[4]) {
+    v4f acc[KW][KA];
+    float bt[KA];
+#pragma unroll
+    for (int j = 0; j < KA; ++j) bt[j] = __shfl(beta, 16 * j + l16, kWave);
+    if constexpr (!kExpandedOnce<KW, KA, NC>) keep_packed(w);
+    contract<KW, KA, NC>(w, image, l16, l4, n, acc);
+    weigh<KW, KA>(acc, al, bt, y);
+  };
+
+  // ---- which entries of its tile this workgroup quantizes: spread over the workgroups of the tile
+  const int spread = G / ncols;
+  const int q_first = spread > 0 ? (bx % spread == 0 ? bx / spread : ncols) : bx;
+  const int q_next = spread > 0 ? ncols : G;
+  const int wprH = 4 * ((H + 127) >> 7);
+  const int nslots = wprH >> 1;
+  const int nj = (nslots + kWBlocks - 1) / kWBlocks;
+  const int base = blk * nj;
+  const size_t hhalf = (size_t)batch * H;
+  const int centry = seqw_entry_pairs(KA, wprH);
+  const size_t chalf = (size_t)gridDim.y * kTileB * centry;
+  int phase = 0;
+  // publishing h_t: thread -> entry and unit
+  const int hp_unit = 4 * kWBlocks * bx + (tid & 15), hp_col = (tid >> 4) & 15;
+  const bool hp_ok = !xwave && hp_unit < H && hp_col < ncols;
+  const size_t hp_at = (size_t)(b0 + (hp_ok ? hp_col : 0)) * H + (hp_ok ? hp_unit : 0);
+
+  // ---- gathering the codes of a step (h waves): thread -> word of the row and entry; the same bytes land where
+  // expand_inputs puts those of the inputs
+  constexpr int kWords = 32 * NC;                   // words of a row, padding included
+  constexpr int kColsPer = 64 * kWBlocks / kWords;  // entries per request
+  constexpr int kColReq = kTileB / kColsPer;        // requests per plane
+  constexpr int kGather = KA * kColReq;
+  const int gt = tid & (64 * kWBlocks - 1);
+  const int gw = gt & (kWords - 1), gc = gt / kWords;
+  const bool gok = gw < wprH;
+  unsigned goff[kColReq];
+#pragma unroll
+  for (int k = 0; k < kColReq; ++k) {
+    const int cc = k * kColsPer + gc;
+    goff[k] = (unsigned)((cc < ncols ? cc : ncols - 1) * centry + (gok ? gw : 0)) * 8u;
+  }
+  const unsigned gboff = (unsigned)(col * centry + KA * wprH + (l4 < KA ? l4 : KA - 1)) * 8u;
+  const int gdst = ((gw >> 5) * kSteps + 4 * ((gw >> 4) & 1) + (gw & 3)) * 64 + 16 * ((gw >> 2) & 3);
+  const int gswz = (((gw >> 2) & 3) << 1) | (((gw >> 4) & 1) << 3);
+
+  // ---- x side of step u: its inputs into the image (one barrier before they are used), the sums into xsum
+  float xbeta = 0.0f;
+  auto stage_inputs = [&](int u) {
+    if (u >= a.steps) return;
+    expand_inputs();
+    xbeta = beta_next;
+    if (u + 1 < a.steps) request_inputs(u + 1);
+  };
+  auto x_side = [&](int u) {
+    float y[4];
+    sums(xbeta, y);
+    xsum[u & 1][blk][lane] = make_float4(y[0], y[1], y[2], y[3]);
+  };
+  if (xwave) {
+    request_inputs(0);
+    stage_inputs(0);
+  }
+  lds_barrier();
+  if (xwave) x_side(0);
+  lds_barrier();  // (the image of the x side may be overwritten)
+
+  for (int t = 0; t < a.steps; ++t) {
+    const unsigned tag = (unsigned)t + 1u;
+    if (xwave) stage_inputs(t + 1);
+    // ---- quantize h_{t-1} of the entries in this workgroup's charge
+    for (int e = q_first; e < ncols; e += q_next) {
+      if (xwave) {
+        for (int i = quantize_exchanges<KA>(a.T) + 1; i > 0; --i) lds_barrier();
+        continue;
+      }
+      float v[NJ];
+      if (t == 0) {
+        load_slots<NJ>(a.h0 + (size_t)(b0 + e) * H, H, base, nj, v);
+      } else {
+        const unsigned long long* src = a.hbuf + ((t - 1) & 1) * hhalf + (size_t)(b0 + e) * H;
+        unsigned long long p[NJ];
+        unsigned spins = 0;
+        for (;;) {
+          bool ready = true;
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            const int idx = (base + j) * 64 + lane;
+            p[j] = (unsigned long long)(unsigned)t << 32;
+            if (j < nj && idx < H) p[j] = get_pair(src + idx);
+          }
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) ready = ready && (unsigned)(p[j] >> 32) == (unsigned)t;
+          if (__all(ready)) break;
+          if (!poll_again(spins, a.limit, flag)) {
+            dead = 1;
+            break;
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) v[j] = __uint_as_float((unsigned)(p[j] & 0xffffffffull));
+      }
+      float beta[KA];
+      unsigned long long mym[KA];
+      with_slots<NJ, true>(nj, [&](auto slots) {
+        float w2[slots()];
+#pragma unroll
+        for (int j = 0; j < slots(); ++j) w2[j] = v[j];
+        quantize_core<KA, slots(), kWBlocks, true>(w2, H, base, nj, a.T, beta, mym, sh, phase);
+      });
+      // through LDS, so that whole cache lines are written at once
+      if (lane < nj && base + lane < nslots) {
+#pragma unroll
+        for (int i = 0; i < KA; ++i)
+          reinterpret_cast<unsigned long long*>(codes + i * wprH)[base + lane] = mym[i];
+      }
+      if (tid == 0) {
+#pragma unroll
+        for (int i = 0; i < KA; ++i) codes[KA * wprH + i] = __float_as_uint(beta[i]);
+      }
+      lds_barrier();
+      if (tid < KA * (wprH + 1))
+        put_pair(a.cbuf + (t & 1) * chalf + ((size_t)tile * kTileB + e) * centry + tid, codes[tid], tag);
+    }
+
+    lds_barrier();
+
+    float beta = 0.0f;
+    if (xwave) {
+      // ---- x side of step t + 1, while the codes are under way
+      x_side(t + 1);
+    } else {
+      // ---- codes of h_{t-1}
+      const char* src = reinterpret_cast<const char*>(a.cbuf + (t & 1) * chalf + (size_t)tile * kTileB * centry);
+      auto at = [](const char* base, unsigned off) { return reinterpret_cast<const unsigned long long*>(base + off); };
+      unsigned long long v[kGather], bv;
+      unsigned spins = 0;
+      for (;;) {
+        bv = get_pair(at(src, gboff));
+#pragma unroll
+        for (int q = 0; q < kGather; ++q) v[q] = get_pair(at(src + (q / kColReq) * wprH * 8, goff[q % kColReq]));
+        bool ready = (unsigned)(bv >> 32) == tag;
+#pragma unroll
+        for (int q = 0; q < kGather; ++q) ready = ready && (unsigned)(v[q] >> 32) == tag;
+        if (__all(ready)) break;
+        if (!poll_again(spins, a.limit, flag)) {
+          dead = 1;
+          break;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < kGather; ++q)
+        image[(q / kColReq) * NC * kSteps * 64 + gdst + ((q % kColReq * kColsPer + gc) ^ gswz)] =
+            expand4_signed(gok ? (uint32_t)(v[q] & 0xffffffffull) : 0u);
+      beta = __uint_as_float((unsigned)(bv & 0xffffffffull));
+    }
+    lds_barrier();
+    const int gone = dead;
+
+    // ---- h side and cell
+    if (!xwave) {
+      float y[4];
+      sums(beta, y);
+      const float4 x4 = xsum[t & 1][blk][lane];
+      const float yx[4] = {x4.x, x4.y, x4.z, x4.w};
+      cell<EPI>(yx, y, bs0, bs1, h, c);
+      if (own) {
+        if (a.hs) a.hs[(size_t)t * hhalf + state] = h;
+      }
+      hout[l16][4 * blk + l4] = h;
+    }
+    if (t + 1 < a.steps) {
+      // published through LDS as well: 16 units are one cache line
+      lds_barrier();
+      if (hp_ok) put_pair(a.hbuf + (t & 1) * hhalf + hp_at, __float_as_uint(hout[(tid >> 4) & 15][tid & 15]), tag);
+    }
+    if (__builtin_amdgcn_readfirstlane(gone)) return;  // (somebody waits in vain: all leave, the piece is done again)
+  }
+  if (own) {
+    a.h0[state] = h;
+    if (EPI == kEpiLstm) a.c0[state] = c;
+  }
+}
+
+// Before a launch: the lock (waited for at most kLockTicks; without it the flag is raised at once), no tags.
+constexpr unsigned kNoLock = 2u;  // (any other value but 0: a wait gave up)
+
+__global__ __launch_bounds__(256) void seqw_reset_kernel(unsigned* flag, unsigned* lock, uint4* pairs, long long units) {
+  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x, nt = (long long)gridDim.x * blockDim.x;
+  for (long long i = t; i < units; i += nt) pairs[i] = make_uint4(0, 0, 0, 0);
+  if (t == 0) *flag = take_resident_lock(lock) ? 0u : kNoLock;
+}
+
+// The piece again from the saved state if the launch before gave up: one workgroup per batch entry.
+template <int KA>
+__global__ __launch_bounds__(64 * kWBlocks) void seqw_recover_kernel(SeqWArgs a, int KW, int gru, unsigned* lock) {
+  __shared__ double sh[2 * kExchange<kWBlocks>];
+  __shared__ float hcur[2][2048];
+  __shared__ uint32_t codes[KA * 64];
+  __shared__ float hbeta[KA];
+  const unsigned why = *a.flag;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && why != kNoLock) give_resident_lock(lock);
+  if (why == 0u) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int H = a.H, b = blockIdx.x, NG = gru ? 3 : 4;
+  const int wprI = 4 * ((a.x.n + 127) >> 7), wprH = 4 * ((H + 127) >> 7);
+  const int nslots = wprH >> 1, nj = (nslots + kWBlocks - 1) / kWBlocks, base = wv * nj;
+  const long long m = (long long)NG * H;
+  int phase = 0;
+  for (int u = tid; u < H; u += 64 * kWBlocks) {
+    hcur[0][u] = a.save_h[(size_t)b * H + u];
+    if (!gru) a.c0[(size_t)b * H + u] = a.save_c[(size_t)b * H + u];
+  }
+  __syncthreads();
+  for (int t = 0; t < a.steps; ++t) {
+    const float* hp = hcur[t & 1];
+    float w[8], beta[KA];
+    unsigned long long mym[KA];
+    load_slots<8>(hp, H, base, nj, w);
+    quantize_core<KA, 8, kWBlocks, false>(w, H, base, nj, a.T, beta, mym, sh, phase);
+#pragma unroll
+    for (int i = 0; i < KA; ++i) {
+      if (lane < nj && base + lane < nslots) {
+        codes[i * 64 + 2 * (base + lane)] = (uint32_t)(mym[i] & 0xffffffffull);
+        codes[i * 64 + 2 * (base + lane) + 1] = (uint32_t)(mym[i] >> 32);
+      }
+      if (tid == 0) hbeta[i] = beta[i];
+    }
+    __syncthreads();
+    const long long row = (long long)t * a.batch + b;
+    for (int u = tid; u < H; u += 64 * kWBlocks) {
+      float y[2][4] = {};
+      for (int s = 0; s < 2; ++s) {
+        const BmvBlock& k = s ? a.h : a.x;
+        const int wpr = s ? wprH : wprI;
+        for (int g = 0; g < NG; ++g) {
+          float sum = 0.0f;
+          for (int i = 0; i < KW; ++i) {
+            const uint32_t* wp = k.Wp + (i * m + (long long)g * H + u) * wpr;
+            float inner = 0.0f;
+            for (int j = 0; j < KA; ++j) {
+              const uint32_t* xp = s ? codes + j * 64 : k.Xp + ((long long)j * a.rows + row) * wpr;
+              int differ = 0;
+              for (int q = 0; q < wpr; ++q) differ += __popc(wp[q] ^ xp[q]);
+              inner = fmaf(s ? hbeta[j] : k.beta[row * KA + j], (float)(k.n - 2 * differ), inner);
+            }
+            sum = fmaf(k.alpha[((long long)g * H + u) * KW + i], inner, sum);
+          }
+          y[s][g] = sum;
+        }
+      }
+      float b0[4], b1[4], h = hp[u], c = 0.0f;
+      for (int g = 0; g < 4; ++g) {
+        b0[g] = (g < NG && a.bias0) ? a.bias0[(long long)g * H + u] : 0.0f;
+        b1[g] = (g < NG && gru && a.bias1) ? a.bias1[(long long)g * H + u] : 0.0f;
+      }
+      const size_t state = (size_t)b * H + u;
+      if (gru) {
+        cell<kEpiGru>(y[0], y[1], b0, b1, h, c);
+      } else {
+        c = a.c0[state];
+        cell<kEpiLstm>(y[0], y[1], b0, b1, h, c);
+        a.c0[state] = c;
+      }
+      hcur[(t + 1) & 1][u] = h;
+      if (a.hs) a.hs[(size_t)t * a.batch * H + state] = h;
+    }
+    __syncthreads();
+  }
+  for (int u = tid; u < H; u += 64 * kWBlocks) a.h0[(size_t)b * H + u] = hcur[a.steps & 1][u];
+}
+
+hipError_t launch_recover(const SeqWArgs& a, int k_w, int k_a, int epi, unsigned* lock, hipStream_t s) {
+  const dim3 grid((unsigned)a.batch), block(64 * kWBlocks);
+  const int gru = epi == kEpiGru;
+  switch (k_a) {
+    case 1: hipLaunchKernelGGL((seqw_recover_kernel<1>), grid, block, 0, s, a, k_w, gru, lock); break;
+    case 2: hipLaunchKernelGGL((seqw_recover_kernel<2>), grid, block, 0, s, a, k_w, gru, lock); break;
+    default: hipLaunchKernelGGL((seqw_recover_kernel<3>), grid, block, 0, s, a, k_w, gru, lock); break;
+  }
+  return hipGetLastError();
+}
+
+// Workgroups of an instantiation that the current device holds at once (asked for once per device).
+template <int KW, int KA, int EPI, int NC>
+int resident_grid() {
+  static std::atomic<int> known[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  const bool tracked = dev >= 0 && dev < 64;
+  if (tracked) {
+    const int k = known[dev].load(std::memory_order_acquire);
+    if (k > 0) return k - 1;
+  }
+  constexpr size_t lds = seqw_lds<KW, KA, NC>();
+  const void* fn = reinterpret_cast<const void*>(&seqw_kernel<KW, KA, EPI, NC>);
+  int cus = 0, per = 0;
+  if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, 64 * kWWaves, lds) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  const int fit = cus * (per < 2 ? per : 2);
+  if (tracked) known[dev].store(fit + 1, std::memory_order_release);
+  return fit;
+}
+
+// launch == nullptr: only asks whether the grid fits
+template <int KW, int KA, int EPI, int NC>
+hipError_t run_one(const SeqWArgs* launch, dim3 grid, hipStream_t s) {
+  const int fit = resident_grid<KW, KA, EPI, NC>();
+  if ((long long)grid.x * grid.y > fit) return hipErrorInvalidValue;
+  if (!launch) return hipSuccess;
+  hipLaunchKernelGGL((seqw_kernel<KW, KA, EPI, NC>), grid, dim3(64 * kWWaves), (seqw_lds<KW, KA, NC>()), s, *launch);
+  return hipGetLastError();
+}
+
+template <int KW, int KA>
+hipError_t run_k(const SeqWArgs* l, dim3 grid, int epi, int nc, hipStream_t s) {
+  if (epi == kEpiLstm) return nc == 1 ? run_one<KW, KA, kEpiLstm, 1>(l, grid, s) : run_one<KW, KA, kEpiLstm, 2>(l, grid, s);
+  return nc == 1 ? run_one<KW, KA, kEpiGru, 1>(l, grid, s) : run_one<KW, KA, kEpiGru, 2>(l, grid, s);
+}
+
+hipError_t run(const SeqWArgs* l, long long I, long long H, long long batch, int k_w, int k_a, int epi, hipStream_t s) {
+  const dim3 grid((unsigned)((H + 4 * kWBlocks - 1) / (4 * kWBlocks)), (unsigned)((batch + kTileB - 1) / kTileB));
+  const int nc = (I > H ? I : H) > 1024 ? 2 : 1;
+  switch (k_w * 4 + k_a) {
+    case 4 * 1 + 1: return run_k<1, 1>(l, grid, epi, nc, s);
+    case 4 * 1 + 2: return run_k<1, 2>(l, grid, epi, nc, s);
+    case 4 * 1 + 3: return run_k<1, 3>(l, grid, epi, nc, s);
+    case 4 * 2 + 1: return run_k<2, 1>(l, grid, epi, nc, s);
+    case 4 * 2 + 2: return run_k<2, 2>(l, grid, epi, nc, s);
+    case 4 * 2 + 3: return run_k<2, 3>(l, grid, epi, nc, s);
+    case 4 * 3 + 1: return run_k<3, 1>(l, grid, epi, nc, s);
+    case 4 * 3 + 2: return run_k<3, 2>(l, grid, epi, nc, s);
+    case 4 * 3 + 3: return run_k<3, 3>(l, grid, epi, nc, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+SeqWScratch seqw_scratch(void* base, long long H, long long B, int k_a) {
+  const long long tiles = (B + kTileB - 1) / kTileB, wpr = 4 * ((H + 127) / 128);
+  SeqWScratch w;
+  size_t off = 256;
+  auto take = [&](size_t bytes) {
+    char* p = base ? static_cast<char*>(base) + off : nullptr;
+    off += (bytes + 255) & ~size_t(255);
+    return p;
+  };
+  w.flag = static_cast<unsigned*>(base);
+  const size_t pairs = off;
+  w.hbuf = reinterpret_cast<unsigned long long*>(take(sizeof(unsigned long long) * 2 * (size_t)B * H));
+  w.cbuf = reinterpret_cast<unsigned long long*>(
+      take(sizeof(unsigned long long) * 2 * (size_t)tiles * kTileB * seqw_entry_pairs(k_a, (int)wpr)));
+  w.pair_bytes = off - pairs;
+  w.save_h = reinterpret_cast<float*>(take(sizeof(float) * (size_t)B * H));
+  w.save_c = reinterpret_cast<float*>(take(sizeof(float) * (size_t)B * H));
+  w.bytes = off;
+  return w;
+}
+
+bool seqw_supported(long long I, long long H, long long B, int k_w, int k_a, int epi) {
+  if (B < 2 || I <= 0 || H <= 0 || I > 2048 || H > 2048 || k_w < 1 || k_w > 3 || k_a < 1 || k_a > 3) return false;
+  if (B > 16 * 256) return false;
+  return run(nullptr, I, H, B, k_w, k_a, epi, nullptr) == hipSuccess;
+}
+
+hipError_t launch_seqw(SeqWArgs a, const SeqWScratch& w, int k_w, int k_a, int epi, hipStream_t s) {
+  a.flag = w.flag;
+  a.hbuf = w.hbuf;
+  a.cbuf = w.cbuf;
+  a.save_h = w.save_h;
+  a.save_c = w.save_c;
+  a.limit = sequence_spin_limit();
+  const long long units = (long long)(w.pair_bytes / sizeof(uint4));
+  const long long blocks = (units + 1023) / 1024;
+  // (the three launches of a piece are put into the queue together: a reset kernel that waits for the lock never stands
+  // between another piece's launches where streams share a hardware queue)
+  std::lock_guard<std::mutex> together(resident_launches());
+  unsigned* const lock = resident_lock();
+  hipLaunchKernelGGL(seqw_reset_kernel, dim3((unsigned)(blocks < 512 ? blocks : 512)), dim3(256), 0, s, w.flag, lock,
+                     reinterpret_cast<uint4*>(w.hbuf), units);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const hipError_t ran = run(&a, a.x.n, a.H, a.batch, k_w, k_a, epi, s);
+  e = launch_recover(a, k_w, k_a, epi, lock, s);
+  return ran != hipSuccess ? ran : e;
+}
+
+// ---- the lock ------------------------------------------------------------------------------------------------
+static __device__ unsigned resident_lock_word;
+
+unsigned* resident_lock() {
+  static std::atomic<unsigned*> known[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  const bool tracked = dev >= 0 && dev < 64;
+  if (tracked) {
+    unsigned* p = known[dev].load(std::memory_order_acquire);
+    if (p) return p;
+  }
+  void* p = nullptr;
+  if (hipGetSymbolAddress(&p, HIP_SYMBOL(resident_lock_word)) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  if (tracked) known[dev].store(static_cast<unsigned*>(p), std::memory_order_release);
+  return static_cast<unsigned*>(p);
+}
+
+std::mutex& resident_launches() {
+  static std::mutex m;
+  return m;
+}
+
+}  // namespace amq

@@ -662,3 +662,43 @@ def test_sequences_of_long_vectors_and_single_tiles(amq, I, H, B, k_w, k_a, step
                 ph = amq.gru_step(*d, I, H, None, None, dx[t], ph, k_a, 2)
             assert torch.equal(ph, hs[t])
         assert torch.equal(dh, hs[-1])
+
+
+@pytest.mark.parametrize("I,H,B,k_w,k_a,steps,polls", [(200, 200, 2, 2, 2, 5, 0), (1024, 1024, 64, 3, 3, 4, 0),
+                                                       (650, 650, 20, 2, 3, 40, 0), (1500, 1030, 17, 3, 2, 4, 0),
+                                                       (64, 40, 33, 1, 1, 4, 0), (130, 72, 5, 2, 2, 900, 0),
+                                                       (300, 300, 18, 2, 3, 6, 1), (100, 1100, 3, 3, 1, 4, 1)])
+def test_resident_sequences(amq, I, H, B, k_w, k_a, steps, polls):
+    # whole sequences in one launch: partly filled tiles, fewer workgroups than batch entries, several pieces, and (with
+    # one poll per wait) the launch that computes a piece again whose waits gave up; biases given, against the per-step
+    # calls, every h_t
+    import torch
+    g = np.random.default_rng(I + 5 * H + B)
+    amq.binding.debug_set_sequence_spin_limit(polls)
+    try:
+        for gates in (4, 3):
+            say("resident I=%d H=%d B=%d W%d/A%d gates=%d steps=%d polls=%d" % (I, H, B, k_w, k_a, gates, steps, polls))
+            Wxp, ax = quantized((g.standard_normal((gates * H, I)) * 0.05).astype(np.float32), k_w)
+            Whp, ah = quantized((g.standard_normal((gates * H, H)) * 0.05).astype(np.float32), k_w)
+            d = [to_dev(t) for t in (Wxp, ax, Whp, ah)]
+            b0, b1 = (to_dev(g.standard_normal(gates * H).astype(np.float32) * 0.1) for _ in range(2))
+            xs = to_dev(g.standard_normal((steps, B, I)).astype(np.float32))
+            dh = to_dev(np.tanh(g.standard_normal((B, H))).astype(np.float32))
+            dc = to_dev(g.standard_normal((B, H)).astype(np.float32))
+            hs = torch.empty((steps, B, H), device=dh.device)
+            ph, pc = dh.clone(), dc.clone()
+            if gates == 4:
+                amq.lstm_sequence(*d, I, H, b0, xs, dh, dc, k_a, 2, hs=hs)
+            else:
+                amq.gru_sequence(*d, I, H, b0, b1, xs, dh, k_a, 2, hs=hs)
+            for t in range(steps):
+                if gates == 4:
+                    ph, pc = amq.lstm_step(*d, I, H, b0, xs[t], ph, pc, k_a, 2)
+                else:
+                    ph = amq.gru_step(*d, I, H, b0, b1, xs[t], ph, k_a, 2)
+                assert torch.equal(ph, hs[t]), t
+            assert torch.equal(dh, hs[-1])
+            if gates == 4:
+                assert torch.equal(dc, pc)
+    finally:
+        amq.binding.debug_set_sequence_spin_limit(0)
