@@ -465,11 +465,28 @@ static int lstm_fused_launch(const uint32_t* Wxp, const float* alpha_x, const ui
   return -1;
 }
 
+static bool apart_from(const float* a, int64_t na, const float* b, int64_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x + sizeof(float) * (size_t)na <= y || y + sizeof(float) * (size_t)nb <= x;
+}
+
 static int lstm_step_launch(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp,
                             const float* alpha_h, int64_t I, int64_t H, int k_w, const float* bias,
                             const float* x, const float* h_prev, const float* c_prev, int64_t B, int k_a,
                             int T, float* h_out, float* c_out, float* hs_out, const StepWs& w,
                             hipStream_t s) {
+  if (B == 1) {
+    // one launch, unless what every workgroup quantizes is overwritten by the workgroups that finish first
+    amq::BmvArgs b = lstm_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias, nullptr, nullptr, nullptr, nullptr, c_prev, 1, h_out,
+                               c_out, hs_out);
+    b.raw[0] = x;
+    b.raw[1] = h_prev;
+    b.T = T;
+    const bool apart = apart_from(h_prev, H, h_out, H) && apart_from(h_prev, H, c_out, H) && apart_from(x, I, h_out, H) &&
+                       apart_from(x, I, c_out, H) && (!hs_out || (apart_from(h_prev, H, hs_out, H) && apart_from(x, I, hs_out, H)));
+    if (apart && amq::bmv_online_supported(b, k_w, k_a, amq::kEpiLstm))
+      return hip_status(amq::launch_bmv_online(b, k_w, k_a, amq::kEpiLstm, s));
+  }
   amq::QuantArgs q{};
   q.seg[0] = amq::QuantSeg{x, I, (int)I, (int)B, w.xp, w.beta_x};
   q.seg[1] = amq::QuantSeg{h_prev, H, (int)H, (int)B, w.hp, w.beta_h};
@@ -991,9 +1008,36 @@ size_t amq_softmax_layer_workspace_bytes(int64_t V, int64_t H, int64_t B, int k_
   return carve_softmax(nullptr, V, H, B, k_a).total;
 }
 
+// The output layer on one hidden state that the product kernel quantizes itself.
+static amq::BmvArgs output_args(const uint32_t* Wsp, const float* alpha_s, int64_t V, int64_t H, const float* bias,
+                                const float* h, int T, float* logprob, const SoftmaxWs& w) {
+  amq::BmvArgs b{};
+  b.blk[0] = amq::BmvBlock{Wsp, alpha_s, nullptr, nullptr, (int)H};
+  b.m = V;
+  b.batch = 1;
+  b.groups = 1;
+  b.bias0 = bias;
+  b.Y = logprob;
+  b.lse_part = w.lse_part;
+  b.lse_cap = w.lse_cap;
+  b.raw[0] = h;
+  b.T = T;
+  return b;
+}
+static int output_online_launch(const amq::BmvArgs& b, int k_w, int k_a, hipStream_t s) {
+  int slots = 0;
+  const int st = hip_status(amq::launch_bmv_online(b, k_w, k_a, amq::kEpiStore, s, &slots));
+  if (st != AMQ_OK) return st;
+  return hip_status(amq::launch_log_softmax_finish(b.Y, 1, b.m, b.lse_part, slots, b.Y, s));
+}
+
 static int softmax_layer_launch(const uint32_t* Wsp, const float* alpha_s, int64_t V, int64_t H, int k_w,
                                 const float* bias, const float* h, int64_t B, int k_a, int T, float* logprob,
                                 const SoftmaxWs& w, hipStream_t s) {
+  if (B == 1 && apart_from(h, H, logprob, V)) {
+    const amq::BmvArgs b = output_args(Wsp, alpha_s, V, H, bias, h, T, logprob, w);
+    if (amq::bmv_online_supported(b, k_w, k_a, amq::kEpiStore)) return output_online_launch(b, k_w, k_a, s);
+  }
   amq::QuantArgs q{};
   q.seg[0] = amq::QuantSeg{h, H, (int)H, (int)B, w.hp, w.beta};
   q.T = T;
@@ -1059,6 +1103,21 @@ static int lm_step_launch(const uint32_t* Ep, const float* alpha_e, int64_t voca
                           const float* bias, const uint32_t* Wsp, const float* alpha_s, int64_t V, int k_ws,
                           const float* bias_s, const int64_t* ids, float* h, float* c, int64_t B, int k_a, int k_as,
                           int T, float* logprob, const StepWs& w, const SoftmaxWs& sw, hipStream_t s) {
+  if (B == 1 && apart_from(h, H, logprob, V)) {
+    // three launches: the cell looks its input up and quantizes h itself and leaves the new state in the workspace
+    // (other workgroups may still be reading h), the output layer quantizes that and moves it to h, and the log-softmax
+    amq::BmvArgs r = lstm_args(Wxp, alpha_x, Whp, alpha_h, E, H, bias, Ep, alpha_e, nullptr, nullptr, c, 1, w.pre0, c, nullptr);
+    r.raw[1] = h;
+    r.row_of = reinterpret_cast<const long long*>(ids);
+    r.rows_of = vocab;
+    r.T = T;
+    amq::BmvArgs o = output_args(Wsp, alpha_s, V, H, bias_s, w.pre0, T, logprob, sw);
+    o.copy_to = h;
+    if (amq::bmv_online_supported(r, k_w, k_a, amq::kEpiLstm) && amq::bmv_online_supported(o, k_ws, k_as, amq::kEpiStore)) {
+      const int st = hip_status(amq::launch_bmv_online(r, k_w, k_a, amq::kEpiLstm, s));
+      return st != AMQ_OK ? st : output_online_launch(o, k_ws, k_as, s);
+    }
+  }
   int st = lm_recurrent_launch(Ep, alpha_e, vocab, E, Wxp, alpha_x, Whp, alpha_h, H, k_w, bias, ids, h, c, B, k_a, T,
                                nullptr, w, s);
   if (st != AMQ_OK) return st;

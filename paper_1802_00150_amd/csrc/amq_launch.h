@@ -167,6 +167,13 @@ struct BmvArgs {
   int lse_cap;          // slots per batch entry the buffer has room for
   const long long* tgt; // several-tiles store kernel only, nullable: one output row index per batch entry ...
   float* tgt_out;       // ... whose output value is also written here, [batch] (Y may then be null)
+  // operands that the kernel quantizes itself (launch_bmv_online): the vectors, or for the x block, without one, a row of
+  // the quantized table that blk[0] describes
+  const float* raw[2];
+  const long long* row_of;  // device, [1]; outside [0, rows_of): the zero vector
+  long long rows_of;
+  float* copy_to;       // store mode, nullable: raw[0] is also copied here
+  int T;
   int lg;               // filled by launch_bmv
   int streaming;        // filled by launch_bmv: planes are read once, load them non-temporal
   int groups;           // small-batch kernel: independent products / cells in one launch (1 otherwise)
@@ -185,6 +192,10 @@ constexpr int kLseMaxSlots = 8192;
 bool bmv_supported(int n0, int n1, int k_a, long long batch, int epi);
 // lse_slots (nullable) receives the number of slots written per batch entry when a.lse_part is set
 hipError_t launch_bmv(BmvArgs a, int k_w, int k_a, int epi, hipStream_t s, int* lse_slots = nullptr);
+
+// One batch entry, operands given as vectors (a.raw): the same kernel with the quantizer in front, no launch of its own.
+bool bmv_online_supported(const BmvArgs& a, int k_w, int k_a, int epi);
+hipError_t launch_bmv_online(BmvArgs a, int k_w, int k_a, int epi, hipStream_t s, int* lse_slots = nullptr);
 
 // ---- batched products on the matrix cores (int8 MFMA on expanded codes), same epilogues ------
 bool mfma_supported(long long batch);

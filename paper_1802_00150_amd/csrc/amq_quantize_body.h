@@ -53,7 +53,8 @@ __device__ __forceinline__ void with_slots(int nj, F f) {
     else if (nj == 3) call(std::integral_constant<int, 3>{});
     else call(std::integral_constant<int, 4>{});
   } else if constexpr (ONLINE && NJ == 8) {
-    if (nj <= 4) call(std::integral_constant<int, 4>{});
+    if (nj <= 2) call(std::integral_constant<int, 2>{});
+    else if (nj <= 4) call(std::integral_constant<int, 4>{});
     else if (nj <= 6) call(std::integral_constant<int, 6>{});
     else call(std::integral_constant<int, 8>{});
   } else {

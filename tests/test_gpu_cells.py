@@ -702,3 +702,44 @@ def test_resident_sequences(amq, I, H, B, k_w, k_a, steps, polls):
                 assert torch.equal(dc, pc)
     finally:
         amq.binding.debug_set_sequence_spin_limit(0)
+
+
+@pytest.mark.parametrize("I,H,V,k_w,k_a", [(300, 300, 2000, 2, 2), (1024, 1024, 42000, 2, 3), (64, 130, 33, 3, 2), (1025, 2048, 9000, 3, 3),
+                                           (2048, 700, 20001, 2, 2), (200, 2049, 500, 2, 2)])
+def test_single_entry_steps_quantize_in_the_product(amq, I, H, V, k_w, k_a):
+    # batch 1: the cell and the output layer quantize their operands themselves; a step whose state is updated in place
+    # goes through the quantizer launch, and both give the same
+    import torch
+    g = np.random.default_rng(I + 7 * H)
+    say("single entry I=%d H=%d V=%d W%d/A%d" % (I, H, V, k_w, k_a))
+    Wxp, ax = quantized((g.standard_normal((4 * H, I)) * 0.05).astype(np.float32), k_w)
+    Whp, ah = quantized((g.standard_normal((4 * H, H)) * 0.05).astype(np.float32), k_w)
+    d = [to_dev(t) for t in (Wxp, ax, Whp, ah)]
+    bias = to_dev(g.standard_normal(4 * H).astype(np.float32) * 0.1)
+    x = to_dev(g.standard_normal((1, I)).astype(np.float32))
+    h = to_dev(np.tanh(g.standard_normal((1, H))).astype(np.float32))
+    c = to_dev(g.standard_normal((1, H)).astype(np.float32))
+    ho, co = amq.lstm_step(*d, I, H, bias, x, h, c, k_a, 2)
+    hi, ci = h.clone(), c.clone()
+    amq.lstm_step(*d, I, H, bias, x, hi, ci, k_a, 2, h_out=hi, c_out=ci)
+    assert torch.equal(ho, hi) and torch.equal(co, ci)
+    h_ref, c_ref = oracle.lstm_step(Wxp, ax, Whp, ah, I, H, host(bias), host(x), host(h), host(c), k_a, 2)
+    assert_vec_close(host(ho), h_ref, "h")
+    assert_vec_close(host(co), c_ref, "c")
+    Wsp, as_ = quantized((g.standard_normal((V, H)) * 0.05).astype(np.float32), k_w)
+    ds = [to_dev(t) for t in (Wsp, as_)]
+    bs = to_dev(g.standard_normal(V).astype(np.float32) * 0.1)
+    one = amq.softmax_layer(*ds, H, bs, h, k_a, 2)
+    two = amq.softmax_layer(*ds, H, bs, torch.cat([h, h]), k_a, 2)
+    assert_vec_close(host(one), host(two)[:1], "log-probabilities")
+    Ep, ae = quantized((g.standard_normal((50, I)) * 0.3).astype(np.float32), k_a)
+    de = [to_dev(t) for t in (Ep, ae)]
+    for word in (0, 49, 50):  # the last is outside the table
+        ids = torch.tensor([word], device=h.device)
+        h1, c1 = h.clone(), c.clone()
+        lp = amq.lm_step(*de, I, *d, H, bias, *ds, bs, ids, h1, c1, k_a, k_a, 2)
+        h2, c2 = torch.cat([h, h]), torch.cat([c, c])
+        lp2 = amq.lm_step(*de, I, *d, H, bias, *ds, bs, torch.cat([ids, ids]), h2, c2, k_a, k_a, 2)
+        assert_vec_close(host(h1), host(h2)[:1], "h")
+        assert_vec_close(host(c1), host(c2)[:1], "c")
+        assert_vec_close(host(lp), host(lp2)[:1], "log-probabilities")
