@@ -314,8 +314,12 @@ int amq_quantize_weights_ex(const float* W, int64_t rows, int64_t cols, int64_t 
  * with respect to w_hat, and the full-precision weights are clipped to [-1, 1]).
  *   amq_dequantize: out [rows][ld_out] (ld_out >= cols) receives w_hat of a row-wise
  *     quantization; an entry is the binary32 left-to-right sum of +-alpha[r][i].
+ *   amq_quantize_reconstruct: amq_quantize_weights and amq_dequantize in one pass, without the
+ *     packed codes: out [rows][ld_out] receives w_hat of W [rows][ld].
  *   amq_clip: w[0..n) clipped to [lo, hi] in place.
  */
+int amq_quantize_reconstruct(const float* W, int64_t rows, int64_t cols, int64_t ld, int k, int T, float* out,
+                             int64_t ld_out, void* stream);
 int amq_dequantize(const uint32_t* planes, const float* alpha, int64_t rows, int64_t cols, int k,
                    float* out, int64_t ld_out, void* stream);
 int amq_clip(float* w, int64_t n, float lo, float hi, void* stream);

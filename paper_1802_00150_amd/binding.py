@@ -32,7 +32,7 @@ EXPORTS = [
     "amq_lm_workspace_bytes", "amq_lm_step", "amq_lm_sequence_workspace_bytes", "amq_lm_sequence",
     "amq_lm_sequence_score_workspace_bytes", "amq_lm_sequence_score",
     "amq_quantize_refined_greedy", "amq_quantize_ternary", "amq_relative_mse",
-    "amq_quantize_weights_ex", "amq_dequantize", "amq_clip",
+    "amq_quantize_weights_ex", "amq_dequantize", "amq_quantize_reconstruct", "amq_clip",
     "amq_gru_reset_before_workspace_bytes", "amq_gru_step_reset_before",
 ]
 
@@ -115,6 +115,7 @@ def lib():
         L.amq_gru_step_reset_before.argtypes = [_p, _p, _p, _p, _i64, _i64, _int, _p, _p, _p, _p, _i64, _int, _int, _p, _p,
                                                 _p, _sz, _p]
         L.amq_quantize_weights_ex.argtypes = [_p, _i64, _i64, _i64, _int, _int, _int, _p, _p, _p]
+        L.amq_quantize_reconstruct.argtypes = [_p, _i64, _i64, _i64, _int, _int, _p, _i64, _p]
         L.amq_dequantize.argtypes = [_p, _p, _i64, _i64, _int, _p, _i64, _p]
         L.amq_clip.argtypes = [_p, _i64, C.c_float, C.c_float, _p]
         _lib = L

@@ -913,6 +913,19 @@ int amq_quantize_weights_ex(const float* W, int64_t rows, int64_t cols, int64_t 
   return quantize_common(W, rows, cols, ld, k, 1, planes, alpha, amq::kQuantLsOnly, stream);
 }
 
+int amq_quantize_reconstruct(const float* W, int64_t rows, int64_t cols, int64_t ld, int k, int T, float* out,
+                             int64_t ld_out, void* stream) {
+  if (!W || !out || !bits_ok(k) || T < 0 || rows <= 0 || cols <= 0 || ld < cols || ld_out < cols) return AMQ_ERR_INVALID;
+  if (cols > AMQ_MAX_QUANT_N || rows > 0x7fffffffLL) return AMQ_ERR_UNSUPPORTED;
+  amq::QuantArgs q{};
+  q.seg[0] = amq::QuantSeg{W, ld, (int)cols, (int)rows, nullptr, nullptr};
+  q.T = T;
+  q.mode = amq::kQuantFull;
+  q.recon = out;
+  q.recon_ld = ld_out;
+  return hip_status(amq::launch_quantize_recon(q, k, static_cast<hipStream_t>(stream)));
+}
+
 int amq_dequantize(const uint32_t* planes, const float* alpha, int64_t rows, int64_t cols, int k, float* out,
                    int64_t ld_out, void* stream) {
   if (!planes || !alpha || !out) return AMQ_ERR_INVALID;

@@ -73,10 +73,14 @@ struct QuantArgs {
   int T;
   int mode;
   GatherSeg gather;
+  float* recon;        // launch_quantize_recon: reconstruction of seg[0], [count][recon_ld]
+  long long recon_ld;
   AMQ_PHASE_MEMBER
 };
 
 hipError_t launch_quantize(const QuantArgs& a, int k, hipStream_t s);
+// seg[0] only: the binary32 code-table value of every entry's code instead of codes and coefficients
+hipError_t launch_quantize_recon(const QuantArgs& a, int k, hipStream_t s);
 
 // ---- comparison quantizer and error measure ------------------------------------------------
 // Refined greedy approximation of `count` vectors X [count][ld] of length n (Sec. 2).

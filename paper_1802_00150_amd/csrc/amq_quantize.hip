@@ -1,27 +1,11 @@
 // Alternating multi-bit quantization (Alg. 2) on gfx950: one workgroup of NW wavefronts per vector, the vector
 // held in registers, every stage of the algorithm in this one kernel (amq_quantize_core.h), and the two staged
 // hooks (Eq. 5 alone, Alg. 1 alone).
-#include "amq_launch.h"
-#include "amq_quantize_body.h"
+#include "amq_quantize_kernels.h"
 
 namespace amq {
 
 namespace {
-
-// The second launch bound is the waves per SIMD that the registers shall allow.
-template <int K>
-constexpr int kQuantWaves = K == 4 ? 3 : 4;
-
-template <int K, int NJ, int NW, bool ONLINE>
-__global__ __launch_bounds__(64 * NW, NW < 16 ? kQuantWaves<K> : 4)
-void quantize_kernel(QuantArgs a) {
-  __shared__ double sh[2 * kExchange<NW>];
-  asm volatile("" ::AMQ_ARG(a.seg[0].X), AMQ_ARG(a.seg[0].ld), AMQ_ARG(a.seg[0].n), AMQ_ARG(a.seg[0].count),
-               AMQ_ARG(a.seg[0].planes), AMQ_ARG(a.seg[0].coef), AMQ_ARG(a.seg[1].X), AMQ_ARG(a.seg[1].ld),
-               AMQ_ARG(a.seg[1].n), AMQ_ARG(a.seg[1].count), AMQ_ARG(a.seg[1].planes), AMQ_ARG(a.seg[1].coef),
-               AMQ_ARG(a.T), AMQ_ARG(a.gather.count));
-  quantize_block<K, NJ, NW, ONLINE>(a, blockIdx.x, sh);
-}
 
 // Staged hooks on one vector per workgroup: Eq. 5 with the codes given (a.mode == kQuantLsOnly), or Alg. 1 with
 // the coefficients given.
@@ -113,12 +97,6 @@ __global__ __launch_bounds__(64 * NW) void quantize_stage_kernel(QuantArgs a) {
   }
 }
 
-template <int K, int NJ, int NW, bool ONLINE = false>
-void launch_one(QuantArgs a, int total, hipStream_t s) {
-  AMQ_PHASE_ATTACH(a);
-  hipLaunchKernelGGL((quantize_kernel<K, NJ, NW, ONLINE>), dim3(total), dim3(64 * NW), 0, s, a);
-}
-
 template <int K>
 hipError_t launch_stage(const QuantArgs& a, int nslots, hipStream_t s) {
   const dim3 grid((unsigned)a.seg[0].count);
@@ -128,61 +106,18 @@ hipError_t launch_stage(const QuantArgs& a, int nslots, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Waves per vector.  Many vectors (throughput): as few waves as hold the vector with at most 16 slots per lane --
-// what a wave does once per vector (reductions, solves, code tables) is then paid by few waves, and 16 slots keep
-// the registers at about 100; then the smallest register form that holds the share.  Few vectors (the on-line case,
-// latency): at most 4 slots per lane over at least 4 waves, and the form of the algorithm made for that.
-template <int K>
-hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
-  const int nvec = a.seg[0].count + a.seg[1].count;
-  const int total = nvec + a.gather.count;  // one workgroup per vector, one per gathered row
-  if (total == 0) return hipSuccess;
-  const int nslots = nvec ? 2 * ((max_n + 127) / 128) : 1;
-  if (nslots > 256) return hipErrorInvalidValue;
-  if (a.mode != kQuantFull) return launch_stage<K>(a, nslots, s);
-  if (nvec < 1024 && nslots <= 64) {
-    if (nslots <= 2) launch_one<K, 2, 1, true>(a, total, s);
-    else if (nslots <= 16) launch_one<K, 4, 4, true>(a, total, s);
-    else if (nslots <= 32) launch_one<K, 4, 8, true>(a, total, s);
-    else launch_one<K, 4, 16, true>(a, total, s);
-    return hipGetLastError();
-  }
-  int nw = 1;
-  while (nw < 16 && (nslots + nw - 1) / nw > 16) nw *= 2;
-  const int nj = (nslots + nw - 1) / nw;
-  switch (nw * 32 + (nj + 1) / 2 * 2) {
-    case 32 + 2: launch_one<K, 2, 1>(a, total, s); break;
-    case 32 + 4: launch_one<K, 4, 1>(a, total, s); break;
-    case 32 + 6: launch_one<K, 6, 1>(a, total, s); break;
-    case 32 + 8: launch_one<K, 8, 1>(a, total, s); break;
-    case 32 + 10: launch_one<K, 10, 1>(a, total, s); break;
-    case 32 + 12: launch_one<K, 12, 1>(a, total, s); break;
-    case 32 + 14: launch_one<K, 14, 1>(a, total, s); break;
-    case 32 + 16: launch_one<K, 16, 1>(a, total, s); break;
-    case 64 + 10: launch_one<K, 10, 2>(a, total, s); break;
-    case 64 + 12: launch_one<K, 12, 2>(a, total, s); break;
-    case 64 + 14: launch_one<K, 14, 2>(a, total, s); break;
-    case 64 + 16: launch_one<K, 16, 2>(a, total, s); break;
-    case 128 + 10: launch_one<K, 10, 4>(a, total, s); break;
-    case 128 + 12: launch_one<K, 12, 4>(a, total, s); break;
-    case 128 + 14: launch_one<K, 14, 4>(a, total, s); break;
-    case 128 + 16: launch_one<K, 16, 4>(a, total, s); break;
-    default:
-      if (nw == 8) launch_one<K, 16, 8>(a, total, s);
-      else launch_one<K, 16, 16>(a, total, s);
-  }
-  return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t launch_quantize(const QuantArgs& a, int k, hipStream_t s) {
-  const int max_n = a.seg[1].count > 0 && a.seg[1].n > a.seg[0].n ? a.seg[1].n : a.seg[0].n;
+  if (a.mode == kQuantFull) return launch_bits<false>(a, k, s);
+  const int nslots = 2 * ((a.seg[0].n + 127) / 128);
+  if (a.seg[0].count == 0) return hipSuccess;
+  if (nslots > 256) return hipErrorInvalidValue;
   switch (k) {
-    case 1: return launch_k<1>(a, max_n, s);
-    case 2: return launch_k<2>(a, max_n, s);
-    case 3: return launch_k<3>(a, max_n, s);
-    case 4: return launch_k<4>(a, max_n, s);
+    case 1: return launch_stage<1>(a, nslots, s);
+    case 2: return launch_stage<2>(a, nslots, s);
+    case 3: return launch_stage<3>(a, nslots, s);
+    case 4: return launch_stage<4>(a, nslots, s);
   }
   return hipErrorInvalidValue;
 }

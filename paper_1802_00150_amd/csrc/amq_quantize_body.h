@@ -64,7 +64,7 @@ __device__ __forceinline__ void with_slots(int nj, F f) {
 
 // vec: index of this workgroup's vector over both segments (then over the gathered rows).  sh:
 // 2 * kExchange<NW> doubles of LDS.  Every wave of the workgroup (NW of them) must call this.
-template <int K, int NJ, int NW, bool ONLINE>
+template <int K, int NJ, int NW, bool ONLINE, bool RECON = false>
 __device__ __forceinline__ void quantize_block(const QuantArgs& a, int vec, double* sh) {
   int phase = 0;
   const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
@@ -98,6 +98,24 @@ __device__ __forceinline__ void quantize_block(const QuantArgs& a, int vec, doub
     quantize_core<K, slots(), NW, ONLINE>(w, n, base, nj, a.T, alpha, mym, sh, phase, AMQ_PHASE_OF(a));
   });
 
+  if constexpr (RECON) {
+    // left to right over the planes, as launch_dequantize forms it; the mask of a slot sits in the slot's lane
+    float* out = a.recon + (long long)vec * a.recon_ld + base * 64 + lane;
+    const int left = min(n - base * 64, nj * 64) - lane;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      float v = 0.0f;
+#pragma unroll
+      for (int i = 0; i < K; ++i) {
+        const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(mym[i] & 0xffffffffull), j);
+        const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(mym[i] >> 32), j);
+        const float term = lane_bit(((unsigned long long)hi << 32) | lo) ? alpha[i] : -alpha[i];
+        v = (i == 0) ? term : v + term;
+      }
+      if (j * 64 < left) out[j * 64] = v;
+    }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < K; ++i)
     if (lane < nj && base + lane < nslots)

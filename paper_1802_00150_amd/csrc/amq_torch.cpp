@@ -26,7 +26,8 @@ namespace {
   X(amq_gru_workspace_bytes) X(amq_gru_step) X(amq_gru_sequence_workspace_bytes) X(amq_gru_sequence)                \
   X(amq_embedding_lookup) X(amq_log_softmax) X(amq_softmax_layer_workspace_bytes) X(amq_softmax_layer)              \
   X(amq_lm_workspace_bytes) X(amq_lm_step) X(amq_lm_sequence_workspace_bytes) X(amq_lm_sequence)                    \
-  X(amq_lm_sequence_score_workspace_bytes) X(amq_lm_sequence_score) X(amq_dequantize)
+  X(amq_lm_sequence_score_workspace_bytes) X(amq_lm_sequence_score) X(amq_dequantize)      \
+  X(amq_quantize_reconstruct)
 
 struct Api {
 #define AMQ_MEMBER(name) decltype(&::name) name = nullptr;
@@ -460,8 +461,15 @@ PyObject* dequantize(PyObject* const* a) {  // planes, alpha, cols, out
 struct FakeQuantize : public torch::autograd::Function<FakeQuantize> {
   static at::Tensor forward(torch::autograd::AutogradContext*, const at::Tensor& W, int64_t k, int64_t T) {
     const at::Tensor w = W.detach().contiguous();
-    auto q = quantize_matrix(w, (int)k, (int)T, 0);
-    return dequantized(q.first, q.second, w.size(1), make({w.size(0), w.size(1)}, at::kFloat, w));
+    if (w.dim() != 2 || w.scalar_type() != at::kFloat || !w.is_cuda())
+      fail(amq_error, "expected a 2-D float32 GPU tensor with unit column stride");
+    const int64_t rows = w.size(0), cols = w.size(1);
+    at::Tensor out = make({rows, cols}, at::kFloat, w);
+    const float* p = static_cast<const float*>(w.data_ptr());
+    float* o = static_cast<float*>(out.data_ptr());
+    void* s = stream();
+    call([&] { return api.amq_quantize_reconstruct(p, rows, cols, cols, (int)k, (int)T, o, cols, s); });
+    return out;
   }
   static torch::autograd::variable_list backward(torch::autograd::AutogradContext*,
                                                  const torch::autograd::variable_list& grad) {

@@ -187,3 +187,14 @@ def test_fake_quantize_forward_and_straight_through_gradient(amq):
     G = to_dev((g.standard_normal((40, 300))).astype(np.float32))
     (What * G).sum().backward()
     assert np.array_equal(host(Wd.grad), host(G))   # d f / d w = d f / d w_hat
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+@pytest.mark.parametrize("rows,cols", [(5, 1), (7, 300), (3, 900), (2, 2049), (1031, 64), (1100, 650), (1500, 2100), (1024, 9000)])
+def test_reconstruction_in_one_pass(amq, rows, cols, k):
+    # both forms of the quantizer, ragged and whole rows: the same values as codes and coefficients expanded afterwards
+    import torch
+    say("reconstruction %d x %d k=%d" % (rows, cols, k))
+    W = to_dev(np.random.default_rng(rows + cols).standard_normal((rows, cols)).astype(np.float32))
+    planes, alpha = amq.quantize_weights(W, k, 2)
+    assert torch.equal(amq.fake_quantize(W, k, 2), amq.dequantize(planes, alpha, cols))
