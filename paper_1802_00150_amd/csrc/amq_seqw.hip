@@ -4,9 +4,9 @@
 // work is half a microsecond: the rest is launch gaps, the cold misses every new kernel starts with, weights fetched
 // and turned into operand layout again at every step, and state that goes through memory.  Here the grid stays
 // resident for the whole sequence:
-//   - a workgroup of 4 waves owns one batch tile (16 entries) and 4 row blocks (16 hidden units, all gates), one row
-//     block per wave; the packed weights of both operand blocks, their coefficients, the biases and the cell state
-//     stay in registers, the weights already in operand layout;
+//   - a workgroup of 8 waves owns one batch tile (16 entries) and 4 row blocks (16 hidden units, all gates), one wave
+//     per row block and operand block; its weights, coefficients, biases and cell state stay in registers, the
+//     weights already in operand layout;
 //   - the inputs do not depend on the recurrence: their codes are all formed (or looked up) before this launch, and the
 //     x-side sums of step t are formed while the codes of h_{t-1} are under way;
 //   - per step two exchanges: every workgroup publishes its h_t; the workgroup in charge of a batch entry (one of
