@@ -7,8 +7,8 @@
  *   - Every pointer is a DEVICE pointer unless its comment says "host".
  *   - The caller owns every buffer, including workspaces.  The library
  *     allocates nothing and keeps no results between calls (it remembers, per
- *     device, which kernels it has configured and where its static scratch
- *     lies).  Inputs are never modified.  Outputs must not alias inputs unless
+ *     device, which kernels it has configured, where its static scratch lies
+ *     and, on the device, the room that running sequences take).  Inputs are never modified.  Outputs must not alias inputs unless
  *     stated.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Calls only enqueue work; they never synchronise the host.
@@ -213,9 +213,10 @@ size_t amq_lstm_sequence_flag_offset(int64_t I, int64_t H, int64_t B, int k_a);
 /*
  * Workspace of the faster forms of amq_lstm_sequence for B > 1.  Where the grid fits the chip (vectors of at most
  * 2048 entries, 1- to 3-bit codes, about 4096 hidden units times batch tiles of 16), pieces of about 4096 / B steps
- * run in one launch whose workgroups stay resident and exchange h_t and its codes through the workspace; such
- * launches take turns on a device, and if the workgroups cannot all become resident a launch that follows computes
- * the piece on its own, so the result does not depend on what else runs.  Otherwise (and on a stream that is being
+ * run in one launch whose workgroups stay resident and exchange h_t and its codes through the workspace.  Such
+ * launches (and those of batch 1) share a device: on several streams they run side by side as far as their workgroups
+ * fit, and wait their turn where they do not; if the workgroups cannot all become resident a launch that follows
+ * computes the piece on its own, so the result does not depend on what else runs.  Otherwise (and on a stream that is being
  * captured) W_x x_t is taken off the recurrent chain with two launches per step.  With a smaller workspace (at least
  * amq_lstm_workspace_bytes) the call runs the steps one after the other.  The arithmetic is the same in all forms.
  */
@@ -233,6 +234,14 @@ int amq_lstm_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t*
  * any kernel hanging.
  */
 void amq_debug_set_sequence_spin_limit(unsigned polls);
+
+/*
+ * Test hook: the launches whose workgroups wait for each other count the room they take on a device in shares of
+ * 32 workgroups (8 on 256 compute units).  Takes `shares` of them (-8 .. 8; negative: gives them back) in stream
+ * order, as another such launch would, so that those of later calls have to wait for room or go without (for as
+ * long as the spin limit says).  Every share taken has to be given back.
+ */
+int amq_debug_hold_sequence_shares(int shares, void* stream);
 
 /*
  * Measurement hook: one of the two launches of a steady-state step of the batched amq_lstm_sequence

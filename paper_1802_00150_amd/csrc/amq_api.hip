@@ -401,8 +401,8 @@ static amq::BmvArgs lstm_args(const uint32_t* Wxp, const float* alpha_x, const u
   return b;
 }
 
-// Whether a sequence takes the resident kernel: a shape it has room for, and a stream that is not being captured (it
-// orders itself after the launches of the kind on other streams, which a graph cannot).
+// Whether a sequence takes the resident kernel: a shape it has room for, and a stream that is not being captured (its
+// launches wait for room among others of the kind and have to be queued together, which a graph does not promise).
 static bool resident_sequence(const ResidentWs& w, int64_t I, int64_t H, int64_t B, int k_w, int k_a, int epi,
                               hipStream_t s) {
   if (!w.total || !amq::seqw_supported(I, H, B, k_w, k_a, epi)) return false;
@@ -602,6 +602,11 @@ size_t amq_lstm_sequence_flag_offset(int64_t I, int64_t H, int64_t B, int k_a) {
 
 void amq_debug_set_sequence_spin_limit(unsigned polls) { amq::set_seqg_spin_limit(polls); }
 
+int amq_debug_hold_sequence_shares(int shares, void* stream) {
+  if (shares < -8 || shares > 8) return AMQ_ERR_INVALID;
+  return hip_status(amq::launch_hold_shares(shares, static_cast<hipStream_t>(stream)));
+}
+
 int amq_lstm_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp, const float* alpha_h,
                       int64_t I, int64_t H, int k_w, const float* bias, const float* xs, int64_t steps,
                       float* h, float* c, int64_t B, int k_a, int T, float* hs, void* workspace,
@@ -618,7 +623,7 @@ int amq_lstm_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t*
     for (int64_t t0 = 0; t0 < steps; t0 += amq::kSeqGMaxSteps) {
       const int n = (int)(steps - t0 < amq::kSeqGMaxSteps ? steps - t0 : amq::kSeqGMaxSteps);
       amq::SeqGArgs q{Wxp, alpha_x, Whp, alpha_h, (int)I, (int)H, bias, xs + t0 * I, n, h, c,
-                      hs ? hs + t0 * H : nullptr, T, 0, w.sync, w.hbuf, w.xq, w.xbeta, t0 == 0, 0};
+                      hs ? hs + t0 * H : nullptr, T, 0, w.sync, w.hbuf, w.xq, w.xbeta, t0 == 0};
       st = hip_status(amq::launch_lstm_seqg(q, k_w, k_a, static_cast<hipStream_t>(stream)));
       if (st != AMQ_OK) return st;
       // a launch that gave up (or found the flag of an earlier one) leaves its rows of hs as NaN
@@ -1332,7 +1337,7 @@ static int lm_sequence_impl(const uint32_t* Ep, const float* alpha_e, int64_t vo
       st = hip_status(amq::launch_quantize(q, k_a, s));
       if (st != AMQ_OK) return st;
       amq::SeqGArgs g{Wxp, alpha_x, Whp, alpha_h, (int)E, (int)H, bias, nullptr, n, h, c, lw.hs, T, 0, w.sync, w.hbuf,
-                      w.xq, w.xbeta, t0 == 0, 0};
+                      w.xq, w.xbeta, t0 == 0};
       st = hip_status(amq::launch_lstm_seqg(g, k_w, k_a, s));
       if (st != AMQ_OK) return st;
       st = output_layer(t0, n);

@@ -6,7 +6,8 @@
 #include <stdint.h>
 
 #include <atomic>
-#include <mutex>
+
+#include "amq_resident.h"
 
 namespace amq {
 
@@ -261,7 +262,7 @@ struct SeqGArgs {
   float* xbeta;         // [steps][k_a]: their coefficients
   int first_piece;      // non-zero: also clear the give-up flag (once per API call; a later piece of the
                         // same call must see a flag an earlier piece raised)
-  unsigned* lock;       // filled by launch_lstm_seqg
+  ResidentClaim claim;  // filled by launch_lstm_seqg
   unsigned spin_limit;  // filled by launch_lstm_seqg: polls of a wait before it gives up
 };
 bool lstm_seqg_supported(long long I, long long H, long long B, int k_w, int k_a);
@@ -275,27 +276,6 @@ hipError_t launch_seqg_poison(const unsigned* sync, float* out, long long count,
 
 // Polls a wait of the resident sequence kernels may take (see set_seqg_spin_limit).
 unsigned sequence_spin_limit();
-
-// Launches whose workgroups wait for each other need all of them resident, so one at a time runs per device: a small
-// kernel before each takes a lock in device memory (null: not available), the last kernel of the group returns it.  The
-// launches of a group are queued together, under resident_launches().
-unsigned* resident_lock();
-std::mutex& resident_launches();
-constexpr unsigned long long kLockTicks = 20000000ull;  // 0.2 s of the 100 MHz clock
-__device__ __forceinline__ bool take_resident_lock(unsigned* lock) {
-  if (!lock) return true;
-  const unsigned long long start = wall_clock64();
-  for (;;) {
-    unsigned free = 0u;
-    if (__hip_atomic_compare_exchange_strong(lock, &free, 1u, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      return true;
-    if (wall_clock64() - start > kLockTicks) return false;
-    __builtin_amdgcn_s_sleep(32);
-  }
-}
-__device__ __forceinline__ void give_resident_lock(unsigned* lock) {
-  if (lock) __hip_atomic_store(lock, 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // ---- whole sequences of a batch in one launch spread over the chip (amq_seqw.hip) ---------------
 struct SeqWArgs {

@@ -187,25 +187,29 @@ __device__ __forceinline__ bool quantize_wg(const void* src_v, unsigned tag, uns
 
 // Before a launch: clears the arrival bytes and the tags of the published state; the give-up flag only
 // for the first launch of an API call.
-// Takes the lock of the resident launches (see take_resident_lock; without it the launch goes ahead all the same, as
-// its waits are bounded).
+// Claims room for the launch (amq_resident.h; without it the launch goes ahead all the same, as its waits are bounded).
 constexpr int kLeft = 1 + kSeqGMaxGrid / 4;  // words of sync after the arrival bytes: workgroups that have left,
-constexpr int kLocked = kLeft + 1;           // and whether the lock is held for this launch
-__global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, int H, int clear_flag, unsigned* lock) {
+constexpr int kClaimed = kLeft + 1;          // and whether room was claimed for this launch
+__global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, int H, int clear_flag, ResidentClaim claim) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
   if (t == 0) {
     if (clear_flag) sync[0] = 0u;
     sync[kLeft] = 0u;
-    sync[kLocked] = (lock && take_resident_lock(lock)) ? 1u : 0u;
+    sync[kClaimed] = take_resident_share(claim) ? 1u : 0u;
   }
   for (int i = 1 + t; i < 1 + kSeqGMaxGrid / 4; i += nt) sync[i] = 0u;
   for (int i = t; i < 2 * H; i += nt) hbuf[i] = 0ull;
 }
 
-// One thread of a workgroup that is about to leave: the last one returns the lock.
-__device__ __forceinline__ void leave(unsigned* sync, unsigned* lock) {
-  if (sync[kLocked] == 0u) return;
-  if (__hip_atomic_fetch_add(sync + kLeft, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) give_resident_lock(lock);
+// One thread of a workgroup that is about to leave: the last one gives the room back.
+__device__ __forceinline__ void leave(unsigned* sync, const ResidentClaim& claim) {
+  if (sync[kClaimed] == 0u) return;
+  if (__hip_atomic_fetch_add(sync + kLeft, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) give_resident_share(claim);
+}
+
+// Should the launch itself fail: nobody is there to leave.
+__global__ void seqg_abandon_kernel(const unsigned* sync, ResidentClaim claim) {
+  if (sync[kClaimed] != 0u) give_resident_share(claim);
 }
 
 __global__ void seqg_poison_kernel(const unsigned* sync, float* out, long long count) {
@@ -245,7 +249,7 @@ __global__ __launch_bounds__(64 * kGWaves, 2) void lstm_seqg_kernel(SeqGArgs a) 
   if (threadIdx.x == 0) gave_up = get_u(a.sync);
   __syncthreads();
   if (gave_up != 0u) {
-    if (threadIdx.x == 0) leave(a.sync, a.lock);
+    if (threadIdx.x == 0) leave(a.sync, a.claim);
     return;
   }
   const unsigned limit = a.spin_limit;
@@ -357,17 +361,21 @@ __global__ __launch_bounds__(64 * kGWaves, 2) void lstm_seqg_kernel(SeqGArgs a) 
     a.h[unit] = hlast;
     a.c[unit] = cst;
   }
-  if (tid == 0) leave(a.sync, a.lock);
+  if (tid == 0) leave(a.sync, a.claim);
 }
 
 template <int KW, int KA>
 hipError_t launch_kk(const SeqGArgs& a, int grid, hipStream_t s) {
   std::lock_guard<std::mutex> together(resident_launches());
-  hipLaunchKernelGGL(seqg_reset_kernel, dim3(8), dim3(256), 0, s, a.sync, a.hbuf, a.H, a.first_piece, a.lock);
+  hipLaunchKernelGGL(seqg_reset_kernel, dim3(8), dim3(256), 0, s, a.sync, a.hbuf, a.H, a.first_piece, a.claim);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((lstm_seqg_kernel<KW, KA>), dim3(grid), dim3(64 * kGWaves), 0, s, a);
-  return hipGetLastError();
+  e = hipGetLastError();
+  if (e == hipSuccess) return e;
+  hipLaunchKernelGGL(seqg_abandon_kernel, dim3(1), dim3(1), 0, s, a.sync, a.claim);
+  (void)hipGetLastError();
+  return e;
 }
 
 int seqg_lg(int I, int H) {
@@ -403,9 +411,9 @@ hipError_t launch_seqg_poison(const unsigned* sync, float* out, long long count,
 hipError_t launch_lstm_seqg(SeqGArgs a, int k_w, int k_a, hipStream_t s) {
   a.lg = seqg_lg(a.I, a.H);
   a.spin_limit = g_spin_limit.load();
-  a.lock = resident_lock();
   const int units_per_wg = kGWaves * (8 >> a.lg);
   const int grid = (a.H + units_per_wg - 1) / units_per_wg;
+  a.claim = resident_claim(grid, true);
   if (grid > kSeqGMaxGrid || a.steps > kSeqGMaxSteps) return hipErrorInvalidValue;
   if (k_w == 2 && k_a == 2) return launch_kk<2, 2>(a, grid, s);
   if (k_w == 2 && k_a == 3) return launch_kk<2, 3>(a, grid, s);

@@ -19,9 +19,9 @@
 //
 // The arithmetic and its order are those of the per-step kernels: the results are the same bit for bit.
 //
-// All workgroups must be resident at once: the host launches this only where the grid fits the chip, and a lock on the
-// device lets one such launch run at a time (the reset kernel takes it, the recovery kernel returns it).  Should the
-// chip be shared in a way this cannot see, the waits are bounded: a workgroup that gives up raises a flag, everyone
+// All workgroups must be resident at once: the host launches this only where the grid fits the chip, and such launches
+// share it by a count kept on the device (amq_resident.h: the reset kernel claims room, the recovery kernel gives it
+// back).  Should the chip be shared in a way this cannot see, the waits are bounded: a workgroup that gives up raises a flag, everyone
 // leaves, and the launch that always follows (seqw_recover_kernel) computes the piece again from the saved initial
 // state, one workgroup per batch entry, with no exchange between workgroups -- slow, but it depends on nobody; without
 // the flag it returns at once.
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(64 * kWWaves, 2) void seqw_kernel(SeqWArgs a) {
     lds_barrier();
   }
 
-  if (*flag != 0u) return;  // (the lock could not be had)
+  if (*flag != 0u) return;  // (there was no room)
 
   // ---- codes of the inputs (x waves), [plane][step * batch + entry][piece]: the tile is KA * NC * 2 requests of 1 KiB
   // (plane, stretch, half of the tile; lane -> entry, 16-byte piece), dealt to the four x waves in turn
@@ -487,24 +487,24 @@ __global__ __launch_bounds__(64 * kWWaves, 2) void seqw_kernel(SeqWArgs a) {
   }
 }
 
-// Before a launch: the lock (waited for at most kLockTicks; without it the flag is raised at once), no tags.
-constexpr unsigned kNoLock = 2u;  // (any other value but 0: a wait gave up)
+// Before a launch: room for it (without it the flag is raised at once), no tags.
+constexpr unsigned kNoRoom = 2u;  // (any other value but 0: a wait gave up)
 
-__global__ __launch_bounds__(256) void seqw_reset_kernel(unsigned* flag, unsigned* lock, uint4* pairs, long long units) {
+__global__ __launch_bounds__(256) void seqw_reset_kernel(unsigned* flag, ResidentClaim claim, uint4* pairs, long long units) {
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x, nt = (long long)gridDim.x * blockDim.x;
   for (long long i = t; i < units; i += nt) pairs[i] = make_uint4(0, 0, 0, 0);
-  if (t == 0) *flag = take_resident_lock(lock) ? 0u : kNoLock;
+  if (t == 0) *flag = take_resident_share(claim) ? 0u : kNoRoom;
 }
 
 // The piece again from the saved state if the launch before gave up: one workgroup per batch entry.
 template <int KA>
-__global__ __launch_bounds__(64 * kWBlocks) void seqw_recover_kernel(SeqWArgs a, int KW, int gru, unsigned* lock) {
+__global__ __launch_bounds__(64 * kWBlocks) void seqw_recover_kernel(SeqWArgs a, int KW, int gru, ResidentClaim claim) {
   __shared__ double sh[2 * kExchange<kWBlocks>];
   __shared__ float hcur[2][2048];
   __shared__ uint32_t codes[KA * 64];
   __shared__ float hbeta[KA];
   const unsigned why = *a.flag;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && why != kNoLock) give_resident_lock(lock);
+  if (blockIdx.x == 0 && threadIdx.x == 0 && why != kNoRoom) give_resident_share(claim);
   if (why == 0u) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -576,13 +576,13 @@ __global__ __launch_bounds__(64 * kWBlocks) void seqw_recover_kernel(SeqWArgs a,
   for (int u = tid; u < H; u += 64 * kWBlocks) a.h0[(size_t)b * H + u] = hcur[a.steps & 1][u];
 }
 
-hipError_t launch_recover(const SeqWArgs& a, int k_w, int k_a, int epi, unsigned* lock, hipStream_t s) {
+hipError_t launch_recover(const SeqWArgs& a, int k_w, int k_a, int epi, const ResidentClaim& claim, hipStream_t s) {
   const dim3 grid((unsigned)a.batch), block(64 * kWBlocks);
   const int gru = epi == kEpiGru;
   switch (k_a) {
-    case 1: hipLaunchKernelGGL((seqw_recover_kernel<1>), grid, block, 0, s, a, k_w, gru, lock); break;
-    case 2: hipLaunchKernelGGL((seqw_recover_kernel<2>), grid, block, 0, s, a, k_w, gru, lock); break;
-    default: hipLaunchKernelGGL((seqw_recover_kernel<3>), grid, block, 0, s, a, k_w, gru, lock); break;
+    case 1: hipLaunchKernelGGL((seqw_recover_kernel<1>), grid, block, 0, s, a, k_w, gru, claim); break;
+    case 2: hipLaunchKernelGGL((seqw_recover_kernel<2>), grid, block, 0, s, a, k_w, gru, claim); break;
+    default: hipLaunchKernelGGL((seqw_recover_kernel<3>), grid, block, 0, s, a, k_w, gru, claim); break;
   }
   return hipGetLastError();
 }
@@ -628,8 +628,12 @@ hipError_t run_k(const SeqWArgs* l, dim3 grid, int epi, int nc, hipStream_t s) {
   return nc == 1 ? run_one<KW, KA, kEpiGru, 1>(l, grid, s) : run_one<KW, KA, kEpiGru, 2>(l, grid, s);
 }
 
+dim3 seqw_grid(long long H, long long batch) {
+  return dim3((unsigned)((H + 4 * kWBlocks - 1) / (4 * kWBlocks)), (unsigned)((batch + kTileB - 1) / kTileB));
+}
+
 hipError_t run(const SeqWArgs* l, long long I, long long H, long long batch, int k_w, int k_a, int epi, hipStream_t s) {
-  const dim3 grid((unsigned)((H + 4 * kWBlocks - 1) / (4 * kWBlocks)), (unsigned)((batch + kTileB - 1) / kTileB));
+  const dim3 grid = seqw_grid(H, batch);
   const int nc = (I > H ? I : H) > 1024 ? 2 : 1;
   switch (k_w * 4 + k_a) {
     case 4 * 1 + 1: return run_k<1, 1>(l, grid, epi, nc, s);
@@ -683,43 +687,81 @@ hipError_t launch_seqw(SeqWArgs a, const SeqWScratch& w, int k_w, int k_a, int e
   a.limit = sequence_spin_limit();
   const long long units = (long long)(w.pair_bytes / sizeof(uint4));
   const long long blocks = (units + 1023) / 1024;
-  // (the three launches of a piece are put into the queue together: a reset kernel that waits for the lock never stands
-  // between another piece's launches where streams share a hardware queue)
+  const dim3 grid = seqw_grid(a.H, a.batch);
+  const ResidentClaim claim = resident_claim((long long)grid.x * grid.y, false);
   std::lock_guard<std::mutex> together(resident_launches());
-  unsigned* const lock = resident_lock();
-  hipLaunchKernelGGL(seqw_reset_kernel, dim3((unsigned)(blocks < 512 ? blocks : 512)), dim3(256), 0, s, w.flag, lock,
+  hipLaunchKernelGGL(seqw_reset_kernel, dim3((unsigned)(blocks < 512 ? blocks : 512)), dim3(256), 0, s, w.flag, claim,
                      reinterpret_cast<uint4*>(w.hbuf), units);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const hipError_t ran = run(&a, a.x.n, a.H, a.batch, k_w, k_a, epi, s);
-  e = launch_recover(a, k_w, k_a, epi, lock, s);
+  e = launch_recover(a, k_w, k_a, epi, claim, s);
   return ran != hipSuccess ? ran : e;
 }
 
-// ---- the lock ------------------------------------------------------------------------------------------------
-static __device__ unsigned resident_lock_word;
+// ---- shares of the chip (amq_resident.h) ---------------------------------------------------------------------
+static __device__ unsigned resident_word;
 
-unsigned* resident_lock() {
-  static std::atomic<unsigned*> known[64];
+namespace {
+
+__global__ void hold_shares_kernel(unsigned* word, unsigned shares) {
+  __hip_atomic_fetch_add(word, shares, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+struct ResidentDevice {
+  std::atomic<unsigned*> word;
+  std::atomic<unsigned> shares;
+};
+
+// Address of the word on the current device and the shares the device has, looked up once per device.
+ResidentClaim resident_device() {
+  static ResidentDevice known[64];
+  ResidentClaim c{};
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+  if (hipGetDevice(&dev) != hipSuccess) return c;
   const bool tracked = dev >= 0 && dev < 64;
-  if (tracked) {
-    unsigned* p = known[dev].load(std::memory_order_acquire);
-    if (p) return p;
+  if (tracked && (c.word = known[dev].word.load(std::memory_order_acquire)) != nullptr) {
+    c.shares = known[dev].shares.load(std::memory_order_relaxed);
+    return c;
   }
   void* p = nullptr;
-  if (hipGetSymbolAddress(&p, HIP_SYMBOL(resident_lock_word)) != hipSuccess) {
+  int cus = 0;
+  if (hipGetSymbolAddress(&p, HIP_SYMBOL(resident_word)) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
     (void)hipGetLastError();
-    return nullptr;
+    return c;
   }
-  if (tracked) known[dev].store(static_cast<unsigned*>(p), std::memory_order_release);
-  return static_cast<unsigned*>(p);
+  c.shares = cus > kShareGrid ? (unsigned)(cus / kShareGrid) : 1u;
+  c.word = static_cast<unsigned*>(p);
+  if (tracked) {
+    known[dev].shares.store(c.shares, std::memory_order_relaxed);
+    known[dev].word.store(c.word, std::memory_order_release);
+  }
+  return c;
+}
+
+}  // namespace
+
+ResidentClaim resident_claim(long long grid, bool light) {
+  ResidentClaim c = resident_device();
+  const long long need = (grid + kShareGrid - 1) / kShareGrid;
+  const unsigned shares = need < (long long)c.shares ? (unsigned)need : c.shares;
+  c.mine = light ? shares << 8 : shares;
+  // as long as a wait of the kernels may take: 2^19 polls are about 0.2 s
+  c.ticks = 40ull * sequence_spin_limit();
+  return c;
 }
 
 std::mutex& resident_launches() {
   static std::mutex m;
   return m;
+}
+
+hipError_t launch_hold_shares(int shares, hipStream_t s) {
+  const ResidentClaim c = resident_device();
+  if (!c.word) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(hold_shares_kernel, dim3(1), dim3(1), 0, s, c.word, (unsigned)shares);
+  return hipGetLastError();
 }
 
 }  // namespace amq
