@@ -191,14 +191,14 @@ __device__ __forceinline__ bool quantize_wg(const void* src_v, unsigned tag, uns
 constexpr int kLeft = 1 + kSeqGMaxGrid / 4;  // words of sync after the arrival bytes: workgroups that have left,
 constexpr int kClaimed = kLeft + 1;          // and whether room was claimed for this launch
 __global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, int H, int clear_flag, ResidentClaim claim) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
   if (t == 0) {
     if (clear_flag) sync[0] = 0u;
     sync[kLeft] = 0u;
     sync[kClaimed] = take_resident_share(claim) ? 1u : 0u;
   }
-  for (int i = 1 + t; i < 1 + kSeqGMaxGrid / 4; i += nt) sync[i] = 0u;
-  for (int i = t; i < 2 * H; i += nt) hbuf[i] = 0ull;
+  for (unsigned i = 1 + t; i < 1 + kSeqGMaxGrid / 4; i += nt) sync[i] = 0u;
+  for (unsigned i = t; i < 2 * (unsigned)H; i += nt) hbuf[i] = 0ull;
 }
 
 // One thread of a workgroup that is about to leave: the last one gives the room back.

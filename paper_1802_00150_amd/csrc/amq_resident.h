@@ -11,6 +11,10 @@
 // workgroup; of a light one (amq_lstm_seqg.hip: one wave per SIMD, up to 144 of its 512 registers) a unit holds three, as
 // long as no full claim is about.  Any placement of the workgroups then leaves room for those still to come.
 //
+// The waves that wait for room must not sit where a grid that has its room still has to go, so a full claim's kernels use
+// at most kResidentRegisters each and a waiting one 8: beside two of the former on a SIMD there is room for four of the
+// latter, as many as a process has hardware queues.
+//
 // The word on the device: full shares in bits 0..7, light ones in bits 8..15, and the door.  Whoever finds no room closes
 // the door and is the next to get some; small claims do not keep a large one waiting for ever.
 #pragma once
@@ -22,6 +26,7 @@ namespace amq {
 
 constexpr int kShareGrid = 32;
 constexpr int kLightPerUnit = 3;
+constexpr int kResidentRegisters = 240;  // (the attribute that limits them counts half: one of the two kinds)
 constexpr unsigned kDoor = 1u << 31;
 
 struct ResidentClaim {
@@ -37,6 +42,7 @@ __device__ __forceinline__ bool resident_room(unsigned used, const ResidentClaim
   const unsigned sum = (used & ~kDoor) + c.mine, full = sum & 255u, light = sum >> 8;
   return full ? full + light <= c.shares : light <= kLightPerUnit * c.shares;
 }
+// To be called by one lane.  (What it reads goes to the scalar unit: a wave that waits here should hold few registers.)
 __device__ __forceinline__ bool take_resident_share(const ResidentClaim& c) {
   if (!c.word) return true;
   const unsigned long long start = wall_clock64();
@@ -45,18 +51,21 @@ __device__ __forceinline__ bool take_resident_share(const ResidentClaim& c) {
     // (the common case is an idle chip: one exchange)
     unsigned next = used;
     if ((used & kDoor) == door) next = resident_room(used, c) ? (used & ~kDoor) + c.mine : used | kDoor;
-    unsigned seen = used;
-    if (next != used && __hip_atomic_compare_exchange_strong(c.word, &seen, next, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED,
-                                                            __HIP_MEMORY_SCOPE_AGENT)) {
-      if (!(next & kDoor)) return true;
-      door = kDoor;
+    if (next != used) {
+      unsigned seen = used;
+      __hip_atomic_compare_exchange_strong(c.word, &seen, next, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if ((unsigned)__builtin_amdgcn_readfirstlane((int)seen) == used) {
+        if (!(next & kDoor)) return true;
+        door = kDoor;
+      }
     }
     if (wall_clock64() - start > c.ticks) {
       if (door) __hip_atomic_fetch_and(c.word, ~kDoor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return false;
     }
     if (next == used || (next & kDoor)) __builtin_amdgcn_s_sleep(32);
-    used = __hip_atomic_load(c.word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    used = (unsigned)__builtin_amdgcn_readfirstlane(
+        (int)__hip_atomic_load(c.word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   }
 }
 __device__ __forceinline__ void give_resident_share(const ResidentClaim& c) {

@@ -170,7 +170,8 @@ constexpr size_t seqw_lds() {
 // NC: stretches of 1024 entries of the longer operand block (1 or 2).  Waves 0 .. 3 take the h side, the cell and the
 // quantizer, waves 4 .. 7 the x side of the next step.
 template <int KW, int KA, int EPI, int NC>
-__global__ __launch_bounds__(64 * kWWaves, 2) void seqw_kernel(SeqWArgs a) {
+__global__ __launch_bounds__(64 * kWWaves, 2) __attribute__((amdgpu_num_vgpr(kResidentRegisters / 2))) void
+seqw_kernel(SeqWArgs a) {
   constexpr int NG = (EPI == kEpiGru) ? 3 : 4;
   constexpr int kImage = KA * NC * kSteps * 64;
   constexpr int NJ = 4 * NC;  // slots per lane of the quantizer
@@ -325,9 +326,9 @@ __global__ __launch_bounds__(64 * kWWaves, 2) void seqw_kernel(SeqWArgs a) {
   const int centry = seqw_entry_pairs(KA, wprH);
   const size_t chalf = (size_t)gridDim.y * kTileB * centry;
   int phase = 0;
-  // publishing h_t: thread -> entry and unit
+  // publishing h_t (h waves): thread -> entry and unit
   const int hp_unit = 4 * kWBlocks * bx + (tid & 15), hp_col = (tid >> 4) & 15;
-  const bool hp_ok = !xwave && hp_unit < H && hp_col < ncols;
+  const bool hp_ok = hp_unit < H && hp_col < ncols;
   const size_t hp_at = (size_t)(b0 + (hp_ok ? hp_col : 0)) * H + (hp_ok ? hp_unit : 0);
 
   // ---- gathering the codes of a step (h waves): thread -> word of the row and entry; the same bytes land where
@@ -362,23 +363,29 @@ __global__ __launch_bounds__(64 * kWWaves, 2) void seqw_kernel(SeqWArgs a) {
     sums(xbeta, y);
     xsum[u & 1][blk][lane] = make_float4(y[0], y[1], y[2], y[3]);
   };
-  if (xwave) {
-    request_inputs(0);
-    stage_inputs(0);
-  }
-  lds_barrier();
-  if (xwave) x_side(0);
-  lds_barrier();  // (the image of the x side may be overwritten)
-
-  for (int t = 0; t < a.steps; ++t) {
+  // ---- a step of the x waves and of the h waves, with the same barriers in both; true: somebody waits in vain, so all
+  // leave and the piece is done again.  Each kind has its own loop over the steps, so that what only one of them keeps
+  // takes no registers in the other.  With one loop for both the forms needed up to 256 registers (W3/A3 on two
+  // stretches 32 more, spilled), now 15 to 40 fewer; 240 are allowed (kResidentRegisters), which leaves W3/A3 on two
+  // stretches 40 to 53 spilled, W2/A3 on two 9 to 11, W3/A2 up to 8.  35 steps, us before / now: 1024 units batch 64
+  // W2/A2 186.0 / 185.5, W3/A2 189.1 / 190.2, W3/A3 229.4 / 229.1; 1500 units batch 20 W2/A3 281.6 / 273.7, W3/A2
+  // 232.9 / 235.6, W3/A3 314.3 / 316.0, GRU W3/A3 329.6 / 311.0.
+  auto x_step = [&](int t) {
+    stage_inputs(t + 1);
+    for (int e = q_first; e < ncols; e += q_next)
+      for (int i = quantize_exchanges<KA>(a.T) + 1; i > 0; --i) lds_barrier();
+    lds_barrier();
+    // x side of step t + 1, while the codes are under way
+    x_side(t + 1);
+    lds_barrier();
+    const int gone = dead;
+    if (t + 1 < a.steps) lds_barrier();
+    return __builtin_amdgcn_readfirstlane(gone) != 0;
+  };
+  auto h_step = [&](int t) {
     const unsigned tag = (unsigned)t + 1u;
-    if (xwave) stage_inputs(t + 1);
     // ---- quantize h_{t-1} of the entries in this workgroup's charge
     for (int e = q_first; e < ncols; e += q_next) {
-      if (xwave) {
-        for (int i = quantize_exchanges<KA>(a.T) + 1; i > 0; --i) lds_barrier();
-        continue;
-      }
       float v[NJ];
       if (t == 0) {
         load_slots<NJ>(a.h0 + (size_t)(b0 + e) * H, H, base, nj, v);
@@ -430,69 +437,77 @@ __global__ __launch_bounds__(64 * kWWaves, 2) void seqw_kernel(SeqWArgs a) {
 
     lds_barrier();
 
-    float beta = 0.0f;
-    if (xwave) {
-      // ---- x side of step t + 1, while the codes are under way
-      x_side(t + 1);
-    } else {
-      // ---- codes of h_{t-1}
-      const char* src = reinterpret_cast<const char*>(a.cbuf + (t & 1) * chalf + (size_t)tile * kTileB * centry);
-      auto at = [](const char* base, unsigned off) { return reinterpret_cast<const unsigned long long*>(base + off); };
-      unsigned long long v[kGather], bv;
-      unsigned spins = 0;
-      for (;;) {
-        bv = get_pair(at(src, gboff));
+    // ---- codes of h_{t-1}
+    const char* src = reinterpret_cast<const char*>(a.cbuf + (t & 1) * chalf + (size_t)tile * kTileB * centry);
+    auto at = [](const char* base, unsigned off) { return reinterpret_cast<const unsigned long long*>(base + off); };
+    unsigned long long v[kGather], bv;
+    unsigned spins = 0;
+    for (;;) {
+      bv = get_pair(at(src, gboff));
 #pragma unroll
-        for (int q = 0; q < kGather; ++q) v[q] = get_pair(at(src + (q / kColReq) * wprH * 8, goff[q % kColReq]));
-        bool ready = (unsigned)(bv >> 32) == tag;
+      for (int q = 0; q < kGather; ++q) v[q] = get_pair(at(src + (q / kColReq) * wprH * 8, goff[q % kColReq]));
+      bool ready = (unsigned)(bv >> 32) == tag;
 #pragma unroll
-        for (int q = 0; q < kGather; ++q) ready = ready && (unsigned)(v[q] >> 32) == tag;
-        if (__all(ready)) break;
-        if (!poll_again(spins, a.limit, flag)) {
-          dead = 1;
-          break;
-        }
+      for (int q = 0; q < kGather; ++q) ready = ready && (unsigned)(v[q] >> 32) == tag;
+      if (__all(ready)) break;
+      if (!poll_again(spins, a.limit, flag)) {
+        dead = 1;
+        break;
       }
-#pragma unroll
-      for (int q = 0; q < kGather; ++q)
-        image[(q / kColReq) * NC * kSteps * 64 + gdst + ((q % kColReq * kColsPer + gc) ^ gswz)] =
-            expand4_signed(gok ? (uint32_t)(v[q] & 0xffffffffull) : 0u);
-      beta = __uint_as_float((unsigned)(bv & 0xffffffffull));
     }
+#pragma unroll
+    for (int q = 0; q < kGather; ++q)
+      image[(q / kColReq) * NC * kSteps * 64 + gdst + ((q % kColReq * kColsPer + gc) ^ gswz)] =
+          expand4_signed(gok ? (uint32_t)(v[q] & 0xffffffffull) : 0u);
+    const float beta = __uint_as_float((unsigned)(bv & 0xffffffffull));
     lds_barrier();
     const int gone = dead;
 
     // ---- h side and cell
-    if (!xwave) {
-      float y[4];
-      sums(beta, y);
-      const float4 x4 = xsum[t & 1][blk][lane];
-      const float yx[4] = {x4.x, x4.y, x4.z, x4.w};
-      cell<EPI>(yx, y, bs0, bs1, h, c);
-      if (own) {
-        if (a.hs) a.hs[(size_t)t * hhalf + state] = h;
-      }
-      hout[l16][4 * blk + l4] = h;
+    float y[4];
+    sums(beta, y);
+    const float4 x4 = xsum[t & 1][blk][lane];
+    const float yx[4] = {x4.x, x4.y, x4.z, x4.w};
+    cell<EPI>(yx, y, bs0, bs1, h, c);
+    if (own) {
+      if (a.hs) a.hs[(size_t)t * hhalf + state] = h;
     }
+    hout[l16][4 * blk + l4] = h;
     if (t + 1 < a.steps) {
       // published through LDS as well: 16 units are one cache line
       lds_barrier();
       if (hp_ok) put_pair(a.hbuf + (t & 1) * hhalf + hp_at, __float_as_uint(hout[(tid >> 4) & 15][tid & 15]), tag);
     }
-    if (__builtin_amdgcn_readfirstlane(gone)) return;  // (somebody waits in vain: all leave, the piece is done again)
+    return __builtin_amdgcn_readfirstlane(gone) != 0;
+  };
+
+  if (!xwave) {
+    lds_barrier();
+    lds_barrier();
+    for (int t = 0; t < a.steps; ++t)
+      if (h_step(t)) return;
+    if (own) {
+      a.h0[state] = h;
+      if (EPI == kEpiLstm) a.c0[state] = c;
+    }
+    return;
   }
-  if (own) {
-    a.h0[state] = h;
-    if (EPI == kEpiLstm) a.c0[state] = c;
-  }
+  request_inputs(0);
+  stage_inputs(0);
+  lds_barrier();
+  x_side(0);
+  lds_barrier();  // (the image may be overwritten)
+  for (int t = 0; t < a.steps; ++t)
+    if (x_step(t)) return;
 }
 
 // Before a launch: room for it (without it the flag is raised at once), no tags.
 constexpr unsigned kNoRoom = 2u;  // (any other value but 0: a wait gave up)
 
-__global__ __launch_bounds__(256) void seqw_reset_kernel(unsigned* flag, ResidentClaim claim, uint4* pairs, long long units) {
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x, nt = (long long)gridDim.x * blockDim.x;
-  for (long long i = t; i < units; i += nt) pairs[i] = make_uint4(0, 0, 0, 0);
+__global__ __launch_bounds__(256) void seqw_reset_kernel(unsigned* flag, ResidentClaim claim, unsigned long long* pairs,
+                                                         unsigned count) {
+  const unsigned t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+  for (unsigned i = t; i < count; i += nt) pairs[i] = 0ull;
   if (t == 0) *flag = take_resident_share(claim) ? 0u : kNoRoom;
 }
 
@@ -607,7 +622,7 @@ int resident_grid() {
     (void)hipGetLastError();
     return 0;
   }
-  const int fit = cus * (per < 2 ? per : 2);
+  const int fit = per > 0 ? cus : 0;  // (one to a compute unit: what a claim counts on)
   if (tracked) known[dev].store(fit + 1, std::memory_order_release);
   return fit;
 }
@@ -685,13 +700,12 @@ hipError_t launch_seqw(SeqWArgs a, const SeqWScratch& w, int k_w, int k_a, int e
   a.save_h = w.save_h;
   a.save_c = w.save_c;
   a.limit = sequence_spin_limit();
-  const long long units = (long long)(w.pair_bytes / sizeof(uint4));
-  const long long blocks = (units + 1023) / 1024;
+  const unsigned pairs = (unsigned)(w.pair_bytes / sizeof(unsigned long long));
+  const unsigned blocks = (pairs + 2047) / 2048;
   const dim3 grid = seqw_grid(a.H, a.batch);
   const ResidentClaim claim = resident_claim((long long)grid.x * grid.y, false);
   std::lock_guard<std::mutex> together(resident_launches());
-  hipLaunchKernelGGL(seqw_reset_kernel, dim3((unsigned)(blocks < 512 ? blocks : 512)), dim3(256), 0, s, w.flag, claim,
-                     reinterpret_cast<uint4*>(w.hbuf), units);
+  hipLaunchKernelGGL(seqw_reset_kernel, dim3(blocks < 512 ? blocks : 512), dim3(256), 0, s, w.flag, claim, w.hbuf, pairs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const hipError_t ran = run(&a, a.x.n, a.H, a.batch, k_w, k_a, epi, s);

@@ -122,6 +122,8 @@ def test_a_claim_waits_only_where_there_is_no_room(amq, held, H, B, k, share):
     [(4, 300, 300, 1, 2, 2, 70), (4, 300, 300, 16, 2, 2, 40), (3, 200, 400, 20, 2, 3, 40), (4, 650, 650, 1, 3, 3, 40)],
     # grids that take the whole chip, one after the other, among small ones
     [(4, 1024, 1024, 64, 3, 3, 12), (4, 1024, 1024, 1, 2, 2, 40), (3, 1024, 1024, 50, 2, 2, 12), (4, 300, 300, 16, 2, 2, 40)],
+    # the forms that hold the most registers on (nearly) every compute unit: a launch that waits must not be in their way
+    [(4, 2048, 2048, 17, 3, 2, 8), (4, 1500, 1500, 32, 3, 3, 8), (3, 1024, 1024, 64, 3, 2, 8), (4, 2048, 2048, 32, 2, 3, 8)],
 ])
 def test_streams_and_threads_share_the_chip(amq, shapes):
     # every thread has a stream, a workspace and a model of its own and enqueues several calls without waiting

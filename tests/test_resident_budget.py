@@ -1,0 +1,69 @@
+"""Registers of the kernels whose workgroups wait for each other, from the built library: a compute unit that holds as many
+of their workgroups as are counted on must still have room for the waves that wait for room (amq_resident.h), or such a
+wave could sit where a grid that has its room already needs to go."""
+import os
+import re
+import struct
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SIMD_REGISTERS = 512   # per lane, both kinds together
+WAITERS = 4            # hardware queues of a process: at most that many kernels wait, all on one SIMD at worst
+
+
+def kernels():
+    """Name -> metadata of every kernel in the library's code objects."""
+    msgpack = pytest.importorskip("msgpack")
+    from paper_1802_00150_amd import build
+    if not os.path.exists(build.LIB):
+        build.build()
+    blob = open(build.LIB, "rb").read()
+    found = {}
+    for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", blob):
+        n, = struct.unpack_from("<Q", blob, m.end())
+        at = m.end() + 8
+        if n > 16:
+            continue  # (the word by itself, no bundle)
+        for _ in range(n):
+            offset, size, length = struct.unpack_from("<QQQ", blob, at)
+            target = blob[at + 24:at + 24 + length]
+            at += 24 + length
+            if b"gfx950" not in target:
+                continue
+            code = blob[m.start() + offset:m.start() + offset + size]
+            for note in re.finditer(b"AMDGPU\0\0", code):
+                namesz, descsz, kind = struct.unpack_from("<III", code, note.start() - 12)
+                if namesz == 7 and kind == 32:
+                    meta = msgpack.unpackb(code[note.end():note.end() + descsz])
+                    found.update({k[".name"]: k for k in meta["amdhsa.kernels"]})
+    return found
+
+
+@pytest.fixture(scope="module")
+def registers():
+    """Kernel name -> registers a wave is given (handed out in eights)."""
+    return {name: (k[".vgpr_count"] + 7) // 8 * 8 for name, k in kernels().items()}
+
+
+def of(registers, pattern, count):
+    hits = {k: v for k, v in registers.items() if re.search(pattern, k)}
+    assert len(hits) == count, sorted(hits)
+    return hits
+
+
+def test_waiting_kernels_hold_few_registers(registers):
+    for name, r in of(registers, "seq[gw]_reset_kernel", 2).items():
+        assert r <= 8, (name, r)
+
+
+def test_room_for_waiting_kernels_beside_a_full_claim(registers):
+    # one workgroup of 8 waves per compute unit: two waves on every SIMD
+    for name, r in of(registers, "11seqw_kernel", 36).items():
+        assert 2 * r + WAITERS * 8 <= SIMD_REGISTERS, (name, r)
+
+
+def test_room_for_waiting_kernels_beside_light_claims(registers):
+    # three workgroups of 4 waves per compute unit: three waves on every SIMD
+    for name, r in of(registers, "16lstm_seqg_kernel", 4).items():
+        assert 3 * r + WAITERS * 8 <= SIMD_REGISTERS, (name, r)
