@@ -30,8 +30,9 @@ def quantized(W, k):
     return oracle.quantize_rows(W, k, 2)
 
 
-# vectors of at most 1024 entries: batch 1 takes the small-batch kernel, every larger batch the fp4
-# matrix-core kernels; longer vectors: the small-batch kernel up to batch 16, the int8 kernel beyond.
+# batch 1 takes the small-batch kernel, every larger batch the fp4 matrix-core kernels where vectors have
+# at most 2048 entries and codes up to 3 bits (4-bit codes: 1024 entries); the rest: the small-batch kernel
+# up to batch 16, the int8 kernel beyond.
 # Sizes are chosen so that batch tiles, row blocks and K chunks are all ragged
 @pytest.mark.parametrize("I,H,B,k_w,k_a", [(40, 24, 3, 2, 2), (130, 33, 2, 3, 3), (300, 300, 1, 2, 2),
                                            (64, 200, 5, 2, 3), (1024, 512, 9, 3, 3), (17, 129, 4, 4, 4),
@@ -102,9 +103,9 @@ def test_gru_step_random(amq, I, H, B, k_w, k_a):
                                                  (128, 64, 48, 2, 4, 3)])
 def test_gru_sequence(amq, I, H, B, k_w, k_a, steps):
     # A whole GRU sequence in one call: every h_t and the final state must equal those of gru_step called
-    # step by step exactly (the sequence call only regroups the work: W_x x_t off the recurrent chain where
-    # the shape allows), with and without the list of hidden states, with the large and with the small
-    # workspace; and agree with the oracle's step-by-step loop.
+    # step by step exactly (the sequence call only regroups the work: one launch for all steps where the shape
+    # allows -- test_gpu_split_step.py has the shapes with two per step), with and without the list of hidden
+    # states, with the large and with the small workspace; and agree with the oracle's step-by-step loop.
     import torch
     g = np.random.default_rng(I * 7 + H + B + steps)
     Wx = (g.standard_normal((3 * H, I)) * 0.08).astype(np.float32)
@@ -435,11 +436,12 @@ def test_lstm_sequence_batched(amq, I, H, B, k_w, k_a, steps):
 @pytest.mark.parametrize("I,H,B,k_w,k_a,steps", [(300, 200, 17, 3, 3, 5), (1024, 1024, 64, 3, 3, 6), (100, 64, 20, 2, 2, 1),
                                                  (130, 1000, 33, 2, 3, 2), (1024, 516, 50, 2, 2, 7)])
 def test_lstm_sequence_split_step_is_bit_identical(amq, I, H, B, k_w, k_a, steps):
-    # With the larger workspace a batched sequence takes W_x x_t off the recurrent chain (front launch:
-    # quantize h_{t-1}, quantize x_{t+2}, x-side sums of step t + 1; back launch: h-side sums + cell).  The
-    # stored x-side sums are the very values the whole-step kernel adds, in the same order, so every h_t and
-    # the final state must equal those of the per-step path (small workspace) and of repeated lstm_step calls
-    # exactly.  Ragged tiles, units and short rows included; 1 and 2 steps cover the ends of the pipeline.
+    # With the larger workspace a batched sequence takes W_x x_t off the recurrent chain: in one launch for all
+    # steps, or on a captured stream with two per step (front launch: quantize h_{t-1}, quantize x_{t+1}, x-side
+    # sums of step t; back launch: h-side sums + cell).  The x-side sums are the very values the whole-step kernel
+    # adds, in the same order, so every h_t and the final state must equal those of the per-step path (small
+    # workspace) and of repeated lstm_step calls exactly.  Ragged tiles, units and short rows included; 1 and 2
+    # steps cover the ends of the pipeline.
     import torch
     g = np.random.default_rng(I * 11 + H + B + steps)
     Wx = (g.standard_normal((4 * H, I)) * 0.08).astype(np.float32)
@@ -459,6 +461,14 @@ def test_lstm_sequence_split_step_is_bit_identical(amq, I, H, B, k_w, k_a, steps
         hs = torch.full((steps, B, H), float("nan"), dtype=torch.float32, device=dh.device)
         amq.lstm_sequence(*d, I, H, dbias, dxs, dh, dc, k_a, 2, ws=ws, hs=hs)
         out.append((host(hs), host(dh), host(dc)))
+    ws, dh, dc = amq.lstm_sequence_workspace(I, H, B, k_a, dxs.device), to_dev(h0), to_dev(c0)
+    hs = torch.full((steps, B, H), float("nan"), dtype=torch.float32, device=dh.device)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):   # (captured: the split step)
+        amq.lstm_sequence(*d, I, H, dbias, dxs, dh, dc, k_a, 2, ws=ws, hs=hs)
+    graph.replay()
+    assert np.array_equal(host(hs), out[0][0]) and np.array_equal(host(dh), out[0][1]) and np.array_equal(host(dc), out[0][2])
     dh, dc = to_dev(h0), to_dev(c0)
     per_step = []
     for t in range(steps):
@@ -477,9 +487,9 @@ def test_lstm_sequence_split_step_is_bit_identical(amq, I, H, B, k_w, k_a, steps
 
 
 def test_split_half_hook_runs_each_launch_alone(amq):
-    # the measurement hook: either launch of the batched sequence path's step on its own.  Its results are no
+    # the measurement hook: either launch of the split step on its own.  Its results are no
     # step of a sequence; it must run on a workspace a sequence call has used, leave finite numbers, and say
-    # so where the sequence call would not take the split path (batch 1) or the half does not exist.
+    # so where there is no split step (batch 1) or the half does not exist.
     import torch
     I, H, B, k_w, k_a = 256, 128, 24, 2, 2
     g = np.random.default_rng(77)
@@ -523,7 +533,7 @@ def test_config3_lstm_1024_batch64(amq):
 
 def test_config3_sequence_call_as_benchmarked(amq):
     # The launch configuration bench.py times: all 35 steps of config 3 through one amq_lstm_sequence call
-    # with the sequence workspace (front and back launch per step).  Every h_t must equal, bit for bit, the
+    # with the sequence workspace (one launch for all steps).  Every h_t must equal, bit for bit, the
     # trajectory of amq_lstm_step calls -- which test_config3_lstm_1024_batch64 checks step by step against the
     # oracle -- and the oracle's step applied to the GPU's own h_{t-1}, c_{t-1} must agree on sampled steps.
     import torch
