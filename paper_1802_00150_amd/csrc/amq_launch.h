@@ -131,7 +131,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);
 // ---- small-batch products with weights in registers and fused epilogues --------------------
 enum { kEpiStore = 0, kEpiLstm = 1, kEpiGru = 2 };
 // Largest batch the small-batch kernel takes.  Where the fp4 matrix-core kernels apply (vectors of at
-// most 1024 entries) they are faster from batch 5 on for a plain product and from batch 2 on for a
+// most 1024 entries; recurrent steps of 1- to 3-bit codes 2048, see mfma4_pair_supported) they are faster from batch 5 on for a plain product and from batch 2 on for a
 // fused cell step (measured, 4096 x 1024 and the 1024-unit LSTM, W2/A2 and W3/A3: plain product 3.6-4.0
 // against 3.8-4.6 us at batch 4, 4.6-5.8 against 3.8-4.6 us at batch 8; LSTM step 5.2-6.6 against
 // 5.9-9.0 us at batch 1, 6.8-9.2 against 5.9-9.0 us at batch 2, 29-44 against 5.5-7.5 us at batch 16);
