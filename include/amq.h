@@ -244,13 +244,13 @@ void amq_debug_set_sequence_spin_limit(unsigned polls);
 int amq_debug_hold_sequence_shares(int shares, void* stream);
 
 /*
- * Measurement hook: one of the two launches of a steady-state step of the batched amq_lstm_sequence
- * path, on its own, so that each can be timed and profiled under its own name.  half = 0: the front
+ * Measurement hook: one of the two launches of a steady-state step of amq_lstm_sequence where it takes two
+ * per step, on its own, so that each can be timed and profiled under its own name.  half = 0: the front
  * launch (quantizes h and x_next, forms the x-side sums from the input codes the workspace holds);
  * half = 1: the back launch (h-side sums + the stored x-side sums + cell; h and c updated in place).
- * workspace: one that an amq_lstm_sequence call of the same shape has used (at least
- * amq_lstm_sequence_workspace_bytes), so that the codes and sums it reads are valid numbers.  The results
- * are not a step of any sequence.  AMQ_ERR_UNSUPPORTED where the sequence call would not take this path.
+ * workspace: at least amq_lstm_sequence_workspace_bytes, zeroed before its first use here, so that the codes
+ * and sums it reads are valid numbers.  The results are not a step of any sequence.  AMQ_ERR_UNSUPPORTED for
+ * the shapes that have no such launches.
  */
 int amq_debug_lstm_split_half(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp,
                               const float* alpha_h, int64_t I, int64_t H, int k_w, const float* bias,
@@ -277,10 +277,10 @@ int amq_gru_step(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp,
  * `steps` consecutive GRU steps (the cell of amq_gru_step) on inputs xs [steps][B][I] that are all given:
  * h [B][H] is read as the initial state and overwritten with the final one; hs (nullable)
  * [steps][B][H] receives every h_t.  Same arithmetic as `steps` calls of amq_gru_step, bit for bit.  Where
- * the shape allows (2 to 128 batch tiles of 16 on at most 2048 row-block x tile tasks, I, H <= 1024, codes
- * of at most 3 bits) and the workspace has amq_gru_sequence_workspace_bytes, the input products leave the
- * recurrent chain as in amq_lstm_sequence; otherwise, and with a workspace of only amq_gru_workspace_bytes,
- * the steps are launched one by one.
+ * the workspace has amq_gru_sequence_workspace_bytes, the same forms as in amq_lstm_sequence for B > 1: one
+ * launch for a piece of the sequence where its grid fits the chip, two launches per step where it does not
+ * (vectors of at most 2048 entries, codes of at most 3 bits, at most 2048 row-block x tile tasks); otherwise,
+ * and with a workspace of only amq_gru_workspace_bytes, the steps are launched one by one.
  *   workspace: at least amq_gru_workspace_bytes(I, H, B, k_a) bytes, 256-byte aligned.
  */
 size_t amq_gru_sequence_workspace_bytes(int64_t I, int64_t H, int64_t B, int k_a);

@@ -488,7 +488,7 @@ def test_lstm_sequence_split_step_is_bit_identical(amq, I, H, B, k_w, k_a, steps
 
 def test_split_half_hook_runs_each_launch_alone(amq):
     # the measurement hook: either launch of the split step on its own.  Its results are no
-    # step of a sequence; it must run on a workspace a sequence call has used, leave finite numbers, and say
+    # step of a sequence; it must run on a workspace that was zeroed and then used, leave finite numbers, and say
     # so where there is no split step (batch 1) or the half does not exist.
     import torch
     I, H, B, k_w, k_a = 256, 128, 24, 2, 2
@@ -498,7 +498,7 @@ def test_split_half_hook_runs_each_launch_alone(amq):
     d = [to_dev(t) for t in (Wxp, ax, Whp, ah)]
     xs = to_dev(g.standard_normal((3, B, I)).astype(np.float32))
     dh, dc = to_dev(np.zeros((B, H), np.float32)), to_dev(np.zeros((B, H), np.float32))
-    ws = amq.lstm_sequence_workspace(I, H, B, k_a, xs.device)
+    ws = amq.lstm_sequence_workspace(I, H, B, k_a, xs.device).zero_()
     amq.lstm_sequence(*d, I, H, None, xs, dh, dc, k_a, 2, ws=ws)
     L = amq.binding.lib()
     s = torch.cuda.current_stream().cuda_stream
