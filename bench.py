@@ -40,11 +40,13 @@ FP4_MFMA_PEAK_TFLOPS = 10100.0               # dense fp4 matrix cores
 GEMV_TRAFFIC_BYTES = (2 * 270918.5 + 8192.2) * 1024
 # the same for the two kernels of the primary workload (profiles/lstm_step_1024_b64_w3a3.md) and for the
 # streamed batch-1 LSTM step (profiles/lstm_step_b1_streamed_1024_w3a3.md)
-LSTM_FUSED_TRAFFIC_BYTES = (2 * 2109.4 + 512.0) * 1024
-LSTM_QUANT_TRAFFIC_BYTES = (2 * 358.0 + 53.0) * 1024
+LSTM_FUSED_TRAFFIC_BYTES = (2 * 2104.4 + 512.0) * 1024
+LSTM_QUANT_TRAFFIC_BYTES = (2 * 340.5 + 53.0) * 1024
 LSTM_B1_TRAFFIC_BYTES = (2 * 271843.8 + 1368.0) * 1024
-LSTM_FRONT_TRAFFIC_BYTES = (2 * 1309.9 + 1077.0) * 1024   # step_front_kernel, steady-state form
-LSTM_BACK_TRAFFIC_BYTES = (2 * 1721.4 + 512.0) * 1024     # step_back_kernel
+LSTM_FRONT_TRAFFIC_BYTES = (2 * 1293.4 + 1077.0) * 1024   # step_front_kernel, steady-state form
+LSTM_BACK_TRAFFIC_BYTES = (2 * 1714.4 + 512.0) * 1024     # step_back_kernel
+# a whole 35-step sequence call: the resident kernel, the quantizer of its inputs, the kernels before and after it
+LSTM_SEQUENCE_TRAFFIC_BYTES = (2 * (22936.5 + 4586.0 + 13.0 + 19.1) + 20182.0 + 927.5 + 1136.1) * 1024
 FP32_VALU_PEAK_TFLOPS = 157.3                # vector fp32
 MIN_TIMED_CALLS = 100
 MIN_WARMUP_CALLS = 10
@@ -222,17 +224,16 @@ def bench_lstm_fused_kernel(amq, cfg, dev, q, iters=300):
 
 
 def bench_lstm_split_launches(amq, cfg, dev, q, iters=300):
-    """Average duration of the two launches of a steady-state step of the batched sequence path, each alone:
-    the front launch (quantize h_{t-1} and x_{t+1}, x-side sums of step t) and the back launch (h-side sums +
-    stored x-side sums + cell).  Returns None where the sequence call does not take that path."""
+    """Average duration of the two launches of a step of a sequence that takes two per step, each alone: the front
+    launch (quantize h_{t-1} and x_{t+1}, x-side sums of step t) and the back launch (h-side sums + stored x-side
+    sums + cell).  Returns None for shapes that have none."""
     import torch
     I, H, B, k_a, T = cfg["I"], cfg["H"], cfg["B"], cfg["k_a"], cfg["T"]
     k_w = q[0].shape[0]
     xs = dv(cfg["xs"][:3], dev)
     h = torch.zeros((B, H), device=dev)
     c = torch.zeros((B, H), device=dev)
-    ws = amq.lstm_sequence_workspace(I, H, B, k_a, dev)
-    amq.lstm_sequence(*q, I, H, None, xs, h, c, k_a, T, ws=ws)   # leaves valid codes and sums in the workspace
+    ws = amq.lstm_sequence_workspace(I, H, B, k_a, dev).zero_()
     L = amq.binding.lib()
     s = torch.cuda.current_stream().cuda_stream
     ptr = [t.data_ptr() for t in q]
@@ -659,7 +660,8 @@ def main():
         out["roofline"] = {"kernel": "seqw_kernel<3,3,lstm>: 35 steps of both W3/A3 products (4096x1024 each, B=64), Alg. 2 "
                                      "on h_t and the cell, whole call with x quantized ahead",
                            "bound": "mfma", "achieved": ach, "peak": FP4_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
-                           "frac": ach / FP4_MFMA_PEAK_TFLOPS, "traffic": None, "traffic_source": None,
+                           "frac": ach / FP4_MFMA_PEAK_TFLOPS, "traffic": LSTM_SEQUENCE_TRAFFIC_BYTES,
+                           "traffic_source": "profiles/lstm_step_1024_b64_w3a3.md",
                            "launch_ms": ms_seq, "flops_per_launch": 4.0 * macs_block * S,
                            "note": "latency-bound: per step two exchanges through memory and one vector's Alg. 2"}
         out["roofline_second_kernel"] = first
