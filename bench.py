@@ -9,8 +9,8 @@ batch of synthetic input that already sits in HBM.  The primary line reports the
 LSTM (hidden 1024, W3/A3) in steps/s; `also` carries the batch-1 LSTM (hidden 300, W2/A2),
 the streamed batch-1 LSTM step and binary GEMV in GB/s (the HBM-bound kernels), the cache-resident
 GEMV latency, the GRU + projection step and the offline weight quantizer.  `roofline` describes the
-kernel of the primary workload that takes the most time, the two after it the launches of a step
-outside that kernel, `roofline_lstm_b1` and `roofline_gemv` the HBM-bound kernels (each fraction against the nominal 8 TB/s and against a read-only streaming probe
+timed sequence call of the primary workload, the two after it the launches of a step where a sequence
+takes two per step, `roofline_lstm_b1` and `roofline_gemv` the HBM-bound kernels (each fraction against the nominal 8 TB/s and against a read-only streaming probe
 measured in the same run).  `cpu_baseline` is the CPU oracle timed on a bounded sample of the primary
 workload.
 
