@@ -197,21 +197,21 @@ int amq_stream_read_probe(const void* buf, size_t bytes, void* sink, void* strea
  * sequence): xs [steps][B][I]; h and c [B][H] are read as the initial state and
  * overwritten with the final state; hs [steps][B][H] (nullable) receives every
  * h_t.  Same arithmetic as `steps` calls of amq_lstm_step.
- * For B = 1 with I, H <= 1024 and 2- or 3-bit codes the recurrence runs inside one
- * launch that occupies the whole chip (pieces of 64 steps), the workgroups exchanging
- * h_t through the workspace.  That launch needs all its workgroups resident at once:
- * do not run it concurrently with other work that keeps compute units busy.  Its waits
- * are bounded.  If one gives up, the return value is still AMQ_OK (the launches were
- * issued; the outcome is only known on the device): h and c hold the state after the
- * last 64-step piece that completed (the initial state if none did), the rows of hs
- * from the piece that gave up onwards hold NaN, and the 32-bit word
- * at byte amq_lstm_sequence_flag_offset(...) of the workspace is non-zero.  A caller
- * that needs to know reads that word after synchronising the stream (it is zero after a
+ * For B = 1 with I, H <= 2048 and 2- or 3-bit codes the recurrence runs inside one launch per
+ * piece of 64 steps (on a stream that is being captured: I, H <= 1024), the workgroups exchanging
+ * h_t through the workspace.  That launch needs all its workgroups resident at once: do not run
+ * it concurrently with other work that keeps compute units busy.  Its waits are bounded.  If one
+ * gives up, the return value is still AMQ_OK (the launches were issued; the outcome is only known
+ * on the device).  With I or H above 1024 a launch that follows then computes the piece on its
+ * own.  With I, H <= 1024 h and c hold the state after the last piece that completed (the
+ * initial state if none did), the rows of hs from the piece that gave up onwards hold NaN, and
+ * the 32-bit word at byte amq_lstm_sequence_flag_offset(...) of the workspace is non-zero.  A
+ * caller that needs to know reads that word after synchronising the stream (it is zero after a
  * completed call; SIZE_MAX: this shape has no such word).
  */
 size_t amq_lstm_sequence_flag_offset(int64_t I, int64_t H, int64_t B, int k_a);
 /*
- * Workspace of the faster forms of amq_lstm_sequence for B > 1.  Where the grid fits the chip (vectors of at most
+ * Workspace of the faster forms of amq_lstm_sequence (B = 1 needs no more than amq_lstm_workspace_bytes).  Where the grid fits the chip (vectors of at most
  * 2048 entries, 1- to 3-bit codes, about 4096 hidden units times batch tiles of 16), pieces of about 4096 / B steps
  * run in one launch whose workgroups stay resident and exchange h_t and its codes through the workspace.  Such
  * launches (and those of batch 1) share a device: on several streams they run side by side as far as their workgroups
@@ -277,10 +277,11 @@ int amq_gru_step(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp,
  * `steps` consecutive GRU steps (the cell of amq_gru_step) on inputs xs [steps][B][I] that are all given:
  * h [B][H] is read as the initial state and overwritten with the final one; hs (nullable)
  * [steps][B][H] receives every h_t.  Same arithmetic as `steps` calls of amq_gru_step, bit for bit.  Where
- * the workspace has amq_gru_sequence_workspace_bytes, the same forms as in amq_lstm_sequence for B > 1: one
- * launch for a piece of the sequence where its grid fits the chip, two launches per step where it does not
- * (vectors of at most 2048 entries, codes of at most 3 bits, at most 2048 row-block x tile tasks); otherwise,
- * and with a workspace of only amq_gru_workspace_bytes, the steps are launched one by one.
+ * the workspace has amq_gru_sequence_workspace_bytes, the same forms as in amq_lstm_sequence: one launch for
+ * a piece of the sequence where its grid fits the chip (at B = 1, should a wait give up, a launch that follows
+ * computes the piece on its own), for B > 1 two launches per step where it does not (vectors of at most 2048
+ * entries, codes of at most 3 bits, at most 2048 row-block x tile tasks); otherwise, and with a workspace of
+ * only amq_gru_workspace_bytes, the steps are launched one by one.
  *   workspace: at least amq_gru_workspace_bytes(I, H, B, k_a) bytes, 256-byte aligned.
  */
 size_t amq_gru_sequence_workspace_bytes(int64_t I, int64_t H, int64_t B, int k_a);

@@ -66,7 +66,7 @@ struct StepWs {
   float* beta_h;
   float* pre0;
   float* pre1;
-  // batch 1 only: scratch of the grid-wide sequence kernel
+  // batch 1 only: scratch of the one-launch recurrence
   unsigned* sync;
   unsigned long long* hbuf;
   uint32_t* xq;
@@ -74,6 +74,21 @@ struct StepWs {
   size_t sync_off;  // byte offset of `sync` in the workspace (SIZE_MAX when the region is absent)
   size_t total;
 };
+
+// The regions of the one-launch recurrence of batch 1; returns their size.
+size_t carve_single(char* base, int64_t I, int64_t H, int k_a, StepWs& w) {
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* p = base ? base + off : nullptr;
+    off += up256(bytes);
+    return p;
+  };
+  w.sync = reinterpret_cast<unsigned*>(take(sizeof(unsigned) * (1 + amq::kSeqGMaxGrid)));
+  w.hbuf = reinterpret_cast<unsigned long long*>(take(sizeof(unsigned long long) * 2 * (size_t)H));
+  w.xq = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * amq::kSeqGMaxSteps * (size_t)k_a * amq_wpr(I)));
+  w.xbeta = reinterpret_cast<float*>(take(sizeof(float) * amq::kSeqGMaxSteps * 4));
+  return off;
+}
 
 StepWs carve(void* ws, int64_t I, int64_t H, int64_t B, int k_a, int gates, int n_pre) {
   StepWs w;
@@ -94,10 +109,7 @@ StepWs carve(void* ws, int64_t I, int64_t H, int64_t B, int k_a, int gates, int 
   w.sync_off = SIZE_MAX;
   if (B == 1 && gates == 4) {
     w.sync_off = off;
-    w.sync = reinterpret_cast<unsigned*>(take(sizeof(unsigned) * (1 + amq::kSeqGMaxGrid)));
-    w.hbuf = reinterpret_cast<unsigned long long*>(take(sizeof(unsigned long long) * 2 * (size_t)H));
-    w.xq = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * amq::kSeqGMaxSteps * (size_t)k_a * amq_wpr(I)));
-    w.xbeta = reinterpret_cast<float*>(take(sizeof(float) * amq::kSeqGMaxSteps * 4));
+    off += carve_single(base ? base + off : nullptr, I, H, k_a, w);
   }
   w.total = off;
   return w;
@@ -140,6 +152,7 @@ struct SeqWs {
   float* xbeta[2];
   float* xsum;
   ResidentWs resident;
+  StepWs single;  // batch 1: the step's regions with those of the one-launch recurrence
   size_t total;
 };
 
@@ -160,6 +173,8 @@ SeqWs carve_seq(void* ws, int64_t I, int64_t H, int64_t B, int k_a, int gates = 
   w.xsum = reinterpret_cast<float*>(take(sizeof(float) * (size_t)B * H * 4));
   w.resident = carve_resident(base ? base + off : nullptr, I, H, B, k_a);
   w.total = off + w.resident.total;
+  w.single = w.step;
+  if (B == 1 && gates == 3) w.total += carve_single(base ? base + w.total : nullptr, I, H, k_a, w.single);
   return w;
 }
 
@@ -401,6 +416,10 @@ static amq::BmvArgs lstm_args(const uint32_t* Wxp, const float* alpha_x, const u
   return b;
 }
 
+// Batch-1 sequences whose one-launch form, should it give up, marks its results (amq_lstm_sequence_flag_offset) instead of
+// computing them again.
+static bool single_marks(int64_t I, int64_t H, int epi) { return epi == amq::kEpiLstm && I <= 1024 && H <= 1024; }
+
 // Whether a sequence takes the resident kernel: a shape it has room for, and a stream that is not being captured (its
 // launches wait for room among others of the kind and have to be queued together, which a graph does not promise).
 static bool resident_sequence(const ResidentWs& w, int64_t I, int64_t H, int64_t B, int k_w, int k_a, int epi,
@@ -429,6 +448,87 @@ static int resident_piece(const ResidentWs& w, const amq::BmvArgs& b, int64_t n,
   q.hs = hs;
   q.T = T;
   return hip_status(amq::launch_seqw(q, amq::seqw_scratch(w.scratch, b.H, b.batch, k_a), k_w, k_a, epi, s));
+}
+
+// Whether a batch-1 sequence runs in one launch per piece (amq_seq1.hip): every shape it takes, on a stream that is not being
+// captured.  (In a graph the launches that claim room are not queued together, so the kernel of light claims serves there,
+// or the per-step launches.)
+static bool single_sequence(int64_t I, int64_t H, int64_t B, int k_w, int k_a, hipStream_t s) {
+  if (!amq::seq1_supported(I, H, B, k_w, k_a) || !grid_fits_device()) return false;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+}
+
+// One piece of `n` steps given the codes of its inputs in w.  Where nothing tells the caller that a wait gave up, a launch
+// that computes the piece again follows.
+static int single_piece(const StepWs& w, const amq::BmvArgs& b, int64_t n, int k_w, int k_a, int epi, int T, float* h, float* c,
+                        float* hs, bool first, hipStream_t s) {
+  const bool marks = single_marks(b.blk[0].n, b.H, epi);
+  amq::Seq1Args q{};
+  q.Wxp = b.blk[0].Wp;
+  q.ax = b.blk[0].alpha;
+  q.Whp = b.blk[1].Wp;
+  q.ah = b.blk[1].alpha;
+  q.I = b.blk[0].n;
+  q.H = (int)b.H;
+  q.bias0 = b.bias0;
+  q.bias1 = b.bias1;
+  q.xq = w.xq;
+  q.xbeta = w.xbeta;
+  q.steps = (int)n;
+  q.h = h;
+  q.c = c;
+  q.hs = hs;
+  q.save_h = marks ? nullptr : w.pre0;
+  q.save_c = marks ? nullptr : w.pre0 + b.H;
+  q.T = T;
+  q.clear_flag = first || !marks;
+  q.sync = w.sync;
+  q.hbuf = w.hbuf;
+  int st = hip_status(amq::launch_seq1(q, k_w, k_a, epi, s));
+  if (st != AMQ_OK || marks) return st;
+  amq::SeqWArgs r{};
+  r.x = b.blk[0];
+  r.x.Xp = w.xq;
+  r.x.beta = w.xbeta;
+  r.h = b.blk[1];
+  r.rows = n;
+  r.H = (int)b.H;
+  r.batch = 1;
+  r.steps = (int)n;
+  r.bias0 = b.bias0;
+  r.bias1 = b.bias1;
+  r.h0 = h;
+  r.c0 = c;
+  r.hs = hs;
+  r.T = T;
+  r.flag = w.sync;
+  r.save_h = q.save_h;
+  r.save_c = q.save_c;
+  return hip_status(amq::launch_seq_recover(r, k_w, k_a, epi, s));
+}
+
+// A whole sequence of given inputs xs [steps][I].
+static int single_run(const amq::BmvArgs& b, const StepWs& w, const float* xs, int64_t steps, int k_w, int k_a, int epi, int T,
+                      float* h, float* c, float* hs, hipStream_t s) {
+  const int64_t I = b.blk[0].n, H = b.H;
+  for (int64_t t0 = 0; t0 < steps; t0 += amq::kSeqGMaxSteps) {
+    const int64_t n = steps - t0 < amq::kSeqGMaxSteps ? steps - t0 : amq::kSeqGMaxSteps;
+    amq::QuantArgs q{};
+    q.seg[0] = amq::QuantSeg{xs + t0 * I, I, (int)I, (int)n, w.xq, w.xbeta};
+    q.T = T;
+    q.mode = amq::kQuantFull;
+    int st = hip_status(amq::launch_quantize(q, k_a, s));
+    if (st != AMQ_OK) return st;
+    st = single_piece(w, b, n, k_w, k_a, epi, T, h, c, hs ? hs + t0 * H : nullptr, t0 == 0, s);
+    if (st != AMQ_OK) return st;
+    // (a launch that gave up, or found the flag of an earlier one, leaves its rows of hs as NaN)
+    if (hs && single_marks(I, H, epi)) {
+      st = hip_status(amq::launch_seqg_poison(w.sync, hs + t0 * H, n * H, s));
+      if (st != AMQ_OK) return st;
+    }
+  }
+  return AMQ_OK;
 }
 
 // A whole sequence of given inputs xs [steps][B][I].
@@ -616,6 +716,12 @@ int amq_lstm_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t*
   int st = check_step(Wxp, alpha_x, Whp, alpha_h, I, H, k_w, xs, h, B, k_a, T, h, workspace, workspace_bytes,
                       need);
   if (st != AMQ_OK) return st;
+  if (steps < (1 << 30) && single_sequence(I, H, B, k_w, k_a, static_cast<hipStream_t>(stream))) {
+    // batch 1: the steps of a piece (at most kSeqGMaxSteps) in one launch over the chip, weights resident in registers
+    const StepWs w = carve(workspace, I, H, B, k_a, 4, 1);
+    return single_run(lstm_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias, nullptr, nullptr, nullptr, nullptr, c, B, h, c, nullptr),
+                      w, xs, steps, k_w, k_a, amq::kEpiLstm, T, h, c, hs, static_cast<hipStream_t>(stream));
+  }
   if (steps < (1 << 30) && amq::lstm_seqg_supported(I, H, B, k_w, k_a) && grid_fits_device()) {
     // batch 1: the whole sequence (in pieces of at most kSeqGMaxSteps steps) in one launch over the
     // chip, weights resident in registers
@@ -792,6 +898,8 @@ int amq_gru_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t* 
   const SeqWs sw = carve_seq(workspace, I, H, B, k_a, 3, 2);
   const amq::BmvArgs probe = gru_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, sw.xq[0], sw.xbeta[0], w.hp,
                                       w.beta_h, h, B, h);
+  if (workspace_bytes >= sw.total && single_sequence(I, H, B, k_w, k_a, s))
+    return single_run(probe, sw.single, xs, steps, k_w, k_a, amq::kEpiGru, T, h, nullptr, hs, s);
   if (workspace_bytes >= sw.total && resident_sequence(sw.resident, I, H, B, k_w, k_a, amq::kEpiGru, s))
     return resident_run(sw.resident, probe, xs, steps, k_w, k_a, amq::kEpiGru, T, h, nullptr, hs, s);
   if (workspace_bytes >= sw.total && amq::step_split_supported(probe, k_w, k_a, amq::kEpiGru)) {
@@ -1324,7 +1432,8 @@ static int lm_sequence_impl(const uint32_t* Ep, const float* alpha_e, int64_t vo
     return score_layer_launch(Wsp, alpha_s, V, H, k_ws, bias_s, lw.hs, rows, k_as, T, o.targets + row0,
                               o.target_logprob + row0, soft_base, o, s);
   };
-  if (B == 1 && amq::lstm_seqg_supported(E, H, B, k_w, k_a) && grid_fits_device()) {
+  const bool single = single_sequence(E, H, B, k_w, k_a, s);
+  if (single || (B == 1 && amq::lstm_seqg_supported(E, H, B, k_w, k_a) && grid_fits_device())) {
     // batch 1: per piece of at most kSeqGMaxSteps steps, look all inputs up (the table the sequence
     // kernel reads its input codes from), run the recurrence in one launch over the chip, then the
     // output layer
@@ -1338,10 +1447,14 @@ static int lm_sequence_impl(const uint32_t* Ep, const float* alpha_e, int64_t vo
       if (st != AMQ_OK) return st;
       amq::SeqGArgs g{Wxp, alpha_x, Whp, alpha_h, (int)E, (int)H, bias, nullptr, n, h, c, lw.hs, T, 0, w.sync, w.hbuf,
                       w.xq, w.xbeta, t0 == 0};
-      st = hip_status(amq::launch_lstm_seqg(g, k_w, k_a, s));
+      st = single ? single_piece(w, lstm_args(Wxp, alpha_x, Whp, alpha_h, E, H, bias, nullptr, nullptr, nullptr, nullptr, c, B, h,
+                                              c, nullptr),
+                                 n, k_w, k_a, amq::kEpiLstm, T, h, c, lw.hs, t0 == 0, s)
+                  : hip_status(amq::launch_lstm_seqg(g, k_w, k_a, s));
       if (st != AMQ_OK) return st;
       st = output_layer(t0, n);
       if (st != AMQ_OK) return st;
+      if (single && !single_marks(E, H, amq::kEpiLstm)) continue;
       // the output layer has just read hidden states that are incomplete if the recurrence gave up (now
       // or in an earlier piece of this call): its results for these steps become NaN
       st = hip_status(o.logprob ? amq::launch_seqg_poison(w.sync, o.logprob + t0 * V, (long long)n * V, s)

@@ -265,6 +265,21 @@ struct SeqGArgs {
   ResidentClaim claim;  // filled by launch_lstm_seqg
   unsigned spin_limit;  // filled by launch_lstm_seqg: polls of a wait before it gives up
 };
+// Words of sync after the arrival bytes: workgroups that have left, and whether room was claimed for this launch.
+constexpr int kSeqGLeft = 1 + kSeqGMaxGrid / 4;
+constexpr int kSeqGClaimed = kSeqGLeft + 1;
+// One thread of a workgroup that is about to leave: the last one gives the room back.
+__device__ __forceinline__ void seqg_leave(unsigned* sync, const ResidentClaim& claim) {
+  if (sync[kSeqGClaimed] == 0u) return;
+  if (__hip_atomic_fetch_add(sync + kSeqGLeft, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1)
+    give_resident_share(claim);
+}
+// Before a launch of this kind (under resident_launches()): claims its room, clears the tags and, if asked, the flag, and
+// publishes the initial state h as that of tag 0 in the second of the two buffers.
+hipError_t launch_seqg_reset(unsigned* sync, unsigned long long* hbuf, const float* h, int H, int clear_flag, const ResidentClaim& claim,
+                             hipStream_t s);
+// Should the launch itself fail: gives the room back.
+void launch_seqg_abandon(const unsigned* sync, const ResidentClaim& claim, hipStream_t s);
 bool lstm_seqg_supported(long long I, long long H, long long B, int k_w, int k_a);
 hipError_t launch_lstm_seqg(SeqGArgs a, int k_w, int k_a, hipStream_t s);
 // Polls before a wait of the sequence kernel gives up (0 restores the default).  Tests of the failure
@@ -273,6 +288,35 @@ void set_seqg_spin_limit(unsigned polls);
 // After a launch of the sequence kernel and whatever consumed its hs: if the give-up flag is set,
 // overwrite out[0 .. count) with NaN (results computed from an incomplete recurrence must not look valid).
 hipError_t launch_seqg_poison(const unsigned* sync, float* out, long long count, hipStream_t s);
+
+// ---- the same for LSTM and GRU and vectors of up to 2048 entries, given the codes of all inputs (amq_seq1.hip) ------
+struct Seq1Args {
+  const uint32_t* Wxp;  // [k_w][gates * H][wpr(I)]
+  const float* ax;      // [gates * H][k_w]
+  const uint32_t* Whp;
+  const float* ah;
+  int I, H;
+  const float* bias0;   // LSTM: [4H]; GRU: bias_x [3H] (nullable)
+  const float* bias1;   // GRU: bias_h [3H] (nullable)
+  const uint32_t* xq;   // [k_a][steps][wpr(I)]
+  const float* xbeta;   // [steps][k_a]
+  int steps;            // at most kSeqGMaxSteps
+  float* h;             // [H] in: h_0, out: h_steps
+  float* c;             // LSTM: the same
+  float* hs;            // [steps][H] or null
+  float* save_h;        // [H], [H] or null: the initial state, for whoever computes the piece again
+  float* save_c;
+  int T;
+  int clear_flag;       // non-zero: an earlier launch's give-up is forgotten
+  unsigned* sync;       // as in SeqGArgs
+  unsigned long long* hbuf;
+  // filled by launch_seq1
+  int lg;
+  unsigned limit;
+  ResidentClaim claim;
+};
+bool seq1_supported(long long I, long long H, long long B, int k_w, int k_a);
+hipError_t launch_seq1(Seq1Args a, int k_w, int k_a, int epi, hipStream_t s);
 
 // Polls a wait of the resident sequence kernels may take (see set_seqg_spin_limit).
 unsigned sequence_spin_limit();
@@ -306,6 +350,10 @@ struct SeqWScratch {
 SeqWScratch seqw_scratch(void* base, long long H, long long B, int k_a);
 bool seqw_supported(long long I, long long H, long long B, int k_w, int k_a, int epi);
 hipError_t launch_seqw(SeqWArgs a, const SeqWScratch& w, int k_w, int k_a, int epi, hipStream_t s);
+
+// What follows such a launch, on its own (flag, saved state and input codes in a): if the flag is set, the piece is
+// computed again from the saved state (batch 1: and the flag cleared).
+hipError_t launch_seq_recover(const SeqWArgs& a, int k_w, int k_a, int epi, hipStream_t s);
 
 // ---- the recurrent step of a sequence with given inputs, cut along the operand blocks ----------
 // Front launch: quantizes the vectors of q (seg[0] = h_{t-1}, seg[1] = a later x, count 0 for none) and of

@@ -1,5 +1,6 @@
 // Whole batch-1 LSTM sequences in one launch, spread over the chip: the recurrence of Eq. 6 with
-// every workgroup keeping its slice of both weight blocks in registers for all time steps.
+// every workgroup keeping its slice of both weight blocks in registers for all time steps.  On a stream that is being
+// captured; elsewhere seq1_kernel (amq_seq1_body.h), which needs more registers and so a full claim of room.
 //
 // At batch 1 a step moves a few hundred KB to 3 MB of packed weights and a few KB of state; run
 // as two launches per step it is bound by launch gaps and by the cold misses every new kernel
@@ -188,28 +189,27 @@ __device__ __forceinline__ bool quantize_wg(const void* src_v, unsigned tag, uns
 // Before a launch: clears the arrival bytes and the tags of the published state; the give-up flag only
 // for the first launch of an API call.
 // Claims room for the launch (amq_resident.h; without it the launch goes ahead all the same, as its waits are bounded).
-constexpr int kLeft = 1 + kSeqGMaxGrid / 4;  // words of sync after the arrival bytes: workgroups that have left,
-constexpr int kClaimed = kLeft + 1;          // and whether room was claimed for this launch
-__global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, int H, int clear_flag, ResidentClaim claim) {
+__global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, const float* h, int H, int clear_flag,
+                                  ResidentClaim claim) {
   const unsigned t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
   if (t == 0) {
     if (clear_flag) sync[0] = 0u;
-    sync[kLeft] = 0u;
-    sync[kClaimed] = take_resident_share(claim) ? 1u : 0u;
+    sync[kSeqGLeft] = 0u;
+    sync[kSeqGClaimed] = take_resident_share(claim) ? 1u : 0u;
   }
   for (unsigned i = 1 + t; i < 1 + kSeqGMaxGrid / 4; i += nt) sync[i] = 0u;
-  for (unsigned i = t; i < 2 * (unsigned)H; i += nt) hbuf[i] = 0ull;
-}
-
-// One thread of a workgroup that is about to leave: the last one gives the room back.
-__device__ __forceinline__ void leave(unsigned* sync, const ResidentClaim& claim) {
-  if (sync[kClaimed] == 0u) return;
-  if (__hip_atomic_fetch_add(sync + kLeft, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) give_resident_share(claim);
+  const unsigned units = (unsigned)H;
+  for (unsigned i = t; i < 2 * units; i += nt) {
+    // (32-bit offsets: a wave that waits here should hold few registers)
+    unsigned v = 0u;
+    if (i >= units) v = *reinterpret_cast<const unsigned*>(reinterpret_cast<const char*>(h) + (i - units) * 4u);
+    *reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(hbuf) + i * 8u) = v;
+  }
 }
 
 // Should the launch itself fail: nobody is there to leave.
 __global__ void seqg_abandon_kernel(const unsigned* sync, ResidentClaim claim) {
-  if (sync[kClaimed] != 0u) give_resident_share(claim);
+  if (sync[kSeqGClaimed] != 0u) give_resident_share(claim);
 }
 
 __global__ void seqg_poison_kernel(const unsigned* sync, float* out, long long count) {
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(64 * kGWaves, 2) void lstm_seqg_kernel(SeqGArgs a) 
   if (threadIdx.x == 0) gave_up = get_u(a.sync);
   __syncthreads();
   if (gave_up != 0u) {
-    if (threadIdx.x == 0) leave(a.sync, a.claim);
+    if (threadIdx.x == 0) seqg_leave(a.sync, a.claim);
     return;
   }
   const unsigned limit = a.spin_limit;
@@ -302,9 +302,9 @@ __global__ __launch_bounds__(64 * kGWaves, 2) void lstm_seqg_kernel(SeqGArgs a) 
   for (int t = 0; t < a.steps && alive; ++t) {
     if (tid < KA * wprI) xq[tid] = xnext;
     if (tid < KA) bx[tid] = bxnext;
-    // h_{t-1}: the caller's state at the first step, afterwards what the grid published (tag t)
-    if (t == 0) alive = quantize_wg<KA, false>(a.h, 0, a.sync, limit, H, a.T, hq, bh, sh, phase);
-    else alive = quantize_wg<KA, true>(a.hbuf + ((t - 1) & 1) * H, (unsigned)t, a.sync, limit, H, a.T, hq, bh, sh, phase);
+    // h_{t-1} as the grid published it, tag t (the initial state, tag 0, by the reset kernel: the caller's h may already
+    // be the result of a workgroup that is through, if there is one step)
+    alive = quantize_wg<KA, true>(a.hbuf + ((t + 1) & 1) * H, (unsigned)t, a.sync, limit, H, a.T, hq, bh, sh, phase);
     if (!alive) break;
     __syncthreads();
 
@@ -361,20 +361,17 @@ __global__ __launch_bounds__(64 * kGWaves, 2) void lstm_seqg_kernel(SeqGArgs a) 
     a.h[unit] = hlast;
     a.c[unit] = cst;
   }
-  if (tid == 0) leave(a.sync, a.claim);
+  if (tid == 0) seqg_leave(a.sync, a.claim);
 }
 
 template <int KW, int KA>
 hipError_t launch_kk(const SeqGArgs& a, int grid, hipStream_t s) {
   std::lock_guard<std::mutex> together(resident_launches());
-  hipLaunchKernelGGL(seqg_reset_kernel, dim3(8), dim3(256), 0, s, a.sync, a.hbuf, a.H, a.first_piece, a.claim);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_seqg_reset(a.sync, a.hbuf, a.h, a.H, a.first_piece, a.claim, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((lstm_seqg_kernel<KW, KA>), dim3(grid), dim3(64 * kGWaves), 0, s, a);
   e = hipGetLastError();
-  if (e == hipSuccess) return e;
-  hipLaunchKernelGGL(seqg_abandon_kernel, dim3(1), dim3(1), 0, s, a.sync, a.claim);
-  (void)hipGetLastError();
+  if (e != hipSuccess) launch_seqg_abandon(a.sync, a.claim, s);
   return e;
 }
 
@@ -395,6 +392,17 @@ bool lstm_seqg_supported(long long I, long long H, long long B, int k_w, int k_a
   const int lg = seqg_lg((int)I, (int)H);
   const int units_per_wg = kGWaves * (8 >> lg);
   return (H + units_per_wg - 1) / units_per_wg <= kSeqGMaxGrid;
+}
+
+hipError_t launch_seqg_reset(unsigned* sync, unsigned long long* hbuf, const float* h, int H, int clear_flag,
+                             const ResidentClaim& claim, hipStream_t s) {
+  hipLaunchKernelGGL(seqg_reset_kernel, dim3(8), dim3(256), 0, s, sync, hbuf, h, H, clear_flag, claim);
+  return hipGetLastError();
+}
+
+void launch_seqg_abandon(const unsigned* sync, const ResidentClaim& claim, hipStream_t s) {
+  hipLaunchKernelGGL(seqg_abandon_kernel, dim3(1), dim3(1), 0, s, sync, claim);
+  (void)hipGetLastError();
 }
 
 unsigned sequence_spin_limit() { return g_spin_limit.load(); }

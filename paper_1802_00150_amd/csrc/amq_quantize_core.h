@@ -793,7 +793,8 @@ __device__ __forceinline__ int code_table_kind(const float (&alpha)[K], CodeTabl
   return 2;
 }
 
-template <int K, int NJ, int NW, bool FULL>
+// WHOLE: slots below it lie inside the vector in every wave that takes this form.
+template <int K, int NJ, int NW, int WHOLE>
 __device__ __forceinline__ void quantize_online(const float (&x)[NJ], int n, int base, int nj, int T, float (&alpha)[K],
                                                 unsigned long long (&mym)[K], double* sh, int& phase,
                                                 unsigned long long* marks) {
@@ -805,8 +806,14 @@ __device__ __forceinline__ void quantize_online(const float (&x)[NJ], int n, int
   const double dn = (double)n;
   const double inv_n = recip_f64(dn);
   auto mean = [&](double s) { return (float)(s * inv_n); };
-  auto inside = [&](int j) { return FULL ? ~0ull : (j < nj ? lanes_inside(n, base + j) : 0ull); };
+  constexpr bool FULL = WHOLE == NJ;
   const unsigned long long lane_inside = FULL ? ~0ull : lanes_inside(n, base + lane_id());
+  // all bits set where this lane has an entry in slot j: one bit operation per use in the chain (a comparison with the
+  // index, or a mask formed by the scalar unit and a select, take several)
+  const int within = min(n - base * 64, nj * 64) - lane_id();
+  int in[NJ];
+#pragma unroll
+  for (int j = WHOLE; j < NJ; ++j) in[j] = (j * 64 - within) >> 31;
   const int outside = NW * NJ * 64 - n;  // entries past the end that the workgroup's slots hold
   const double field[3] = {1.0, 0x1p15, 0x1p30};
   int no_counts[1] = {0};
@@ -821,7 +828,7 @@ __device__ __forceinline__ void quantize_online(const float (&x)[NJ], int n, int
     xc[j] = x[j] + 0.0f;
     const unsigned b = __float_as_uint(xc[j]);
     u[j] = (int)min(b, b + 0x7fffffffu);
-    if (!FULL) u[j] = lane_bit(inside(j)) ? u[j] : -1;
+    if (j >= WHOLE) u[j] |= ~in[j];
     wd[j] = fabs((double)xc[j]);
     r[j] = xc[j];
     sum[0] = (j == 0) ? wd[j] : sum[0] + wd[j];
@@ -857,7 +864,7 @@ __device__ __forceinline__ void quantize_online(const float (&x)[NJ], int n, int
       for (int j = 0; j < NJ; ++j) {
         const float before = r[j];
         float rn = before - copysignf(a, before);
-        if (!FULL) rn = lane_bit(inside(j)) ? rn : 0.0f;
+        if (j >= WHOLE) rn = __int_as_float(__float_as_int(rn) & in[j]);
         r[j] = rn;
         double m;  // plane i agrees with the sign of w
         if (i == 1) {
@@ -1093,8 +1100,10 @@ __device__ __forceinline__ void quantize_core(const float (&x)[NJ], int n, int b
   base = __builtin_amdgcn_readfirstlane(base);
   const bool full = nj == NJ && (base + NJ) * 64 <= n;
   if constexpr (ONLINE) {
-    if (full) quantize_online<K, NJ, NW, true>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
-    else quantize_online<K, NJ, NW, false>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+    if (full) quantize_online<K, NJ, NW, NJ>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+    else if (NW == 1 && nj == NJ && (NJ - 1) * 64 <= n)
+      quantize_online<K, NJ, NW, NW == 1 ? NJ - 1 : 0>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+    else quantize_online<K, NJ, NW, 0>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
   } else if (full) {
     quantize_magnitudes<K, NJ, NW, NJ>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
   } else {

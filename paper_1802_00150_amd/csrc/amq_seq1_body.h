@@ -1,0 +1,344 @@
+// Whole recurrent sequences of one batch entry in one launch, spread over the chip (Eq. 6 over a sequence): LSTM and GRU,
+// vectors of up to 2048 entries.
+//
+// A step at batch 1 is a chain of latencies: h_{t-1} becomes visible to whoever needs it, is quantized (Alg. 2: three or
+// four dependent sums over the whole vector), multiplied, and passed through the cell.  The weights stay in registers for
+// the whole sequence and every reader quantizes h_{t-1} itself, so that one exchange per step is all there is:
+//   - lane = (hidden unit, gate, 16-byte chunk of the row), a hidden unit takes 4 * Gl lanes (Gl = chunks per row rounded
+//     up to a power of two, at most 16), a lane holds the KW plane chunks of both operand blocks of U units;
+//   - h_t is published as 8-byte {value, step tag} pairs, each written with one 64-bit device-scope store; readers poll the
+//     pairs they need until all carry the tag of the step, so the data is its own arrival signal.  Two buffers in turn
+//     suffice: a buffer is written again by waves that have seen every pair of the step between;
+//   - the codes of all inputs are formed (or looked up) before this launch, and the x-side sums of step t + 1 are formed
+//     after h_t has been published, while it is under way.
+// QW = 1: every wave is on its own -- it polls and quantizes the whole vector (up to 8 slots of 64 entries per lane) and
+// multiplies its own rows, with no barrier anywhere in a step.  QW = 4: the four waves of a workgroup quantize together.
+// One wave takes longer over the entries and needs no exchange between waves (about 250 cycles less per sum).
+//
+// Bound: latency -- at 300 units about 1.0 us until h_t is seen, 0.9 for Alg. 2, the rest products, cell and LDS.  Measured, us
+// per step in sequences of 35, form before -> here, W2/A2: LSTM 300 units 3.50 -> 2.60, 650 4.31 -> 3.08, 1024 5.04 -> 3.53
+// (lstm_seqg_kernel), 2048 8.69 -> 4.06; GRU 300 8.06 -> 2.66, 1024 8.09 -> 3.46, 2048 8.50 -> 4.17 (two launches per step);
+// W3/A3: LSTM 300 4.22 -> 3.29, 1024 5.79 -> 4.53, 2048 11.0 -> 5.59, GRU 9.23 -> 3.50, 9.61 -> 4.36, 10.3 -> 5.63.
+//
+// The order of additions is that of the per-step kernels (amq_bmv_body.h); JOINT false: that of lstm_seqg_kernel, which
+// sums the two operand blocks of a row apart.
+//
+// Every wait is bounded.  If one gives up a flag is raised and everybody leaves; the caller of this launch follows it with
+// one that either computes the piece again from the saved state or marks what was derived from it (launch_seqg_poison).
+#pragma once
+#include "amq_launch.h"
+#include "amq_quantize_body.h"
+
+namespace amq {
+
+namespace seq1 {
+
+constexpr int k1Waves = 4;
+
+template <int KW, int KA, int EPI, int QW, int NJ, int U, bool JOINT>
+__global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
+  constexpr int NG = EPI == kEpiGru ? 3 : 4;
+  constexpr int kChunks = 16;
+  __shared__ double sh[2 * kExchange<QW>];
+  __shared__ __attribute__((aligned(16))) uint4 hq[QW == 1 ? k1Waves : 2][KA][kChunks];  // codes of h_{t-1}
+  __shared__ float hb[2][KA];                                                           // and coefficients (QW = 4)
+  __shared__ int dead;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int I = a.I, H = a.H, lg = a.lg, Gl = 1 << lg;
+  const int cprI = (I + 127) >> 7, cprH = (H + 127) >> 7;
+  const int c = lane & (Gl - 1), gate = (lane >> lg) & 3, uo = lane >> (lg + 2);
+  const int per = 16 >> lg;  // units of a wave side by side
+  const int unit0 = (blockIdx.x * k1Waves + wv) * U * per + uo;
+  if (tid == 0) dead = 0;
+
+  // an earlier launch of the same call gave up
+  __shared__ unsigned gave_up;
+  if (tid == 0) gave_up = __hip_atomic_load(a.sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (gave_up != 0u) {
+    if (tid == 0) seqg_leave(a.sync, a.claim);
+    return;
+  }
+
+  // ---- once: this lane's plane chunks and coefficients of both blocks
+  uint4 wq[2][U][KW];
+  float al[2][U][KW];
+  const int g = gate < NG ? gate : NG - 1;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const uint4* Wp4 = reinterpret_cast<const uint4*>(k ? a.Whp : a.Wxp);
+    const float* alpha = k ? a.ah : a.ax;
+    const int cpr = k ? cprH : cprI;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int unit = unit0 + u * per;
+      const bool ok = unit < H && c < cpr && gate < NG;
+      const int row = g * H + (unit < H ? unit : 0);
+#pragma unroll
+      for (int i = 0; i < KW; ++i) {
+        const uint4 t = Wp4[((long long)i * NG * H + row) * cpr + (c < cpr ? c : 0)];
+        wq[k][u][i] = ok ? t : make_uint4(0, 0, 0, 0);
+        al[k][u][i] = alpha[row * KW + i];
+      }
+    }
+  }
+  float bits[2][U];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int n = k ? H : I, left = n - 128 * c;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      bits[k][u] = unit0 + u * per < H && gate < NG && left > 0 ? (float)(left > 128 ? 128 : left) : 0.0f;
+  }
+  // the cell of slot u is applied by the lane of gate u (chunk 0) of its units
+  const int mine = U == 1 ? 0 : gate & (U - 1);
+  const int unit = unit0 + mine * per;
+  const bool cell = c == 0 && gate < U && unit < H;
+  float b0[NG], b1[NG], cst = 0.0f, hlast = 0.0f;
+#pragma unroll
+  for (int r = 0; r < NG; ++r) {
+    b0[r] = (cell && a.bias0) ? a.bias0[r * H + unit] : 0.0f;
+    b1[r] = (EPI == kEpiGru && cell && a.bias1) ? a.bias1[r * H + unit] : 0.0f;
+  }
+  if (cell) {
+    hlast = a.h[unit];
+    if (EPI == kEpiLstm) cst = a.c[unit];
+    if (a.save_h) {
+      a.save_h[unit] = hlast;
+      if (EPI == kEpiLstm) a.save_c[unit] = cst;
+    }
+  }
+
+  const int nslots = (H + 63) >> 6;
+  const int nj = (nslots + QW - 1) / QW, base = QW == 1 ? 0 : wv * nj;
+  int phase = 0;
+  const unsigned limit = a.limit;
+
+  // codes of x_t: this lane's chunk and the coefficients, requested a step ahead
+  uint4 xv[KA];
+  float xb[KA];
+  auto request_x = [&](int t) {
+    const uint4* Xp4 = reinterpret_cast<const uint4*>(a.xq);
+    const int cc = c < cprI ? c : 0;
+#pragma unroll
+    for (int j = 0; j < KA; ++j) {
+      xv[j] = Xp4[((long long)j * a.steps + t) * cprI + cc];
+      xb[j] = a.xbeta[t * KA + j];
+    }
+  };
+  auto dots = [&](int k, int u, const uint4 (&v)[KA], const float (&bt)[KA]) {
+    float acc = 0.0f;
+#pragma unroll
+    for (int i = 0; i < KW; ++i) {
+      float inner = 0.0f;
+#pragma unroll
+      for (int j = 0; j < KA; ++j) inner = fmaf(bt[j], bits[k][u] - 2.0f * (float)popc4(wq[k][u][i], v[j]), inner);
+      acc = fmaf(al[k][u][i], inner, acc);
+    }
+    return acc;
+  };
+  float px[U];  // x-side sums of the step to come: per lane, or (JOINT false) already over the row
+  auto x_side = [&]() {
+    if (c >= cprI) {
+#pragma unroll
+      for (int j = 0; j < KA; ++j) xv[j] = make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      px[u] = dots(0, u, xv, xb);
+      if constexpr (!JOINT) px[u] = group_sum(px[u], lg);
+    }
+  };
+  request_x(0);
+  x_side();
+  if (a.steps > 1) request_x(1);
+
+  // (a wave on its own that owns no unit publishes nothing, so nobody would wait for it to have read a buffer)
+  const int steps = QW == 1 && (int)(blockIdx.x * k1Waves + wv) * U * per >= H ? 0 : a.steps;
+  bool alive = true;
+  for (int t = 0; t < steps; ++t) {
+    // ---- h_{t-1}, published with tag t (the initial state with tag 0, by the launch before)
+    float alpha[KA];
+    unsigned long long mym[KA];
+    float w[NJ];
+    {
+      const unsigned long long* src = a.hbuf + ((t + 1) & 1) * H;
+      unsigned long long p[NJ];
+      unsigned spins = 0;
+      for (;;) {
+        bool ready = true;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int e = (base + j) * 64 + lane;
+          p[j] = __hip_atomic_load(src + (e < H ? e : H - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) ready = ready && (unsigned)(p[j] >> 32) == (unsigned)t;
+        if (__all(ready)) break;
+        ++spins;
+        if (spins >= limit) {
+          __hip_atomic_store(a.sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          alive = false;
+          break;
+        }
+        if ((spins & 63u) == 0 && __hip_atomic_load(a.sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+          alive = false;
+          break;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        w[j] = j < nj && (base + j) * 64 + lane < H ? __uint_as_float((unsigned)(p[j] & 0xffffffffull)) : 0.0f;
+    }
+    if (QW == 1 && !alive) break;
+    quantize_core<KA, NJ, QW, true>(w, H, base, nj, a.T, alpha, mym, sh, phase);
+
+    // ---- codes and coefficients to the lanes that multiply
+    uint4* const codes = hq[QW == 1 ? wv : t & 1][0];
+    if (lane < (base + nj >= nslots ? 2 * cprH - base : nj)) {
+#pragma unroll
+      for (int j = 0; j < KA; ++j)
+        reinterpret_cast<unsigned long long*>(codes + j * kChunks)[base + lane] = mym[j];
+    }
+    float bt[KA];
+    if constexpr (QW == 1) {
+      // (LDS serves the accesses of a wave in order)
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int j = 0; j < KA; ++j) bt[j] = alpha[j];
+    } else {
+      if (tid == 0) {
+#pragma unroll
+        for (int j = 0; j < KA; ++j) hb[t & 1][j] = alpha[j];
+      }
+      if (!alive) dead = 1;
+      lds_barrier();
+      if (__builtin_amdgcn_readfirstlane(dead) != 0) {
+        alive = false;
+        break;
+      }
+#pragma unroll
+      for (int j = 0; j < KA; ++j) bt[j] = hb[t & 1][j];
+    }
+    uint4 hv[KA];
+#pragma unroll
+    for (int j = 0; j < KA; ++j) {
+      const uint4 v = codes[j * kChunks + (c < cprH ? c : 0)];
+      hv[j] = c < cprH ? v : make_uint4(0, 0, 0, 0);
+    }
+
+    // ---- the sums of the gates, summed over the chunks of a row: y of the gate this lane belongs to (GRU candidate: its
+    // h side in yh, its x side in y)
+    float y[U], yh[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float ph = dots(1, u, hv, bt);
+      if constexpr (EPI == kEpiGru) {
+        y[u] = group_sum(gate == 2 ? px[u] : px[u] + ph, lg);
+        yh[u] = group_sum(ph, lg);
+      } else if constexpr (JOINT) {
+        y[u] = group_sum(px[u] + ph, lg);
+      } else {
+        y[u] = px[u] + group_sum(ph, lg);
+      }
+    }
+    const int first = lane & ~(4 * Gl - 1);
+    auto of_gate = [&](const float (&v)[U], int r) {
+      float s = __shfl(v[0], first + r * Gl, kWave);
+#pragma unroll
+      for (int u = 1; u < U; ++u) {
+        const float o = __shfl(v[u], first + r * Gl, kWave);
+        s = mine == u ? o : s;
+      }
+      return s;
+    };
+    if constexpr (EPI == kEpiLstm) {
+      const float gi = sigmoidf_dev(of_gate(y, 0) + b0[0]);
+      const float gf = sigmoidf_dev(of_gate(y, 1) + b0[1]);
+      const float go = sigmoidf_dev(of_gate(y, 2) + b0[2]);
+      const float gg = tanhf_dev(of_gate(y, 3) + b0[3]);
+      cst = fmaf(gf, cst, gi * gg);
+      hlast = go * tanhf_dev(cst);
+    } else {
+      const float r = sigmoidf_dev(of_gate(y, 0) + b0[0] + b1[0]);
+      const float z = sigmoidf_dev(of_gate(y, 1) + b0[1] + b1[1]);
+      const float nn = tanhf_dev(fmaf(r, of_gate(yh, 2) + b1[2], of_gate(y, 2) + b0[2]));
+      hlast = fmaf(z, hlast - nn, nn);
+    }
+    if (cell) {
+      if (t + 1 < a.steps)
+        __hip_atomic_store(a.hbuf + (t & 1) * H + unit,
+                           ((unsigned long long)(unsigned)(t + 1) << 32) | __float_as_uint(hlast), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      if (a.hs) a.hs[(long long)t * H + unit] = hlast;
+    }
+    // ---- while h_t is under way
+    if (t + 1 < a.steps) {
+      x_side();
+      if (t + 2 < a.steps) request_x(t + 2);
+    }
+  }
+
+  if (alive && cell) {
+    a.h[unit] = hlast;
+    if (EPI == kEpiLstm) a.c[unit] = cst;
+  }
+  __syncthreads();
+  if (tid == 0) seqg_leave(a.sync, a.claim);
+}
+
+template <int KW, int KA, int EPI, int QW, int NJ, int U, bool JOINT>
+hipError_t run_form(const Seq1Args& a, hipStream_t s) {
+  const int units = k1Waves * U * (16 >> a.lg);
+  const int grid = (a.H + units - 1) / units;
+  if (grid > kSeqGMaxGrid) return hipErrorInvalidValue;
+  Seq1Args q = a;
+  q.claim = resident_claim(grid, false);
+  std::lock_guard<std::mutex> together(resident_launches());
+  hipError_t e = launch_seqg_reset(q.sync, q.hbuf, q.h, q.H, q.clear_flag, q.claim, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((seq1_kernel<KW, KA, EPI, QW, NJ, U, JOINT>), dim3((unsigned)grid), dim3(64 * k1Waves), 0, s, q);
+  e = hipGetLastError();
+  if (e != hipSuccess) launch_seqg_abandon(q.sync, q.claim, s);
+  return e;
+}
+
+// How many slots of 64 entries a lane of the quantizing waves holds: as many as H needs, so that no slot is computed for
+// nothing.  Up to 512 units a wave is on its own, beyond four share the work: at 512 units one wave takes 2.88 (W2/A2) and
+// 3.68 us (W3/A3) per step against 2.97 and 4.24 for four, and at 640 its chain is the longer one.  Vectors above 1024
+// entries take 16 lanes per row and gate and two units per lane, so that 2048 units are 256 workgroups; there four waves
+// always share the work (fewer forms; 300 units with inputs of 1500: 2.97 against 2.81 us).
+template <int KW, int KA, int EPI>
+hipError_t run_cell(const Seq1Args& a, hipStream_t s) {
+  constexpr bool kApart = EPI == kEpiLstm;  // (short vectors: the order of lstm_seqg_kernel)
+  if (a.lg == 4) {
+    switch ((a.H + 255) / 256) {
+      case 1: case 2: return run_form<KW, KA, EPI, 4, 2, 2, true>(a, s);
+      case 3: case 4: return run_form<KW, KA, EPI, 4, 4, 2, true>(a, s);
+      case 5: return run_form<KW, KA, EPI, 4, 5, 2, true>(a, s);
+      case 6: return run_form<KW, KA, EPI, 4, 6, 2, true>(a, s);
+      case 7: return run_form<KW, KA, EPI, 4, 7, 2, true>(a, s);
+    }
+    return run_form<KW, KA, EPI, 4, 8, 2, true>(a, s);
+  }
+  switch ((a.H + 63) / 64) {
+    case 1: case 2: case 3: case 4: return run_form<KW, KA, EPI, 1, 4, 1, !kApart>(a, s);
+    case 5: return run_form<KW, KA, EPI, 1, 5, 1, !kApart>(a, s);
+    case 6: return run_form<KW, KA, EPI, 1, 6, 1, !kApart>(a, s);
+    case 7: return run_form<KW, KA, EPI, 1, 7, 1, !kApart>(a, s);
+    case 8: return run_form<KW, KA, EPI, 1, 8, 1, !kApart>(a, s);
+  }
+  return a.H <= 768 ? run_form<KW, KA, EPI, 4, 3, 1, !kApart>(a, s) : run_form<KW, KA, EPI, 4, 4, 1, !kApart>(a, s);
+}
+
+template <int KW>
+hipError_t run_weights(const Seq1Args& a, int k_a, int epi, hipStream_t s) {
+  if (k_a == 2) return epi == kEpiGru ? run_cell<KW, 2, kEpiGru>(a, s) : run_cell<KW, 2, kEpiLstm>(a, s);
+  return epi == kEpiGru ? run_cell<KW, 3, kEpiGru>(a, s) : run_cell<KW, 3, kEpiLstm>(a, s);
+}
+
+}  // namespace seq1
+
+}  // namespace amq

@@ -513,7 +513,7 @@ __global__ __launch_bounds__(256) void seqw_reset_kernel(unsigned* flag, Residen
 
 // The piece again from the saved state if the launch before gave up: one workgroup per batch entry.
 template <int KA>
-__global__ __launch_bounds__(64 * kWBlocks) void seqw_recover_kernel(SeqWArgs a, int KW, int gru, ResidentClaim claim) {
+__global__ __launch_bounds__(64 * kWBlocks) void seqw_recover_kernel(SeqWArgs a, int KW, int gru, ResidentClaim claim, int clear) {
   __shared__ double sh[2 * kExchange<kWBlocks>];
   __shared__ float hcur[2][2048];
   __shared__ uint32_t codes[KA * 64];
@@ -589,15 +589,16 @@ __global__ __launch_bounds__(64 * kWBlocks) void seqw_recover_kernel(SeqWArgs a,
     __syncthreads();
   }
   for (int u = tid; u < H; u += 64 * kWBlocks) a.h0[(size_t)b * H + u] = hcur[a.steps & 1][u];
+  if (clear && tid == 0) *a.flag = 0u;  // (one workgroup: nobody else reads it)
 }
 
-hipError_t launch_recover(const SeqWArgs& a, int k_w, int k_a, int epi, const ResidentClaim& claim, hipStream_t s) {
+hipError_t launch_recover(const SeqWArgs& a, int k_w, int k_a, int epi, const ResidentClaim& claim, hipStream_t s, int clear = 0) {
   const dim3 grid((unsigned)a.batch), block(64 * kWBlocks);
   const int gru = epi == kEpiGru;
   switch (k_a) {
-    case 1: hipLaunchKernelGGL((seqw_recover_kernel<1>), grid, block, 0, s, a, k_w, gru, claim); break;
-    case 2: hipLaunchKernelGGL((seqw_recover_kernel<2>), grid, block, 0, s, a, k_w, gru, claim); break;
-    default: hipLaunchKernelGGL((seqw_recover_kernel<3>), grid, block, 0, s, a, k_w, gru, claim); break;
+    case 1: hipLaunchKernelGGL((seqw_recover_kernel<1>), grid, block, 0, s, a, k_w, gru, claim, clear); break;
+    case 2: hipLaunchKernelGGL((seqw_recover_kernel<2>), grid, block, 0, s, a, k_w, gru, claim, clear); break;
+    default: hipLaunchKernelGGL((seqw_recover_kernel<3>), grid, block, 0, s, a, k_w, gru, claim, clear); break;
   }
   return hipGetLastError();
 }
@@ -711,6 +712,10 @@ hipError_t launch_seqw(SeqWArgs a, const SeqWScratch& w, int k_w, int k_a, int e
   const hipError_t ran = run(&a, a.x.n, a.H, a.batch, k_w, k_a, epi, s);
   e = launch_recover(a, k_w, k_a, epi, claim, s);
   return ran != hipSuccess ? ran : e;
+}
+
+hipError_t launch_seq_recover(const SeqWArgs& a, int k_w, int k_a, int epi, hipStream_t s) {
+  return launch_recover(a, k_w, k_a, epi, ResidentClaim{}, s, a.batch == 1);
 }
 
 // ---- shares of the chip (amq_resident.h) ---------------------------------------------------------------------

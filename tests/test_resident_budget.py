@@ -67,3 +67,9 @@ def test_room_for_waiting_kernels_beside_light_claims(registers):
     # three workgroups of 4 waves per compute unit: three waves on every SIMD
     for name, r in of(registers, "16lstm_seqg_kernel", 4).items():
         assert 3 * r + WAITERS * 8 <= SIMD_REGISTERS, (name, r)
+
+
+def test_room_for_waiting_kernels_beside_single_sequences(registers):
+    # one workgroup of 4 waves per compute unit: a wave on every SIMD
+    for name, r in of(registers, "11seq1_kernel", 104).items():
+        assert r + WAITERS * 8 <= SIMD_REGISTERS, (name, r)
