@@ -95,10 +95,21 @@ __device__ __forceinline__ void quantize_block(const QuantArgs& a, int vec, doub
   with_slots<NJ, ONLINE>(nj, [&](auto slots) {
     float w[slots()];
     load_slots<slots()>(x, n, base, nj, w);
-    quantize_core<K, slots(), NW, ONLINE>(w, n, base, nj, a.T, alpha, mym, sh, phase, AMQ_PHASE_OF(a));
+    if constexpr (RECON && !ONLINE) {
+      float v[slots()];
+      quantize_core<K, slots(), NW, ONLINE, true>(w, n, base, nj, a.T, alpha, mym, sh, phase, AMQ_PHASE_OF(a), v);
+      float* out = a.recon + (long long)vec * a.recon_ld + base * 64 + lane;
+      const int left = min(n - base * 64, nj * 64) - lane;
+#pragma unroll
+      for (int j = 0; j < slots(); ++j)
+        if (j * 64 < left) out[j * 64] = v[j];
+    } else {
+      quantize_core<K, slots(), NW, ONLINE>(w, n, base, nj, a.T, alpha, mym, sh, phase, AMQ_PHASE_OF(a));
+    }
   });
 
   if constexpr (RECON) {
+    if (!ONLINE) return;
     // left to right over the planes, as launch_dequantize forms it; the mask of a slot sits in the slot's lane
     float* out = a.recon + (long long)vec * a.recon_ld + base * 64 + lane;
     const int left = min(n - base * 64, nj * 64) - lane;

@@ -109,16 +109,16 @@ __device__ __forceinline__ double recip_f64(double d) {
 // (0,2), .., (1,2), ..): G_ij = n - 2 d_ij, alpha_i = (sum_j cof_ji q_j) / det with exact cofactors and an
 // exact determinant for n <= 16384: the cofactors are integers of at most 45 bits, and at K = 4, where the
 // determinant may have 56, it is formed from terms n * cof that are multiples of 16 (every 3 x 3 minor of a
-// +-1 matrix is a multiple of 4), hence exact too.  A singular G leaves alpha unchanged.
+// +-1 matrix is a multiple of 4), hence exact too.  A singular G leaves alpha unchanged (returns false).
 template <int K>
-__device__ __forceinline__ void ls_solve_f64(int n, const double* d, const double (&q)[K], float (&alpha)[K]) {
+__device__ __forceinline__ bool ls_solve_f64(int n, const double* d, const double (&q)[K], float (&alpha)[K]) {
   const double dn = (double)n;
   if constexpr (K == 1) {
     alpha[0] = (float)(q[0] / dn);
   } else if constexpr (K == 2) {
     const double a = dn - 2.0 * d[0];
     const double det = dn * dn - a * a;
-    if (det == 0.0) return;
+    if (det == 0.0) return false;
     const double inv = recip_f64(det);
     alpha[0] = (float)((dn * q[0] + (-a) * q[1]) * inv);
     alpha[1] = (float)(((-a) * q[0] + dn * q[1]) * inv);
@@ -128,7 +128,7 @@ __device__ __forceinline__ void ls_solve_f64(int n, const double* d, const doubl
     const double c00 = nn - c * c, c01 = c * b - a * dn, c02 = a * c - dn * b;
     const double c11 = nn - b * b, c12 = a * b - dn * c, c22 = nn - a * a;
     const double det = dn * c00 + a * c01 + b * c02;
-    if (det == 0.0) return;
+    if (det == 0.0) return false;
     const double inv = recip_f64(det);
     alpha[0] = (float)((c00 * q[0] + c01 * q[1] + c02 * q[2]) * inv);
     alpha[1] = (float)((c01 * q[0] + c11 * q[1] + c12 * q[2]) * inv);
@@ -148,13 +148,14 @@ __device__ __forceinline__ void ls_solve_f64(int n, const double* d, const doubl
     const double c13 = b * s5 - dn * s2 + g * s1, c22 = c * s4 - f * s2 + dn * s0;
     const double c23 = e * s2 - b * s4 - g * s0, c33 = b * s3 - e * s1 + dn * s0;
     const double det = (dn * c00 + a * c01) + (b * c02 + c * c03);
-    if (det == 0.0) return;
+    if (det == 0.0) return false;
     const double inv = recip_f64(det);
     alpha[0] = (float)((c00 * q[0] + c01 * q[1] + c02 * q[2] + c03 * q[3]) * inv);
     alpha[1] = (float)((c01 * q[0] + c11 * q[1] + c12 * q[2] + c13 * q[3]) * inv);
     alpha[2] = (float)((c02 * q[0] + c12 * q[1] + c22 * q[2] + c23 * q[3]) * inv);
     alpha[3] = (float)((c03 * q[0] + c13 * q[1] + c23 * q[2] + c33 * q[3]) * inv);
   }
+  return true;
 }
 
 // v_writelane_b32: lane `lane` (a constant) of `old` takes the wave-uniform `value`.  (The compiler's
@@ -258,11 +259,15 @@ __device__ __forceinline__ void block_totals(double (&v)[NV], double (*sh)[16 * 
 //     disagreement counts of the plane pairs likewise.  No code is formed before the last pass.
 //   - C_t is accumulated by ONE binary64 addition under the comparison's own mask as the lane mask (a masked
 //     addition costs 5.3 cycles of a SIMD, measured; selecting +-w first costs 13).
-//   - alpha_K of the greedy start is needed only where the first Gram matrix is singular, so its sum travels with
-//     the first Eq.-5 reduction instead of having a reduction of its own.
+//   - alpha_K of the greedy start is needed only where the first Gram matrix is singular (or T = 0): its sum of |r| is
+//     formed there and nowhere else, and at two planes no residual at all (k = 2: 16384 x 4096 73.6 -> 69.3, 42000 x 300
+//     25.3 -> 23.4, 20000 x 1500 44.0 -> 40.5; k = 3 2 to 5 %).
+//   - the reconstruction is read off the table by position, not put together from the planes (a select per midpoint
+//     instead of two lane reads, a select and an addition per plane: 16000 x 4096 at k = 3 / 4 with its copy of the gradient
+//     247 / 403 -> 229 / 371, 42000 x 300 67 / 130 -> 57 / 109).
 // Bound: vector-instruction issue at k >= 3 and HBM at k <= 2 for many vectors, the chain of reductions for a few.
 // Measured (us) against the form that compared w with all midpoints and selected +-w per plane, k = 2 / 3 / 4:
-// 16384 x 4096 135 / 239 / 443 -> 76 / 125 / 285, 4096 x 2048 33 / 54 / 100 -> 10.5 / 19 / 39, 128 vectors of 1024
+// 16384 x 4096 135 / 239 / 443 -> 69 / 127 / 290, 4096 x 2048 33 / 54 / 100 -> 10.8 / 19.8 / 41, 128 vectors of 1024
 // (launches back to back) 4.4 / 5.9 / 10.1 -> 3.4 / 4.4 / 6.7.
 
 // A value the compiler must take as new: keeps it from holding the comparison masks of one pass in scalar registers
@@ -425,6 +430,7 @@ struct CodeTable {
   static constexpr int H = 1 << (K - 1);
   int thr[H > 1 ? H - 1 : 1];
   unsigned bm[K];
+  int val[H];  // bits of the values, not negative (filled by code_table)
 };
 
 __device__ __forceinline__ int uniform_bits(float v) { return __builtin_amdgcn_readfirstlane(__float_as_int(v)); }
@@ -459,6 +465,8 @@ __device__ __forceinline__ void code_table_any_order(const float (&alpha)[K], Co
   for (int t = 0; t < H - 1; ++t) ct.thr[t] = __builtin_amdgcn_readlane(mid, t);
 #pragma unroll
   for (int i = 0; i < K; ++i) ct.bm[i] = (unsigned)__ballot((sp & (1 << (K - 1 - i))) != 0) & ((1u << H) - 1u);
+#pragma unroll
+  for (int t = 0; t < H; ++t) ct.val[t] = __builtin_amdgcn_readlane(__float_as_int(sv), t);
 }
 
 template <int K>
@@ -471,6 +479,8 @@ __device__ __forceinline__ void code_table(const float (&alpha)[K], CodeTable<K>
       ct.thr[0] = uniform_bits(0.5f * (v2 + v3));
       ct.bm[0] = 3u;
       ct.bm[1] = 2u;
+      ct.val[0] = uniform_bits(v2);
+      ct.val[1] = uniform_bits(v3);
       return;
     }
   } else if constexpr (K == 3) {
@@ -486,6 +496,10 @@ __device__ __forceinline__ void code_table(const float (&alpha)[K], CodeTable<K>
       ct.bm[0] = swap ? 0xeu : 0xfu;
       ct.bm[1] = swap ? 0xdu : 0xcu;
       ct.bm[2] = swap ? 0xbu : 0xau;
+      ct.val[0] = uniform_bits(lo);
+      ct.val[1] = uniform_bits(v5);
+      ct.val[2] = uniform_bits(v6);
+      ct.val[3] = uniform_bits(v7);
       return;
     }
   }
@@ -513,10 +527,11 @@ constexpr int kSignMaskSlots = 4;
 // slots each.  On return alpha holds the coefficients and lane j of each wave, in mym[i], the 64 packed codes of
 // its slot j of plane i.  Slots below MASKED lie inside the vector; an entry of the others that does not is 0 and its u
 // is -1, below every midpoint (branches around absent slots cost a vector of 650 entries twice the time of 640).
-template <int K, int NJ, int NW, int MASKED>
+template <int K, int NJ, int NW, int MASKED, bool RECON = false>
 __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n, int base, int nj, int T,
                                                     float (&alpha)[K], unsigned long long (&mym)[K],
-                                                    double* sh, int& phase, unsigned long long* marks) {
+                                                    double* sh, int& phase, unsigned long long* marks,
+                                                    float* recon = nullptr) {
   (void)marks;  // phase timers of the profiling build: 2 = greedy done, 4 + 4 * cycle + {0: reduction, 1: solve, 2: table, 3: assignment}
   constexpr int H = 1 << (K - 1);
   constexpr int NT = H > 1 ? H - 1 : 1;
@@ -556,12 +571,16 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
   alpha[0] = mean(l1);
   if constexpr (K == 1) {
     // the sign codes are final: Eq. 5 returns mean |w| again and the only midpoint is 0
+    if constexpr (RECON) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) recon[j] = r[j] < 0.0f ? -alpha[0] : alpha[0];
+    }
     mym[0] = ~lane_neg & lane_inside;
     return;
   } else {
     // ---- greedy stages 2 .. K (Eq. 4): the residual loses the previous plane, its sign is the next plane.
-    // s[i] = sum of |w| where plane i agrees with the sign of w, cnt = disagreement counts of the plane pairs.
-    double s[K];     // s[1 .. K-1]; s[0] carries sum |r| of the last stage into the first Eq.-5 reduction
+    // s[i - 1] = sum of |w| where plane i agrees with the sign of w, cnt = disagreement counts of the plane pairs.
+    double s[K - 1];
     int cnt[NP];
 #pragma unroll
     for (int i = 0; i < NP; ++i) cnt[i] = 0;
@@ -577,9 +596,12 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
         unsigned long long before = 0ull;  // previous plane against the sign of w
         if (NJ > 4 && i > 2) r[j] = opaque_v(r[j]);
         if (i > 1) before = __ballot(r[j] < 0.0f);
-        float rn = r[j] - copysignf(a, r[j]);  // (a difference is never -0.0)
-        if (j >= MASKED) rn = lane_bit(in) ? rn : 0.0f;
-        r[j] = rn;
+        float rn = 0.0f;
+        if (K > 2) {
+          rn = r[j] - copysignf(a, r[j]);  // (a difference is never -0.0)
+          if (j >= MASKED) rn = lane_bit(in) ? rn : 0.0f;
+          r[j] = rn;
+        }
         unsigned long long f[1];
         if (i == 1) {
           f[0] = __ballot(u[j] >= abits);
@@ -594,24 +616,39 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
         if (i > 1) f[0] &= in;
         add_count<NJ>(cnt[i - 1], f[0]);
         masked_add<1>(si, wd[j], f);
-        const double ra = (double)fabsf(rn);
-        sr[0] = (j == 0) ? ra : sr[0] + ra;
+        if (i + 1 < K) {
+          const double ra = (double)fabsf(rn);
+          sr[0] = (j == 0) ? ra : sr[0] + ra;
+        }
         if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
       }
-      s[i] = si[0];
+      s[i - 1] = si[0];
       if (i + 1 < K) {
         AMQ_PHASE(marks, 14);
         exchange_totals<NW, 1, 0>(sr, no_counts, sh, phase);
         AMQ_PHASE(marks, 15);
         alpha[i] = mean(sr[0]);
-      } else {
-        s[0] = sr[0];
       }
     }
     AMQ_PHASE(marks, 2);
-    exchange_totals<NW, K, NP>(s, cnt, sh, phase);
-    alpha[K - 1] = mean(s[0]);
+    exchange_totals<NW, K - 1, NP>(s, cnt, sh, phase);
+    auto last_greedy_coefficient = [&]() {  // (the whole workgroup or nobody)
+      double sr[1] = {0.0};
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        double w0 = wd[j];
+        asm volatile("" : "+v"(w0));  // (otherwise the binary32 value is kept in registers from the start for this)
+        float rj = (float)w0;
+#pragma unroll
+        for (int i = 0; i + 1 < K; ++i) rj = rj - copysignf(alpha[i], rj);
+        if (j >= MASKED) rj = u[j] >= 0 ? rj : 0.0f;
+        sr[0] = (j == 0) ? (double)fabsf(rj) : sr[0] + (double)fabsf(rj);
+      }
+      exchange_totals<NW, 1, 0>(sr, no_counts, sh, phase);
+      alpha[K - 1] = mean(sr[0]);
+    };
     if (T == 0) {
+      last_greedy_coefficient();
       // the greedy result itself: its planes are formed again from the coefficients
 #pragma unroll
       for (int i = 0; i < K; ++i) mym[i] = 0ull;
@@ -620,11 +657,15 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
         double w0 = wd[j];
         asm volatile("" : "+v"(w0));  // (otherwise the binary32 value is kept in registers from the start for this)
         float rj = (float)w0;
+        float v = 0.0f;
 #pragma unroll
         for (int i = 0; i < K; ++i) {
           keep_in_lane(mym[i], __ballot(rj >= 0.0f), j);
+          const float term = rj >= 0.0f ? alpha[i] : -alpha[i];
+          v = i == 0 ? term : v + term;
           rj = rj - copysignf(alpha[i], rj);
         }
+        if constexpr (RECON) recon[j] = v;
       }
 #pragma unroll
       for (int i = 0; i < K; ++i) mym[i] &= lane_inside;
@@ -634,7 +675,7 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
     q[0] = l1;
 #pragma unroll
     for (int i = 1; i < K; ++i) {
-      q[i] = 2.0 * s[i] - l1;
+      q[i] = 2.0 * s[i - 1] - l1;
       d[i - 1] = (double)(n - cnt[i - 1]);
     }
 #pragma unroll
@@ -643,7 +684,7 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
     CodeTable<K> ct;
     for (int it = 0;; ++it) {
       AMQ_PHASE(marks, 4 + 4 * it);
-      ls_solve_f64<K>(n, d, q, alpha);
+      if (!ls_solve_f64<K>(n, d, q, alpha) && it == 0) last_greedy_coefficient();
       AMQ_PHASE(marks, 5 + 4 * it);
       code_table<K>(alpha, ct);
       AMQ_PHASE(marks, 6 + 4 * it);
@@ -691,6 +732,19 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
         }
     }
 
+    if constexpr (RECON) {
+      // the value of the position, by selects from the smallest up, with the sign of w (the table is symmetric, exactly)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        float v = __int_as_float(ct.val[0]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) v = u[j] >= ct.thr[t] ? __int_as_float(ct.val[t + 1]) : v;
+        recon[j] = __double2hiint(wd[j]) < 0 ? 0.0f - v : v;
+        if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+      return;
+    }
+
     // ---- the last pass: the comparison masks, slot j in lane j, then the planes in the lanes
     unsigned long long ge[NT];
 #pragma unroll
@@ -734,7 +788,7 @@ __device__ __forceinline__ double one_if(bool yes) { return __hiloint2double(yes
 // Eq. 5 from the inner products g of the planes (integers; pairs in the order of ls_solve_f64), which are exact, as are
 // all intermediate values that are in ls_solve_f64.
 template <int K>
-__device__ __forceinline__ void ls_solve_gram(int n, double dn, const double* g, const double (&q)[K], float (&alpha)[K]) {
+__device__ __forceinline__ bool ls_solve_gram(int n, double dn, const double* g, const double (&q)[K], float (&alpha)[K]) {
   if constexpr (K == 2) {
     const double a = g[0];
     const double det = __builtin_fma(-a, a, dn * dn);
@@ -743,6 +797,7 @@ __device__ __forceinline__ void ls_solve_gram(int n, double dn, const double* g,
     const float a1 = (float)(__builtin_fma(-a, q[0], dn * q[1]) * inv);
     alpha[0] = det != 0.0 ? a0 : alpha[0];  // (a select, so that the neighbouring steps stay one block of code)
     alpha[1] = det != 0.0 ? a1 : alpha[1];
+    return det != 0.0;
   } else if constexpr (K == 3) {
     const double a = g[0], b = g[1], c = g[2];
     const double nn = dn * dn;
@@ -756,11 +811,12 @@ __device__ __forceinline__ void ls_solve_gram(int n, double dn, const double* g,
     alpha[0] = det != 0.0 ? a0 : alpha[0];
     alpha[1] = det != 0.0 ? a1 : alpha[1];
     alpha[2] = det != 0.0 ? a2 : alpha[2];
+    return det != 0.0;
   } else {
     double d[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) d[i] = 0.5 * (dn - g[i]);
-    ls_solve_f64<K>(n, d, q, alpha);
+    return ls_solve_f64<K>(n, d, q, alpha);
   }
 }
 
@@ -848,14 +904,16 @@ __device__ __forceinline__ void quantize_online(const float (&x)[NJ], int n, int
     mym[0] = ~signs_in_lanes() & lane_inside;
     return;
   } else {
-    // ---- greedy stages; red: the sum of |r| of the last stage, s[1 .. K-1], then the packed counts
-    double red[4 * ((K + NPW + 3) / 4)];
+    // ---- greedy stages; red: the sum of |r| of the last stage, s[1 .. K-1], then the packed counts.  A wave on its own
+    // forms that sum only where it is needed (a workgroup always: other waves of it may count its barriers).
+    constexpr int SK = NW == 1 ? 1 : 0;
+    double red[4 * ((K - SK + NPW + 3) / 4)];
     auto tally = [&](int pair, double m) {
-      double& acc = red[K + pair / 3];
+      double& acc = red[K - SK + pair / 3];
       acc = __builtin_fma(m, field[pair % 3], acc);
     };
 #pragma unroll
-    for (int i = 0; i < NPW; ++i) red[K + i] = 0.0;
+    for (int i = 0; i < NPW; ++i) red[K - SK + i] = 0.0;
 #pragma unroll
     for (int i = 1; i < K; ++i) {
       const float a = alpha[i - 1];
@@ -879,25 +937,40 @@ __device__ __forceinline__ void quantize_online(const float (&x)[NJ], int n, int
         tally(i - 1, m);
         sr += fabs((double)rn);
       }
-      red[i] = si;
+      red[i - SK] = si;
       if (i + 1 < K) {
         double one[1] = {sr};
         AMQ_PHASE(marks, 14);
         exchange_totals<NW, 1, 0>(one, no_counts, sh, phase);
         AMQ_PHASE(marks, 15);
         alpha[i] = mean(one[0]);
-      } else {
+      } else if (SK == 0) {
         red[0] = sr;
       }
     }
     AMQ_PHASE(marks, 2);
-    exchange_raw<NW, K + NPW>(red, sh, phase);
+    exchange_raw<NW, K - SK + NPW>(red, sh, phase);
     auto total_of = [&](const double* e, int i) { return readlane_d(e[i & ~3], total_lane<NW>(i)); };
     auto counts_of = [&](const double* e, int i) {
       return (unsigned long long)__double_as_longlong(readlane_d(e[i & ~3] + 0x1p52, total_lane<NW>(i)));
     };
-    alpha[K - 1] = mean(total_of(red, 0));
+    auto last_greedy_coefficient = [&]() {
+      if (SK == 0) return;
+      double one[1] = {0.0};
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        float rj = xc[j];
+#pragma unroll
+        for (int i = 0; i + 1 < K; ++i) rj = rj - copysignf(alpha[i], rj);
+        if (j >= WHOLE) rj = __int_as_float(__float_as_int(rj) & in[j]);
+        one[0] += fabs((double)rj);
+      }
+      exchange_totals<NW, 1, 0>(one, no_counts, sh, phase);
+      alpha[K - 1] = mean(one[0]);
+    };
+    if (SK == 0) alpha[K - 1] = mean(total_of(red, 0));
     if (T == 0) {
+      last_greedy_coefficient();
 #pragma unroll
       for (int i = 0; i < K; ++i) mym[i] = 0ull;
 #pragma unroll
@@ -917,11 +990,11 @@ __device__ __forceinline__ void quantize_online(const float (&x)[NJ], int n, int
     {
       unsigned long long p[NPW];
 #pragma unroll
-      for (int i = 0; i < NPW; ++i) p[i] = counts_of(red, K + i);
+      for (int i = 0; i < NPW; ++i) p[i] = counts_of(red, K - SK + i);
       q[0] = l1;
 #pragma unroll
       for (int i = 1; i < K; ++i) {
-        q[i] = __builtin_fma(2.0, total_of(red, i), -l1);
+        q[i] = __builtin_fma(2.0, total_of(red, i - SK), -l1);
         // plane 0 against plane i; entries past the end agree from the second stage on
         g[i - 1] = (double)(2 * (count_of(p[(i - 1) / 3], (i - 1) % 3) - (i > 1 ? outside : 0)) - n);
       }
@@ -934,7 +1007,8 @@ __device__ __forceinline__ void quantize_online(const float (&x)[NJ], int n, int
     int kind;
     for (int it = 0;; ++it) {
       AMQ_PHASE(marks, 4 + 4 * it);
-      ls_solve_gram<K>(n, dn, g, q, alpha);
+      const bool solved = ls_solve_gram<K>(n, dn, g, q, alpha);
+      if (SK != 0 && it == 0 && __builtin_expect(__ballot(!solved) != 0ull, 0)) last_greedy_coefficient();
       AMQ_PHASE(marks, 5 + 4 * it);
       kind = code_table_kind<K>(alpha, ct);
       AMQ_PHASE(marks, 6 + 4 * it);
@@ -1093,10 +1167,12 @@ __device__ __forceinline__ int quantize_exchanges(int T) {
 // The same for a wave that may or may not have all its slots inside the vector (a wave-uniform choice; the
 // waves of a workgroup meet at the same barriers either way).
 // ONLINE: the latency-bound form.
-template <int K, int NJ, int NW, bool ONLINE>
+// RECON (throughput form): recon[j] receives the value of this lane's code in slot j instead of codes in mym.
+template <int K, int NJ, int NW, bool ONLINE, bool RECON = false>
 __device__ __forceinline__ void quantize_core(const float (&x)[NJ], int n, int base, int nj, int T, float (&alpha)[K],
                                               unsigned long long (&mym)[K], double* sh, int& phase,
-                                              unsigned long long* marks = nullptr) {
+                                              unsigned long long* marks = nullptr, float* recon = nullptr) {
+  static_assert(!(ONLINE && RECON), "the latency form leaves codes");
   base = __builtin_amdgcn_readfirstlane(base);
   const bool full = nj == NJ && (base + NJ) * 64 <= n;
   if constexpr (ONLINE) {
@@ -1105,13 +1181,13 @@ __device__ __forceinline__ void quantize_core(const float (&x)[NJ], int n, int b
       quantize_online<K, NJ, NW, NW == 1 ? NJ - 1 : 0>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
     else quantize_online<K, NJ, NW, 0>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
   } else if (full) {
-    quantize_magnitudes<K, NJ, NW, NJ>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+    quantize_magnitudes<K, NJ, NW, NJ, RECON>(x, n, base, nj, T, alpha, mym, sh, phase, marks, recon);
   } else {
     // a single wave usually takes the form of its own number of slots, an even one: only the last two can be short
     if (NW == 1 && (NJ - 2) * 64 < n)
-      quantize_magnitudes<K, NJ, NW, NW == 1 ? NJ - 2 : 0>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+      quantize_magnitudes<K, NJ, NW, NW == 1 ? NJ - 2 : 0, RECON>(x, n, base, nj, T, alpha, mym, sh, phase, marks, recon);
     else
-      quantize_magnitudes<K, NJ, NW, 0>(x, n, base, nj, T, alpha, mym, sh, phase, marks);
+      quantize_magnitudes<K, NJ, NW, 0, RECON>(x, n, base, nj, T, alpha, mym, sh, phase, marks, recon);
   }
 }
 
