@@ -584,8 +584,8 @@ static int lstm_step_launch(const uint32_t* Wxp, const float* alpha_x, const uin
     b.T = T;
     const bool apart = apart_from(h_prev, H, h_out, H) && apart_from(h_prev, H, c_out, H) && apart_from(x, I, h_out, H) &&
                        apart_from(x, I, c_out, H) && (!hs_out || (apart_from(h_prev, H, hs_out, H) && apart_from(x, I, hs_out, H)));
-    if (apart && amq::bmv_online_supported(b, k_w, k_a, amq::kEpiLstm))
-      return hip_status(amq::launch_bmv_online(b, k_w, k_a, amq::kEpiLstm, s));
+    if (apart && amq::cell1_supported(b, k_w, k_a, amq::kEpiLstm))
+      return hip_status(amq::launch_cell1(b, k_w, k_a, amq::kEpiLstm, s));
   }
   amq::QuantArgs q{};
   q.seg[0] = amq::QuantSeg{x, I, (int)I, (int)B, w.xp, w.beta_x};
@@ -843,6 +843,15 @@ static int gru_step_launch(const uint32_t* Wxp, const float* alpha_x, const uint
                            int64_t I, int64_t H, int k_w, const float* bias_x, const float* bias_h, const float* x,
                            const float* h_prev, int64_t B, int k_a, int T, float* h_out, const StepWs& w,
                            hipStream_t s) {
+  if (B == 1) {  // one launch, as in lstm_step_launch
+    amq::BmvArgs b = gru_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, nullptr, nullptr, nullptr, nullptr, h_prev, 1,
+                              h_out);
+    b.raw[0] = x;
+    b.raw[1] = h_prev;
+    b.T = T;
+    if (apart_from(h_prev, H, h_out, H) && apart_from(x, I, h_out, H) && amq::cell1_supported(b, k_w, k_a, amq::kEpiGru))
+      return hip_status(amq::launch_cell1(b, k_w, k_a, amq::kEpiGru, s));
+  }
   amq::QuantArgs q{};
   q.seg[0] = amq::QuantSeg{x, I, (int)I, (int)B, w.xp, w.beta_x};
   q.seg[1] = amq::QuantSeg{h_prev, H, (int)H, (int)B, w.hp, w.beta_h};
@@ -1152,7 +1161,7 @@ static amq::BmvArgs output_args(const uint32_t* Wsp, const float* alpha_s, int64
 }
 static int output_online_launch(const amq::BmvArgs& b, int k_w, int k_a, hipStream_t s) {
   int slots = 0;
-  const int st = hip_status(amq::launch_bmv_online(b, k_w, k_a, amq::kEpiStore, s, &slots));
+  const int st = hip_status(amq::launch_bmv_online(b, k_w, k_a, s, &slots));
   if (st != AMQ_OK) return st;
   return hip_status(amq::launch_log_softmax_finish(b.Y, 1, b.m, b.lse_part, slots, b.Y, s));
 }
@@ -1162,7 +1171,7 @@ static int softmax_layer_launch(const uint32_t* Wsp, const float* alpha_s, int64
                                 const SoftmaxWs& w, hipStream_t s) {
   if (B == 1 && apart_from(h, H, logprob, V)) {
     const amq::BmvArgs b = output_args(Wsp, alpha_s, V, H, bias, h, T, logprob, w);
-    if (amq::bmv_online_supported(b, k_w, k_a, amq::kEpiStore)) return output_online_launch(b, k_w, k_a, s);
+    if (amq::bmv_online_supported(b, k_w, k_a)) return output_online_launch(b, k_w, k_a, s);
   }
   amq::QuantArgs q{};
   q.seg[0] = amq::QuantSeg{h, H, (int)H, (int)B, w.hp, w.beta};
@@ -1239,8 +1248,8 @@ static int lm_step_launch(const uint32_t* Ep, const float* alpha_e, int64_t voca
     r.T = T;
     amq::BmvArgs o = output_args(Wsp, alpha_s, V, H, bias_s, w.pre0, T, logprob, sw);
     o.copy_to = h;
-    if (amq::bmv_online_supported(r, k_w, k_a, amq::kEpiLstm) && amq::bmv_online_supported(o, k_ws, k_as, amq::kEpiStore)) {
-      const int st = hip_status(amq::launch_bmv_online(r, k_w, k_a, amq::kEpiLstm, s));
+    if (amq::cell1_supported(r, k_w, k_a, amq::kEpiLstm) && amq::bmv_online_supported(o, k_ws, k_as)) {
+      const int st = hip_status(amq::launch_cell1(r, k_w, k_a, amq::kEpiLstm, s));
       return st != AMQ_OK ? st : output_online_launch(o, k_ws, k_as, s);
     }
   }

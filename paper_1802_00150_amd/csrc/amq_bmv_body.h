@@ -21,12 +21,12 @@ namespace amq {
 
 // LSE (store mode only): also leave, per batch entry and wave, the (max, sum of exponentials) of
 // the outputs the wave produced, for a log-softmax over the rows that follows.
-// ONLINE (one batch entry, one group): the operands are given as vectors (a.raw) that every workgroup quantizes for
-// itself while its weights are on the way, or (x block) as a row of a quantized table.  Against a quantizer launch of its
-// own that is about a microsecond of arithmetic in every workgroup instead of a launch (2.5 us on the host, 1.6 to 3.4 us
-// between dependent kernels).
+// ONLINE (plain product, one batch entry, one group): the operand is given as a vector (a.raw[0]) that every workgroup
+// quantizes for itself while its weights are on the way.  Against a quantizer launch of its own that is about a microsecond
+// of arithmetic in every workgroup instead of a launch (2.5 us on the host, 1.6 to 3.4 us between dependent kernels).
 template <int KW, int KA, int NSEG, int NBLK, int EPI, bool LSE, bool ONLINE>
-__device__ __forceinline__ void bmv_body(const BmvArgs& a, uint4* xs, double* sh, float (*bts)[4]) {
+__device__ __forceinline__ void bmv_body(const BmvArgs& a, uint4* xs, double* sh, float* bts) {
+  static_assert(!ONLINE || (EPI == kEpiStore && NBLK == 1), "steps of one entry: amq_cell1.hip");
   const int lane = lane_id(), wv = wave_id();
   const int lg = a.lg;
   const int G = 1 << lg, R = 64 >> lg;
@@ -51,13 +51,10 @@ __device__ __forceinline__ void bmv_body(const BmvArgs& a, uint4* xs, double* sh
 
   // (the vectors to quantize are requested before anything else: the loads return in order)
   constexpr int kRawSlots = ONLINE ? 8 : 1;
-  float raw[NBLK][kRawSlots];
+  float raw[kRawSlots];
   if constexpr (ONLINE) {
-#pragma unroll
-    for (int k = 0; k < NBLK; ++k) {
-      const int nj = (2 * cpr[k] + 3) >> 2;
-      if (a.raw[k]) load_slots<kRawSlots>(a.raw[k], a.blk[k].n, __builtin_amdgcn_readfirstlane(wv) * nj, nj, raw[k]);
-    }
+    const int nj = (2 * cpr[0] + 3) >> 2;
+    load_slots<kRawSlots>(a.raw[0], a.blk[0].n, __builtin_amdgcn_readfirstlane(wv) * nj, nj, raw);
   }
 
   // rows of this lane: segment s covers rows seg_base(s) + [0, R)
@@ -114,38 +111,24 @@ __device__ __forceinline__ void bmv_body(const BmvArgs& a, uint4* xs, double* sh
 #pragma unroll
   for (int k = 0; k < NBLK; ++k) {
     if constexpr (ONLINE) {
-      if (a.raw[k]) {
-        int phase = 0;
-        const int n = a.blk[k].n, nj = (2 * cpr[k] + 3) >> 2, base = __builtin_amdgcn_readfirstlane(wv) * nj;
-        float alpha[KA];
-        unsigned long long mym[KA];
-        if (k > 0) lds_barrier();  // (the exchange buffers are used again)
-        with_slots<kRawSlots, true>(nj, [&](auto slots) {
-          float v[slots()];
+      int phase = 0;
+      const int n = a.blk[0].n, nj = (2 * cpr[0] + 3) >> 2, base = __builtin_amdgcn_readfirstlane(wv) * nj;
+      float alpha[KA];
+      unsigned long long mym[KA];
+      with_slots<kRawSlots, true>(nj, [&](auto slots) {
+        float v[slots()];
 #pragma unroll
-          for (int j = 0; j < slots(); ++j) v[j] = raw[k][j];
-          quantize_core<KA, slots(), 4, true>(v, n, base, nj, a.T, alpha, mym, sh, phase);
-        });
+        for (int j = 0; j < slots(); ++j) v[j] = raw[j];
+        quantize_core<KA, slots(), 4, true>(v, n, base, nj, a.T, alpha, mym, sh, phase);
+      });
 #pragma unroll
-        for (int i = 0; i < KA; ++i) {
-          if (lane < nj && base + lane < 2 * cpr[k])
-            reinterpret_cast<unsigned long long*>(xs + xoff[k] + i * cpr[k])[base + lane] = mym[i];
-          if (threadIdx.x == 0) bts[k][i] = alpha[i];
-        }
-        if (k == 0 && a.copy_to && blockIdx.x == 0)
-          for (int t = threadIdx.x; t < n; t += 256) a.copy_to[t] = a.raw[k][t];
-      } else {
-        const long long id = a.row_of[0];
-        const bool there = id >= 0 && id < a.rows_of;
-        const long long r = there ? id : 0;
-        const uint4* src = reinterpret_cast<const uint4*>(a.blk[k].Xp);
-        for (int t = threadIdx.x; t < KA * cpr[k]; t += 256) {
-          const int j = t / cpr[k];
-          const uint4 v = src[(j * a.rows_of + r) * cpr[k] + (t - j * cpr[k])];
-          xs[xoff[k] + t] = there ? v : make_uint4(0, 0, 0, 0);
-        }
-        if (threadIdx.x < KA) bts[k][threadIdx.x] = there ? a.blk[k].beta[r * KA + threadIdx.x] : 0.0f;
+      for (int i = 0; i < KA; ++i) {
+        if (lane < nj && base + lane < 2 * cpr[0])
+          reinterpret_cast<unsigned long long*>(xs + i * cpr[0])[base + lane] = mym[i];
+        if (threadIdx.x == 0) bts[i] = alpha[i];
       }
+      if (a.copy_to && blockIdx.x == 0)
+        for (int t = threadIdx.x; t < n; t += 256) a.copy_to[t] = a.raw[0][t];
       continue;
     }
     const int total = KA * batch * cpr[k];
@@ -186,7 +169,7 @@ __device__ __forceinline__ void bmv_body(const BmvArgs& a, uint4* xs, double* sh
 #pragma unroll
       for (int j = 0; j < KA; ++j) {
         xq[j] = (sub < cpr[k]) ? xs[xoff[k] + (j * batch + b) * cpr[k] + sub] : make_uint4(0, 0, 0, 0);
-        bt[j] = ONLINE ? bts[k][j] : beta[b * KA + j];
+        bt[j] = ONLINE ? bts[j] : beta[b * KA + j];
       }
 #pragma unroll
       for (int s = 0; s < NSEG; ++s) {
@@ -214,7 +197,10 @@ __device__ __forceinline__ void bmv_body(const BmvArgs& a, uint4* xs, double* sh
         float pm = kLseLow, ps = 0.0f;
 #pragma unroll
         for (int s = 0; s < NSEG; ++s)
-          if (sub == 0 && ok[s]) lse_merge(pm, ps, yv[s], 1.0f);
+          if (sub == 0 && ok[s]) pm = fmaxf(pm, yv[s]);
+#pragma unroll
+        for (int s = 0; s < NSEG; ++s)
+          if (sub == 0 && ok[s]) ps += __expf(yv[s] - pm);
         lse_wave_merge(pm, ps);
         if (lane == 0) {
           float* dst = lse_part + ((long long)b * lse_slots + wave_global) * 2;

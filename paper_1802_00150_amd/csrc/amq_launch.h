@@ -198,9 +198,13 @@ bool bmv_supported(int n0, int n1, int k_a, long long batch, int epi);
 // lse_slots (nullable) receives the number of slots written per batch entry when a.lse_part is set
 hipError_t launch_bmv(BmvArgs a, int k_w, int k_a, int epi, hipStream_t s, int* lse_slots = nullptr);
 
-// One batch entry, operands given as vectors (a.raw): the same kernel with the quantizer in front, no launch of its own.
-bool bmv_online_supported(const BmvArgs& a, int k_w, int k_a, int epi);
-hipError_t launch_bmv_online(BmvArgs a, int k_w, int k_a, int epi, hipStream_t s, int* lse_slots = nullptr);
+// One batch entry, the operand given as a vector (a.raw[0]): a plain product with the quantizer in front, no launch of its own.
+bool bmv_online_supported(const BmvArgs& a, int k_w, int k_a);
+hipError_t launch_bmv_online(BmvArgs a, int k_w, int k_a, hipStream_t s, int* lse_slots);
+// A recurrent step of one batch entry likewise (a.raw; x may be a row of a table, a.row_of, instead).  Results must be apart
+// from the vectors.
+bool cell1_supported(const BmvArgs& a, int k_w, int k_a, int epi);
+hipError_t launch_cell1(BmvArgs a, int k_w, int k_a, int epi, hipStream_t s);
 
 // ---- batched products on the matrix cores (int8 MFMA on expanded codes), same epilogues ------
 bool mfma_supported(long long batch);

@@ -343,7 +343,8 @@ constexpr int kExchange = NW == 1 ? 1 : 2 * 16 * NW;
 // sums of all values take one matrix instruction each and one more, 16 partial sums (value, block) go to LDS in one
 // write, and after the one barrier every lane reads one (value, block, wave) entry of each four waves, and two matrix
 // instructions sum over waves and blocks.  Measured over four waves: 356 cycles for one value, 530 for four.
-// sh: 2 * kExchange<NW> doubles, the two buffers used alternately.
+// sh: 2 * kExchange<NW> doubles, the two buffers used alternately.  A workgroup may hold several groups of NW waves that work on
+// a vector each, with an sh each, in step: all pass the same barriers.
 template <int NW>
 __device__ __forceinline__ constexpr int total_lane(int i) { return (i & 3) * (NW == 1 ? 1 : 4); }
 
@@ -360,7 +361,7 @@ __device__ __forceinline__ void exchange_raw(double (&e)[4 * ((NE + 3) / 4)], do
       e[4 * g] = t;
     } else {
       const int lane = lane_id();
-      if (lane < 16) sh[phase * kExchange<NW> + (g * NW + wave_id()) * 16 + lane] = t;
+      if (lane < 16) sh[phase * kExchange<NW> + (g * NW + (wave_id() & (NW - 1))) * 16 + lane] = t;
     }
   }
   if constexpr (NW > 1) {

@@ -4,8 +4,7 @@
 // A step at batch 1 is a chain of latencies: h_{t-1} becomes visible to whoever needs it, is quantized (Alg. 2: three or
 // four dependent sums over the whole vector), multiplied, and passed through the cell.  The weights stay in registers for
 // the whole sequence and every reader quantizes h_{t-1} itself, so that one exchange per step is all there is:
-//   - lane = (hidden unit, gate, 16-byte chunk of the row), a hidden unit takes 4 * Gl lanes (Gl = chunks per row rounded
-//     up to a power of two, at most 16), a lane holds the KW plane chunks of both operand blocks of U units;
+//   - a hidden unit's rows are spread over adjacent lanes (amq_unit_lanes.h), their weights in registers;
 //   - h_t is published as 8-byte {value, step tag} pairs, each written with one 64-bit device-scope store; readers poll the
 //     pairs they need until all carry the tag of the step, so the data is its own arrival signal.  Two buffers in turn
 //     suffice: a buffer is written again by waves that have seen every pair of the step between;
@@ -28,6 +27,7 @@
 #pragma once
 #include "amq_launch.h"
 #include "amq_quantize_body.h"
+#include "amq_unit_lanes.h"
 
 namespace amq {
 
@@ -45,11 +45,11 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
   __shared__ int dead;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int I = a.I, H = a.H, lg = a.lg, Gl = 1 << lg;
+  const int I = a.I, H = a.H;
   const int cprI = (I + 127) >> 7, cprH = (H + 127) >> 7;
-  const int c = lane & (Gl - 1), gate = (lane >> lg) & 3, uo = lane >> (lg + 2);
-  const int per = 16 >> lg;  // units of a wave side by side
-  const int unit0 = (blockIdx.x * k1Waves + wv) * U * per + uo;
+  const UnitLanes l(a.lg, lane);
+  const int c = l.c, per = l.per;
+  const int unit0 = (blockIdx.x * k1Waves + wv) * U * per + l.uo;
   if (tid == 0) dead = 0;
 
   // an earlier launch of the same call gave up
@@ -61,40 +61,10 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
     return;
   }
 
-  // ---- once: this lane's plane chunks and coefficients of both blocks
-  uint4 wq[2][U][KW];
-  float al[2][U][KW];
-  const int g = gate < NG ? gate : NG - 1;
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const uint4* Wp4 = reinterpret_cast<const uint4*>(k ? a.Whp : a.Wxp);
-    const float* alpha = k ? a.ah : a.ax;
-    const int cpr = k ? cprH : cprI;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int unit = unit0 + u * per;
-      const bool ok = unit < H && c < cpr && gate < NG;
-      const int row = g * H + (unit < H ? unit : 0);
-#pragma unroll
-      for (int i = 0; i < KW; ++i) {
-        const uint4 t = Wp4[((long long)i * NG * H + row) * cpr + (c < cpr ? c : 0)];
-        wq[k][u][i] = ok ? t : make_uint4(0, 0, 0, 0);
-        al[k][u][i] = alpha[row * KW + i];
-      }
-    }
-  }
-  float bits[2][U];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int n = k ? H : I, left = n - 128 * c;
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      bits[k][u] = unit0 + u * per < H && gate < NG && left > 0 ? (float)(left > 128 ? 128 : left) : 0.0f;
-  }
-  // the cell of slot u is applied by the lane of gate u (chunk 0) of its units
-  const int mine = U == 1 ? 0 : gate & (U - 1);
-  const int unit = unit0 + mine * per;
-  const bool cell = c == 0 && gate < U && unit < H;
+  UnitWeights<KW, U> q;
+  load_unit_weights<KW, U, NG>(q, l, unit0, a.Wxp, a.ax, I, a.Whp, a.ah, H);
+  const int unit = unit0 + unit_slot<U>(l) * per;
+  const bool cell = c == 0 && l.gate < U && unit < H;
   float b0[NG], b1[NG], cst = 0.0f, hlast = 0.0f;
 #pragma unroll
   for (int r = 0; r < NG; ++r) {
@@ -127,17 +97,6 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
       xb[j] = a.xbeta[t * KA + j];
     }
   };
-  auto dots = [&](int k, int u, const uint4 (&v)[KA], const float (&bt)[KA]) {
-    float acc = 0.0f;
-#pragma unroll
-    for (int i = 0; i < KW; ++i) {
-      float inner = 0.0f;
-#pragma unroll
-      for (int j = 0; j < KA; ++j) inner = fmaf(bt[j], bits[k][u] - 2.0f * (float)popc4(wq[k][u][i], v[j]), inner);
-      acc = fmaf(al[k][u][i], inner, acc);
-    }
-    return acc;
-  };
   float px[U];  // x-side sums of the step to come: per lane, or (JOINT false) already over the row
   auto x_side = [&]() {
     if (c >= cprI) {
@@ -146,8 +105,8 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      px[u] = dots(0, u, xv, xb);
-      if constexpr (!JOINT) px[u] = group_sum(px[u], lg);
+      px[u] = unit_dot(q, 0, u, xv, xb);
+      if constexpr (!JOINT) px[u] = group_sum(px[u], l.lg);
     }
   };
   request_x(0);
@@ -229,44 +188,10 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
       hv[j] = c < cprH ? v : make_uint4(0, 0, 0, 0);
     }
 
-    // ---- the sums of the gates, summed over the chunks of a row: y of the gate this lane belongs to (GRU candidate: its
-    // h side in yh, its x side in y)
-    float y[U], yh[U];
+    float ph[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const float ph = dots(1, u, hv, bt);
-      if constexpr (EPI == kEpiGru) {
-        y[u] = group_sum(gate == 2 ? px[u] : px[u] + ph, lg);
-        yh[u] = group_sum(ph, lg);
-      } else if constexpr (JOINT) {
-        y[u] = group_sum(px[u] + ph, lg);
-      } else {
-        y[u] = px[u] + group_sum(ph, lg);
-      }
-    }
-    const int first = lane & ~(4 * Gl - 1);
-    auto of_gate = [&](const float (&v)[U], int r) {
-      float s = __shfl(v[0], first + r * Gl, kWave);
-#pragma unroll
-      for (int u = 1; u < U; ++u) {
-        const float o = __shfl(v[u], first + r * Gl, kWave);
-        s = mine == u ? o : s;
-      }
-      return s;
-    };
-    if constexpr (EPI == kEpiLstm) {
-      const float gi = sigmoidf_dev(of_gate(y, 0) + b0[0]);
-      const float gf = sigmoidf_dev(of_gate(y, 1) + b0[1]);
-      const float go = sigmoidf_dev(of_gate(y, 2) + b0[2]);
-      const float gg = tanhf_dev(of_gate(y, 3) + b0[3]);
-      cst = fmaf(gf, cst, gi * gg);
-      hlast = go * tanhf_dev(cst);
-    } else {
-      const float r = sigmoidf_dev(of_gate(y, 0) + b0[0] + b1[0]);
-      const float z = sigmoidf_dev(of_gate(y, 1) + b0[1] + b1[1]);
-      const float nn = tanhf_dev(fmaf(r, of_gate(yh, 2) + b1[2], of_gate(y, 2) + b0[2]));
-      hlast = fmaf(z, hlast - nn, nn);
-    }
+    for (int u = 0; u < U; ++u) ph[u] = unit_dot(q, 1, u, hv, bt);
+    unit_cell<EPI, U, JOINT, NG>(l, px, ph, b0, b1, hlast, cst);
     if (cell) {
       if (t + 1 < a.steps)
         __hip_atomic_store(a.hbuf + (t & 1) * H + unit,
