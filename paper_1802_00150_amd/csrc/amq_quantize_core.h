@@ -544,7 +544,24 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
   const unsigned long long lane_inside = MASKED == NJ ? ~0ull : lanes_inside(n, base + lane_id());
 
   int u[NJ];                     // order-preserving integer of |w| with the tie rule folded in
-  double wd[NJ];                 // w
+  // w: as the binary64 value that the additions take, or (where registers are what limits the waves) as the binary32 value,
+  // converted at every use
+  constexpr bool kNarrow = NJ > 16 || (K == 2 && NW > 1);
+  using Held = typename std::conditional<kNarrow, float, double>::type;
+  Held held[NJ];
+  auto wide = [&](int j) {
+    if constexpr (kNarrow) return (double)opaque_v(held[j]);
+    else return held[j];
+  };
+  auto narrow = [&](int j) {
+    Held w0 = held[j];
+    asm volatile("" : "+v"(w0));  // (otherwise what is formed from it here and earlier is kept in registers from the start)
+    return (float)w0;
+  };
+  auto sign_bits = [&](int j) {
+    if constexpr (kNarrow) return __float_as_int(held[j]);
+    else return __double2hiint(held[j]);
+  };
   float r[NJ];                   // greedy residual
   unsigned long long neg[NJ <= kSignMaskSlots ? NJ : 1];  // w < 0
   unsigned long long lane_neg = 0ull;                     // the same, slot j in lane j
@@ -557,12 +574,12 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
     // b, or bits(|w|) - 1 = b + 0x7fffffff (mod 2^32) for a set sign bit: the smaller of the two in both cases
     u[j] = (int)min(b, b + 0x7fffffffu);
     if (j >= MASKED) u[j] = j * 64 < within ? u[j] : -1;
-    wd[j] = (double)xc;
+    held[j] = (Held)xc;
     const unsigned long long ng = __ballot(xc < 0.0f);
     if constexpr (NJ <= kSignMaskSlots) neg[j] = ng;
     keep_in_lane(lane_neg, ng, j);
     r[j] = xc;
-    sum[0] = (j == 0) ? fabs(wd[j]) : sum[0] + fabs(wd[j]);
+    sum[0] = (j == 0) ? fabs(wide(j)) : sum[0] + fabs(wide(j));
     if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
   }
   AMQ_PHASE(marks, 12);
@@ -609,14 +626,14 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
         } else {
           const unsigned long long ng = __ballot(rn < 0.0f);
           if constexpr (NJ <= kSignMaskSlots) f[0] = ~(ng ^ neg[j]);
-          else f[0] = __ballot((__float_as_int(rn) ^ __double2hiint(wd[j])) >= 0);
+          else f[0] = __ballot((__float_as_int(rn) ^ sign_bits(j)) >= 0);
           // pairs (i - 1, i) of planes beyond the first: both signs are at hand
           add_count<NJ>(cnt[K == 3 ? 2 : (i == 2 ? 3 : 5)], (before ^ ng) & in);
           if (K == 4 && i == 3) add_count<NJ>(cnt[4], (__ballot(u[j] >= a0bits) ^ f[0]) & in);
         }
         if (i > 1) f[0] &= in;
         add_count<NJ>(cnt[i - 1], f[0]);
-        masked_add<1>(si, wd[j], f);
+        masked_add<1>(si, wide(j), f);
         if (i + 1 < K) {
           const double ra = (double)fabsf(rn);
           sr[0] = (j == 0) ? ra : sr[0] + ra;
@@ -637,9 +654,7 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
       double sr[1] = {0.0};
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        double w0 = wd[j];
-        asm volatile("" : "+v"(w0));  // (otherwise the binary32 value is kept in registers from the start for this)
-        float rj = (float)w0;
+        float rj = narrow(j);
 #pragma unroll
         for (int i = 0; i + 1 < K; ++i) rj = rj - copysignf(alpha[i], rj);
         if (j >= MASKED) rj = u[j] >= 0 ? rj : 0.0f;
@@ -655,9 +670,7 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
       for (int i = 0; i < K; ++i) mym[i] = 0ull;
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        double w0 = wd[j];
-        asm volatile("" : "+v"(w0));  // (otherwise the binary32 value is kept in registers from the start for this)
-        float rj = (float)w0;
+        float rj = narrow(j);
         float v = 0.0f;
 #pragma unroll
         for (int i = 0; i < K; ++i) {
@@ -703,7 +716,7 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
           ge[t] = __ballot(u[j] >= ct.thr[t]);
           add_count<NJ>(cn[t], ge[t]);
         }
-        masked_add<NT>(c, wd[j], ge);
+        masked_add<NT>(c, wide(j), ge);
         if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
       }
       AMQ_PHASE(marks, 7 + 4 * it);
@@ -740,7 +753,7 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
         float v = __int_as_float(ct.val[0]);
 #pragma unroll
         for (int t = 0; t < NT; ++t) v = u[j] >= ct.thr[t] ? __int_as_float(ct.val[t + 1]) : v;
-        recon[j] = __double2hiint(wd[j]) < 0 ? 0.0f - v : v;
+        recon[j] = sign_bits(j) < 0 ? 0.0f - v : v;
         if (NJ > 4 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
       }
       return;
@@ -1184,9 +1197,11 @@ __device__ __forceinline__ void quantize_core(const float (&x)[NJ], int n, int b
   } else if (full) {
     quantize_magnitudes<K, NJ, NW, NJ, RECON>(x, n, base, nj, T, alpha, mym, sh, phase, marks, recon);
   } else {
-    // a single wave usually takes the form of its own number of slots, an even one: only the last two can be short
-    if (NW == 1 && (NJ - 2) * 64 < n)
-      quantize_magnitudes<K, NJ, NW, NW == 1 ? NJ - 2 : 0, RECON>(x, n, base, nj, T, alpha, mym, sh, phase, marks, recon);
+    // a single wave usually takes the form of its own number of slots, one of the even ones (beyond 16 every fourth): only
+    // the last two (four) can be short
+    constexpr int kLast = NJ > 16 ? 4 : 2;
+    if (NW == 1 && (NJ - kLast) * 64 < n)
+      quantize_magnitudes<K, NJ, NW, NW == 1 ? NJ - kLast : 0, RECON>(x, n, base, nj, T, alpha, mym, sh, phase, marks, recon);
     else
       quantize_magnitudes<K, NJ, NW, 0, RECON>(x, n, base, nj, T, alpha, mym, sh, phase, marks, recon);
   }

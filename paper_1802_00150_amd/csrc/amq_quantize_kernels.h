@@ -9,11 +9,10 @@ namespace amq {
 namespace {
 
 // The second launch bound is the waves per SIMD that the registers shall allow.
-template <int K>
-constexpr int kQuantWaves = K == 4 ? 3 : 4;
+constexpr int quant_waves(int k, int nj) { return k == 4 && nj > 16 ? 2 : k == 4 || nj > 24 ? 3 : 4; }
 
 template <int K, int NJ, int NW, bool ONLINE, bool RECON>
-__global__ __launch_bounds__(64 * NW, NW < 16 ? kQuantWaves<K> : 4)
+__global__ __launch_bounds__(64 * NW, NW < 16 ? quant_waves(K, NJ) : 4)
 void quantize_kernel(QuantArgs a) {
   __shared__ double sh[2 * kExchange<NW>];
   asm volatile("" ::AMQ_ARG(a.seg[0].X), AMQ_ARG(a.seg[0].ld), AMQ_ARG(a.seg[0].n), AMQ_ARG(a.seg[0].count),
@@ -29,10 +28,44 @@ void launch_one(QuantArgs a, int total, hipStream_t s) {
   hipLaunchKernelGGL((quantize_kernel<K, NJ, NW, ONLINE, RECON>), dim3(total), dim3(64 * NW), 0, s, a);
 }
 
-// Waves per vector.  Many vectors (throughput): as few waves as hold the vector with at most 16 slots per lane --
-// what a wave does once per vector (reductions, solves, code tables) is then paid by few waves, and 16 slots keep
-// the registers at about 100; then the smallest register form that holds the share.  Few vectors (the on-line case,
-// latency): at most 4 slots per lane over at least 4 waves, and the form of the algorithm made for that.
+// Wide forms: 20 to 32 slots per lane, vectors of 1025 .. 2048 entries on one wave and up to 4096 on two.  What a wave does once
+// per vector (reductions, solves, code tables) takes as long as 20 slots' work at k = 2, 30 to 50 beyond, so half the waves
+// per vector win over the registers that the slots take (three or two waves per SIMD) -- given enough vectors to fill the
+// chip.  Measured, us, 16384 vectors, 16 slots / here: k = 2 of 1100 / 1500 / 2048 / 3000 / 4096 entries 29.7 / 31.3 / 34.0 /
+// 56.6 / 67.2 -> 22.6 / 25.2 / 27.7 / 51.6 / 65.6, k = 3 59.4 / 62.3 / 65.1 / 116 / 126 -> 40.5 / 45.3 / 55.0 / 96.8 / 121,
+// k = 4 131 / 139 / 148 / 267 / 290 -> 83.6 / 93.2 / 129 / 208 / 284; reconstruction k = 3 54.5 / 62.2 / 66.4 / 120 / 132 ->
+// 41.5 / 47.3 / 60.2 / 104 / 115.  Number of vectors from which on they are ahead:
+constexpr int wide_rows(int k, bool recon, int nw, int nj) {
+  if (recon && k == 2 && nj > (nw == 1 ? 24 : 20)) return 1 << 30;  // (bound by its stores: 16384 x 1700 36.1 against 37.1)
+  if (nw == 2 && nj > 24)  // (4096 entries, k = 2: 8192 vectors 33.6 against 33.8, 4096 19.2 against 20.0)
+    return recon ? 4096 : k == 3 ? 8192 : 12288;
+  return 1536;             // (1100 vectors of 1700 entries, k = 3: 9.6 against 10.4; 2000 11.2 against 10.5)
+}
+
+template <int K, bool RECON>
+bool launch_wide(const QuantArgs& a, int total, int nw, int nj, hipStream_t s) {
+  constexpr bool kAll = !(RECON && K == 2);
+  switch (nw * 64 + (nj + 3) / 4 * 4) {
+    case 64 + 20: launch_one<K, 20, 1, false, RECON>(a, total, s); return true;
+    case 64 + 24: launch_one<K, 24, 1, false, RECON>(a, total, s); return true;
+    case 128 + 20: launch_one<K, 20, 2, false, RECON>(a, total, s); return true;
+  }
+  if constexpr (kAll) {
+    switch (nw * 64 + (nj + 3) / 4 * 4) {
+      case 64 + 28: launch_one<K, 28, 1, false, RECON>(a, total, s); return true;
+      case 64 + 32: launch_one<K, 32, 1, false, RECON>(a, total, s); return true;
+      case 128 + 24: launch_one<K, 24, 2, false, RECON>(a, total, s); return true;
+      case 128 + 28: launch_one<K, 28, 2, false, RECON>(a, total, s); return true;
+      case 128 + 32: launch_one<K, 32, 2, false, RECON>(a, total, s); return true;
+    }
+  }
+  return false;
+}
+
+// Waves per vector.  Many vectors (throughput): the wide forms above where they are ahead, otherwise as few waves as hold
+// the vector with at most 16 slots per lane, which keep the registers at about 100; then the smallest register form that
+// holds the share.  Few vectors (the on-line case, latency): at most 4 slots per lane over at least 4 waves, and the form of
+// the algorithm made for that.
 template <int K, bool RECON>
 hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
   const int nvec = a.seg[0].count + a.seg[1].count;
@@ -46,6 +79,11 @@ hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
     else if (nslots <= 32) launch_one<K, 4, 8, true, RECON>(a, total, s);
     else launch_one<K, 4, 16, true, RECON>(a, total, s);
     return hipGetLastError();
+  }
+  if constexpr (K >= 2) {
+    const int nw = nslots <= 32 ? 1 : 2, nj = (nslots + nw - 1) / nw;
+    if (nslots > 16 && nslots <= 64 && nvec >= wide_rows(K, RECON, nw, nj) && launch_wide<K, RECON>(a, total, nw, nj, s))
+      return hipGetLastError();
   }
   int nw = 1;
   while (nw < 16 && (nslots + nw - 1) / nw > 16) nw *= 2;
