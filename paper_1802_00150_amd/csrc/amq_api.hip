@@ -556,6 +556,8 @@ static int lstm_fused_launch(const uint32_t* Wxp, const float* alpha_x, const ui
                              float* hs_out, hipStream_t s) {
   const amq::BmvArgs b = lstm_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias, Xp, beta_x, Hp, beta_h, c_prev, B, h_out,
                                    c_out, hs_out);
+  if (amq::mfma32_cell_supported(b, k_w, k_a, amq::kEpiLstm))
+    return hip_status(amq::launch_mfma32_cell(b, k_w, k_a, amq::kEpiLstm, s));
   if (amq::mfma4_pair_supported(b, k_w, k_a, amq::kEpiLstm))
     return hip_status(amq::launch_mfma4_pair(b, k_w, k_a, amq::kEpiLstm, s));
   if (amq::bmv_supported((int)I, (int)H, k_a, B, amq::kEpiLstm))
@@ -861,6 +863,8 @@ static int gru_step_launch(const uint32_t* Wxp, const float* alpha_x, const uint
   if (st != AMQ_OK) return st;
   const amq::BmvArgs b = gru_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, w.xp, w.beta_x, w.hp, w.beta_h,
                                   h_prev, B, h_out);
+  if (amq::mfma32_cell_supported(b, k_w, k_a, amq::kEpiGru))
+    return hip_status(amq::launch_mfma32_cell(b, k_w, k_a, amq::kEpiGru, s));
   if (amq::mfma4_pair_supported(b, k_w, k_a, amq::kEpiGru))
     return hip_status(amq::launch_mfma4_pair(b, k_w, k_a, amq::kEpiGru, s));
   if (amq::bmv_supported((int)I, (int)H, k_a, B, amq::kEpiGru))

@@ -227,6 +227,10 @@ hipError_t launch_mfma4_pair(const BmvArgs& a, int k_w, int k_a, int epi, hipStr
 bool mfma4w_cell_supported(const BmvArgs& a, int k_w, int k_a, int epi);
 hipError_t launch_mfma4w_cell(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s);
 
+// the recurrent steps of large batches on the 32 x 32 form of the instruction
+bool mfma32_cell_supported(const BmvArgs& a, int k_w, int k_a, int epi);
+hipError_t launch_mfma32_cell(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s);
+
 // ---- output layer -----------------------------------------------------------------------
 // out[b][v] = Y[b][v] - log(sum_u exp(Y[b][u])); out may alias Y.
 hipError_t launch_log_softmax(const float* Y, long long B, long long V, float* out, hipStream_t s);
