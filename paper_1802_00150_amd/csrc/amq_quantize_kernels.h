@@ -64,8 +64,17 @@ bool launch_wide(const QuantArgs& a, int total, int nw, int nj, hipStream_t s) {
 
 // Waves per vector.  Many vectors (throughput): the wide forms above where they are ahead, otherwise as few waves as hold
 // the vector with at most 16 slots per lane, which keep the registers at about 100; then the smallest register form that
-// holds the share.  Few vectors (the on-line case, latency): at most 4 slots per lane over at least 4 waves, and the form of
-// the algorithm made for that.
+// holds the share.  Few vectors (the on-line case, latency): at most 4 slots per lane over 4 or 8 waves, and the form of
+// the algorithm made for that.  It buys its short chain with every wave of a vector solving the same small systems, so it
+// ends where those waves no longer fit the chip side by side: about two vectors per compute unit, three at k = 3.  Beyond
+// 2048 entries it would take 16 waves per vector, whose exchange costs more than the slots that they save, already at one
+// vector.  Both give the same codes and coefficients, to the bit.  Measured, us, latency / throughput form, 512 and 700
+// vectors: 300 entries k = 2 3.48 / 3.06 (reconstruction) and 3.97 / 3.11, k = 4 7.97 / 6.06 and 10.3 / 6.1; 650 entries k = 2
+// 3.64 / 3.67 and 4.17 / 3.78, k = 3 at 700 5.18 / 5.38 and at 1000 6.03 / 5.42, k = 4 8.67 / 9.26 and 10.9 / 9.3; 2048 entries
+// k = 2 4.71 / 4.82 and 5.76 / 4.88.  4096 entries, 1 and 512 vectors: k = 2 4.37 / 3.92 and 8.05 / 4.98, k = 3 6.17 / 5.94 and
+// 11.6 / 7.6, k = 4 13.2 / 10.1, reconstruction k = 3 6.46 / 5.95 and 12.8 / 8.4.
+constexpr int online_vectors(int k, bool recon) { return k == 3 && !recon ? 768 : 600; }
+
 template <int K, bool RECON>
 hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
   const int nvec = a.seg[0].count + a.seg[1].count;
@@ -73,11 +82,10 @@ hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
   if (total == 0) return hipSuccess;
   const int nslots = nvec ? 2 * ((max_n + 127) / 128) : 1;
   if (nslots > 256) return hipErrorInvalidValue;
-  if (nvec < 1024 && nslots <= 64) {
+  if (nslots <= 32 && nvec < online_vectors(K, RECON)) {
     if (nslots <= 2) launch_one<K, 2, 1, true, RECON>(a, total, s);
     else if (nslots <= 16) launch_one<K, 4, 4, true, RECON>(a, total, s);
-    else if (nslots <= 32) launch_one<K, 4, 8, true, RECON>(a, total, s);
-    else launch_one<K, 4, 16, true, RECON>(a, total, s);
+    else launch_one<K, 4, 8, true, RECON>(a, total, s);
     return hipGetLastError();
   }
   if constexpr (K >= 2) {
