@@ -420,11 +420,12 @@ static amq::BmvArgs lstm_args(const uint32_t* Wxp, const float* alpha_x, const u
 // computing them again.
 static bool single_marks(int64_t I, int64_t H, int epi) { return epi == amq::kEpiLstm && I <= 1024 && H <= 1024; }
 
-// Whether a sequence takes the resident kernel: a shape it has room for, and a stream that is not being captured (its
+// Whether a sequence takes the resident kernels: a shape (and number of steps) for one of them, and a stream that is not being captured (its
 // launches wait for room among others of the kind and have to be queued together, which a graph does not promise).
-static bool resident_sequence(const ResidentWs& w, int64_t I, int64_t H, int64_t B, int k_w, int k_a, int epi,
+static bool resident_sequence(const ResidentWs& w, int64_t I, int64_t H, int64_t B, int k_w, int k_a, int epi, int64_t steps,
                               hipStream_t s) {
-  if (!w.total || !amq::seqw_supported(I, H, B, k_w, k_a, epi)) return false;
+  const int64_t piece = steps < piece_steps(B) ? steps : piece_steps(B);
+  if (!w.total || !amq::seqw_supported(I, H, B, k_w, k_a, epi, piece)) return false;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   return hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
 }
@@ -754,7 +755,7 @@ int amq_lstm_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t*
     const SeqWs sw = carve_seq(workspace, I, H, B, k_a);
     const amq::BmvArgs probe = lstm_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias, sw.xq[0], sw.xbeta[0], w.hp, w.beta_h,
                                          c, B, h, c, nullptr);
-    if (workspace_bytes >= sw.total && resident_sequence(sw.resident, I, H, B, k_w, k_a, amq::kEpiLstm, s))
+    if (workspace_bytes >= sw.total && resident_sequence(sw.resident, I, H, B, k_w, k_a, amq::kEpiLstm, steps, s))
       return resident_run(sw.resident, probe, xs, steps, k_w, k_a, amq::kEpiLstm, T, h, c, hs, s);
     if (workspace_bytes >= sw.total && amq::step_split_supported(probe, k_w, k_a, amq::kEpiLstm)) {
       auto step_args = [&](int64_t t) {
@@ -913,7 +914,7 @@ int amq_gru_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t* 
                                       w.beta_h, h, B, h);
   if (workspace_bytes >= sw.total && single_sequence(I, H, B, k_w, k_a, s))
     return single_run(probe, sw.single, xs, steps, k_w, k_a, amq::kEpiGru, T, h, nullptr, hs, s);
-  if (workspace_bytes >= sw.total && resident_sequence(sw.resident, I, H, B, k_w, k_a, amq::kEpiGru, s))
+  if (workspace_bytes >= sw.total && resident_sequence(sw.resident, I, H, B, k_w, k_a, amq::kEpiGru, steps, s))
     return resident_run(sw.resident, probe, xs, steps, k_w, k_a, amq::kEpiGru, T, h, nullptr, hs, s);
   if (workspace_bytes >= sw.total && amq::step_split_supported(probe, k_w, k_a, amq::kEpiGru)) {
     // As in amq_lstm_sequence: the inputs are given, so W_x x_t leaves the recurrent chain.  Front launch of
@@ -1516,7 +1517,7 @@ static int lm_sequence_impl(const uint32_t* Ep, const float* alpha_e, int64_t vo
     return hip_status(amq::launch_step_back(b, k_w, k_a, amq::kEpiLstm, s));
   };
   const int64_t piece = lm_piece_steps(B);
-  const bool resident = resident_sequence(lw.resident, E, H, B, k_w, k_a, amq::kEpiLstm, s);
+  const bool resident = resident_sequence(lw.resident, E, H, B, k_w, k_a, amq::kEpiLstm, steps, s);
   for (int64_t t0 = 0; t0 < steps; t0 += piece) {
     const int64_t n = steps - t0 < piece ? steps - t0 : piece;
     if (resident) {

@@ -356,8 +356,13 @@ struct SeqWScratch {
   size_t pair_bytes, bytes;  // bytes: size of the whole region (256-byte aligned base)
 };
 SeqWScratch seqw_scratch(void* base, long long H, long long B, int k_a);
-bool seqw_supported(long long I, long long H, long long B, int k_w, int k_a, int epi);
+bool seqw_supported(long long I, long long H, long long B, int k_w, int k_a, int epi, long long steps);  // steps: of a launch
 hipError_t launch_seqw(SeqWArgs a, const SeqWScratch& w, int k_w, int k_a, int epi, hipStream_t s);
+
+// Where the chip has no workgroup for every tile of the batch: groups of tiles take turns (amq_seqw_tiles.hip).  The number of
+// workgroups of such a launch (0: not taken), and the launch itself, between those of launch_seqw.
+long long seqw_tiles_grid(long long I, long long H, long long B, int k_w, int k_a, int epi);
+hipError_t launch_seqw_tiles(const SeqWArgs& a, int k_w, int k_a, int epi, hipStream_t s);
 
 // What follows such a launch, on its own (flag, saved state and input codes in a): if the flag is set, the piece is
 // computed again from the saved state (batch 1: and the flag cleared).

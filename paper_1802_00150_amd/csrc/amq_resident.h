@@ -7,7 +7,7 @@
 //
 // What is counted: shares of 32 workgroups -- workgroups go to the 8 dies in turn and, on a die, to its 4 shader engines,
 // so a share is at most one workgroup per engine (8 compute units) and the sums hold for every engine, not only for the
-// chip.  A full claim (amq_seqw.hip: two waves per SIMD, most of its registers) counts on a compute unit of its own per
+// chip.  A full claim (amq_seqw.hip, amq_seqw_tiles.hip: two waves per SIMD, most of its registers) counts on a compute unit of its own per
 // workgroup; of a light one (amq_lstm_seqg.hip: one wave per SIMD, up to 144 of its 512 registers) a unit holds three, as
 // long as no full claim is about.  Any placement of the workgroups then leaves room for those still to come.
 //

@@ -28,144 +28,11 @@
 #include <atomic>
 #include <mutex>
 
-#include "amq_launch.h"
-#include "amq_quantize_body.h"
+#include "amq_seqw_body.h"
 
 namespace amq {
 
 namespace {
-
-constexpr int kWBlocks = 4;             // row blocks per workgroup
-constexpr int kWWaves = 2 * kWBlocks;   // waves per workgroup: one per row block and operand block
-constexpr int kBlocksPad = kWBlocks + 1;
-constexpr int kWTurn = 9;       // 16-byte units per row in the LDS piece that turns rows into operands (128 B + 16 B pad)
-
-// Pairs that the codes and coefficients of one batch entry take in the exchange buffer: whole cache lines of 16.
-__host__ __device__ constexpr int seqw_entry_pairs(int k_a, int wpr) { return (k_a * (wpr + 1) + 15) & ~15; }
-
-__device__ __forceinline__ void put_pair(unsigned long long* p, unsigned value, unsigned tag) {
-  __hip_atomic_store(p, ((unsigned long long)tag << 32) | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long get_pair(const unsigned long long* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// One failed poll: counts it, and decides whether to give up (too many, or somebody else has).
-__device__ __forceinline__ bool poll_again(unsigned& spins, unsigned limit, unsigned* flag) {
-  ++spins;
-  if (spins > limit) {
-    __hip_atomic_store(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return false;
-  }
-  return (spins & 63u) != 0 || __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
-}
-
-// Products of one wave's row block (16 rows) with one batch tile: packed weights in operand layout, activations as the
-// expanded image in LDS (see amq_pair_body.h for both layouts).  The accumulators start at minus the contribution of
-// the positions past the end of the vectors, so they end as the dot products of the codes.
-template <int KW, int KA, int NC>
-__device__ __forceinline__ void contract(const uint4 (&araw)[NC][KW][2], const uint4* image, int l16, int l4, int n,
-                                         v4f (&acc)[KW][KA]) {
-  constexpr int kAllSteps = NC * kSteps;
-  const int halves = (n + 511) >> 9;
-  const float start = (float)(n - halves * 512);
-#pragma unroll
-  for (int i = 0; i < KW; ++i)
-#pragma unroll
-    for (int j = 0; j < KA; ++j) acc[i][j] = v4f{start, start, start, start};
-  const uint4* const my = image + 16 * l4;
-  auto b_operand = [&](int j, int t) { return my[(j * kAllSteps + t) * 64 + (l16 ^ ((l4 << 1) | (((t >> 2) & 1) << 3)))]; };
-  uint4 aop[KW], anx[KW], bop[KA], bnx[KA];
-#pragma unroll
-  for (int j = 0; j < KA; ++j) bop[j] = b_operand(j, 0);
-#pragma unroll
-  for (int i = 0; i < KW; ++i) aop[i] = expand4_signed(word_of(araw[0][i], 0));
-#pragma unroll
-  for (int half = 0; half < 2 * NC; ++half) {
-    if (half > 0 && half >= halves) break;  // (uniform)
-#pragma unroll
-    for (int t = 4 * half; t < 4 * half + 4; ++t) {
-      if (t + 1 < kAllSteps) {
-#pragma unroll
-        for (int j = 0; j < KA; ++j) bnx[j] = b_operand(j, t + 1);
-#pragma unroll
-        for (int i = 0; i < KW; ++i) anx[i] = expand4_signed(word_of(araw[(t + 1) / kSteps][i], (t + 1) % kSteps));
-      }
-#pragma unroll
-      for (int i = 0; i < KW; ++i)
-#pragma unroll
-        for (int j = 0; j < KA; ++j) acc[i][j] = mfma_fp4(aop[i], bop[j], acc[i][j]);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < KW; ++i) aop[i] = anx[i];
-#pragma unroll
-      for (int j = 0; j < KA; ++j) bop[j] = bnx[j];
-    }
-  }
-  settle_accumulators<16>();
-#pragma unroll
-  for (int i = 0; i < KW; ++i)
-#pragma unroll
-    for (int j = 0; j < KA; ++j) asm volatile("" : "+v"(acc[i][j]));
-}
-
-// Keeps the compiler from expanding these words once, ahead of the loop over the steps, and holding the result.
-template <int NC, int KW>
-__device__ __forceinline__ void keep_packed(uint4 (&w)[NC][KW][2]) {
-#pragma unroll
-  for (int ch = 0; ch < NC; ++ch)
-#pragma unroll
-    for (int i = 0; i < KW; ++i)
-#pragma unroll
-      for (int v = 0; v < 2; ++v) asm volatile("" : "+v"(w[ch][i][v].x), "+v"(w[ch][i][v].y), "+v"(w[ch][i][v].z), "+v"(w[ch][i][v].w));
-}
-
-// y_r = sum_i alpha_ri sum_j beta_j d_ij of this lane's four rows (the gates of its hidden unit) and batch entry.
-template <int KW, int KA>
-__device__ __forceinline__ void weigh(const v4f (&acc)[KW][KA], const float (&al)[4][KW], const float (&bt)[KA],
-                                      float (&y)[4]) {
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    float s = 0.0f;
-#pragma unroll
-    for (int i = 0; i < KW; ++i) {
-      float inner = 0.0f;
-#pragma unroll
-      for (int j = 0; j < KA; ++j) inner = fmaf(bt[j], acc[i][j][r], inner);
-      s = fmaf(al[r][i], inner, s);
-    }
-    y[r] = s;
-  }
-}
-
-// Eq. 6 on one unit's sums; bias0 / bias1 as the per-step kernels take them.  h: h_{t-1} in, h_t out.
-template <int EPI>
-__device__ __forceinline__ void cell(const float (&yx)[4], const float (&yh)[4], const float (&b0)[4], const float (&b1)[4],
-                                     float& h, float& c) {
-  if constexpr (EPI == kEpiLstm) {
-    const float gi = sigmoidf_dev(yx[0] + yh[0] + b0[0]);
-    const float gf = sigmoidf_dev(yx[1] + yh[1] + b0[1]);
-    const float go = sigmoidf_dev(yx[2] + yh[2] + b0[2]);
-    const float gg = tanhf_dev(yx[3] + yh[3] + b0[3]);
-    c = fmaf(gf, c, gi * gg);
-    h = go * tanhf_dev(c);
-  } else {
-    const float rg = sigmoidf_dev(yx[0] + yh[0] + b0[0] + b1[0]);
-    const float z = sigmoidf_dev(yx[1] + yh[1] + b0[1] + b1[1]);
-    const float nn = tanhf_dev(fmaf(rg, yh[2] + b1[2], yx[2] + b0[2]));
-    h = fmaf(z, h - nn, nn);
-  }
-}
-
-// Whether the weights stay in registers as matrix operands (32 registers per plane and stretch) or packed: as far as the
-// registers go.
-template <int KW, int KA, int NC>
-constexpr bool kExpandedOnce = NC == 1 && KW * KA < 9;
-
-template <int KW, int KA, int NC>
-constexpr size_t seqw_lds() {
-  return sizeof(uint4) * (2 * KA * NC * kSteps * 64);
-}
 
 // NC: stretches of 1024 entries of the longer operand block (1 or 2).  Waves 0 .. 3 take the h side, the cell and the
 // quantizer, waves 4 .. 7 the x side of the next step.
@@ -688,10 +555,18 @@ SeqWScratch seqw_scratch(void* base, long long H, long long B, int k_a) {
   return w;
 }
 
-bool seqw_supported(long long I, long long H, long long B, int k_w, int k_a, int epi) {
+// Steps from which on the tiles of a batch take turns rather than launches each step: the launch costs about 20 us before its first
+// step (claim, cleared pairs, weights, what follows it) that the per-step form has not, and saves 1.5 to 6 us per step.  us, per-step
+// form / here, W2/A2: 1024 units batch 80 4 steps 38.2 / 41.8, 6 steps 54.3 / 54.7, 8 steps 71.2 / 67.5; 1500 units batch 64 48.1 / 51.2,
+// 68.5 / 69.1, 88.6 / 86.3; 512 units batch 200 36.3 / 38.5, 53.6 / 49.6, 70.1 / 60.9; 1024 batch 80 W3/A3 46.6 / 52.1, 67.4 / 69.7,
+// 88.2 / 88.9 and 12 steps 130 / 124.
+constexpr long long kTiledSteps = 8;
+
+bool seqw_supported(long long I, long long H, long long B, int k_w, int k_a, int epi, long long steps) {
   if (B < 2 || I <= 0 || H <= 0 || I > 2048 || H > 2048 || k_w < 1 || k_w > 3 || k_a < 1 || k_a > 3) return false;
   if (B > 16 * 256) return false;
-  return run(nullptr, I, H, B, k_w, k_a, epi, nullptr) == hipSuccess;
+  return run(nullptr, I, H, B, k_w, k_a, epi, nullptr) == hipSuccess ||
+         (steps >= kTiledSteps && seqw_tiles_grid(I, H, B, k_w, k_a, epi) > 0);
 }
 
 hipError_t launch_seqw(SeqWArgs a, const SeqWScratch& w, int k_w, int k_a, int epi, hipStream_t s) {
@@ -703,13 +578,15 @@ hipError_t launch_seqw(SeqWArgs a, const SeqWScratch& w, int k_w, int k_a, int e
   a.limit = sequence_spin_limit();
   const unsigned pairs = (unsigned)(w.pair_bytes / sizeof(unsigned long long));
   const unsigned blocks = (pairs + 2047) / 2048;
+  const bool one = run(nullptr, a.x.n, a.H, a.batch, k_w, k_a, epi, nullptr) == hipSuccess;  // a workgroup per tile fits
   const dim3 grid = seqw_grid(a.H, a.batch);
-  const ResidentClaim claim = resident_claim((long long)grid.x * grid.y, false);
+  const ResidentClaim claim =
+      resident_claim(one ? (long long)grid.x * grid.y : seqw_tiles_grid(a.x.n, a.H, a.batch, k_w, k_a, epi), false);
   std::lock_guard<std::mutex> together(resident_launches());
   hipLaunchKernelGGL(seqw_reset_kernel, dim3(blocks < 512 ? blocks : 512), dim3(256), 0, s, w.flag, claim, w.hbuf, pairs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const hipError_t ran = run(&a, a.x.n, a.H, a.batch, k_w, k_a, epi, s);
+  const hipError_t ran = one ? run(&a, a.x.n, a.H, a.batch, k_w, k_a, epi, s) : launch_seqw_tiles(a, k_w, k_a, epi, s);
   e = launch_recover(a, k_w, k_a, epi, claim, s);
   return ran != hipSuccess ? ran : e;
 }

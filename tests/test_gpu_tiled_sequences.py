@@ -1,0 +1,71 @@
+"""GPU: sequences of batches whose tiles take turns on a workgroup (amq_seqw_tiles.hip) against the same entries in batches that have a
+workgroup for every tile, bit for bit; and what follows when a wait gives up."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def amq():
+    import paper_1802_00150_amd as m
+    m.binding.lib()
+    return m
+
+
+def case(amq, gates, I, H, B, k_w, k_a, steps):
+    import torch
+    g = torch.Generator(device="cuda:0").manual_seed(7 * I + 3 * H + B + gates + steps)
+    randn = lambda *s: torch.randn(*s, generator=g, device="cuda:0")  # noqa: E731
+    d = [*amq.quantize_weights(randn(gates * H, I) * 0.05, k_w, 2), *amq.quantize_weights(randn(gates * H, H) * 0.05, k_w, 2)]
+    bias = [randn(gates * H) * 0.1 for _ in range(2)]
+    xs, h0, c0 = randn(steps, B, I), torch.tanh(randn(B, H)), randn(B, H)
+
+    def run(lo, hi, T, hs=True):
+        x, h, c = xs[:, lo:hi].contiguous(), h0[lo:hi].clone(), c0[lo:hi].clone()
+        out = torch.full((steps, hi - lo, H), float("nan"), device=x.device) if hs else None
+        if gates == 4:
+            amq.lstm_sequence(*d, I, H, bias[0], x, h, c, k_a, T, hs=out)
+        else:
+            amq.gru_sequence(*d, I, H, *bias, x, h, k_a, T, hs=out)
+        return [v for v in (out, h, c if gates == 4 else None) if v is not None]
+    return run
+
+
+# groups of 2 to 4 tiles, a last tile of 1 to 16 entries, groups of unequal numbers of tiles (one of a single tile), more entries than
+# workgroups in a group and fewer, one and two stretches of 1024 entries, the fewest steps and several pieces; and shapes and
+# numbers of steps next to those
+@pytest.mark.parametrize("gates,I,H,B,k_w,k_a,steps", [
+    (4, 1024, 1024, 65, 2, 2, 8), (4, 1024, 1024, 128, 3, 3, 9), (3, 1024, 1024, 256, 2, 3, 40), (4, 1000, 1008, 180, 2, 2, 7),
+    (4, 2048, 2048, 33, 3, 2, 8), (4, 2048, 2048, 40, 2, 2, 8), (3, 2047, 2040, 97, 2, 2, 10), (3, 300, 2048, 128, 2, 2, 18),
+    (4, 200, 260, 330, 2, 2, 14), (4, 129, 500, 200, 3, 3, 8), (3, 2048, 520, 161, 3, 2, 9), (4, 1025, 650, 112, 2, 2, 37),
+    (4, 650, 650, 256, 3, 3, 11), (3, 1500, 1500, 48, 2, 2, 8), (4, 650, 1500, 96, 3, 2, 9), (4, 16, 650, 113, 2, 3, 8),
+    (4, 300, 300, 256, 2, 3, 8), (4, 2048, 2048, 129, 2, 2, 8), (3, 800, 800, 512, 2, 2, 9)])
+def test_same_bits_as_batches_that_fit(amq, gates, I, H, B, k_w, k_a, steps):
+    import torch
+    for T in (2, 0):
+        print("tiled", gates, I, H, B, k_w, k_a, steps, T, flush=True)
+        run = case(amq, gates, I, H, B, k_w, k_a, steps)
+        whole = run(0, B, T)
+        again = run(0, B, T, hs=False)
+        assert all(torch.equal(a, b) for a, b in zip(whole[1:], again))
+        for lo in sorted({0, (B // 32) * 16, max(0, B - 20)}):
+            hi = min(B, lo + 20)
+            for w, p in zip(whole, run(lo, hi, T)):
+                w = w[:, lo:hi] if w.dim() == 3 else w[lo:hi]
+                assert bool(torch.isfinite(p).all()) and torch.equal(w, p), (lo, int((w != p).sum()))
+
+
+@pytest.mark.parametrize("gates,H,B", [(4, 1024, 80), (3, 2048, 64)])
+def test_gives_up_and_recovers(amq, gates, H, B):
+    """With a wait that ends at its first failed poll the launch gives up, and the one behind it computes the piece."""
+    import torch
+    run = case(amq, gates, H, H, B, 2, 2, 8)
+    want = run(0, B, 2)
+    amq.binding.debug_set_sequence_spin_limit(1)
+    try:
+        got = run(0, B, 2)
+        torch.cuda.synchronize()
+    finally:
+        amq.binding.debug_set_sequence_spin_limit(0)
+    for w, g in zip(want, got):
+        assert torch.equal(w, g)

@@ -73,3 +73,9 @@ def test_room_for_waiting_kernels_beside_single_sequences(registers):
     # one workgroup of 4 waves per compute unit: a wave on every SIMD
     for name, r in of(registers, "11seq1_kernel", 104).items():
         assert r + WAITERS * 8 <= SIMD_REGISTERS, (name, r)
+
+
+def test_room_for_waiting_kernels_beside_tiled_sequences(registers):
+    # one workgroup of 8 waves per compute unit, as amq_seqw.hip
+    for name, r in of(registers, "17seqw_tiles_kernel", 12).items():
+        assert 2 * r + WAITERS * 8 <= SIMD_REGISTERS, (name, r)
