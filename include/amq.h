@@ -212,7 +212,8 @@ int amq_stream_read_probe(const void* buf, size_t bytes, void* sink, void* strea
 size_t amq_lstm_sequence_flag_offset(int64_t I, int64_t H, int64_t B, int k_a);
 /*
  * Workspace of the faster forms of amq_lstm_sequence (B = 1 needs no more than amq_lstm_workspace_bytes).  Where the grid fits the chip (vectors of at most
- * 2048 entries, 1- to 3-bit codes, about 4096 hidden units times batch tiles of 16), pieces of about 4096 / B steps
+ * 2048 entries, 1- to 3-bit codes, about 4096 hidden units times batch tiles of 16) or, from 8 steps on, two to four tiles
+ * can take turns on a workgroup (2- and 3-bit codes; how far, is measured: amq_seqw_tiles.hip), pieces of about 4096 / B steps
  * run in one launch whose workgroups stay resident and exchange h_t and its codes through the workspace.  Such
  * launches (and those of batch 1) share a device: on several streams they run side by side as far as their workgroups
  * fit, and wait their turn where they do not; if the workgroups cannot all become resident a launch that follows
@@ -278,7 +279,7 @@ int amq_gru_step(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp,
  * h [B][H] is read as the initial state and overwritten with the final one; hs (nullable)
  * [steps][B][H] receives every h_t.  Same arithmetic as `steps` calls of amq_gru_step, bit for bit.  Where
  * the workspace has amq_gru_sequence_workspace_bytes, the same forms as in amq_lstm_sequence: one launch for
- * a piece of the sequence where its grid fits the chip (at B = 1, should a wait give up, a launch that follows
+ * a piece of the sequence where its grid fits the chip or its tiles can take turns (at B = 1, should a wait give up, a launch that follows
  * computes the piece on its own), for B > 1 two launches per step where it does not (vectors of at most 2048
  * entries, codes of at most 3 bits, at most 2048 row-block x tile tasks); otherwise, and with a workspace of
  * only amq_gru_workspace_bytes, the steps are launched one by one.
