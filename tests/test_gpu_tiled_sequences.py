@@ -69,3 +69,26 @@ def test_gives_up_and_recovers(amq, gates, H, B):
         amq.binding.debug_set_sequence_spin_limit(0)
     for w, g in zip(want, got):
         assert torch.equal(w, g)
+
+
+def test_side_by_side_on_streams(amq):
+    """Launches that want the whole chip, from several streams, with smaller ones between: each waits for its room."""
+    import time
+
+    import torch
+    shapes = [(4, 1024, 1024, 128, 2, 2, 16), (3, 650, 650, 192, 2, 3, 16), (4, 300, 300, 16, 2, 2, 16), (4, 2048, 2048, 64, 2, 2, 16)]
+    runs = [case(amq, *s) for s in shapes]
+    want = [r(0, s[3], 2) for r, s in zip(runs, shapes)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in shapes]
+    start = time.perf_counter()
+    got = [[] for _ in shapes]
+    for _ in range(3):
+        for k, (r, s, q) in enumerate(zip(runs, shapes, streams)):
+            with torch.cuda.stream(q):
+                got[k].append(r(0, s[3], 2))
+    torch.cuda.synchronize()
+    assert time.perf_counter() - start < 0.2, "somebody waited for room that was there"
+    for w, g in zip(want, got):
+        for one in g:
+            assert all(torch.equal(a, b) for a, b in zip(w, one))
