@@ -481,7 +481,7 @@ static int single_piece(const StepWs& w, const amq::BmvArgs& b, int64_t n, int k
   q.c = c;
   q.hs = hs;
   q.save_h = marks ? nullptr : w.pre0;
-  q.save_c = marks ? nullptr : w.pre0 + b.H;
+  q.save_c = marks || epi == amq::kEpiGru ? nullptr : w.pre0 + b.H;
   q.T = T;
   q.clear_flag = first || !marks;
   q.sync = w.sync;

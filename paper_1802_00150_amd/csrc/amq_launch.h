@@ -283,9 +283,10 @@ __device__ __forceinline__ void seqg_leave(unsigned* sync, const ResidentClaim& 
     give_resident_share(claim);
 }
 // Before a launch of this kind (under resident_launches()): claims its room, clears the tags and, if asked, the flag, and
-// publishes the initial state h as that of tag 0 in the second of the two buffers.
-hipError_t launch_seqg_reset(unsigned* sync, unsigned long long* hbuf, const float* h, int H, int clear_flag, const ResidentClaim& claim,
-                             hipStream_t s);
+// publishes the initial state h as that of tag 0 in the second of the two buffers.  save_h, save_c [H] (nullable): receive the
+// initial state.
+hipError_t launch_seqg_reset(unsigned* sync, unsigned long long* hbuf, const float* h, const float* c, float* save_h,
+                             float* save_c, int H, int clear_flag, const ResidentClaim& claim, hipStream_t s);
 // Should the launch itself fail: gives the room back.
 void launch_seqg_abandon(const unsigned* sync, const ResidentClaim& claim, hipStream_t s);
 bool lstm_seqg_supported(long long I, long long H, long long B, int k_w, int k_a);
@@ -312,7 +313,7 @@ struct Seq1Args {
   float* h;             // [H] in: h_0, out: h_steps
   float* c;             // LSTM: the same
   float* hs;            // [steps][H] or null
-  float* save_h;        // [H], [H] or null: the initial state, for whoever computes the piece again
+  float* save_h;        // [H], [H] or null (GRU: save_c null): receive the initial state, for whoever computes the piece again
   float* save_c;
   int T;
   int clear_flag;       // non-zero: an earlier launch's give-up is forgotten

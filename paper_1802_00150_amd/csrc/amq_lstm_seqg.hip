@@ -189,8 +189,10 @@ __device__ __forceinline__ bool quantize_wg(const void* src_v, unsigned tag, uns
 // Before a launch: clears the arrival bytes and the tags of the published state; the give-up flag only
 // for the first launch of an API call.
 // Claims room for the launch (amq_resident.h; without it the launch goes ahead all the same, as its waits are bounded).
-__global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, const float* h, int H, int clear_flag,
-                                  ResidentClaim claim) {
+// The initial state is saved here, where every entry of it is sure to be: a workgroup of the launch itself that finds the flag
+// of another one set has to leave at once.
+__global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, const float* h, const float* c, float* save_h,
+                                  float* save_c, int H, int clear_flag, ResidentClaim claim) {
   const unsigned t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
   if (t == 0) {
     if (clear_flag) sync[0] = 0u;
@@ -204,6 +206,12 @@ __global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, cons
     unsigned v = 0u;
     if (i >= units) v = *reinterpret_cast<const unsigned*>(reinterpret_cast<const char*>(h) + (i - units) * 4u);
     *reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(hbuf) + i * 8u) = v;
+    if (i >= units && save_h) *reinterpret_cast<unsigned*>(reinterpret_cast<char*>(save_h) + (i - units) * 4u) = v;
+  }
+  if (save_c) {
+    for (unsigned i = t; i < units; i += nt)
+      *reinterpret_cast<float*>(reinterpret_cast<char*>(save_c) + i * 4u) =
+          *reinterpret_cast<const float*>(reinterpret_cast<const char*>(c) + i * 4u);
   }
 }
 
@@ -367,7 +375,7 @@ __global__ __launch_bounds__(64 * kGWaves, 2) void lstm_seqg_kernel(SeqGArgs a) 
 template <int KW, int KA>
 hipError_t launch_kk(const SeqGArgs& a, int grid, hipStream_t s) {
   std::lock_guard<std::mutex> together(resident_launches());
-  hipError_t e = launch_seqg_reset(a.sync, a.hbuf, a.h, a.H, a.first_piece, a.claim, s);
+  hipError_t e = launch_seqg_reset(a.sync, a.hbuf, a.h, nullptr, nullptr, nullptr, a.H, a.first_piece, a.claim, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((lstm_seqg_kernel<KW, KA>), dim3(grid), dim3(64 * kGWaves), 0, s, a);
   e = hipGetLastError();
@@ -394,9 +402,9 @@ bool lstm_seqg_supported(long long I, long long H, long long B, int k_w, int k_a
   return (H + units_per_wg - 1) / units_per_wg <= kSeqGMaxGrid;
 }
 
-hipError_t launch_seqg_reset(unsigned* sync, unsigned long long* hbuf, const float* h, int H, int clear_flag,
-                             const ResidentClaim& claim, hipStream_t s) {
-  hipLaunchKernelGGL(seqg_reset_kernel, dim3(8), dim3(256), 0, s, sync, hbuf, h, H, clear_flag, claim);
+hipError_t launch_seqg_reset(unsigned* sync, unsigned long long* hbuf, const float* h, const float* c, float* save_h,
+                             float* save_c, int H, int clear_flag, const ResidentClaim& claim, hipStream_t s) {
+  hipLaunchKernelGGL(seqg_reset_kernel, dim3(8), dim3(256), 0, s, sync, hbuf, h, c, save_h, save_c, H, clear_flag, claim);
   return hipGetLastError();
 }
 

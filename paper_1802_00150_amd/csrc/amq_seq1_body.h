@@ -74,10 +74,6 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
   if (cell) {
     hlast = a.h[unit];
     if (EPI == kEpiLstm) cst = a.c[unit];
-    if (a.save_h) {
-      a.save_h[unit] = hlast;
-      if (EPI == kEpiLstm) a.save_c[unit] = cst;
-    }
   }
 
   const int nslots = (H + 63) >> 6;
@@ -222,7 +218,7 @@ hipError_t run_form(const Seq1Args& a, hipStream_t s) {
   Seq1Args q = a;
   q.claim = resident_claim(grid, false);
   std::lock_guard<std::mutex> together(resident_launches());
-  hipError_t e = launch_seqg_reset(q.sync, q.hbuf, q.h, q.H, q.clear_flag, q.claim, s);
+  hipError_t e = launch_seqg_reset(q.sync, q.hbuf, q.h, q.c, q.save_h, q.save_c, q.H, q.clear_flag, q.claim, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((seq1_kernel<KW, KA, EPI, QW, NJ, U, JOINT>), dim3((unsigned)grid), dim3(64 * k1Waves), 0, s, q);
   e = hipGetLastError();

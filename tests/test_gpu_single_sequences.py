@@ -153,6 +153,44 @@ def test_a_piece_whose_waits_give_up_is_computed_again(amq, gates, I, H, k):
         assert np.array_equal(host(g), w)
 
 
+@pytest.mark.parametrize("gates,I,H,k", [(3, 2048, 2048, 2), (3, 300, 2000, 3), (4, 2048, 2048, 3)])
+def test_recovers_from_a_state_that_is_all_saved(amq, gates, I, H, k):
+    # beside a launch that holds all but a few compute units: the workgroups that fit give up, those that arrive when it has
+    # ended find the flag raised and leave at once, and the launch that follows must find the state of them all.  (Nothing in
+    # the workspace is left from an earlier call.)
+    import time
+
+    import torch
+    m = Model(amq, gates, I, H, k, k, 4)
+    m.start()
+    m.call()
+    ref = [host(t) for t in m.result()]
+    holder = Model(amq, 4, 960, 960, 2, 2, 64)  # 60 workgroups x 4 tiles
+    holder.xs, holder.ws = torch.randn(64, 64, 960, device="cuda:0"), amq.lstm_sequence_workspace(960, 960, 64, 2, "cuda:0")
+    holder.h0, holder.c0 = torch.zeros(64, 960, device="cuda:0"), torch.zeros(64, 960, device="cuda:0")
+    side = torch.cuda.Stream()
+    say("late workgroups: gates=%d I=%d H=%d k=%d" % (gates, I, H, k))
+    for _ in range(3):
+        m.start()
+        m.ws.fill_(0xA5)
+        holder.start()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            holder.call(hs=False)
+        time.sleep(1e-4)
+        amq.binding.debug_set_sequence_spin_limit(1)
+        try:
+            m.call()
+            torch.cuda.synchronize()
+        finally:
+            amq.binding.debug_set_sequence_spin_limit(0)
+        got = [host(t) for t in m.result()]
+        for t in range(4):  # (few steps: sums in another order, as above)
+            assert_vec_close(got[0][t], ref[0][t], "h_%d" % (t + 1))
+        for g, w in zip(got[1:], ref[1:]):
+            assert_vec_close(g, w, "state")
+
+
 def test_small_workspace_and_other_codes_take_the_steps(amq):
     # a GRU workspace without the regions of the one-launch form, and code widths it does not take
     import torch
