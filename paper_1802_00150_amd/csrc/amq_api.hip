@@ -480,8 +480,8 @@ static int single_piece(const StepWs& w, const amq::BmvArgs& b, int64_t n, int k
   q.h = h;
   q.c = c;
   q.hs = hs;
-  q.save_h = marks ? nullptr : w.pre0;
-  q.save_c = marks || epi == amq::kEpiGru ? nullptr : w.pre0 + b.H;
+  q.save_h = w.pre0;
+  q.save_c = epi == amq::kEpiGru ? nullptr : w.pre0 + b.H;
   q.T = T;
   q.clear_flag = first || !marks;
   q.sync = w.sync;
@@ -523,9 +523,9 @@ static int single_run(const amq::BmvArgs& b, const StepWs& w, const float* xs, i
     if (st != AMQ_OK) return st;
     st = single_piece(w, b, n, k_w, k_a, epi, T, h, c, hs ? hs + t0 * H : nullptr, t0 == 0, s);
     if (st != AMQ_OK) return st;
-    // (a launch that gave up, or found the flag of an earlier one, leaves its rows of hs as NaN)
-    if (hs && single_marks(I, H, epi)) {
-      st = hip_status(amq::launch_seqg_poison(w.sync, hs + t0 * H, n * H, s));
+    // (a launch that gave up, or found the flag of an earlier one, leaves its rows of hs as NaN and the state as it was)
+    if (single_marks(I, H, epi)) {
+      st = hip_status(amq::launch_seqg_undo(w.sync, hs ? hs + t0 * H : nullptr, n * H, h, c, w.pre0, w.pre0 + H, (int)H, s));
       if (st != AMQ_OK) return st;
     }
   }
@@ -732,14 +732,13 @@ int amq_lstm_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t*
     for (int64_t t0 = 0; t0 < steps; t0 += amq::kSeqGMaxSteps) {
       const int n = (int)(steps - t0 < amq::kSeqGMaxSteps ? steps - t0 : amq::kSeqGMaxSteps);
       amq::SeqGArgs q{Wxp, alpha_x, Whp, alpha_h, (int)I, (int)H, bias, xs + t0 * I, n, h, c,
-                      hs ? hs + t0 * H : nullptr, T, 0, w.sync, w.hbuf, w.xq, w.xbeta, t0 == 0};
+                      hs ? hs + t0 * H : nullptr, T, 0, w.sync, w.hbuf, w.xq, w.xbeta, t0 == 0, w.pre0, w.pre0 + H};
       st = hip_status(amq::launch_lstm_seqg(q, k_w, k_a, static_cast<hipStream_t>(stream)));
       if (st != AMQ_OK) return st;
-      // a launch that gave up (or found the flag of an earlier one) leaves its rows of hs as NaN
-      if (hs) {
-        st = hip_status(amq::launch_seqg_poison(w.sync, hs + t0 * H, (long long)n * H, static_cast<hipStream_t>(stream)));
-        if (st != AMQ_OK) return st;
-      }
+      // a launch that gave up (or found the flag of an earlier one) leaves its rows of hs as NaN and the state as it was
+      st = hip_status(amq::launch_seqg_undo(w.sync, hs ? hs + t0 * H : nullptr, (long long)n * H, h, c, w.pre0, w.pre0 + H, (int)H,
+                                            static_cast<hipStream_t>(stream)));
+      if (st != AMQ_OK) return st;
     }
     return AMQ_OK;
   }
@@ -1460,7 +1459,7 @@ static int lm_sequence_impl(const uint32_t* Ep, const float* alpha_e, int64_t vo
       st = hip_status(amq::launch_quantize(q, k_a, s));
       if (st != AMQ_OK) return st;
       amq::SeqGArgs g{Wxp, alpha_x, Whp, alpha_h, (int)E, (int)H, bias, nullptr, n, h, c, lw.hs, T, 0, w.sync, w.hbuf,
-                      w.xq, w.xbeta, t0 == 0};
+                      w.xq, w.xbeta, t0 == 0, w.pre0, w.pre0 + H};
       st = single ? single_piece(w, lstm_args(Wxp, alpha_x, Whp, alpha_h, E, H, bias, nullptr, nullptr, nullptr, nullptr, c, B, h,
                                               c, nullptr),
                                  n, k_w, k_a, amq::kEpiLstm, T, h, c, lw.hs, t0 == 0, s)
@@ -1470,9 +1469,9 @@ static int lm_sequence_impl(const uint32_t* Ep, const float* alpha_e, int64_t vo
       if (st != AMQ_OK) return st;
       if (single && !single_marks(E, H, amq::kEpiLstm)) continue;
       // the output layer has just read hidden states that are incomplete if the recurrence gave up (now
-      // or in an earlier piece of this call): its results for these steps become NaN
-      st = hip_status(o.logprob ? amq::launch_seqg_poison(w.sync, o.logprob + t0 * V, (long long)n * V, s)
-                                : amq::launch_seqg_poison(w.sync, o.target_logprob + t0, n, s));
+      // or in an earlier piece of this call): its results for these steps become NaN, and the state is put back
+      st = hip_status(amq::launch_seqg_undo(w.sync, o.logprob ? o.logprob + t0 * V : o.target_logprob + t0,
+                                            o.logprob ? (long long)n * V : n, h, c, w.pre0, w.pre0 + H, (int)H, s));
       if (st != AMQ_OK) return st;
     }
     return AMQ_OK;

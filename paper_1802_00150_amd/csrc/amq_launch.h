@@ -270,6 +270,8 @@ struct SeqGArgs {
   float* xbeta;         // [steps][k_a]: their coefficients
   int first_piece;      // non-zero: also clear the give-up flag (once per API call; a later piece of the
                         // same call must see a flag an earlier piece raised)
+  float* save_h;        // [H], [H]: receive the initial state
+  float* save_c;
   ResidentClaim claim;  // filled by launch_lstm_seqg
   unsigned spin_limit;  // filled by launch_lstm_seqg: polls of a wait before it gives up
 };
@@ -283,8 +285,8 @@ __device__ __forceinline__ void seqg_leave(unsigned* sync, const ResidentClaim& 
     give_resident_share(claim);
 }
 // Before a launch of this kind (under resident_launches()): claims its room, clears the tags and, if asked, the flag, and
-// publishes the initial state h as that of tag 0 in the second of the two buffers.  save_h, save_c [H] (nullable): receive the
-// initial state.
+// publishes the initial state h as that of tag 0 in the second of the two buffers.  save_h, save_c [H]: receive the
+// initial state (GRU: c, save_c null).
 hipError_t launch_seqg_reset(unsigned* sync, unsigned long long* hbuf, const float* h, const float* c, float* save_h,
                              float* save_c, int H, int clear_flag, const ResidentClaim& claim, hipStream_t s);
 // Should the launch itself fail: gives the room back.
@@ -295,8 +297,10 @@ hipError_t launch_lstm_seqg(SeqGArgs a, int k_w, int k_a, hipStream_t s);
 // path set it to 1, which makes the first wait that is not satisfied at once give up.
 void set_seqg_spin_limit(unsigned polls);
 // After a launch of the sequence kernel and whatever consumed its hs: if the give-up flag is set,
-// overwrite out[0 .. count) with NaN (results computed from an incomplete recurrence must not look valid).
-hipError_t launch_seqg_poison(const unsigned* sync, float* out, long long count, hipStream_t s);
+// overwrite out[0 .. count) (nullable) with NaN (results computed from an incomplete recurrence must not look valid) and put the
+// state back to that before the launch: waves that were not the ones to give up may have finished and written theirs.
+hipError_t launch_seqg_undo(const unsigned* sync, float* out, long long count, float* h, float* c, const float* save_h,
+                            const float* save_c, int H, hipStream_t s);
 
 // ---- the same for LSTM and GRU and vectors of up to 2048 entries, given the codes of all inputs (amq_seq1.hip) ------
 struct Seq1Args {
@@ -313,7 +317,7 @@ struct Seq1Args {
   float* h;             // [H] in: h_0, out: h_steps
   float* c;             // LSTM: the same
   float* hs;            // [steps][H] or null
-  float* save_h;        // [H], [H] or null (GRU: save_c null): receive the initial state, for whoever computes the piece again
+  float* save_h;        // [H], [H] (GRU: save_c null): receive the initial state, for whoever computes the piece again or takes it back
   float* save_c;
   int T;
   int clear_flag;       // non-zero: an earlier launch's give-up is forgotten

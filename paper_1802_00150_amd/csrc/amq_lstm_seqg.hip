@@ -20,10 +20,10 @@
 //     until all carry the tag of the step: the data is its own arrival signal, so the steps need no
 //     barrier and no ordering between separate locations.
 // Every wait spins a bounded number of times; if one gives up (the grid was not resident as a whole)
-// it raises a flag in the workspace, every workgroup leaves, the state outputs h and c are not
-// written and hs is incomplete.  The flag is cleared once per API call, not per launch: the later
-// launches of a longer sequence see it and leave at once, and launch_seqg_poison turns whatever was
-// derived from hs into NaN.
+// it raises a flag in the workspace and every workgroup leaves that comes to look at it; hs is incomplete
+// then, and of h and c the units of those that were through before are written.  The flag is cleared
+// once per API call, not per launch: the later launches of a longer sequence see it and leave at once,
+// and launch_seqg_undo puts h and c back and turns whatever was derived from hs into NaN.
 #include <atomic>
 
 #include "amq_launch.h"
@@ -206,7 +206,7 @@ __global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, cons
     unsigned v = 0u;
     if (i >= units) v = *reinterpret_cast<const unsigned*>(reinterpret_cast<const char*>(h) + (i - units) * 4u);
     *reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(hbuf) + i * 8u) = v;
-    if (i >= units && save_h) *reinterpret_cast<unsigned*>(reinterpret_cast<char*>(save_h) + (i - units) * 4u) = v;
+    if (i >= units) *reinterpret_cast<unsigned*>(reinterpret_cast<char*>(save_h) + (i - units) * 4u) = v;
   }
   if (save_c) {
     for (unsigned i = t; i < units; i += nt)
@@ -220,11 +220,15 @@ __global__ void seqg_abandon_kernel(const unsigned* sync, ResidentClaim claim) {
   if (sync[kSeqGClaimed] != 0u) give_resident_share(claim);
 }
 
-__global__ void seqg_poison_kernel(const unsigned* sync, float* out, long long count) {
+__global__ void seqg_undo_kernel(const unsigned* sync, float* out, long long count, float* h, float* c, const float* save_h,
+                                 const float* save_c, int H) {
   if (*sync == 0u) return;
-  const long long nt = (long long)gridDim.x * blockDim.x;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += nt)
-    out[i] = __builtin_nanf("");
+  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x, nt = (long long)gridDim.x * blockDim.x;
+  for (long long i = t; i < count; i += nt) out[i] = __builtin_nanf("");
+  for (long long i = t; i < H; i += nt) {
+    h[i] = save_h[i];
+    c[i] = save_c[i];
+  }
 }
 
 template <int KW, int KA>
@@ -375,7 +379,7 @@ __global__ __launch_bounds__(64 * kGWaves, 2) void lstm_seqg_kernel(SeqGArgs a) 
 template <int KW, int KA>
 hipError_t launch_kk(const SeqGArgs& a, int grid, hipStream_t s) {
   std::lock_guard<std::mutex> together(resident_launches());
-  hipError_t e = launch_seqg_reset(a.sync, a.hbuf, a.h, nullptr, nullptr, nullptr, a.H, a.first_piece, a.claim, s);
+  hipError_t e = launch_seqg_reset(a.sync, a.hbuf, a.h, a.c, a.save_h, a.save_c, a.H, a.first_piece, a.claim, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((lstm_seqg_kernel<KW, KA>), dim3(grid), dim3(64 * kGWaves), 0, s, a);
   e = hipGetLastError();
@@ -416,11 +420,12 @@ void launch_seqg_abandon(const unsigned* sync, const ResidentClaim& claim, hipSt
 unsigned sequence_spin_limit() { return g_spin_limit.load(); }
 void set_seqg_spin_limit(unsigned polls) { g_spin_limit.store(polls ? polls : kSpinLimit); }
 
-hipError_t launch_seqg_poison(const unsigned* sync, float* out, long long count, hipStream_t s) {
-  if (!out || count <= 0) return hipSuccess;
-  const long long blocks = (count + 255) / 256;
-  hipLaunchKernelGGL(seqg_poison_kernel, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), 0, s, sync, out,
-                     count);
+hipError_t launch_seqg_undo(const unsigned* sync, float* out, long long count, float* h, float* c, const float* save_h,
+                            const float* save_c, int H, hipStream_t s) {
+  if (!out) count = 0;
+  const long long blocks = ((count > H ? count : H) + 255) / 256;
+  hipLaunchKernelGGL(seqg_undo_kernel, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), 0, s, sync, out, count, h,
+                     c, save_h, save_c, H);
   return hipGetLastError();
 }
 

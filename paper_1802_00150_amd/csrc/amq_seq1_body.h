@@ -23,7 +23,8 @@
 // sums the two operand blocks of a row apart.
 //
 // Every wait is bounded.  If one gives up a flag is raised and everybody leaves; the caller of this launch follows it with
-// one that either computes the piece again from the saved state or marks what was derived from it (launch_seqg_poison).
+// one that either computes the piece again from the saved state or takes it back and marks what was derived from it
+// (launch_seqg_undo).
 #pragma once
 #include "amq_launch.h"
 #include "amq_quantize_body.h"

@@ -191,6 +191,39 @@ def test_recovers_from_a_state_that_is_all_saved(amq, gates, I, H, k):
             assert_vec_close(g, w, "state")
 
 
+@pytest.mark.parametrize("captured", [False, True])
+@pytest.mark.parametrize("I,H,hs", [(300, 300, True), (700, 1024, True), (1024, 1024, False)])
+def test_a_piece_that_is_given_up_leaves_the_state_as_it_was(amq, I, H, hs, captured):
+    # in the last step the first to look find nothing and give up, while the last ones find all of it there and finish
+    import torch
+    m = Model(amq, 4, I, H, 2, 2, 2)
+    m.start()
+    m.call(hs)
+    ref = m.result()
+    graph = torch.cuda.CUDAGraph() if captured else None
+    say("given up: I=%d H=%d hs=%s captured=%s" % (I, H, hs, captured))
+    amq.binding.debug_set_sequence_spin_limit(1)
+    try:
+        torch.cuda.synchronize()
+        if captured:
+            with torch.cuda.graph(graph):
+                m.call(hs)
+        seen = 0
+        for _ in range(20):
+            m.start_in_place()
+            graph.replay() if captured else m.call(hs)
+            torch.cuda.synchronize()
+            gave_up = amq.lstm_sequence_abandoned(m.ws, I, H, 1, 2)
+            seen += gave_up
+            want = (torch.full_like(m.hs, float("nan")), m.h0, m.c0) if gave_up else ref
+            for got, w in list(zip(m.result(), want))[0 if hs else 1:]:
+                assert torch.equal(got.nan_to_num(7.0), w.nan_to_num(7.0))
+    finally:
+        amq.binding.debug_set_sequence_spin_limit(0)
+    say("%d of 20" % seen)
+    assert seen > 0
+
+
 def test_small_workspace_and_other_codes_take_the_steps(amq):
     # a GRU workspace without the regions of the one-launch form, and code widths it does not take
     import torch
