@@ -1,6 +1,6 @@
 // Whole batch-1 LSTM sequences in one launch, spread over the chip: the recurrence of Eq. 6 with
 // every workgroup keeping its slice of both weight blocks in registers for all time steps.  On a stream that is being
-// captured; elsewhere seq1_kernel (amq_seq1_body.h), which needs more registers and so a full claim of room.
+// captured; elsewhere seq1_kernel (amq_seq1_body.h), some forms of which need more registers than a light claim of room counts on.
 //
 // At batch 1 a step moves a few hundred KB to 3 MB of packed weights and a few KB of state; run
 // as two launches per step it is bound by launch gaps and by the cold misses every new kernel

@@ -7,13 +7,14 @@
 //
 // What is counted: shares of 32 workgroups -- workgroups go to the 8 dies in turn and, on a die, to its 4 shader engines,
 // so a share is at most one workgroup per engine (8 compute units) and the sums hold for every engine, not only for the
-// chip.  A full claim (amq_seqw.hip, amq_seqw_tiles.hip: two waves per SIMD, most of its registers) counts on a compute unit of its own per
-// workgroup; of a light one (amq_lstm_seqg.hip: one wave per SIMD, up to 144 of its 512 registers) a unit holds three, as
-// long as no full claim is about.  Any placement of the workgroups then leaves room for those still to come.
+// chip.  A full claim counts on a compute unit of its own per workgroup; of a light one a unit holds three, as long as no full
+// claim is about.  Any placement of the workgroups then leaves room for those still to come.
 //
-// The waves that wait for room must not sit where a grid that has its room still has to go, so a full claim's kernels use
-// at most kResidentRegisters each and a waiting one 8: beside two of the former on a SIMD there is room for four of the
-// latter, as many as a process has hardware queues.
+// The waves that wait for room must not sit where a grid that has its room still has to go: beside the waves that a claim may
+// put on a SIMD there must be room, in its 512 registers, for four waiting ones of 8, as many as a process has hardware
+// queues.  Full claims: amq_seqw.hip and amq_seqw_tiles.hip with two waves per SIMD of at most kResidentRegisters, and the forms
+// of amq_seq1_body.h that are not light, with one of at most 256.  Light claims: amq_lstm_seqg.hip (up to 144 registers) and
+// the forms of amq_seq1_body.h for 513 to 1024 units (up to 160), with one wave per SIMD and workgroup.
 //
 // The word on the device: full shares in bits 0..7, light ones in bits 8..15, and the door.  Whoever finds no room closes
 // the door and is the next to get some; small claims do not keep a large one waiting for ever.

@@ -217,7 +217,10 @@ hipError_t run_form(const Seq1Args& a, hipStream_t s) {
   const int grid = (a.H + units - 1) / units;
   if (grid > kSeqGMaxGrid) return hipErrorInvalidValue;
   Seq1Args q = a;
-  q.claim = resident_claim(grid, false);
+  // Light for the forms of 513 to 1024 units (at most 160 registers), which are the large grids of vectors up to 1024 entries.
+  // Measured, 35 steps on 3 / 4 streams, us until all have finished, full / light: 650 units W2/A2 249 / 272 -> 152 / 233, 1024
+  // units 264 / 288 -> 232 / 248, W3/A3 251 / 339 -> 212 / 294.  Grids of up to 512 units are one or two shares of eight as they are.
+  q.claim = resident_claim(grid, QW == 4 && U == 1);
   std::lock_guard<std::mutex> together(resident_launches());
   hipError_t e = launch_seqg_reset(q.sync, q.hbuf, q.h, q.c, q.save_h, q.save_c, q.H, q.clear_flag, q.claim, s);
   if (e != hipSuccess) return e;

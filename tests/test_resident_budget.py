@@ -75,6 +75,12 @@ def test_room_for_waiting_kernels_beside_single_sequences(registers):
         assert r + WAITERS * 8 <= SIMD_REGISTERS, (name, r)
 
 
+def test_room_for_waiting_kernels_beside_light_single_sequences(registers):
+    # (four waves quantize together, one unit per lane: the forms whose claim is light) three workgroups of 4 waves per unit
+    for name, r in of(registers, r"11seq1_kernelI(Li\dE){3}Li4ELi\dELi1E", 16).items():
+        assert 3 * r + WAITERS * 8 <= SIMD_REGISTERS, (name, r)
+
+
 def test_room_for_waiting_kernels_beside_tiled_sequences(registers):
     # one workgroup of 8 waves per compute unit, as amq_seqw.hip
     for name, r in of(registers, "17seqw_tiles_kernel", 12).items():
