@@ -216,6 +216,8 @@ hipError_t launch_mfma4(BmvArgs a, int k_w, int k_a, int epi, hipStream_t s, int
 // at least 32 columns (store mode only)
 bool mfma4w_supported(const BmvArgs& a, int k_w, int k_a);
 hipError_t launch_mfma4w(const BmvArgs& a, int k_w, int k_a, hipStream_t s, int* lse_slots = nullptr);
+// 16 x 16 tasks of the SIMD that has the most of them there; 0 where it is not taken
+int mfma4w_most_tasks(const BmvArgs& a, int k_w, int k_a);
 // large plain products on the 32 x 32 form of the instruction, any vector length whose staged planes fit LDS
 bool mfma32_supported(const BmvArgs& a, int k_w, int k_a);
 hipError_t launch_mfma32(const BmvArgs& a, int k_w, int k_a, hipStream_t s, int* lse_slots = nullptr);

@@ -396,19 +396,23 @@ __global__ __launch_bounds__(64 * kWaves) void mfma32_kernel(BmvArgs a, int rb_p
 // and the columns fill them.
 constexpr int max_tiles(int kw, int ka) { return kw * ka <= 4 ? 2 : 1; }
 
+// Row blocks of a workgroup: about one workgroup per compute unit.
+inline int blocks_each(int rowblocks, int groups) {
+  const int splits = groups < 256 ? 256 / groups : 1;
+  return (rowblocks + splits - 1) / splits;
+}
+
 template <int KW, int KA, int NT, int NP, int OUT>
 hipError_t launch_form(BmvArgs a, hipStream_t s, int* lse_slots) {
   const int rowblocks = (int)((a.m + kTileN - 1) / kTileN);
   const int groups = (a.batch + NT * kTileN - 1) / (NT * kTileN);
-  // about one workgroup per compute unit, the row blocks dealt out evenly: a SIMD's two waves take blocks s, s + 4, s + 8 ..
+  // The row blocks are dealt out evenly: a SIMD's two waves take blocks s, s + 4, s + 8 ..
   // of the workgroup, so what counts is the quarter of `per` rounded up, and that is least for the smallest `per` that fits.
   // (Multiples of the 8 waves instead left compute units idle: 10000 x 1024 W2/A3 batch 256 13.3 against 10.8 us, 42000 x
   // 1024 W3/A3 batch 64 15.5 / 13.0, 10000 x 1500 W2/A3 batch 256 16.1 / 13.9, 10000 x 650 W3/A3 batch 256 12.9 / 10.6;
   // no difference from about 16 blocks per wave on.)
-  int splits = 256 / groups;
-  if (splits < 1) splits = 1;
-  const int per = (rowblocks + splits - 1) / splits;
-  splits = (rowblocks + per - 1) / per;
+  const int per = blocks_each(rowblocks, groups);
+  const int splits = (rowblocks + per - 1) / per;
   const int per_xcd = (splits * groups + kXcds - 1) / kXcds;
   const size_t lds = lds_bytes(KW, KA, NT, a.blk[0].n);
   static std::atomic<unsigned long long> configured{0};

@@ -541,6 +541,14 @@ __global__ __launch_bounds__(64 * NWV) void mfma4p_kernel(BmvArgs a, int rowbloc
 // Tiles per wave: as many as keep the accumulators within about 100 registers.
 constexpr int max_tiles(int kw, int ka) { return 24 / (kw * ka) > 4 ? 4 : 24 / (kw * ka); }
 
+// Row blocks of a workgroup: about one workgroup per compute unit (registers and the staged activations allow no second one);
+// in multiples of 4, so that its four SIMDs (waves w and w + 4 share one) get the same number of passes.
+int blocks_each(int rowblocks, int groups) {
+  const int splits = groups < 256 ? 256 / groups : 1;
+  const int per = ((rowblocks + splits - 1) / splits + 3) / 4 * 4;
+  return per < kWaves ? kWaves : per;
+}
+
 template <int KW, int KA, int NBT>
 hipError_t launch_one(BmvArgs a, hipStream_t s, int* lse_slots) {
   if constexpr (NBT > max_tiles(KW, KA) || NBT < 2) {
@@ -548,14 +556,7 @@ hipError_t launch_one(BmvArgs a, hipStream_t s, int* lse_slots) {
   } else {
     const int rowblocks = (int)((a.m + 15) / 16);
     const int groups = (a.batch + NBT * kTileB - 1) / (NBT * kTileB);
-    // about one workgroup per compute unit (registers and the staged activations allow no second
-    // one); row blocks per workgroup in multiples of 4, so that its four SIMDs (waves w and w + 4
-    // share one) get the same number of passes
-    int splits = 256 / groups;
-    if (splits < 1) splits = 1;
-    int per = (rowblocks + splits - 1) / splits;
-    per = (per + 3) / 4 * 4;
-    if (per < kWaves) per = kWaves;
+    const int per = blocks_each(rowblocks, groups);
     const size_t lds = (size_t)NBT * KA * kPlaneBytes + sizeof(int) * NBT * KA * kTileB;
     static std::atomic<unsigned long long> configured{0};
     {
@@ -781,6 +782,12 @@ bool mfma4w_supported(const BmvArgs& a, int k_w, int k_a) {
   const long long rowblocks = (a.m + 15) / 16;
   const long long groups = (a.batch + nbt * kTileB - 1) / (nbt * kTileB);
   return rowblocks * groups >= 2048;
+}
+
+int mfma4w_most_tasks(const BmvArgs& a, int k_w, int k_a) {
+  if (!mfma4w_supported(a, k_w, k_a)) return 0;
+  const int nbt = tiles_per_wave(k_w, k_a, a.batch);
+  return blocks_each((int)((a.m + 15) / 16), (a.batch + nbt * kTileB - 1) / (nbt * kTileB)) / 4 * nbt;
 }
 
 hipError_t launch_mfma4w(const BmvArgs& a, int k_w, int k_a, hipStream_t s, int* lse_slots) {

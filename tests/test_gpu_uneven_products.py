@@ -30,7 +30,11 @@ def operands(amq, m, n, B, k_w, k_a):
 # row blocks per workgroup: 1, 2, 5, 9 (one wave has two), 10, 11, 23; the last workgroup short; groups of columns short
 @pytest.mark.parametrize("m,n,B,k_w,k_a", [(35233, 1000, 17, 2, 3), (35168, 1024, 31, 2, 3), (10000, 1024, 256, 2, 3),
                                            (9200, 770, 255, 2, 3), (42000, 800, 65, 3, 3), (11000, 1024, 270, 3, 3),
-                                           (5001, 1024, 600, 3, 2), (3001, 300, 1000, 2, 2)])
+                                           (5001, 1024, 600, 3, 2), (3001, 300, 1000, 2, 2),
+                                           # either side of the lines that the padding of columns and the rounding of
+                                           # blocks draw: batch 48, a full batch and one more, 13 blocks in rounds of 4
+                                           (42000, 900, 48, 2, 3), (42000, 900, 49, 2, 3), (16000, 1024, 128, 3, 2),
+                                           (16000, 1024, 129, 3, 2), (10000, 1024, 300, 3, 3), (10000, 1024, 384, 3, 3)])
 def test_outputs(amq, m, n, B, k_w, k_a):
     W, _, X, bias, ref = operands(amq, m, n, B, k_w, k_a)
     tol = 1e-4 * ref.abs() + 1e-4 * ref.pow(2).mean(1, keepdim=True).sqrt()
