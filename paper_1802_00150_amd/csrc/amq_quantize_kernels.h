@@ -34,12 +34,18 @@ void launch_one(QuantArgs a, int total, hipStream_t s) {
 // chip.  Measured, us, 16384 vectors, 16 slots / here: k = 2 of 1100 / 1500 / 2048 / 3000 / 4096 entries 29.7 / 31.3 / 34.0 /
 // 56.6 / 67.2 -> 22.6 / 25.2 / 27.7 / 51.6 / 65.6, k = 3 59.4 / 62.3 / 65.1 / 116 / 126 -> 40.5 / 45.3 / 55.0 / 96.8 / 121,
 // k = 4 131 / 139 / 148 / 267 / 290 -> 83.6 / 93.2 / 129 / 208 / 284; reconstruction k = 3 54.5 / 62.2 / 66.4 / 120 / 132 ->
-// 41.5 / 47.3 / 60.2 / 104 / 115.  Number of vectors from which on they are ahead:
-constexpr int wide_rows(int k, bool recon, int nw, int nj) {
-  if (recon && k == 2 && nj > (nw == 1 ? 24 : 20)) return 1 << 30;  // (bound by its stores: 16384 x 1700 36.1 against 37.1)
+// 41.5 / 47.3 / 60.2 / 104 / 115.  At k = 3 on one wave 32 slots spill (84 bytes per lane, reconstruction 64) and are ahead all the
+// same (1540 / 2300 / 4096 / 16384 vectors of 2048 entries 5 / 4 / 11 / 15 %, reconstruction -1 / -3 / 3 / 9 %); the others of
+// these forms spill nothing worth the name.  Where they are ahead:
+constexpr bool wide_ahead(int k, bool recon, int nw, int nj, int vectors) {
+  if (recon && k == 2 && nj > (nw == 1 ? 24 : 20)) return false;  // (bound by its stores: 16384 x 1700 36.1 against 37.1)
   if (nw == 2 && nj > 24)  // (4096 entries, k = 2: 8192 vectors 33.6 against 33.8, 4096 19.2 against 20.0)
-    return recon ? 4096 : k == 3 ? 8192 : 12288;
-  return 1536;             // (1100 vectors of 1700 entries, k = 3: 9.6 against 10.4; 2000 11.2 against 10.5)
+    return vectors >= (recon ? 4096 : k == 3 ? 8192 : 12288);
+  if (nw == 2 && nj > 20 && (k == 2 || (recon && k == 3))) return vectors >= 4096;  // (2500 x 2900 5 and 11 % behind)
+  // Rounds of two waves per SIMD against two waves per vector in rounds of three: 1536 vectors are one of the latter (18.7 against
+  // 17.0 at 2048 entries), 2048 one of the former, and some more leave its second nearly empty (2200 29.6 against 27.4)
+  if (k == 4 && nw == 1 && nj > (recon ? 28 : 24)) return (vectors > 1536 && vectors <= 2048) || vectors >= 2700;
+  return vectors >= 1536;  // (1100 vectors of 1700 entries, k = 3: 9.6 against 10.4; 2000 11.2 against 10.5)
 }
 
 template <int K, bool RECON>
@@ -72,8 +78,13 @@ bool launch_wide(const QuantArgs& a, int total, int nw, int nj, hipStream_t s) {
 // vectors: 300 entries k = 2 3.48 / 3.06 (reconstruction) and 3.97 / 3.11, k = 4 7.97 / 6.06 and 10.3 / 6.1; 650 entries k = 2
 // 3.64 / 3.67 and 4.17 / 3.78, k = 3 at 700 5.18 / 5.38 and at 1000 6.03 / 5.42, k = 4 8.67 / 9.26 and 10.9 / 9.3; 2048 entries
 // k = 2 4.71 / 4.82 and 5.76 / 4.88.  4096 entries, 1 and 512 vectors: k = 2 4.37 / 3.92 and 8.05 / 4.98, k = 3 6.17 / 5.94 and
-// 11.6 / 7.6, k = 4 13.2 / 10.1, reconstruction k = 3 6.46 / 5.95 and 12.8 / 8.4.
-constexpr int online_vectors(int k, bool recon) { return k == 3 && !recon ? 768 : 600; }
+// 11.6 / 7.6, k = 4 13.2 / 10.1, reconstruction k = 3 6.46 / 5.95 and 12.8 / 8.4.  A wave on its own whose 16 slots are not all
+// full is slow enough for the line of k = 3 at k = 1 and in reconstructions too (680 vectors of 1000 entries k = 1 2.82 / 2.97, of
+// 1024 2.80 / 2.56, reconstruction k = 3 6.2 / 6.45).
+constexpr int online_vectors(int k, bool recon, int n) {
+  const bool partly = n > 896 && n < 1024 && (k == 1 || k == 3);
+  return (k == 3 && !recon) || partly ? 768 : 600;
+}
 
 template <int K, bool RECON>
 hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
@@ -82,7 +93,7 @@ hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
   if (total == 0) return hipSuccess;
   const int nslots = nvec ? 2 * ((max_n + 127) / 128) : 1;
   if (nslots > 256) return hipErrorInvalidValue;
-  if (nslots <= 32 && nvec < online_vectors(K, RECON)) {
+  if (nslots <= 32 && nvec < online_vectors(K, RECON, max_n)) {
     if (nslots <= 2) launch_one<K, 2, 1, true, RECON>(a, total, s);
     else if (nslots <= 16) launch_one<K, 4, 4, true, RECON>(a, total, s);
     else launch_one<K, 4, 8, true, RECON>(a, total, s);
@@ -90,7 +101,7 @@ hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
   }
   if constexpr (K >= 2) {
     const int nw = nslots <= 32 ? 1 : 2, nj = (nslots + nw - 1) / nw;
-    if (nslots > 16 && nslots <= 64 && nvec >= wide_rows(K, RECON, nw, nj) && launch_wide<K, RECON>(a, total, nw, nj, s))
+    if (nslots > 16 && nslots <= 64 && wide_ahead(K, RECON, nw, nj, nvec) && launch_wide<K, RECON>(a, total, nw, nj, s))
       return hipGetLastError();
   }
   int nw = 1;

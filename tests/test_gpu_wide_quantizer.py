@@ -10,13 +10,14 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("k", [2, 3, 4])
-@pytest.mark.parametrize("rows", [1535, 1536, 4096, 12288])
+@pytest.mark.parametrize("rows", [1535, 1536, 1537, 2048, 2049, 2700, 4096, 12288])
 def test_wide_forms_and_special_rows(k, rows):
     import torch
 
     import paper_1802_00150_amd as amq
-    lengths = {1535: (1100, 3000), 1536: (1025, 1152, 1153, 1280, 1281, 1500, 1536, 1537, 1792, 1793, 2000, 2048, 2049, 2304, 2560,
-                                          2561, 3000, 3072), 4096: (3073, 3333, 3584, 3585, 4000, 4096), 12288: (3100, 4096)}[rows]
+    many = (1025, 1152, 1153, 1280, 1281, 1500, 1536, 1537, 1792, 1793, 2000, 2048, 2049, 2304, 2560, 2561, 3000, 3072)
+    lengths = {1535: (1100, 3000), 1536: many, 1537: many if k == 4 else (1100,), 2048: (1700, 2048), 2049: (1700, 2048),
+               2700: (1700, 2048), 4096: (2561, 3072, 3073, 3333, 3584, 3585, 4000, 4096), 12288: (3100, 4096)}[rows]
     for n in lengths:
         print("wide k=%d rows=%d n=%d" % (k, rows, n), flush=True)
         g = np.random.default_rng(31 * n + k)
