@@ -5,7 +5,7 @@
 // The 32 rows of a wave are ordered unit by unit, four rows each (the GRU's fourth stays unused), so that the C layout (lane =
 // column l % 32, register r = row 8 (r / 4) + 4 (l / 32) + r % 4) leaves all gates of a unit in four adjacent registers: lane
 // half kb holds units 2 q + kb of its column.  State and results pass between the halves with two shuffles so that each lane
-// loads and stores 16 adjacent bytes.  The activation operands of the workgroup's 32 entries are staged in LDS as in the plain
+// loads and stores 16 adjacent bytes, in one request where the tensors of the state are aligned to them.  The activation operands of the workgroup's 32 entries are staged in LDS as in the plain
 // kernel, both blocks at once where they fit, otherwise one after the other; weight pieces go from memory to registers two
 // ahead of their use.
 //
@@ -34,13 +34,13 @@ __host__ __device__ constexpr int cell_wave_floats(int kw, int ka) { return kTil
 
 template <int KW, int KA, int EPI, int WV>
 __global__ __launch_bounds__(64 * WV, 8 / WV) void mfma32_cell_kernel(BmvArgs a, int rowblocks, int tiles, int per_xcd,
-                                                                       int together) {
+                                                                       int together, int aligned) {
   constexpr int NG = EPI == kEpiGru ? 3 : 4;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   asm volatile("" ::AMQ_ARG(a.blk[0].Wp), AMQ_ARG(a.blk[0].alpha), AMQ_ARG(a.blk[0].Xp), AMQ_ARG(a.blk[0].beta),
                AMQ_ARG(a.blk[0].n), AMQ_ARG(a.blk[1].Wp), AMQ_ARG(a.blk[1].alpha), AMQ_ARG(a.blk[1].Xp), AMQ_ARG(a.blk[1].beta),
                AMQ_ARG(a.blk[1].n), AMQ_ARG(a.H), AMQ_ARG(a.batch), AMQ_ARG(a.bias0), AMQ_ARG(a.bias1), AMQ_ARG(rowblocks),
-               AMQ_ARG(tiles), AMQ_ARG(per_xcd), AMQ_ARG(together));
+               AMQ_ARG(tiles), AMQ_ARG(per_xcd), AMQ_ARG(together), AMQ_ARG(aligned));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, kb = lane >> 5;
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(64 * WV, 8 / WV) void mfma32_cell_kernel(BmvArgs a,
 #pragma unroll
     for (int j = 0; j < KA; ++j) beta[k][j] = (k ? a.blk[1].beta : a.blk[0].beta)[bc * KA + j];
   const int u4 = rb * kUnits + 4 * kb;  // the four adjacent units this lane loads and stores
-  const bool vec = (H & 3) == 0 && u4 + 4 <= H;
+  const bool vec = aligned && (H & 3) == 0 && u4 + 4 <= H;
   const size_t at = (size_t)bc * H + u4;
   float prev[4];
   {
@@ -345,11 +345,14 @@ hipError_t run(const BmvArgs& a, hipStream_t s) {
   const int groups = (rowblocks + WV - 1) / WV * tiles, per_xcd = (groups + kXcds - 1) / kXcds;
   const size_t i0 = cell_image_bytes(KA, a.blk[0].n), i1 = cell_image_bytes(KA, a.blk[1].n), co = (size_t)WV * cell_wave_floats(KW, KA) * sizeof(float);
   const bool together = i0 + i1 + co <= (size_t)kMaxLds;
+  const uintptr_t state = reinterpret_cast<uintptr_t>(EPI == kEpiGru ? a.h_prev : a.c_prev) | reinterpret_cast<uintptr_t>(a.h_out) |
+                          reinterpret_cast<uintptr_t>(EPI == kEpiGru ? nullptr : a.c_out) | reinterpret_cast<uintptr_t>(a.hs_out);
   static std::atomic<unsigned long long> configured{0};
   const hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&mfma32_cell_kernel<KW, KA, EPI, WV>), kMaxLds, configured);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((mfma32_cell_kernel<KW, KA, EPI, WV>), dim3((unsigned)(per_xcd * kXcds)), dim3(64 * WV),
-                     (together ? i0 + i1 : i0 > i1 ? i0 : i1) + co, s, a, rowblocks, tiles, per_xcd, together ? 1 : 0);
+                     (together ? i0 + i1 : i0 > i1 ? i0 : i1) + co, s, a, rowblocks, tiles, per_xcd, together ? 1 : 0,
+                     (state & 15) == 0 ? 1 : 0);
   return hipGetLastError();
 }
 

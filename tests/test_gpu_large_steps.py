@@ -71,3 +71,33 @@ def test_steps(amq, I, H, B, k_w, k_a):
             assert torch.equal(hs[0], got) and torch.equal(hs[1], h2) and torch.equal(hp, h2)
         # (hardware exponential and reciprocal: a few 1e-7 absolute; sums of at most 9 products with 24-bit factors below that)
         assert float((got.double() - h1).abs().max()) < 1e-5
+
+
+@pytest.mark.parametrize("gates,I,H,B,k_w,k_a", [(4, 1100, 1100, 250, 2, 2), (3, 1024, 1024, 256, 2, 3)])
+def test_state_at_any_float(amq, gates, I, H, B, k_w, k_a):
+    """The tensors of the state may begin at any multiple of four bytes, each for itself."""
+    import torch
+    g = torch.Generator(device="cuda:0").manual_seed(I + B)
+    randn = lambda *s: torch.randn(*s, generator=g, device="cuda:0")  # noqa: E731
+    d = [*amq.quantize_weights(randn(gates * H, I) * 0.04, k_w, 2), *amq.quantize_weights(randn(gates * H, H) * 0.04, k_w, 2)]
+    x, h, c = randn(B, I), torch.tanh(randn(B, H)), randn(B, H)
+
+    def place(offset, values=None):
+        room = torch.full((B * H + 8,), 7.0, device="cuda:0")
+        t = room[offset:offset + B * H].view(B, H)
+        return room, t if values is None else t.copy_(values)
+
+    def step(h_at, c_at, ho_at, co_at):
+        rooms = [place(ho_at), place(co_at)]
+        if gates == 4:
+            amq.lstm_step(*d, I, H, None, x, place(h_at, h)[1], place(c_at, c)[1], k_a, 2, h_out=rooms[0][1], c_out=rooms[1][1])
+        else:
+            amq.gru_step(*d, I, H, None, None, x, place(h_at, h)[1], k_a, 2, h_out=rooms[0][1])
+        for (room, _), at in zip(rooms, (ho_at, co_at)):  # nothing around them is written
+            assert bool((room[:at] == 7.0).all()) and bool((room[at + B * H:] == 7.0).all())
+        return [t for _, t in rooms[:2 if gates == 4 else 1]]
+
+    want = step(0, 0, 0, 0)
+    for at in ((1, 0, 0, 0), (0, 3, 0, 0), (0, 0, 2, 0), (0, 0, 0, 1), (3, 1, 2, 3)):
+        print("state at", at, flush=True)
+        assert all(torch.equal(a, b) for a, b in zip(step(*at), want))
