@@ -356,46 +356,65 @@ hipError_t run(const BmvArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Up to a task per SIMD the workgroups have four waves, so that every compute unit gets one.
-constexpr long long kFewTasks = 1024;
+// Workgroups have four waves as long as every one of them gets a compute unit of its own, otherwise eight.
+constexpr int kCompute = 256;
+struct Groups {
+  bool few;
+  long long rounds;  // of workgroups on the chip
+};
+Groups groups_of(long long H, long long batch) {
+  const long long rowblocks = (H + kUnits - 1) / kUnits, tiles = (batch + kTileN - 1) / kTileN;
+  if ((rowblocks + 3) / 4 * tiles <= kCompute) return Groups{true, 1};
+  return Groups{false, ((rowblocks + 7) / 8 * tiles + kCompute - 1) / kCompute};
+}
 
 template <int KW, int KA>
 hipError_t run_k(const BmvArgs& a, int epi, hipStream_t s) {
-  const long long tasks = (a.H + kUnits - 1) / kUnits * ((a.batch + kTileN - 1) / kTileN);
-  const bool few = tasks <= kFewTasks;
+  const bool few = groups_of(a.H, a.batch).few;
   if (epi == kEpiGru) return few ? run<KW, KA, kEpiGru, 4>(a, s) : run<KW, KA, kEpiGru, 8>(a, s);
   return few ? run<KW, KA, kEpiLstm, 4>(a, s) : run<KW, KA, kEpiLstm, 8>(a, s);
 }
 
 }  // namespace
 
-// Steps of 2- and 3-bit codes and vectors of at most 2048 entries, from the number of tasks (8 units x 32 entries) on at which it
-// is ahead of the kernels on 16 x 16 tiles.  Measured, us per step with its quantizer, LSTM, 16 x 16 / here:
-//   - a vector above 1024 entries: beyond a task per SIMD always (1100 units batch 256 W2/A2 24.1 / 19.5, 1500 batch 256 W2/A2,
-//     W3/A3 27.3 / 20.6, 40.1 / 33.2, 2048 batch 256 36.7 / 27.9, 55.5 / 47.9); below with two-bit activations (2048 batch 128
-//     W2/A2 21.6 / 19.7, 1300 batch 128 16.2 / 15.6, W3/A2 19.6 / 18.5, but 1500 batch 64 12.2 / 15.1), with three where one of
-//     the vectors is short (300 and 2000 entries batch 128 W3/A3 32.8 / 24.5, 2048 and 2048 31.6 / 33.0);
+// Steps of 2- and 3-bit codes and vectors of at most 2048 entries.  Both this kernel and those on 16 x 16 tiles take as long as
+// the compute unit with the most to do: here a round of workgroups, of four waves or of eight, there `other` workgroups of 16
+// units and 16 entries.  Measured, us per step with its quantizer, 16 x 16 / here, LSTM:
+//   - a vector above 1024 entries.  16 x 16 takes 4.2 (W2/A2) to 6.1 (W3/A3) per workgroup and 5 to 6 more, whatever the lengths up
+//     to 2048; here a round takes as long as the vectors are.  2048 units, batch 64 / 128 / 160 / 256 / 272 / 400 W2/A2 13.3 / 18.0,
+//     20.9 / 19.2, 26.3 / 25.4, 38.2 / 28.7, 42.3 / 44.3, 59.1 / 47.4, W3/A2 15.8 / 21.7, 25.5 / 23.7, 32.1 / 33.8, 47.3 / 42.0,
+//     53.8 / 64.0, 74.7 / 69.1, W3/A3 18.9 / 29.5, 30.2 / 32.2, 37.9 / 40.3, 55.9 / 48.1, 63.1 / 76.2, 89.1 / 81.4; 300 and 2000 entries
+//     batch 128 W3/A3 32.8 / 24.5, 1100 units batch 256 W2/A2 24.1 / 19.5;
 //   - up to 1024 entries the 16 x 16 kernel takes two batch tiles per wave at four plane products and stays ahead (1024 units
-//     batch 256 11.9 / 13.5); six: 1024 units batch 256 W2/A3 21.4 / 16.6, 512 28.9 / 23.0, 650 units batch 256 15.6 / 17.4, 1024
-//     38.2 / 39.3; nine: 1024 units batch 256 20.9 / 19.4, 512 33.3 / 27.2, 650 units batch 200 20.8 / 20.0, 1024 units batch 128
-//     12.2 / 18.0.
+//     batch 256 11.9 / 13.5).  Six: 1024 units batch 256 W2/A3 21.4 / 16.6, 512 28.9 / 23.0, 650 units batch 256 15.6 / 17.4, 1024
+//     38.2 / 39.3; nine: 1024 units batch 256 20.9 / 19.4, 512 33.3 / 27.2, 650 units batch 200 20.8 / 20.0, 900 units batch 140
+//     14.6 / 20.0, 1024 units batch 128 12.2 / 18.0.  A second round wants to be filled more than at longer vectors: batch 600
+//     900 units W2/A3 31.2 / 39.3, 1024 units W3/A2 33.2 / 38.0, W3/A3 40.9 / 45.2.
 bool mfma32_cell_supported(const BmvArgs& a, int k_w, int k_a, int epi) {
   if (epi != kEpiLstm && epi != kEpiGru) return false;
   if (a.groups > 1 || k_w < 2 || k_w > 3 || k_a < 2 || k_a > 3) return false;
   const int nmax = a.blk[0].n > a.blk[1].n ? a.blk[0].n : a.blk[1].n;
   if (nmax > 2048) return false;  // (one block's image fits LDS)
   if (a.m * ((nmax + 127) / 128) * k_w >= (1LL << 28) || (long long)a.batch * a.H >= (1LL << 29)) return false;
-  const long long tasks = (a.H + kUnits - 1) / kUnits * ((a.batch + kTileN - 1) / kTileN);
   const int products = k_w * k_a, np = even_half_pieces(a.blk[0].n) + even_half_pieces(a.blk[1].n);
+  const Groups g = groups_of(a.H, a.batch);
+  const long long work = (a.H + 15) / 16 * ((a.batch + 15) / 16), other = (work + kCompute - 1) / kCompute;
+  const long long past = other - 8 * (g.rounds - 1);  // (a full round of eight waves is eight of those)
   if (nmax > 1024) {
-    if (tasks > kFewTasks) return true;
-    return k_a == 2 ? tasks > 640 : tasks > 896 && np <= 10;
+    const bool light = np <= 10 || (np <= 12 && k_a == 2);
+    if (g.few) return other >= (light ? 3 : np <= 12 || k_a == 2 ? 4 : 5);
+    if (light || g.rounds > 2) return true;
+    if (g.rounds == 1) return other >= (products == 9 && np > 12 ? 6 : 5);
+    return past >= (products == 4 ? 1 : np <= 12 ? 2 : 3);
   }
   const bool padded = even_half_pieces(a.blk[0].n) != pieces_per_half(a.blk[0].n) ||
                       even_half_pieces(a.blk[1].n) != pieces_per_half(a.blk[1].n);
   if (products == 4) return false;
-  if (products == 6) return tasks > 768 && (tasks <= 2 * kFewTasks || !padded);
-  return tasks > 560;
+  if (g.few) return products == 6 ? (a.H + kUnits - 1) / kUnits * ((a.batch + kTileN - 1) / kTileN) > 768 : work >= 528;
+  if (products == 6 && padded && g.rounds > 1) return false;
+  if (g.rounds != 2) return true;
+  const bool gru = epi == kEpiGru;  // (the 16 x 16 kernel leaves a quarter of a GRU's tiles empty, too)
+  return past >= (products == 6 ? (gru ? 4 : 5) : gru && !padded ? 1 : 3);
 }
 
 hipError_t launch_mfma32_cell(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s) {

@@ -40,7 +40,10 @@ def reference(amq, gates, I, H, d, bias, x, h, c, k_a):
 # (I, H, B): one wave more and fewer than the lines, H % 8 and % 4, B % 32, blocks of 300 and 2000 entries, LDS shared
 SHAPES = [(1024, 1024, 256, 2, 3), (1024, 1024, 193, 2, 3), (700, 1021, 257, 2, 3), (650, 650, 250, 3, 3), (1024, 1030, 225, 3, 3),
           (1100, 1100, 250, 2, 2), (2048, 2048, 256, 2, 2), (2048, 2047, 129, 3, 3), (300, 2000, 128, 3, 3), (2000, 333, 520, 2, 3),
-          (1300, 1306, 127, 2, 2), (1500, 1500, 225, 3, 2), (1025, 64, 2600, 2, 2), (1, 1500, 200, 2, 2)]
+          (1300, 1306, 127, 2, 2), (1500, 1500, 225, 3, 2), (1025, 64, 2600, 2, 2), (1, 1500, 200, 2, 2),
+          # workgroups of four waves beyond one for every compute unit; a second round nearly empty and nearly full; a third
+          (900, 900, 272, 3, 3), (900, 900, 140, 3, 3), (2048, 2048, 272, 3, 2), (2048, 2048, 400, 2, 3), (1024, 1024, 600, 2, 3),
+          (1024, 1024, 1000, 3, 3), (2048, 2000, 560, 2, 2)]
 
 
 @pytest.mark.parametrize("I,H,B,k_w,k_a", SHAPES)
