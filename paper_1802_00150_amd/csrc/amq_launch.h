@@ -367,8 +367,9 @@ bool seqw_supported(long long I, long long H, long long B, int k_w, int k_a, int
 hipError_t launch_seqw(SeqWArgs a, const SeqWScratch& w, int k_w, int k_a, int epi, hipStream_t s);
 
 // Where the chip has no workgroup for every tile of the batch: groups of tiles take turns (amq_seqw_tiles.hip).  The number of
-// workgroups of such a launch (0: not taken), and the launch itself, between those of launch_seqw.
-long long seqw_tiles_grid(long long I, long long H, long long B, int k_w, int k_a, int epi);
+// workgroups of such a launch (0: not taken; kAnySteps: that of a shape that is), and the launch itself, between those of launch_seqw.
+constexpr long long kAnySteps = 1LL << 40;
+long long seqw_tiles_grid(long long I, long long H, long long B, int k_w, int k_a, int epi, long long steps);
 hipError_t launch_seqw_tiles(const SeqWArgs& a, int k_w, int k_a, int epi, hipStream_t s);
 
 // What follows such a launch, on its own (flag, saved state and input codes in a): if the flag is set, the piece is

@@ -555,18 +555,11 @@ SeqWScratch seqw_scratch(void* base, long long H, long long B, int k_a) {
   return w;
 }
 
-// Steps from which on the tiles of a batch take turns rather than launches each step: the launch costs about 20 us before its first
-// step (claim, cleared pairs, weights, what follows it) that the per-step form has not, and saves 1.5 to 6 us per step.  us, per-step
-// form / here, W2/A2: 1024 units batch 80 4 steps 38.2 / 41.8, 6 steps 54.3 / 54.7, 8 steps 71.2 / 67.5; 1500 units batch 64 48.1 / 51.2,
-// 68.5 / 69.1, 88.6 / 86.3; 512 units batch 200 36.3 / 38.5, 53.6 / 49.6, 70.1 / 60.9; 1024 batch 80 W3/A3 46.6 / 52.1, 67.4 / 69.7,
-// 88.2 / 88.9 and 12 steps 130 / 124.
-constexpr long long kTiledSteps = 8;
-
 bool seqw_supported(long long I, long long H, long long B, int k_w, int k_a, int epi, long long steps) {
   if (B < 2 || I <= 0 || H <= 0 || I > 2048 || H > 2048 || k_w < 1 || k_w > 3 || k_a < 1 || k_a > 3) return false;
   if (B > 16 * 256) return false;
   return run(nullptr, I, H, B, k_w, k_a, epi, nullptr) == hipSuccess ||
-         (steps >= kTiledSteps && seqw_tiles_grid(I, H, B, k_w, k_a, epi) > 0);
+         seqw_tiles_grid(I, H, B, k_w, k_a, epi, steps) > 0;
 }
 
 hipError_t launch_seqw(SeqWArgs a, const SeqWScratch& w, int k_w, int k_a, int epi, hipStream_t s) {
@@ -581,7 +574,7 @@ hipError_t launch_seqw(SeqWArgs a, const SeqWScratch& w, int k_w, int k_a, int e
   const bool one = run(nullptr, a.x.n, a.H, a.batch, k_w, k_a, epi, nullptr) == hipSuccess;  // a workgroup per tile fits
   const dim3 grid = seqw_grid(a.H, a.batch);
   const ResidentClaim claim =
-      resident_claim(one ? (long long)grid.x * grid.y : seqw_tiles_grid(a.x.n, a.H, a.batch, k_w, k_a, epi), false);
+      resident_claim(one ? (long long)grid.x * grid.y : seqw_tiles_grid(a.x.n, a.H, a.batch, k_w, k_a, epi, kAnySteps), false);
   std::lock_guard<std::mutex> together(resident_launches());
   hipLaunchKernelGGL(seqw_reset_kernel, dim3(blocks < 512 ? blocks : 512), dim3(256), 0, s, w.flag, claim, w.hbuf, pairs);
   hipError_t e = hipGetLastError();

@@ -426,6 +426,13 @@ int units_that_fit() {
   return fit;
 }
 
+// Steps from which on the tiles of a batch take turns rather than launches each step: the launch costs about 20 us before its first
+// step (claim, cleared pairs, weights, what follows it) that the per-step form has not, and saves 1.5 to 6 us per step.  us, per-step
+// form / here, W2/A2: 1024 units batch 80 4 steps 38.2 / 41.8, 6 steps 54.3 / 54.7, 8 steps 71.2 / 67.5; 1500 units batch 64 48.1 / 51.2,
+// 68.5 / 69.1, 88.6 / 86.3; 512 units batch 200 36.3 / 38.5, 53.6 / 49.6, 70.1 / 60.9; 1024 batch 80 W3/A3 46.6 / 52.1, 67.4 / 69.7,
+// 88.2 / 88.9 and 12 steps 130 / 124.
+constexpr long long kTiledSteps = 8;
+
 // Where this is ahead of what else such a batch takes (two launches per step, amq_step.hip, amq_mfma32_cell.hip).  us per step, that
 // form / here, W2/A2 and W3/A3 (LSTM, 35 steps):
 //   2 tiles each: 512 units batch 256 9.3 / 7.0 and 11.3 / 9.2; 650 batch 192 10.2 / 7.4 and 12.8 / 9.9; 1024 batch 128 9.3 / 7.5 and
@@ -436,24 +443,29 @@ int units_that_fit() {
 // Not: more tiles than that (1500 units batch 192 20.9 / 24.4).  Where workgroups quantize two entries of a step, the price of the second
 // is Alg. 2 again: at 4 tiles each that is too much (800 units batch 256 12.9 / 13.7), below 512 units at 3-bit activations also
 // (450 units batch 160 W2/A3 9.6 / 10.0), and three entries always.  On two stretches with 3 bits registers run out (spilled: 40 to 97):
-// W3/A3 at 1500 units batch 64 14.2 / 16.5, W2/A3 11.9 / 13.2, while W3/A2 is ahead up to 3 tiles (batch 96 19.7 / 15.7).  And as long as
+// W3/A3 at 1500 units batch 64 14.2 / 16.5, W2/A3 11.9 / 13.2, while W3/A2 (47 to 51 spilled, 148 to 156 bytes per lane) is ahead with 3
+// tiles (batch 96 19.7 / 15.7) but not with 2 (2048 units batch 48 LSTM 13.1 / 13.7, GRU 12.7 / 14.1; 12 steps 13.3 / 14.8 and 12.8 / 15.0).
+// On one stretch W3/A2 spills 15 registers (64 bytes) and is ahead all the same (1024 units batch 80 9.6 / 8.2, 192 17.2 / 11.1).  Two tiles
+// on two stretches are the only ones for which the launch's own cost shows beyond 8 steps (2048 units batch 48, inputs of 300, 8 steps 4 to
+// 6 % behind): from 12 on.  And as long as
 // the per-step launch has a wave of workgroups for all tiles (two per compute unit) three tiles on two stretches are not ahead either
 // (1500 units batch 80 11.0 / 11.8).
-bool worth_it(int k_w, int k_a, int nc, long long width, long long tiles, long long each) {
+bool worth_it(int k_w, int k_a, int nc, long long width, long long tiles, long long each, long long steps) {
   const long long entries = each * kTileB;
   if (each > kMostTiles || entries > 2 * width || (each == 4 && entries > width)) return false;
   if (nc == 1) return k_a == 2 || width >= 32;
-  return each == 2 || (tiles * width > 512 && (each == 3 || k_w == 2));
+  if (each == 2) return k_w == 2 && steps >= 12;
+  return tiles * width > 512 && (each == 3 || k_w == 2);
 }
 
 // launch == nullptr: only asks for the grid (0: not taken)
 template <int KW, int KA, int EPI, int NC>
-dim3 run_one(const SeqWArgs* launch, long long H, long long batch, hipStream_t s) {
+dim3 run_one(const SeqWArgs* launch, long long H, long long batch, long long steps, hipStream_t s) {
   const long long width = (H + 4 * kWBlocks - 1) / (4 * kWBlocks), tiles = (batch + kTileB - 1) / kTileB;
   const long long room = units_that_fit<KW, KA, EPI, NC>() / width;
   if (room == 0) return dim3(0);
   const long long each = (tiles + room - 1) / room;
-  if (!worth_it(KW, KA, NC, width, tiles, each)) return dim3(0);
+  if (!worth_it(KW, KA, NC, width, tiles, each, steps)) return dim3(0);
   const dim3 grid((unsigned)width, (unsigned)((tiles + each - 1) / each));
   if (launch)
     hipLaunchKernelGGL((seqw_tiles_kernel<KW, KA, EPI, NC>), grid, dim3(64 * kWWaves),
@@ -462,37 +474,38 @@ dim3 run_one(const SeqWArgs* launch, long long H, long long batch, hipStream_t s
 }
 
 template <int KW, int KA, int EPI>
-dim3 run_k(const SeqWArgs* l, long long H, long long batch, int nc, hipStream_t s) {
-  if (nc == 1) return run_one<KW, KA, EPI, 1>(l, H, batch, s);
-  if constexpr (KA == 2) return run_one<KW, KA, EPI, 2>(l, H, batch, s);
+dim3 run_k(const SeqWArgs* l, long long H, long long batch, long long steps, int nc, hipStream_t s) {
+  if (nc == 1) return run_one<KW, KA, EPI, 1>(l, H, batch, steps, s);
+  if constexpr (KA == 2) return run_one<KW, KA, EPI, 2>(l, H, batch, steps, s);
   return dim3(0);
 }
 
 template <int KW, int KA>
-dim3 run_epi(const SeqWArgs* l, long long H, long long batch, int epi, int nc, hipStream_t s) {
-  return epi == kEpiLstm ? run_k<KW, KA, kEpiLstm>(l, H, batch, nc, s) : run_k<KW, KA, kEpiGru>(l, H, batch, nc, s);
+dim3 run_epi(const SeqWArgs* l, long long H, long long batch, long long steps, int epi, int nc, hipStream_t s) {
+  return epi == kEpiLstm ? run_k<KW, KA, kEpiLstm>(l, H, batch, steps, nc, s) : run_k<KW, KA, kEpiGru>(l, H, batch, steps, nc, s);
 }
 
-dim3 run(const SeqWArgs* l, long long I, long long H, long long batch, int k_w, int k_a, int epi, hipStream_t s) {
+dim3 run(const SeqWArgs* l, long long I, long long H, long long batch, int k_w, int k_a, int epi, long long steps, hipStream_t s) {
   const int nc = (I > H ? I : H) > 1024 ? 2 : 1;
   switch (k_w * 4 + k_a) {
-    case 4 * 2 + 2: return run_epi<2, 2>(l, H, batch, epi, nc, s);
-    case 4 * 2 + 3: return run_epi<2, 3>(l, H, batch, epi, nc, s);
-    case 4 * 3 + 2: return run_epi<3, 2>(l, H, batch, epi, nc, s);
-    case 4 * 3 + 3: return run_epi<3, 3>(l, H, batch, epi, nc, s);
+    case 4 * 2 + 2: return run_epi<2, 2>(l, H, batch, steps, epi, nc, s);
+    case 4 * 2 + 3: return run_epi<2, 3>(l, H, batch, steps, epi, nc, s);
+    case 4 * 3 + 2: return run_epi<3, 2>(l, H, batch, steps, epi, nc, s);
+    case 4 * 3 + 3: return run_epi<3, 3>(l, H, batch, steps, epi, nc, s);
   }
   return dim3(0);
 }
 
 }  // namespace
 
-long long seqw_tiles_grid(long long I, long long H, long long B, int k_w, int k_a, int epi) {
-  const dim3 grid = run(nullptr, I, H, B, k_w, k_a, epi, nullptr);
+long long seqw_tiles_grid(long long I, long long H, long long B, int k_w, int k_a, int epi, long long steps) {
+  if (steps < kTiledSteps) return 0;
+  const dim3 grid = run(nullptr, I, H, B, k_w, k_a, epi, steps, nullptr);
   return (long long)grid.x * grid.y;
 }
 
 hipError_t launch_seqw_tiles(const SeqWArgs& a, int k_w, int k_a, int epi, hipStream_t s) {
-  if (run(&a, a.x.n, a.H, a.batch, k_w, k_a, epi, s).x == 0) return hipErrorInvalidValue;
+  if (run(&a, a.x.n, a.H, a.batch, k_w, k_a, epi, kAnySteps, s).x == 0) return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

@@ -39,7 +39,9 @@ def case(amq, gates, I, H, B, k_w, k_a, steps):
     (4, 2048, 2048, 33, 3, 2, 8), (4, 2048, 2048, 40, 2, 2, 8), (3, 2047, 2040, 97, 2, 2, 10), (3, 300, 2048, 128, 2, 2, 18),
     (4, 200, 260, 330, 2, 2, 14), (4, 129, 500, 200, 3, 3, 8), (3, 2048, 520, 161, 3, 2, 9), (4, 1025, 650, 112, 2, 2, 37),
     (4, 650, 650, 256, 3, 3, 11), (3, 1500, 1500, 48, 2, 2, 8), (4, 650, 1500, 96, 3, 2, 9), (4, 16, 650, 113, 2, 3, 8),
-    (4, 300, 300, 256, 2, 3, 8), (4, 2048, 2048, 129, 2, 2, 8), (3, 800, 800, 512, 2, 2, 9)])
+    (4, 300, 300, 256, 2, 3, 8), (4, 2048, 2048, 129, 2, 2, 8), (3, 800, 800, 512, 2, 2, 9),
+    # two tiles on two stretches: 12 steps and fewer
+    (4, 2048, 2048, 40, 2, 2, 12), (3, 1500, 1500, 48, 2, 2, 13), (4, 1100, 1300, 70, 2, 2, 11)])
 def test_same_bits_as_batches_that_fit(amq, gates, I, H, B, k_w, k_a, steps):
     import torch
     for T in (2, 0):
