@@ -447,15 +447,16 @@ constexpr long long kTiledSteps = 8;
 // tiles (batch 96 19.7 / 15.7) but not with 2 (2048 units batch 48 LSTM 13.1 / 13.7, GRU 12.7 / 14.1; 12 steps 13.3 / 14.8 and 12.8 / 15.0).
 // On one stretch W3/A2 spills 15 registers (64 bytes) and is ahead all the same (1024 units batch 80 9.6 / 8.2, 192 17.2 / 11.1).  Two tiles
 // on two stretches are the only ones for which the launch's own cost shows beyond 8 steps (2048 units batch 48, inputs of 300, 8 steps 4 to
-// 6 % behind): from 12 on.  And as long as
-// the per-step launch has a wave of workgroups for all tiles (two per compute unit) three tiles on two stretches are not ahead either
-// (1500 units batch 80 11.0 / 11.8).
+// 6 % behind): from 12 on.  And as long as the per-step launch has one round of workgroups for all tiles, two per compute unit and a
+// few, three tiles are not ahead either (1500 units batch 80 11.0 / 11.8, 700 batch 176 W3/A3 12.5 / 14.7, 600 batch 208 W2/A3 11.4 /
+// 13.4, 740 batch 176 W3/A3, 517 workgroups, 12.4 / 13.8; 606 batch 224, 532, 19.4 / 14.0), save for W2/A2 with one entry of a step per
+// workgroup (872 batch 144 8 % ahead).
 bool worth_it(int k_w, int k_a, int nc, long long width, long long tiles, long long each, long long steps) {
   const long long entries = each * kTileB;
   if (each > kMostTiles || entries > 2 * width || (each == 4 && entries > width)) return false;
+  if (each > 2 && tiles * width <= 520) return nc == 1 && k_w * k_a == 4 && entries <= width;
   if (nc == 1) return k_a == 2 || width >= 32;
-  if (each == 2) return k_w == 2 && steps >= 12;
-  return tiles * width > 512 && (each == 3 || k_w == 2);
+  return each == 2 ? k_w == 2 && steps >= 12 : each == 3 || k_w == 2;
 }
 
 // launch == nullptr: only asks for the grid (0: not taken)

@@ -41,7 +41,9 @@ def case(amq, gates, I, H, B, k_w, k_a, steps):
     (4, 650, 650, 256, 3, 3, 11), (3, 1500, 1500, 48, 2, 2, 8), (4, 650, 1500, 96, 3, 2, 9), (4, 16, 650, 113, 2, 3, 8),
     (4, 300, 300, 256, 2, 3, 8), (4, 2048, 2048, 129, 2, 2, 8), (3, 800, 800, 512, 2, 2, 9),
     # two tiles on two stretches: 12 steps and fewer
-    (4, 2048, 2048, 40, 2, 2, 12), (3, 1500, 1500, 48, 2, 2, 13), (4, 1100, 1300, 70, 2, 2, 11)])
+    (4, 2048, 2048, 40, 2, 2, 12), (3, 1500, 1500, 48, 2, 2, 13), (4, 1100, 1300, 70, 2, 2, 11),
+    # three tiles of 484, 517 and 532 workgroups per step, and of 495 with one entry of a step per workgroup
+    (4, 700, 700, 176, 3, 3, 8), (3, 740, 740, 176, 2, 3, 8), (4, 606, 606, 224, 3, 2, 8), (3, 872, 872, 144, 2, 2, 8)])
 def test_same_bits_as_batches_that_fit(amq, gates, I, H, B, k_w, k_a, steps):
     import torch
     for T in (2, 0):
