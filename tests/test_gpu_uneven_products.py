@@ -34,7 +34,9 @@ def operands(amq, m, n, B, k_w, k_a):
                                            # either side of the lines that the padding of columns and the rounding of
                                            # blocks draw: batch 48, a full batch and one more, 13 blocks in rounds of 4
                                            (42000, 900, 48, 2, 3), (42000, 900, 49, 2, 3), (16000, 1024, 128, 3, 2),
-                                           (16000, 1024, 129, 3, 2), (10000, 1024, 300, 3, 3), (10000, 1024, 384, 3, 3)])
+                                           (16000, 1024, 129, 3, 2), (10000, 1024, 300, 3, 3), (10000, 1024, 384, 3, 3),
+                                           # columns of Y that begin at any multiple of four bytes
+                                           (9997, 1024, 400, 3, 3), (9998, 800, 300, 2, 3), (9999, 1500, 65, 2, 2)])
 def test_outputs(amq, m, n, B, k_w, k_a):
     W, _, X, bias, ref = operands(amq, m, n, B, k_w, k_a)
     tol = 1e-4 * ref.abs() + 1e-4 * ref.pow(2).mean(1, keepdim=True).sqrt()
