@@ -546,7 +546,7 @@ __device__ __forceinline__ void quantize_magnitudes(const float (&x)[NJ], int n,
   int u[NJ];                     // order-preserving integer of |w| with the tie rule folded in
   // w: as the binary64 value that the additions take, or (where registers are what limits the waves) as the binary32 value,
   // converted at every use
-  constexpr bool kNarrow = NJ > 16 || (K == 2 && NW > 1);
+  constexpr bool kNarrow = NJ > 16 || (K == 2 && NW > 1) || (K == 4 && NW == 16);
   using Held = typename std::conditional<kNarrow, float, double>::type;
   Held held[NJ];
   auto wide = [&](int j) {
