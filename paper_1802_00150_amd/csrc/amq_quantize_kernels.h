@@ -44,7 +44,7 @@ constexpr bool wide_ahead(int k, bool recon, int nw, int nj, int vectors) {
   if (recon && k == 2 && nj > (nw == 1 ? 24 : 20)) return false;  // (bound by its stores: 16384 x 1700 36.1 against 37.1)
   if (nw == 2 && nj > 24)  // (4096 entries, k = 2: 8192 vectors 33.6 against 33.8, 4096 19.2 against 20.0)
     return vectors >= (recon ? 4096 : k == 3 ? 8192 : 12288);
-  if (nw == 2 && nj > 20 && (k == 2 || (recon && k == 3))) return vectors >= 4096;  // (2500 x 2900 5 and 11 % behind)
+  // (2500 vectors of 2900 entries are 5 % behind at k = 2, of 2816 and 3072, whose slots are all full, 5 to 13 % ahead)
   // Rounds of two waves per SIMD against two waves per vector in rounds of three: 1536 vectors are one of the latter (18.7 against
   // 17.0 at 2048 entries), 2048 one of the former, and some more leave its second nearly empty (2200 29.6 against 27.4)
   if (k == 4 && nw == 1 && nj > (recon ? 28 : 24)) return (vectors > 1536 && vectors <= 2048) || vectors >= 2700;
@@ -77,7 +77,7 @@ bool launch_wide(const QuantArgs& a, int total, int nw, int nj, hipStream_t s) {
 // the algorithm made for that.  It buys its short chain with every wave of a vector solving the same small systems, so it
 // ends where those waves no longer fit the chip side by side: about two vectors per compute unit, three at k = 3.  Beyond
 // 2048 entries it would take 16 waves per vector, whose exchange costs more than the slots that they save, already at one
-// vector.  Both give the same codes and coefficients, to the bit.  Measured, us, latency / throughput form, 512 and 700
+// vector (but for one range of lengths at k = 3, below).  Both give the same codes and coefficients, to the bit.  Measured, us, latency / throughput form, 512 and 700
 // vectors: 300 entries k = 2 3.48 / 3.06 (reconstruction) and 3.97 / 3.11, k = 4 7.97 / 6.06 and 10.3 / 6.1; 650 entries k = 2
 // 3.64 / 3.67 and 4.17 / 3.78, k = 3 at 700 5.18 / 5.38 and at 1000 6.03 / 5.42, k = 4 8.67 / 9.26 and 10.9 / 9.3; 2048 entries
 // k = 2 4.71 / 4.82 and 5.76 / 4.88.  4096 entries, 1 and 512 vectors: k = 2 4.37 / 3.92 and 8.05 / 4.98, k = 3 6.17 / 5.94 and
@@ -101,6 +101,14 @@ hipError_t launch_k(const QuantArgs& a, int max_n, hipStream_t s) {
     else if (nslots <= 16) launch_one<K, 4, 4, true, RECON>(a, total, s);
     else launch_one<K, 4, 8, true, RECON>(a, total, s);
     return hipGetLastError();
+  }
+  if constexpr (K == 3 && !RECON) {
+    // As long as every vector has a compute unit, and 16 slots of four waves are not all full: 16 and 250 vectors of 3840 entries
+    // 6.77 / 7.33 and 7.12 / 7.5, 300 11.7 / 7.9; 16 of 4096 6.66 / 6.43
+    if (nslots > 56 && nslots <= 64 && max_n < 4096 && nvec <= 256) {
+      launch_one<K, 4, 16, true, RECON>(a, total, s);
+      return hipGetLastError();
+    }
   }
   if constexpr (K >= 2) {
     const int nw = nslots <= 32 ? 1 : 2, nj = (nslots + nw - 1) / nw;

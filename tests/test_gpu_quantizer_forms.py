@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("k", [1, 2, 3, 4])
-@pytest.mark.parametrize("n", [1, 64, 65, 128, 129, 511, 513, 896, 897, 1023, 1024, 1025, 2047, 2048, 2049, 2176, 3001, 4095, 4096])
+@pytest.mark.parametrize("n", [1, 64, 65, 128, 129, 511, 513, 896, 897, 1023, 1024, 1025, 2047, 2048, 2049, 2176, 3001, 3584, 3585, 4095, 4096])
 def test_few_and_many_vectors_alike(k, n):
     import torch
 
@@ -24,7 +24,7 @@ def test_few_and_many_vectors_alike(k, n):
         pr, ar = oracle.quantize_rows(first, k, T)
         assert_coef_close(host(A[:5]), ar)
         compare_codes(first, planes_host(P[:, :5].contiguous()), pr, ar)
-        for rows in (1, 3, 599, 600, 767):                       # the line: 600 vectors, 768 at k = 3 and some lengths
+        for rows in (1, 3, 256, 257, 599, 600, 767):  # the line: 600 vectors, 768 at k = 3 and some lengths, 256 beyond 2048
             print("forms k=%d n=%d T=%d rows=%d" % (k, n, T, rows), flush=True)
             p, a = amq.quantize_activations(X[:rows].contiguous(), k, T)
             assert torch.equal(p, P[:, :rows]) and torch.equal(a, A[:rows])
