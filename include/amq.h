@@ -212,7 +212,7 @@ int amq_stream_read_probe(const void* buf, size_t bytes, void* sink, void* strea
 size_t amq_lstm_sequence_flag_offset(int64_t I, int64_t H, int64_t B, int k_a);
 /*
  * Workspace of the faster forms of amq_lstm_sequence (B = 1 needs no more than amq_lstm_workspace_bytes).  Where the grid fits the chip (vectors of at most
- * 2048 entries, 1- to 3-bit codes, about 4096 hidden units times batch tiles of 16) or, from 8 steps on, two to four tiles
+ * 2048 entries, 1- to 3-bit codes, about 4096 hidden units times batch tiles of 16) or, from 8 or 12 steps on, two to four tiles
  * can take turns on a workgroup (2- and 3-bit codes; how far, is measured: amq_seqw_tiles.hip), pieces of about 4096 / B steps
  * run in one launch whose workgroups stay resident and exchange h_t and its codes through the workspace.  Such
  * launches (and those of batch 1) share a device: on several streams they run side by side as far as their workgroups

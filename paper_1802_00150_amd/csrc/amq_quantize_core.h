@@ -267,8 +267,9 @@ __device__ __forceinline__ void block_totals(double (&v)[NV], double (*sh)[16 * 
 //     247 / 403 -> 229 / 371, 42000 x 300 67 / 130 -> 57 / 109).
 // Bound: vector-instruction issue at k >= 3 and HBM at k <= 2 for many vectors, the chain of reductions for a few.
 // Measured (us) against the form that compared w with all midpoints and selected +-w per plane, k = 2 / 3 / 4:
-// 16384 x 4096 135 / 239 / 443 -> 69 / 127 / 290, 4096 x 2048 33 / 54 / 100 -> 10.8 / 19.8 / 41, 128 vectors of 1024
-// (launches back to back) 4.4 / 5.9 / 10.1 -> 3.4 / 4.4 / 6.7.
+// 16384 x 4096 135 / 239 / 443 -> 65 / 122 / 285, 4096 x 2048 33 / 54 / 100 -> 9.9 / 18.1 / 36, 128 vectors of 1024
+// 4.4 / 5.9 / 10.1 -> 3.4 / 4.0 / 6.7 (normal values, launches back to back; with an event around each and heavy tails
+// 16384 x 4096 takes 73 / 133 / 298).
 
 // A value the compiler must take as new: keeps it from holding the comparison masks of one pass in scalar registers
 // for a later pass (16 slots of them spill), where forming them again is one comparison.

@@ -231,7 +231,10 @@ hipError_t run_form(const Seq1Args& a, hipStream_t s) {
 }
 
 // How many slots of 64 entries a lane of the quantizing waves holds: as many as H needs, so that no slot is computed for
-// nothing.  Up to 512 units a wave is on its own, beyond four share the work: at 512 units one wave takes 2.88 (W2/A2) and
+// nothing.  What the forms between are worth, us per step W2/A2 / W3/A3 with the next larger of 4, 6, 8 (one wave), 4 (four
+// waves) or 8 (two units per lane) instead: 300 units LSTM 2.58 -> 2.60 / 3.19 -> 3.35, GRU 2.54 -> 2.65 / 3.26 -> 3.47, 448 units 2.71
+// -> 2.80 / 3.44 -> 3.55, 768 3.12 -> 3.17 / 3.73 -> 3.89, 1200 3.40 -> 3.71 / 4.54 -> 5.08, 1500 3.47 -> 3.70 / 4.71 -> 5.11, 1700 3.61 ->
+// 3.73 / 4.85 -> 5.12; 500 units with inputs of 1500 3.07 -> 3.29 / 4.09 -> 4.47.  Up to 512 units a wave is on its own, beyond four share the work: at 512 units one wave takes 2.88 (W2/A2) and
 // 3.68 us (W3/A3) per step against 2.97 and 4.24 for four, and at 640 its chain is the longer one.  Vectors above 1024
 // entries take 16 lanes per row and gate and two units per lane, so that 2048 units are 256 workgroups; there four waves
 // always share the work (fewer forms; 300 units with inputs of 1500: 2.97 against 2.81 us).
