@@ -20,8 +20,10 @@
 // The linear workgroup index is dealt out so that the workgroups of one XCD work on neighbouring row ranges: each
 // XCD's L2 then holds its share of the weights.
 //
-// Bound: two waves of a SIMD share it oldest first, so the second mostly fills the first one's epilogues; the matrix
-// cores are busy about 60 % of the time.  Measured (us), int8 or 16 x 16 kernel -> here: 10000 x 1500 W2/A2 at batch 256
+// Bound: power.  A wave alone in its contraction keeps the matrix cores busy at the 1.5 to 1.8 GHz that the chip then holds; a
+// better balance between the two waves of a SIMD (row blocks drawn by ticket: last end 28.8 -> 28.1 us) and fewer vector
+// instructions per output (a log-sum-exp without its maximum) change the time by less than 1 %, while the contraction's precedence
+// does (below).  Measured (us), int8 or 16 x 16 kernel -> here: 10000 x 1500 W2/A2 at batch 256
 // 35.9 -> 13.4, 6144 x 2048 W2/A2 batch 256 29.1 -> 15.6, 20000 x 2048 W3/A3 batch 40 33.9 -> 16.8, 2000 x 512 W2/A2
 // batch 1024 11.8 -> 7.3, 10000 x 650 W2/A3 batch 700 22.6 -> 19.1, 10000 x 1024 W2/A3 batch 1024 34.5 -> 32.5.
 #pragma once
@@ -67,6 +69,12 @@ __host__ __device__ constexpr size_t lds_bytes(int kw, int ka, int nt, int n) {
 // output per column.
 enum { kOutY = 0, kOutYLse = 1, kOutScore = 2 };
 
+// Where the columns of a (k-block, piece) of the image begin: no two pieces of a row of up to 8 meet in a bank.
+template <int NP>
+__device__ __forceinline__ int swizzle(int half, int p) {
+  return NP > 0 ? 8 * half | (NP == 2 ? 4 : 2) * p : 0;
+}
+
 template <int N, int I = 0, typename F>
 __device__ __forceinline__ void static_for(F f) {
   if constexpr (I < N) {
@@ -107,35 +115,53 @@ __global__ __launch_bounds__(64 * kWaves) void mfma32_kernel(BmvArgs a, int rb_p
     for (int i = 0; i < KW; ++i) w[i] = at[i * plane];
   };
 
-  // ---- stage the activation operands: item -> (tile, plane, piece, k-block, column), columns adjacent; the
-  // requests of a thread go out together (four at a time for long vectors), the first weight pieces behind them
+  // ---- stage the activation operands.  Rows of up to 8 pieces: item -> (tile, plane, column, piece), pieces adjacent, so that a
+  // request takes whole rows, and the weights after the first piece are asked for when every wave has asked for its share of the
+  // image.  (Columns adjacent, 16 bytes of 64 rows per request, and all weights behind them: the image is complete 3.3 us after
+  // the start, not 2.2; 10000 x 1024 W2/A3 batch 256 13.4 us, not 12.5.)  Column c of (k-block, piece) lies at c ^ swizzle: the
+  // writes of 16 lanes then meet all banks, and so do the reads.
+  // Longer rows: columns adjacent, four requests of a thread at a time, the first weight pieces behind them (pieces adjacent:
+  // 0 to 8 % slower, 8475 x 2068 W3/A3 batch 99 24.0 / 24.9).
   uint4 w[kRing][KW];
   {
     const uint4* Xp4 = reinterpret_cast<const uint4*>(a.blk[0].Xp);
     uint4* dst = reinterpret_cast<uint4*>(smem);
     const int items = NT * KA * np * 64;
     constexpr int kBatch = NP > 0 ? (NT * KA * NP * 64 + 64 * kWaves - 1) / (64 * kWaves) : 4;  // (NP > 0: all of them)
+    struct Item {
+      unsigned tj, col, half, p;
+    };
+    auto item = [&](unsigned e) {
+      Item x;
+      if constexpr (NP > 0) {
+        const unsigned q = e / (2u * NP), g = e % (2u * NP);
+        x = Item{q / kTileN, q % kTileN, g / NP, g % NP};
+      } else {
+        const unsigned q = e >> 6;
+        x = Item{q / (unsigned)np, e & 31, (e >> 5) & 1, q % (unsigned)np};
+      }
+      return x;
+    };
     for (int e0 = 0; e0 < items; e0 += kBatch * 64 * kWaves) {  // (uniform)
       uint4 xw[kBatch];
 #pragma unroll
       for (int v = 0; v < kBatch; ++v) {
-        const unsigned e = min(e0 + tid + v * 64 * kWaves, items - 1);
-        const unsigned q = e >> 6, p = q % (unsigned)np, tj = q / (unsigned)np;
-        const int col = bg0 + (int)(tj / KA) * kTileN + (int)(e & 31), g = (int)(((e >> 5) & 1) * np + p);
-        xw[v] = Xp4[((size_t)(tj % KA) * batch + (col < batch ? col : batch - 1)) * wq + (g < wq ? g : 0)];
+        const Item x = item(min(e0 + tid + v * 64 * kWaves, items - 1));
+        const int col = bg0 + (int)(x.tj / KA) * kTileN + (int)x.col, g = (int)x.half * np + (int)x.p;
+        xw[v] = Xp4[((size_t)(x.tj % KA) * batch + (col < batch ? col : batch - 1)) * wq + (g < wq ? g : 0)];
       }
       if (e0 == 0) {
 #pragma unroll
-        for (int p = 0; p < kRing; ++p) request(rb_first + wv, p, w[p]);
+        for (int p = 0; p < (NP > 0 ? 1 : kRing); ++p) request(rb_first + wv, p, w[p]);
       }
 #pragma unroll
       for (int v = 0; v < kBatch; ++v) {
         const unsigned e = e0 + tid + v * 64 * kWaves;
         if (e < (unsigned)items) {
-          const unsigned q = e >> 6, p = q % (unsigned)np, tj = q / (unsigned)np;
-          const int g = (int)(((e >> 5) & 1) * np + p);
+          const Item x = item(e);
+          const int g = (int)x.half * np + (int)x.p;
           const uint32_t ws[4] = {xw[v].x, xw[v].y, xw[v].z, xw[v].w};
-          uint4* d = dst + (tj * steps + 4 * p) * 64 + (e & 63);
+          uint4* d = dst + (x.tj * steps + 4 * x.p) * 64 + 32 * x.half + (x.col ^ swizzle<NP>(x.half, x.p));
           if (128 * (g + 1) <= n) {
 #pragma unroll
             for (int s = 0; s < 4; ++s) d[s * 64] = expand4_signed(ws[s]);
@@ -149,6 +175,10 @@ __global__ __launch_bounds__(64 * kWaves) void mfma32_kernel(BmvArgs a, int rb_p
           }
         }
       }
+    }
+    if constexpr (NP > 0) {
+#pragma unroll
+      for (int p = 1; p < kRing; ++p) request(rb_first + wv, p, w[p]);
     }
   }
 
@@ -177,23 +207,25 @@ __global__ __launch_bounds__(64 * kWaves) void mfma32_kernel(BmvArgs a, int rb_p
     lse_m[t] = kLseLow;
     lse_s[t] = 0.0f;
   }
-  const uint4* const img = reinterpret_cast<const uint4*>(smem) + lane;
+  const uint4* const img = reinterpret_cast<const uint4*>(smem) + 32 * kb;
   float* const mine = reinterpret_cast<float*>(smem + image_bytes(KA, NT, n)) + wv * kTileN * (KW + 1);
-  __syncthreads();
+  if constexpr (NP > 0) lds_barrier();  // (the weights under way are not waited for)
+  else __syncthreads();
 
   uint4 bop[NT][KA], bnx[NT][KA], aop[KW], anx[KW];
-  auto fetch = [&](int step, uint4 (&b)[NT][KA]) {
+  // column: this lane's place in the piece of the step
+  auto fetch = [&](int step, int column, uint4 (&b)[NT][KA]) {
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int j = 0; j < KA; ++j) b[t][j] = img[((t * KA + j) * steps + step) * 64];
+      for (int j = 0; j < KA; ++j) b[t][j] = img[((t * KA + j) * steps + step) * 64 + column];
   };
   auto expand = [&](const uint4 (&from)[KW], int word, uint4 (&to)[KW]) {
 #pragma unroll
     for (int i = 0; i < KW; ++i)
       to[i] = expand4_signed(word == 0 ? from[i].x : word == 1 ? from[i].y : word == 2 ? from[i].z : from[i].w);
   };
-  fetch(0, bop);
+  fetch(0, l32 ^ swizzle<NP>(kb, 0), bop);
   expand(w[0], 0, aop);
 
   for (int rb = rb_first + wv; rb < rb_end; rb += kWaves) {
@@ -210,13 +242,17 @@ __global__ __launch_bounds__(64 * kWaves) void mfma32_kernel(BmvArgs a, int rb_p
       bias_req = a.bias0 ? a.bias0[bi < m ? bi : m - 1] : 0.0f;
     }
 
+    // Of the two waves of a SIMD the one in its contraction goes first; by age, a wave in its epilogue keeps the matrix cores from
+    // the younger one (42000 x 1024 W2/A2 batch 2240 scored 146 -> 136 us, 25433 x 445 W3/A3 batch 959 54.7 -> 51.8; longer rows
+    // +-2 %).
+    if constexpr (NP > 0) __builtin_amdgcn_s_setprio(2);
     v16f acc[NT][KW][KA];
-    // k-step s of the piece in `cur` (the piece after it in `nxt`): the operands of the following step are fetched and
-    // expanded under the matrix instructions
-    auto step = [&](int index, auto s_c, const uint4 (&cur)[KW], const uint4 (&nxt)[KW], auto first_c) {
+    // k-step s of the piece in `cur` (the piece after it in `nxt`): the operands of the following step are fetched (from
+    // `column` of its piece) and expanded under the matrix instructions
+    auto step = [&](int index, int column, auto s_c, const uint4 (&cur)[KW], const uint4 (&nxt)[KW], auto first_c) {
       constexpr int s = decltype(s_c)::value;
       constexpr bool FIRST = decltype(first_c)::value;
-      fetch(index + 1 == steps ? 0 : index + 1, bnx);
+      fetch(index + 1 == steps ? 0 : index + 1, column, bnx);
       if constexpr (s < 3) expand(cur, s + 1, anx); else expand(nxt, 0, anx);
 #pragma unroll
       for (int i = 0; i < KW; ++i)
@@ -241,10 +277,11 @@ __global__ __launch_bounds__(64 * kWaves) void mfma32_kernel(BmvArgs a, int rb_p
       for (int i = 0; i < KW; ++i) aop[i] = anx[i];
     };
     auto piece = [&](int p, const uint4 (&cur)[KW], const uint4 (&nxt)[KW], auto first_c) {
-      step(4 * p, std::integral_constant<int, 0>{}, cur, nxt, first_c);
-      step(4 * p + 1, std::integral_constant<int, 1>{}, cur, nxt, std::false_type{});
-      step(4 * p + 2, std::integral_constant<int, 2>{}, cur, nxt, std::false_type{});
-      step(4 * p + 3, std::integral_constant<int, 3>{}, cur, nxt, std::false_type{});
+      const int here = l32 ^ swizzle<NP>(kb, p), there = l32 ^ swizzle<NP>(kb, p + 1 == np ? 0 : p + 1);
+      step(4 * p, here, std::integral_constant<int, 0>{}, cur, nxt, first_c);
+      step(4 * p + 1, here, std::integral_constant<int, 1>{}, cur, nxt, std::false_type{});
+      step(4 * p + 2, here, std::integral_constant<int, 2>{}, cur, nxt, std::false_type{});
+      step(4 * p + 3, there, std::integral_constant<int, 3>{}, cur, nxt, std::false_type{});
     };
     // a ring slot is asked for its next piece as soon as it has been used up
     if constexpr (NP > 0) {
@@ -272,6 +309,7 @@ __global__ __launch_bounds__(64 * kWaves) void mfma32_kernel(BmvArgs a, int rb_p
     // (pinned in uniform control flow: the compiler takes a matrix instruction for lane-local and would sink it under
     // the store predicates)
     settle_accumulators<32>();
+    if constexpr (NP > 0) __builtin_amdgcn_s_setprio(0);
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
