@@ -11,8 +11,7 @@
 // tiles and only the per-output epilogue grows with the tile count.  A workgroup of 8 waves stages NBT * 16
 // batch entries (all planes) in LDS once and its waves walk over row blocks.  mfma4w_kernel works on
 // {-1, +1} codes (the staged activations hold 0.0 beyond the end of a vector), so its accumulators are the
-// dot products of the codes and no popcount enters; mfma4wc_kernel still uses {0, 1} codes with popcount
-// corrections.
+// dot products of the codes and no popcount enters, and so does mfma4wc_kernel.
 #include <type_traits>
 
 #include "amq_device.h"
@@ -24,17 +23,16 @@ namespace amq {
 namespace {
 
 constexpr int kWaves = 8;
+constexpr int kTurn = 9;  // 16-byte units per row in the piece of LDS that turns weight rows into operands (128 B + 16 B pad)
 
 // Contraction of one operand block of a row block with NBT staged batch tiles: units u = (k-step t,
 // tile bt); the LDS reads (and, when the step changes, the weight expansion) of unit u + 1 are
 // issued under the matrix instructions of unit u.  `tile` points at this lane's 16 bytes of step 0
 // of the block's first tile and plane ([tile][plane][kPlaneBytes] layout).
-template <int KW, int KA, int NBT, bool SIGNED = false>
+template <int KW, int KA, int NBT>
 __device__ __forceinline__ void contract_tiles(const uint4 (&araw)[KW][2], const unsigned char* tile,
                                                v4f (&acc)[NBT][KW][KA]) {
-  // weight words as {0, 1} codes, or as {-1, +1} codes (then the staged tiles are signed too and hold 0.0
-  // beyond the end of a vector, and the accumulators are the dot products of the codes themselves)
-  auto expand = [](uint32_t w) { return SIGNED ? expand4_signed(w) : expand4(w); };
+  // (the staged tiles hold 0.0 beyond the end of a vector, so the accumulators are the dot products of the codes)
 #pragma unroll
   for (int bt = 0; bt < NBT; ++bt)
 #pragma unroll
@@ -45,7 +43,7 @@ __device__ __forceinline__ void contract_tiles(const uint4 (&araw)[KW][2], const
 #pragma unroll
   for (int j = 0; j < KA; ++j) bop[j] = *reinterpret_cast<const uint4*>(tile + j * kPlaneBytes);
 #pragma unroll
-  for (int i = 0; i < KW; ++i) aop[i] = expand(word_of(araw[i], 0));
+  for (int i = 0; i < KW; ++i) aop[i] = expand4_signed(word_of(araw[i], 0));
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int u = 0; u < kSteps * NBT; ++u) {
@@ -57,7 +55,7 @@ __device__ __forceinline__ void contract_tiles(const uint4 (&araw)[KW][2], const
         bnx[j] = *reinterpret_cast<const uint4*>(tile + (bn * KA + j) * kPlaneBytes + tn * kTileB * 64);
       if (bn == 0) {
 #pragma unroll
-        for (int i = 0; i < KW; ++i) anx[i] = expand(word_of(araw[i], tn));
+        for (int i = 0; i < KW; ++i) anx[i] = expand4_signed(word_of(araw[i], tn));
       }
     }
 #pragma unroll
@@ -92,9 +90,8 @@ __device__ __forceinline__ void contract_tiles(const uint4 (&araw)[KW][2], const
       for (int j = 0; j < KA; ++j) asm volatile("" : "+v"(acc[bt][i][j]));
 }
 
-// Stages the packed activation words of one operand block (NBT * 16 batch entries from bg0 on,
-// KA planes) into LDS as 4-bit codes, [tile][plane][step][batch entry][k-block][16 B], and adds
-// leaves their popcounts in pops [tile][plane][batch entry].
+// The packed activation words of one operand block (NBT * 16 batch entries from bg0 on, KA planes): requests, and then, staged
+// in LDS as {-1, +1} 4-bit codes with 0.0 at the positions from nlen on, [tile][plane][step][batch entry][k-block][16 B].
 template <int KA, int NBT, int NTHREADS>
 __device__ __forceinline__ void load_activation_words(const uint32_t* Xp, int batch, int bg0, int wq,
                                                       uint4 (&xw)[(NBT * KA * kTileB * 8 + NTHREADS - 1) / NTHREADS]) {
@@ -112,12 +109,9 @@ __device__ __forceinline__ void load_activation_words(const uint32_t* Xp, int ba
     xw[it] = valid ? v : make_uint4(0, 0, 0, 0);
   }
 }
-// SIGNED: {-1, +1} codes with 0.0 at the positions from nlen on (no popcounts are needed then: pops may be
-// null).
-template <int KA, int NBT, int NTHREADS, bool SIGNED = false>
-__device__ __forceinline__ void stage_activation_words(
-    const uint4 (&xw)[(NBT * KA * kTileB * 8 + NTHREADS - 1) / NTHREADS], unsigned char* btile, int* pops,
-    int nlen = 0) {
+template <int KA, int NBT, int NTHREADS>
+__device__ __forceinline__ void stage_activation_words(const uint4 (&xw)[(NBT * KA * kTileB * 8 + NTHREADS - 1) / NTHREADS],
+                                                       unsigned char* btile, int nlen) {
   constexpr int kGroupB = NBT * kTileB;
   constexpr int kItems = NBT * KA * kTileB * 8;
   constexpr int kIter = (kItems + NTHREADS - 1) / NTHREADS;
@@ -127,32 +121,19 @@ __device__ __forceinline__ void stage_activation_words(
     const int q = e & 7, nn = (e >> 3) % kGroupB, j = (e >> 3) / kGroupB;
     const int bt = nn >> 4, n16 = nn & 15;
     const uint4 w4 = xw[it];
-    // popcount of the row: its 8 groups sit in 8 consecutive lanes (every lane takes part)
-    int pc = 0;
-    if constexpr (!SIGNED) pc = sum8(__popc(w4.x) + __popc(w4.y) + __popc(w4.z) + __popc(w4.w));
     if (e < kItems) {
-      if constexpr (!SIGNED) {
-        if (q == 0) pops[(bt * KA + j) * kTileB + n16] = pc;
-      }
       // words 4q .. 4q+3 of the row: k-block q >> 1, steps 4 * (q & 1) + 0..3
       uint4* dst = reinterpret_cast<uint4*>(btile + (bt * KA + j) * kPlaneBytes + ((4 * (q & 1)) * kTileB + n16) * 64 +
                                             (q >> 1) * 16);
-      if constexpr (SIGNED) {
-        // word 4q + c of the row holds positions 32 (4q + c) .. + 31
-        auto inside = [&](int c) {
-          const int left = nlen - 32 * (4 * q + c);
-          return left >= 32 ? 0xffffffffu : left <= 0 ? 0u : ((1u << left) - 1u);
-        };
-        dst[0 * kTileB * 4] = expand4_signed_valid(w4.x, inside(0));
-        dst[1 * kTileB * 4] = expand4_signed_valid(w4.y, inside(1));
-        dst[2 * kTileB * 4] = expand4_signed_valid(w4.z, inside(2));
-        dst[3 * kTileB * 4] = expand4_signed_valid(w4.w, inside(3));
-      } else {
-        dst[0 * kTileB * 4] = expand4(w4.x);
-        dst[1 * kTileB * 4] = expand4(w4.y);
-        dst[2 * kTileB * 4] = expand4(w4.z);
-        dst[3 * kTileB * 4] = expand4(w4.w);
-      }
+      // word 4q + c of the row holds positions 32 (4q + c) .. + 31
+      auto inside = [&](int c) {
+        const int left = nlen - 32 * (4 * q + c);
+        return left >= 32 ? 0xffffffffu : left <= 0 ? 0u : ((1u << left) - 1u);
+      };
+      dst[0 * kTileB * 4] = expand4_signed_valid(w4.x, inside(0));
+      dst[1 * kTileB * 4] = expand4_signed_valid(w4.y, inside(1));
+      dst[2 * kTileB * 4] = expand4_signed_valid(w4.z, inside(2));
+      dst[3 * kTileB * 4] = expand4_signed_valid(w4.w, inside(3));
     }
   }
 }
@@ -178,14 +159,11 @@ __global__ __launch_bounds__(64 * kWaves) void mfma4w_kernel(BmvArgs a, int rb_p
   int rb_end = rb_first + rb_per_wg;
   if (rb_end > rowblocks) rb_end = rowblocks;
 
-  // ---- prologue: packed activation words, 16 bytes per thread and round, coalesced.  Item e:
-  // group q = e % 8 of the row of batch entry (e / 8) % kGroupB of plane e / (8 kGroupB).
-  {
-    uint4 xw[kIter];
-    load_activation_words<KA, NBT, 64 * kWaves>(a.blk[0].Xp, batch, bg0, wq, xw);
-    stage_activation_words<KA, NBT, 64 * kWaves, true>(xw, btile, nullptr, nlen);
-    __syncthreads();
-  }
+  // ---- packed activation words, 16 bytes per thread and round, coalesced.  Item e: group q = e % 8 of the row of batch entry
+  // (e / 8) % kGroupB of plane e / (8 kGroupB).  Staged when the first weights have been asked for too (after the barrier instead:
+  // 42000 x 1024 W3/A3 batch 64 17.0 us, now 16.2, W2/A2 batch 32 10.1, 9.8).
+  uint4 xw[kIter];
+  load_activation_words<KA, NBT, 64 * kWaves>(a.blk[0].Xp, batch, bg0, wq, xw);
 
   // coefficients of this lane's batch column, one column per tile
   int bcol[NBT];
@@ -236,9 +214,15 @@ __global__ __launch_bounds__(64 * kWaves) void mfma4w_kernel(BmvArgs a, int rb_p
     const int bi = rbc * 16 + l16;
     bs = a.bias0 ? a.bias0[bi < m ? bi : m - 1] : 0.0f;
   };
+  // Of the two waves of a SIMD the one in its contraction goes first (by age, a wave in its epilogue keeps the matrix cores from the
+  // younger one), from more than four row blocks per wave on: W2/A2, us, 10000 x 900 batch 1000 25.0 -> 23.7, 42000 x 1024 batch 256
+  // 24.6 -> 23.5; with two or three 0 to 2 % slower (10000 x 1024 W3/A3 batch 128 12.7 / 12.9).
+  const bool contraction_first = rb_per_wg > 4 * kWaves;
   uint4 anext[KW][2];
   float coef_next, bias_next;
   request_rowblock(rb_first + wv, anext, coef_next, bias_next);
+  stage_activation_words<KA, NBT, 64 * kWaves>(xw, btile, nlen);
+  lds_barrier();  // (the weights under way are not waited for)
 
   for (int rb = rb_first + wv; rb < rb_end; rb += kWaves) {
     // ---- weight side of the row block, shared by all tiles
@@ -265,7 +249,9 @@ __global__ __launch_bounds__(64 * kWaves) void mfma4w_kernel(BmvArgs a, int rb_p
     }
     // ---- contraction with all tiles
     v4f acc[NBT][KW][KA];
-    contract_tiles<KW, KA, NBT, true>(araw, tile, acc);
+    if (contraction_first) __builtin_amdgcn_s_setprio(2);
+    contract_tiles<KW, KA, NBT>(araw, tile, acc);
+    if (contraction_first) __builtin_amdgcn_s_setprio(0);
 
     // ---- epilogue per tile, lane = (batch column l16, row quad l4): the accumulators are the dot products
     // d_ij of the codes (integers, exact in binary32);  y = sum_i alpha_i sum_j beta_j d_ij
@@ -371,10 +357,10 @@ __global__ __launch_bounds__(64 * NWV) void mfma4wc_kernel(BmvArgs a, int rb_per
   constexpr int kBlockBytes = NBT * KA * kPlaneBytes;
   constexpr int kIter = (NBT * KA * kTileB * 8 + 64 * NWV - 1) / (64 * NWV);
   unsigned char* btile = smem;                                        // [block][tile][plane][kPlaneBytes]
-  int* pops = reinterpret_cast<int*>(smem + 2 * kBlockBytes);         // [block][tile][plane][kTileB]
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint4* const mine = reinterpret_cast<uint4*>(smem + 2 * kBlockBytes) + wv * (kTileB * kTurn);  // this wave's piece
   const int l16 = lane & 15, l4 = lane >> 4;
   const int bg0 = blockIdx.y * kGroupB;
   const int batch = a.batch;
@@ -389,20 +375,58 @@ __global__ __launch_bounds__(64 * NWV) void mfma4wc_kernel(BmvArgs a, int rb_per
   int rb_end = rb_first + rb_per_wg;
   if (rb_end > rowblocks) rb_end = rowblocks;
 
-  {
-    uint4 xw[2][kIter];
+  uint4 xw[2][kIter];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) load_activation_words<KA, NBT, 64 * NWV>(a.blk[k].Xp, batch, bg0, wq[k], xw[k]);
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-      stage_activation_words<KA, NBT, 64 * NWV>(xw[k], btile + k * kBlockBytes, pops + k * NBT * KA * kTileB);
-    __syncthreads();
-  }
+  for (int k = 0; k < 2; ++k) load_activation_words<KA, NBT, 64 * NWV>(a.blk[k].Xp, batch, bg0, wq[k], xw[k]);
 
-  // per batch column of this lane (one per tile) and operand block: beta_j and n - 2 popc(x_j)
+  // Requests of a row block, all unconditional on clamped rows and units (what a row outside the matrix gives is not used, a piece
+  // past the end of a row meets 0.0 of the staged operand): weight words, whole rows of 128 bytes by 8 adjacent lanes (16 bytes of
+  // 64 rows per request keep the memory pipe busy four times as long), to be turned into the A view through LDS; row coefficients
+  // and biases, one value per lane (lane l < 16 KW: coefficient l % KW of tile row l / KW); previous state in the C view (lane =
+  // (unit l4, batch column l16)).  Those of the first row block go out before the activations are staged, those of the next one
+  // before the contraction of the current: asked for where they were used, the weights of either operand block and the
+  // coefficients cost a trip to memory each (W2/A2, us per step with its quantizer: LSTM 600 units batch 600 16.8 -> 14.6, GRU 1024
+  // units batch 256 with a projection of 10000 words 27.0 -> 26.5).
+  struct Row {
+    uint4 w[2][KW][2];
+    float coef[2], bias[2], prev[NBT];
+  };
+  auto request = [&](int rb, Row& r) {
+    rb = rb < rowblocks ? rb : rowblocks - 1;
+    auto matrix_row = [&](int tile_row) {
+      const int unit = rb * 4 + (tile_row >> 2), gate = tile_row & 3;
+      return (gate < NG ? gate : 0) * H + (unit < H ? unit : H - 1);
+    };
+    const int rows[2] = {matrix_row(lane >> 3), matrix_row(8 + (lane >> 3))}, row = matrix_row(l16);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const uint4* const Wp4 = reinterpret_cast<const uint4*>(a.blk[k].Wp) + ((lane & 7) < wq[k] ? (lane & 7) : 0);
+      const int plane = m * wq[k];
+#pragma unroll
+      for (int i = 0; i < KW; ++i)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) r.w[k][i][v] = Wp4[rows[v] * wq[k] + i * plane];
+    }
+    const int cl = lane < 16 * KW ? lane : 0, crow = matrix_row(cl / KW);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) r.coef[k] = a.blk[k].alpha[crow * KW + cl % KW];
+    r.bias[0] = a.bias0 ? a.bias0[row] : 0.0f;
+    r.bias[1] = (EPI == kEpiGru && a.bias1) ? a.bias1[row] : 0.0f;
+    const int unit = rb * 4 + l4;
+#pragma unroll
+    for (int bt = 0; bt < NBT; ++bt) {
+      const int col = bg0 + bt * kTileB + l16;
+      const int t = (col < batch ? col : batch - 1) * H + (unit < H ? unit : H - 1);
+      r.prev[bt] = (EPI == kEpiLstm) ? a.c_prev[t] : a.h_prev[t];
+    }
+  };
+  Row next;
+  request(rb_first + wv, next);
+
+  // per batch column of this lane (one per tile) and operand block: beta_j
   int bcol[NBT];
   bool bok[NBT];
-  float btv[2][NBT][KA], cx[2][NBT][KA];
+  float btv[2][NBT][KA];
 #pragma unroll
   for (int bt = 0; bt < NBT; ++bt) {
     bcol[bt] = bg0 + bt * kTileB + l16;
@@ -411,74 +435,45 @@ __global__ __launch_bounds__(64 * NWV) void mfma4wc_kernel(BmvArgs a, int rb_per
 #pragma unroll
     for (int k = 0; k < 2; ++k)
 #pragma unroll
-      for (int j = 0; j < KA; ++j) {
-        btv[k][bt][j] = a.blk[k].beta[bc * KA + j];
-        cx[k][bt][j] = (float)(nlen[k] - 2 * pops[((k * NBT + bt) * KA + j) * kTileB + l16]);
-      }
+      for (int j = 0; j < KA; ++j) btv[k][bt][j] = a.blk[k].beta[bc * KA + j];
   }
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    stage_activation_words<KA, NBT, 64 * NWV>(xw[k], btile + k * kBlockBytes, nlen[k]);
+  lds_barrier();  // (the requests under way are not waited for)
 
   for (int rb = rb_first + wv; rb < rb_end; rb += NWV) {
+    Row now = next;
+    if (rb + NWV < rb_end) request(rb + NWV, next);
     // C view: this lane's hidden unit, rows r = gate r
     const int unit_c = rb * 4 + l4;
     const bool uok = unit_c < H;
-    int crow[4];
     float bias0[4], bias1[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      crow[r] = (uok && r < NG) ? r * H + unit_c : 0;
-      bias0[r] = a.bias0 ? a.bias0[crow[r]] : 0.0f;
-      bias1[r] = (EPI == kEpiGru && a.bias1) ? a.bias1[crow[r]] : 0.0f;
+      bias0[r] = __shfl(now.bias[0], 4 * l4 + r, kWave);
+      bias1[r] = EPI == kEpiGru ? __shfl(now.bias[1], 4 * l4 + r, kWave) : 0.0f;
     }
-    float prev[NBT];
-#pragma unroll
-    for (int bt = 0; bt < NBT; ++bt) {
-      const int bc = bok[bt] ? bcol[bt] : batch - 1;
-      const int t = bc * H + (uok ? unit_c : 0);
-      prev[bt] = (EPI == kEpiLstm) ? a.c_prev[t] : a.h_prev[t];
-    }
-    // A view: lane = (tile row l16 = 4 * unit + gate, k-block l4)
-    const int unit_a = rb * 4 + (l16 >> 2), gate_a = l16 & 3;
-    const bool wok = unit_a < H && gate_a < NG;
-    const int wrow = wok ? gate_a * H + unit_a : 0;
 
     float ysum[2][NBT][4];
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      const uint4* Wp4 = reinterpret_cast<const uint4*>(a.blk[k].Wp);
-      uint4 araw[KW][2];
-      {
-        const int base = wrow * wq[k];
-        const int plane = m * wq[k];
-#pragma unroll
-        for (int i = 0; i < KW; ++i)
-#pragma unroll
-          for (int v = 0; v < 2; ++v) {
-            const int g = 2 * l4 + v;
-            const uint4 t4 = Wp4[base + i * plane + (g < wq[k] ? g : 0)];
-            araw[i][v] = (wok && g < wq[k]) ? t4 : make_uint4(0, 0, 0, 0);
-          }
-      }
       float alr[4][KW];
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int i = 0; i < KW; ++i) alr[r][i] = a.blk[k].alpha[crow[r] * KW + i];
-      // 2 popc of every weight row plane, fetched for the rows of the C view
-      float pw2[KW][4];
+        for (int i = 0; i < KW; ++i) alr[r][i] = __shfl(now.coef[k], (4 * l4 + r) * KW + i, kWave);
+      // (lane = (tile row l16 = 4 * unit + gate, k-block l4); LDS serves the accesses of a wave in order)
 #pragma unroll
       for (int i = 0; i < KW; ++i) {
-        int pc = 0;
 #pragma unroll
-        for (int v = 0; v < 2; ++v)
-          pc += __popc(araw[i][v].x) + __popc(araw[i][v].y) + __popc(araw[i][v].z) + __popc(araw[i][v].w);
-        pc += __shfl_xor(pc, 16, kWave);
-        pc += __shfl_xor(pc, 32, kWave);
+        for (int v = 0; v < 2; ++v) mine[(8 * v + (lane >> 3)) * kTurn + (lane & 7)] = now.w[k][i][v];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) pw2[i][r] = (float)(2 * __shfl(pc, 4 * l4 + r, kWave));
+        for (int v = 0; v < 2; ++v) now.w[k][i][v] = mine[l16 * kTurn + 2 * l4 + v];
       }
       v4f acc[NBT][KW][KA];
-      contract_tiles<KW, KA, NBT>(araw, btile + k * kBlockBytes + l16 * 64 + l4 * 16, acc);
-      // d_ij = 4 acc_ij - 2 popc(w_i) + (n - 2 popc(x_j)) (integers below 2^24: exact in binary32),
+      contract_tiles<KW, KA, NBT>(now.w[k], btile + k * kBlockBytes + l16 * 64 + l4 * 16, acc);
+      // the accumulators are the dot products d_ij of the codes (integers, exact in binary32):
       // y = sum_i alpha_i sum_j beta_j d_ij
 #pragma unroll
       for (int bt = 0; bt < NBT; ++bt)
@@ -489,8 +484,7 @@ __global__ __launch_bounds__(64 * NWV) void mfma4wc_kernel(BmvArgs a, int rb_per
           for (int i = 0; i < KW; ++i) {
             float inner = 0.0f;
 #pragma unroll
-            for (int j = 0; j < KA; ++j)
-              inner = fmaf(btv[k][bt][j], 4.0f * acc[bt][i][j][r] - pw2[i][r] + cx[k][bt][j], inner);
+            for (int j = 0; j < KA; ++j) inner = fmaf(btv[k][bt][j], acc[bt][i][j][r], inner);
             y = fmaf(alr[r][i], inner, y);
           }
           ysum[k][bt][r] = y;
@@ -507,7 +501,7 @@ __global__ __launch_bounds__(64 * NWV) void mfma4wc_kernel(BmvArgs a, int rb_per
         const float gf = sigmoidf_dev(ysum[0][bt][1] + ysum[1][bt][1] + bias0[1]);
         const float go = sigmoidf_dev(ysum[0][bt][2] + ysum[1][bt][2] + bias0[2]);
         const float gg = tanhf_dev(ysum[0][bt][3] + ysum[1][bt][3] + bias0[3]);
-        const float c = fmaf(gf, prev[bt], gi * gg);
+        const float c = fmaf(gf, now.prev[bt], gi * gg);
         const float h = go * tanhf_dev(c);
         if (bok[bt] && uok) {
           a.c_out[t] = c;
@@ -518,7 +512,7 @@ __global__ __launch_bounds__(64 * NWV) void mfma4wc_kernel(BmvArgs a, int rb_per
         const float rg = sigmoidf_dev(ysum[0][bt][0] + ysum[1][bt][0] + bias0[0] + bias1[0]);
         const float z = sigmoidf_dev(ysum[0][bt][1] + ysum[1][bt][1] + bias0[1] + bias1[1]);
         const float nn = tanhf_dev(fmaf(rg, ysum[1][bt][2] + bias1[2], ysum[0][bt][2] + bias0[2]));
-        if (bok[bt] && uok) a.h_out[t] = fmaf(z, prev[bt] - nn, nn);
+        if (bok[bt] && uok) a.h_out[t] = fmaf(z, now.prev[bt] - nn, nn);
       }
     }
   }
@@ -640,7 +634,7 @@ hipError_t launch_cell_one(const BmvArgs& a, hipStream_t s) {
     int per = (rowblocks + splits - 1) / splits;
     per = (per + 3) / 4 * 4;
     if (per < NWV) per = NWV;
-    const size_t lds = (size_t)2 * NBT * KA * kPlaneBytes + sizeof(int) * 2 * NBT * KA * kTileB;
+    const size_t lds = (size_t)2 * NBT * KA * kPlaneBytes + sizeof(uint4) * NWV * kTileB * kTurn;
     static std::atomic<unsigned long long> configured{0};
     {
       hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&mfma4wc_kernel<KW, KA, NBT, EPI, NWV>), (int)lds,
