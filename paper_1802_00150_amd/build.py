@@ -23,7 +23,7 @@ LIB_PHASES = os.path.join(HERE, "libamq_phases.so")
 TORCH_BINDING = os.path.join(HERE, "_amq_torch.so")
 TORCH_BINDING_SOURCE = os.path.join(CSRC, "amq_torch.cpp")
 
-SOURCES = ["amq_api.hip", "amq_quantize.hip", "amq_quantize_recon.hip", "amq_gemm.hip", "amq_bmv.hip", "amq_bmv_online.hip", "amq_cell1.hip", "amq_mfma.hip", "amq_mfma4.hip", "amq_mfma4w.hip", "amq_mfma32.hip", "amq_mfma32_w3.hip", "amq_mfma32_cell.hip", "amq_step.hip", "amq_seqw.hip", "amq_seqw_tiles.hip", "amq_lstm_seqg.hip", "amq_seq1.hip", "amq_seq1_w3.hip", "amq_cells.hip", "amq_lm.hip", "amq_baselines.hip"]
+SOURCES = ["amq_api.hip", "amq_quantize.hip", "amq_quantize_recon.hip", "amq_gemm.hip", "amq_bmv.hip", "amq_bmv_online.hip", "amq_cell1.hip", "amq_mfma.hip", "amq_mfma4.hip", "amq_mfma4w.hip", "amq_mfma32.hip", "amq_mfma32_w3.hip", "amq_mfma32_cell.hip", "amq_step.hip", "amq_step_once.hip", "amq_seqw.hip", "amq_seqw_tiles.hip", "amq_lstm_seqg.hip", "amq_seq1.hip", "amq_seq1_w3.hip", "amq_cells.hip", "amq_lm.hip", "amq_baselines.hip"]
 # packed-fp32 instructions are disabled on purpose; -ffp-contract=off keeps single binary32
 # operations single (the code-assignment comparison must round like the reference arithmetic).
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",

@@ -578,17 +578,20 @@ static int lstm_step_launch(const uint32_t* Wxp, const float* alpha_x, const uin
                             const float* x, const float* h_prev, const float* c_prev, int64_t B, int k_a,
                             int T, float* h_out, float* c_out, float* hs_out, const StepWs& w,
                             hipStream_t s) {
-  if (B == 1) {
-    // one launch, unless what every workgroup quantizes is overwritten by the workgroups that finish first
-    amq::BmvArgs b = lstm_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias, nullptr, nullptr, nullptr, nullptr, c_prev, 1, h_out,
+  {
+    // one launch, unless what workgroups quantize is overwritten by the workgroups that finish first
+    amq::BmvArgs b = lstm_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias, nullptr, nullptr, nullptr, nullptr, c_prev, B, h_out,
                                c_out, hs_out);
     b.raw[0] = x;
     b.raw[1] = h_prev;
     b.T = T;
-    const bool apart = apart_from(h_prev, H, h_out, H) && apart_from(h_prev, H, c_out, H) && apart_from(x, I, h_out, H) &&
-                       apart_from(x, I, c_out, H) && (!hs_out || (apart_from(h_prev, H, hs_out, H) && apart_from(x, I, hs_out, H)));
+    const int64_t nx = B * I, nh = B * H;
+    const bool apart = apart_from(h_prev, nh, h_out, nh) && apart_from(h_prev, nh, c_out, nh) && apart_from(x, nx, h_out, nh) &&
+                       apart_from(x, nx, c_out, nh) && (!hs_out || (apart_from(h_prev, nh, hs_out, nh) && apart_from(x, nx, hs_out, nh)));
     if (apart && amq::cell1_supported(b, k_w, k_a, amq::kEpiLstm))
       return hip_status(amq::launch_cell1(b, k_w, k_a, amq::kEpiLstm, s));
+    if (apart && amq::step_once_supported(b, k_w, k_a, amq::kEpiLstm, s))
+      return hip_status(amq::launch_step_once(b, k_w, k_a, amq::kEpiLstm, s));
   }
   amq::QuantArgs q{};
   q.seg[0] = amq::QuantSeg{x, I, (int)I, (int)B, w.xp, w.beta_x};
@@ -845,14 +848,15 @@ static int gru_step_launch(const uint32_t* Wxp, const float* alpha_x, const uint
                            int64_t I, int64_t H, int k_w, const float* bias_x, const float* bias_h, const float* x,
                            const float* h_prev, int64_t B, int k_a, int T, float* h_out, const StepWs& w,
                            hipStream_t s) {
-  if (B == 1) {  // one launch, as in lstm_step_launch
-    amq::BmvArgs b = gru_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, nullptr, nullptr, nullptr, nullptr, h_prev, 1,
+  if (apart_from(h_prev, B * H, h_out, B * H) && apart_from(x, B * I, h_out, B * H)) {  // one launch, as in lstm_step_launch
+    amq::BmvArgs b = gru_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, nullptr, nullptr, nullptr, nullptr, h_prev, B,
                               h_out);
     b.raw[0] = x;
     b.raw[1] = h_prev;
     b.T = T;
-    if (apart_from(h_prev, H, h_out, H) && apart_from(x, I, h_out, H) && amq::cell1_supported(b, k_w, k_a, amq::kEpiGru))
-      return hip_status(amq::launch_cell1(b, k_w, k_a, amq::kEpiGru, s));
+    if (amq::cell1_supported(b, k_w, k_a, amq::kEpiGru)) return hip_status(amq::launch_cell1(b, k_w, k_a, amq::kEpiGru, s));
+    if (amq::step_once_supported(b, k_w, k_a, amq::kEpiGru, s))
+      return hip_status(amq::launch_step_once(b, k_w, k_a, amq::kEpiGru, s));
   }
   amq::QuantArgs q{};
   q.seg[0] = amq::QuantSeg{x, I, (int)I, (int)B, w.xp, w.beta_x};

@@ -376,6 +376,11 @@ hipError_t launch_seqw_tiles(const SeqWArgs& a, int k_w, int k_a, int epi, hipSt
 // computed again from the saved state (batch 1: and the flag cleared).
 hipError_t launch_seq_recover(const SeqWArgs& a, int k_w, int k_a, int epi, hipStream_t s);
 
+// ---- the recurrent step of a small batch in one launch (amq_step_once.hip) -----------------------
+// a.raw: x_t and h_{t-1}, which no output may overlap.  Asks the stream whether it is being captured (then: not supported).
+bool step_once_supported(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s);
+hipError_t launch_step_once(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s);
+
 // ---- the recurrent step of a sequence with given inputs, cut along the operand blocks ----------
 // Front launch: quantizes the vectors of q (seg[0] = h_{t-1}, seg[1] = a later x, count 0 for none) and of
 // q2 (nullable; more inputs, at the first step), and forms the x-side product x (nullable; operand block 0

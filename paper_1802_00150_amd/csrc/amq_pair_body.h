@@ -32,6 +32,8 @@
 // The stored sums are exactly the values that otherwise travel from the x wave's registers, so the
 // results stay bit-identical.
 #pragma once
+#include <type_traits>
+
 #include "amq_device.h"
 #include "amq_launch.h"
 
@@ -60,8 +62,14 @@ constexpr int pair_body_rowblocks() {
 //
 // bx, by: row-block group and batch group of this workgroup.  turn: pair_body_lds() bytes of LDS, 16-byte
 // aligned.  xch (kPairBoth only): (NWV / 2) * NBT * 64 float4 of LDS.
-template <int KW, int KA, int NBT, int EPI, int NWV, int MODE = kPairBoth, int NC = 1>
-__device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int bx, int by, uint4* turn, float4* xch) {
+// Stage: where the activations come from.  By default the codes and coefficients lie in memory; otherwise stage(image, kb, beta)
+// is called when the wave's weights are in operand layout: it fills the images, passes a barrier after that and leaves the
+// coefficients of the wave's block as request_column_coefficients() does.
+struct PairFromMemory {};
+template <int KW, int KA, int NBT, int EPI, int NWV, int MODE = kPairBoth, int NC = 1, typename Stage = PairFromMemory>
+__device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int bx, int by, uint4* turn, float4* xch,
+                                          Stage stage = Stage{}) {
+  constexpr bool kFromMemory = std::is_same<Stage, PairFromMemory>::value;
   static_assert(EPI == kEpiLstm || EPI == kEpiGru, "cell modes only");
   constexpr int NG = (EPI == kEpiGru) ? 3 : 4;
   constexpr int NBLK = MODE == kPairBoth ? 2 : 1;  // operand blocks whose activations the workgroup stages
@@ -230,16 +238,23 @@ __device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int b
     }
   };
 
-  request_activations();
-  __builtin_amdgcn_sched_barrier(0);  // the shared requests go out first: every wave waits for them
-  request_weights();
-  AMQ_PHASE_WHEN(bx == 0 && by == 0, AMQ_PHASE_OF(a), 8, 1);
-  expand_activations();
-  AMQ_PHASE_WHEN(bx == 0 && by == 0, AMQ_PHASE_OF(a), 8, 9);
-  lds_barrier();
-  AMQ_PHASE_WHEN(bx == 0 && by == 0, AMQ_PHASE_OF(a), 8, 2);
-  turn_weights();
-  AMQ_PHASE_WHEN(bx == 0 && by == 0, AMQ_PHASE_OF(a), 8, 4);
+  if constexpr (kFromMemory) {
+    request_activations();
+    __builtin_amdgcn_sched_barrier(0);  // the shared requests go out first: every wave waits for them
+    request_weights();
+    AMQ_PHASE_WHEN(bx == 0 && by == 0, AMQ_PHASE_OF(a), 8, 1);
+    expand_activations();
+    AMQ_PHASE_WHEN(bx == 0 && by == 0, AMQ_PHASE_OF(a), 8, 9);
+    lds_barrier();
+    AMQ_PHASE_WHEN(bx == 0 && by == 0, AMQ_PHASE_OF(a), 8, 2);
+    turn_weights();
+    AMQ_PHASE_WHEN(bx == 0 && by == 0, AMQ_PHASE_OF(a), 8, 4);
+  } else {
+    request_weights();
+    request_row_operands();
+    turn_weights();
+    stage(image, kb, beta_req);
+  }
   // this lane's operand of (tile, plane, k-step)
   constexpr int kAllSteps = NC * kSteps;
   const uint4* const myimage = image + (MODE == kPairBoth ? kb : 0) * (NBT * KA * kAllSteps * 64) + 16 * l4;
@@ -287,7 +302,7 @@ __device__ __forceinline__ void pair_body(const BmvArgs& a, int rowblocks, int b
           for (int j = 0; j < KA; ++j)
             acc[bt][i][j] = mfma_fp4(aop[i], bop[bt][j], acc[bt][i][j]);
       __builtin_amdgcn_sched_barrier(0);
-      if (t == 0) {
+      if (kFromMemory && t == 0) {
         // under the contraction: here they return before the epilogue and delay no operand request
         request_column_coefficients();
         request_row_operands();

@@ -1,0 +1,258 @@
+// A recurrent step of a small batch in one launch (Eq. 6): quantization of x_t and h_{t-1}, products, cell.
+//
+// Two launches (quantizer, then products and cell) cost a launch each on the host (2.3 us) and, on the device, the gap between
+// dependent kernels, the second kernel's start and the cold fetch of its weights, one after the other.  Here the first workgroups of
+// the grid quantize, one batch entry's two vectors each, and the others (amq_pair_body.h: one batch tile and 4 row blocks each)
+// fetch their weights, turn them into operand layout and then wait for the codes of their tile.  What is handed over are 8-byte
+// {word, tag} pairs, one device-scope store each, polled until all that a lane needs carry the tag of the launch: the data is its own
+// arrival signal.
+//
+// Whom a workgroup waits for comes before it in the grid and waits for nobody.  Should the chip be shared such that those
+// workgroups get no room for longer than a wait takes (kHandOverPolls), the waiting workgroup quantizes the vectors of its tile
+// itself: it needs nobody then, so results depend neither on the order of the workgroups nor on how many are resident.  The
+// inputs are therefore read by workgroups that start late; the host takes this path only where no output overlaps them.
+//
+// The pairs live in memory of the library (a slot per launch, taken in turn), which is zero at first and is written by nobody else; a
+// tag is used once in 2^32 launches, so an old pair is not taken for a new one.  Should as many later launches as there are slots have
+// overwritten a slot that is still waited for, those waits end as above.  A captured launch would carry the same tag at every replay:
+// there the step stays two launches.
+//
+// The arithmetic and its order are those of the two launches: the results are the same bit for bit.
+#include <atomic>
+#include <type_traits>
+
+#include "amq_launch.h"
+#include "amq_pair_body.h"
+#include "amq_quantize_body.h"
+#include "amq_seqw_body.h"
+
+namespace amq {
+
+namespace {
+
+constexpr int kOnceWaves = 8;
+constexpr unsigned kHandOverPolls = 64;  // about 40 us
+constexpr int kHandOverSlots = 32;
+constexpr int kSlotPairs = 16384;        // 128 KiB
+static __device__ unsigned long long hand_over[kHandOverSlots][kSlotPairs];
+
+// Pairs of a vector: the words of its codes, plane by plane, then the coefficients; whole cache lines of 16.
+__host__ __device__ constexpr int vector_pairs(int k_a, int wpr) { return (k_a * (wpr + 1) + 15) & ~15; }
+
+struct OnceArgs {
+  BmvArgs b;                 // raw[0], raw[1]: the inputs and the previous state
+  unsigned long long* pairs; // this launch's slot: vectors x_0 .. , then h_0 ..
+  unsigned tag, polls;
+  int rowblocks, gx;         // gx: workgroups of a batch tile
+};
+
+// NC: stretches of 1024 entries of the longer operand block (1 or 2).  (The register bounds are such that nothing is spilled: a few
+// bytes of scratch per lane cost 0.7 us here.)
+template <int KW, int KA, int EPI, int NC>
+__global__ __launch_bounds__(64 * kOnceWaves, NC == 1 && KW * KA <= 4 ? 4 : 2) void step_once_kernel(OnceArgs o) {
+  constexpr int NW = kOnceWaves / 2;  // waves per vector
+  constexpr int NJ = 4 * NC;          // slots per lane
+  constexpr int kWords = 32 * NC;     // words of a row, padding included
+  __shared__ double sh[2][2 * kExchange<NW>];
+  __shared__ __attribute__((aligned(8))) uint32_t codes[2][KA * (kWords + 1)];
+  __shared__ float4 xch[(kOnceWaves / 2) * 64];
+  __shared__ int missed;
+  extern __shared__ __attribute__((aligned(16))) uint4 turn[];
+  const BmvArgs& a = o.b;
+  asm volatile("" ::AMQ_ARG(a.blk[0].Wp), AMQ_ARG(a.blk[0].alpha), AMQ_ARG(a.blk[0].n), AMQ_ARG(a.blk[1].Wp),
+               AMQ_ARG(a.blk[1].alpha), AMQ_ARG(a.blk[1].n), AMQ_ARG(a.m), AMQ_ARG(a.H), AMQ_ARG(a.batch), AMQ_ARG(a.bias0),
+               AMQ_ARG(a.bias1), AMQ_ARG(a.c_prev), AMQ_ARG(a.h_prev), AMQ_ARG(a.h_out), AMQ_ARG(a.c_out), AMQ_ARG(a.raw[0]),
+               AMQ_ARG(a.raw[1]), AMQ_ARG(a.T), AMQ_ARG(o.pairs), AMQ_ARG(o.tag), AMQ_ARG(o.rowblocks), AMQ_ARG(o.gx));
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int batch = a.batch;
+  // (formed from the arguments at every use: as captured variables they are kept in memory)
+  auto wpr = [&](int k) { return 4 * (((k ? a.blk[1].n : a.blk[0].n) + 127) >> 7); };
+  auto vector_at = [&](int k, int entry) {
+    return o.pairs + (k ? batch * vector_pairs(KA, wpr(0)) + entry * vector_pairs(KA, wpr(1)) : entry * vector_pairs(KA, wpr(0)));
+  };
+
+  // The codes and coefficients of a batch entry's two vectors in LDS, a half of the waves each; ends with a barrier.
+  auto quantize_entry = [&](int entry, int& phase) {
+    const int k = wv / NW, n = k ? a.blk[1].n : a.blk[0].n, w = wpr(k);
+    const int nslots = w >> 1, nj = (nslots + NW - 1) / NW, base = (wv & (NW - 1)) * nj;
+    const float* const x = (k ? a.raw[1] : a.raw[0]) + (size_t)entry * n;
+    float beta[KA];
+    unsigned long long mym[KA];
+    with_slots<NJ, true>(nj, [&](auto slots) {
+      float v[slots()];
+      load_slots<slots()>(x, n, base, nj, v);
+      quantize_core<KA, slots(), NW, true>(v, n, base, nj, a.T, beta, mym, sh[k], phase);
+    });
+    if (lane < nj && base + lane < nslots) {
+#pragma unroll
+      for (int i = 0; i < KA; ++i) reinterpret_cast<unsigned long long*>(codes[k] + i * w)[base + lane] = mym[i];
+    }
+    if ((wv & (NW - 1)) == 0 && lane == 0) {
+#pragma unroll
+      for (int i = 0; i < KA; ++i) codes[k][KA * w + i] = __float_as_uint(beta[i]);
+    }
+    lds_barrier();
+  };
+
+  if ((int)blockIdx.x < batch) {
+    int phase = 0;
+    const int entry = blockIdx.x, k = wv / NW, t = tid & (64 * NW - 1);
+    quantize_entry(entry, phase);
+    const int w = wpr(k);
+    if (t < KA * (w + 1)) put_pair(vector_at(k, entry) + t, codes[k][t], o.tag);
+    return;
+  }
+
+  const int at = (int)blockIdx.x - batch, bx = at % o.gx, by = at / o.gx;
+  const int b0 = by * kTileB, ncols = batch - b0 < kTileB ? batch - b0 : kTileB;
+  if (tid == 0) missed = 0;
+  auto stage = [&](uint4* image, int kb, float (&beta)[1]) {
+    // thread -> word of a row (plane by plane, block by block) and batch column: adjacent lanes, adjacent pairs
+    constexpr int kColsPer = 64 * kOnceWaves / kWords, kColReq = kTileB / kColsPer;
+    const int gw = tid & (kWords - 1), gc = tid / kWords;
+    const int dst = ((gw >> 5) * kSteps + 4 * ((gw >> 4) & 1) + (gw & 3)) * 64 + 16 * ((gw >> 2) & 3);
+    const int swz = (((gw >> 2) & 3) << 1) | (((gw >> 4) & 1) << 3);
+    auto place = [&](int k, int j, int col, uint32_t word) {
+      image[(k * KA + j) * NC * kSteps * 64 + dst + (col ^ swz)] = expand4_signed(word);
+    };
+    const int l16 = lane & 15, l4 = lane >> 4, plane = l4 < KA ? l4 : KA - 1;
+    lds_barrier();  // (missed is set)
+    unsigned long long v[2][KA][kColReq], bv;
+    unsigned spins = 0;
+    for (;;) {
+      bv = get_pair(vector_at(kb, b0 + (l16 < ncols ? l16 : ncols - 1)) + KA * wpr(kb) + plane);
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int q = 0; q < kColReq; ++q) {
+          const int col = q * kColsPer + gc;
+          // (columns past the batch and words past the row are not asked for)
+#pragma unroll
+          for (int j = 0; j < KA; ++j) v[k][j][q] = (unsigned long long)o.tag << 32;
+          if (col < ncols && gw < wpr(k)) {
+            const unsigned long long* const from = vector_at(k, b0 + col) + gw;
+#pragma unroll
+            for (int j = 0; j < KA; ++j) v[k][j][q] = get_pair(from + j * wpr(k));
+          }
+        }
+      bool ready = (unsigned)(bv >> 32) == o.tag;
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int j = 0; j < KA; ++j)
+#pragma unroll
+          for (int q = 0; q < kColReq; ++q) ready = ready && (unsigned)(v[k][j][q] >> 32) == o.tag;
+      if (__all(ready)) break;
+      if (++spins >= o.polls) {
+        missed = 1;
+        break;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int j = 0; j < KA; ++j)
+#pragma unroll
+        for (int q = 0; q < kColReq; ++q)
+          place(k, j, q * kColsPer + gc, gw < wpr(k) ? (uint32_t)(v[k][j][q] & 0xffffffffull) : 0u);
+    beta[0] = __uint_as_float((unsigned)(bv & 0xffffffffull));
+    lds_barrier();
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(missed) != 0, 0)) {
+      // the tile's vectors by this workgroup, entry after entry
+      int phase = 0;
+      for (int col = 0; col < ncols; ++col) {
+        quantize_entry(b0 + col, phase);
+        for (int t = tid; t < 2 * KA * kWords; t += 64 * kOnceWaves) {  // (whole rounds: kWords is the word's period)
+          const int k = t / (KA * kWords), j = t / kWords % KA;
+          place(k, j, col, gw < wpr(k) ? codes[k][j * wpr(k) + gw] : 0u);
+        }
+        if (l16 == col) beta[0] = __uint_as_float(codes[kb][KA * wpr(kb) + plane]);
+        lds_barrier();
+      }
+    }
+  };
+  pair_body<KW, KA, 1, EPI, kOnceWaves, kPairBoth, NC>(a, o.rowblocks, bx, by, turn, xch, stage);
+}
+
+template <int KW, int KA, int EPI, int NC>
+hipError_t run_one(const OnceArgs& o, int grid, hipStream_t s) {
+  constexpr size_t lds = pair_body_lds<KW, KA, 1, kOnceWaves, kPairBoth, NC>();
+  static std::atomic<unsigned long long> configured{0};
+  hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&step_once_kernel<KW, KA, EPI, NC>), (int)lds, configured);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((step_once_kernel<KW, KA, EPI, NC>), dim3((unsigned)grid), dim3(64 * kOnceWaves), lds, s, o);
+  return hipGetLastError();
+}
+
+template <int KW, int KA>
+hipError_t run_k(const OnceArgs& o, int grid, int epi, int nc, hipStream_t s) {
+  if (epi == kEpiLstm) return nc == 1 ? run_one<KW, KA, kEpiLstm, 1>(o, grid, s) : run_one<KW, KA, kEpiLstm, 2>(o, grid, s);
+  return nc == 1 ? run_one<KW, KA, kEpiGru, 1>(o, grid, s) : run_one<KW, KA, kEpiGru, 2>(o, grid, s);
+}
+
+// The slot memory of the current device and its compute units, looked up once per device (null: not to be had).
+unsigned long long* hand_over_memory(int& units) {
+  struct Device {
+    std::atomic<void*> memory;
+    std::atomic<int> units;
+  };
+  static Device known[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+  void* p = known[dev].memory.load(std::memory_order_acquire);
+  if (p) {
+    units = known[dev].units.load(std::memory_order_relaxed);
+  } else {
+    if (hipGetSymbolAddress(&p, HIP_SYMBOL(hand_over)) != hipSuccess ||
+        hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    known[dev].units.store(units, std::memory_order_relaxed);
+    known[dev].memory.store(p, std::memory_order_release);
+  }
+  return static_cast<unsigned long long*>(p);
+}
+
+int row_groups(const BmvArgs& a) { return (int)(((a.H + 3) / 4 + kOnceWaves / 2 - 1) / (kOnceWaves / 2)); }
+long long workgroups(const BmvArgs& a) { return a.batch + (long long)row_groups(a) * ((a.batch + kTileB - 1) / kTileB); }
+
+}  // namespace
+
+// Shapes of the paired kernel, 2- and 3-bit codes, as long as every workgroup has a compute unit of its own.  Two launches / one,
+// us per LSTM step: W2/A2 300 units batch 4 7.2 / 6.0, 64 7.3 / 6.5, 650 batch 13 7.1 / 6.65, 1024 batch 48 (240 workgroups) 7.7 / 7.3,
+// 1500 batch 20 8.5 / 8.5, 2048 batch 4 8.9 / 8.1; W3/A3 300 batch 8 8.2 / 7.55, 1024 batch 8 8.8 / 8.5, 32 9.0 / 9.0.  Beyond, the
+// waiting workgroups are in the way of each other: 1024 units batch 64 (320 workgroups) W2/A2 7.8 / 8.2, W3/A3 9.3 / 10.5.
+bool step_once_supported(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s) {
+  if (a.batch < 2 || k_w < 2 || k_w > 3 || k_a < 2 || k_a > 3 || !a.raw[0] || !a.raw[1]) return false;
+  if (!mfma4_pair_supported(a, k_w, k_a, epi) || mfma32_cell_supported(a, k_w, k_a, epi)) return false;
+  long long pairs = 0;
+  for (const BmvBlock& k : a.blk) pairs += (long long)a.batch * vector_pairs(k_a, 4 * ((k.n + 127) >> 7));
+  int units = 0;
+  if (pairs > kSlotPairs || !hand_over_memory(units) || workgroups(a) > units) return false;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+}
+
+hipError_t launch_step_once(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s) {
+  static std::atomic<unsigned> launches{0};
+  int units = 0;
+  unsigned long long* const memory = hand_over_memory(units);
+  if (!memory) return hipErrorInvalidValue;
+  OnceArgs o{};
+  o.b = a;
+  AMQ_PHASE_ATTACH(o.b);
+  do o.tag = launches.fetch_add(1, std::memory_order_relaxed);
+  while (o.tag == 0u);  // (0 is what the slots hold at first)
+  o.pairs = memory + (size_t)(o.tag % kHandOverSlots) * kSlotPairs;
+  o.polls = sequence_spin_limit() < kHandOverPolls ? sequence_spin_limit() : kHandOverPolls;
+  o.rowblocks = (int)((a.H + 3) / 4);
+  o.gx = row_groups(a);
+  const int grid = (int)workgroups(a);
+  const int nc = a.blk[0].n > 1024 || a.blk[1].n > 1024 ? 2 : 1;
+  if (k_w == 2) return k_a == 2 ? run_k<2, 2>(o, grid, epi, nc, s) : run_k<2, 3>(o, grid, epi, nc, s);
+  return k_a == 2 ? run_k<3, 2>(o, grid, epi, nc, s) : run_k<3, 3>(o, grid, epi, nc, s);
+}
+
+}  // namespace amq

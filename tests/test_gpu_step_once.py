@@ -1,0 +1,103 @@
+"""GPU: recurrent steps of small batches in one launch (amq_step_once.hip).  Steps whose state is updated in place take two launches
+and the same arithmetic: the two agree bit for bit, also where every wait gives up and the workgroups quantize for themselves, on
+several streams with more launches than there are slots, and in a replayed graph."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def amq():
+    import paper_1802_00150_amd as m
+    m.binding.lib()
+    return m
+
+
+class Step:
+    def __init__(self, amq, gates, I, H, B, k_w, k_a, seed=0):
+        import torch
+        print("step in one launch gates=%d I=%d H=%d B=%d W%d/A%d" % (gates, I, H, B, k_w, k_a), flush=True)
+        g = torch.Generator(device="cuda:0").manual_seed(I + 3 * H + B + seed)
+        randn = lambda *s: torch.randn(*s, generator=g, device="cuda:0")  # noqa: E731
+        self.amq, self.gates, self.args, self.k_a = amq, gates, (I, H), k_a
+        self.d = [*amq.quantize_weights(randn(gates * H, I) * 0.04, k_w, 2), *amq.quantize_weights(randn(gates * H, H) * 0.04, k_w, 2)]
+        self.bias = [randn(gates * H) * 0.1 for _ in range(1 if gates == 4 else 2)]
+        self.x, self.h, self.c = randn(B, I), torch.tanh(randn(B, H)), randn(B, H)
+        self.ws = (amq.lstm_workspace if gates == 4 else amq.gru_workspace)(I, H, B, k_a, "cuda:0")
+
+    def into(self, h, h_out, c, c_out):
+        if self.gates == 4:
+            self.amq.lstm_step(*self.d, *self.args, *self.bias, self.x, h, c, self.k_a, 2, ws=self.ws, h_out=h_out, c_out=c_out)
+            return h_out, c_out
+        self.amq.gru_step(*self.d, *self.args, *self.bias, self.x, h, self.k_a, 2, ws=self.ws, h_out=h_out)
+        return (h_out,)
+
+    def two_launches(self):
+        h, c = self.h.clone(), self.c.clone()
+        return self.into(h, h, c, c)
+
+    def once(self):
+        import torch
+        return self.into(self.h, torch.full_like(self.h, -7.0), self.c, torch.full_like(self.c, -7.0))
+
+
+def same(a, b):
+    import torch
+    return all(torch.equal(p, q) for p, q in zip(a, b))
+
+
+# one entry more and fewer than a tile, ragged units and vectors, one and two stretches, blocks of unequal stretches, the most
+# workgroups that still take this path (240 of 256) and more
+SHAPES = [(300, 300, 2, 2, 2), (650, 650, 13, 2, 2), (1, 1030, 17, 2, 3), (128, 1024, 16, 2, 2), (700, 701, 33, 3, 2),
+          (1500, 1500, 20, 2, 2), (2048, 2048, 5, 3, 3), (2000, 333, 31, 3, 3), (1024, 1024, 48, 2, 3), (1024, 1024, 64, 3, 3)]
+
+
+@pytest.mark.parametrize("gates", [4, 3])
+@pytest.mark.parametrize("I,H,B,k_w,k_a", SHAPES)
+def test_same_as_two_launches(amq, gates, I, H, B, k_w, k_a):
+    s = Step(amq, gates, I, H, B, k_w, k_a)
+    want = s.two_launches()
+    for _ in range(3):
+        assert same(s.once(), want)
+    amq.binding.debug_set_sequence_spin_limit(1)  # (every wait gives up at its first poll)
+    try:
+        got = s.once()
+    finally:
+        amq.binding.debug_set_sequence_spin_limit(0)
+    assert same(got, want)
+
+
+def test_streams_and_slots(amq):
+    import torch
+    steps = [Step(amq, 4, 300, 300, 7, 2, 2), Step(amq, 3, 650, 650, 20, 3, 3), Step(amq, 4, 1100, 1024, 9, 2, 3)]
+    want = [s.two_launches() for s in steps]
+    streams = [torch.cuda.Stream() for _ in steps]
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(40):
+        for i, s in enumerate(steps):
+            with torch.cuda.stream(streams[i]):
+                got.append((i, s.once()))
+    torch.cuda.synchronize()
+    assert all(same(g, want[i]) for i, g in got)
+
+
+def test_graph_replays(amq):
+    import torch
+    s = Step(amq, 4, 300, 300, 7, 2, 2)
+    want = s.two_launches()
+    h, c = torch.empty_like(s.h), torch.empty_like(s.c)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        s.into(s.h, h, s.c, c)
+    for _ in range(3):
+        h.fill_(-7.0), c.fill_(-7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert same((h, c), want)
+        x = s.x.clone()
+        s.x.copy_(x.flip(0))  # other inputs in the same place
+        graph.replay()
+        torch.cuda.synchronize()
+        assert same((h, c), s.two_launches())
+        s.x.copy_(x)
