@@ -375,7 +375,7 @@ __global__ __launch_bounds__(256) void seqw_reset_kernel(unsigned* flag, Residen
                                                          unsigned count) {
   const unsigned t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
   for (unsigned i = t; i < count; i += nt) pairs[i] = 0ull;
-  if (t == 0) *flag = take_resident_share(claim) ? 0u : kNoRoom;
+  if (t == 0) *flag = take_resident_share(claim) != 0u ? 0u : kNoRoom;
 }
 
 // The piece again from the saved state if the launch before gave up: one workgroup per batch entry.
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(64 * kWBlocks) void seqw_recover_kernel(SeqWArgs a,
   __shared__ uint32_t codes[KA * 64];
   __shared__ float hbeta[KA];
   const unsigned why = *a.flag;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && why != kNoRoom) give_resident_share(claim);
+  if (blockIdx.x == 0 && threadIdx.x == 0 && why != kNoRoom) give_resident_share(claim, claim.mine);
   if (why == 0u) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -162,3 +162,24 @@ def test_streams_and_threads_share_the_chip(amq, shapes):
             for g, w in zip(call, ref):
                 assert torch.equal(g, w), (i, shapes[i])
     assert took < 0.2, "a launch waited until its time for room was up"
+
+
+@pytest.mark.parametrize("gates,I,H,k_w,k_a", [(4, 128, 128, 2, 2), (4, 200, 160, 2, 3), (3, 300, 300, 2, 2), (4, 1000, 224, 3, 3),
+                                               (4, 448, 448, 2, 2), (3, 448, 449, 3, 2)])
+def test_single_sequences_on_one_die_or_spread(amq, held, gates, I, H, k_w, k_a):
+    # 2, 5, 19, 28, 28 and 29 workgroups: alone on the chip those in between sit on one die, beside another launch nobody does; the
+    # room that either took is given back (a call that needs it finds it)
+    import torch
+    say("one die or spread: gates=%d I=%d H=%d W%d/A%d" % (gates, I, H, k_w, k_a))
+    s = Sequence(amq, gates, I, H, 1, k_w, k_a, 70)
+    ws = s.workspace()
+    alone = [s.run(ws) for _ in range(2)]
+    held(SHARES - 1)
+    torch.cuda.synchronize()
+    start = time.perf_counter()
+    beside = [s.run(ws) for _ in range(3)]
+    torch.cuda.synchronize()
+    assert time.perf_counter() - start < 0.1
+    for got in alone[1:] + beside:
+        for g, w in zip(got, alone[0]):
+            assert torch.equal(g, w)
