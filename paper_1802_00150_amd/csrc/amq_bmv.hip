@@ -37,10 +37,27 @@ hipError_t launch_epi(const BmvArgs& a, int epi, hipStream_t s, int* lse_slots) 
   for (int k = 0; k < nblk; ++k) lds += (size_t)KA * a.batch * ((a.blk[k].n + 127) / 128) * 16;
   switch (epi) {
     case kEpiStore: {
-      // four row groups per wave (all loads in flight) when there are enough rows to fill the
-      // chip that way; one row group per wave for small products, where parallelism matters more
-      const long long waves4 = (a.m + 4LL * R - 1) / (4LL * R);
-      if (waves4 * a.groups >= 2048) return launch_one<KW, KA, 4, 1, kEpiStore>(a, waves4, lds, s, lse_slots);
+      // One row group per wave.  From where that is more waves than the chip holds (8192; `waves4` is a quarter of them): four
+      // (all loads in flight) for products read from memory and groups of them, where the pairs of a log-softmax are left (one
+      // group would leave more of them than fit), and for 1-bit weights, whose waves have little else to hide their start with
+      // (42000 x 4096 W1/A1 batch 2 6.0 us, 6.9 with one).  One vector: two, unless they take more rounds of resident waves.
+      // With several vectors a wave is bound by its own arithmetic, and one group (41 to 65 registers) leaves room for twice the waves
+      // of four.  us per product, four groups / two / one: 20000 x 4096 W2/A2 batch 1 4.8 / 4.2 / 4.5, W3/A3 6.7 / 5.9 / 6.5, batch 3
+      // 13.1 / 10.9 / 11.0, batch 12 40.6 / 32.8 / 30.5; 42000 x 4096 W3/A3 batch 12 75 / 67 / 60; 42000 x 2048 W3/A3 batch 1 (5250
+      // waves of two groups) 6.5 / 7.0; below, 10000 x 4096 W2/A2 4.1 / 3.5 / 3.25.
+      const long long waves4 = (a.m + 4LL * R - 1) / (4LL * R), waves2 = (a.m + 2LL * R - 1) / (2LL * R);
+      if (waves4 * a.groups >= 2048) {
+        if (KW == 1 || a.streaming || a.groups > 1 || a.lse_part) return launch_one<KW, KA, 4, 1, kEpiStore>(a, waves4, lds, s, lse_slots);
+        if constexpr (KW > 1) {
+          // (resident waves of the chip, by the registers of the two forms)
+          constexpr long long kOf2 = 1024 * (KW + KA <= 4 ? 8 : KW == 2 && KA == 3 ? 6 : 5), kOf4 = 1024 * (KW + KA <= 4 ? 5 : 4);
+          if (a.batch == 1) {
+            if ((waves2 + kOf2 - 1) / kOf2 > (waves4 + kOf4 - 1) / kOf4)
+              return launch_one<KW, KA, 4, 1, kEpiStore>(a, waves4, lds, s, lse_slots);
+            return launch_one<KW, KA, 2, 1, kEpiStore>(a, waves2, lds, s, lse_slots);
+          }
+        }
+      }
       return launch_one<KW, KA, 1, 1, kEpiStore>(a, (a.m + R - 1) / R, lds, s, lse_slots);
     }
     case kEpiLstm: return launch_one<KW, KA, 4, 2, kEpiLstm>(a, (a.H + R - 1) / R, lds, s, nullptr);

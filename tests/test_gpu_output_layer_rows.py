@@ -1,5 +1,6 @@
 """GPU: the output layer of one batch entry at every number of row groups per wave (amq_bmv_online.hip), on either side of the lines
-between them, with rows that fill no group and workgroups with waves that have none."""
+between them, with rows that fill no group and workgroups with waves that have none; plain products on either side of theirs
+(amq_bmv.hip)."""
 import pytest
 
 from test_gpu_uneven_products import operands
@@ -28,3 +29,20 @@ def test_log_probabilities(amq, V, n, k_w, k_a):
     tol = 1e-4 * ref.pow(2).mean().sqrt() + 1e-5 * want.abs()
     assert bool(((got.double() - want).abs() <= tol).all())
     assert torch.equal(amq.softmax_layer(*W, n, bias, x, k_a, 2), got)
+
+
+# 2047 quarters of the waves, 2048, a row and a half group more; one vector, few and the most that this kernel takes
+@pytest.mark.parametrize("m,n", [(2 * 8188, 4096), (2 * 8188 + 1, 4000), (2 * 8192 + 5, 2100), (4 * 8188, 2048), (4 * 8188 + 1, 1025),
+                                 (4 * 8188 + 7, 1999), (8 * 8188 + 3, 1024), (16385, 8192)])
+@pytest.mark.parametrize("B,k_w,k_a", [(1, 2, 2), (1, 3, 3), (2, 2, 3), (4, 1, 4), (16, 3, 2)])
+def test_products(amq, m, n, B, k_w, k_a):
+    import torch
+    W, _, X, bias, ref = operands(amq, m, n, B, k_w, k_a)
+    tol = 1e-4 * ref.abs() + 1e-4 * ref.pow(2).mean(1, keepdim=True).sqrt()
+    Y = amq.binary_gemm(*W, n, *X, bias=bias)
+    assert bool(((Y.double() - ref).abs() <= tol).all())
+    # half of the rows at a time are fewer waves than the line, and the same sums
+    h = m // 2
+    parts = [amq.binary_gemm(W[0][:, r].contiguous(), W[1][r].contiguous(), n, *X, bias=bias[r]) for r in (slice(0, h), slice(h, m))]
+    if n > 1024 or B <= 4:  # (else the matrix cores)
+        assert torch.equal(torch.cat(parts, 1), Y)
