@@ -425,9 +425,7 @@ static bool single_marks(int64_t I, int64_t H, int epi) { return epi == amq::kEp
 static bool resident_sequence(const ResidentWs& w, int64_t I, int64_t H, int64_t B, int k_w, int k_a, int epi, int64_t steps,
                               hipStream_t s) {
   const int64_t piece = steps < piece_steps(B) ? steps : piece_steps(B);
-  if (!w.total || !amq::seqw_supported(I, H, B, k_w, k_a, epi, piece)) return false;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+  return w.total && amq::seqw_supported(I, H, B, k_w, k_a, epi, piece) && !amq::maybe_captured(s);
 }
 
 // One piece of `n` steps on it, given the codes of the piece's inputs (in w) and, in b, everything else.
@@ -455,9 +453,7 @@ static int resident_piece(const ResidentWs& w, const amq::BmvArgs& b, int64_t n,
 // captured.  (In a graph the launches that claim room are not queued together, so the kernel of light claims serves there,
 // or the per-step launches.)
 static bool single_sequence(int64_t I, int64_t H, int64_t B, int k_w, int k_a, hipStream_t s) {
-  if (!amq::seq1_supported(I, H, B, k_w, k_a) || !grid_fits_device()) return false;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+  return amq::seq1_supported(I, H, B, k_w, k_a) && grid_fits_device() && !amq::maybe_captured(s);
 }
 
 // One piece of `n` steps given the codes of its inputs in w.  Where nothing tells the caller that a wait gave up, a launch

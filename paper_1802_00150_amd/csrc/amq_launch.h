@@ -26,6 +26,15 @@ inline hipError_t ensure_dynamic_lds(const void* fn, int bytes, std::atomic<unsi
   return hipSuccess;
 }
 
+// Whether the stream is being captured, or cannot be asked (the null stream while a blocking stream is being captured; the
+// launches that follow must not find the query's error).
+inline bool maybe_captured(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 #ifdef AMQ_PHASE_TIMING
 // Profiling build only: the device buffer the phase timers write to (null: timers off), set through
 // the extra entry point amq_debug_set_phase_buffer of that build.

@@ -231,8 +231,7 @@ bool step_once_supported(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_
   for (const BmvBlock& k : a.blk) pairs += (long long)a.batch * vector_pairs(k_a, 4 * ((k.n + 127) >> 7));
   int units = 0;
   if (pairs > kSlotPairs || !hand_over_memory(units) || workgroups(a) > units) return false;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+  return !maybe_captured(s);
 }
 
 hipError_t launch_step_once(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s) {

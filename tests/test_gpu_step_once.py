@@ -101,3 +101,34 @@ def test_graph_replays(amq):
         torch.cuda.synchronize()
         assert same((h, c), s.two_launches())
         s.x.copy_(x)
+
+
+def test_null_stream_beside_a_captured_one(amq):
+    # whether the null stream is being captured cannot be asked while a blocking stream is: steps and sequences run all the same
+    import ctypes
+    import torch
+    s = Step(amq, 4, 300, 300, 7, 2, 2)
+    want = s.two_launches()
+    xs, ws = s.x.repeat(5, 1, 1), amq.lstm_sequence_workspace(300, 300, 7, 2, "cuda:0")
+
+    def sequence(h, c):
+        amq.lstm_sequence(*s.d, *s.args, *s.bias, xs, h, c, 2, 2, ws=ws)
+        return h, c
+    seq = sequence(s.h.clone(), s.c.clone())
+    hip, stream = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p()
+    assert hip.hipStreamCreate(ctypes.byref(stream)) == 0
+    x, h, c = torch.zeros(16, device="cuda:0"), torch.empty_like(s.h), torch.empty_like(s.c)
+    state = s.h.clone(), s.c.clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(torch.cuda.ExternalStream(stream.value)):
+        graph.capture_begin(capture_error_mode="relaxed")
+        try:
+            x.add_(1)
+            with torch.cuda.stream(torch.cuda.default_stream()):
+                s.into(s.h, h, s.c, c)
+                got = sequence(*state)
+        finally:
+            graph.capture_end()
+    torch.cuda.synchronize()
+    assert same((h, c), want) and same(got, seq)
