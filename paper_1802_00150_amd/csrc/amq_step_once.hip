@@ -53,8 +53,10 @@ __global__ __launch_bounds__(64 * kOnceWaves, NC == 1 && KW * KA <= 4 ? 4 : 2) v
   constexpr int NW = kOnceWaves / 2;  // waves per vector
   constexpr int NJ = 4 * NC;          // slots per lane
   constexpr int kWords = 32 * NC;     // words of a row, padding included
+  constexpr int kEntry = (KA * (kWords + 1) + 1) & ~1;  // codes and coefficients of a vector, written in 8-byte pieces
+  static_assert(kEntry * sizeof(uint32_t) % sizeof(unsigned long long) == 0, "the second vector's codes are aligned too");
   __shared__ double sh[2][2 * kExchange<NW>];
-  __shared__ __attribute__((aligned(8))) uint32_t codes[2][KA * (kWords + 1)];
+  __shared__ __attribute__((aligned(8))) uint32_t codes[2][kEntry];
   __shared__ float4 xch[(kOnceWaves / 2) * 64];
   __shared__ int missed;
   extern __shared__ __attribute__((aligned(16))) uint4 turn[];
