@@ -245,6 +245,13 @@ void amq_debug_set_sequence_spin_limit(unsigned polls);
 int amq_debug_hold_sequence_shares(int shares, void* stream);
 
 /*
+ * Test hook: a number that grows by one (modulo 2^32) with every step of amq_lstm_step and amq_gru_step that this process issues
+ * as one launch with a hand-over between its workgroups (batches of 2 and more).  `next` >= 0 sets it, so that a test reaches
+ * numbers it would not count up to.
+ */
+unsigned amq_debug_one_launch_steps(int64_t next);
+
+/*
  * Measurement hook: one of the two launches of a steady-state step of amq_lstm_sequence where it takes two
  * per step, on its own, so that each can be timed and profiled under its own name.  half = 0: the front
  * launch (quantizes h and x_next, forms the x-side sums from the input codes the workspace holds);

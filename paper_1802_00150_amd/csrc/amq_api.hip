@@ -704,6 +704,8 @@ size_t amq_lstm_sequence_flag_offset(int64_t I, int64_t H, int64_t B, int k_a) {
 
 void amq_debug_set_sequence_spin_limit(unsigned polls) { amq::set_seqg_spin_limit(polls); }
 
+unsigned amq_debug_one_launch_steps(int64_t next) { return amq::step_once_launches(next); }
+
 int amq_debug_hold_sequence_shares(int shares, void* stream) {
   if (shares < -8 || shares > 8) return AMQ_ERR_INVALID;
   return hip_status(amq::launch_hold_shares(shares, static_cast<hipStream_t>(stream)));

@@ -391,6 +391,8 @@ hipError_t launch_seq_recover(const SeqWArgs& a, int k_w, int k_a, int epi, hipS
 // a.raw: x_t and h_{t-1}, which no output may overlap.  Asks the stream whether it is being captured (then: not supported).
 bool step_once_supported(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s);
 hipError_t launch_step_once(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s);
+// Test hook: tag of the next such launch; next >= 0 sets it.
+unsigned step_once_launches(long long next);
 
 // ---- the recurrent step of a sequence with given inputs, cut along the operand blocks ----------
 // Front launch: quantizes the vectors of q (seg[0] = h_{t-1}, seg[1] = a later x, count 0 for none) and of

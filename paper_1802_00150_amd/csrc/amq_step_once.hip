@@ -34,6 +34,8 @@ constexpr int kOnceWaves = 8;
 constexpr unsigned kHandOverPolls = 64;  // about 40 us
 constexpr int kHandOverSlots = 32;
 constexpr int kSlotPairs = 16384;        // 128 KiB
+constexpr int kMostCycles = 4;
+std::atomic<unsigned> next_tag{1};
 static __device__ unsigned long long hand_over[kHandOverSlots][kSlotPairs];
 
 // Pairs of a vector: the words of its codes, plane by plane, then the coefficients; whole cache lines of 16.
@@ -227,6 +229,12 @@ long long workgroups(const BmvArgs& a) { return a.batch + (long long)row_groups(
 // 1500 batch 20 8.5 / 8.5, 2048 batch 4 8.9 / 8.1; W3/A3 300 batch 8 8.2 / 7.55, 1024 batch 8 8.8 / 8.5, 32 9.0 / 9.0.  Beyond, the
 // waiting workgroups are in the way of each other: 1024 units batch 64 (320 workgroups) W2/A2 7.8 / 8.2, W3/A3 9.3 / 10.5.
 bool step_once_supported(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s) {
+  // Cycles of the quantizer beyond the usual two: four waves per vector beside the workgroups that wait take 0.44 (2 bits) to 0.78 us
+  // (3 bits, 1024 entries) per cycle, the quantizer by itself 0.36 and 0.58.  Two launches / one, W2/A2, us, T = 2, 4, 6, 10, 20: 300
+  // units batch 4 6.5 / 6.1, 7.2 / 6.9, 7.9 / 7.75, 9.4 / 9.4, 13.0 / 13.7; 650 batch 13 7.0 / 6.8, 7.8 / 7.7, 8.6 / 8.6, 10.3 / 10.4,
+  // 14.3 / 15.0.  From about 40 on the waits give up before the codes are there, and every workgroup quantizes its tile: 650 batch 13
+  // T = 100 47 / 631.
+  if (a.T > kMostCycles) return false;
   if (a.batch < 2 || k_w < 2 || k_w > 3 || k_a < 2 || k_a > 3 || !a.raw[0] || !a.raw[1]) return false;
   if (!mfma4_pair_supported(a, k_w, k_a, epi) || mfma32_cell_supported(a, k_w, k_a, epi)) return false;
   long long pairs = 0;
@@ -236,15 +244,18 @@ bool step_once_supported(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_
   return !maybe_captured(s);
 }
 
+unsigned step_once_launches(long long next) {
+  return next < 0 ? next_tag.load(std::memory_order_relaxed) : next_tag.exchange((unsigned)next, std::memory_order_relaxed);
+}
+
 hipError_t launch_step_once(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s) {
-  static std::atomic<unsigned> launches{0};
   int units = 0;
   unsigned long long* const memory = hand_over_memory(units);
   if (!memory) return hipErrorInvalidValue;
   OnceArgs o{};
   o.b = a;
   AMQ_PHASE_ATTACH(o.b);
-  do o.tag = launches.fetch_add(1, std::memory_order_relaxed);
+  do o.tag = next_tag.fetch_add(1, std::memory_order_relaxed);
   while (o.tag == 0u);  // (0 is what the slots hold at first)
   o.pairs = memory + (size_t)(o.tag % kHandOverSlots) * kSlotPairs;
   o.polls = sequence_spin_limit() < kHandOverPolls ? sequence_spin_limit() : kHandOverPolls;

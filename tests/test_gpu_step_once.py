@@ -19,7 +19,7 @@ class Step:
         print("step in one launch gates=%d I=%d H=%d B=%d W%d/A%d" % (gates, I, H, B, k_w, k_a), flush=True)
         g = torch.Generator(device="cuda:0").manual_seed(I + 3 * H + B + seed)
         randn = lambda *s: torch.randn(*s, generator=g, device="cuda:0")  # noqa: E731
-        self.amq, self.gates, self.args, self.k_a = amq, gates, (I, H), k_a
+        self.amq, self.gates, self.args, self.k_a, self.T = amq, gates, (I, H), k_a, 2
         self.d = [*amq.quantize_weights(randn(gates * H, I) * 0.04, k_w, 2), *amq.quantize_weights(randn(gates * H, H) * 0.04, k_w, 2)]
         self.bias = [randn(gates * H) * 0.1 for _ in range(1 if gates == 4 else 2)]
         self.x, self.h, self.c = randn(B, I), torch.tanh(randn(B, H)), randn(B, H)
@@ -27,9 +27,9 @@ class Step:
 
     def into(self, h, h_out, c, c_out):
         if self.gates == 4:
-            self.amq.lstm_step(*self.d, *self.args, *self.bias, self.x, h, c, self.k_a, 2, ws=self.ws, h_out=h_out, c_out=c_out)
+            self.amq.lstm_step(*self.d, *self.args, *self.bias, self.x, h, c, self.k_a, self.T, ws=self.ws, h_out=h_out, c_out=c_out)
             return h_out, c_out
-        self.amq.gru_step(*self.d, *self.args, *self.bias, self.x, h, self.k_a, 2, ws=self.ws, h_out=h_out)
+        self.amq.gru_step(*self.d, *self.args, *self.bias, self.x, h, self.k_a, self.T, ws=self.ws, h_out=h_out)
         return (h_out,)
 
     def two_launches(self):
@@ -39,6 +39,13 @@ class Step:
     def once(self):
         import torch
         return self.into(self.h, torch.full_like(self.h, -7.0), self.c, torch.full_like(self.c, -7.0))
+
+
+def launched_once(amq, call):
+    """Result of the call, and whether it was issued as one launch."""
+    before = amq.binding.debug_one_launch_steps()
+    got = call()
+    return got, amq.binding.debug_one_launch_steps() - before == 1
 
 
 def same(a, b):
@@ -65,6 +72,15 @@ def test_same_as_two_launches(amq, gates, I, H, B, k_w, k_a):
     finally:
         amq.binding.debug_set_sequence_spin_limit(0)
     assert same(got, want)
+
+
+@pytest.mark.parametrize("T,once", [(0, True), (4, True), (5, False), (60, False)])
+def test_many_cycles_take_two_launches(amq, T, once):
+    # one launch would be slower, and from about 40 cycles on much slower: its waits are shorter than the quantizer takes
+    s = Step(amq, 4, 300, 300, 7, 2, 2)
+    s.T = T
+    got, one = launched_once(amq, s.once)
+    assert one == once and same(got, s.two_launches())
 
 
 def test_streams_and_slots(amq):
