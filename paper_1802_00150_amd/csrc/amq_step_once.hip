@@ -33,7 +33,7 @@ namespace {
 constexpr int kOnceWaves = 8;
 constexpr unsigned kHandOverPolls = 64;  // about 40 us
 constexpr int kHandOverSlots = 32;
-constexpr int kSlotPairs = 16384;        // 128 KiB
+constexpr int kSlotPairs = 8192;         // 64 KiB
 constexpr int kMostCycles = 4;
 std::atomic<unsigned> next_tag{1};
 static __device__ unsigned long long hand_over[kHandOverSlots][kSlotPairs];
@@ -100,6 +100,8 @@ __global__ __launch_bounds__(64 * kOnceWaves, NC == 1 && KW * KA <= 4 ? 4 : 2) v
   };
 
   if ((int)blockIdx.x < batch) {
+    // (ahead of the waiting waves of a workgroup beside it: 650 units batch 13 on two streams 3.84 -> 3.71 us per step)
+    __builtin_amdgcn_s_setprio(3);
     int phase = 0;
     const int entry = blockIdx.x, k = wv / NW, t = tid & (64 * NW - 1);
     quantize_entry(entry, phase);
@@ -224,10 +226,15 @@ long long workgroups(const BmvArgs& a) { return a.batch + (long long)row_groups(
 
 }  // namespace
 
-// Shapes of the paired kernel, 2- and 3-bit codes, as long as every workgroup has a compute unit of its own.  Two launches / one,
-// us per LSTM step: W2/A2 300 units batch 4 7.2 / 6.0, 64 7.3 / 6.5, 650 batch 13 7.1 / 6.65, 1024 batch 48 (240 workgroups) 7.7 / 7.3,
-// 1500 batch 20 8.5 / 8.5, 2048 batch 4 8.9 / 8.1; W3/A3 300 batch 8 8.2 / 7.55, 1024 batch 8 8.8 / 8.5, 32 9.0 / 9.0.  Beyond, the
-// waiting workgroups are in the way of each other: 1024 units batch 64 (320 workgroups) W2/A2 7.8 / 8.2, W3/A3 9.3 / 10.5.
+// Shapes of the paired kernel, 2- and 3-bit weights and 2-bit activations, as long as the workgroups are few.  Two launches / one,
+// us per LSTM step W2/A2 on one stream, and per step of two and four streams that are kept busy: 300 units batch 8 6.6 / 6.1, 3.45 /
+// 3.2, 1.89 / 1.74; 512 batch 16 6.6 / 6.3, 3.49 / 3.44, 1.92 / 1.89; 650 batch 13 7.1 / 6.7, 3.72 / 3.76, 2.10 / 2.10.  With more
+// workgroups the quantizing ones find waiting ones of another stream beside them, where the quantizer by itself, which needs few
+// registers and no LDS, fits anywhere: 650 batch 16 (57) 7.1 / 6.9, 3.7 / 3.9, 2.1 / 2.2, 1024 batch 12 (76) 7.0 / 7.0, 3.7 / 4.1, 2.1 / 2.3,
+// batch 48 (240) 7.4 / 7.6, 4.0 / 4.9, 2.5 / 3.3.  Up to four entries have fewer such encounters: 1024 batch 4 (68) 7.0 / 6.6, 3.56 / 3.52,
+// 2.04 / 1.96, 1300 batch 4 (86) 8.2 / 7.8, 4.2 / 4.0, 2.4 / 2.3, 1500 batch 4 (98) 8.2 / 7.9, 4.2 / 4.1, 2.43 / 2.56.
+// 3-bit activations are quantized slower here than by themselves: a step that is waited for takes 21.4 us and not 20.7 (650 units batch
+// 13), one among others 8.8 and not 8.7.
 bool step_once_supported(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s) {
   // Cycles of the quantizer beyond the usual two: four waves per vector beside the workgroups that wait take 0.44 (2 bits) to 0.78 us
   // (3 bits, 1024 entries) per cycle, the quantizer by itself 0.36 and 0.58.  Two launches / one, W2/A2, us, T = 2, 4, 6, 10, 20: 300
@@ -235,12 +242,12 @@ bool step_once_supported(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_
   // 14.3 / 15.0.  From about 40 on the waits give up before the codes are there, and every workgroup quantizes its tile: 650 batch 13
   // T = 100 47 / 631.
   if (a.T > kMostCycles) return false;
-  if (a.batch < 2 || k_w < 2 || k_w > 3 || k_a < 2 || k_a > 3 || !a.raw[0] || !a.raw[1]) return false;
+  if (a.batch < 2 || k_w < 2 || k_w > 3 || k_a != 2 || !a.raw[0] || !a.raw[1]) return false;
   if (!mfma4_pair_supported(a, k_w, k_a, epi) || mfma32_cell_supported(a, k_w, k_a, epi)) return false;
   long long pairs = 0;
   for (const BmvBlock& k : a.blk) pairs += (long long)a.batch * vector_pairs(k_a, 4 * ((k.n + 127) >> 7));
   int units = 0;
-  if (pairs > kSlotPairs || !hand_over_memory(units) || workgroups(a) > units) return false;
+  if (pairs > kSlotPairs || !hand_over_memory(units) || 32 * workgroups(a) > (a.batch <= 4 ? 12 : 7) * units) return false;
   return !maybe_captured(s);
 }
 
@@ -249,6 +256,7 @@ unsigned step_once_launches(long long next) {
 }
 
 hipError_t launch_step_once(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s) {
+  if (k_a != 2) return hipErrorInvalidValue;
   int units = 0;
   unsigned long long* const memory = hand_over_memory(units);
   if (!memory) return hipErrorInvalidValue;
@@ -263,8 +271,7 @@ hipError_t launch_step_once(const BmvArgs& a, int k_w, int k_a, int epi, hipStre
   o.gx = row_groups(a);
   const int grid = (int)workgroups(a);
   const int nc = a.blk[0].n > 1024 || a.blk[1].n > 1024 ? 2 : 1;
-  if (k_w == 2) return k_a == 2 ? run_k<2, 2>(o, grid, epi, nc, s) : run_k<2, 3>(o, grid, epi, nc, s);
-  return k_a == 2 ? run_k<3, 2>(o, grid, epi, nc, s) : run_k<3, 3>(o, grid, epi, nc, s);
+  return k_w == 2 ? run_k<2, 2>(o, grid, epi, nc, s) : run_k<3, 2>(o, grid, epi, nc, s);
 }
 
 }  // namespace amq

@@ -53,19 +53,25 @@ def same(a, b):
     return all(torch.equal(p, q) for p, q in zip(a, b))
 
 
-# one entry more and fewer than a tile, ragged units and vectors, one and two stretches, blocks of unequal stretches, the most
-# workgroups that still take this path (240 of 256) and more
-SHAPES = [(300, 300, 2, 2, 2), (650, 650, 13, 2, 2), (1, 1030, 17, 2, 3), (128, 1024, 16, 2, 2), (700, 701, 33, 3, 2),
-          (1500, 1500, 20, 2, 2), (2048, 2048, 5, 3, 3), (2000, 333, 31, 3, 3), (1024, 1024, 48, 2, 3), (1024, 1024, 64, 3, 3)]
+# one launch: one entry more and fewer than a tile, ragged units and vectors, one and two stretches, blocks of unequal stretches, the
+# most workgroups that still take this path (56 of 256, up to four entries 96) ...
+ONCE = [(300, 300, 2, 2, 2), (650, 650, 13, 2, 2), (1, 300, 17, 2, 2), (2048, 333, 16, 3, 2), (701, 650, 15, 3, 2),
+        (129, 1030, 4, 2, 2), (1024, 1024, 4, 3, 2), (1500, 1500, 2, 3, 2), (33, 1, 7, 2, 2)]
+# ... and two: one workgroup more, other numbers of bits, larger batches
+TWICE = [(701, 650, 16, 3, 2), (1024, 1024, 5, 2, 2), (1536, 1537, 2, 2, 2), (300, 300, 4, 2, 3), (1, 1030, 17, 2, 3), (128, 1024, 16, 2, 2),
+         (700, 701, 33, 3, 2), (1500, 1500, 20, 2, 2), (2048, 2048, 5, 3, 3), (2000, 333, 31, 3, 3), (1024, 1024, 48, 2, 3),
+         (1024, 1024, 64, 3, 3)]
 
 
 @pytest.mark.parametrize("gates", [4, 3])
-@pytest.mark.parametrize("I,H,B,k_w,k_a", SHAPES)
+@pytest.mark.parametrize("I,H,B,k_w,k_a", ONCE + TWICE)
 def test_same_as_two_launches(amq, gates, I, H, B, k_w, k_a):
     s = Step(amq, gates, I, H, B, k_w, k_a)
-    want = s.two_launches()
+    want, one = launched_once(amq, s.two_launches)
+    assert not one
     for _ in range(3):
-        assert same(s.once(), want)
+        got, one = launched_once(amq, s.once)
+        assert one == ((I, H, B, k_w, k_a) in ONCE) and same(got, want)
     amq.binding.debug_set_sequence_spin_limit(1)  # (every wait gives up at its first poll)
     try:
         got = s.once()
@@ -85,7 +91,7 @@ def test_many_cycles_take_two_launches(amq, T, once):
 
 def test_streams_and_slots(amq):
     import torch
-    steps = [Step(amq, 4, 300, 300, 7, 2, 2), Step(amq, 3, 650, 650, 20, 3, 3), Step(amq, 4, 1100, 1024, 9, 2, 3)]
+    steps = [Step(amq, 4, 300, 300, 7, 2, 2), Step(amq, 3, 650, 650, 14, 3, 2), Step(amq, 4, 1100, 1024, 4, 2, 2)]
     want = [s.two_launches() for s in steps]
     streams = [torch.cuda.Stream() for _ in steps]
     torch.cuda.synchronize()
