@@ -12,9 +12,9 @@
 // itself: it needs nobody then, so results depend neither on the order of the workgroups nor on how many are resident.  The
 // inputs are therefore read by workgroups that start late; the host takes this path only where no output overlaps them.
 //
-// The pairs live in memory of the library (a slot per launch, taken in turn), which is zero at first and is written by nobody else; a
-// tag is used once in 2^32 launches, so an old pair is not taken for a new one.  Should as many later launches as there are slots have
-// overwritten a slot that is still waited for, those waits end as above.  A captured launch would carry the same tag at every replay:
+// The pairs live in memory of the library (a slot per launch, taken in turn), which is zero at first and is written by nobody else.  A
+// tag is used again after 2^32 launches; all slots are cleared four times in between, so that an old pair is not taken for a new one.
+// Should that, or as many later launches as there are slots, meet a slot that is still waited for, those waits end as above.  A captured launch would carry the same tag at every replay:
 // there the step stays two launches.
 //
 // The arithmetic and its order are those of the two launches: the results are the same bit for bit.
@@ -34,6 +34,7 @@ constexpr int kOnceWaves = 8;
 constexpr unsigned kHandOverPolls = 64;  // about 40 us
 constexpr int kHandOverSlots = 32;
 constexpr int kSlotPairs = 8192;         // 64 KiB
+constexpr unsigned kClearEvery = 1u << 30;
 constexpr int kMostCycles = 4;
 std::atomic<unsigned> next_tag{1};
 static __device__ unsigned long long hand_over[kHandOverSlots][kSlotPairs];
@@ -47,6 +48,10 @@ struct OnceArgs {
   unsigned tag, polls;
   int rowblocks, gx;         // gx: workgroups of a batch tile
 };
+
+__global__ __launch_bounds__(256) void clear_slots_kernel(unsigned long long* pairs) {
+  put_pair(pairs + blockIdx.x * 256 + threadIdx.x, 0u, 0u);
+}
 
 // NC: stretches of 1024 entries of the longer operand block (1 or 2).  (The register bounds are such that nothing is spilled: a few
 // bytes of scratch per lane cost 0.7 us here.)
@@ -263,8 +268,15 @@ hipError_t launch_step_once(const BmvArgs& a, int k_w, int k_a, int epi, hipStre
   OnceArgs o{};
   o.b = a;
   AMQ_PHASE_ATTACH(o.b);
-  do o.tag = next_tag.fetch_add(1, std::memory_order_relaxed);
-  while (o.tag == 0u);  // (0 is what the slots hold at first)
+  do {
+    o.tag = next_tag.fetch_add(1, std::memory_order_relaxed);
+    if (o.tag % kClearEvery == 0u) {
+      static_assert(kHandOverSlots * kSlotPairs % 256 == 0, "whole workgroups");
+      hipLaunchKernelGGL(clear_slots_kernel, dim3(kHandOverSlots * kSlotPairs / 256), dim3(256), 0, s, memory);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+  } while (o.tag == 0u);  // (0 is what cleared slots hold)
   o.pairs = memory + (size_t)(o.tag % kHandOverSlots) * kSlotPairs;
   o.polls = sequence_spin_limit() < kHandOverPolls ? sequence_spin_limit() : kHandOverPolls;
   o.rowblocks = (int)((a.H + 3) / 4);
