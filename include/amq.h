@@ -232,7 +232,8 @@ int amq_lstm_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t*
  * one-launch recurrence gives up, for launches issued from now on (process-wide; 0
  * restores the default of 2^19).  With 1 the first wait that is not satisfied at once
  * gives up, every workgroup leaves, and the documented failure state results without
- * any kernel hanging.
+ * any kernel hanging; and the waits of steps that take one launch (batches of 2 and more) are never satisfied, so
+ * that every workgroup quantizes for itself, with the same results.
  */
 void amq_debug_set_sequence_spin_limit(unsigned polls);
 

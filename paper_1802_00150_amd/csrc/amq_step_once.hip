@@ -45,6 +45,7 @@ __host__ __device__ constexpr int vector_pairs(int k_a, int wpr) { return (k_a *
 struct OnceArgs {
   BmvArgs b;                 // raw[0], raw[1]: the inputs and the previous state
   unsigned long long* pairs; // this launch's slot: vectors x_0 .. , then h_0 ..
+  unsigned long long* awaited;  // where the codes are looked for: the same, or (test hook) a slot in which this tag never is
   unsigned tag, polls;
   int rowblocks, gx;         // gx: workgroups of a batch tile
 };
@@ -71,14 +72,14 @@ __global__ __launch_bounds__(64 * kOnceWaves, NC == 1 && KW * KA <= 4 ? 4 : 2) v
   asm volatile("" ::AMQ_ARG(a.blk[0].Wp), AMQ_ARG(a.blk[0].alpha), AMQ_ARG(a.blk[0].n), AMQ_ARG(a.blk[1].Wp),
                AMQ_ARG(a.blk[1].alpha), AMQ_ARG(a.blk[1].n), AMQ_ARG(a.m), AMQ_ARG(a.H), AMQ_ARG(a.batch), AMQ_ARG(a.bias0),
                AMQ_ARG(a.bias1), AMQ_ARG(a.c_prev), AMQ_ARG(a.h_prev), AMQ_ARG(a.h_out), AMQ_ARG(a.c_out), AMQ_ARG(a.raw[0]),
-               AMQ_ARG(a.raw[1]), AMQ_ARG(a.T), AMQ_ARG(o.pairs), AMQ_ARG(o.tag), AMQ_ARG(o.rowblocks), AMQ_ARG(o.gx));
+               AMQ_ARG(a.raw[1]), AMQ_ARG(a.T), AMQ_ARG(o.pairs), AMQ_ARG(o.awaited), AMQ_ARG(o.tag), AMQ_ARG(o.rowblocks), AMQ_ARG(o.gx));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int batch = a.batch;
   // (formed from the arguments at every use: as captured variables they are kept in memory)
   auto wpr = [&](int k) { return 4 * (((k ? a.blk[1].n : a.blk[0].n) + 127) >> 7); };
-  auto vector_at = [&](int k, int entry) {
-    return o.pairs + (k ? batch * vector_pairs(KA, wpr(0)) + entry * vector_pairs(KA, wpr(1)) : entry * vector_pairs(KA, wpr(0)));
+  auto vector_at = [&](unsigned long long* slot, int k, int entry) {
+    return slot + (k ? batch * vector_pairs(KA, wpr(0)) + entry * vector_pairs(KA, wpr(1)) : entry * vector_pairs(KA, wpr(0)));
   };
 
   // The codes and coefficients of a batch entry's two vectors in LDS, a half of the waves each; ends with a barrier.
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(64 * kOnceWaves, NC == 1 && KW * KA <= 4 ? 4 : 2) v
     const int entry = blockIdx.x, k = wv / NW, t = tid & (64 * NW - 1);
     quantize_entry(entry, phase);
     const int w = wpr(k);
-    if (t < KA * (w + 1)) put_pair(vector_at(k, entry) + t, codes[k][t], o.tag);
+    if (t < KA * (w + 1)) put_pair(vector_at(o.pairs, k, entry) + t, codes[k][t], o.tag);
     return;
   }
 
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(64 * kOnceWaves, NC == 1 && KW * KA <= 4 ? 4 : 2) v
     unsigned long long v[2][KA][kColReq], bv;
     unsigned spins = 0;
     for (;;) {
-      bv = get_pair(vector_at(kb, b0 + (l16 < ncols ? l16 : ncols - 1)) + KA * wpr(kb) + plane);
+      bv = get_pair(vector_at(o.awaited, kb, b0 + (l16 < ncols ? l16 : ncols - 1)) + KA * wpr(kb) + plane);
 #pragma unroll
       for (int k = 0; k < 2; ++k)
 #pragma unroll
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(64 * kOnceWaves, NC == 1 && KW * KA <= 4 ? 4 : 2) v
 #pragma unroll
           for (int j = 0; j < KA; ++j) v[k][j][q] = (unsigned long long)o.tag << 32;
           if (col < ncols && gw < wpr(k)) {
-            const unsigned long long* const from = vector_at(k, b0 + col) + gw;
+            const unsigned long long* const from = vector_at(o.awaited, k, b0 + col) + gw;
 #pragma unroll
             for (int j = 0; j < KA; ++j) v[k][j][q] = get_pair(from + j * wpr(k));
           }
@@ -279,6 +280,7 @@ hipError_t launch_step_once(const BmvArgs& a, int k_w, int k_a, int epi, hipStre
   } while (o.tag == 0u);  // (0 is what cleared slots hold)
   o.pairs = memory + (size_t)(o.tag % kHandOverSlots) * kSlotPairs;
   o.polls = sequence_spin_limit() < kHandOverPolls ? sequence_spin_limit() : kHandOverPolls;
+  o.awaited = o.polls > 1 ? o.pairs : memory + (size_t)((o.tag + 1) % kHandOverSlots) * kSlotPairs;
   o.rowblocks = (int)((a.H + 3) / 4);
   o.gx = row_groups(a);
   const int grid = (int)workgroups(a);

@@ -1,6 +1,7 @@
 """GPU: recurrent steps of small batches in one launch (amq_step_once.hip).  Steps whose state is updated in place take two launches
 and the same arithmetic: the two agree bit for bit, also where every wait gives up and the workgroups quantize for themselves, on
-several streams with more launches than there are slots, and in a replayed graph."""
+several streams whose launches take every slot several times, when tags come round, and in a replayed graph.  Which form a step took is
+read from the library's count."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -72,12 +73,13 @@ def test_same_as_two_launches(amq, gates, I, H, B, k_w, k_a):
     for _ in range(3):
         got, one = launched_once(amq, s.once)
         assert one == ((I, H, B, k_w, k_a) in ONCE) and same(got, want)
-    amq.binding.debug_set_sequence_spin_limit(1)  # (every wait gives up at its first poll)
+    # every wait gives up: the codes are looked for where they never are
+    amq.binding.debug_set_sequence_spin_limit(1)
     try:
-        got = s.once()
+        got, one = launched_once(amq, s.once)
     finally:
         amq.binding.debug_set_sequence_spin_limit(0)
-    assert same(got, want)
+    assert one == ((I, H, B, k_w, k_a) in ONCE) and same(got, want)
 
 
 @pytest.mark.parametrize("T,once", [(0, True), (4, True), (5, False), (60, False)])
@@ -95,12 +97,13 @@ def test_streams_and_slots(amq):
     want = [s.two_launches() for s in steps]
     streams = [torch.cuda.Stream() for _ in steps]
     torch.cuda.synchronize()
-    got = []
+    got, before = [], amq.binding.debug_one_launch_steps()
     for _ in range(40):
         for i, s in enumerate(steps):
             with torch.cuda.stream(streams[i]):
                 got.append((i, s.once()))
     torch.cuda.synchronize()
+    assert amq.binding.debug_one_launch_steps() - before == len(got) > 3 * 32  # (slots)
     assert all(same(g, want[i]) for i, g in got)
 
 
@@ -133,8 +136,10 @@ def test_graph_replays(amq):
     want = s.two_launches()
     h, c = torch.empty_like(s.h), torch.empty_like(s.c)
     graph = torch.cuda.CUDAGraph()
+    before = amq.binding.debug_one_launch_steps()
     with torch.cuda.graph(graph):
         s.into(s.h, h, s.c, c)
+    assert amq.binding.debug_one_launch_steps() == before  # (a captured tag would come back at every replay)
     for _ in range(3):
         h.fill_(-7.0), c.fill_(-7.0)
         graph.replay()
