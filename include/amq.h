@@ -245,6 +245,9 @@ void amq_debug_set_sequence_spin_limit(unsigned polls);
  */
 int amq_debug_hold_sequence_shares(int shares, void* stream);
 
+/* Test hook: the room that such launches have taken when the stream gets there (0: none), written to room [1]. */
+int amq_debug_sequence_room(uint32_t* room, void* stream);
+
 /*
  * Test hook: a number that grows by one (modulo 2^32) with every step of amq_lstm_step and amq_gru_step that this process issues
  * as one launch with a hand-over between its workgroups (batches of 2 and more).  `next` >= 0 sets it, so that a test reaches

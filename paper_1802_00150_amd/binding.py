@@ -25,7 +25,7 @@ EXPORTS = [
     "amq_lstm_workspace_bytes", "amq_lstm_step", "amq_lstm_step_static", "amq_lstm_step_packed",
     "amq_lstm_step_packed_grouped", "amq_stream_read_probe", "amq_lstm_sequence",
     "amq_lstm_sequence_flag_offset", "amq_lstm_sequence_workspace_bytes", "amq_debug_set_sequence_spin_limit",
-    "amq_debug_hold_sequence_shares", "amq_debug_one_launch_steps",
+    "amq_debug_hold_sequence_shares", "amq_debug_sequence_room", "amq_debug_one_launch_steps",
     "amq_gru_sequence", "amq_gru_sequence_workspace_bytes",
     "amq_debug_lstm_split_half",
     "amq_gru_workspace_bytes", "amq_gru_step",
@@ -80,6 +80,7 @@ def lib():
         L.amq_debug_set_sequence_spin_limit.argtypes = [C.c_uint]
         L.amq_debug_set_sequence_spin_limit.restype = None
         L.amq_debug_hold_sequence_shares.argtypes = [_int, _p]
+        L.amq_debug_sequence_room.argtypes = [_p, _p]
         L.amq_debug_one_launch_steps.argtypes = [_i64]
         L.amq_debug_one_launch_steps.restype = C.c_uint
         L.amq_lstm_step.argtypes = [_p, _p, _p, _p, _i64, _i64, _int, _p, _p, _p, _p, _i64, _int, _int, _p, _p,
@@ -347,6 +348,11 @@ def debug_set_sequence_spin_limit(polls):
 def debug_hold_sequence_shares(shares):
     """Test hook: takes (negative: gives back) shares of the chip that the one-launch sequences claim room in."""
     _check(lib().amq_debug_hold_sequence_shares(int(shares), _stream()))
+
+
+def debug_sequence_room(room):
+    """Test hook: writes the room that one-launch sequences have taken, when the stream gets there, to the int32 tensor `room` [1]."""
+    _check(lib().amq_debug_sequence_room(_dev(room, torch.int32), _stream()))
 
 
 def debug_one_launch_steps(next=-1):

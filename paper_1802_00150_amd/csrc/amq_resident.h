@@ -17,7 +17,8 @@
 // the forms of amq_seq1_body.h for 513 to 1024 units (up to 160), with one wave per SIMD and workgroup.
 //
 // A launch that finds the chip its own (no claim, nobody waiting) may take more room than it needs, `alone`, to put its workgroups
-// where they hear of each other sooner.
+// where they hear of each other sooner.  What other streams would have done beside it they then do later, or on fewer compute units of
+// that die, so this is only for a program that uses one stream: note_stream() and lone_stream().
 //
 // The word on the device: full shares in bits 0..7, light ones in bits 8..15, and the door.  Whoever finds no room closes
 // the door and is the next to get some; small claims do not keep a large one waiting for ever.
@@ -42,6 +43,13 @@ struct ResidentClaim {
 };
 ResidentClaim resident_claim(long long grid, bool light);
 std::mutex& resident_launches();
+
+// Every call of the library: the stream it is on.
+void note_stream(hipStream_t s);
+// Asked once per launch that could use a chip of its own (under resident_launches()): whether the calls since some such launches ago
+// were all on one stream.  A stream that is given up for another counts for a while and then no more.  Only the time a call takes
+// depends on the answer.
+bool lone_stream();
 
 __device__ __forceinline__ bool resident_room(unsigned used, const ResidentClaim& c) {
   const unsigned sum = (used & ~kDoor) + c.mine, full = sum & 255u, light = sum >> 8;
@@ -80,5 +88,7 @@ __device__ __forceinline__ void give_resident_share(const ResidentClaim& c, unsi
 }
 // Test hook: takes (or with a negative number gives back) full shares without waiting.
 hipError_t launch_hold_shares(int shares, hipStream_t s);
+// Test hook: writes the word to `room`.
+hipError_t launch_read_shares(unsigned* room, hipStream_t s);
 
 }  // namespace amq

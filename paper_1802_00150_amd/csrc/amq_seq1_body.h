@@ -26,11 +26,13 @@
 // sit on one die: workgroups go to the dies in turn, so of eight times as many every eighth takes part and the others leave at
 // once.  What is published then comes back from that die's own L2.  us per 35-step sequence, spread / on one die: LSTM 200
 // units W2/A2 85.7 / 74.7, 300 units 89.8 / 81.2, W2/A3 110.7 / 105.7, W3/A3 113.3 / 109.4, 400 units 93.3 / 83.5, 448 units 97.5 / 81.7, GRU 300
-// units 93.6 / 79.9, 448 units W3/A3 125.4 / 120.3.  Nothing but the time depends on where they are.  Two to four streams of
-// such sequences stay within a few per cent either way (300 units 106 / 108, 122 / 120, 133 / 138; W3/A3 at 300 and 400 units up to 6 %
-// behind), as the launches are eight times as wide.  Two workgroups of four quantizing waves on a unit are
-// in each other's way (650 units 109 / 192), so larger grids stay spread.  On a die they count for four engines instead of 32, which
-// is room that launches on other streams would lack: seqg_reset_kernel takes it only if there is no other claim, and records it.
+// units 93.6 / 79.9, 448 units W3/A3 125.4 / 120.3.  Nothing but the time depends on where they are.
+// Two workgroups of four quantizing waves on a unit are in each other's way (650 units 109 / 192), so larger grids stay spread.
+// On a die they count for four engines instead of 32, which is room, and on that die compute units, that other streams would lack: us
+// per 60 steps beside a second stream, spread / on one die, 300 units on two streams 162 / 169, beside 600 units batch 40 286 / 292, beside
+// a quantizer of 16384 x 4096 214 / 269 (and that, three times, 226 / 260), 448 units beside a 10000 x 1024 product of 1024 vectors, six
+// times, 284 / 326.  So this is only for a program that calls the library on one stream (lone_stream()), and seqg_reset_kernel
+// takes that room only if there is no other claim, and records it.
 //
 // Every wait is bounded.  If one gives up a flag is raised and everybody leaves; the caller of this launch follows it with
 // one that either computes the piece again from the saved state or takes it back and marks what was derived from it
@@ -242,9 +244,9 @@ hipError_t run_form(const Seq1Args& a, hipStream_t s) {
   // units 264 / 288 -> 232 / 248, W3/A3 251 / 339 -> 212 / 294.  Grids of up to 512 units are one or two shares of eight as they are.
   q.claim = resident_claim(grid, QW == 4 && U == 1);
   q.groups = grid;
-  const bool die = QW == 1 && q.claim.word && q.claim.shares == 8u && grid > kDieEngines && grid <= kDieGrid;
-  if (die) q.claim.alone = (unsigned)((grid + kDieEngines - 1) / kDieEngines);
   std::lock_guard<std::mutex> together(resident_launches());
+  const bool die = QW == 1 && q.claim.word && q.claim.shares == 8u && grid > kDieEngines && grid <= kDieGrid && lone_stream();
+  if (die) q.claim.alone = (unsigned)((grid + kDieEngines - 1) / kDieEngines);
   hipError_t e = launch_seqg_reset(q.sync, q.hbuf, q.h, q.c, q.save_h, q.save_c, q.H, q.clear_flag, q.claim, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((seq1_kernel<KW, KA, EPI, QW, NJ, U, JOINT>), dim3((unsigned)(die ? kDies * grid : grid)), dim3(64 * k1Waves), 0, s,

@@ -597,6 +597,10 @@ __global__ void hold_shares_kernel(unsigned* word, unsigned shares) {
   __hip_atomic_fetch_add(word, shares, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__global__ void read_shares_kernel(unsigned* word, unsigned* room) {
+  *room = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 struct ResidentDevice {
   std::atomic<unsigned*> word;
   std::atomic<unsigned> shares;
@@ -646,10 +650,37 @@ std::mutex& resident_launches() {
   return m;
 }
 
+namespace {
+constexpr int kCrowdPieces = 32;
+std::atomic<hipStream_t> latest_stream{nullptr};
+std::atomic<bool> any_stream{false};
+std::atomic<int> crowd{0};  // launches for which the change of streams still counts
+}  // namespace
+
+// (several threads at once: a change of streams that one of them misses is seen at its next call)
+void note_stream(hipStream_t s) {
+  if (latest_stream.load(std::memory_order_relaxed) == s && any_stream.load(std::memory_order_relaxed)) return;
+  latest_stream.store(s, std::memory_order_relaxed);
+  if (any_stream.exchange(true, std::memory_order_relaxed)) crowd.store(kCrowdPieces, std::memory_order_relaxed);
+}
+
+bool lone_stream() {
+  const int left = crowd.load(std::memory_order_relaxed);
+  if (left > 0) crowd.store(left - 1, std::memory_order_relaxed);
+  return left == 0;
+}
+
 hipError_t launch_hold_shares(int shares, hipStream_t s) {
   const ResidentClaim c = resident_device();
   if (!c.word) return hipErrorInvalidValue;
   hipLaunchKernelGGL(hold_shares_kernel, dim3(1), dim3(1), 0, s, c.word, (unsigned)shares);
+  return hipGetLastError();
+}
+
+hipError_t launch_read_shares(unsigned* room, hipStream_t s) {
+  const ResidentClaim c = resident_device();
+  if (!c.word) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(read_shares_kernel, dim3(1), dim3(1), 0, s, c.word, room);
   return hipGetLastError();
 }
 
