@@ -383,31 +383,38 @@ __global__ __launch_bounds__(64 * NWV) void mfma4wc_kernel(BmvArgs a, int rb_per
   // past the end of a row meets 0.0 of the staged operand): weight words, whole rows of 128 bytes by 8 adjacent lanes (16 bytes of
   // 64 rows per request keep the memory pipe busy four times as long), to be turned into the A view through LDS; row coefficients
   // and biases, one value per lane (lane l < 16 KW: coefficient l % KW of tile row l / KW); previous state in the C view (lane =
-  // (unit l4, batch column l16)).  Those of the first row block go out before the activations are staged, those of the next one
-  // before the contraction of the current: asked for where they were used, the weights of either operand block and the
-  // coefficients cost a trip to memory each (W2/A2, us per step with its quantizer: LSTM 600 units batch 600 16.8 -> 14.6, GRU 1024
-  // units batch 256 with a projection of 10000 words 27.0 -> 26.5).
+  // (unit l4, batch column l16)).  Those of the first row block go out between the staging of the activations and the barrier, those
+  // of the next one before the contraction of the current: asked for where they were used, the weights of either operand block and
+  // the coefficients cost a trip to memory each.  us per LSTM step on packed operands, where they were used / all before the staging,
+  // which they delay / here: W2/A2 600 units batch 600 12.6 / 10.2 / 9.6, 1024 batch 256 8.2 / 8.35 / 7.6, W1/A2 6.7 / 7.1 / 6.5, W4/A1 9.5 /
+  // 10.0 / 8.5, W2/A3 1000 units batch 160 11.0 / 10.2 / 9.3.  Of 78 combinations of size and bits none is slower than the first.
+  // With four planes in a workgroup of eight waves only block 0 is asked for a row block ahead, block 1 when its row block begins: both
+  // are 256 registers with 9 spilled (W4/A1 LSTM), block 0 is 240 and none.
+  constexpr bool kBothBlocks = KW < 4 || NWV < 8;
   struct Row {
     uint4 w[2][KW][2];
     float coef[2], bias[2], prev[NBT];
   };
-  auto request = [&](int rb, Row& r) {
+  auto matrix_row = [&](int rb, int tile_row) {
+    const int unit = rb * 4 + (tile_row >> 2), gate = tile_row & 3;
+    return (gate < NG ? gate : 0) * H + (unit < H ? unit : H - 1);
+  };
+  auto request_weights = [&](int rb, int k, Row& r) {
     rb = rb < rowblocks ? rb : rowblocks - 1;
-    auto matrix_row = [&](int tile_row) {
-      const int unit = rb * 4 + (tile_row >> 2), gate = tile_row & 3;
-      return (gate < NG ? gate : 0) * H + (unit < H ? unit : H - 1);
-    };
-    const int rows[2] = {matrix_row(lane >> 3), matrix_row(8 + (lane >> 3))}, row = matrix_row(l16);
+    const int rows[2] = {matrix_row(rb, lane >> 3), matrix_row(rb, 8 + (lane >> 3))};
+    const uint4* const Wp4 = reinterpret_cast<const uint4*>(a.blk[k].Wp) + ((lane & 7) < wq[k] ? (lane & 7) : 0);
+    const int plane = m * wq[k];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const uint4* const Wp4 = reinterpret_cast<const uint4*>(a.blk[k].Wp) + ((lane & 7) < wq[k] ? (lane & 7) : 0);
-      const int plane = m * wq[k];
+    for (int i = 0; i < KW; ++i)
 #pragma unroll
-      for (int i = 0; i < KW; ++i)
-#pragma unroll
-        for (int v = 0; v < 2; ++v) r.w[k][i][v] = Wp4[rows[v] * wq[k] + i * plane];
-    }
-    const int cl = lane < 16 * KW ? lane : 0, crow = matrix_row(cl / KW);
+      for (int v = 0; v < 2; ++v) r.w[k][i][v] = Wp4[rows[v] * wq[k] + i * plane];
+  };
+  auto request = [&](int rb, Row& r) {
+    request_weights(rb, 0, r);
+    if constexpr (kBothBlocks) request_weights(rb, 1, r);
+    rb = rb < rowblocks ? rb : rowblocks - 1;
+    const int row = matrix_row(rb, l16);
+    const int cl = lane < 16 * KW ? lane : 0, crow = matrix_row(rb, cl / KW);
 #pragma unroll
     for (int k = 0; k < 2; ++k) r.coef[k] = a.blk[k].alpha[crow * KW + cl % KW];
     r.bias[0] = a.bias0 ? a.bias0[row] : 0.0f;
@@ -420,8 +427,6 @@ __global__ __launch_bounds__(64 * NWV) void mfma4wc_kernel(BmvArgs a, int rb_per
       r.prev[bt] = (EPI == kEpiLstm) ? a.c_prev[t] : a.h_prev[t];
     }
   };
-  Row next;
-  request(rb_first + wv, next);
 
   // per batch column of this lane (one per tile) and operand block: beta_j
   int bcol[NBT];
@@ -440,10 +445,13 @@ __global__ __launch_bounds__(64 * NWV) void mfma4wc_kernel(BmvArgs a, int rb_per
 #pragma unroll
   for (int k = 0; k < 2; ++k)
     stage_activation_words<KA, NBT, 64 * NWV>(xw[k], btile + k * kBlockBytes, nlen[k]);
+  Row next;
+  request(rb_first + wv, next);
   lds_barrier();  // (the requests under way are not waited for)
 
   for (int rb = rb_first + wv; rb < rb_end; rb += NWV) {
     Row now = next;
+    if constexpr (!kBothBlocks) request_weights(rb, 1, now);
     if (rb + NWV < rb_end) request(rb + NWV, next);
     // C view: this lane's hidden unit, rows r = gate r
     const int unit_c = rb * 4 + l4;
@@ -600,7 +608,7 @@ int tiles_per_wave(int k_w, int k_a, int batch) {
 }
 
 // Cell modes: tiles per wave bounded by the accumulators (as above) and by the LDS that both
-// operand blocks' activation tiles take (2 * NBT * KA * 8 KiB <= 144 KiB).  With at most four
+// operand blocks' activation tiles take (2 * NBT * KA * 8 KiB <= 144 KiB, of 160 with the waves' pieces of 2.25).  With at most four
 // plane pairs, two tiles per wave in 8-wave workgroups fit 256 registers and keep two waves on
 // every SIMD (each hides the other's load latencies: measured faster than four tiles per wave
 // with one wave per SIMD); beyond that, 4-wave workgroups with up to 512 registers per wave.

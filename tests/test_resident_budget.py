@@ -46,6 +46,14 @@ def registers():
     return {name: (k[".vgpr_count"] + 7) // 8 * 8 for name, k in kernels().items()}
 
 
+def test_large_steps_spill_nothing():
+    # recurrent steps with several tiles per wave, every number of bits (amq_mfma4w.hip)
+    hits = {n: k for n, k in kernels().items() if "14mfma4wc_kernel" in n}
+    assert len(hits) == 38, sorted(hits)
+    for name, k in hits.items():
+        assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, (name, k[".vgpr_spill_count"])
+
+
 def of(registers, pattern, count):
     hits = {k: v for k, v in registers.items() if re.search(pattern, k)}
     assert len(hits) == count, sorted(hits)
