@@ -138,7 +138,8 @@ __device__ __forceinline__ void stage_activation_words(const uint4 (&xw)[(NBT * 
   }
 }
 
-template <int KW, int KA, int NBT>
+// FIRST: a wave in its contraction has precedence (launch_one).
+template <int KW, int KA, int NBT, bool FIRST>
 __global__ __launch_bounds__(64 * kWaves) void mfma4w_kernel(BmvArgs a, int rb_per_wg, int rowblocks) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int kGroupB = NBT * kTileB;               // batch entries per workgroup
@@ -160,10 +161,15 @@ __global__ __launch_bounds__(64 * kWaves) void mfma4w_kernel(BmvArgs a, int rb_p
   if (rb_end > rowblocks) rb_end = rowblocks;
 
   // ---- packed activation words, 16 bytes per thread and round, coalesced.  Item e: group q = e % 8 of the row of batch entry
-  // (e / 8) % kGroupB of plane e / (8 kGroupB).  Staged when the first weights have been asked for too (after the barrier instead:
-  // 42000 x 1024 W3/A3 batch 64 17.0 us, now 16.2, W2/A2 batch 32 10.1, 9.8).
+  // (e / 8) % kGroupB of plane e / (8 kGroupB).  Staged while the coefficients are under way, before the first weights are asked for;
+  // with twelve products per tile at once, or the words would be spilled (W4/A3 4096 x 512 batch 256 9.1 us, 9.8).
+  constexpr bool kAtOnce = KW * KA >= 12;
   uint4 xw[kIter];
   load_activation_words<KA, NBT, 64 * kWaves>(a.blk[0].Xp, batch, bg0, wq, xw);
+  if constexpr (kAtOnce) {
+    stage_activation_words<KA, NBT, 64 * kWaves>(xw, btile, nlen);
+    lds_barrier();
+  }
 
   // coefficients of this lane's batch column, one column per tile
   int bcol[NBT];
@@ -214,15 +220,11 @@ __global__ __launch_bounds__(64 * kWaves) void mfma4w_kernel(BmvArgs a, int rb_p
     const int bi = rbc * 16 + l16;
     bs = a.bias0 ? a.bias0[bi < m ? bi : m - 1] : 0.0f;
   };
-  // Of the two waves of a SIMD the one in its contraction goes first (by age, a wave in its epilogue keeps the matrix cores from the
-  // younger one), from more than four row blocks per wave on: W2/A2, us, 10000 x 900 batch 1000 25.0 -> 23.7, 42000 x 1024 batch 256
-  // 24.6 -> 23.5; with two or three 0 to 2 % slower (10000 x 1024 W3/A3 batch 128 12.7 / 12.9).
-  const bool contraction_first = rb_per_wg > 4 * kWaves;
   uint4 anext[KW][2];
   float coef_next, bias_next;
+  if constexpr (!kAtOnce) stage_activation_words<KA, NBT, 64 * kWaves>(xw, btile, nlen);
   request_rowblock(rb_first + wv, anext, coef_next, bias_next);
-  stage_activation_words<KA, NBT, 64 * kWaves>(xw, btile, nlen);
-  lds_barrier();  // (the weights under way are not waited for)
+  if constexpr (!kAtOnce) lds_barrier();  // (the weights under way are not waited for)
 
   for (int rb = rb_first + wv; rb < rb_end; rb += kWaves) {
     // ---- weight side of the row block, shared by all tiles
@@ -249,9 +251,9 @@ __global__ __launch_bounds__(64 * kWaves) void mfma4w_kernel(BmvArgs a, int rb_p
     }
     // ---- contraction with all tiles
     v4f acc[NBT][KW][KA];
-    if (contraction_first) __builtin_amdgcn_s_setprio(2);
+    if constexpr (FIRST) __builtin_amdgcn_s_setprio(2);
     contract_tiles<KW, KA, NBT>(araw, tile, acc);
-    if (contraction_first) __builtin_amdgcn_s_setprio(0);
+    if constexpr (FIRST) __builtin_amdgcn_s_setprio(0);
 
     // ---- epilogue per tile, lane = (batch column l16, row quad l4): the accumulators are the dot products
     // d_ij of the codes (integers, exact in binary32);  y = sum_i alpha_i sum_j beta_j d_ij
@@ -551,6 +553,10 @@ int blocks_each(int rowblocks, int groups) {
   return per < kWaves ? kWaves : per;
 }
 
+// Of the two waves of a SIMD the one in its contraction goes first (by age, a wave in its epilogue keeps the matrix cores from the
+// younger one), from more than four row blocks per wave on: us, 10000 x 900 W2/A2 batch 1000 25.0 -> 23.7, 20000 x 300 W4/A3 batch 1000
+// 93 -> 83; with two or three 0 to 2 % slower (10000 x 1024 W3/A3 batch 128 12.7 / 12.9).  A form of its own, as the branch splits the
+// contraction's scheduling (W4/A3 18 registers spilled, 6).
 template <int KW, int KA, int NBT>
 hipError_t launch_one(BmvArgs a, hipStream_t s, int* lse_slots) {
   if constexpr (NBT > max_tiles(KW, KA) || NBT < 2) {
@@ -559,10 +565,12 @@ hipError_t launch_one(BmvArgs a, hipStream_t s, int* lse_slots) {
     const int rowblocks = (int)((a.m + 15) / 16);
     const int groups = (a.batch + NBT * kTileB - 1) / (NBT * kTileB);
     const int per = blocks_each(rowblocks, groups);
-    const size_t lds = (size_t)NBT * KA * kPlaneBytes + sizeof(int) * NBT * KA * kTileB;
-    static std::atomic<unsigned long long> configured{0};
+    const bool first = per > 4 * kWaves;
+    const auto kernel = first ? &mfma4w_kernel<KW, KA, NBT, true> : &mfma4w_kernel<KW, KA, NBT, false>;
+    constexpr size_t lds = (size_t)NBT * KA * kPlaneBytes;
+    static std::atomic<unsigned long long> configured[2] = {{0}, {0}};
     {
-      hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&mfma4w_kernel<KW, KA, NBT>), (int)lds, configured);
+      hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), (int)lds, configured[first]);
       if (e != hipSuccess) return e;
     }
     dim3 grid((unsigned)((rowblocks + per - 1) / per), (unsigned)groups);
@@ -570,7 +578,7 @@ hipError_t launch_one(BmvArgs a, hipStream_t s, int* lse_slots) {
     if (slots > kLseMaxSlots || slots > a.lse_cap) a.lse_part = nullptr;
     a.lse_slots = (int)slots;
     if (lse_slots) *lse_slots = a.lse_part ? (int)slots : 0;
-    hipLaunchKernelGGL((mfma4w_kernel<KW, KA, NBT>), grid, dim3(64 * kWaves), lds, s, a, per, rowblocks);
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * kWaves), lds, s, a, per, rowblocks);
     return hipGetLastError();
   }
 }

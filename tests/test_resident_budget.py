@@ -54,6 +54,14 @@ def test_large_steps_spill_nothing():
         assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, (name, k[".vgpr_spill_count"])
 
 
+def test_large_products_spill_little():
+    # several tiles per wave (amq_mfma4w.hip): a few coefficients where 96 accumulators are held, no operands
+    hits = {n: k for n, k in kernels().items() if "13mfma4w_kernel" in n}
+    assert len(hits) == 74, sorted(hits)
+    for name, k in hits.items():
+        assert k[".vgpr_spill_count"] <= 8, (name, k[".vgpr_spill_count"])
+
+
 def of(registers, pattern, count):
     hits = {k: v for k, v in registers.items() if re.search(pattern, k)}
     assert len(hits) == count, sorted(hits)
