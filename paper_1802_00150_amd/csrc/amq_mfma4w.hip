@@ -162,8 +162,9 @@ __global__ __launch_bounds__(64 * kWaves) void mfma4w_kernel(BmvArgs a, int rb_p
 
   // ---- packed activation words, 16 bytes per thread and round, coalesced.  Item e: group q = e % 8 of the row of batch entry
   // (e / 8) % kGroupB of plane e / (8 kGroupB).  Staged while the coefficients are under way, before the first weights are asked for;
-  // with twelve products per tile at once, or the words would be spilled (W4/A3 4096 x 512 batch 256 9.1 us, 9.8).
-  constexpr bool kAtOnce = KW * KA >= 12;
+  // with nine products per tile after that (W3/A3 20000 x 900 batch 70 10.2 us, 10.9), with twelve at once, or the words would be spilled
+  // (W4/A3 4096 x 512 batch 256 9.1, 9.8).
+  constexpr bool kWeightsFirst = KW * KA == 9, kAtOnce = KW * KA >= 12;
   uint4 xw[kIter];
   load_activation_words<KA, NBT, 64 * kWaves>(a.blk[0].Xp, batch, bg0, wq, xw);
   if constexpr (kAtOnce) {
@@ -222,8 +223,9 @@ __global__ __launch_bounds__(64 * kWaves) void mfma4w_kernel(BmvArgs a, int rb_p
   };
   uint4 anext[KW][2];
   float coef_next, bias_next;
+  if constexpr (kWeightsFirst) request_rowblock(rb_first + wv, anext, coef_next, bias_next);
   if constexpr (!kAtOnce) stage_activation_words<KA, NBT, 64 * kWaves>(xw, btile, nlen);
-  request_rowblock(rb_first + wv, anext, coef_next, bias_next);
+  if constexpr (!kWeightsFirst) request_rowblock(rb_first + wv, anext, coef_next, bias_next);
   if constexpr (!kAtOnce) lds_barrier();  // (the weights under way are not waited for)
 
   for (int rb = rb_first + wv; rb < rb_end; rb += kWaves) {
