@@ -83,7 +83,8 @@ __device__ __forceinline__ void static_for(F f) {
   }
 }
 
-template <int KW, int KA, int NT, int NP, int OUT>
+// AHEAD: a wave in its contraction has precedence (contraction_first).
+template <int KW, int KA, int NT, int NP, int OUT, bool AHEAD>
 __global__ __launch_bounds__(64 * kWaves) void mfma32_kernel(BmvArgs a, int rb_per_wg, int rowblocks, int groups,
                                                               int per_xcd) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -119,9 +120,11 @@ __global__ __launch_bounds__(64 * kWaves) void mfma32_kernel(BmvArgs a, int rb_p
   // request takes whole rows, and the weights after the first piece are asked for when every wave has asked for its share of the
   // image.  (Columns adjacent, 16 bytes of 64 rows per request, and all weights behind them: the image is complete 3.3 us after
   // the start, not 2.2; 10000 x 1024 W2/A3 batch 256 13.4 us, not 12.5.)  Column c of (k-block, piece) lies at c ^ swizzle: the
-  // writes of 16 lanes then meet all banks, and so do the reads.
+  // writes of 16 lanes then meet all banks, and so do the reads.  Rows of 5 and 6 pieces, which no number of lanes divides into, columns
+  // adjacent (10000 x 650 W2/A2 batch 100 5.7 / 6.0, 36000 x 650 W2/A3 batch 40 7.3 / 7.6).
   // Longer rows: columns adjacent, four requests of a thread at a time, the first weight pieces behind them (pieces adjacent:
   // 0 to 8 % slower, 8475 x 2068 W3/A3 batch 99 24.0 / 24.9).
+  constexpr bool kWholeRows = NP == 2 || NP == 4;
   uint4 w[kRing][KW];
   {
     const uint4* Xp4 = reinterpret_cast<const uint4*>(a.blk[0].Xp);
@@ -133,7 +136,7 @@ __global__ __launch_bounds__(64 * kWaves) void mfma32_kernel(BmvArgs a, int rb_p
     };
     auto item = [&](unsigned e) {
       Item x;
-      if constexpr (NP > 0) {
+      if constexpr (kWholeRows) {
         const unsigned q = e / (2u * NP), g = e % (2u * NP);
         x = Item{q / kTileN, q % kTileN, g / NP, g % NP};
       } else {
@@ -242,10 +245,7 @@ __global__ __launch_bounds__(64 * kWaves) void mfma32_kernel(BmvArgs a, int rb_p
       bias_req = a.bias0 ? a.bias0[bi < m ? bi : m - 1] : 0.0f;
     }
 
-    // Of the two waves of a SIMD the one in its contraction goes first; by age, a wave in its epilogue keeps the matrix cores from
-    // the younger one (42000 x 1024 W2/A2 batch 2240 scored 146 -> 136 us, 25433 x 445 W3/A3 batch 959 54.7 -> 51.8; longer rows
-    // +-2 %).
-    if constexpr (NP > 0) __builtin_amdgcn_s_setprio(2);
+    if constexpr (AHEAD) __builtin_amdgcn_s_setprio(2);
     v16f acc[NT][KW][KA];
     // k-step s of the piece in `cur` (the piece after it in `nxt`): the operands of the following step are fetched (from
     // `column` of its piece) and expanded under the matrix instructions
@@ -309,7 +309,7 @@ __global__ __launch_bounds__(64 * kWaves) void mfma32_kernel(BmvArgs a, int rb_p
     // (pinned in uniform control flow: the compiler takes a matrix instruction for lane-local and would sink it under
     // the store predicates)
     settle_accumulators<32>();
-    if constexpr (NP > 0) __builtin_amdgcn_s_setprio(0);
+    if constexpr (AHEAD) __builtin_amdgcn_s_setprio(0);
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -442,6 +442,16 @@ inline int blocks_each(int rowblocks, int groups) {
   return (rowblocks + splits - 1) / splits;
 }
 
+// Whether, of the two waves of a SIMD, the one in its contraction goes first.  By age, a wave in its epilogue keeps the matrix cores
+// from the younger one: 42000 x 1024 W2/A2 batch 2240 scored 146 -> 136 us, 25433 x 445 W3/A3 batch 959 54.7 -> 51.8, 36000 x 589 W2/A3
+// batch 70 10.5 -> 9.8 (rows of more than 1024 entries +-2 %, left alone).  Not where a SIMD has three row blocks, two of them the older
+// wave's, which age serves better (10000 x 300 W3/A2 batch 256 7.44 / 7.68; from 769 entries on no difference), nor with short rows and
+// one tile per wave where half of the SIMDs have five (20000 x 250 W2/A2 batch 200 8.41 / 8.75, but two tiles, batch 256, 13.3 / 12.8).
+inline bool contraction_first(int np, int nt, int per) {
+  const int of_simd = (per + 3) / 4;
+  return np > 0 && !(np < 4 && of_simd == 3) && !(np == 2 && nt == 1 && of_simd == 5 && per <= 18);
+}
+
 template <int KW, int KA, int NT, int NP, int OUT>
 hipError_t launch_form(BmvArgs a, hipStream_t s, int* lse_slots) {
   const int rowblocks = (int)((a.m + kTileN - 1) / kTileN);
@@ -457,15 +467,19 @@ hipError_t launch_form(BmvArgs a, hipStream_t s, int* lse_slots) {
   const int splits = (rowblocks + per - 1) / per;
   const int per_xcd = (splits * groups + kXcds - 1) / kXcds;
   const size_t lds = lds_bytes(KW, KA, NT, a.blk[0].n);
-  static std::atomic<unsigned long long> configured{0};
-  hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(&mfma32_kernel<KW, KA, NT, NP, OUT>), kMaxLds, configured);
+  const bool first = contraction_first(NP, NT, per);
+  auto* kernel = &mfma32_kernel<KW, KA, NT, NP, OUT, false>;
+  if constexpr (NP > 0) {
+    if (first) kernel = &mfma32_kernel<KW, KA, NT, NP, OUT, true>;
+  }
+  static std::atomic<unsigned long long> configured[2] = {{0}, {0}};
+  hipError_t e = ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), kMaxLds, configured[first]);
   if (e != hipSuccess) return e;
   if (OUT != kOutY) {
     a.lse_slots = splits;
     if (lse_slots) *lse_slots = splits;
   }
-  hipLaunchKernelGGL((mfma32_kernel<KW, KA, NT, NP, OUT>), dim3((unsigned)(per_xcd * kXcds)), dim3(64 * kWaves), lds, s, a,
-                     per, rowblocks, groups, per_xcd);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(per_xcd * kXcds)), dim3(64 * kWaves), lds, s, a, per, rowblocks, groups, per_xcd);
   return hipGetLastError();
 }
 

@@ -25,6 +25,21 @@ def test_products(amq, n, m, B, k_w, k_a):
     assert bool(((Y.double() - ref).abs() <= tol).all())
 
 
+# amq_mfma32_body.h: three row blocks per SIMD, half of the SIMDs with five, one and two tiles of columns per wave
+@pytest.mark.parametrize("n", [300, 650, 1000])
+@pytest.mark.parametrize("m,B,k_w,k_a", [(10000, 256, 3, 2), (20000, 200, 2, 2), (20000, 200, 2, 3), (36000, 256, 2, 2)])
+def test_precedence_by_row_blocks(amq, n, m, B, k_w, k_a):
+    test_products(amq, n, m, B, k_w, k_a)
+
+
+# amq_mfma4w.hip: eight, nine and twelve products per tile, at most four row blocks per wave and more
+@pytest.mark.parametrize("n", [129, 1000])
+@pytest.mark.parametrize("m,B", [(2000, 500), (9001, 70), (30001, 300)])
+@pytest.mark.parametrize("k_w,k_a", [(2, 4), (3, 3), (3, 4), (4, 3), (4, 2)])
+def test_many_products_per_tile(amq, n, m, B, k_w, k_a):
+    test_products(amq, n, m, B, k_w, k_a)
+
+
 # batches of the kernel with several tiles per wave: one, two and more row blocks per wave, units not a multiple of 4
 @pytest.mark.parametrize("I,H,B,k_w,k_a", [(1, 1024, 256, 2, 2), (129, 1021, 250, 2, 2), (1024, 602, 600, 2, 2), (300, 1001, 200, 1, 3),
                                            (897, 1003, 161, 4, 1), (640, 1024, 190, 1, 1), (513, 1002, 130, 2, 4)])
