@@ -1,4 +1,6 @@
 // Small-batch binary matrix-vector products (amq_bmv_body.h) on quantized operands: instantiations and launch rules.
+#include <atomic>
+
 #include "amq_bmv_body.h"
 
 namespace amq {
@@ -9,6 +11,25 @@ template <int KW, int KA, int NSEG, int NBLK, int EPI, bool LSE = false>
 __global__ __launch_bounds__(256) void bmv_kernel(BmvArgs a) {
   extern __shared__ uint4 xs[];
   bmv_body<KW, KA, NSEG, NBLK, EPI, LSE, false>(a, xs, nullptr, nullptr);
+}
+
+// Waves of a plain product that the chip holds at once, asked once per form (one kind of chip is built for).
+template <int KW, int KA, int NSEG>
+long long resident_waves() {
+  static std::atomic<long long> known{0};
+  long long waves = known.load(std::memory_order_relaxed);
+  if (waves == 0) {
+    int dev = 0, units = 0, blocks = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &blocks, reinterpret_cast<const void*>(&bmv_kernel<KW, KA, NSEG, 1, kEpiStore, false>), 256, 0) != hipSuccess) {
+      (void)hipGetLastError();  // (only the split depends on it)
+    }
+    waves = 4LL * (units > 0 ? units : 256) * (blocks > 0 ? blocks : 4);
+    known.store(waves, std::memory_order_relaxed);
+  }
+  return waves;
 }
 
 template <int KW, int KA, int NSEG, int NBLK, int EPI>
@@ -40,19 +61,20 @@ hipError_t launch_epi(const BmvArgs& a, int epi, hipStream_t s, int* lse_slots) 
       // One row group per wave.  From where that is more waves than the chip holds (8192; `waves4` is a quarter of them): four
       // (all loads in flight) for products read from memory and groups of them, where the pairs of a log-softmax are left (one
       // group would leave more of them than fit), and for 1-bit weights, whose waves have little else to hide their start with
-      // (42000 x 4096 W1/A1 batch 2 6.0 us, 6.9 with one).  One vector: two, unless they take more rounds of resident waves.
+      // (42000 x 4096 W1/A1 batch 2 6.0 us, 6.9 with one).  One vector, and two with 2-bit weights and 1-bit activations (34000 x 4096 7.4,
+      // 8.0 with one): two, unless they take more rounds of resident waves (42000 x 2500 W2/A1 5.6 / 6.0); W4/A4 always (25000 x 4096
+      // 13.8, 14.8 with four).
       // With several vectors a wave is bound by its own arithmetic, and one group (41 to 65 registers) leaves room for twice the waves
       // of four.  us per product, four groups / two / one: 20000 x 4096 W2/A2 batch 1 4.8 / 4.2 / 4.5, W3/A3 6.7 / 5.9 / 6.5, batch 3
-      // 13.1 / 10.9 / 11.0, batch 12 40.6 / 32.8 / 30.5; 42000 x 4096 W3/A3 batch 12 75 / 67 / 60; 42000 x 2048 W3/A3 batch 1 (5250
-      // waves of two groups) 6.5 / 7.0; below, 10000 x 4096 W2/A2 4.1 / 3.5 / 3.25.
+      // 13.1 / 10.9 / 11.0, batch 12 40.6 / 32.8 / 30.5; 42000 x 4096 W3/A3 batch 12 75 / 67 / 60; 25000 x 4096 W4/A1 batch 1 10.8 / 9.8 / -; 42000 x 2048 W3/A3
+      // batch 1 (5250 waves of two groups) 6.5 / 7.0; below, 10000 x 4096 W2/A2 4.1 / 3.5 / 3.25.
       const long long waves4 = (a.m + 4LL * R - 1) / (4LL * R), waves2 = (a.m + 2LL * R - 1) / (2LL * R);
       if (waves4 * a.groups >= 2048) {
         if (KW == 1 || a.streaming || a.groups > 1 || a.lse_part) return launch_one<KW, KA, 4, 1, kEpiStore>(a, waves4, lds, s, lse_slots);
         if constexpr (KW > 1) {
-          // (resident waves of the chip, by the registers of the two forms)
-          constexpr long long kOf2 = 1024 * (KW + KA <= 4 ? 8 : KW == 2 && KA == 3 ? 6 : 5), kOf4 = 1024 * (KW + KA <= 4 ? 5 : 4);
-          if (a.batch == 1) {
-            if ((waves2 + kOf2 - 1) / kOf2 > (waves4 + kOf4 - 1) / kOf4)
+          if (a.batch == 1 || (KW * KA == 2 && a.batch == 2)) {
+            const long long of2 = resident_waves<KW, KA, 2>(), of4 = resident_waves<KW, KA, 4>();
+            if (KW * KA < 16 && (waves2 + of2 - 1) / of2 > (waves4 + of4 - 1) / of4)
               return launch_one<KW, KA, 4, 1, kEpiStore>(a, waves4, lds, s, lse_slots);
             return launch_one<KW, KA, 2, 1, kEpiStore>(a, waves2, lds, s, lse_slots);
           }

@@ -34,7 +34,7 @@ def test_log_probabilities(amq, V, n, k_w, k_a):
 # 2047 quarters of the waves, 2048, a row and a half group more; one vector, few and the most that this kernel takes
 @pytest.mark.parametrize("m,n", [(2 * 8188, 4096), (2 * 8188 + 1, 4000), (2 * 8192 + 5, 2100), (4 * 8188, 2048), (4 * 8188 + 1, 1025),
                                  (4 * 8188 + 7, 1999), (8 * 8188 + 3, 1024), (16385, 8192)])
-@pytest.mark.parametrize("B,k_w,k_a", [(1, 2, 2), (1, 3, 3), (2, 2, 3), (4, 1, 4), (16, 3, 2)])
+@pytest.mark.parametrize("B,k_w,k_a", [(1, 2, 2), (1, 3, 3), (2, 2, 3), (4, 1, 4), (16, 3, 2), (1, 4, 4), (1, 4, 1), (2, 2, 1)])
 def test_products(amq, m, n, B, k_w, k_a):
     import torch
     W, _, X, bias, ref = operands(amq, m, n, B, k_w, k_a)
