@@ -14,8 +14,8 @@
 //
 // The pairs live in memory of the library (a slot per launch, taken in turn), which is zero at first and is written by nobody else.  A
 // tag is used again after 2^32 launches; all slots are cleared four times in between, so that an old pair is not taken for a new one.
-// Should that, or as many later launches as there are slots, meet a slot that is still waited for, those waits end as above.  A captured launch would carry the same tag at every replay:
-// there the step stays two launches.
+// Should that, or as many later launches as there are slots, meet a slot that is still waited for, those waits end as above.  A captured
+// launch would carry the same tag at every replay: there the step stays two launches.
 //
 // The arithmetic and its order are those of the two launches: the results are the same bit for bit.
 #include <atomic>
@@ -39,12 +39,10 @@ constexpr int kMostCycles = 4;
 std::atomic<unsigned> next_tag{1};
 static __device__ unsigned long long hand_over[kHandOverSlots][kSlotPairs];
 
-// Pairs of a vector: the words of its codes, plane by plane, then the coefficients; whole cache lines of 16.
-__host__ __device__ constexpr int vector_pairs(int k_a, int wpr) { return (k_a * (wpr + 1) + 15) & ~15; }
-
 struct OnceArgs {
   BmvArgs b;                 // raw[0], raw[1]: the inputs and the previous state
-  unsigned long long* pairs; // this launch's slot: vectors x_0 .. , then h_0 ..
+  // this launch's slot: vectors x_0 .. , then h_0 .., of each the words of its codes, plane by plane, then the coefficients
+  unsigned long long* pairs;
   unsigned long long* awaited;  // where the codes are looked for: the same, or (test hook) a slot in which this tag never is
   unsigned tag, polls;
   int rowblocks, gx;         // gx: workgroups of a batch tile
@@ -79,7 +77,7 @@ __global__ __launch_bounds__(64 * kOnceWaves, NC == 1 && KW * KA <= 4 ? 4 : 2) v
   // (formed from the arguments at every use: as captured variables they are kept in memory)
   auto wpr = [&](int k) { return 4 * (((k ? a.blk[1].n : a.blk[0].n) + 127) >> 7); };
   auto vector_at = [&](unsigned long long* slot, int k, int entry) {
-    return slot + (k ? batch * vector_pairs(KA, wpr(0)) + entry * vector_pairs(KA, wpr(1)) : entry * vector_pairs(KA, wpr(0)));
+    return slot + (k ? batch * seqw_entry_pairs(KA, wpr(0)) + entry * seqw_entry_pairs(KA, wpr(1)) : entry * seqw_entry_pairs(KA, wpr(0)));
   };
 
   // The codes and coefficients of a batch entry's two vectors in LDS, a half of the waves each; ends with a barrier.
@@ -251,7 +249,7 @@ bool step_once_supported(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_
   if (a.batch < 2 || k_w < 2 || k_w > 3 || k_a != 2 || !a.raw[0] || !a.raw[1]) return false;
   if (!mfma4_pair_supported(a, k_w, k_a, epi) || mfma32_cell_supported(a, k_w, k_a, epi)) return false;
   long long pairs = 0;
-  for (const BmvBlock& k : a.blk) pairs += (long long)a.batch * vector_pairs(k_a, 4 * ((k.n + 127) >> 7));
+  for (const BmvBlock& k : a.blk) pairs += (long long)a.batch * seqw_entry_pairs(k_a, 4 * ((k.n + 127) >> 7));
   int units = 0;
   if (pairs > kSlotPairs || !hand_over_memory(units) || 32 * workgroups(a) > (a.batch <= 4 ? 12 : 7) * units) return false;
   return !maybe_captured(s);
