@@ -10,11 +10,8 @@
  *     is, per device, which kernels it has configured and where its static
  *     memory lies, and in that memory the room that running sequences take and
  *     2 MiB through which the workgroups of a one-launch step hand over codes
- *     (shared by all streams and callers; nothing there outlives its launch);
- *     and, for the process, the latest stream it was called on and whether that
- *     changed lately (batch-1 sequences take more of the chip where it did
- *     not; results do not depend on it).  Inputs are never modified.  Outputs
- *     must not alias inputs unless stated.
+ *     (shared by all streams and callers; nothing there outlives its launch).
+ *     Inputs are never modified.  Outputs must not alias inputs unless stated.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Calls only enqueue work; they never synchronise the host.
  *   - Return value: AMQ_OK, or an error code.  Arguments are validated on the
@@ -221,8 +218,7 @@ size_t amq_lstm_sequence_flag_offset(int64_t I, int64_t H, int64_t B, int k_a);
  * can take turns on a workgroup (2- and 3-bit codes; how far, is measured: amq_seqw_tiles.hip), pieces of about 4096 / B steps
  * run in one launch whose workgroups stay resident and exchange h_t and its codes through the workspace.  Such
  * launches (and those of batch 1) share a device: on several streams they run side by side as far as their workgroups
- * fit, and wait their turn where they do not (a batch-1 sequence of up to 448 units takes two to seven eighths of the room
- * if the calls before it were all on its stream, one eighth otherwise); if the workgroups cannot all become resident a launch
+ * fit, and wait their turn where they do not; if the workgroups cannot all become resident a launch
  * that follows computes the piece on its own, so the result does not depend on what else runs.  Otherwise (and on a stream that is being
  * captured) W_x x_t is taken off the recurrent chain with two launches per step.  With a smaller workspace (at least
  * amq_lstm_workspace_bytes) the call runs the steps one after the other.  The arithmetic is the same in all forms.

@@ -32,13 +32,6 @@ int hip_status(hipError_t e) {
   return AMQ_ERR_HIP;
 }
 
-// The stream of a call.
-hipStream_t on(void* stream) {
-  const hipStream_t s = static_cast<hipStream_t>(stream);
-  amq::note_stream(s);
-  return s;
-}
-
 // Address of `scratch` on the current device, looked up once per device.
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
@@ -302,7 +295,7 @@ int quantize_common(const float* X, int64_t rows, int64_t n, int64_t ld, int k, 
   a.seg[1] = amq::QuantSeg{nullptr, 0, 0, 0, nullptr, nullptr};
   a.T = T;
   a.mode = mode;
-  return hip_status(amq::launch_quantize(a, k, on(stream)));
+  return hip_status(amq::launch_quantize(a, k, static_cast<hipStream_t>(stream)));
 }
 
 }  // namespace
@@ -355,7 +348,7 @@ int amq_binary_dots(const uint32_t* Wp, int64_t m, int64_t n, int k_w, const uin
   const float* dummy = reinterpret_cast<const float*>(Wp);
   amq::GemmArgs g = gemm_args(Wp, dummy, m, n, k_w, Xp, dummy, batch, k_a, nullptr, 0, nullptr);
   g.D = D;
-  return run_product(g, on(stream));
+  return run_product(g, static_cast<hipStream_t>(stream));
 }
 
 int amq_binary_gemm(const uint32_t* Wp, const float* alpha, int64_t m, int64_t n, int k_w,
@@ -365,7 +358,7 @@ int amq_binary_gemm(const uint32_t* Wp, const float* alpha, int64_t m, int64_t n
   if (st != AMQ_OK) return st;
   if (!alpha || !beta || !Y) return AMQ_ERR_INVALID;
   amq::GemmArgs g = gemm_args(Wp, alpha, m, n, k_w, Xp, beta, batch, k_a, bias, accumulate ? 1 : 0, Y);
-  return run_product(g, on(stream));
+  return run_product(g, static_cast<hipStream_t>(stream));
 }
 
 int amq_binary_gemv(const uint32_t* Wp, const float* alpha, int64_t m, int64_t n, int k_w,
@@ -389,7 +382,7 @@ int amq_binary_gemv_grouped(int64_t groups, const uint32_t* Wp, const float* alp
   g.g_Xp = (long long)k_a * wpr;
   g.g_beta = k_a;
   g.g_Y = m;
-  return run_product(g, on(stream));
+  return run_product(g, static_cast<hipStream_t>(stream));
 }
 
 size_t amq_lstm_workspace_bytes(int64_t I, int64_t H, int64_t B, int k_a) {
@@ -642,13 +635,13 @@ int amq_lstm_step_packed_grouped(int64_t groups, const uint32_t* Wxp, const floa
   b.g_Xp1 = (long long)k_a * amq_wpr(H);
   b.g_beta = b.g_beta1 = k_a;
   b.g_state = H;
-  return hip_status(amq::launch_bmv(b, k_w, k_a, amq::kEpiLstm, on(stream)));
+  return hip_status(amq::launch_bmv(b, k_w, k_a, amq::kEpiLstm, static_cast<hipStream_t>(stream)));
 }
 
 int amq_stream_read_probe(const void* buf, size_t bytes, void* sink, void* stream) {
   if (!buf || !sink || bytes == 0 || (bytes & 15) || !aligned(buf, 16) || !aligned(sink, 8)) return AMQ_ERR_INVALID;
   return hip_status(amq::launch_stream_read(buf, bytes, static_cast<unsigned long long*>(sink),
-                                            on(stream)));
+                                            static_cast<hipStream_t>(stream)));
 }
 
 int amq_lstm_step_packed(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp, const float* alpha_h,
@@ -661,7 +654,7 @@ int amq_lstm_step_packed(const uint32_t* Wxp, const float* alpha_x, const uint32
   if (!aligned(Wxp, 16) || !aligned(Whp, 16) || !aligned(Xp, 16) || !aligned(Hp, 16)) return AMQ_ERR_INVALID;
   if (I > AMQ_MAX_QUANT_N || H > AMQ_MAX_QUANT_N || B > (1 << 24)) return AMQ_ERR_UNSUPPORTED;
   int st = lstm_fused_launch(Wxp, alpha_x, Whp, alpha_h, I, H, k_w, bias, Xp, beta_x, Hp, beta_h, c_prev, B, k_a,
-                             h_out, c_out, nullptr, on(stream));
+                             h_out, c_out, nullptr, static_cast<hipStream_t>(stream));
   return st >= 0 ? st : AMQ_ERR_UNSUPPORTED;
 }
 
@@ -676,7 +669,7 @@ int amq_lstm_step(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp
   if (st != AMQ_OK) return st;
   StepWs w = carve(workspace, I, H, B, k_a, 4, 1);
   return lstm_step_launch(Wxp, alpha_x, Whp, alpha_h, I, H, k_w, bias, x, h_prev, c_prev, B, k_a, T, h_out,
-                          c_out, nullptr, w, on(stream));
+                          c_out, nullptr, w, static_cast<hipStream_t>(stream));
 }
 
 int amq_lstm_step_static(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp, const float* alpha_h,
@@ -696,7 +689,7 @@ int amq_lstm_step_static(const uint32_t* Wxp, const float* alpha_x, const uint32
   // coefficients by the quantizer, pre-activations by the first product), so nothing is cleared
   StepWs w = carve(ws, I, H, B, k_a, 4, 1);
   return lstm_step_launch(Wxp, alpha_x, Whp, alpha_h, I, H, k_w, bias, x, h_prev, c_prev, B, k_a, T, h_out,
-                          c_out, nullptr, w, on(stream));
+                          c_out, nullptr, w, static_cast<hipStream_t>(stream));
 }
 
 size_t amq_lstm_sequence_workspace_bytes(int64_t I, int64_t H, int64_t B, int k_a) {
@@ -715,12 +708,12 @@ unsigned amq_debug_one_launch_steps(int64_t next) { return amq::step_once_launch
 
 int amq_debug_hold_sequence_shares(int shares, void* stream) {
   if (shares < -8 || shares > 8) return AMQ_ERR_INVALID;
-  return hip_status(amq::launch_hold_shares(shares, on(stream)));
+  return hip_status(amq::launch_hold_shares(shares, static_cast<hipStream_t>(stream)));
 }
 
 int amq_debug_sequence_room(uint32_t* room, void* stream) {
   if (!room) return AMQ_ERR_INVALID;
-  return hip_status(amq::launch_read_shares(room, on(stream)));
+  return hip_status(amq::launch_read_shares(room, static_cast<hipStream_t>(stream)));
 }
 
 int amq_lstm_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp, const float* alpha_h,
@@ -732,11 +725,11 @@ int amq_lstm_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t*
   int st = check_step(Wxp, alpha_x, Whp, alpha_h, I, H, k_w, xs, h, B, k_a, T, h, workspace, workspace_bytes,
                       need);
   if (st != AMQ_OK) return st;
-  if (steps < (1 << 30) && single_sequence(I, H, B, k_w, k_a, on(stream))) {
+  if (steps < (1 << 30) && single_sequence(I, H, B, k_w, k_a, static_cast<hipStream_t>(stream))) {
     // batch 1: the steps of a piece (at most kSeqGMaxSteps) in one launch over the chip, weights resident in registers
     const StepWs w = carve(workspace, I, H, B, k_a, 4, 1);
     return single_run(lstm_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias, nullptr, nullptr, nullptr, nullptr, c, B, h, c, nullptr),
-                      w, xs, steps, k_w, k_a, amq::kEpiLstm, T, h, c, hs, on(stream));
+                      w, xs, steps, k_w, k_a, amq::kEpiLstm, T, h, c, hs, static_cast<hipStream_t>(stream));
   }
   if (steps < (1 << 30) && amq::lstm_seqg_supported(I, H, B, k_w, k_a) && grid_fits_device()) {
     // batch 1: the whole sequence (in pieces of at most kSeqGMaxSteps steps) in one launch over the
@@ -746,17 +739,17 @@ int amq_lstm_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t*
       const int n = (int)(steps - t0 < amq::kSeqGMaxSteps ? steps - t0 : amq::kSeqGMaxSteps);
       amq::SeqGArgs q{Wxp, alpha_x, Whp, alpha_h, (int)I, (int)H, bias, xs + t0 * I, n, h, c,
                       hs ? hs + t0 * H : nullptr, T, 0, w.sync, w.hbuf, w.xq, w.xbeta, t0 == 0, w.pre0, w.pre0 + H};
-      st = hip_status(amq::launch_lstm_seqg(q, k_w, k_a, on(stream)));
+      st = hip_status(amq::launch_lstm_seqg(q, k_w, k_a, static_cast<hipStream_t>(stream)));
       if (st != AMQ_OK) return st;
       // a launch that gave up (or found the flag of an earlier one) leaves its rows of hs as NaN and the state as it was
       st = hip_status(amq::launch_seqg_undo(w.sync, hs ? hs + t0 * H : nullptr, (long long)n * H, h, c, w.pre0, w.pre0 + H, (int)H,
-                                            on(stream)));
+                                            static_cast<hipStream_t>(stream)));
       if (st != AMQ_OK) return st;
     }
     return AMQ_OK;
   }
   StepWs w = carve(workspace, I, H, B, k_a, 4, 1);
-  hipStream_t s = on(stream);
+  hipStream_t s = static_cast<hipStream_t>(stream);
   {
     // The inputs are all given, so W_x x_t is taken off the recurrent chain where the shape allows and the
     // workspace has room (amq_lstm_sequence_workspace_bytes): per step a front launch (quantize h_{t-1} and,
@@ -825,7 +818,7 @@ int amq_debug_lstm_split_half(const uint32_t* Wxp, const float* alpha_x, const u
                              B, h, c, nullptr);
   b.Y = sw.xsum;
   if (!amq::step_split_supported(b, k_w, k_a, amq::kEpiLstm)) return AMQ_ERR_UNSUPPORTED;
-  hipStream_t s = on(stream);
+  hipStream_t s = static_cast<hipStream_t>(stream);
   if (half == 1) return hip_status(amq::launch_step_back(b, k_w, k_a, amq::kEpiLstm, s));
   amq::QuantArgs q{};
   q.seg[0] = amq::QuantSeg{h, H, (int)H, (int)B, sw.step.hp, sw.step.beta_h};
@@ -903,7 +896,7 @@ int amq_gru_step(const uint32_t* Wxp, const float* alpha_x, const uint32_t* Whp,
   if (st != AMQ_OK) return st;
   const StepWs w = carve(workspace, I, H, B, k_a, 3, 2);
   return gru_step_launch(Wxp, alpha_x, Whp, alpha_h, I, H, k_w, bias_x, bias_h, x, h_prev, B, k_a, T, h_out, w,
-                         on(stream));
+                         static_cast<hipStream_t>(stream));
 }
 
 size_t amq_gru_sequence_workspace_bytes(int64_t I, int64_t H, int64_t B, int k_a) {
@@ -920,7 +913,7 @@ int amq_gru_sequence(const uint32_t* Wxp, const float* alpha_x, const uint32_t* 
   int st = check_step(Wxp, alpha_x, Whp, alpha_h, I, H, k_w, xs, h, B, k_a, T, h, workspace, workspace_bytes, need);
   if (st != AMQ_OK) return st;
   if (steps >= (1 << 30)) return AMQ_ERR_UNSUPPORTED;
-  hipStream_t s = on(stream);
+  hipStream_t s = static_cast<hipStream_t>(stream);
   const StepWs w = carve(workspace, I, H, B, k_a, 3, 2);
   const SeqWs sw = carve_seq(workspace, I, H, B, k_a, 3, 2);
   const amq::BmvArgs probe = gru_args(Wxp, alpha_x, Whp, alpha_h, I, H, bias_x, bias_h, sw.xq[0], sw.xbeta[0], w.hp,
@@ -1013,7 +1006,7 @@ int amq_gru_step_reset_before(const uint32_t* Wxp, const float* alpha_x, const u
   if (st != AMQ_OK) return st;
   GruRbWs w = carve_gru_rb(workspace, I, H, B, k_a);
   if (g_out) w.g = g_out;
-  hipStream_t s = on(stream);
+  hipStream_t s = static_cast<hipStream_t>(stream);
   amq::QuantArgs q{};
   q.seg[0] = amq::QuantSeg{x, I, (int)I, (int)B, w.base.xp, w.base.beta_x};
   q.seg[1] = amq::QuantSeg{h_prev, H, (int)H, (int)B, w.base.hp, w.base.beta_h};
@@ -1063,7 +1056,7 @@ int amq_quantize_reconstruct(const float* W, int64_t rows, int64_t cols, int64_t
   q.mode = amq::kQuantFull;
   q.recon = out;
   q.recon_ld = ld_out;
-  return hip_status(amq::launch_quantize_recon(q, k, on(stream)));
+  return hip_status(amq::launch_quantize_recon(q, k, static_cast<hipStream_t>(stream)));
 }
 
 int amq_dequantize(const uint32_t* planes, const float* alpha, int64_t rows, int64_t cols, int k, float* out,
@@ -1072,13 +1065,13 @@ int amq_dequantize(const uint32_t* planes, const float* alpha, int64_t rows, int
   if (!bits_ok(k) || rows <= 0 || cols <= 0 || ld_out < cols) return AMQ_ERR_INVALID;
   if (cols > (1 << 30) || rows > (1LL << 33)) return AMQ_ERR_UNSUPPORTED;
   return hip_status(amq::launch_dequantize(planes, alpha, rows, (int)cols, k, out, ld_out,
-                                           on(stream)));
+                                           static_cast<hipStream_t>(stream)));
 }
 
 int amq_clip(float* w, int64_t n, float lo, float hi, void* stream) {
   if (!w || n <= 0 || !(lo <= hi)) return AMQ_ERR_INVALID;
   if (n > (1LL << 39)) return AMQ_ERR_UNSUPPORTED;
-  return hip_status(amq::launch_clip(w, n, lo, hi, on(stream)));
+  return hip_status(amq::launch_clip(w, n, lo, hi, static_cast<hipStream_t>(stream)));
 }
 
 int amq_quantize_refined_greedy(const float* W, int64_t rows, int64_t cols, int64_t ld, int k, uint32_t* planes,
@@ -1088,7 +1081,7 @@ int amq_quantize_refined_greedy(const float* W, int64_t rows, int64_t cols, int6
   if (!aligned(planes, 16)) return AMQ_ERR_INVALID;
   if (cols > AMQ_MAX_QUANT_N || rows > 0x7fffffffLL) return AMQ_ERR_UNSUPPORTED;
   return hip_status(amq::launch_refined_greedy(W, ld, (int)cols, (int)rows, k, planes, alpha,
-                                               on(stream)));
+                                               static_cast<hipStream_t>(stream)));
 }
 
 int amq_quantize_ternary(const float* W, int64_t rows, int64_t cols, int64_t ld, int T, uint32_t* planes,
@@ -1098,7 +1091,7 @@ int amq_quantize_ternary(const float* W, int64_t rows, int64_t cols, int64_t ld,
   if (!aligned(planes, 16)) return AMQ_ERR_INVALID;
   if (cols > AMQ_MAX_QUANT_N || rows > 0x7fffffffLL) return AMQ_ERR_UNSUPPORTED;
   return hip_status(amq::launch_ternary(W, ld, (int)cols, (int)rows, T, planes, alpha,
-                                        on(stream)));
+                                        static_cast<hipStream_t>(stream)));
 }
 
 int amq_relative_mse(const float* W, int64_t rows, int64_t cols, int64_t ld, int k, const uint32_t* planes,
@@ -1107,7 +1100,7 @@ int amq_relative_mse(const float* W, int64_t rows, int64_t cols, int64_t ld, int
   if (!bits_ok(k) || rows <= 0 || cols <= 0 || ld < cols) return AMQ_ERR_INVALID;
   if (cols > (1 << 30) || rows > (1LL << 33)) return AMQ_ERR_UNSUPPORTED;
   return hip_status(amq::launch_relative_mse(W, rows, (int)cols, ld, k, planes, alpha, row_err, row_norm, result,
-                                             on(stream)));
+                                             static_cast<hipStream_t>(stream)));
 }
 
 int amq_embedding_lookup(const uint32_t* Ep, const float* alpha_e, int64_t vocab, int64_t n, int k,
@@ -1118,13 +1111,13 @@ int amq_embedding_lookup(const uint32_t* Ep, const float* alpha_e, int64_t vocab
   amq::QuantArgs q{};
   q.mode = amq::kQuantFull;
   q.gather = amq::GatherSeg{Ep, alpha_e, vocab, reinterpret_cast<const long long*>(ids), (int)n, (int)B, Xp, beta};
-  return hip_status(amq::launch_quantize(q, k, on(stream)));
+  return hip_status(amq::launch_quantize(q, k, static_cast<hipStream_t>(stream)));
 }
 
 int amq_log_softmax(const float* Y, int64_t B, int64_t V, float* out, void* stream) {
   if (!Y || !out || B <= 0 || V <= 0) return AMQ_ERR_INVALID;
   if (B > 0x7fffffffLL || V > (1LL << 31)) return AMQ_ERR_UNSUPPORTED;
-  return hip_status(amq::launch_log_softmax(Y, B, V, out, on(stream)));
+  return hip_status(amq::launch_log_softmax(Y, B, V, out, static_cast<hipStream_t>(stream)));
 }
 
 // Workspace of the output layer: the quantized h_t and the (max, sum of exponentials) pairs the
@@ -1217,7 +1210,7 @@ int amq_softmax_layer(const uint32_t* Wsp, const float* alpha_s, int64_t V, int6
   if (H > AMQ_MAX_QUANT_N || B > (1 << 24) || V > (1LL << 31)) return AMQ_ERR_UNSUPPORTED;
   SoftmaxWs w = carve_softmax(workspace, V, H, B, k_a);
   return softmax_layer_launch(Wsp, alpha_s, V, H, k_w, bias, h, B, k_a, T, logprob, w,
-                              on(stream));
+                              static_cast<hipStream_t>(stream));
 }
 
 // The recurrent half of a language-model step: lookup + on-line quantization (one launch), then the
@@ -1297,7 +1290,7 @@ int amq_lm_step(const uint32_t* Ep, const float* alpha_e, int64_t vocab, int64_t
   if (st != AMQ_OK) return st;
   if (!aligned(Wsp, 16) || !aligned(Ep, 16)) return AMQ_ERR_INVALID;
   if (V > (1LL << 31)) return AMQ_ERR_UNSUPPORTED;
-  hipStream_t s = on(stream);
+  hipStream_t s = static_cast<hipStream_t>(stream);
   StepWs w = carve(workspace, E, H, B, k_a, 4, 1);
   SoftmaxWs sw = carve_softmax(static_cast<char*>(workspace) + need_step, V, H, B, k_as);
 
@@ -1444,7 +1437,7 @@ static int lm_sequence_impl(const uint32_t* Ep, const float* alpha_e, int64_t vo
   if (st != AMQ_OK) return st;
   if (!aligned(Wsp, 16) || !aligned(Ep, 16)) return AMQ_ERR_INVALID;
   if (V > (1LL << 31) || steps >= (1 << 30)) return AMQ_ERR_UNSUPPORTED;
-  hipStream_t s = on(stream);
+  hipStream_t s = static_cast<hipStream_t>(stream);
   LmSeqWs lw = carve_lm_seq(workspace, E, H, V, B, k_a, k_as);
   StepWs w = carve(workspace, E, H, B, k_a, 4, 1);
   char* soft_base = static_cast<char*>(workspace) + lw.soft_off;

@@ -289,12 +289,11 @@ struct SeqGArgs {
 // Words of sync after the arrival bytes: workgroups that have left, and the room claimed for this launch (0: none).
 constexpr int kSeqGLeft = 1 + kSeqGMaxGrid / 4;
 constexpr int kSeqGClaimed = kSeqGLeft + 1;
-// One thread of a workgroup that is about to leave, of `count` in all: the last one gives the room back.
-__device__ __forceinline__ void seqg_leave(unsigned* sync, const ResidentClaim& claim, unsigned count) {
-  const unsigned taken = sync[kSeqGClaimed];
-  if (taken == 0u) return;
-  if (__hip_atomic_fetch_add(sync + kSeqGLeft, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == count - 1)
-    give_resident_share(claim, taken);
+// One thread of a workgroup that is about to leave: the last one gives the room back.
+__device__ __forceinline__ void seqg_leave(unsigned* sync, const ResidentClaim& claim) {
+  if (sync[kSeqGClaimed] == 0u) return;
+  if (__hip_atomic_fetch_add(sync + kSeqGLeft, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1)
+    give_resident_share(claim);
 }
 // Before a launch of this kind (under resident_launches()): claims its room, clears the tags and, if asked, the flag, and
 // publishes the initial state h as that of tag 0 in the second of the two buffers.  save_h, save_c [H]: receive the
@@ -337,7 +336,6 @@ struct Seq1Args {
   unsigned long long* hbuf;
   // filled by launch_seq1
   int lg;
-  int groups;           // workgroups that take part
   unsigned limit;
   ResidentClaim claim;
 };

@@ -197,7 +197,7 @@ __global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, cons
   if (t == 0) {
     if (clear_flag) sync[0] = 0u;
     sync[kSeqGLeft] = 0u;
-    sync[kSeqGClaimed] = take_resident_share(claim);
+    sync[kSeqGClaimed] = take_resident_share(claim) ? claim.mine : 0u;
   }
   for (unsigned i = 1 + t; i < 1 + kSeqGMaxGrid / 4; i += nt) sync[i] = 0u;
   const unsigned units = (unsigned)H;
@@ -217,7 +217,7 @@ __global__ void seqg_reset_kernel(unsigned* sync, unsigned long long* hbuf, cons
 
 // Should the launch itself fail: nobody is there to leave.
 __global__ void seqg_abandon_kernel(const unsigned* sync, ResidentClaim claim) {
-  if (sync[kSeqGClaimed] != 0u) give_resident_share(claim, sync[kSeqGClaimed]);
+  if (sync[kSeqGClaimed] != 0u) give_resident_share(claim);
 }
 
 __global__ void seqg_undo_kernel(const unsigned* sync, float* out, long long count, float* h, float* c, const float* save_h,
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(64 * kGWaves, 2) void lstm_seqg_kernel(SeqGArgs a) 
   if (threadIdx.x == 0) gave_up = get_u(a.sync);
   __syncthreads();
   if (gave_up != 0u) {
-    if (threadIdx.x == 0) seqg_leave(a.sync, a.claim, gridDim.x);
+    if (threadIdx.x == 0) seqg_leave(a.sync, a.claim);
     return;
   }
   const unsigned limit = a.spin_limit;
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(64 * kGWaves, 2) void lstm_seqg_kernel(SeqGArgs a) 
     a.h[unit] = hlast;
     a.c[unit] = cst;
   }
-  if (tid == 0) seqg_leave(a.sync, a.claim, gridDim.x);
+  if (tid == 0) seqg_leave(a.sync, a.claim);
 }
 
 template <int KW, int KA>

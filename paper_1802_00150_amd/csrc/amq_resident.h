@@ -16,10 +16,6 @@
 // of amq_seq1_body.h that are not light, with one of at most 256.  Light claims: amq_lstm_seqg.hip (up to 144 registers) and
 // the forms of amq_seq1_body.h for 513 to 1024 units (up to 160), with one wave per SIMD and workgroup.
 //
-// A launch that finds the chip its own (no claim, nobody waiting) may take more room than it needs, `alone`, to put its workgroups
-// where they hear of each other sooner.  What other streams would have done beside it they then do later, or on fewer compute units of
-// that die, so this is only for a program that uses one stream: note_stream() and lone_stream().
-//
 // The word on the device: full shares in bits 0..7, light ones in bits 8..15, and the door.  Whoever finds no room closes
 // the door and is the next to get some; small claims do not keep a large one waiting for ever.
 #pragma once
@@ -37,54 +33,44 @@ constexpr unsigned kDoor = 1u << 31;
 struct ResidentClaim {
   unsigned* word;            // null: no room is counted on this device
   unsigned mine;             // full shares, or light shares << 8
-  unsigned alone;            // non-zero: taken instead of `mine` where there is no other claim
   unsigned shares;           // shares of the device
   unsigned long long ticks;  // of the 100 MHz clock: how long to wait for room
 };
 ResidentClaim resident_claim(long long grid, bool light);
 std::mutex& resident_launches();
 
-// Every call of the library: the stream it is on.
-void note_stream(hipStream_t s);
-// Asked once per launch that could use a chip of its own (under resident_launches()): whether the calls since some such launches ago
-// were all on one stream.  A stream that is given up for another counts for a while and then no more.  Only the time a call takes
-// depends on the answer.
-bool lone_stream();
-
 __device__ __forceinline__ bool resident_room(unsigned used, const ResidentClaim& c) {
   const unsigned sum = (used & ~kDoor) + c.mine, full = sum & 255u, light = sum >> 8;
   return full ? full + light <= c.shares : light <= kLightPerUnit * c.shares;
 }
-// To be called by one lane.  What was taken (0: there was no room).  (What it reads goes to the scalar unit: a wave that waits here
-// should hold few registers.)
-__device__ __forceinline__ unsigned take_resident_share(const ResidentClaim& c) {
-  if (!c.word) return c.mine;
+// To be called by one lane.  (What it reads goes to the scalar unit: a wave that waits here should hold few registers.)
+__device__ __forceinline__ bool take_resident_share(const ResidentClaim& c) {
+  if (!c.word) return true;
   const unsigned long long start = wall_clock64();
   unsigned used = 0u, door = 0u;  // door: set once it is this claim that holds it
   for (;;) {
     // (the common case is an idle chip: one exchange)
     unsigned next = used;
-    const unsigned mine = c.alone && used == 0u ? c.alone : c.mine;
-    if ((used & kDoor) == door) next = resident_room(used, c) ? (used & ~kDoor) + mine : used | kDoor;
+    if ((used & kDoor) == door) next = resident_room(used, c) ? (used & ~kDoor) + c.mine : used | kDoor;
     if (next != used) {
       unsigned seen = used;
       __hip_atomic_compare_exchange_strong(c.word, &seen, next, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if ((unsigned)__builtin_amdgcn_readfirstlane((int)seen) == used) {
-        if (!(next & kDoor)) return mine;
+        if (!(next & kDoor)) return true;
         door = kDoor;
       }
     }
     if (wall_clock64() - start > c.ticks) {
       if (door) __hip_atomic_fetch_and(c.word, ~kDoor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      return 0u;
+      return false;
     }
     if (next == used || (next & kDoor)) __builtin_amdgcn_s_sleep(32);
     used = (unsigned)__builtin_amdgcn_readfirstlane(
         (int)__hip_atomic_load(c.word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   }
 }
-__device__ __forceinline__ void give_resident_share(const ResidentClaim& c, unsigned taken) {
-  if (c.word) __hip_atomic_fetch_sub(c.word, taken, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void give_resident_share(const ResidentClaim& c) {
+  if (c.word) __hip_atomic_fetch_sub(c.word, c.mine, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Test hook: takes (or with a negative number gives back) full shares without waiting.
 hipError_t launch_hold_shares(int shares, hipStream_t s);

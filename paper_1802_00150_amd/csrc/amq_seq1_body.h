@@ -22,17 +22,10 @@
 // The order of additions is that of the per-step kernels (amq_bmv_body.h); JOINT false: that of lstm_seqg_kernel, which
 // sums the two operand blocks of a row apart.
 //
-// Where the chip is its own and a quarter of a die's compute units stay free (QW = 1, at most kDieGrid workgroups), all workgroups
-// sit on one die: workgroups go to the dies in turn, so of eight times as many every eighth takes part and the others leave at
-// once.  What is published then comes back from that die's own L2.  us per 35-step sequence, spread / on one die: LSTM 200
-// units W2/A2 85.7 / 74.7, 300 units 89.8 / 81.2, W2/A3 110.7 / 105.7, W3/A3 113.3 / 109.4, 400 units 93.3 / 83.5, 448 units 97.5 / 81.7, GRU 300
-// units 93.6 / 79.9, 448 units W3/A3 125.4 / 120.3.  Nothing but the time depends on where they are.
-// Two workgroups of four quantizing waves on a unit are in each other's way (650 units 109 / 192), so larger grids stay spread.
-// On a die they count for four engines instead of 32, which is room, and on that die compute units, that other streams would lack: us
-// per 60 steps beside a second stream, spread / on one die, 300 units on two streams 162 / 169, beside 600 units batch 40 286 / 292, beside
-// a quantizer of 16384 x 4096 214 / 269 (and that, three times, 226 / 260), 448 units beside a 10000 x 1024 product of 1024 vectors, six
-// times, 284 / 326.  So this is only for a program that calls the library on one stream (lone_stream()), and seqg_reset_kernel
-// takes that room only if there is no other claim, and records it.
+// The workgroups are spread over the dies.  All of them on one (up to 28, every eighth of eight times as many), whose own L2 answers
+// sooner, was faster alone, 300 units W2/A2 145 -> 125 us per 60 steps, but most compute units of that die are then busy for
+// whatever else runs, and everybody waits for the last die: a copy of 256 MiB on another stream 117 -> 143 us (448 units 126 -> 155),
+// a 4096 x 4096 bf16 product 163 -> 193, with the sequence beside it 184 -> 212.
 //
 // Every wait is bounded.  If one gives up a flag is raised and everybody leaves; the caller of this launch follows it with
 // one that either computes the piece again from the saved state or takes it back and marks what was derived from it
@@ -47,8 +40,6 @@ namespace amq {
 namespace seq1 {
 
 constexpr int k1Waves = 4;
-constexpr int kDies = 8, kDieEngines = 4;
-constexpr int kDieGrid = 28;  // (seven of eight shares: a launch on another stream still finds one)
 
 template <int KW, int KA, int EPI, int QW, int NJ, int U, bool JOINT>
 __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
@@ -64,25 +55,17 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
   const int cprI = (I + 127) >> 7, cprH = (H + 127) >> 7;
   const UnitLanes l(a.lg, lane);
   const int c = l.c, per = l.per;
+  const int unit0 = (blockIdx.x * k1Waves + wv) * U * per + l.uo;
   if (tid == 0) dead = 0;
 
-  // an earlier launch of the same call gave up; the room that was taken
-  __shared__ unsigned gave_up, taken;
-  if (tid == 0) {
-    gave_up = __hip_atomic_load(a.sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (QW == 1) taken = a.sync[kSeqGClaimed];
-  }
+  // an earlier launch of the same call gave up
+  __shared__ unsigned gave_up;
+  if (tid == 0) gave_up = __hip_atomic_load(a.sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  int group = (int)blockIdx.x;
-  if (QW == 1 && (int)gridDim.x != a.groups) {
-    if (__builtin_amdgcn_readfirstlane((int)taken) == (int)a.claim.alone) group = group % kDies ? a.groups : group / kDies;
-    if (group >= a.groups) return;
-  }
   if (gave_up != 0u) {
-    if (tid == 0) seqg_leave(a.sync, a.claim, (unsigned)a.groups);
+    if (tid == 0) seqg_leave(a.sync, a.claim);
     return;
   }
-  const int unit0 = (group * k1Waves + wv) * U * per + l.uo;
 
   UnitWeights<KW, U> q;
   load_unit_weights<KW, U, NG>(q, l, unit0, a.Wxp, a.ax, I, a.Whp, a.ah, H);
@@ -133,7 +116,7 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
   if (a.steps > 1) request_x(1);
 
   // (a wave on its own that owns no unit publishes nothing, so nobody would wait for it to have read a buffer)
-  const int steps = QW == 1 && (group * k1Waves + wv) * U * per >= H ? 0 : a.steps;
+  const int steps = QW == 1 && (int)(blockIdx.x * k1Waves + wv) * U * per >= H ? 0 : a.steps;
   bool alive = true;
   for (int t = 0; t < steps; ++t) {
     // ---- h_{t-1}, published with tag t (the initial state with tag 0, by the launch before)
@@ -230,7 +213,7 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
     if (EPI == kEpiLstm) a.c[unit] = cst;
   }
   __syncthreads();
-  if (tid == 0) seqg_leave(a.sync, a.claim, (unsigned)a.groups);
+  if (tid == 0) seqg_leave(a.sync, a.claim);
 }
 
 template <int KW, int KA, int EPI, int QW, int NJ, int U, bool JOINT>
@@ -243,14 +226,10 @@ hipError_t run_form(const Seq1Args& a, hipStream_t s) {
   // Measured, 35 steps on 3 / 4 streams, us until all have finished, full / light: 650 units W2/A2 249 / 272 -> 152 / 233, 1024
   // units 264 / 288 -> 232 / 248, W3/A3 251 / 339 -> 212 / 294.  Grids of up to 512 units are one or two shares of eight as they are.
   q.claim = resident_claim(grid, QW == 4 && U == 1);
-  q.groups = grid;
   std::lock_guard<std::mutex> together(resident_launches());
-  const bool die = QW == 1 && q.claim.word && q.claim.shares == 8u && grid > kDieEngines && grid <= kDieGrid && lone_stream();
-  if (die) q.claim.alone = (unsigned)((grid + kDieEngines - 1) / kDieEngines);
   hipError_t e = launch_seqg_reset(q.sync, q.hbuf, q.h, q.c, q.save_h, q.save_c, q.H, q.clear_flag, q.claim, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((seq1_kernel<KW, KA, EPI, QW, NJ, U, JOINT>), dim3((unsigned)(die ? kDies * grid : grid)), dim3(64 * k1Waves), 0, s,
-                     q);
+  hipLaunchKernelGGL((seq1_kernel<KW, KA, EPI, QW, NJ, U, JOINT>), dim3((unsigned)grid), dim3(64 * k1Waves), 0, s, q);
   e = hipGetLastError();
   if (e != hipSuccess) launch_seqg_abandon(q.sync, q.claim, s);
   return e;

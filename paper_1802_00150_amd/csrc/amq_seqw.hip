@@ -375,7 +375,7 @@ __global__ __launch_bounds__(256) void seqw_reset_kernel(unsigned* flag, Residen
                                                          unsigned count) {
   const unsigned t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
   for (unsigned i = t; i < count; i += nt) pairs[i] = 0ull;
-  if (t == 0) *flag = take_resident_share(claim) != 0u ? 0u : kNoRoom;
+  if (t == 0) *flag = take_resident_share(claim) ? 0u : kNoRoom;
 }
 
 // The piece again from the saved state if the launch before gave up: one workgroup per batch entry.
@@ -386,7 +386,7 @@ __global__ __launch_bounds__(64 * kWBlocks) void seqw_recover_kernel(SeqWArgs a,
   __shared__ uint32_t codes[KA * 64];
   __shared__ float hbeta[KA];
   const unsigned why = *a.flag;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && why != kNoRoom) give_resident_share(claim, claim.mine);
+  if (blockIdx.x == 0 && threadIdx.x == 0 && why != kNoRoom) give_resident_share(claim);
   if (why == 0u) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -648,26 +648,6 @@ ResidentClaim resident_claim(long long grid, bool light) {
 std::mutex& resident_launches() {
   static std::mutex m;
   return m;
-}
-
-namespace {
-constexpr int kCrowdPieces = 32;
-std::atomic<hipStream_t> latest_stream{nullptr};
-std::atomic<bool> any_stream{false};
-std::atomic<int> crowd{0};  // launches for which the change of streams still counts
-}  // namespace
-
-// (several threads at once: a change of streams that one of them misses is seen at its next call)
-void note_stream(hipStream_t s) {
-  if (latest_stream.load(std::memory_order_relaxed) == s && any_stream.load(std::memory_order_relaxed)) return;
-  latest_stream.store(s, std::memory_order_relaxed);
-  if (any_stream.exchange(true, std::memory_order_relaxed)) crowd.store(kCrowdPieces, std::memory_order_relaxed);
-}
-
-bool lone_stream() {
-  const int left = crowd.load(std::memory_order_relaxed);
-  if (left > 0) crowd.store(left - 1, std::memory_order_relaxed);
-  return left == 0;
 }
 
 hipError_t launch_hold_shares(int shares, hipStream_t s) {
