@@ -236,9 +236,13 @@ long long workgroups(const BmvArgs& a) { return a.batch + (long long)row_groups(
 // workgroups the quantizing ones find waiting ones of another stream beside them, where the quantizer by itself, which needs few
 // registers and no LDS, fits anywhere: 650 batch 16 (57) 7.1 / 6.9, 3.7 / 3.9, 2.1 / 2.2, 1024 batch 12 (76) 7.0 / 7.0, 3.7 / 4.1, 2.1 / 2.3,
 // batch 48 (240) 7.4 / 7.6, 4.0 / 4.9, 2.5 / 3.3.  Up to four entries have fewer such encounters: 1024 batch 4 (68) 7.0 / 6.6, 3.56 / 3.52,
-// 2.04 / 1.96, 1300 batch 4 (86) 8.2 / 7.8, 4.2 / 4.0, 2.4 / 2.3, 1500 batch 4 (98) 8.2 / 7.9, 4.2 / 4.1, 2.43 / 2.56.
-// 3-bit activations are quantized slower here than by themselves: a step that is waited for takes 21.4 us and not 20.7 (650 units batch
-// 13), one among others 8.8 and not 8.7.
+// 2.04 / 1.96, 1300 batch 4 (86) 8.2 / 7.8, 4.2 / 4.0, 2.4 / 2.3, 1500 batch 4 (98) 8.2 / 7.9, 4.2 / 4.1, 2.43 / 2.56.  Vectors of up to
+// 512 entries are quantized in less time: state handed on from step to step, 200 units batch 48 (87) 7.31 / 7.00, 3.95 / 3.93, 2.19 / 2.17,
+// 345 batch 25 (69) 7.09 / 6.84, 3.86 / 3.82, 2.15 / 2.13, W3/A2 384 batch 32 (80) 7.55 / 7.13, 4.14 / 4.07, 2.27 / 2.26, 448 batch 25 (81)
+// 7.43 / 7.05, 4.10 / 4.02, 2.27 / 2.22; beyond, W2/A2 345 batch 48 (114) 7.23 / 7.00, 3.96 / 4.02, 2.23 / 2.29.
+// 3-bit activations are quantized slower here than by themselves: a step that is waited for takes 20.8 us and not 20.5 (650 units batch
+// 13 W3/A3), one among others 9.3 and not 9.1; below 512 units others gain (300 batch 16 8.33 / 8.32, 4.28 / 4.40, 2.28 / 2.39) but
+// one that is waited for still does not (19.8 / 19.6).
 bool step_once_supported(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s) {
   // Cycles of the quantizer beyond the usual two: four waves per vector beside the workgroups that wait take 0.44 (2 bits) to 0.78 us
   // (3 bits, 1024 entries) per cycle, the quantizer by itself 0.36 and 0.58.  Two launches / one, W2/A2, us, T = 2, 4, 6, 10, 20: 300
@@ -251,7 +255,8 @@ bool step_once_supported(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_
   long long pairs = 0;
   for (const BmvBlock& k : a.blk) pairs += (long long)a.batch * seqw_entry_pairs(k_a, 4 * ((k.n + 127) >> 7));
   int units = 0;
-  if (pairs > kSlotPairs || !hand_over_memory(units) || 32 * workgroups(a) > (a.batch <= 4 ? 12 : 7) * units) return false;
+  const int most = a.batch <= 4 ? 12 : a.blk[0].n <= 512 && a.blk[1].n <= 512 ? 11 : 7;  // workgroups per 32 units
+  if (pairs > kSlotPairs || !hand_over_memory(units) || 32 * workgroups(a) > most * units) return false;
   return !maybe_captured(s);
 }
 
