@@ -230,32 +230,37 @@ long long workgroups(const BmvArgs& a) { return a.batch + (long long)row_groups(
 
 }  // namespace
 
-// Shapes of the paired kernel, 2- and 3-bit weights and 2-bit activations, as long as the workgroups are few.  Two launches / one,
-// us per LSTM step W2/A2 on one stream, and per step of two and four streams that are kept busy: 300 units batch 8 6.6 / 6.1, 3.45 /
-// 3.2, 1.89 / 1.74; 512 batch 16 6.6 / 6.3, 3.49 / 3.44, 1.92 / 1.89; 650 batch 13 7.1 / 6.7, 3.72 / 3.76, 2.10 / 2.10.  With more
-// workgroups the quantizing ones find waiting ones of another stream beside them, where the quantizer by itself, which needs few
-// registers and no LDS, fits anywhere: 650 batch 16 (57) 7.1 / 6.9, 3.7 / 3.9, 2.1 / 2.2, 1024 batch 12 (76) 7.0 / 7.0, 3.7 / 4.1, 2.1 / 2.3,
-// batch 48 (240) 7.4 / 7.6, 4.0 / 4.9, 2.5 / 3.3.  Up to four entries have fewer such encounters: 1024 batch 4 (68) 7.0 / 6.6, 3.56 / 3.52,
-// 2.04 / 1.96, 1300 batch 4 (86) 8.2 / 7.8, 4.2 / 4.0, 2.4 / 2.3, 1500 batch 4 (98) 8.2 / 7.9, 4.2 / 4.1, 2.43 / 2.56.  Vectors of up to
-// 512 entries are quantized in less time: state handed on from step to step, 200 units batch 48 (87) 7.31 / 7.00, 3.95 / 3.93, 2.19 / 2.17,
-// 345 batch 25 (69) 7.09 / 6.84, 3.86 / 3.82, 2.15 / 2.13, W3/A2 384 batch 32 (80) 7.55 / 7.13, 4.14 / 4.07, 2.27 / 2.26, 448 batch 25 (81)
-// 7.43 / 7.05, 4.10 / 4.02, 2.27 / 2.22; beyond, W2/A2 345 batch 48 (114) 7.23 / 7.00, 3.96 / 4.02, 2.23 / 2.29.
-// 3-bit activations are quantized slower here than by themselves: a step that is waited for takes 20.8 us and not 20.5 (650 units batch
-// 13 W3/A3), one among others 9.3 and not 9.1; below 512 units others gain (300 batch 16 8.33 / 8.32, 4.28 / 4.40, 2.28 / 2.39) but
-// one that is waited for still does not (19.8 / 19.6).
+// Shapes of the paired kernel, 2- and 3-bit weights and 2-bit activations, as long as the workgroups are few.  The quantizing ones carry
+// the registers and the LDS of the whole step: on several busy streams they find waiting workgroups of other steps beside them,
+// where the quantizer by itself fits anywhere.  Two launches / one, us per LSTM step on one stream, and per step of two and four streams
+// that work is queued on; h_t becomes h_{t-1} of the next step:
+//   W2/A2 300 units batch 8 (27 workgroups) 6.83 / 6.45, 3.59 / 3.41, 2.01 / 1.87; 650 batch 13 (54) 7.45 / 7.27, 4.02 / 4.07, 2.23 / 2.26;
+//   beyond, 1024 batch 16 (80) 7.49 / 7.55, 4.03 / 4.36, 2.27 / 2.49; W3/A2 the same 8.05 / 7.91, 4.34 / 4.54, 2.49 / 2.64.
+// Up to four entries have fewer such encounters: 1024 batch 4 (68) W2/A2 7.27 / 6.82, 3.88 / 3.80, 2.16 / 2.04; beyond, 1500 batch 4 (98)
+// 8.60 / 8.36, 4.47 / 4.37, 2.49 / 2.65, 2048 batch 4 (132) 9.02 / 8.87, 4.72 / 4.97, 2.96 / 3.90.
+// Vectors of up to 512 entries are quantized in less time, and 3-bit weights take longer to turn meanwhile: 200 units batch 48 (87)
+// W2/A2 7.31 / 7.00, 3.95 / 3.93, 2.19 / 2.17, W3/A2 256 batch 56 (120) 7.65 / 7.19, 4.23 / 4.12, 2.34 / 2.31; beyond, W2/A2 512 batch 32
+// (96) 6.96 / 6.81, 3.86 / 4.02, 2.15 / 2.23, W3/A2 512 batch 40 (136) 7.43 / 7.16, 4.22 / 4.27, 2.35 / 2.37.
+// 3-bit activations are quantized slower here than by themselves, which longer vectors and 2-bit weights do not make up for: 650 units batch
+// 13 (54) W3/A3 9.08 / 9.31, 4.76 / 4.81, 2.71 / 2.60, 300 batch 16 (35) W2/A3 7.85 / 8.04, 4.15 / 4.14, 2.29 / 2.21, W3/A3 8.32 / 8.33, 4.40 /
+// 4.28, 2.39 / 2.28, 512 batch 8 (40) 8.05 / 7.81, 4.22 / 4.01, 2.32 / 2.14.  (One that is waited for 19.3 / 19.5.)
+// What the host saves, a launch of 2.3 us, is in none of these: a program that feeds two or more streams from one thread takes 12.3 to
+// 13.3 us per step in two launches and 10.2 to 11.0 in one.
 bool step_once_supported(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s) {
   // Cycles of the quantizer beyond the usual two: four waves per vector beside the workgroups that wait take 0.44 (2 bits) to 0.78 us
   // (3 bits, 1024 entries) per cycle, the quantizer by itself 0.36 and 0.58.  Two launches / one, W2/A2, us, T = 2, 4, 6, 10, 20: 300
   // units batch 4 6.5 / 6.1, 7.2 / 6.9, 7.9 / 7.75, 9.4 / 9.4, 13.0 / 13.7; 650 batch 13 7.0 / 6.8, 7.8 / 7.7, 8.6 / 8.6, 10.3 / 10.4,
   // 14.3 / 15.0.  From about 40 on the waits give up before the codes are there, and every workgroup quantizes its tile: 650 batch 13
-  // T = 100 47 / 631.
-  if (a.T > kMostCycles) return false;
-  if (a.batch < 2 || k_w < 2 || k_w > 3 || k_a != 2 || !a.raw[0] || !a.raw[1]) return false;
+  // T = 100 47 / 631.  3-bit activations have no lead to lose.
+  if (a.T > (k_a == 2 ? kMostCycles : 2)) return false;
+  if (a.batch < 2 || k_w < 2 || k_w > 3 || !a.raw[0] || !a.raw[1]) return false;
+  const bool shorter = a.blk[0].n <= 512 && a.blk[1].n <= 512;
+  if (k_a != 2 && !(k_a == 3 && k_w == 3 && shorter)) return false;
   if (!mfma4_pair_supported(a, k_w, k_a, epi) || mfma32_cell_supported(a, k_w, k_a, epi)) return false;
   long long pairs = 0;
   for (const BmvBlock& k : a.blk) pairs += (long long)a.batch * seqw_entry_pairs(k_a, 4 * ((k.n + 127) >> 7));
   int units = 0;
-  const int most = a.batch <= 4 ? 12 : a.blk[0].n <= 512 && a.blk[1].n <= 512 ? 11 : 7;  // workgroups per 32 units
+  const int most = shorter ? (k_w == 3 && k_a == 2 ? 15 : 11) : a.batch <= 4 ? 12 : 7;  // workgroups per 32 units
   if (pairs > kSlotPairs || !hand_over_memory(units) || 32 * workgroups(a) > most * units) return false;
   return !maybe_captured(s);
 }
@@ -265,7 +270,6 @@ unsigned step_once_launches(long long next) {
 }
 
 hipError_t launch_step_once(const BmvArgs& a, int k_w, int k_a, int epi, hipStream_t s) {
-  if (k_a != 2) return hipErrorInvalidValue;
   int units = 0;
   unsigned long long* const memory = hand_over_memory(units);
   if (!memory) return hipErrorInvalidValue;
@@ -288,6 +292,7 @@ hipError_t launch_step_once(const BmvArgs& a, int k_w, int k_a, int epi, hipStre
   o.gx = row_groups(a);
   const int grid = (int)workgroups(a);
   const int nc = a.blk[0].n > 1024 || a.blk[1].n > 1024 ? 2 : 1;
+  if (k_a == 3) return epi == kEpiLstm ? run_one<3, 3, kEpiLstm, 1>(o, grid, s) : run_one<3, 3, kEpiGru, 1>(o, grid, s);
   return k_w == 2 ? run_k<2, 2>(o, grid, epi, nc, s) : run_k<3, 2>(o, grid, epi, nc, s);
 }
 

@@ -55,13 +55,13 @@ def same(a, b):
 
 
 # one launch: one entry more and fewer than a tile, ragged units and vectors, one and two stretches, blocks of unequal stretches, the
-# most workgroups that still take this path (56 of 256, with vectors of up to 512 entries 88, up to four entries 96) ...
+# most workgroups that still take this path (56 of 256, up to four entries 96, with vectors of up to 512 entries 88 and W3/A2 120) ...
 ONCE = [(300, 300, 2, 2, 2), (650, 650, 13, 2, 2), (1, 300, 17, 2, 2), (2048, 333, 16, 3, 2), (701, 650, 15, 3, 2),
         (129, 1030, 4, 2, 2), (1024, 1024, 4, 3, 2), (1500, 1500, 2, 3, 2), (33, 1, 7, 2, 2),
-        (512, 512, 24, 2, 2), (200, 201, 48, 3, 2)]
+        (512, 512, 24, 2, 2), (256, 256, 56, 3, 2), (200, 201, 48, 3, 3), (512, 512, 4, 3, 3)]
 # ... and two: one workgroup more, other numbers of bits, larger batches
-TWICE = [(701, 650, 16, 3, 2), (1024, 1024, 5, 2, 2), (1536, 1537, 2, 2, 2), (512, 512, 25, 3, 2), (513, 300, 25, 2, 2),
-         (300, 300, 4, 2, 3), (1, 1030, 17, 2, 3), (128, 1024, 16, 2, 2), (700, 701, 33, 3, 2), (1500, 1500, 20, 2, 2),
+TWICE = [(701, 650, 16, 3, 2), (1024, 1024, 5, 2, 2), (1536, 1537, 2, 2, 2), (512, 512, 25, 2, 2), (256, 257, 56, 3, 2), (513, 300, 25, 2, 2),
+         (300, 300, 4, 2, 3), (513, 512, 4, 3, 3), (512, 512, 25, 3, 3), (1, 1030, 17, 2, 3), (128, 1024, 16, 2, 2), (700, 701, 33, 3, 2), (1500, 1500, 20, 2, 2),
          (2048, 2048, 5, 3, 3), (2000, 333, 31, 3, 3), (1024, 1024, 48, 2, 3), (1024, 1024, 64, 3, 3)]
 
 
@@ -83,10 +83,10 @@ def test_same_as_two_launches(amq, gates, I, H, B, k_w, k_a):
     assert one == ((I, H, B, k_w, k_a) in ONCE) and same(got, want)
 
 
-@pytest.mark.parametrize("T,once", [(0, True), (4, True), (5, False), (60, False)])
-def test_many_cycles_take_two_launches(amq, T, once):
+@pytest.mark.parametrize("T,k,once", [(0, 2, True), (4, 2, True), (5, 2, False), (60, 2, False), (2, 3, True), (3, 3, False)])
+def test_many_cycles_take_two_launches(amq, T, k, once):
     # one launch would be slower, and from about 40 cycles on much slower: its waits are shorter than the quantizer takes
-    s = Step(amq, 4, 300, 300, 7, 2, 2)
+    s = Step(amq, 4, 300, 300, 7, k, k)
     s.T = T
     got, one = launched_once(amq, s.once)
     assert one == once and same(got, s.two_launches())
