@@ -11,7 +11,9 @@
 //     x-side sums of step t are formed while the codes of h_{t-1} are under way;
 //   - per step two exchanges: every workgroup publishes its h_t; the workgroup in charge of a batch entry (one of
 //     those of its tile) gathers the entry's whole h_t, quantizes it (the shared quantizer core on 4 waves) and
-//     publishes its codes, which all workgroups of the tile gather as matrix operands.
+//     publishes its codes, which all workgroups of the tile gather as matrix operands.  What is published goes through LDS
+//     to the x side's waves, which store it: a wave's loads are counted behind its stores, and a store takes 1500 cycles
+//     until it is acknowledged, which the polls of the h side's waves would otherwise wait for.
 // What is exchanged are 8-byte {value, step tag} pairs, each written with one device-scope store; the readers poll
 // the pairs they need until all carry the tag of the step (one way across the chip: about 0.55 us measured), so the
 // data is its own arrival signal: no barrier, no ordering between locations.  Two buffers in turn suffice: whoever
@@ -33,6 +35,13 @@
 namespace amq {
 
 namespace {
+
+// How long a workgroup that quantizes waits before it asks for h_{t-1} for the first time, in units of 64 cycles.  A store is seen
+// elsewhere after about 1400 cycles, and a gather that comes too early is a whole trip (1600 to 1900 cycles) before the next.  Measured
+// with 0 / 10 / 12 / 14 / 16, us per 35 steps: 1024 units batch 64 W2/A2 180 / 181 / 178 / 177 / 178, GRU 187 / 181 / 179 / 178 / 178,
+// W3/A3 235 / 230 / 228 / 226 / 226, 650 units batch 20 166 / 160 / 158 / 159 / 159, 2000 units batch 5 228 / 216 / 215 / 216 / 217.  (The
+// codes are asked for at once: any delay there is lost, 4 units 2 us, 12 units 8 us.)
+constexpr int kFirstPoll = 14;
 
 // NC: stretches of 1024 entries of the longer operand block (1 or 2).  Waves 0 .. 3 take the h side, the cell and the
 // quantizer, waves 4 .. 7 the x side of the next step.
@@ -193,7 +202,7 @@ seqw_kernel(SeqWArgs a) {
   const int centry = seqw_entry_pairs(KA, wprH);
   const size_t chalf = (size_t)gridDim.y * kTileB * centry;
   int phase = 0;
-  // publishing h_t (h waves): thread -> entry and unit
+  // publishing h_t (x waves): thread -> entry and unit
   const int hp_unit = 4 * kWBlocks * bx + (tid & 15), hp_col = (tid >> 4) & 15;
   const bool hp_ok = hp_unit < H && hp_col < ncols;
   const size_t hp_at = (size_t)(b0 + (hp_ok ? hp_col : 0)) * H + (hp_ok ? hp_unit : 0);
@@ -238,20 +247,31 @@ seqw_kernel(SeqWArgs a) {
   // W2/A2 186.0 / 185.5, W3/A2 189.1 / 190.2, W3/A3 229.4 / 229.1; 1500 units batch 20 W2/A3 281.6 / 273.7, W3/A2
   // 232.9 / 235.6, W3/A3 314.3 / 316.0, GRU W3/A3 329.6 / 311.0.
   auto x_step = [&](int t) {
+    const unsigned tag = (unsigned)t + 1u;
     stage_inputs(t + 1);
-    for (int e = q_first; e < ncols; e += q_next)
+    for (int e = q_first; e < ncols; e += q_next) {
       for (int i = quantize_exchanges<KA>(a.T) + 1; i > 0; --i) lds_barrier();
+      if (gt < KA * (wprH + 1))
+        put_pair(a.cbuf + (t & 1) * chalf + ((size_t)tile * kTileB + e) * centry + gt, codes[gt], tag);
+    }
     lds_barrier();
     // x side of step t + 1, while the codes are under way
     x_side(t + 1);
     lds_barrier();
     const int gone = dead;
-    if (t + 1 < a.steps) lds_barrier();
+    lds_barrier();
+    // h_t, through LDS: 16 units are one cache line
+    if (hp_ok) {
+      const float ht = hout[(tid >> 4) & 15][tid & 15];
+      if (t + 1 < a.steps) put_pair(a.hbuf + (t & 1) * hhalf + hp_at, __float_as_uint(ht), tag);
+      if (a.hs) a.hs[(size_t)t * hhalf + hp_at] = ht;
+    }
     return __builtin_amdgcn_readfirstlane(gone) != 0;
   };
   auto h_step = [&](int t) {
     const unsigned tag = (unsigned)t + 1u;
     // ---- quantize h_{t-1} of the entries in this workgroup's charge
+    if (t > 0 && q_first < ncols) __builtin_amdgcn_s_sleep(kFirstPoll);
     for (int e = q_first; e < ncols; e += q_next) {
       float v[NJ];
       if (t == 0) {
@@ -298,8 +318,6 @@ seqw_kernel(SeqWArgs a) {
         for (int i = 0; i < KA; ++i) codes[KA * wprH + i] = __float_as_uint(beta[i]);
       }
       lds_barrier();
-      if (tid < KA * (wprH + 1))
-        put_pair(a.cbuf + (t & 1) * chalf + ((size_t)tile * kTileB + e) * centry + tid, codes[tid], tag);
     }
 
     lds_barrier();
@@ -336,15 +354,8 @@ seqw_kernel(SeqWArgs a) {
     const float4 x4 = xsum[t & 1][blk][lane];
     const float yx[4] = {x4.x, x4.y, x4.z, x4.w};
     cell<EPI>(yx, y, bs0, bs1, h, c);
-    if (own) {
-      if (a.hs) a.hs[(size_t)t * hhalf + state] = h;
-    }
     hout[l16][4 * blk + l4] = h;
-    if (t + 1 < a.steps) {
-      // published through LDS as well: 16 units are one cache line
-      lds_barrier();
-      if (hp_ok) put_pair(a.hbuf + (t & 1) * hhalf + hp_at, __float_as_uint(hout[(tid >> 4) & 15][tid & 15]), tag);
-    }
+    lds_barrier();
     return __builtin_amdgcn_readfirstlane(gone) != 0;
   };
 
