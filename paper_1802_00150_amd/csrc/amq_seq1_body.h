@@ -14,8 +14,8 @@
 // multiplies its own rows, with no barrier anywhere in a step.  QW = 4: the four waves of a workgroup quantize together.
 // One wave takes longer over the entries and needs no exchange between waves (about 250 cycles less per sum).
 //
-// Bound: latency -- at 300 units about 1.0 us until h_t is seen, 0.9 for Alg. 2, the rest products, cell and LDS.  Measured, us
-// per step in sequences of 35, form before -> here, W2/A2: LSTM 300 units 3.50 -> 2.60, 650 4.31 -> 3.08, 1024 5.04 -> 3.53
+// Bound: latency -- at 300 units about 0.9 us until h_t is seen, 0.8 for Alg. 2, the rest products, cell and LDS.  Measured, us
+// per step in sequences of 35, form before -> here, W2/A2: LSTM 300 units 3.50 -> 2.47, 650 4.31 -> 2.97, 1024 5.04 -> 3.06
 // (lstm_seqg_kernel), 2048 8.69 -> 4.06; GRU 300 8.06 -> 2.66, 1024 8.09 -> 3.46, 2048 8.50 -> 4.17 (two launches per step);
 // W3/A3: LSTM 300 4.22 -> 3.29, 1024 5.79 -> 4.53, 2048 11.0 -> 5.59, GRU 9.23 -> 3.50, 9.61 -> 4.36, 10.3 -> 5.63.
 //
@@ -41,10 +41,25 @@ namespace seq1 {
 
 constexpr int k1Waves = 4;
 
+// How long a wave waits, after the x side of the next step, before it asks for h_t for the first time, in units of 64 cycles: h_t is
+// seen elsewhere about 1400 cycles after it was stored, and a poll that finds a part of it costs another trip (about 900).  The x side
+// itself takes the longer the more planes a lane has, so the wait is the rest.  Swept over 0 to 14 units for each form; two more or fewer
+// cost 1 %.  0: the form asks at once, as two units per lane (or nine plane products of an LSTM) fill that time.  us per 35 steps, at once /
+// here: LSTM W2/A2 300 units 89.6 / 86.4, 448 99.5 / 93.6, 650 110.8 / 103.9, 1024 113.3 / 107.2, W2/A3 350 118.8 / 114.9, W3/A2 350 95.9 / 90.2,
+// GRU W2/A2 300 93.3 / 88.8, 650 110.1 / 105.7, W2/A3 200 110.8 / 107.1, W3/A3 256 116.2 / 111.2; forms that stay, had they waited: 1500
+// units W2/A2 123.8 / 125.3, GRU W3/A2 650 108.6 / 111.1, LSTM W2/A3 768 128.5 / 130.2.
+constexpr int first_poll(int kw, int ka, bool gru, int qw, int nj, int u) {
+  const int planes = kw * ka;
+  if (u == 2) return 0;
+  if (gru) return planes == 4 ? (qw == 1 ? 8 : 7) : planes == 9 ? 3 : qw == 4 && kw == 3 ? 0 : 5;
+  return planes == 4 ? 5 : planes == 9 ? 0 : ka == 2 ? 4 : qw == 4 && nj == 3 ? 0 : 2;
+}
+
 template <int KW, int KA, int EPI, int QW, int NJ, int U, bool JOINT>
 __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
   constexpr int NG = EPI == kEpiGru ? 3 : 4;
   constexpr int kChunks = 16;
+  constexpr int kFirstPoll = first_poll(KW, KA, EPI == kEpiGru, QW, NJ, U);
   __shared__ double sh[2 * kExchange<QW>];
   __shared__ __attribute__((aligned(16))) uint4 hq[QW == 1 ? k1Waves : 2][KA][kChunks];  // codes of h_{t-1}
   __shared__ float hb[2][KA];                                                           // and coefficients (QW = 4)
@@ -118,7 +133,10 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
   // (a wave on its own that owns no unit publishes nothing, so nobody would wait for it to have read a buffer)
   const int steps = QW == 1 && (int)(blockIdx.x * k1Waves + wv) * U * per >= H ? 0 : a.steps;
   bool alive = true;
+  const int first_wait = kFirstPoll > 0 ? opaque_s(kFirstPoll) : 0;
   for (int t = 0; t < steps; ++t) {
+    if (kFirstPoll > 0 && t > 0)
+      for (int i = 0; i < first_wait; ++i) __builtin_amdgcn_s_sleep(1);
     // ---- h_{t-1}, published with tag t (the initial state with tag 0, by the launch before)
     float alpha[KA];
     unsigned long long mym[KA];
@@ -194,6 +212,11 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
 #pragma unroll
     for (int u = 0; u < U; ++u) ph[u] = unit_dot(q, 1, u, hv, bt);
     unit_cell<EPI, U, JOINT, NG>(l, px, ph, b0, b1, hlast, cst);
+    if constexpr (kFirstPoll > 0) {
+      // the inputs of the next step, asked for a step ago: waited for here and not behind the store, with which loads are counted
+#pragma unroll
+      for (int j = 0; j < KA; ++j) asm volatile("" : "+v"(xv[j].x), "+v"(xv[j].y), "+v"(xv[j].z), "+v"(xv[j].w), "+v"(xb[j]));
+    }
     if (cell) {
       if (t + 1 < a.steps)
         __hip_atomic_store(a.hbuf + (t & 1) * H + unit,
@@ -204,6 +227,10 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
     // ---- while h_t is under way
     if (t + 1 < a.steps) {
       x_side();
+      if constexpr (kFirstPoll > 0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) asm volatile("" : "+v"(px[u]));
+      }
       if (t + 2 < a.steps) request_x(t + 2);
     }
   }
