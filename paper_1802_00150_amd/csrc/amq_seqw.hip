@@ -43,6 +43,108 @@ namespace {
 // codes are asked for at once: any delay there is lost, 4 units 2 us, 12 units 8 us.)
 constexpr int kFirstPoll = 14;
 
+// Whether the two waves of a row block share the contraction of its h side, half of K each (the x side's wave has nothing else to do
+// then).  The matrix instructions of a compute unit's SIMD are the same either way; what two waves halve is the expansion of weights that
+// do not stay expanded in registers, at the price of the partial sums' way through LDS and a barrier.  us per 35 steps, alone / shared: two
+// stretches W2/A2 2048 units 222.0 / 218.6, 1500 units 211.4 / 208.8, W3/A3 342.1 / 320.1, 304.6 / 292.1 (fewer registers spilled as well),
+// W1/A1 1800 units 150.9 / 146.1, W2/A1 165.0 / 158.1; six plane products 225.3 / 228.4, 190 / 198, W3/A1 179 / 200; one stretch W2/A2 180 /
+// 188, W3/A3 228 / 232.
+template <int KW, int KA, int NC>
+constexpr bool kSharedK = NC == 2 && KW * KA != 6 && !(KW == 3 && KA == 1);
+
+// `contract` over a stretch of K: halves of 512 positions first, first + 1 (first even) of the `halves` that the vectors have, weights
+// packed in operand layout, a word per k-step.  The sums begin at `start`.
+template <int KW, int KA, int NC>
+__device__ __forceinline__ void contract_part(const uint4 (&araw)[2][KW], const uint4* image, int l16, int l4, int first, int halves,
+                                              float start, v4f (&acc)[KW][KA]) {
+  constexpr int kAllSteps = NC * kSteps;
+#pragma unroll
+  for (int i = 0; i < KW; ++i)
+#pragma unroll
+    for (int j = 0; j < KA; ++j) acc[i][j] = v4f{start, start, start, start};
+  const uint4* const my = image + 16 * l4 + first * 4 * 64;
+  auto b_operand = [&](int j, int t) { return my[(j * kAllSteps + t) * 64 + (l16 ^ ((l4 << 1) | (((t >> 2) & 1) << 3)))]; };
+  auto word = [](const uint4& q, int t) { return (t & 3) == 0 ? q.x : (t & 3) == 1 ? q.y : (t & 3) == 2 ? q.z : q.w; };
+  uint4 aop[KW], anx[KW], bop[KA], bnx[KA];
+#pragma unroll
+  for (int j = 0; j < KA; ++j) bop[j] = b_operand(j, 0);
+#pragma unroll
+  for (int i = 0; i < KW; ++i) aop[i] = expand4_signed(araw[0][i].x);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (h > 0 && first + h >= halves) break;  // (uniform)
+#pragma unroll
+    for (int t = 4 * h; t < 4 * h + 4; ++t) {
+      if (t + 1 < 8) {
+#pragma unroll
+        for (int j = 0; j < KA; ++j) bnx[j] = b_operand(j, t + 1);
+#pragma unroll
+        for (int i = 0; i < KW; ++i) anx[i] = expand4_signed(word(araw[(t + 1) / 4][i], t + 1));
+      }
+#pragma unroll
+      for (int i = 0; i < KW; ++i)
+#pragma unroll
+        for (int j = 0; j < KA; ++j) acc[i][j] = mfma_fp4(aop[i], bop[j], acc[i][j]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < KW; ++i) aop[i] = anx[i];
+#pragma unroll
+      for (int j = 0; j < KA; ++j) bop[j] = bnx[j];
+    }
+  }
+  settle_accumulators<16>();
+#pragma unroll
+  for (int i = 0; i < KW; ++i)
+#pragma unroll
+    for (int j = 0; j < KA; ++j) asm volatile("" : "+v"(acc[i][j]));
+}
+
+// Partial sums from one wave to another through LDS, [piece][lane]: integers of at most 1024, which binary16 holds exactly, so the
+// sums are the same in whatever order they are formed.
+template <int KW, int KA>
+constexpr int kPartPieces = (KW * KA * 2 + 3) / 4;  // pieces of 16 bytes per lane
+typedef _Float16 Half2 __attribute__((ext_vector_type(2)));
+
+template <int KW, int KA>
+__device__ __forceinline__ void put_part(const v4f (&acc)[KW][KA], uint4* part, int lane) {
+  unsigned d[4 * kPartPieces<KW, KA>] = {};
+#pragma unroll
+  for (int q = 0; q < KW * KA; ++q)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const v4f& v = acc[q / KA][q % KA];
+      d[2 * q + e] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(v[2 * e], v[2 * e + 1]));
+    }
+#pragma unroll
+  for (int p = 0; p < kPartPieces<KW, KA>; ++p) part[p * 64 + lane] = make_uint4(d[4 * p], d[4 * p + 1], d[4 * p + 2], d[4 * p + 3]);
+}
+
+template <int KW, int KA>
+__device__ __forceinline__ void add_part(v4f (&acc)[KW][KA], const uint4* part, int lane) {
+  uint4 piece[kPartPieces<KW, KA>];
+#pragma unroll
+  for (int p = 0; p < kPartPieces<KW, KA>; ++p) piece[p] = part[p * 64 + lane];
+#pragma unroll
+  for (int q = 0; q < KW * KA; ++q)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int at = 2 * q + e;
+      const uint4& v = piece[at >> 2];
+      const unsigned w = (at & 3) == 0 ? v.x : (at & 3) == 1 ? v.y : (at & 3) == 2 ? v.z : v.w;
+      const Half2 x = __builtin_bit_cast(Half2, w);
+      acc[q / KA][q % KA][2 * e] += (float)x[0];
+      acc[q / KA][q % KA][2 * e + 1] += (float)x[1];
+    }
+}
+
+template <int KW>
+__device__ __forceinline__ void keep_packed_part(uint4 (&w)[2][KW]) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < KW; ++i) asm volatile("" : "+v"(w[h][i].x), "+v"(w[h][i].y), "+v"(w[h][i].z), "+v"(w[h][i].w));
+}
+
 // NC: stretches of 1024 entries of the longer operand block (1 or 2).  Waves 0 .. 3 take the h side, the cell and the
 // quantizer, waves 4 .. 7 the x side of the next step.
 template <int KW, int KA, int EPI, int NC>
@@ -56,6 +158,8 @@ seqw_kernel(SeqWArgs a) {
   __shared__ uint32_t codes[KA * 32 * NC + KA];            // codes of one entry, then its coefficients
   __shared__ float hout[kTileB][4 * kBlocksPad];           // h_t of the workgroup's units
   __shared__ float4 xsum[2][kWBlocks][64];  // x-side sums of two consecutive steps
+  constexpr bool kShared = kSharedK<KW, KA, NC>;
+  __shared__ uint4 part[kShared ? kWBlocks : 1][kShared ? kPartPieces<KW, KA> * 64 : 1];  // h-side sums over the second half of K
   extern __shared__ __attribute__((aligned(16))) uint4 lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -79,8 +183,9 @@ seqw_kernel(SeqWArgs a) {
   const int piece0 = lane & 7;
 
   // ---- once: this wave's weights in operand layout (rows through a padded piece of LDS, amq_pair_body.h; four waves
-  // at a time), coefficients, state
-  uint4 w[NC][KW][2];
+  // at a time), coefficients, state.  Where K is shared: the x waves also take the second stretch of the h side (two halves of
+  // 512 positions), and the h waves keep the first.
+  uint4 w[NC][KW][2], wh[2][KW];
   {
     int u = rb * 4 + ((lane >> 3) & 3);
     u = u < H ? u : H - 1;
@@ -118,23 +223,50 @@ seqw_kernel(SeqWArgs a) {
     a.save_h[state] = h;
     if (EPI == kEpiLstm) a.save_c[state] = c;
   }
+  const int hhalves = (H + 511) >> 9;          // halves that the h side's vectors have
+  const bool shared_k = kShared && hhalves > 2;  // (otherwise the x waves have no part in the h side)
 #pragma unroll
   for (int side = 0; side < 2; ++side) {
     if (xwave == (side == 1)) {
       uint4* const mine = lds + blk * (kTileB * kWTurn);
       const int row = 4 * ((lane >> 3) & 3) + (lane >> 5);
+      auto turn = [&](uint4 (&t)[2], uint32_t keep) {
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+          mine[(row + 2 * v) * kWTurn + piece0] = make_uint4(t[v].x & keep, t[v].y & keep, t[v].z & keep, t[v].w & keep);
+#pragma unroll
+        for (int v = 0; v < 2; ++v) t[v] = mine[l16 * kWTurn + l4 + 4 * v];
+      };
 #pragma unroll
       for (int ch = 0; ch < NC; ++ch) {
         const uint32_t keep = 8 * ch + piece0 < wq ? 0xffffffffu : 0u;
 #pragma unroll
+        for (int i = 0; i < KW; ++i) turn(w[ch][i], keep);
+      }
+      if (side == 0 && kShared) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int i = 0; i < KW; ++i) wh[h][i] = w[0][i][h];
+      } else if (side == 1 && shared_k) {
+        int u = rb * 4 + ((lane >> 3) & 3);
+        u = u < H ? u : H - 1;
+        const int wqh = (H + 127) >> 7;
+        const size_t plane = (size_t)NG * H * wqh * 16;
+#pragma unroll
         for (int i = 0; i < KW; ++i) {
+          uint4 t[2];
+          const int p = 8 + piece0;
 #pragma unroll
           for (int v = 0; v < 2; ++v) {
-            const uint4 t = w[ch][i][v];
-            mine[(row + 2 * v) * kWTurn + piece0] = make_uint4(t.x & keep, t.y & keep, t.z & keep, t.w & keep);
+            int g = 2 * v + (lane >> 5);
+            g = g < NG ? g : NG - 1;
+            t[v] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.h.Wp) + i * plane +
+                                                   (unsigned)((g * H + u) * wqh + (p < wqh ? p : 0)) * 16u);
           }
+          turn(t, p < wqh ? 0xffffffffu : 0u);
 #pragma unroll
-          for (int v = 0; v < 2; ++v) w[ch][i][v] = mine[l16 * kWTurn + l4 + 4 * v];
+          for (int h = 0; h < 2; ++h) wh[h][i] = t[h];
         }
       }
     }
@@ -185,8 +317,17 @@ seqw_kernel(SeqWArgs a) {
     float bt[KA];
 #pragma unroll
     for (int j = 0; j < KA; ++j) bt[j] = __shfl(beta, 16 * j + l16, kWave);
-    if constexpr (!kExpandedOnce<KW, KA, NC>) keep_packed(w);
-    contract<KW, KA, NC>(w, image, l16, l4, n, acc);
+    if (kShared && !xwave) {
+      if constexpr (KW * KA > 4) keep_packed_part(wh);
+      contract_part<KW, KA, NC>(wh, image, l16, l4, 0, hhalves, (float)(H - hhalves * 512), acc);
+      if (shared_k) {
+        lds_barrier();
+        add_part<KW, KA>(acc, part[blk], lane);
+      }
+    } else {
+      if constexpr (!kExpandedOnce<KW, KA, NC>) keep_packed(w);
+      contract<KW, KA, NC>(w, image, l16, l4, n, acc);
+    }
     weigh<KW, KA>(acc, al, bt, y);
   };
 
@@ -243,9 +384,7 @@ seqw_kernel(SeqWArgs a) {
   // leave and the piece is done again.  Each kind has its own loop over the steps, so that what only one of them keeps
   // takes no registers in the other.  With one loop for both the forms needed up to 256 registers (W3/A3 on two
   // stretches 32 more, spilled), now 15 to 40 fewer; 240 are allowed (kResidentRegisters), which leaves W3/A3 on two
-  // stretches 40 to 53 spilled, W2/A3 on two 9 to 11, W3/A2 up to 8.  35 steps, us before / now: 1024 units batch 64
-  // W2/A2 186.0 / 185.5, W3/A2 189.1 / 190.2, W3/A3 229.4 / 229.1; 1500 units batch 20 W2/A3 281.6 / 273.7, W3/A2
-  // 232.9 / 235.6, W3/A3 314.3 / 316.0, GRU W3/A3 329.6 / 311.0.
+  // stretches 18 to 30 spilled, W2/A2, W2/A3 on two and W3/A2 up to 4.
   auto x_step = [&](int t) {
     const unsigned tag = (unsigned)t + 1u;
     stage_inputs(t + 1);
@@ -259,6 +398,13 @@ seqw_kernel(SeqWArgs a) {
     x_side(t + 1);
     lds_barrier();
     const int gone = dead;
+    if (shared_k) {
+      v4f acc[KW][KA];
+      if constexpr (KW * KA > 4) keep_packed_part(wh);
+      contract_part<KW, KA, NC>(wh, lds, l16, l4, 2, hhalves, 0.0f, acc);
+      put_part<KW, KA>(acc, part[blk], lane);
+      lds_barrier();
+    }
     lds_barrier();
     // h_t, through LDS: 16 units are one cache line
     if (hp_ok) {
