@@ -325,7 +325,14 @@ seqw_kernel(SeqWArgs a) {
         add_part<KW, KA>(acc, part[blk], lane);
       }
     } else {
-      if constexpr (!kExpandedOnce<KW, KA, NC>) keep_packed(w);
+      if constexpr (NC == 1 && KW * KA == 9) {
+        // the first half's weights stay expanded, for which there are registers (us per 35 steps, none / these: 1024 units batch 64 227.3 /
+        // 224.1, GRU 228.0 / 222.2, 512 units batch 30 191.5 / 185.5)
+#pragma unroll
+        for (int i = 0; i < KW; ++i) asm volatile("" : "+v"(w[0][i][1].x), "+v"(w[0][i][1].y), "+v"(w[0][i][1].z), "+v"(w[0][i][1].w));
+      } else if constexpr (!kExpandedOnce<KW, KA, NC>) {
+        keep_packed(w);
+      }
       contract<KW, KA, NC>(w, image, l16, l4, n, acc);
     }
     weigh<KW, KA>(acc, al, bt, y);
