@@ -11,7 +11,8 @@
 //     x-side sums of step t are formed while the codes of h_{t-1} are under way;
 //   - per step two exchanges: every workgroup publishes its h_t; the workgroup in charge of a batch entry (one of
 //     those of its tile) gathers the entry's whole h_t, quantizes it (the shared quantizer core on 4 waves) and
-//     publishes its codes, which all workgroups of the tile gather as matrix operands.  What is published goes through LDS
+//     publishes its codes, which all workgroups of the tile gather as matrix operands (both kinds of wave, where the x side
+//     leaves time).  What is published goes through LDS
 //     to the x side's waves, which store it: a wave's loads are counted behind its stores, and a store takes 1500 cycles
 //     until it is acknowledged, which the polls of the h side's waves would otherwise wait for.
 // What is exchanged are 8-byte {value, step tag} pairs, each written with one device-scope store; the readers poll
@@ -146,10 +147,9 @@ __device__ __forceinline__ void keep_packed_part(uint4 (&w)[2][KW]) {
 }
 
 // NC: stretches of 1024 entries of the longer operand block (1 or 2).  Waves 0 .. 3 take the h side, the cell and the
-// quantizer, waves 4 .. 7 the x side of the next step.
-template <int KW, int KA, int EPI, int NC>
-__global__ __launch_bounds__(64 * kWWaves, 2) __attribute__((amdgpu_num_vgpr(kResidentRegisters / 2))) void
-seqw_kernel(SeqWArgs a) {
+// quantizer, waves 4 .. 7 the x side of the next step.  BOTH: the x waves gather half of the codes as well (both_gather).
+template <int KW, int KA, int EPI, int NC, bool BOTH>
+__device__ __forceinline__ void seqw_body(const SeqWArgs& a) {
   constexpr int NG = (EPI == kEpiGru) ? 3 : 4;
   constexpr int kImage = KA * NC * kSteps * 64;
   constexpr int NJ = 4 * NC;  // slots per lane of the quantizer
@@ -355,14 +355,14 @@ seqw_kernel(SeqWArgs a) {
   const bool hp_ok = hp_unit < H && hp_col < ncols;
   const size_t hp_at = (size_t)(b0 + (hp_ok ? hp_col : 0)) * H + (hp_ok ? hp_unit : 0);
 
-  // ---- gathering the codes of a step (h waves): thread -> word of the row and entry; the same bytes land where
-  // expand_inputs puts those of the inputs
-  constexpr int kWords = 32 * NC;                   // words of a row, padding included
-  constexpr int kColsPer = 64 * kWBlocks / kWords;  // entries per request
-  constexpr int kColReq = kTileB / kColsPer;        // requests per plane
+  // ---- gathering the codes of a step, by the h waves or (BOTH) half of the tile's entries by either kind: thread -> word of the row
+  // and entry; the same bytes land where expand_inputs puts those of the inputs
+  constexpr int kWords = 32 * NC;                              // words of a row, padding included
+  constexpr int kColsPer = 64 * kWBlocks / kWords;             // entries per request
+  constexpr int kColReq = kTileB / kColsPer / (BOTH ? 2 : 1);  // requests per plane
   constexpr int kGather = KA * kColReq;
   const int gt = tid & (64 * kWBlocks - 1);
-  const int gw = gt & (kWords - 1), gc = gt / kWords;
+  const int gw = gt & (kWords - 1), gc = (BOTH && xwave ? kTileB / 2 : 0) + gt / kWords;
   const bool gok = gw < wprH;
   unsigned goff[kColReq];
 #pragma unroll
@@ -373,6 +373,32 @@ seqw_kernel(SeqWArgs a) {
   const unsigned gboff = (unsigned)(col * centry + KA * wprH + (l4 < KA ? l4 : KA - 1)) * 8u;
   const int gdst = ((gw >> 5) * kSteps + 4 * ((gw >> 4) & 1) + (gw & 3)) * 64 + 16 * ((gw >> 2) & 3);
   const int gswz = (((gw >> 2) & 3) << 1) | (((gw >> 4) & 1) << 3);
+  // returns this lane's coefficient (h waves)
+  auto gather_codes = [&](int t) {
+    const unsigned tag = (unsigned)t + 1u;
+    const char* src = reinterpret_cast<const char*>(a.cbuf + (t & 1) * chalf + (size_t)tile * kTileB * centry);
+    auto at = [](const char* base, unsigned off) { return reinterpret_cast<const unsigned long long*>(base + off); };
+    unsigned long long v[kGather], bv = (unsigned long long)tag << 32;
+    unsigned spins = 0;
+    for (;;) {
+      if (!xwave) bv = get_pair(at(src, gboff));
+#pragma unroll
+      for (int q = 0; q < kGather; ++q) v[q] = get_pair(at(src + (q / kColReq) * wprH * 8, goff[q % kColReq]));
+      bool ready = (unsigned)(bv >> 32) == tag;
+#pragma unroll
+      for (int q = 0; q < kGather; ++q) ready = ready && (unsigned)(v[q] >> 32) == tag;
+      if (__all(ready)) break;
+      if (!poll_again(spins, a.limit, flag)) {
+        dead = 1;
+        break;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kGather; ++q)
+      lds[(q / kColReq) * NC * kSteps * 64 + gdst + ((q % kColReq * kColsPer + gc) ^ gswz)] =
+          expand4_signed(gok ? (uint32_t)(v[q] & 0xffffffffull) : 0u);
+    return __uint_as_float((unsigned)(bv & 0xffffffffull));
+  };
 
   // ---- x side of step u: its inputs into the image (one barrier before they are used), the sums into xsum
   float xbeta = 0.0f;
@@ -391,7 +417,7 @@ seqw_kernel(SeqWArgs a) {
   // leave and the piece is done again.  Each kind has its own loop over the steps, so that what only one of them keeps
   // takes no registers in the other.  With one loop for both the forms needed up to 256 registers (W3/A3 on two
   // stretches 32 more, spilled), now 15 to 40 fewer; 240 are allowed (kResidentRegisters), which leaves W3/A3 on two
-  // stretches 18 to 30 spilled, W2/A2, W2/A3 on two and W3/A2 up to 4.
+  // stretches 18 to 50 spilled and four other forms up to 4.
   auto x_step = [&](int t) {
     const unsigned tag = (unsigned)t + 1u;
     stage_inputs(t + 1);
@@ -403,6 +429,7 @@ seqw_kernel(SeqWArgs a) {
     lds_barrier();
     // x side of step t + 1, while the codes are under way
     x_side(t + 1);
+    if constexpr (BOTH) gather_codes(t);
     lds_barrier();
     const int gone = dead;
     if (shared_k) {
@@ -422,7 +449,6 @@ seqw_kernel(SeqWArgs a) {
     return __builtin_amdgcn_readfirstlane(gone) != 0;
   };
   auto h_step = [&](int t) {
-    const unsigned tag = (unsigned)t + 1u;
     // ---- quantize h_{t-1} of the entries in this workgroup's charge
     if (t > 0 && q_first < ncols) __builtin_amdgcn_s_sleep(kFirstPoll);
     for (int e = q_first; e < ncols; e += q_next) {
@@ -476,28 +502,7 @@ seqw_kernel(SeqWArgs a) {
     lds_barrier();
 
     // ---- codes of h_{t-1}
-    const char* src = reinterpret_cast<const char*>(a.cbuf + (t & 1) * chalf + (size_t)tile * kTileB * centry);
-    auto at = [](const char* base, unsigned off) { return reinterpret_cast<const unsigned long long*>(base + off); };
-    unsigned long long v[kGather], bv;
-    unsigned spins = 0;
-    for (;;) {
-      bv = get_pair(at(src, gboff));
-#pragma unroll
-      for (int q = 0; q < kGather; ++q) v[q] = get_pair(at(src + (q / kColReq) * wprH * 8, goff[q % kColReq]));
-      bool ready = (unsigned)(bv >> 32) == tag;
-#pragma unroll
-      for (int q = 0; q < kGather; ++q) ready = ready && (unsigned)(v[q] >> 32) == tag;
-      if (__all(ready)) break;
-      if (!poll_again(spins, a.limit, flag)) {
-        dead = 1;
-        break;
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < kGather; ++q)
-      image[(q / kColReq) * NC * kSteps * 64 + gdst + ((q % kColReq * kColsPer + gc) ^ gswz)] =
-          expand4_signed(gok ? (uint32_t)(v[q] & 0xffffffffull) : 0u);
-    const float beta = __uint_as_float((unsigned)(bv & 0xffffffffull));
+    const float beta = gather_codes(t);
     lds_barrier();
     const int gone = dead;
 
@@ -531,6 +536,23 @@ seqw_kernel(SeqWArgs a) {
   for (int t = 0; t < a.steps; ++t)
     if (x_step(t)) return;
 }
+
+template <int KW, int KA, int EPI, int NC>
+__global__ __launch_bounds__(64 * kWWaves, 2) __attribute__((amdgpu_num_vgpr(kResidentRegisters / 2))) void
+seqw_kernel(SeqWArgs a) {
+  seqw_body<KW, KA, EPI, NC, true>(a);
+}
+template <int KW, int KA, int EPI>
+__global__ __launch_bounds__(64 * kWWaves, 2) __attribute__((amdgpu_num_vgpr(kResidentRegisters / 2))) void
+seqw_apart_kernel(SeqWArgs a) {
+  seqw_body<KW, KA, EPI, 2, false>(a);
+}
+
+// Whether the x waves gather half of the codes.  They do so once their x side is done, which must be before the codes arrive: not with
+// inputs of more than 1536 entries that are longer than the state or meet 3-bit weights.  us per 35 steps, h waves alone / both: 1024 units batch
+// 64 W3/A3 223.6 / 219.8, 300 units batch 64 W3/A3 185.8 / 179.4, 1500 units batch 20 W2/A2 209.1 / 201.5, W2/A3 261.0 / 247.7, 2048 units batch 16 W2/A2
+// 220.1 / 218.4; W3/A2 240.8 / 248.1, 300 units with inputs of 2048 W2/A2 164.0 / 168.9.
+constexpr bool both_gather(int k_w, long long I, long long H) { return I <= 1536 || (k_w < 3 && I <= H); }
 
 // Before a launch: room for it (without it the flag is raised at once), no tags.
 constexpr unsigned kNoRoom = 2u;  // (any other value but 0: a wait gave up)
@@ -634,8 +656,14 @@ hipError_t launch_recover(const SeqWArgs& a, int k_w, int k_a, int epi, const Re
   return hipGetLastError();
 }
 
+template <int KW, int KA, int EPI, int NC, bool BOTH>
+constexpr auto kernel_of() {
+  if constexpr (BOTH) return &seqw_kernel<KW, KA, EPI, NC>;
+  else return &seqw_apart_kernel<KW, KA, EPI>;
+}
+
 // Workgroups of an instantiation that the current device holds at once (asked for once per device).
-template <int KW, int KA, int EPI, int NC>
+template <int KW, int KA, int EPI, int NC, bool BOTH>
 int resident_grid() {
   static std::atomic<int> known[64];
   int dev = 0;
@@ -646,7 +674,7 @@ int resident_grid() {
     if (k > 0) return k - 1;
   }
   constexpr size_t lds = seqw_lds<KW, KA, NC>();
-  const void* fn = reinterpret_cast<const void*>(&seqw_kernel<KW, KA, EPI, NC>);
+  const void* fn = reinterpret_cast<const void*>(kernel_of<KW, KA, EPI, NC, BOTH>());
   int cus = 0, per = 0;
   if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -660,19 +688,24 @@ int resident_grid() {
 }
 
 // launch == nullptr: only asks whether the grid fits
-template <int KW, int KA, int EPI, int NC>
+template <int KW, int KA, int EPI, int NC, bool BOTH = true>
 hipError_t run_one(const SeqWArgs* launch, dim3 grid, hipStream_t s) {
-  const int fit = resident_grid<KW, KA, EPI, NC>();
+  const int fit = resident_grid<KW, KA, EPI, NC, BOTH>();
   if ((long long)grid.x * grid.y > fit) return hipErrorInvalidValue;
   if (!launch) return hipSuccess;
-  hipLaunchKernelGGL((seqw_kernel<KW, KA, EPI, NC>), grid, dim3(64 * kWWaves), (seqw_lds<KW, KA, NC>()), s, *launch);
+  hipLaunchKernelGGL((kernel_of<KW, KA, EPI, NC, BOTH>()), grid, dim3(64 * kWWaves), (seqw_lds<KW, KA, NC>()), s, *launch);
   return hipGetLastError();
 }
 
+template <int KW, int KA, int EPI>
+hipError_t run_cell(const SeqWArgs* l, dim3 grid, int nc, bool both, hipStream_t s) {
+  if (nc == 1) return run_one<KW, KA, EPI, 1>(l, grid, s);
+  return both ? run_one<KW, KA, EPI, 2>(l, grid, s) : run_one<KW, KA, EPI, 2, false>(l, grid, s);
+}
+
 template <int KW, int KA>
-hipError_t run_k(const SeqWArgs* l, dim3 grid, int epi, int nc, hipStream_t s) {
-  if (epi == kEpiLstm) return nc == 1 ? run_one<KW, KA, kEpiLstm, 1>(l, grid, s) : run_one<KW, KA, kEpiLstm, 2>(l, grid, s);
-  return nc == 1 ? run_one<KW, KA, kEpiGru, 1>(l, grid, s) : run_one<KW, KA, kEpiGru, 2>(l, grid, s);
+hipError_t run_k(const SeqWArgs* l, dim3 grid, int epi, int nc, bool both, hipStream_t s) {
+  return epi == kEpiLstm ? run_cell<KW, KA, kEpiLstm>(l, grid, nc, both, s) : run_cell<KW, KA, kEpiGru>(l, grid, nc, both, s);
 }
 
 dim3 seqw_grid(long long H, long long batch) {
@@ -682,16 +715,17 @@ dim3 seqw_grid(long long H, long long batch) {
 hipError_t run(const SeqWArgs* l, long long I, long long H, long long batch, int k_w, int k_a, int epi, hipStream_t s) {
   const dim3 grid = seqw_grid(H, batch);
   const int nc = (I > H ? I : H) > 1024 ? 2 : 1;
+  const bool both = both_gather(k_w, I, H);
   switch (k_w * 4 + k_a) {
-    case 4 * 1 + 1: return run_k<1, 1>(l, grid, epi, nc, s);
-    case 4 * 1 + 2: return run_k<1, 2>(l, grid, epi, nc, s);
-    case 4 * 1 + 3: return run_k<1, 3>(l, grid, epi, nc, s);
-    case 4 * 2 + 1: return run_k<2, 1>(l, grid, epi, nc, s);
-    case 4 * 2 + 2: return run_k<2, 2>(l, grid, epi, nc, s);
-    case 4 * 2 + 3: return run_k<2, 3>(l, grid, epi, nc, s);
-    case 4 * 3 + 1: return run_k<3, 1>(l, grid, epi, nc, s);
-    case 4 * 3 + 2: return run_k<3, 2>(l, grid, epi, nc, s);
-    case 4 * 3 + 3: return run_k<3, 3>(l, grid, epi, nc, s);
+    case 4 * 1 + 1: return run_k<1, 1>(l, grid, epi, nc, both, s);
+    case 4 * 1 + 2: return run_k<1, 2>(l, grid, epi, nc, both, s);
+    case 4 * 1 + 3: return run_k<1, 3>(l, grid, epi, nc, both, s);
+    case 4 * 2 + 1: return run_k<2, 1>(l, grid, epi, nc, both, s);
+    case 4 * 2 + 2: return run_k<2, 2>(l, grid, epi, nc, both, s);
+    case 4 * 2 + 3: return run_k<2, 3>(l, grid, epi, nc, both, s);
+    case 4 * 3 + 1: return run_k<3, 1>(l, grid, epi, nc, both, s);
+    case 4 * 3 + 2: return run_k<3, 2>(l, grid, epi, nc, both, s);
+    case 4 * 3 + 3: return run_k<3, 3>(l, grid, epi, nc, both, s);
   }
   return hipErrorInvalidValue;
 }

@@ -1,5 +1,7 @@
 """GPU: resident sequences whose vectors are longer than 1024 entries, where two waves share the contraction of a row block
-(amq_seqw.hip), against per-step calls, bit for bit: the partial sums are integers that binary16 holds, so nothing may be lost."""
+(amq_seqw.hip), against per-step calls, bit for bit: the partial sums are integers that binary16 holds, so nothing may be lost.  And
+either side of the line between codes gathered by one and by both of the two waves (inputs of 1536 entries; longer ones not longer
+than the state, with 1- and 2-bit weights)."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -10,7 +12,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("gates,I,H,B,k_w,k_a", [
     (4, 1025, 1025, 2, 2, 2), (4, 64, 1536, 17, 2, 2), (3, 2048, 1537, 5, 2, 2), (4, 2048, 2048, 16, 3, 3), (3, 1100, 1024, 20, 3, 3),
     (4, 1300, 513, 4, 2, 2), (4, 2047, 2047, 3, 1, 1), (3, 1030, 1281, 18, 1, 2), (4, 700, 1500, 20, 1, 3), (3, 1536, 1536, 2, 2, 1),
-    (4, 33, 1100, 3, 3, 3), (4, 1025, 1600, 3, 2, 3)])
+    (4, 33, 1100, 3, 3, 3), (4, 1025, 1600, 3, 2, 3),
+    (4, 1536, 1200, 9, 2, 2), (4, 1537, 1200, 9, 2, 2), (4, 1537, 1537, 8, 3, 2), (3, 1537, 1537, 7, 2, 3), (4, 2000, 300, 24, 2, 2),
+    (3, 1600, 40, 9, 3, 3), (4, 300, 24, 16, 2, 2), (3, 100, 1000, 8, 1, 3)])
 def test_same_bits_as_steps(gates, I, H, B, k_w, k_a):
     import torch
     import paper_1802_00150_amd as amq

@@ -101,3 +101,9 @@ def test_room_for_waiting_kernels_beside_tiled_sequences(registers):
     # one workgroup of 8 waves per compute unit, as amq_seqw.hip
     for name, r in of(registers, "17seqw_tiles_kernel", 12).items():
         assert 2 * r + WAITERS * 8 <= SIMD_REGISTERS, (name, r)
+
+
+def test_room_for_waiting_kernels_beside_sequences_with_long_inputs(registers):
+    # one workgroup of 8 waves per compute unit, as the other kernel of amq_seqw.hip
+    for name, r in of(registers, "17seqw_apart_kernel", 18).items():
+        assert 2 * r + WAITERS * 8 <= SIMD_REGISTERS, (name, r)
