@@ -417,7 +417,7 @@ __device__ __forceinline__ void seqw_body(const SeqWArgs& a) {
   // leave and the piece is done again.  Each kind has its own loop over the steps, so that what only one of them keeps
   // takes no registers in the other.  With one loop for both the forms needed up to 256 registers (W3/A3 on two
   // stretches 32 more, spilled), now 15 to 40 fewer; 240 are allowed (kResidentRegisters), which leaves W3/A3 on two
-  // stretches 18 to 50 spilled and four other forms up to 4.
+  // stretches 30 to 76 spilled and four other forms up to 4.
   auto x_step = [&](int t) {
     const unsigned tag = (unsigned)t + 1u;
     stage_inputs(t + 1);
