@@ -100,42 +100,27 @@ __device__ __forceinline__ void contract_part(const uint4 (&araw)[2][KW], const 
     for (int j = 0; j < KA; ++j) asm volatile("" : "+v"(acc[i][j]));
 }
 
-// Partial sums from one wave to another through LDS, [piece][lane]: integers of at most 1024, which binary16 holds exactly, so the
-// sums are the same in whatever order they are formed.
+// Partial sums from one wave to another through LDS, [piece][lane]: integers of at most 1024 in binary32, so the sums are the same in
+// whatever order they are formed.
 template <int KW, int KA>
-constexpr int kPartPieces = (KW * KA * 2 + 3) / 4;  // pieces of 16 bytes per lane
-typedef _Float16 Half2 __attribute__((ext_vector_type(2)));
+constexpr int kPartPieces = KW * KA;  // pieces of 16 bytes per lane
 
 template <int KW, int KA>
-__device__ __forceinline__ void put_part(const v4f (&acc)[KW][KA], uint4* part, int lane) {
-  unsigned d[4 * kPartPieces<KW, KA>] = {};
+__device__ __forceinline__ void put_part(const v4f (&acc)[KW][KA], float4* part, int lane) {
 #pragma unroll
-  for (int q = 0; q < KW * KA; ++q)
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const v4f& v = acc[q / KA][q % KA];
-      d[2 * q + e] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(v[2 * e], v[2 * e + 1]));
-    }
-#pragma unroll
-  for (int p = 0; p < kPartPieces<KW, KA>; ++p) part[p * 64 + lane] = make_uint4(d[4 * p], d[4 * p + 1], d[4 * p + 2], d[4 * p + 3]);
+  for (int q = 0; q < KW * KA; ++q) {
+    const v4f& v = acc[q / KA][q % KA];
+    part[q * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+  }
 }
 
 template <int KW, int KA>
-__device__ __forceinline__ void add_part(v4f (&acc)[KW][KA], const uint4* part, int lane) {
-  uint4 piece[kPartPieces<KW, KA>];
+__device__ __forceinline__ void add_part(v4f (&acc)[KW][KA], const float4* part, int lane) {
 #pragma unroll
-  for (int p = 0; p < kPartPieces<KW, KA>; ++p) piece[p] = part[p * 64 + lane];
-#pragma unroll
-  for (int q = 0; q < KW * KA; ++q)
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int at = 2 * q + e;
-      const uint4& v = piece[at >> 2];
-      const unsigned w = (at & 3) == 0 ? v.x : (at & 3) == 1 ? v.y : (at & 3) == 2 ? v.z : v.w;
-      const Half2 x = __builtin_bit_cast(Half2, w);
-      acc[q / KA][q % KA][2 * e] += (float)x[0];
-      acc[q / KA][q % KA][2 * e + 1] += (float)x[1];
-    }
+  for (int q = 0; q < KW * KA; ++q) {
+    const float4 v = part[q * 64 + lane];
+    acc[q / KA][q % KA] += v4f{v.x, v.y, v.z, v.w};
+  }
 }
 
 template <int KW>
@@ -159,7 +144,7 @@ __device__ __forceinline__ void seqw_body(const SeqWArgs& a) {
   __shared__ float hout[kTileB][4 * kBlocksPad];           // h_t of the workgroup's units
   __shared__ float4 xsum[2][kWBlocks][64];  // x-side sums of two consecutive steps
   constexpr bool kShared = kSharedK<KW, KA, NC>;
-  __shared__ uint4 part[kShared ? kWBlocks : 1][kShared ? kPartPieces<KW, KA> * 64 : 1];  // h-side sums over the second half of K
+  __shared__ float4 part[kShared ? kWBlocks : 1][kShared ? kPartPieces<KW, KA> * 64 : 1];  // h-side sums over the second half of K
   extern __shared__ __attribute__((aligned(16))) uint4 lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -417,7 +402,7 @@ __device__ __forceinline__ void seqw_body(const SeqWArgs& a) {
   // leave and the piece is done again.  Each kind has its own loop over the steps, so that what only one of them keeps
   // takes no registers in the other.  With one loop for both the forms needed up to 256 registers (W3/A3 on two
   // stretches 32 more, spilled), now 15 to 40 fewer; 240 are allowed (kResidentRegisters), which leaves W3/A3 on two
-  // stretches 30 to 76 spilled and four other forms up to 4.
+  // stretches 13 to 47 spilled and four other forms up to 4.
   auto x_step = [&](int t) {
     const unsigned tag = (unsigned)t + 1u;
     stage_inputs(t + 1);
