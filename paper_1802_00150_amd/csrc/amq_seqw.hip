@@ -42,7 +42,12 @@ namespace {
 // with 0 / 10 / 12 / 14 / 16, us per 35 steps: 1024 units batch 64 W2/A2 180 / 181 / 178 / 177 / 178, GRU 187 / 181 / 179 / 178 / 178,
 // W3/A3 235 / 230 / 228 / 226 / 226, 650 units batch 20 166 / 160 / 158 / 159 / 159, 2000 units batch 5 228 / 216 / 215 / 216 / 217.  (The
 // codes are asked for at once: any delay there is lost, 4 units 2 us, 12 units 8 us.)
-constexpr int kFirstPoll = 14;
+// Up to kFewWorkgroups workgroups per tile, no more than there are dies, finish close together and are seen sooner.  Measured there with
+// 0 / 4 / 8 / 14: 20 units batch 5 W2/A2 233 / 234 / 238 / 244, 64 batch 5 171 / 172 / 175 / 180, GRU 8 batch 2 158 / 160 / 164 / 170, 100 units with
+// inputs of 600 batch 8 189 / 187 / 187 / 192; over 24 kinds of call each, the mean (the least) of the speed without any wait or later store: 20
+// units 1.008 / 1.008 / 1.002 / 0.983 (0.988 / 0.988 / 0.967 / 0.924), 64 1.010 / 1.017 / 1.030 / 1.011 (0.981 / 0.992 / 0.973 / 0.935), 100 1.011 /
+// 1.017 / 1.029 / 1.021 (0.981 / 0.985 / 0.993 / 0.976); beyond, 160 1.018 / 1.026 / 1.034 / 1.035 (0.994 / 1.001 / 1.002 / 1.014).
+constexpr int kFirstPoll = 14, kFirstPollFew = 4, kFewWorkgroups = 8;
 
 // Whether the two waves of a row block share the contraction of its h side, half of K each (the x side's wave has nothing else to do
 // then).  The matrix instructions of a compute unit's SIMD are the same either way; what two waves halve is the expansion of weights that
@@ -435,7 +440,10 @@ __device__ __forceinline__ void seqw_body(const SeqWArgs& a) {
   };
   auto h_step = [&](int t) {
     // ---- quantize h_{t-1} of the entries in this workgroup's charge
-    if (t > 0 && q_first < ncols) __builtin_amdgcn_s_sleep(kFirstPoll);
+    if (t > 0 && q_first < ncols) {
+      __builtin_amdgcn_s_sleep(kFirstPollFew);
+      if (G > kFewWorkgroups) __builtin_amdgcn_s_sleep(kFirstPoll - kFirstPollFew);
+    }
     for (int e = q_first; e < ncols; e += q_next) {
       float v[NJ];
       if (t == 0) {

@@ -1,0 +1,62 @@
+"""GPU: sequences in one launch at the lines between their forms -- how long the first poll waits, and which waves gather the codes
+(amq_seqw.hip, amq_seq1_body.h) -- against per-step calls, bit for bit.  The word in which such a launch says how it ended is
+read as well: the workspace is filled with a pattern first, so that per-step launches in its place, a wait that gave up or a launch
+without room would show."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+FILL = 0xA5
+ENDED, GAVE_UP = 0, 1
+
+
+@pytest.fixture(scope="module")
+def amq():
+    import paper_1802_00150_amd as m
+    m.binding.lib()
+    return m
+
+
+def last_bytes(H, B, k_a):
+    """Bytes of what a batched sequence's launch keeps at the end of the workspace, its word first."""
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    wpr = 4 * ((H + 127) // 128)
+    entry = (k_a * (wpr + 1) + 15) // 16 * 16
+    return up(256 + up(16 * B * H) + up(16 * ((B + 15) // 16) * 16 * entry) + 2 * up(4 * B * H))
+
+
+def same_bits_as_steps(amq, gates, I, H, B, k_w, k_a, steps=4):
+    """Runs the sequence and the steps; returns the word of the launch (None for a single entry)."""
+    import torch
+    print("lines", gates, I, H, B, k_w, k_a, flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(I + 3 * H + 5 * B + gates)
+    randn = lambda *s: torch.randn(*s, generator=g, device="cuda:0")  # noqa: E731
+    d = [*amq.quantize_weights(randn(gates * H, I) * 0.05, k_w, 2), *amq.quantize_weights(randn(gates * H, H) * 0.05, k_w, 2)]
+    bias = [randn(gates * H) * 0.1 for _ in range(2)]
+    xs, h, c = randn(steps, B, I), torch.tanh(randn(B, H)), randn(B, H)
+    hs = torch.full((steps, B, H), float("nan"), device=h.device)
+    hq, cq = h.clone(), c.clone()
+    ws = (amq.lstm_sequence_workspace if gates == 4 else amq.gru_sequence_workspace)(I, H, B, k_a, h.device).fill_(FILL)
+    if gates == 4:
+        amq.lstm_sequence(*d, I, H, bias[0], xs, hq, cq, k_a, 2, ws=ws, hs=hs)
+    else:
+        amq.gru_sequence(*d, I, H, *bias, xs, hq, k_a, 2, ws=ws, hs=hs)
+    word = None
+    if B > 1:
+        at = ws.numel() - last_bytes(H, B, k_a)
+        word = int(ws[at:at + 4].view(torch.int32).item())
+    for t in range(steps):
+        if gates == 4:
+            h, c = amq.lstm_step(*d, I, H, bias[0], xs[t], h, c, k_a, 2)
+        else:
+            h = amq.gru_step(*d, I, H, *bias, xs[t], h, k_a, 2)
+        assert bool(torch.isfinite(h).all()) and torch.equal(hs[t], h), (t, int((hs[t] != h).sum()))
+    assert torch.equal(hq, h) and (gates == 3 or torch.equal(cq, c))
+    return word
+
+
+# one workgroup per tile, one with several entries, eight and nine of them; long inputs
+@pytest.mark.parametrize("gates,I,H,B,k_w,k_a", [
+    (4, 8, 8, 2, 2, 2), (3, 20, 20, 33, 3, 1), (4, 128, 128, 5, 2, 2), (3, 129, 129, 5, 2, 3), (4, 600, 112, 16, 1, 2), (3, 1024, 130, 17, 3, 3)])
+def test_few_workgroups(amq, gates, I, H, B, k_w, k_a):
+    assert same_bits_as_steps(amq, gates, I, H, B, k_w, k_a) == ENDED
