@@ -43,17 +43,26 @@ constexpr int k1Waves = 4;
 
 // How long a wave waits, after the x side of the next step, before it asks for h_t for the first time, in units of 64 cycles: h_t is
 // seen elsewhere about 1400 cycles after it was stored, and a poll that finds a part of it costs another trip (about 900).  The x side
-// itself takes the longer the more planes a lane has, so the wait is the rest.  Swept over 0 to 14 units for each form; two more or fewer
-// cost 1 %.  0: the form asks at once, as two units per lane (or nine plane products of an LSTM) fill that time.  us per 35 steps, at once /
-// here: LSTM W2/A2 300 units 89.6 / 86.4, 448 99.5 / 93.6, 650 110.8 / 103.9, 1024 113.3 / 107.2, W2/A3 350 118.8 / 114.9, W3/A2 350 95.9 / 90.2,
-// GRU W2/A2 300 93.3 / 88.8, 650 110.1 / 105.7, W2/A3 200 110.8 / 107.1, W3/A3 256 116.2 / 111.2; forms that stay, had they waited: 1500
-// units W2/A2 123.8 / 125.3, GRU W3/A2 650 108.6 / 111.1, LSTM W2/A3 768 128.5 / 130.2.
+// itself takes the longer the more gates and plane products a lane has, so the wait is the rest: 8 or 7, 5, 3 for the four, six and nine
+// products of a GRU, 5, 4 or 2, 0 for an LSTM, 0 with two units per lane.  Swept over 0 to 14 units for each form; two more or fewer cost 1 %.
+// us per 35 steps, at once / here: LSTM W2/A2 300 units 90.9 / 86.4, 448 97.8 / 90.7, 650 109.3 / 103.0, 1024 112.9 / 107.1, W2/A3 350
+// 121.0 / 116.7, W3/A2 350 97.0 / 90.9, GRU W2/A2 300 92.4 / 88.5, 650 109.8 / 105.2, W2/A3 200 110.5 / 106.3, W3/A3 256 113.4 / 109.0.  Four
+// waves gain nothing with 3-bit weights in a GRU or 3-bit activations in an LSTM of up to 768 units: at once / with the 5 or 2 units of the
+// others W3/A2 650 108.9 / 109.6, 1024 112.3 / 114, W2/A3 650 129.9 / 130.4, 768 129.2 / 130.0; nor do two units per lane: 1500 units W2/A2
+// 123.8 / 125.3.  LSTMs of six products and up to 256 units ask at once: with the wait 1 to 2 % faster from 200 units on, but 4 % slower
+// below even where it is passed over (W3/A2 112 units 76.5 / 79.4), as the x side then is not formed under the first poll.
 constexpr int first_poll(int kw, int ka, bool gru, int qw, int nj, int u) {
   const int planes = kw * ka;
   if (u == 2) return 0;
   if (gru) return planes == 4 ? (qw == 1 ? 8 : 7) : planes == 9 ? 3 : qw == 4 && kw == 3 ? 0 : 5;
+  if (planes == 6 && qw == 1 && nj == 4) return 0;
   return planes == 4 ? 5 : planes == 9 ? 0 : ka == 2 ? 4 : qw == 4 && nj == 3 ? 0 : 2;
 }
+
+// States longer than this wait.  Shorter ones are a few workgroups that finish close together, and their first poll succeeds: us per 35
+// steps, at once / wait / here, LSTM W2/A2 16 units 75.8 / 81.2 / 77.6, 64 80.9 / 84.3 / 80.9, 144 80.5 / 84.1 / 81.1, GRU W2/A2 64 75.5 /
+// 79.8 / 73.1, W3/A3 128 105.9 / 105.8 / 102.8; above, at once / here, LSTM 200 units 86.0 / 84.1, GRU 160 91.7 / 87.5.
+constexpr int first_poll_from(bool gru) { return gru ? 128 : 192; }
 
 template <int KW, int KA, int EPI, int QW, int NJ, int U, bool JOINT>
 __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
@@ -133,7 +142,9 @@ __global__ __launch_bounds__(64 * k1Waves, 2) void seq1_kernel(Seq1Args a) {
   // (a wave on its own that owns no unit publishes nothing, so nobody would wait for it to have read a buffer)
   const int steps = QW == 1 && (int)(blockIdx.x * k1Waves + wv) * U * per >= H ? 0 : a.steps;
   bool alive = true;
-  const int first_wait = kFirstPoll > 0 ? opaque_s(kFirstPoll) : 0;
+  // (a loop over single units, of a count that the compiler does not see: with one s_sleep of the whole count forms of more than 256 units
+  // are up to 2.6 % slower, in the mean 0.2 %)
+  const int first_wait = kFirstPoll > 0 && (QW > 1 || NJ > 4 || H > first_poll_from(EPI == kEpiGru)) ? opaque_s(kFirstPoll) : 0;
   for (int t = 0; t < steps; ++t) {
     if (kFirstPoll > 0 && t > 0)
       for (int i = 0; i < first_wait; ++i) __builtin_amdgcn_s_sleep(1);

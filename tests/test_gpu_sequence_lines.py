@@ -60,3 +60,40 @@ def same_bits_as_steps(amq, gates, I, H, B, k_w, k_a, steps=4):
     (4, 8, 8, 2, 2, 2), (3, 20, 20, 33, 3, 1), (4, 128, 128, 5, 2, 2), (3, 129, 129, 5, 2, 3), (4, 600, 112, 16, 1, 2), (3, 1024, 130, 17, 3, 3)])
 def test_few_workgroups(amq, gates, I, H, B, k_w, k_a):
     assert same_bits_as_steps(amq, gates, I, H, B, k_w, k_a) == ENDED
+
+
+# the longest states that ask at once and the shortest that wait: 192 units of an LSTM, 128 of a GRU; LSTMs of six plane products up to 256.
+# LSTMs against the form that captured streams take, which adds in the same order
+@pytest.mark.parametrize("gates,H,k_w,k_a", [
+    (4, 40, 2, 2), (4, 192, 2, 2), (4, 193, 2, 2), (3, 128, 2, 2), (3, 129, 3, 3), (4, 256, 2, 3), (4, 257, 2, 3), (4, 200, 3, 2), (3, 100, 3, 2)])
+def test_single_entries(amq, gates, H, k_w, k_a):
+    import torch
+    I, steps = H + 30, 70
+    if gates == 3:
+        assert same_bits_as_steps(amq, gates, I, H, 1, k_w, k_a, steps) is None
+        return
+    print("lines", gates, I, H, 1, k_w, k_a, flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(H)
+    randn = lambda *s: torch.randn(*s, generator=g, device="cuda:0")  # noqa: E731
+    d = [*amq.quantize_weights(randn(4 * H, I) * 0.05, k_w, 2), *amq.quantize_weights(randn(4 * H, H) * 0.05, k_w, 2)]
+    bias, xs, h0, c0 = randn(4 * H) * 0.1, randn(steps, 1, I), torch.tanh(randn(1, H)), randn(1, H)
+    h, c, hs = h0.clone(), c0.clone(), torch.full((steps, 1, H), float("nan"), device=h0.device)
+    ws = amq.lstm_sequence_workspace(I, H, 1, k_a, h.device).fill_(FILL)
+
+    def call():
+        amq.lstm_sequence(*d, I, H, bias, xs, h, c, k_a, 2, ws=ws, hs=hs)
+
+    call()
+    assert not amq.lstm_sequence_abandoned(ws, I, H, 1, k_a)
+    got = [t.clone() for t in (hs, h, c)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for _ in range(2):
+        h.copy_(h0)
+        c.copy_(c0)
+        hs.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(got, (hs, h, c)):
+            assert bool(torch.isfinite(b).all()) and torch.equal(a, b)
