@@ -541,11 +541,19 @@ seqw_apart_kernel(SeqWArgs a) {
   seqw_body<KW, KA, EPI, 2, false>(a);
 }
 
-// Whether the x waves gather half of the codes.  They do so once their x side is done, which must be before the codes arrive: not with
-// inputs of more than 1536 entries that are longer than the state or meet 3-bit weights.  us per 35 steps, h waves alone / both: 1024 units batch
-// 64 W3/A3 223.6 / 219.8, 300 units batch 64 W3/A3 185.8 / 179.4, 1500 units batch 20 W2/A2 209.1 / 201.5, W2/A3 261.0 / 247.7, 2048 units batch 16 W2/A2
-// 220.1 / 218.4; W3/A2 240.8 / 248.1, 300 units with inputs of 2048 W2/A2 164.0 / 168.9.
-constexpr bool both_gather(int k_w, long long I, long long H) { return I <= 1536 || (k_w < 3 && I <= H); }
+// Whether the x waves gather half of the codes.  They do so once their x side is done, which must be before the codes arrive.  The x side
+// takes the longer the more planes the weights have and with a fourth half of 512 inputs; the codes come the sooner the shorter the state
+// is (slots per lane of the quantizer).  Three such reasons are one too many.  Time of the h waves alone / both, mean (range) of 16 to 70 kinds
+// of call for each: 1-bit weights 1.035 to 1.043 whatever the lengths (1.00 to 1.08), 1.01 up to 256 units; 2 bits 1.035 (1.00 to 1.06),
+// up to 1024 units 1.025, with longer inputs 1.020, both 0.992 (0.95 to 1.04), up to 256 units 0.992 and 0.966; 3 bits 1.017 (0.98 to 1.05), up to 1024
+// units 0.979, with longer inputs 0.982, both 0.949.  us per 35 steps, LSTMs batch 16, inputs of 1536 and 1600: 1200 units W2/A2 200.4 / 190.8
+// and 200.5 / 192.6, W3/A3 286.1 / 282.9 and 292.6 / 297.6, 1024 units W2/A3 224.5 / 221.4 and 225.6 / 227.7, W3/A2 191.0 / 193.5 and 196.4 / 204.7.  Nine plane
+// products of a GRU with inputs of two stretches are slower with both throughout, 0.95 (0.92 to 0.99): 1500 units batch 20 278.5 / 283.2; with
+// inputs of 300 273.7 / 269.6.
+constexpr bool both_gather(int k_w, int k_a, bool gru, long long I, long long H) {
+  if (gru && k_w * k_a == 9 && I > 1024) return false;
+  return k_w + (I > 1536) + (H <= 1024) + (H <= 256) <= 3;
+}
 
 // Before a launch: room for it (without it the flag is raised at once), no tags.
 constexpr unsigned kNoRoom = 2u;  // (any other value but 0: a wait gave up)
@@ -708,7 +716,7 @@ dim3 seqw_grid(long long H, long long batch) {
 hipError_t run(const SeqWArgs* l, long long I, long long H, long long batch, int k_w, int k_a, int epi, hipStream_t s) {
   const dim3 grid = seqw_grid(H, batch);
   const int nc = (I > H ? I : H) > 1024 ? 2 : 1;
-  const bool both = both_gather(k_w, I, H);
+  const bool both = both_gather(k_w, k_a, epi == kEpiGru, I, H);
   switch (k_w * 4 + k_a) {
     case 4 * 1 + 1: return run_k<1, 1>(l, grid, epi, nc, both, s);
     case 4 * 1 + 2: return run_k<1, 2>(l, grid, epi, nc, both, s);

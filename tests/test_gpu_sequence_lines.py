@@ -97,3 +97,13 @@ def test_single_entries(amq, gates, H, k_w, k_a):
         torch.cuda.synchronize()
         for a, b in zip(got, (hs, h, c)):
             assert bool(torch.isfinite(b).all()) and torch.equal(a, b)
+
+
+# either side of 256 and 1024 units and of inputs of 1536 for every number of weight planes; a GRU's nine plane products with inputs of
+# one and of two stretches
+@pytest.mark.parametrize("gates,I,H,B,k_w,k_a", [
+    (4, 1537, 256, 9, 1, 2), (3, 1537, 257, 9, 1, 1), (4, 1536, 256, 9, 2, 2), (3, 1100, 257, 17, 2, 3), (4, 1537, 1024, 5, 2, 2), (4, 1537, 1025, 5, 2, 3),
+    (4, 1500, 1024, 16, 3, 3), (4, 1500, 1025, 16, 3, 2), (4, 1537, 1025, 4, 3, 1), (3, 1024, 1030, 18, 3, 3), (3, 1025, 1030, 18, 3, 3),
+    (3, 1536, 1500, 2, 3, 3)])
+def test_who_gathers(amq, gates, I, H, B, k_w, k_a):
+    assert same_bits_as_steps(amq, gates, I, H, B, k_w, k_a) == ENDED
