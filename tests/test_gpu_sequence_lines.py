@@ -107,3 +107,24 @@ def test_single_entries(amq, gates, H, k_w, k_a):
     (3, 1536, 1500, 2, 3, 3)])
 def test_who_gathers(amq, gates, I, H, B, k_w, k_a):
     assert same_bits_as_steps(amq, gates, I, H, B, k_w, k_a) == ENDED
+
+
+# one or both kinds of wave gather, with and without a shared contraction, which has two barriers more: with waits that end at their second
+# poll the launch gives up, all waves leave, and the piece is computed alone
+@pytest.mark.parametrize("gates,I,H,B,k_w,k_a", [
+    (4, 300, 1024, 18, 2, 2), (4, 1500, 1500, 18, 2, 2), (3, 1100, 1300, 3, 3, 3), (4, 600, 1100, 16, 3, 3), (4, 2000, 1024, 18, 2, 2),
+    (4, 2000, 1100, 18, 3, 3), (3, 1700, 1030, 5, 3, 2)])
+def test_gives_up(amq, gates, I, H, B, k_w, k_a):
+    amq.binding.debug_set_sequence_spin_limit(1)
+    try:
+        assert same_bits_as_steps(amq, gates, I, H, B, k_w, k_a) == GAVE_UP
+    finally:
+        amq.binding.debug_set_sequence_spin_limit(0)
+
+
+# lengths on both sides of every half of 512 positions that the shared contraction splits at, by which launch they were computed
+@pytest.mark.parametrize("gates,I,H,B,k_w,k_a", [
+    (4, 1025, 1025, 2, 2, 2), (4, 64, 1536, 17, 2, 2), (3, 2048, 1537, 5, 2, 2), (4, 2048, 2048, 16, 3, 3), (4, 2047, 2047, 3, 1, 1),
+    (3, 1030, 1281, 18, 1, 2), (4, 700, 1500, 20, 1, 3), (3, 1536, 1536, 2, 2, 1), (4, 33, 1100, 3, 3, 3), (4, 1537, 1537, 8, 3, 2)])
+def test_long_states_take_one_launch(amq, gates, I, H, B, k_w, k_a):
+    assert same_bits_as_steps(amq, gates, I, H, B, k_w, k_a) == ENDED
