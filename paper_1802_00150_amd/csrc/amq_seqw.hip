@@ -52,9 +52,10 @@ constexpr int kFirstPoll = 14, kFirstPollFew = 4, kFewWorkgroups = 8;
 // Whether the two waves of a row block share the contraction of its h side, half of K each (the x side's wave has nothing else to do
 // then).  The matrix instructions of a compute unit's SIMD are the same either way; what two waves halve is the expansion of weights that
 // do not stay expanded in registers, at the price of the partial sums' way through LDS and a barrier.  us per 35 steps, alone / shared: two
-// stretches W2/A2 2048 units 222.0 / 218.6, 1500 units 211.4 / 208.8, W3/A3 342.1 / 320.1, 304.6 / 292.1 (fewer registers spilled as well),
-// W1/A1 1800 units 150.9 / 146.1, W2/A1 165.0 / 158.1; six plane products 225.3 / 228.4, 190 / 198, W3/A1 179 / 200; one stretch W2/A2 180 /
-// 188, W3/A3 228 / 232.
+// stretches W2/A2 2048 units batch 16 222.9 / 219.3, 1500 batch 20 204.0 / 200.5, W3/A3 334.6 / 325.4, 288.7 / 287.9, GRU 2048 batch 5 331.8 /
+// 301.8 (fewer registers spilled as well), W1/A1 1500 143.8 / 139.2, W2/A1 153.0 / 146.6, W1/A2 191.1 / 189.6, W1/A3 237.0 / 232.2; six plane
+// products W2/A3 250.1 / 252.7, W3/A2 216.1 / 221.5; W3/A1 161.1 / 158.6, but 2048 units 177.6 / 196.8.  On one stretch it lost 2 to 4 % where that was
+// tried, before the x waves gathered codes: W2/A2 180 / 188, W3/A3 228 / 232.
 template <int KW, int KA, int NC>
 constexpr bool kSharedK = NC == 2 && KW * KA != 6 && !(KW == 3 && KA == 1);
 
@@ -316,8 +317,8 @@ __device__ __forceinline__ void seqw_body(const SeqWArgs& a) {
       }
     } else {
       if constexpr (NC == 1 && KW * KA == 9) {
-        // the first half's weights stay expanded, for which there are registers (us per 35 steps, none / these: 1024 units batch 64 227.3 /
-        // 224.1, GRU 228.0 / 222.2, 512 units batch 30 191.5 / 185.5)
+        // the first half's weights stay expanded, for which there are registers (us per 35 steps when it was introduced, none / these:
+        // 1024 units batch 64 227.3 / 224.1, GRU 228.0 / 222.2, 512 units batch 30 191.5 / 185.5)
 #pragma unroll
         for (int i = 0; i < KW; ++i) asm volatile("" : "+v"(w[0][i][1].x), "+v"(w[0][i][1].y), "+v"(w[0][i][1].z), "+v"(w[0][i][1].w));
       } else if constexpr (!kExpandedOnce<KW, KA, NC>) {
@@ -543,13 +544,13 @@ seqw_apart_kernel(SeqWArgs a) {
 
 // Whether the x waves gather half of the codes.  They do so once their x side is done, which must be before the codes arrive.  The x side
 // takes the longer the more planes the weights have and with a fourth half of 512 inputs; the codes come the sooner the shorter the state
-// is (slots per lane of the quantizer).  Three such reasons are one too many.  Time of the h waves alone / both, mean (range) of 16 to 70 kinds
-// of call for each: 1-bit weights 1.035 to 1.043 whatever the lengths (1.00 to 1.08), 1.01 up to 256 units; 2 bits 1.035 (1.00 to 1.06),
-// up to 1024 units 1.025, with longer inputs 1.020, both 0.992 (0.95 to 1.04), up to 256 units 0.992 and 0.966; 3 bits 1.017 (0.98 to 1.05), up to 1024
-// units 0.979, with longer inputs 0.982, both 0.949.  us per 35 steps, LSTMs batch 16, inputs of 1536 and 1600: 1200 units W2/A2 200.4 / 190.8
-// and 200.5 / 192.6, W3/A3 286.1 / 282.9 and 292.6 / 297.6, 1024 units W2/A3 224.5 / 221.4 and 225.6 / 227.7, W3/A2 191.0 / 193.5 and 196.4 / 204.7.  Nine plane
-// products of a GRU with inputs of two stretches are slower with both throughout, 0.95 (0.92 to 0.99): 1500 units batch 20 278.5 / 283.2; with
-// inputs of 300 273.7 / 269.6.
+// is (slots per lane of the quantizer).  Three such reasons are one too many.  Time of the h waves alone / both, mean (range) of 16 to 70
+// kinds of call for each: 1-bit weights 1.035 to 1.043 whatever the lengths (1.00 to 1.08), 1.01 up to 256 units; 2 bits 1.035 (1.00 to
+// 1.06), up to 1024 units 1.025, with longer inputs 1.020, both 0.992 (0.95 to 1.04), up to 256 units 0.992 and 0.966; 3 bits 1.017 (0.98 to
+// 1.05), up to 1024 units 0.979, with longer inputs 0.982, both 0.949.  us per 35 steps, LSTMs batch 16, inputs of 1536 and 1600: 1200
+// units W2/A2 200.4 / 190.8 and 200.5 / 192.6, W3/A3 286.1 / 282.9 and 292.6 / 297.6, 1024 units W2/A3 224.5 / 221.4 and 225.6 / 227.7, W3/A2
+// 191.0 / 193.5 and 196.4 / 204.7.  Nine plane products of a GRU with inputs of two stretches are slower with both throughout, 0.95
+// (0.92 to 0.99): 1500 units batch 20 278.5 / 283.2; with inputs of 300 273.7 / 269.6.
 constexpr bool both_gather(int k_w, int k_a, bool gru, long long I, long long H) {
   if (gru && k_w * k_a == 9 && I > 1024) return false;
   return k_w + (I > 1536) + (H <= 1024) + (H <= 256) <= 3;
