@@ -40,13 +40,13 @@ FP4_MFMA_PEAK_TFLOPS = 10100.0               # dense fp4 matrix cores
 GEMV_TRAFFIC_BYTES = (2 * 270918.5 + 8192.2) * 1024
 # the same for the two kernels of the primary workload (profiles/lstm_step_1024_b64_w3a3.md) and for the
 # streamed batch-1 LSTM step (profiles/lstm_step_b1_streamed_1024_w3a3.md)
-LSTM_FUSED_TRAFFIC_BYTES = (2 * 2104.4 + 512.0) * 1024
-LSTM_QUANT_TRAFFIC_BYTES = (2 * 340.5 + 53.0) * 1024
+LSTM_FUSED_TRAFFIC_BYTES = (2 * 2102.9 + 512.0) * 1024
+LSTM_QUANT_TRAFFIC_BYTES = (2 * 337.0 + 53.0) * 1024
 LSTM_B1_TRAFFIC_BYTES = (2 * 271843.8 + 1368.0) * 1024
-LSTM_FRONT_TRAFFIC_BYTES = (2 * 1293.4 + 1077.0) * 1024   # step_front_kernel, steady-state form
-LSTM_BACK_TRAFFIC_BYTES = (2 * 1714.4 + 512.0) * 1024     # step_back_kernel
+LSTM_FRONT_TRAFFIC_BYTES = (2 * 1296.9 + 1077.0) * 1024   # step_front_kernel, steady-state form
+LSTM_BACK_TRAFFIC_BYTES = (2 * 1707.4 + 512.0) * 1024     # step_back_kernel
 # a whole 35-step sequence call: the resident kernel, the quantizer of its inputs, the kernels before and after it
-LSTM_SEQUENCE_TRAFFIC_BYTES = (2 * (22936.5 + 4586.0 + 13.0 + 19.1) + 20182.0 + 927.5 + 1136.1) * 1024
+LSTM_SEQUENCE_TRAFFIC_BYTES = (2 * (22827.3 + 4598.0 + 8.5 + 16.1) + 20182.0 + 927.5 + 1136.1) * 1024
 FP32_VALU_PEAK_TFLOPS = 157.3                # vector fp32
 MIN_TIMED_CALLS = 100
 MIN_WARMUP_CALLS = 10

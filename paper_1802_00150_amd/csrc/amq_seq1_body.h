@@ -15,9 +15,9 @@
 // One wave takes longer over the entries and needs no exchange between waves (about 250 cycles less per sum).
 //
 // Bound: latency -- at 300 units about 0.9 us until h_t is seen, 0.8 for Alg. 2, the rest products, cell and LDS.  Measured, us
-// per step in sequences of 35, form before -> here, W2/A2: LSTM 300 units 3.50 -> 2.47, 650 4.31 -> 2.97, 1024 5.04 -> 3.06
-// (lstm_seqg_kernel), 2048 8.69 -> 4.06; GRU 300 8.06 -> 2.66, 1024 8.09 -> 3.46, 2048 8.50 -> 4.17 (two launches per step);
-// W3/A3: LSTM 300 4.22 -> 3.29, 1024 5.79 -> 4.53, 2048 11.0 -> 5.59, GRU 9.23 -> 3.50, 9.61 -> 4.36, 10.3 -> 5.63.
+// per step in sequences of 35, forms before this kernel -> now, W2/A2: LSTM 300 units 3.50 -> 2.47, 650 4.31 -> 2.93, 1024 5.04 -> 3.08
+// (lstm_seqg_kernel), 2048 8.69 -> 3.71; GRU 300 8.06 -> 2.51, 1024 8.09 -> 3.12, 2048 8.50 -> 3.85 (two launches per step);
+// W3/A3: LSTM 300 4.22 -> 3.25, 1024 5.79 -> 3.90, 2048 11.0 -> 5.03, GRU 9.23 -> 3.27, 9.61 -> 3.92, 10.3 -> 5.18.
 //
 // The order of additions is that of the per-step kernels (amq_bmv_body.h); JOINT false: that of lstm_seqg_kernel, which
 // sums the two operand blocks of a row apart.
@@ -274,10 +274,11 @@ hipError_t run_form(const Seq1Args& a, hipStream_t s) {
 }
 
 // How many slots of 64 entries a lane of the quantizing waves holds: as many as H needs, so that no slot is computed for
-// nothing.  What the forms between are worth, us per step W2/A2 / W3/A3 with the next larger of 4, 6, 8 (one wave), 4 (four
-// waves) or 8 (two units per lane) instead: 300 units LSTM 2.58 -> 2.60 / 3.19 -> 3.35, GRU 2.54 -> 2.65 / 3.26 -> 3.47, 448 units 2.71
-// -> 2.80 / 3.44 -> 3.55, 768 3.12 -> 3.17 / 3.73 -> 3.89, 1200 3.40 -> 3.71 / 4.54 -> 5.08, 1500 3.47 -> 3.70 / 4.71 -> 5.11, 1700 3.61 ->
-// 3.73 / 4.85 -> 5.12; 500 units with inputs of 1500 3.07 -> 3.29 / 4.09 -> 4.47.  Up to 512 units a wave is on its own, beyond four share the work: at 512 units one wave takes 2.88 (W2/A2) and
+// nothing.  What the forms between were worth when they were added (no form waited before its first poll then), us per step W2/A2 /
+// W3/A3 with the next larger of 4, 6, 8 (one wave), 4 (four waves) or 8 (two units per lane) instead: 300 units LSTM 2.58 -> 2.60 / 3.19 ->
+// 3.35, GRU 2.54 -> 2.65 / 3.26 -> 3.47, 448 units 2.71 -> 2.80 / 3.44 -> 3.55, 768 3.12 -> 3.17 / 3.73 -> 3.89, 1200 3.40 -> 3.71 / 4.54 -> 5.08,
+// 1500 3.47 -> 3.70 / 4.71 -> 5.11, 1700 3.61 -> 3.73 / 4.85 -> 5.12; 500 units with inputs of 1500 3.07 -> 3.29 / 4.09 -> 4.47.  Up to 512
+// units a wave is on its own, beyond four share the work: at 512 units one wave took 2.88 (W2/A2) and
 // 3.68 us (W3/A3) per step against 2.97 and 4.24 for four, and at 640 its chain is the longer one.  Vectors above 1024
 // entries take 16 lanes per row and gate and two units per lane, so that 2048 units are 256 workgroups; there four waves
 // always share the work (fewer forms; 300 units with inputs of 1500: 2.97 against 2.81 us).

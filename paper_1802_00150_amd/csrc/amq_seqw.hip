@@ -12,9 +12,9 @@
 //   - per step two exchanges: every workgroup publishes its h_t; the workgroup in charge of a batch entry (one of
 //     those of its tile) gathers the entry's whole h_t, quantizes it (the shared quantizer core on 4 waves) and
 //     publishes its codes, which all workgroups of the tile gather as matrix operands (both kinds of wave, where the x side
-//     leaves time).  What is published goes through LDS
-//     to the x side's waves, which store it: a wave's loads are counted behind its stores, and a store takes 1500 cycles
-//     until it is acknowledged, which the polls of the h side's waves would otherwise wait for.
+//     leaves time).  What is published goes through LDS to the x side's waves, which store it: a wave's loads are counted
+//     behind its stores, and a store takes 1500 cycles until it is acknowledged, which the polls of the h side's waves would
+//     otherwise wait for.
 // What is exchanged are 8-byte {value, step tag} pairs, each written with one device-scope store; the readers poll
 // the pairs they need until all carry the tag of the step (one way across the chip: about 0.55 us measured), so the
 // data is its own arrival signal: no barrier, no ordering between locations.  Two buffers in turn suffice: whoever

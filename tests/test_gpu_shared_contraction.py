@@ -1,7 +1,7 @@
 """GPU: resident sequences whose vectors are longer than 1024 entries, where two waves share the contraction of a row block
-(amq_seqw.hip), against per-step calls, bit for bit: the partial sums are integers that binary16 holds, so nothing may be lost.  And
-either side of the line between codes gathered by one and by both of the two waves (inputs of 1536 entries; longer ones not longer
-than the state, with 1- and 2-bit weights)."""
+(amq_seqw.hip), against per-step calls, bit for bit: the partial sums are integers of at most 1024, which binary32 holds, so nothing may
+be lost.  And inputs on either side of 1536 entries, where the gather of the codes by one or by both of the two waves changes with the
+weights' bits and the state's length."""
 import pytest
 
 pytestmark = pytest.mark.gpu
